@@ -1246,9 +1246,11 @@ __global__ __launch_bounds__(256) void mix_alpha_update_kernel(const float* __re
   if (threadIdx.x < 8) g[threadIdx.x] = red[0][threadIdx.x];
   __syncthreads();
   if ((int)threadIdx.x < n) {
-    double mean = 0.0;
-    for (int q = 0; q < n; ++q) mean += (double)state[kMixP + q] * g[q];
-    const float grad = (float)((double)state[kMixP + threadIdx.x] * (g[threadIdx.x] - mean));
+    // the g_q nearly agree, and the stored p sum to one only to float32 rounding: without the division their
+    // common part would stay in the difference (times that rounding, 1e-4 of the gradient where they agree to 1e-3)
+    double mean = 0.0, sum_p = 0.0;
+    for (int q = 0; q < n; ++q) { mean += (double)state[kMixP + q] * g[q]; sum_p += (double)state[kMixP + q]; }
+    const float grad = (float)((double)state[kMixP + threadIdx.x] * (g[threadIdx.x] - mean / sum_p));
     state[kMixGrad + threadIdx.x] = grad;
     float a = state[kMixAlpha + threadIdx.x];
     if (update) {
