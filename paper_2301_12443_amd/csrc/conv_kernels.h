@@ -14,8 +14,8 @@
 //    consecutive pixels of one channel.  The pixel range is split over workgroups;
 //    partial tiles go to scratch and are summed by an ordered second stage, so the
 //    result does not depend on scheduling.
-//  * direct kernels: plain one-thread-per-output loops in fp32, used for the
-//    float32 precision and as a cross-check of the MFMA kernels.
+//  * direct kernels: plain one-thread-per-output loops in fp32, the cross-check of the
+//    MFMA kernels (pbd_opts.force_direct).
 #pragma once
 #include <type_traits>
 
