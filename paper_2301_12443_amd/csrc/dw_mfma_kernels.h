@@ -1,0 +1,367 @@
+// Depthwise convolutions (bf16, stride 1, 3 x 3 / 5 x 5 / 7 x 7) on the matrix cores.
+//
+// v_mfma_f32_4x4x4_16b_bf16 multiplies sixteen independent 4 x 4 matrices in 8 cycles: one per channel.  A row of a
+// depthwise filter applied to a run of pixels is a product with a banded (Toeplitz) matrix,
+//   out[n] = sum_k T[n][k] x[k],  T[n][k] = w[k - n],   n = 0..3 output columns,  k = 0..3 of a quad of input columns,
+// so four output columns meet K + 3 input columns in NT = ceil((K + 3) / 4) products per filter row: 28 of 48
+// multiply-adds are real at K = 7, 20 of 32 at K = 5, 12 of 32 at K = 3, at 128 multiply-adds a cycle and SIMD against
+// 16 of the vector ALUs.  Products of bf16 numbers are exact in float32 and sums are kept there, as in the kernels on the
+// vector ALUs.  (A tap outside the filter is a product with zero: an infinity or NaN among the inputs can reach
+// outputs up to three columns further than the filter does.  Inputs of these layers are outputs of a rectifier or of a
+// normalisation over the batch, where it would have spread to the whole channel.)
+//
+// Layout.  An operand lane holds four consecutive pixels of ONE channel, so tiles lie in LDS channel by channel,
+// [channel][row][column]; the 4 pixels x 8 channels that a thread loads (four 16-byte chunks) are transposed in
+// registers on their way there (16 byte permutes per 32 elements).  Pitches (bytes): CHP = 8 odd, ROWP so that
+// the 16 lanes of an LDS cycle (4 channels x 4 row strips) hit 16 different 8-byte banks.
+// A workgroup of four waves owns 16 x 16 outputs x 32 channels: wave = (16 channels) x (8 of 16 columns).  Lane
+// 4 c + j of the data operand is channel c and row strip j (output rows 4 j .. 4 j + 3), so one 8-byte LDS read of input row
+// 4 j + y serves every (output row, filter row) pair with the sum y: 40 reads for 168 products at K = 7.
+#pragma once
+#include "conv_kernels.h"
+
+namespace pbd {
+
+constexpr int kDwTile = 16;           // output rows and columns of a tile
+constexpr int kDwCh = 32;             // channels of a workgroup
+
+typedef short dw_s16x4 __attribute__((ext_vector_type(4)));
+typedef float dw_f32x4 __attribute__((ext_vector_type(4)));
+
+template <int K> struct DwGeom {
+  static constexpr int IN = kDwTile + K - 1;            // input rows and columns behind a tile
+  static constexpr int NQ = (IN + 3) / 4;               // quads of input columns
+  static constexpr int NT = (K + 6) / 4;                // quads that four output columns meet
+  static constexpr int ROWP = K == 7 ? 56 : 40;         // bytes per row of a channel: 4 ROWP = 32 odd (mod 128)
+  static constexpr int CHP = (IN * ROWP + 31) / 32 * 32 + 8;   // bytes per channel: 8 (mod 32)
+  static constexpr int ITEMS = IN * NQ * (kDwCh / 8);   // 4 pixels x 8 channels each
+  static constexpr int NLOAD = (ITEMS + 255) / 256;
+  static constexpr int WROW = K == 3 ? 8 : 16;          // bytes of a filter row in LDS
+};
+constexpr int kDwOutP = kDwCh * 2 + 16;                 // staged output: bytes per pixel ...
+constexpr int kDwOutRow = kDwTile * kDwOutP + 16;       // ... and per row of 16
+
+__device__ __forceinline__ unsigned dw_lo2(unsigned a, unsigned b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }  // low halves
+__device__ __forceinline__ unsigned dw_hi2(unsigned a, unsigned b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }  // high halves
+// A lane's shift by n = 0..3 elements over a run of element pairs: whole pairs by a bit-wise select on all-ones or
+// all-zeros (n >= 2), the odd element by a byte permute with the lane's own selector.  (Written as conditional expressions
+// on the run's elements the compiler keeps the run in scratch memory and indexes it.)
+__device__ __forceinline__ unsigned dw_sel(unsigned mask, unsigned set, unsigned clear) { return (set & mask) | (clear & ~mask); }
+constexpr unsigned kDwSelLow = 0x03020100u, kDwSelMid = 0x05040302u, kDwSelHigh = 0x07060504u;   // lo | lo.hi, hi.lo | hi
+
+// the four 16-byte chunks (8 channels) of four neighbouring pixels -> eight channels of four pixels, CH_PITCH bytes apart
+template <int CH_PITCH>
+__device__ __forceinline__ void dw_store_transposed(unsigned char* dst, const uint4 (&p)[4]) {
+  const unsigned a[4][4] = {{p[0].x, p[0].y, p[0].z, p[0].w}, {p[1].x, p[1].y, p[1].z, p[1].w},
+                            {p[2].x, p[2].y, p[2].z, p[2].w}, {p[3].x, p[3].y, p[3].z, p[3].w}};
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    *reinterpret_cast<uint2*>(dst + (2 * m) * CH_PITCH) = make_uint2(dw_lo2(a[0][m], a[1][m]), dw_lo2(a[2][m], a[3][m]));
+    *reinterpret_cast<uint2*>(dst + (2 * m + 1) * CH_PITCH) = make_uint2(dw_hi2(a[0][m], a[1][m]), dw_hi2(a[2][m], a[3][m]));
+  }
+}
+
+// Work items: (tile, channel group), group fastest (neighbouring groups share the 128-byte lines of a pixel), a
+// workgroup takes `per_block` tiles of one group one after the other (its filters stay in registers).
+struct DwArgs {
+  int N, H, W, ncv;             // images, height, width, 8-channel vectors
+  int tiles_h, tiles_w, tiles;  // tiles = N * tiles_h * tiles_w
+  int groups, per_block;        // channel groups, tiles per workgroup
+  unsigned bytes;               // of the input tensor (and of the output: the shapes agree)
+  int stream;                   // nontemporal stores
+};
+
+// y = x * w (FLIP: mirrored filter, the backward-data pass of the same layer), optionally a folded batch norm and
+// activation behind it.
+// Bound by memory at K = 3, by LDS traffic and latency at K = 7; measured figures at the dispatch rule (dw_mfma()).
+template <int K, bool FLIP>
+__global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
+                                                         bf16_t* __restrict__ dst, const float* __restrict__ a,
+                                                         const float* __restrict__ b, int act, DwArgs g) {
+  typedef DwGeom<K> G;
+  constexpr int NT = G::NT, pad = K / 2;
+  constexpr int LDS = G::CHP * kDwCh > kDwOutRow * kDwTile ? G::CHP * kDwCh : kDwOutRow * kDwTile;
+  static_assert(kDwCh * K * G::WROW <= LDS, "the filters fit where the tile goes");
+  __shared__ __attribute__((aligned(16))) unsigned char smem[LDS];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int slice = wave & 1, half = wave >> 1;
+  const int wg = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int cv0 = (wg % g.groups) * (kDwCh / 8);
+  const int tile_begin = (wg / g.groups) * g.per_block, tile_end = min(g.tiles, tile_begin + g.per_block);
+  const __amdgpu_buffer_rsrc_t xr = tensor_rsrc(x, g.bytes);
+  const int ch = slice * 16 + (lane >> 2), strip = lane & 3;         // (strip: also this lane's output column of the filter operand)
+
+  // ---- filters: [channel][filter row][tap] in LDS, then each lane's Toeplitz rows into registers ----
+  for (int i = tid; i < K * K * (kDwCh / 2); i += 256) {
+    const int tap = i / (kDwCh / 2), c2 = i % (kDwCh / 2);
+    const int t = FLIP ? K * K - 1 - tap : tap;
+    unsigned v = 0;
+    if (cv0 * 8 + 2 * c2 < g.ncv * 8) v = *reinterpret_cast<const unsigned*>(w + (size_t)tap * g.ncv * 8 + cv0 * 8 + 2 * c2);
+    unsigned short* p = reinterpret_cast<unsigned short*>(smem + (2 * c2 * K + t / K) * G::WROW) + t % K;
+    p[0] = (unsigned short)v;
+    p[K * G::WROW / 2] = (unsigned short)(v >> 16);
+  }
+  __syncthreads();
+  const unsigned far = strip >= 2 ? ~0u : 0u, odd = strip & 1 ? kDwSelMid : kDwSelHigh;
+  dw_s16x4 wt[K][NT];
+#pragma unroll
+  for (int r = 0; r < K; ++r) {
+    // element pairs P[-2 .. 2 NT - 1] of the filter row with zeros around it
+    unsigned P[2 * NT + 2];
+#pragma unroll
+    for (int i = 0; i < 2 * NT + 2; ++i) P[i] = 0u;
+    const unsigned char* row = smem + (ch * K + r) * G::WROW;
+    const uint2 q0 = *reinterpret_cast<const uint2*>(row);
+    P[2] = q0.x; P[3] = K == 3 ? q0.y & 0xffffu : q0.y;              // (the last tap's partner was never written)
+    if (K > 3) {
+      const uint2 q1 = *reinterpret_cast<const uint2*>(row + 8);
+      P[4] = K == 5 ? q1.x & 0xffffu : q1.x;
+      if (K > 5) P[5] = q1.y & 0xffffu;
+    }
+    // T[n][k] of quad t = tap 4 t + k - n, n = this lane's column: two pairs further back for n >= 2, half a pair for odd n
+    unsigned E[2 * NT + 1];
+#pragma unroll
+    for (int i = 0; i < 2 * NT + 1; ++i) E[i] = dw_sel(far, P[i], P[i + 1]);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const unsigned d0 = __builtin_amdgcn_perm(E[2 * t + 1], E[2 * t], odd);
+      const unsigned d1 = __builtin_amdgcn_perm(E[2 * t + 2], E[2 * t + 1], odd);
+      wt[r][t] = __builtin_bit_cast(dw_s16x4, make_uint2(d0, d1));
+    }
+  }
+  float ea = 1.f, eb = 0.f;
+  if (a && cv0 * 8 + ch < g.ncv * 8) { ea = a[cv0 * 8 + ch]; eb = b[cv0 * 8 + ch]; }
+
+  for (int tile = tile_begin; tile < tile_end; ++tile) {
+    int t_ = tile;
+    const int tw = t_ % g.tiles_w; t_ /= g.tiles_w;
+    const int th = t_ % g.tiles_h, n = t_ / g.tiles_h;
+    const int h0 = th * kDwTile, w0 = tw * kDwTile;
+    // ---- the tile's input, all loads in flight together ----
+    uint4 raw[G::NLOAD][4];
+#pragma unroll
+    for (int i = 0; i < G::NLOAD; ++i) {
+      const int c = tid + i * 256;
+      const int cvl = c % (kDwCh / 8), quad = (c / (kDwCh / 8)) % G::NQ, row = c / (kDwCh / 8) / G::NQ;
+      const int h = h0 - pad + row, w_ = w0 - pad + 4 * quad;
+      const bool rok = c < G::ITEMS && (unsigned)h < (unsigned)g.H && cv0 + cvl < g.ncv;
+      const unsigned off = (unsigned)(((n * g.H + h) * g.W + w_) * g.ncv + cv0 + cvl) * 16u;
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+        raw[i][p] = buffer_load16(xr, rok && 4 * quad + p < G::IN && (unsigned)(w_ + p) < (unsigned)g.W ? off + (unsigned)(p * g.ncv) * 16u : kOutOfRange);
+    }
+    __syncthreads();                                     // the previous tile (or the filters) has been read
+#pragma unroll
+    for (int i = 0; i < G::NLOAD; ++i) {
+      const int c = tid + i * 256;
+      const int cvl = c % (kDwCh / 8), quad = (c / (kDwCh / 8)) % G::NQ, row = c / (kDwCh / 8) / G::NQ;
+      if (c < G::ITEMS) dw_store_transposed<G::CHP>(smem + cvl * 8 * G::CHP + row * G::ROWP + quad * 8, raw[i]);
+    }
+    __syncthreads();
+
+    // ---- products: acc[rho][q] = output rows 4 strip + rho, output columns 8 half + 4 q + 0..3 ----
+    dw_f32x4 acc[4][2];
+#pragma unroll
+    for (int o = 0; o < 4; ++o)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) acc[o][q] = dw_f32x4{0.f, 0.f, 0.f, 0.f};
+    const unsigned char* in = smem + ch * G::CHP + 4 * strip * G::ROWP + half * 16;
+#pragma unroll
+    for (int c = 0; c < NT + 1; ++c)
+#pragma unroll
+      for (int y = 0; y < K + 3; ++y) {
+        const dw_s16x4 d = *reinterpret_cast<const dw_s16x4*>(in + y * G::ROWP + c * 8);
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+          const int r = y - o;
+          if (r < 0 || r >= K) continue;
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const int t = c - q;
+            if (t < 0 || t >= NT) continue;
+            acc[o][q] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(wt[r][t], d, acc[o][q], 0, 0, 0);
+          }
+        }
+      }
+
+    // ---- output through LDS: pixel-major, then 16-byte stores ----
+    if (a) {                                             // folded inference-mode BN + activation (teacher)
+#pragma unroll
+      for (int o = 0; o < 4; ++o)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int m = 0; m < 4; ++m) acc[o][q][m] = apply_act(fmaf(acc[o][q][m], ea, eb), act);
+    }
+    __syncthreads();                                     // every wave has read the input tile
+    // lanes 4 apart hold neighbouring channels: the even channel packs columns 0 and 1 of both, the odd one columns 2 and 3
+    unsigned char* so = smem + (ch >> 1) * 4 + ((ch & 1) * 2 + half * 8) * kDwOutP;
+#pragma unroll
+    for (int o = 0; o < 4; ++o)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          const int v0 = __float_as_int(acc[o][q][m]), v2 = __float_as_int(acc[o][q][m + 2]);
+          const int lo = __builtin_amdgcn_update_dpp(v0, v2, 0x114, 0xf, 0xa, false);   // row_shr:4 into the odd channels
+          const int hi = __builtin_amdgcn_update_dpp(v2, v0, 0x104, 0xf, 0x5, false);   // row_shl:4 into the even channels
+          *reinterpret_cast<unsigned*>(so + (4 * strip + o) * kDwOutRow + (q * 4 + m) * kDwOutP) = pack_bf2(__int_as_float(lo), __int_as_float(hi));
+        }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kDwTile * kDwTile * (kDwCh / 8) / 256; ++i) {
+      const int c = tid + i * 256;
+      const int cvl = c % (kDwCh / 8), col = (c / (kDwCh / 8)) % kDwTile, row = c / (kDwCh / 8) / kDwTile;
+      const int h = h0 + row, w_ = w0 + col;
+      if (h >= g.H || w_ >= g.W || cv0 + cvl >= g.ncv) continue;
+      const uint4 v = *reinterpret_cast<const uint4*>(smem + row * kDwOutRow + col * kDwOutP + cvl * 16);
+      bf16_t* out = dst + ((((size_t)n * g.H + h) * g.W + w_) * g.ncv + cv0 + cvl) * 8;
+      if (g.stream) {
+        const u32x4 q = {v.x, v.y, v.z, v.w};
+        __builtin_nontemporal_store(q, reinterpret_cast<u32x4*>(out));
+      } else {
+        *reinterpret_cast<uint4*>(out) = v;
+      }
+    }
+  }
+}
+
+// Backward-weight of the same layers: dW[r][s] = sum over pixels of x[p + r][q + s] dy[p][q], per channel.
+// A product takes four neighbouring columns of one input row: A[i][k] = x[y][4 c + i + k] (s = i + 4 it: the four lanes of a
+// channel read the same quads and shift them by their own i), B[k][j] = dy[y - j - 4 jt][4 c + k] (r = j + 4 jt), so
+// D[i][j] accumulates filter tap (r, s): 49 of 64 multiply-adds are real at K = 7, 25 of 64 at K = 5, 9 of 16 at K = 3, and
+// x and dy are read once for all taps.  A shifted quad of x meets dy's quads c (it = 0) and c - 1 (it = 1).  Rows of dy
+// outside the tile are a row of zeros.  A workgroup walks per_block tiles with its accumulators in registers; the two
+// column halves meet in LDS at the end; one partial result per workgroup as in the other kernels.
+template <int K>
+__global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
+                                                               float* __restrict__ part, DwArgs g) {
+  typedef DwGeom<K> G;
+  constexpr int pad = K / 2, NIT = K == 3 ? 1 : 2;
+  constexpr int ROWX = G::NQ * 8, CHX = (G::IN * ROWX + 31) / 32 * 32 + 8;          // x: rows of whole quads
+  constexpr int ROWD = kDwTile * 2, CHD = kDwTile * ROWD + 8;                        // dy: 16 x 16 pixels a channel
+  constexpr int ZERO = CHX * kDwCh + CHD * kDwCh;                                    // a row of zeros
+  __shared__ __attribute__((aligned(16))) unsigned char smem[ZERO + ROWD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int slice = wave & 1, half = wave >> 1;
+  const int wg = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int cv0 = (wg % g.groups) * (kDwCh / 8), chunk = wg / g.groups;
+  const int tile_begin = chunk * g.per_block, tile_end = min(g.tiles, tile_begin + g.per_block);
+  const __amdgpu_buffer_rsrc_t xr = tensor_rsrc(x, g.bytes), dr = tensor_rsrc(dy, g.bytes);
+  const int ch = slice * 16 + (lane >> 2), n4 = lane & 3;             // n4: s offset of the x operand, r offset of the dy operand
+  const unsigned far = n4 >= 2 ? ~0u : 0u, odd = n4 & 1 ? kDwSelMid : kDwSelLow;
+  if (tid < ROWD / 8) *reinterpret_cast<uint2*>(smem + ZERO + tid * 8) = make_uint2(0u, 0u);
+
+  dw_f32x4 acc[NIT][NIT];
+#pragma unroll
+  for (int i = 0; i < NIT; ++i)
+#pragma unroll
+    for (int j = 0; j < NIT; ++j) acc[i][j] = dw_f32x4{0.f, 0.f, 0.f, 0.f};
+
+  uint4 rx[G::NLOAD][4], rd[4];
+  auto load_tile = [&](int tile) {
+    int t_ = tile;
+    const int tw = t_ % g.tiles_w; t_ /= g.tiles_w;
+    const int th = t_ % g.tiles_h, n = t_ / g.tiles_h;
+    const int h0 = th * kDwTile, w0 = tw * kDwTile;
+#pragma unroll
+    for (int i = 0; i < G::NLOAD; ++i) {
+      const int c = tid + i * 256;
+      const int cvl = c % (kDwCh / 8), quad = (c / (kDwCh / 8)) % G::NQ, row = c / (kDwCh / 8) / G::NQ;
+      const int h = h0 - pad + row, w_ = w0 - pad + 4 * quad;
+      const bool rok = c < G::ITEMS && (unsigned)h < (unsigned)g.H && cv0 + cvl < g.ncv;
+      const unsigned off = (unsigned)(((n * g.H + h) * g.W + w_) * g.ncv + cv0 + cvl) * 16u;
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+        rx[i][p] = buffer_load16(xr, rok && 4 * quad + p < G::IN && (unsigned)(w_ + p) < (unsigned)g.W ? off + (unsigned)(p * g.ncv) * 16u : kOutOfRange);
+    }
+    const int cvl = tid % (kDwCh / 8), quad = (tid / (kDwCh / 8)) % 4, drow = tid / (kDwCh / 8) / 4;
+    const int h = h0 + drow, w_ = w0 + 4 * quad;
+    const unsigned off = (unsigned)(((n * g.H + h) * g.W + w_) * g.ncv + cv0 + cvl) * 16u;
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+      rd[p] = buffer_load16(dr, h < g.H && w_ + p < g.W && cv0 + cvl < g.ncv ? off + (unsigned)(p * g.ncv) * 16u : kOutOfRange);
+  };
+
+  if (tile_begin < tile_end) load_tile(tile_begin);
+  for (int tile = tile_begin; tile < tile_end; ++tile) {
+    __syncthreads();                                     // the previous tile has been read
+#pragma unroll
+    for (int i = 0; i < G::NLOAD; ++i) {
+      const int c = tid + i * 256;
+      const int cvl = c % (kDwCh / 8), quad = (c / (kDwCh / 8)) % G::NQ, row = c / (kDwCh / 8) / G::NQ;
+      if (c < G::ITEMS) dw_store_transposed<CHX>(smem + cvl * 8 * CHX + row * ROWX + quad * 8, rx[i]);
+    }
+    dw_store_transposed<CHD>(smem + CHX * kDwCh + (tid % (kDwCh / 8)) * 8 * CHD + (tid / (kDwCh / 8) / 4) * ROWD + ((tid / (kDwCh / 8)) % 4) * 8, rd);
+    __syncthreads();
+    if (tile + 1 < tile_end) load_tile(tile + 1);        // in flight behind this tile's products
+
+    const unsigned char* xp = smem + ch * CHX + half * 16;
+    const unsigned char* dp = smem + CHX * kDwCh + ch * CHD + half * 16;
+    const unsigned char* zp = smem + ZERO + half * 16;
+#pragma unroll 2
+    for (int y = 0; y < G::IN; ++y) {
+      const unsigned char* db[NIT];
+#pragma unroll
+      for (int jt = 0; jt < NIT; ++jt) {
+        const int row = y - n4 - 4 * jt;
+        db[jt] = (unsigned)row < (unsigned)kDwTile ? dp + row * ROWD : zp;
+      }
+      dw_s16x4 d[NIT][2];
+#pragma unroll
+      for (int jt = 0; jt < NIT; ++jt)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) d[jt][q] = *reinterpret_cast<const dw_s16x4*>(db[jt] + q * 8);
+      // the shifted quads of the input row: c = 0 .. NIT of this half (two quads of dy each)
+      uint2 xq[NIT + 2];
+#pragma unroll
+      for (int c = 0; c < NIT + 2; ++c) xq[c] = *reinterpret_cast<const uint2*>(xp + y * ROWX + c * 8);
+      unsigned D[2 * (NIT + 2)];
+#pragma unroll
+      for (int c = 0; c < NIT + 2; ++c) { D[2 * c] = xq[c].x; D[2 * c + 1] = xq[c].y; }
+      unsigned E[2 * (NIT + 1) + 1];
+#pragma unroll
+      for (int i = 0; i < 2 * (NIT + 1) + 1; ++i) E[i] = dw_sel(far, D[i + 1], D[i]);
+#pragma unroll
+      for (int c = 0; c < NIT + 1; ++c) {
+        const unsigned s0 = __builtin_amdgcn_perm(E[2 * c + 1], E[2 * c], odd);
+        const unsigned s1 = __builtin_amdgcn_perm(E[2 * c + 2], E[2 * c + 1], odd);
+        const dw_s16x4 xs = __builtin_bit_cast(dw_s16x4, make_uint2(s0, s1));
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+          const int q = c - it;
+          if (q < 0 || q > 1) continue;
+#pragma unroll
+          for (int jt = 0; jt < NIT; ++jt)
+            acc[it][jt] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(xs, d[jt][q], acc[it][jt], 0, 0, 0);
+        }
+      }
+    }
+  }
+  // ---- the two column halves of a slice meet in LDS; lane 4 c + j holds taps (r = 4 jt + j, s = 4 it + v) of channel c ----
+  __syncthreads();
+  float* red = reinterpret_cast<float*>(smem);
+  if (half) {
+#pragma unroll
+    for (int it = 0; it < NIT; ++it)
+#pragma unroll
+      for (int jt = 0; jt < NIT; ++jt)
+        *reinterpret_cast<dw_f32x4*>(red + ((slice * NIT * NIT + it * NIT + jt) * 64 + lane) * 4) = acc[it][jt];
+  }
+  __syncthreads();
+  if (half || cv0 * 8 + ch >= g.ncv * 8) return;
+#pragma unroll
+  for (int it = 0; it < NIT; ++it)
+#pragma unroll
+    for (int jt = 0; jt < NIT; ++jt) {
+      const dw_f32x4 o = *reinterpret_cast<const dw_f32x4*>(red + ((slice * NIT * NIT + it * NIT + jt) * 64 + lane) * 4);
+      const int r = 4 * jt + n4;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int s = 4 * it + v;
+        if (r < K && s < K) part[((size_t)chunk * K * K + r * K + s) * (g.ncv * 8) + cv0 * 8 + ch] = acc[it][jt][v] + o[v];
+      }
+    }
+}
+
+}  // namespace pbd

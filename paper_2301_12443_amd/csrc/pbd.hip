@@ -23,6 +23,7 @@
 #include "conv_kernels.h"
 #include "conv_dma_kernels.h"
 #include "conv_f32_kernels.h"
+#include "dw_mfma_kernels.h"
 #include "ew_kernels.h"
 
 using namespace pbd;
@@ -256,26 +257,34 @@ ColGrid col_grid(long M, int Cp, int rows_per_thread = 8, int max_blocks = 512) 
 inline ColGrid bn_stats_grid(long M, int Cp) { return col_grid(M, Cp, 8, 1024); }
 inline ColGrid bn_bwd_grid(long M, int Cp) { return col_grid(M, Cp, 8, 1024); }
 
-// Partial results of a depthwise backward-weight: row chunks of the column-grid kernel, or blocks of
-// tiles of the LDS-tiled kernel (bf16, stride 1, odd k <= 7, image at least 8 x 12).
-inline bool dw_tiled(bool bf16, int k, int stride, int pad, int h_out, int w_out) {
+// Depthwise layers on the matrix cores (bf16, stride 1, odd k <= 7, image at least 8 x 12): tiles and channel groups of
+// one launch, and how many tiles a workgroup takes so that about `blocks` workgroups result.
+inline bool dw_on_mfma(bool bf16, int k, int stride, int pad, int h_out, int w_out) {
   return bf16 && (k == 3 || k == 5 || k == 7) && pad == k / 2 && stride == 1 && h_out >= 8 && w_out >= 12;
 }
-struct DwWgradCfg { bool tiled; int chunks, tiles_h, tiles_w, ntiles, tiles_per_block; ColGrid g; };
+inline DwArgs dw_args(int N, int h, int w, int Cp, int blocks) {
+  DwArgs g{};
+  g.N = N; g.H = h; g.W = w; g.ncv = Cp / 8;
+  g.tiles_h = (h + kDwTile - 1) / kDwTile;
+  g.tiles_w = (w + kDwTile - 1) / kDwTile;
+  g.tiles = N * g.tiles_h * g.tiles_w;
+  g.groups = (Cp + kDwCh - 1) / kDwCh;
+  g.per_block = (int)std::max(1L, ((long)g.tiles * g.groups + blocks - 1) / blocks);
+  g.bytes = (unsigned)((size_t)N * h * w * Cp * 2);
+  return g;
+}
+inline int dw_chunks(const DwArgs& g) { return (g.tiles + g.per_block - 1) / g.per_block; }
+
+// Partial results of a depthwise backward-weight: row chunks of the column-grid kernel, or workgroups of
+// dw_wgrad_mfma_kernel (three resident workgroups per compute unit; it also wins on 8-wide images, unlike the forward kernel).
+struct DwWgradCfg { bool mfma; int chunks; DwArgs m; ColGrid g; };
 inline DwWgradCfg dw_wgrad_cfg(bool bf16, int N, int h_out, int w_out, int Cp, int k, int stride, int pad) {
   DwWgradCfg w{};
   const long M = (long)N * h_out * w_out;
-  // the tile kernel also wins on 8-wide images (half of each 8 x 16 tile empty: 11 us against 21 us for
-  // 256 x 8 x 8 x 256), unlike the forward and backward-data tile kernels
-  w.tiled = dw_tiled(bf16, k, stride, pad, h_out, std::max(w_out, w_out >= 8 ? 12 : 0));
-  if (w.tiled) {
-    w.tiles_h = (h_out + 7) / 8;
-    w.tiles_w = (w_out + 15) / 16;
-    w.ntiles = N * w.tiles_h * w.tiles_w;
-    const int cvblocks = (Cp / 8 + 7) / 8;
-    const int want = std::max(1, std::min(w.ntiles, 1024 / cvblocks));
-    w.tiles_per_block = (w.ntiles + want - 1) / want;
-    w.chunks = (w.ntiles + w.tiles_per_block - 1) / w.tiles_per_block;
+  w.mfma = dw_on_mfma(bf16, k, stride, pad, h_out, std::max(w_out, w_out >= 8 ? 12 : 0));
+  if (w.mfma) {
+    w.m = dw_args(N, h_out, w_out, Cp, 768);
+    w.chunks = dw_chunks(w.m);
   } else {
     w.g = col_grid(M, Cp, 16, k <= 3 ? 512 : 768 / k);
     w.chunks = w.g.chunks;
@@ -1013,30 +1022,27 @@ template <class T> struct Exec {
   // ---- depthwise ----------------------------------------------------------
   // sliding-window depthwise kernels: odd k in {3,5,7} with "same" padding, 4 outputs per thread
   static constexpr int kDwSlide = 4;
+  static constexpr int kDwFwdBlocks = 2048;      // two rounds of the four workgroups that a compute unit holds
   static bool dw_slides(const OpPlan& op) {
     return (op.d.k == 3 || op.d.k == 5 || op.d.k == 7) && op.d.pad == op.d.k / 2 && (op.d.stride == 1 || op.d.stride == 2);
   }
-  // LDS-tiled kernels: bf16, stride 1, images of at least one tile row and most of a tile's width
-  static bool dw_tiles(const OpPlan& op) {
-    return dw_tiled(sizeof(T) == 2, op.d.k, op.d.stride, op.d.pad, op.out.h, op.out.w);
-  }
+  bool dw_mfma(const OpPlan& op) const { return dw_on_mfma(mfma(), op.d.k, op.d.stride, op.d.pad, op.out.h, op.out.w); }
   void dw_fwd(const OpPlan& op, const T* x, const T* w, T* y, const float* a, const float* b, int act) {
     const int N = c->o.batch, ncv = op.cout_p / 8;
     const long nvec = (long)N * op.out.h * op.out.w * ncv;
-    // one profile class per kernel template: tile (LDS), slide (registers), plain
+    // one profile class per kernel template: mfma (matrix cores), slide (registers), plain
     char cls[32];
-    snprintf(cls, sizeof cls, "dw_fwd%s_k%d", dw_tiles(op) ? "_tile" : dw_slides(op) ? (op.d.stride == 1 ? "_slide" : "_slide_s2") : "", op.d.k);
+    snprintf(cls, sizeof cls, "dw_fwd%s_k%d", dw_mfma(op) ? "_mfma" : dw_slides(op) ? (op.d.stride == 1 ? "_slide" : "_slide_s2") : "", op.d.k);
     ProfScope ps(c, cls, bytes_of(op.in) + bytes_of(op.out), 2.0 * N * op.out.h * op.out.w * op.d.c_out * op.d.k * op.d.k,
                  net, blk, opi);
     const unsigned xe = (unsigned)((size_t)N * op.in.h * op.in.w * op.cin_p);
-    if (dw_tiles(op)) {
+    if (dw_mfma(op)) {
       if constexpr (sizeof(T) == 2) {
-        const int th = (op.out.h + kDwTileH - 1) / kDwTileH, tw = (op.out.w + kDwTileW - 1) / kDwTileW;
-        const dim3 grid(N * th * tw, (ncv + kDwTileCv - 1) / kDwTileCv);
-#define PBD_DWT(K_) launch(c, dw_tile_kernel<K_, false>, grid, 256, 0, st, (const bf16_t*)x, (const bf16_t*)w, (bf16_t*)y, a, b, act, 0, \
-    N, op.in.h, op.in.w, ncv, th, tw, xe * 2u, streams(op.out) ? 1 : 0)
-        if (op.d.k == 3) PBD_DWT(3); else if (op.d.k == 5) PBD_DWT(5); else PBD_DWT(7);
-#undef PBD_DWT
+        DwArgs g = dw_args(N, op.out.h, op.out.w, op.cout_p, kDwFwdBlocks);
+        g.stream = streams(op.out) ? 1 : 0;
+#define PBD_DWM(K_) launch(c, dw_mfma_kernel<K_, false>, dw_chunks(g) * g.groups, 256, 0, st, (const bf16_t*)x, (const bf16_t*)w, (bf16_t*)y, a, b, act, g)
+        if (op.d.k == 3) PBD_DWM(3); else if (op.d.k == 5) PBD_DWM(5); else PBD_DWM(7);
+#undef PBD_DWM
       }
       return;
     }
@@ -1058,22 +1064,22 @@ template <class T> struct Exec {
     const int N = c->o.batch, ncv = op.cout_p / 8;
     const long nvec = (long)N * op.in.h * op.in.w * ncv;
     char cls[32];
-    snprintf(cls, sizeof cls, "dw_dgrad%s_k%d", dw_tiles(op) ? "_tile" : dw_slides(op) ? (op.d.stride == 1 ? "_slide" : "_s2") : "", op.d.k);
+    snprintf(cls, sizeof cls, "dw_dgrad%s_k%d", dw_mfma(op) && !accumulate ? "_mfma" : dw_slides(op) ? (op.d.stride == 1 ? "_slide" : "_s2") : "", op.d.k);
     ProfScope ps(c, cls, bytes_of(op.in) + bytes_of(op.out), 2.0 * N * op.out.h * op.out.w * op.d.c_out * op.d.k * op.d.k,
                  net, blk, opi);
     const unsigned de = (unsigned)((size_t)N * op.out.h * op.out.w * op.cout_p);
-    if (dw_tiles(op)) {
+    if (dw_mfma(op) && !accumulate) {          // mirrored filter over dy
       if constexpr (sizeof(T) == 2) {
-        const int th = (op.in.h + kDwTileH - 1) / kDwTileH, tw = (op.in.w + kDwTileW - 1) / kDwTileW;
-        const dim3 grid(N * th * tw, (ncv + kDwTileCv - 1) / kDwTileCv);
-#define PBD_DWT(K_) launch(c, dw_tile_kernel<K_, true>, grid, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)w, (bf16_t*)dx, (const float*)nullptr, \
-    (const float*)nullptr, 0, accumulate ? 1 : 0, N, op.out.h, op.out.w, ncv, th, tw, de * 2u, streams(op.in) ? 1 : 0)
-        if (op.d.k == 3) PBD_DWT(3); else if (op.d.k == 5) PBD_DWT(5); else PBD_DWT(7);
-#undef PBD_DWT
+        DwArgs g = dw_args(N, op.in.h, op.in.w, op.cin_p, kDwFwdBlocks);
+        g.stream = streams(op.in) ? 1 : 0;
+#define PBD_DWM(K_) launch(c, dw_mfma_kernel<K_, true>, dw_chunks(g) * g.groups, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)w, (bf16_t*)dx, \
+    (const float*)nullptr, (const float*)nullptr, 0, g)
+        if (op.d.k == 3) PBD_DWM(3); else if (op.d.k == 5) PBD_DWM(5); else PBD_DWM(7);
+#undef PBD_DWM
       }
       return;
     }
-    if (dw_slides(op) && op.d.stride == 1) {   // mirrored filter over dy: same sliding sum
+    if (dw_slides(op) && op.d.stride == 1) {   // the same sliding sum, optionally added to what dx holds
       const long nitem = (long)N * op.in.h * ((op.in.w + kDwSlide - 1) / kDwSlide) * ncv;
 #define PBD_DWS(K_) launch(c, dw_slide_kernel<T, K_, 1, kDwSlide, true>, grid_for(nitem), 256, 0, st, dy, w, dx, (const float*)nullptr, \
     (const float*)nullptr, 0, accumulate ? 1 : 0, N, op.out.h, op.out.w, op.in.h, op.in.w, ncv, op.d.pad, de)
@@ -1098,16 +1104,12 @@ template <class T> struct Exec {
     const DwWgradCfg cfg = dw_wgrad_cfg(mfma(), N, op.out.h, op.out.w, op.cout_p, op.d.k, op.d.stride, op.d.pad);
     {
       char cls[32];
-      snprintf(cls, sizeof cls, "dw_wgrad%s_k%d", cfg.tiled ? "_tile" : "", op.d.k <= 3 ? 3 : cfg.tiled ? op.d.k : 7);
+      snprintf(cls, sizeof cls, "dw_wgrad%s_k%d", cfg.mfma ? "_mfma" : "", op.d.k <= 3 ? 3 : cfg.mfma ? op.d.k : 7);
       ProfScope ps(c, cls, bytes_of(op.in) + bytes_of(op.out),
                    2.0 * N * op.out.h * op.out.w * op.d.c_out * op.d.k * op.d.k, net, blk, opi);
-      if (cfg.tiled) {
+      if (cfg.mfma) {
         if constexpr (sizeof(T) == 2) {
-          const int ncv = op.cout_p / 8;
-          const dim3 grid(cfg.chunks, (ncv + kDwTileCv - 1) / kDwTileCv);
-          const unsigned bytes = (unsigned)((size_t)N * op.out.h * op.out.w * op.cout_p * 2);
-#define PBD_DWW(K_) launch(c, dw_wgrad_tile_kernel<K_>, grid, 64 * K_, 0, st, (const bf16_t*)dy, (const bf16_t*)x, red(), N, op.out.h, \
-    op.out.w, ncv, cfg.tiles_h, cfg.tiles_w, cfg.ntiles, cfg.tiles_per_block, bytes)
+#define PBD_DWW(K_) launch(c, dw_wgrad_mfma_kernel<K_>, cfg.chunks * cfg.m.groups, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)x, red(), cfg.m)
           if (op.d.k == 3) PBD_DWW(3); else if (op.d.k == 5) PBD_DWW(5); else PBD_DWW(7);
 #undef PBD_DWW
         }
