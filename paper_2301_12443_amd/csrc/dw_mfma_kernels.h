@@ -67,13 +67,19 @@ struct DwArgs {
   int N, H, W, ncv;             // images, height, width, 8-channel vectors
   int tiles_h, tiles_w, tiles;  // tiles = N * tiles_h * tiles_w
   int groups, per_block;        // channel groups, tiles per workgroup
-  unsigned bytes;               // of the input tensor (and of the output: the shapes agree)
+  unsigned bytes;               // of the input tensor (and of the output: the shapes agree at stride 1)
   int stream;                   // nontemporal stores
+  int P, Q;                     // stride 2: height, width and bytes of dy (tiles are counted over it)
+  unsigned dy_bytes;
 };
 
 // y = x * w (FLIP: mirrored filter, the backward-data pass of the same layer), optionally a folded batch norm and
 // activation behind it.
-// Bound by memory at K = 3, by LDS traffic and latency at K = 7; measured figures at the dispatch rule (dw_mfma()).
+// Bound by the latency of load - stage - multiply - stage - store at three to four workgroups per compute unit (no unit is
+// busy all the time).  Launch averages over the supernet step (batch 64, 96 MB in and out each) against a tile kernel on
+// the vector ALUs: 7 x 7 72 -> 37 us, 5 x 5 40 -> 30, 3 x 3 24.4 -> 24.7 (and MobileNetV2's at batch 33: 11.6 -> 8.3).
+// Slower: the next tile's loads in flight behind the products (K = 7 40 us, K = 5 31: the registers cost a workgroup per
+// compute unit); 64 channels a workgroup (K = 5 31 us, batch 33 12.6 against 11.4).
 template <int K, bool FLIP>
 __global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
                                                          bf16_t* __restrict__ dst, const float* __restrict__ a,
@@ -232,12 +238,14 @@ __global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16
 // D[i][j] accumulates filter tap (r, s): 49 of 64 multiply-adds are real at K = 7, 25 of 64 at K = 5, 9 of 16 at K = 3, and
 // x and dy are read once for all taps.  A shifted quad of x meets dy's quads c (it = 0) and c - 1 (it = 1).  Rows of dy
 // outside the tile are a row of zeros.  A workgroup walks per_block tiles with its accumulators in registers; the two
-// column halves meet in LDS at the end; one partial result per workgroup as in the other kernels.
+// column halves meet in LDS at the end; one partial result per workgroup as in the other kernels.  Bound by the shifts and
+// LDS reads.  Launch averages over the supernet step against a tile kernel on the vector ALUs: 7 x 7 90 -> 39 us, 5 x 5
+// 72 -> 35, 3 x 3 37 -> 26.
 template <int K>
 __global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
                                                                float* __restrict__ part, DwArgs g) {
   typedef DwGeom<K> G;
-  constexpr int pad = K / 2, NIT = K == 3 ? 1 : 2;
+  constexpr int pad = K / 2, NIT = K == 3 ? 1 : 2, QS = K == 7 ? 1 : 2;    // (QS: accumulators per tap block, one per quad column where registers allow)
   constexpr int ROWX = G::NQ * 8, CHX = (G::IN * ROWX + 31) / 32 * 32 + 8;          // x: rows of whole quads
   constexpr int ROWD = kDwTile * 2, CHD = kDwTile * ROWD + 8;                        // dy: 16 x 16 pixels a channel
   constexpr int ZERO = CHX * kDwCh + CHD * kDwCh;                                    // a row of zeros
@@ -252,11 +260,11 @@ __global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __r
   const unsigned far = n4 >= 2 ? ~0u : 0u, odd = n4 & 1 ? kDwSelMid : kDwSelLow;
   if (tid < ROWD / 8) *reinterpret_cast<uint2*>(smem + ZERO + tid * 8) = make_uint2(0u, 0u);
 
-  dw_f32x4 acc[NIT][NIT];
+  dw_f32x4 sum[NIT][NIT];                                // over the tiles, each summed on its own first (shorter chains of additions)
 #pragma unroll
   for (int i = 0; i < NIT; ++i)
 #pragma unroll
-    for (int j = 0; j < NIT; ++j) acc[i][j] = dw_f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NIT; ++j) sum[i][j] = dw_f32x4{0.f, 0.f, 0.f, 0.f};
 
   uint4 rx[G::NLOAD][4], rd[4];
   auto load_tile = [&](int tile) {
@@ -299,6 +307,13 @@ __global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __r
     const unsigned char* xp = smem + ch * CHX + half * 16;
     const unsigned char* dp = smem + CHX * kDwCh + ch * CHD + half * 16;
     const unsigned char* zp = smem + ZERO + half * 16;
+    dw_f32x4 acc[NIT][NIT][QS];
+#pragma unroll
+    for (int i = 0; i < NIT; ++i)
+#pragma unroll
+      for (int j = 0; j < NIT; ++j)
+#pragma unroll
+        for (int q = 0; q < QS; ++q) acc[i][j][q] = dw_f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 2
     for (int y = 0; y < G::IN; ++y) {
       const unsigned char* db[NIT];
@@ -333,10 +348,14 @@ __global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __r
           if (q < 0 || q > 1) continue;
 #pragma unroll
           for (int jt = 0; jt < NIT; ++jt)
-            acc[it][jt] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(xs, d[jt][q], acc[it][jt], 0, 0, 0);
+            acc[it][jt][q % QS] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(xs, d[jt][q], acc[it][jt][q % QS], 0, 0, 0);
         }
       }
     }
+#pragma unroll
+    for (int i = 0; i < NIT; ++i)
+#pragma unroll
+      for (int j = 0; j < NIT; ++j) sum[i][j] += QS == 2 ? acc[i][j][0] + acc[i][j][QS - 1] : acc[i][j][0];
   }
   // ---- the two column halves of a slice meet in LDS; lane 4 c + j holds taps (r = 4 jt + j, s = 4 it + v) of channel c ----
   __syncthreads();
@@ -346,7 +365,7 @@ __global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __r
     for (int it = 0; it < NIT; ++it)
 #pragma unroll
       for (int jt = 0; jt < NIT; ++jt)
-        *reinterpret_cast<dw_f32x4*>(red + ((slice * NIT * NIT + it * NIT + jt) * 64 + lane) * 4) = acc[it][jt];
+        *reinterpret_cast<dw_f32x4*>(red + ((slice * NIT * NIT + it * NIT + jt) * 64 + lane) * 4) = sum[it][jt];
   }
   __syncthreads();
   if (half || cv0 * 8 + ch >= g.ncv * 8) return;
@@ -359,8 +378,122 @@ __global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __r
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int s = 4 * it + v;
-        if (r < K && s < K) part[((size_t)chunk * K * K + r * K + s) * (g.ncv * 8) + cv0 * 8 + ch] = acc[it][jt][v] + o[v];
+        if (r < K && s < K) part[((size_t)chunk * K * K + r * K + s) * (g.ncv * 8) + cv0 * 8 + ch] = sum[it][jt][v] + o[v];
       }
+    }
+}
+
+// Backward-weight of a stride-2 layer, dW[r][s] = sum x[2 p + r - pad][2 q + s - pad] dy[p][q].  Columns (and rows) of x of one
+// parity are a stride-1 problem with at most (K + 1) / 2 <= 4 taps, so one product covers all taps of a parity pair: the four
+// pixels a thread loads lie two columns apart, LDS holds [channel][row][column parity][column], and with y the row of
+// x in the tile, A[i][k] = x[y][parity][4 c + i + k] (s = 2 i + parity), B[k][j] = dy[(y >> 1) - j][4 c + k] (r = 2 j + (y & 1)).
+// Tile: 8 x 16 pixels of dy, 32 channels; wave = (16 channels) x (column parity), so no two waves share a tap.
+// Bound by the shifts (vector ALUs) and LDS reads at 8 waves per compute unit; against one thread per 8 channels and filter
+// row (dw_wgrad_kernel): 5 x 5, MobileNetV2 batch 128 69 -> 41 us a launch, batch 33 28 -> 13; 7 x 7, supernet 52 -> 30.
+constexpr int kDwS2TileH = 8;
+template <int K>
+__global__ __launch_bounds__(256, 2) void dw_wgrad_s2_mfma_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
+                                                                  float* __restrict__ part, DwArgs g) {
+  constexpr int pad = K / 2, IH = 2 * kDwS2TileH - 2 + K, NQ = 5, CVB = kDwCh / 8;
+  constexpr int ROWX = 2 * NQ * 8, CHX = (IH * ROWX + 31) / 32 * 32 + 8;
+  constexpr int ROWD = kDwTile * 2, CHD = kDwS2TileH * ROWD + 8;
+  constexpr int ITEMS = IH * 2 * NQ * CVB, NLOAD = (ITEMS + 255) / 256;
+  constexpr int DITEMS = kDwS2TileH * 4 * CVB;                        // (128: half of the threads)
+  constexpr int ZERO = CHX * kDwCh + CHD * kDwCh;                     // a row of zeros
+  __shared__ __attribute__((aligned(16))) unsigned char smem[ZERO + ROWD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int slice = wave & 1, par = wave >> 1;
+  const int wg = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int cv0 = (wg % g.groups) * CVB, chunk = wg / g.groups;
+  const int tile_begin = chunk * g.per_block, tile_end = min(g.tiles, tile_begin + g.per_block);
+  const __amdgpu_buffer_rsrc_t xr = tensor_rsrc(x, g.bytes), dr = tensor_rsrc(dy, g.dy_bytes);
+  const int ch = slice * 16 + (lane >> 2), n4 = lane & 3;
+  const unsigned far = n4 >= 2 ? ~0u : 0u, odd = n4 & 1 ? kDwSelMid : kDwSelLow;
+  if (tid < ROWD / 8) *reinterpret_cast<uint2*>(smem + ZERO + tid * 8) = make_uint2(0u, 0u);
+
+  dw_f32x4 sum[2];                                       // by row parity; over the tiles, each summed on its own first
+  sum[0] = sum[1] = dw_f32x4{0.f, 0.f, 0.f, 0.f};
+  uint4 rx[NLOAD][4], rd[4];
+  auto load_tile = [&](int tile) {
+    int t_ = tile;
+    const int tw = t_ % g.tiles_w; t_ /= g.tiles_w;
+    const int th = t_ % g.tiles_h, n = t_ / g.tiles_h;
+    const int p0 = th * kDwS2TileH, q0 = tw * kDwTile;
+#pragma unroll
+    for (int i = 0; i < NLOAD; ++i) {
+      const int c = tid + i * 256;
+      const int cvl = c % CVB, quad = (c / CVB) % NQ, rp = c / CVB / NQ;   // rp = row * 2 + column parity
+      const int h = 2 * p0 - pad + (rp >> 1), w_ = 2 * q0 - pad + 8 * quad + (rp & 1);
+      const bool rok = c < ITEMS && (unsigned)h < (unsigned)g.H && cv0 + cvl < g.ncv;
+      const unsigned off = (unsigned)(((n * g.H + h) * g.W + w_) * g.ncv + cv0 + cvl) * 16u;
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+        rx[i][p] = buffer_load16(xr, rok && (unsigned)(w_ + 2 * p) < (unsigned)g.W ? off + (unsigned)(2 * p * g.ncv) * 16u : kOutOfRange);
+    }
+    const int cvl = tid % CVB, quad = (tid / CVB) % 4, drow = tid / CVB / 4;
+    const int h = p0 + drow, w_ = q0 + 4 * quad;
+    const unsigned off = (unsigned)(((n * g.P + h) * g.Q + w_) * g.ncv + cv0 + cvl) * 16u;
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+      rd[p] = buffer_load16(dr, tid < DITEMS && h < g.P && w_ + p < g.Q && cv0 + cvl < g.ncv ? off + (unsigned)(p * g.ncv) * 16u : kOutOfRange);
+  };
+
+  if (tile_begin < tile_end) load_tile(tile_begin);
+  for (int tile = tile_begin; tile < tile_end; ++tile) {
+    __syncthreads();                                     // the previous tile has been read
+#pragma unroll
+    for (int i = 0; i < NLOAD; ++i) {
+      const int c = tid + i * 256;
+      const int cvl = c % CVB, quad = (c / CVB) % NQ, rp = c / CVB / NQ;
+      if (c < ITEMS) dw_store_transposed<CHX>(smem + cvl * 8 * CHX + rp * (NQ * 8) + quad * 8, rx[i]);
+    }
+    if (tid < DITEMS)
+      dw_store_transposed<CHD>(smem + CHX * kDwCh + (tid % CVB) * 8 * CHD + (tid / CVB / 4) * ROWD + ((tid / CVB) % 4) * 8, rd);
+    __syncthreads();
+    if (tile + 1 < tile_end) load_tile(tile + 1);        // in flight behind this tile's products
+
+    const unsigned char* xp = smem + ch * CHX + par * (NQ * 8);
+    const unsigned char* dp = smem + CHX * kDwCh + ch * CHD;
+    const unsigned char* zp = smem + ZERO;
+    dw_f32x4 acc[2];
+    acc[0] = acc[1] = dw_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int y2 = 0; y2 < (IH + 1) / 2; ++y2) {
+      const int row = y2 - n4;
+      const unsigned char* db = (unsigned)row < (unsigned)kDwS2TileH ? dp + row * ROWD : zp;
+      dw_s16x4 d[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) d[q] = *reinterpret_cast<const dw_s16x4*>(db + q * 8);
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int y = min(2 * y2 + e, IH - 1);           // (IH is odd: the last odd row is the last row once more, into taps r >= K)
+        unsigned D[2 * NQ];
+#pragma unroll
+        for (int c = 0; c < NQ; ++c) {
+          const uint2 v = *reinterpret_cast<const uint2*>(xp + y * ROWX + c * 8);
+          D[2 * c] = v.x; D[2 * c + 1] = v.y;
+        }
+        unsigned E[2 * NQ - 1];
+#pragma unroll
+        for (int i = 0; i < 2 * NQ - 1; ++i) E[i] = dw_sel(far, D[i + 1], D[i]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const unsigned s0 = __builtin_amdgcn_perm(E[2 * c + 1], E[2 * c], odd);
+          const unsigned s1 = __builtin_amdgcn_perm(E[2 * c + 2], E[2 * c + 1], odd);
+          acc[e] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(dw_s16x4, make_uint2(s0, s1)), d[c], acc[e], 0, 0, 0);
+        }
+      }
+    }
+    sum[0] += acc[0];
+    sum[1] += acc[1];
+  }
+  if (cv0 * 8 + ch >= g.ncv * 8) return;
+#pragma unroll
+  for (int e = 0; e < 2; ++e)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = 2 * n4 + e, s = 2 * v + par;
+      if (r < K && s < K) part[((size_t)chunk * K * K + r * K + s) * (g.ncv * 8) + cv0 * 8 + ch] = sum[e][v];
     }
 }
 

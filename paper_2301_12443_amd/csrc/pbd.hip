@@ -257,15 +257,17 @@ ColGrid col_grid(long M, int Cp, int rows_per_thread = 8, int max_blocks = 512) 
 inline ColGrid bn_stats_grid(long M, int Cp) { return col_grid(M, Cp, 8, 1024); }
 inline ColGrid bn_bwd_grid(long M, int Cp) { return col_grid(M, Cp, 8, 1024); }
 
-// Depthwise layers on the matrix cores (bf16, stride 1, odd k <= 7, image at least 8 x 12): tiles and channel groups of
-// one launch, and how many tiles a workgroup takes so that about `blocks` workgroups result.
+// Depthwise layers on the matrix cores (bf16, stride 1).  3 x 3: images of at least 8 x 12 (below that a 16 x 16 tile is mostly
+// padding and the sliding-window kernels win: 7 x 7 x 960, batch 128: 12.5 against 18 us; 8 x 8 x 256, batch 256: 6.3 against 9.6);
+// 5 x 5 and 7 x 7: all images (7 x 7 x 640, 5 x 5, batch 33: 6.1 us against 15 on the sliding windows, backward-weight 9.4 against 23).
 inline bool dw_on_mfma(bool bf16, int k, int stride, int pad, int h_out, int w_out) {
-  return bf16 && (k == 3 || k == 5 || k == 7) && pad == k / 2 && stride == 1 && h_out >= 8 && w_out >= 12;
+  return bf16 && (k == 3 || k == 5 || k == 7) && pad == k / 2 && stride == 1 && (k > 3 || (h_out >= 8 && w_out >= 12));
 }
-inline DwArgs dw_args(int N, int h, int w, int Cp, int blocks) {
+// Tiles and channel groups of a launch, and how many tiles a workgroup takes so that about `blocks` workgroups result.
+inline DwArgs dw_args(int N, int h, int w, int Cp, int blocks, int tile_h = kDwTile) {
   DwArgs g{};
   g.N = N; g.H = h; g.W = w; g.ncv = Cp / 8;
-  g.tiles_h = (h + kDwTile - 1) / kDwTile;
+  g.tiles_h = (h + tile_h - 1) / tile_h;
   g.tiles_w = (w + kDwTile - 1) / kDwTile;
   g.tiles = N * g.tiles_h * g.tiles_w;
   g.groups = (Cp + kDwCh - 1) / kDwCh;
@@ -276,14 +278,21 @@ inline DwArgs dw_args(int N, int h, int w, int Cp, int blocks) {
 inline int dw_chunks(const DwArgs& g) { return (g.tiles + g.per_block - 1) / g.per_block; }
 
 // Partial results of a depthwise backward-weight: row chunks of the column-grid kernel, or workgroups of
-// dw_wgrad_mfma_kernel (three resident workgroups per compute unit; it also wins on 8-wide images, unlike the forward kernel).
+// dw_wgrad_mfma_kernel (three resident workgroups per compute unit; it also wins on 8-wide images, unlike the forward kernel)
+// or, at stride 2, of dw_wgrad_s2_mfma_kernel.
 struct DwWgradCfg { bool mfma; int chunks; DwArgs m; ColGrid g; };
-inline DwWgradCfg dw_wgrad_cfg(bool bf16, int N, int h_out, int w_out, int Cp, int k, int stride, int pad) {
+inline DwWgradCfg dw_wgrad_cfg(bool bf16, int N, int h_in, int w_in, int h_out, int w_out, int Cp, int k, int stride, int pad) {
   DwWgradCfg w{};
   const long M = (long)N * h_out * w_out;
   w.mfma = dw_on_mfma(bf16, k, stride, pad, h_out, std::max(w_out, w_out >= 8 ? 12 : 0));
   if (w.mfma) {
     w.m = dw_args(N, h_out, w_out, Cp, 768);
+    w.chunks = dw_chunks(w.m);
+  } else if (bf16 && (k == 3 || k == 5 || k == 7) && pad == k / 2 && stride == 2) {
+    w.mfma = true;
+    w.m = dw_args(N, h_out, w_out, Cp, 512, kDwS2TileH);      // (two resident workgroups per compute unit)
+    w.m.P = h_out; w.m.Q = w_out; w.m.dy_bytes = w.m.bytes;
+    w.m.H = h_in; w.m.W = w_in; w.m.bytes = (unsigned)((size_t)N * h_in * w_in * Cp * 2);
     w.chunks = dw_chunks(w.m);
   } else {
     w.g = col_grid(M, Cp, 16, k <= 3 ? 512 : 768 / k);
@@ -577,8 +586,8 @@ int plan(pbd_ctx* c) {
         const ColGrid g = bn_bwd_grid(M, op.cout_p);   // the larger of the two reductions' grids
         need_red(((size_t)g.chunks * 2 * op.cout_p + (size_t)g.slabs * g.chunks) * 4);   // (+ one loss partial a workgroup)
         if (op.dw) {
-          const DwWgradCfg gw = dw_wgrad_cfg(bf && !c->o.force_direct, c->o.batch, op.out.h, op.out.w, op.cout_p, op.d.k,
-                                             op.d.stride, op.d.pad);
+          const DwWgradCfg gw = dw_wgrad_cfg(bf && !c->o.force_direct, c->o.batch, op.in.h, op.in.w, op.out.h, op.out.w,
+                                             op.cout_p, op.d.k, op.d.stride, op.d.pad);
           need_red((size_t)gw.chunks * op.d.k * op.d.k * op.cout_p * 4);
         } else if (bf && !c->o.force_direct) {
           const WgradCfg w = op.s2d ? wgrad_cfg(M, op.d.c_out, kS2dK, 16) : wgrad_cfg(M, op.d.c_out, op.d.k * op.d.k * op.cin_p, op.d.k * op.d.k);
@@ -1101,15 +1110,15 @@ template <class T> struct Exec {
   }
   void dw_wgrad(const OpPlan& op, const T* dy, const T* x, float* dw) {
     const int N = c->o.batch;
-    const DwWgradCfg cfg = dw_wgrad_cfg(mfma(), N, op.out.h, op.out.w, op.cout_p, op.d.k, op.d.stride, op.d.pad);
+    const DwWgradCfg cfg = dw_wgrad_cfg(mfma(), N, op.in.h, op.in.w, op.out.h, op.out.w, op.cout_p, op.d.k, op.d.stride, op.d.pad);
     {
       char cls[32];
-      snprintf(cls, sizeof cls, "dw_wgrad%s_k%d", cfg.mfma ? "_mfma" : "", op.d.k <= 3 ? 3 : cfg.mfma ? op.d.k : 7);
+      snprintf(cls, sizeof cls, "dw_wgrad%s_k%d", cfg.mfma ? (op.d.stride == 2 ? "_s2_mfma" : "_mfma") : "", op.d.k <= 3 ? 3 : cfg.mfma ? op.d.k : 7);
       ProfScope ps(c, cls, bytes_of(op.in) + bytes_of(op.out),
                    2.0 * N * op.out.h * op.out.w * op.d.c_out * op.d.k * op.d.k, net, blk, opi);
       if (cfg.mfma) {
         if constexpr (sizeof(T) == 2) {
-#define PBD_DWW(K_) launch(c, dw_wgrad_mfma_kernel<K_>, cfg.chunks * cfg.m.groups, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)x, red(), cfg.m)
+#define PBD_DWW(K_) launch(c, op.d.stride == 2 ? dw_wgrad_s2_mfma_kernel<K_> : dw_wgrad_mfma_kernel<K_>, cfg.chunks * cfg.m.groups, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)x, red(), cfg.m)
           if (op.d.k == 3) PBD_DWW(3); else if (op.d.k == 5) PBD_DWW(5); else PBD_DWW(7);
 #undef PBD_DWW
         }

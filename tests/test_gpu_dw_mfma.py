@@ -1,5 +1,5 @@
-"""Depthwise convolutions on the matrix cores (dw_mfma_kernel, dw_wgrad_mfma_kernel) at the edges of their 16 x 16-pixel x
-32-channel tiles: every operation of a one-block step, and the teacher's folded form, against the plain fp64 oracle
+"""Depthwise convolutions on the matrix cores (dw_mfma_kernel, dw_wgrad_mfma_kernel, dw_wgrad_s2_mfma_kernel) at the edges
+of their tiles of 16 x 16 or 8 x 16 pixels x 32 channels: every operation of a one-block step, and the teacher's folded form, against the plain fp64 oracle
 primitives on the tensors that the library read (local_parity.py).  Its bounds: one bfloat16 rounding of a result (2^-9 of
 it, 2e-2 of the largest allowed) forward and backward-data; the weight gradient is float32, a sum of n products of
 bfloat16 numbers, off by at most n 2^-24 of the sum of their magnitudes - a wrong tap, shift or mask is off by the size of
@@ -11,30 +11,37 @@ from paper_2301_12443_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
-# (batch, h, w, channels, k)
+# (batch, h, w, channels, k, stride)
 SHAPES = [
-    (1, 8, 12, 8, 3),         # the smallest image, one vector of channels
-    (3, 16, 16, 40, 5),       # exactly one tile, a channel group and a quarter
-    (2, 17, 33, 72, 7),       # one row and one column into the next tiles
-    (1, 15, 31, 32, 3),       # one short of a tile both ways
-    (2, 14, 14, 144, 5),      # the late layers: one ragged tile
-    (1, 49, 13, 24, 7),       # three tiles and a row
-    (40, 32, 20, 96, 7),      # several tiles per workgroup, forward and backward
-    (3, 9, 8, 64, 3),         # 8 wide: only the weight gradient takes the matrix cores
-    (2, 31, 47, 16, 5),       # half a channel group
+    (1, 8, 12, 8, 3, 1),         # the smallest image, one vector of channels
+    (3, 16, 16, 40, 5, 1),       # exactly one tile, a channel group and a quarter
+    (2, 17, 33, 72, 7, 1),       # one row and one column into the next tiles
+    (1, 15, 31, 32, 3, 1),       # one short of a tile both ways
+    (2, 14, 14, 144, 5, 1),      # the late layers: one ragged tile
+    (1, 49, 13, 24, 7, 1),       # three tiles and a row
+    (40, 32, 20, 96, 7, 1),      # several tiles per workgroup, forward and backward
+    (3, 9, 8, 64, 3, 1),         # 8 wide: only the weight gradient takes the matrix cores
+    (2, 31, 47, 16, 5, 1),       # half a channel group
+    (5, 4, 5, 40, 5, 1),      # a corner of a tile
+    (3, 16, 32, 40, 3, 2),    # stride 2 (8 x 16 tiles of the output): exactly one tile of an even image
+    (2, 17, 33, 72, 5, 2),    # one output row and column into the next tiles, odd image
+    (2, 31, 30, 24, 7, 2),
+    (60, 33, 63, 96, 7, 2),   # several tiles per workgroup
+    (4, 7, 7, 32, 5, 2),
+    (2, 2, 3, 16, 3, 2),
 ]
 
 
-@pytest.mark.parametrize("n,h,w,c,k", SHAPES)
-def test_every_operation_of_a_small_block(n, h, w, c, k):
+@pytest.mark.parametrize("n,h,w,c,k,stride", SHAPES)
+def test_every_operation_of_a_small_block(n, h, w, c, k, stride):
     t, b = W.Block(), W.Block()
     v = t.cba(0, c, 1, act=W.ACT_RELU6)
-    v = t.cba(v, c, k, groups=c, act=W.ACT_RELU6)
+    v = t.cba(v, c, k, stride, groups=c, act=W.ACT_RELU6)
     t.cba(v, 16, 1, act=W.ACT_NONE)
     v = b.cba(0, c, 1, act=W.ACT_RELU6)
     # two readers of v: the second backward-data launch adds onto the first one's result
-    d1 = b.cba(v, c, k, groups=c, act=W.ACT_RELU6)
-    d2 = b.cba(v, c, 3, groups=c, act=W.ACT_NONE)
+    d1 = b.cba(v, c, k, stride, groups=c, act=W.ACT_RELU6)
+    d2 = b.cba(v, c, 3, stride, groups=c, act=W.ACT_NONE)
     b.cba(b.add(d1, d2), 16, 1, act=W.ACT_NONE)
     wl = W.Workload("dw_mfma", n, (8, h, w), [t], [b], "bf16", lr=0.05)
     worst = local_parity.run_and_check(wl, n)
