@@ -79,6 +79,7 @@ struct OpPlan {
   size_t e_w = 0, e_gamma = 0, e_beta = 0;
   size_t s_rmean = 0, s_rvar = 0, s_mean = 0, s_invstd = 0, s_k2 = 0, s_k3 = 0;
   long e_wt = -1;           // element offset in the block's transposed-weight arena
+  long e_part = -1;         // element offset of the weight gradient's partial sums among the block's deferred ones (-1: summed at once)
   // scratch byte offsets
   size_t y = 0, idx = 0;
   int mix_slot = -1;        // student mix op: which 32-float state record of the block it owns
@@ -97,6 +98,10 @@ struct BlockPlan {
   size_t master = 0, mom = 0, grad = 0, wc = 0, wt = 0, table = 0;  // byte offsets (param region)
   size_t wt_elems = 0;
   std::vector<TransposeEntry> ttable;
+  // weight gradients whose partial sums are added in one launch per block (sum_partials_batch_kernel): the table and its byte
+  // offset (param region), and the scratch byte offset of the partial sums
+  std::vector<SumEntry> stable;
+  size_t sum_table = 0, parts = 0;
   size_t scratch_bytes = 0, red_bytes = 0;
   size_t scr_off = 0, red_off = 0;   // absolute workspace offsets of this block's scratch regions
   size_t mix = 0;                // byte offset (param region) of the mix ops' state records
@@ -410,7 +415,7 @@ DmaCfg dma_cfg(long M, int NC, int Kred, int CA, int num_cu, int epi) {
     const int bn = kBN[i];
     if (narrow && bn > 128) continue;
     const long tn = (NC + bn - 1) / bn, T = tm * tn;
-    const long slots = (bn <= 128 ? 2 : 1) * (long)num_cu;       // (narrow tiles: two resident workgroups per unit)
+    const long slots = (bn <= 128 && T > num_cu ? 2 : 1) * (long)num_cu;       // (narrow tiles: two resident workgroups per unit)
     const long full = T / slots, r = T % slots;
     double rounds = (double)full;
     if (r) rounds += (full >= 1 && r <= slots / 4) ? 0.66 : 1.0;
@@ -471,6 +476,11 @@ WgradCfg wgrad_f32_cfg(long M, int K, int J) {
 }
 
 constexpr int kMseBlocks = 1024;
+
+// Partial sums of a weight gradient of up to 4 MB wait for the block's one summing launch; larger ones, whose sum is memory
+// traffic rather than a launch, are added at once while the caches hold them (ResNet-50 x1.5 at batch 256: 53 sums of 46 MB on
+// average at 5.2 TB/s).
+constexpr size_t kDeferredElems = (size_t)1 << 20;
 
 // the stem that is run on the space-to-depth copy of the input: first block, reads A_0, 7 x 7, stride 2, pad 3,
 // at most 4 input channels, even image size, bf16 MFMA path
@@ -535,6 +545,7 @@ int plan(pbd_ctx* c) {
     bp.wc = bf ? take(e * 2) : bp.master;
     bp.wt = take(std::max<size_t>(et, 1) * es);
     bp.table = take(std::max<size_t>(bp.ttable.size(), 1) * sizeof(TransposeEntry));
+    bp.sum_table = take(std::max<size_t>(bp.ops.size(), 1) * sizeof(SumEntry));
     bp.mix = take((size_t)std::max(bp.nmix, 1) * kMixState * sizeof(float));
     bp.alpha_defined.assign(bp.nmix, 0);
   }
@@ -572,8 +583,14 @@ int plan(pbd_ctx* c) {
   size_t smax = 0;
   size_t ssum = 0;
   for (BlockPlan& bp : c->net[1]) {
-    size_t s = 0;
+    size_t s = 0, parts = 0;      // (parts: elements of the deferred partial sums)
     red = kMseBlocks * sizeof(float);
+    auto defer = [&](OpPlan& op, int splits) {
+      if (splits < 2 || (size_t)splits * op.wn > kDeferredElems) return;
+      op.e_part = (long)parts;
+      bp.stable.push_back({(long)parts, (long)op.e_w, (long)op.wn, splits, 0});
+      parts += (size_t)splits * op.wn;
+    };
     bp.val.assign(bp.shapes.size(), 0);
     bp.dval.assign(bp.shapes.size(), 0);
     for (size_t v = 1; v < bp.shapes.size(); ++v) {
@@ -589,10 +606,12 @@ int plan(pbd_ctx* c) {
           const DwWgradCfg gw = dw_wgrad_cfg(bf && !c->o.force_direct, c->o.batch, op.in.h, op.in.w, op.out.h, op.out.w,
                                              op.cout_p, op.d.k, op.d.stride, op.d.pad);
           need_red((size_t)gw.chunks * op.d.k * op.d.k * op.cout_p * 4);
+          defer(op, gw.chunks);
         } else if (bf && !c->o.force_direct) {
           const WgradCfg w = op.s2d ? wgrad_cfg(M, op.d.c_out, kS2dK, 16) : wgrad_cfg(M, op.d.c_out, op.d.k * op.d.k * op.cin_p, op.d.k * op.d.k);
           // (the stem on the space-to-depth input: partial sums and their sum in the repacked layout, then unpacked)
           need_red(op.s2d ? ((size_t)w.splits + 1) * op.d.c_out * kS2dK * 4 : (size_t)w.splits * op.wn * 4);
+          if (!op.s2d) defer(op, w.splits);
           // per-row-tile batch-norm sums from the convolution's store (64-row tiles at most), and their regrouping
           need_red(((size_t)(M + 63) / 64 + kStatGroupsMax + 1) * 2 * op.cout_p * 4);
           const long Min = (long)c->o.batch * op.in.h * op.in.w;
@@ -602,6 +621,7 @@ int plan(pbd_ctx* c) {
         } else if (!bf && !c->o.force_direct) {
           const WgradCfg w = wgrad_f32_cfg(M, op.d.c_out, op.d.k * op.d.k * op.cin_p);
           if (w.splits > 1) need_red((size_t)w.splits * op.wn * 4);
+          defer(op, w.splits);
         }
       } else if (op.d.type == OP_POOL) {
         op.idx = s; s += align_up((size_t)M * op.cout_p);
@@ -609,7 +629,8 @@ int plan(pbd_ctx* c) {
         need_red((size_t)kMixDotBlocks * 8 * sizeof(float));
       }
     }
-    bp.scratch_bytes = align_up(s);
+    bp.parts = s;
+    bp.scratch_bytes = align_up(s + parts * 4);
     bp.red_bytes = align_up(red);
     smax = std::max(smax, bp.scratch_bytes + bp.red_bytes);
     ssum += bp.scratch_bytes + bp.red_bytes;
@@ -728,6 +749,12 @@ template <class T> struct Exec {
     return dma_for((long)c->o.batch * op.out.h * op.out.w, op.d.c_out, kS2dK, 64).use ? 64 : 16;
   }
   float* red() const { return red_static ? red_static : wsf(red_off); }
+  // where a layer's weight-gradient partial sums go, and whether they are added with the whole block's (the caller
+  // that brings its own scratch has them added at once: same association, same bits)
+  bool deferred(const OpPlan& op) const { return op.e_part >= 0 && !red_static; }
+  float* parts(const OpPlan& op) const {
+    return deferred(op) ? wsf(c->net[1][blk].scr_off + c->net[1][blk].parts) + op.e_part : red();
+  }
   double bytes_of(Shape s) const { return (double)c->o.batch * s.h * s.w * round8(s.c) * sizeof(T); }
   bool mfma() const { return sizeof(T) == 2 && !c->o.force_direct; }
   // The batch-norm passes over a tensor of this shape use nontemporal loads and stores (bf16 tensors far larger than
@@ -960,7 +987,7 @@ template <class T> struct Exec {
                       (unsigned)(M * op.d.c_out * 2), (unsigned)((size_t)N * op.in.h * op.in.w * op.cin_p * 2),
                       w.tiles_k, w.tiles_j, w.splits};
         const dim3 grid(w.tiles_k * w.tiles_j * w.splits);
-        float* part = w.splits == 1 ? dw : red();
+        float* part = w.splits == 1 ? dw : parts(op);
         long wn_run = (long)op.wn;
         float* dw_run = dw;                        // where the summed gradient goes
         double bytes_run = bytes;
@@ -990,7 +1017,7 @@ template <class T> struct Exec {
 #undef PBD_WG
           }
         }
-        if (w.splits > 1) {
+        if (w.splits > 1 && !deferred(op)) {
           ProfScope ps(c, "sum_partials", (double)(w.splits + 1) * wn_run * 4, 0, net, blk, opi);
           sum_partials(part, dw_run, wn_run, w.splits);
         }
@@ -1006,12 +1033,12 @@ template <class T> struct Exec {
                       w.BKP / pq, (w.BKP % pq) / op.out.w, w.BKP % op.out.w,
                       (unsigned)(M * op.d.c_out * 4), (unsigned)((size_t)N * op.in.h * op.in.w * op.cin_p * 4),
                       w.tiles_k, w.tiles_j, w.splits};
-        float* part = w.splits == 1 ? dw : red();
+        float* part = w.splits == 1 ? dw : parts(op);
         {
           ProfScope ps(c, "wgrad_f32", bytes, flops, net, blk, opi);
           launch(c, wgrad_f32_kernel<kF32WgradUnr>, w.tiles_k * w.tiles_j * w.splits, kF32Threads, 0, st, dy, x, part, g);
         }
-        if (w.splits > 1) {
+        if (w.splits > 1 && !deferred(op)) {
           ProfScope ps(c, "sum_partials", (double)(w.splits + 1) * op.wn * 4, 0, net, blk, opi);
           sum_partials(part, dw, (long)op.wn, w.splits);
         }
@@ -1024,8 +1051,21 @@ template <class T> struct Exec {
   }
 
   void sum_partials(const float* part, float* out, long n, int splits) {
-    if (splits >= 64) launch(c, sum_partials_kernel<32>, grid_for(n / 4, 8), 256, 0, st, part, out, n, splits, n);
-    else launch(c, sum_partials_kernel<8>, grid_for(n / 4, 32), 256, 0, st, part, out, n, splits, n);
+    if (splits >= kManySplits) launch(c, sum_partials_kernel<32>, grid_for(n / 4, 8), 256, 0, st, part, out, n, splits);
+    else launch(c, sum_partials_kernel<8>, grid_for(n / 4, 32), 256, 0, st, part, out, n, splits);
+  }
+  // the block's deferred sums, ahead of the update that reads them
+  void sum_deferred(const BlockPlan& bp) {
+    if (bp.stable.empty() || red_static) return;
+    double bytes = 0;
+    long rows = 1;                  // workgroups that the layer with the most of them can use
+    for (const SumEntry& e : bp.stable) {
+      bytes += (double)(e.splits + 1) * e.n * 4;
+      rows = std::max(rows, (e.n / 4 + (e.splits >= kManySplits ? 7 : 31)) / (e.splits >= kManySplits ? 8 : 32));
+    }
+    ProfScope ps(c, "sum_partials_batch", bytes, 0, net, blk, -1);
+    launch(c, sum_partials_batch_kernel, dim3((unsigned)std::min(rows, 256L), (unsigned)bp.stable.size()), 256, 0, st,
+           wsf(bp.scr_off + bp.parts), wsf(bp.grad), reinterpret_cast<const SumEntry*>(c->ws + bp.sum_table));
   }
 
   // ---- depthwise ----------------------------------------------------------
@@ -1118,7 +1158,7 @@ template <class T> struct Exec {
                    2.0 * N * op.out.h * op.out.w * op.d.c_out * op.d.k * op.d.k, net, blk, opi);
       if (cfg.mfma) {
         if constexpr (sizeof(T) == 2) {
-#define PBD_DWW(K_) launch(c, op.d.stride == 2 ? dw_wgrad_s2_mfma_kernel<K_> : dw_wgrad_mfma_kernel<K_>, cfg.chunks * cfg.m.groups, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)x, red(), cfg.m)
+#define PBD_DWW(K_) launch(c, op.d.stride == 2 ? dw_wgrad_s2_mfma_kernel<K_> : dw_wgrad_mfma_kernel<K_>, cfg.chunks * cfg.m.groups, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)x, parts(op), cfg.m)
           if (op.d.k == 3) PBD_DWW(3); else if (op.d.k == 5) PBD_DWW(5); else PBD_DWW(7);
 #undef PBD_DWW
         }
@@ -1127,16 +1167,17 @@ template <class T> struct Exec {
         const size_t smem = 256 * 8 * sizeof(float) * (op.d.k <= 3 ? 3 : 7);
         if (op.d.k <= 3)
           launch(c, dw_wgrad_kernel<T, 3, 3>, dim3(g.slabs, g.chunks, 1), 256, smem, st,
-              dy, x, red(), N, op.in.h, op.in.w, op.out.h, op.out.w, op.cout_p, op.d.k, op.d.stride, op.d.pad, g,
+              dy, x, parts(op), N, op.in.h, op.in.w, op.out.h, op.out.w, op.cout_p, op.d.k, op.d.stride, op.d.pad, g,
               (unsigned)((size_t)N * op.in.h * op.in.w * op.cin_p));
         else
           launch(c, dw_wgrad_kernel<T, 7, 1>, dim3(g.slabs, g.chunks, op.d.k), 256, smem, st,
-              dy, x, red(), N, op.in.h, op.in.w, op.out.h, op.out.w, op.cout_p, op.d.k, op.d.stride, op.d.pad, g,
+              dy, x, parts(op), N, op.in.h, op.in.w, op.out.h, op.out.w, op.cout_p, op.d.k, op.d.stride, op.d.pad, g,
               (unsigned)((size_t)N * op.in.h * op.in.w * op.cin_p));
       }
     }
+    if (deferred(op)) return;
     ProfScope ps(c, "sum_partials", (double)(cfg.chunks + 1) * op.wn * 4, 0, net, blk, opi);
-    sum_partials(red(), dw, (long)op.wn, cfg.chunks);
+    sum_partials(parts(op), dw, (long)op.wn, cfg.chunks);
   }
 
   // ---- joins / pool -------------------------------------------------------
@@ -1588,6 +1629,7 @@ template <class T> struct Exec {
     // ---- decoupled update of this block only -----------------------------
     if (!arch) {
       opi = -1;
+      sum_deferred(bp);
       const long n4 = (long)bp.arena_elems / 4;
       ProfScope ps(c, "sgd_momentum", (double)bp.arena_elems * (20 + (sizeof(T) == 2 ? 2 : 0)), 0, net, blk, opi);
       if constexpr (sizeof(T) == 2)
@@ -2067,6 +2109,9 @@ int pbd_bind(pbd_ctx* c, void* dev_ws, size_t bytes, void* hip_stream) {
         }
       }
       if (net == 1) {
+        if (!bp.stable.empty())
+          HIP_TRY(c, hipMemcpyAsync(c->ws + bp.sum_table, bp.stable.data(), bp.stable.size() * sizeof(SumEntry),
+                                    hipMemcpyHostToDevice, c->stream));
         if (!bp.ttable.empty())
           HIP_TRY(c, hipMemcpyAsync(c->ws + bp.table, bp.ttable.data(), bp.ttable.size() * sizeof(TransposeEntry),
                                     hipMemcpyHostToDevice, c->stream));
