@@ -61,6 +61,43 @@ __device__ __forceinline__ void dw_store_transposed(unsigned char* dst, const ui
   }
 }
 
+// The producer's batch norm and rectifier, applied to what a kernel stages (FOLD): the input is then the producing layer's
+// convolution output y, and the normalised tensor z = act((y - mean) * (gamma * invstd) + beta) is neither written nor read.  The
+// arithmetic and the rounding are bn_apply_kernel's, so every value is what it would have stored; pixels outside the image
+// stay zero.  ~45 vector operations per 8 channels and pixel (halo included) beside matrix instructions that leave the vector
+// ALUs idle.
+struct DwFold { float mu[kDwCh], a[kDwCh], b[kDwCh]; };
+__device__ __forceinline__ void dw_fold_load(DwFold& f, const NormFold& fold, int c0, int C, int tid) {
+  if (tid < kDwCh) {
+    const int c = c0 + tid;
+    const bool in = c < C;
+    f.mu[tid] = in ? fold.mean[c] : 0.f;
+    f.a[tid] = in ? fold.gamma[c] * fold.invstd[c] : 0.f;
+    f.b[tid] = in ? fold.beta[c] : 0.f;
+  }
+}
+// p: four pixels x 8 channels as loaded; bit i of ok: pixel i lies in the image.  ReLU or ReLU6 (hi = infinity or 6)
+__device__ __forceinline__ void dw_fold_apply(uint4 (&p)[4], const DwFold& f, int c8, unsigned ok, float hi) {
+  float mu[8], a[8], b[8];
+#pragma unroll
+  for (int e = 0; e < 8; e += 4) {
+    const float4 m4 = *reinterpret_cast<const float4*>(f.mu + c8 + e), a4 = *reinterpret_cast<const float4*>(f.a + c8 + e),
+                 b4 = *reinterpret_cast<const float4*>(f.b + c8 + e);
+    mu[e] = m4.x; mu[e + 1] = m4.y; mu[e + 2] = m4.z; mu[e + 3] = m4.w;
+    a[e] = a4.x; a[e + 1] = a4.y; a[e + 2] = a4.z; a[e + 3] = a4.w;
+    b[e] = b4.x; b[e + 1] = b4.y; b[e + 2] = b4.z; b[e + 3] = b4.w;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float v[8];
+    IO<bf16_t>::unpack(p[i], v);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = fminf(fmaxf(fmaf(v[e] - mu[e], a[e], b[e]), 0.f), hi);
+    const bool in = (ok >> i) & 1u;
+    p[i] = in ? make_uint4(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7])) : make_uint4(0u, 0u, 0u, 0u);
+  }
+}
+
 // Work items: (tile, channel group), group fastest (neighbouring groups share the 128-byte lines of a pixel), a
 // workgroup takes `per_block` tiles of one group one after the other (its filters stay in registers).
 struct DwArgs {
@@ -80,15 +117,16 @@ struct DwArgs {
 // the vector ALUs: 7 x 7 72 -> 37 us, 5 x 5 40 -> 30, 3 x 3 24.4 -> 24.7 (and MobileNetV2's at batch 33: 11.6 -> 8.3).
 // Slower: the next tile's loads in flight behind the products (K = 7 40 us, K = 5 31: the registers cost a workgroup per
 // compute unit); 64 channels a workgroup (K = 5 31 us, batch 33 12.6 against 11.4).
-template <int K, bool FLIP>
+template <int K, bool FLIP, bool FOLD = false>
 __global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
                                                          bf16_t* __restrict__ dst, const float* __restrict__ a,
-                                                         const float* __restrict__ b, int act, DwArgs g) {
+                                                         const float* __restrict__ b, int act, DwArgs g, NormFold fold) {
   typedef DwGeom<K> G;
   constexpr int NT = G::NT, pad = K / 2;
   constexpr int LDS = G::CHP * kDwCh > kDwOutRow * kDwTile ? G::CHP * kDwCh : kDwOutRow * kDwTile;
   static_assert(kDwCh * K * G::WROW <= LDS, "the filters fit where the tile goes");
   __shared__ __attribute__((aligned(16))) unsigned char smem[LDS];
+  __shared__ __attribute__((aligned(16))) DwFold folded;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slice = wave & 1, half = wave >> 1;
   const int wg = xcd_contiguous(blockIdx.x, gridDim.x);
@@ -97,6 +135,8 @@ __global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16
   const __amdgpu_buffer_rsrc_t xr = tensor_rsrc(x, g.bytes);
   const int ch = slice * 16 + (lane >> 2), strip = lane & 3;         // (strip: also this lane's output column of the filter operand)
 
+  if (FOLD) dw_fold_load(folded, fold, cv0 * 8, g.ncv * 8, tid);
+  const float hi = fold.act == ACT_RELU6 ? 6.f : __builtin_inff();
   // ---- filters: [channel][filter row][tap] in LDS, then each lane's Toeplitz rows into registers ----
   for (int i = tid; i < K * K * (kDwCh / 2); i += 256) {
     const int tap = i / (kDwCh / 2), c2 = i % (kDwCh / 2);
@@ -145,6 +185,7 @@ __global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16
     const int h0 = th * kDwTile, w0 = tw * kDwTile;
     // ---- the tile's input, all loads in flight together ----
     uint4 raw[G::NLOAD][4];
+    unsigned ok = 0;                                     // bit 4 i + p: pixel p of item i lies in the image
 #pragma unroll
     for (int i = 0; i < G::NLOAD; ++i) {
       const int c = tid + i * 256;
@@ -153,14 +194,18 @@ __global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16
       const bool rok = c < G::ITEMS && (unsigned)h < (unsigned)g.H && cv0 + cvl < g.ncv;
       const unsigned off = (unsigned)(((n * g.H + h) * g.W + w_) * g.ncv + cv0 + cvl) * 16u;
 #pragma unroll
-      for (int p = 0; p < 4; ++p)
-        raw[i][p] = buffer_load16(xr, rok && 4 * quad + p < G::IN && (unsigned)(w_ + p) < (unsigned)g.W ? off + (unsigned)(p * g.ncv) * 16u : kOutOfRange);
+      for (int p = 0; p < 4; ++p) {
+        const bool in = rok && 4 * quad + p < G::IN && (unsigned)(w_ + p) < (unsigned)g.W;
+        raw[i][p] = buffer_load16(xr, in ? off + (unsigned)(p * g.ncv) * 16u : kOutOfRange);
+        if (FOLD) ok |= (in ? 1u : 0u) << (4 * i + p);
+      }
     }
     __syncthreads();                                     // the previous tile (or the filters) has been read
 #pragma unroll
     for (int i = 0; i < G::NLOAD; ++i) {
       const int c = tid + i * 256;
       const int cvl = c % (kDwCh / 8), quad = (c / (kDwCh / 8)) % G::NQ, row = c / (kDwCh / 8) / G::NQ;
+      if (FOLD) dw_fold_apply(raw[i], folded, cvl * 8, ok >> (4 * i), hi);
       if (c < G::ITEMS) dw_store_transposed<G::CHP>(smem + cvl * 8 * G::CHP + row * G::ROWP + quad * 8, raw[i]);
     }
     __syncthreads();
@@ -241,15 +286,16 @@ __global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16
 // column halves meet in LDS at the end; one partial result per workgroup as in the other kernels.  Bound by the shifts and
 // LDS reads.  Launch averages over the supernet step against a tile kernel on the vector ALUs: 7 x 7 90 -> 39 us, 5 x 5
 // 72 -> 35, 3 x 3 37 -> 26.
-template <int K>
+template <int K, bool FOLD = false>
 __global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
-                                                               float* __restrict__ part, DwArgs g) {
+                                                               float* __restrict__ part, DwArgs g, NormFold fold) {
   typedef DwGeom<K> G;
   constexpr int pad = K / 2, NIT = K == 3 ? 1 : 2, QS = K == 7 ? 1 : 2;    // (QS: accumulators per tap block, one per quad column where registers allow)
   constexpr int ROWX = G::NQ * 8, CHX = (G::IN * ROWX + 31) / 32 * 32 + 8;          // x: rows of whole quads
   constexpr int ROWD = kDwTile * 2, CHD = kDwTile * ROWD + 8;                        // dy: 16 x 16 pixels a channel
   constexpr int ZERO = CHX * kDwCh + CHD * kDwCh;                                    // a row of zeros
   __shared__ __attribute__((aligned(16))) unsigned char smem[ZERO + ROWD];
+  __shared__ __attribute__((aligned(16))) DwFold folded;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slice = wave & 1, half = wave >> 1;
   const int wg = xcd_contiguous(blockIdx.x, gridDim.x);
@@ -266,8 +312,12 @@ __global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __r
 #pragma unroll
     for (int j = 0; j < NIT; ++j) sum[i][j] = dw_f32x4{0.f, 0.f, 0.f, 0.f};
 
+  if (FOLD) dw_fold_load(folded, fold, cv0 * 8, g.ncv * 8, tid);     // (visible behind the first tile's barrier)
+  const float hi = fold.act == ACT_RELU6 ? 6.f : __builtin_inff();
   uint4 rx[G::NLOAD][4], rd[4];
+  unsigned ok = 0;                                       // bit 4 i + p: pixel p of item i of rx lies in the image
   auto load_tile = [&](int tile) {
+    ok = 0;
     int t_ = tile;
     const int tw = t_ % g.tiles_w; t_ /= g.tiles_w;
     const int th = t_ % g.tiles_h, n = t_ / g.tiles_h;
@@ -280,8 +330,11 @@ __global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __r
       const bool rok = c < G::ITEMS && (unsigned)h < (unsigned)g.H && cv0 + cvl < g.ncv;
       const unsigned off = (unsigned)(((n * g.H + h) * g.W + w_) * g.ncv + cv0 + cvl) * 16u;
 #pragma unroll
-      for (int p = 0; p < 4; ++p)
-        rx[i][p] = buffer_load16(xr, rok && 4 * quad + p < G::IN && (unsigned)(w_ + p) < (unsigned)g.W ? off + (unsigned)(p * g.ncv) * 16u : kOutOfRange);
+      for (int p = 0; p < 4; ++p) {
+        const bool in = rok && 4 * quad + p < G::IN && (unsigned)(w_ + p) < (unsigned)g.W;
+        rx[i][p] = buffer_load16(xr, in ? off + (unsigned)(p * g.ncv) * 16u : kOutOfRange);
+        if (FOLD) ok |= (in ? 1u : 0u) << (4 * i + p);
+      }
     }
     const int cvl = tid % (kDwCh / 8), quad = (tid / (kDwCh / 8)) % 4, drow = tid / (kDwCh / 8) / 4;
     const int h = h0 + drow, w_ = w0 + 4 * quad;
@@ -298,6 +351,7 @@ __global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __r
     for (int i = 0; i < G::NLOAD; ++i) {
       const int c = tid + i * 256;
       const int cvl = c % (kDwCh / 8), quad = (c / (kDwCh / 8)) % G::NQ, row = c / (kDwCh / 8) / G::NQ;
+      if (FOLD) dw_fold_apply(rx[i], folded, cvl * 8, ok >> (4 * i), hi);
       if (c < G::ITEMS) dw_store_transposed<CHX>(smem + cvl * 8 * CHX + row * ROWX + quad * 8, rx[i]);
     }
     dw_store_transposed<CHD>(smem + CHX * kDwCh + (tid % (kDwCh / 8)) * 8 * CHD + (tid / (kDwCh / 8) / 4) * ROWD + ((tid / (kDwCh / 8)) % 4) * 8, rd);

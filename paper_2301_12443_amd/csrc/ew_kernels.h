@@ -457,10 +457,12 @@ __device__ __forceinline__ void finalize_sums(const float* __restrict__ part, in
 
 // mean, biased variance -> inv std; running statistics
 //   rm <- (1-rho) rm + rho mean,  rv <- (1-rho) rv + rho var m/(m-1)
+// keep (optional): [2][Cp] copies of gamma and beta as the step's normalisation uses them (the update overwrites both),
+// for a normalised tensor that is not written and may be asked for later
 template <class T>
 __global__ void bn_finalize_kernel(const float* __restrict__ part, const T* __restrict__ y, int chunks,
                                    int Cp, double m, float* mean, float* invstd, float* rmean,
-                                   float* rvar, float eps, float rho) {
+                                   float* rvar, float eps, float rho, const float* gamma, const float* beta, float* keep) {
   const int c = blockIdx.x * kFinalizeChannels + (threadIdx.x & (kFinalizeChannels - 1)), lane = threadIdx.x >> 3;
   double s1, s2;
   finalize_sums(part, chunks, Cp, c, lane, s1, s2);
@@ -469,6 +471,7 @@ __global__ void bn_finalize_kernel(const float* __restrict__ part, const T* __re
   const double mu = (y ? (double)(float)y[c] : 0.0) + shift;     // y: the pivot row the sums were shifted by, if any
   double var = s2 / m - shift * shift;
   if (var < 0.0) var = 0.0;
+  if (keep) { keep[c] = gamma[c]; keep[Cp + c] = beta[c]; }
   mean[c] = (float)mu;
   invstd[c] = (float)(1.0 / sqrt(var + (double)eps));
   rmean[c] = (1.f - rho) * rmean[c] + rho * (float)mu;

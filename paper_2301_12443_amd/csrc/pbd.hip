@@ -78,6 +78,7 @@ struct OpPlan {
   // student: element offsets in the block's flat arena; byte offsets for statistics
   size_t e_w = 0, e_gamma = 0, e_beta = 0;
   size_t s_rmean = 0, s_rvar = 0, s_mean = 0, s_invstd = 0, s_k2 = 0, s_k3 = 0;
+  size_t s_keep = 0;        // gamma and beta of the last step, where the normalised output is not written (depthwise_reader)
   long e_wt = -1;           // element offset in the block's transposed-weight arena
   long e_part = -1;         // element offset of the weight gradient's partial sums among the block's deferred ones (-1: summed at once)
   // scratch byte offsets
@@ -530,6 +531,7 @@ int plan(pbd_ctx* c) {
       op.e_beta = e; e += op.cout_p;
       for (size_t* s : {&op.s_rmean, &op.s_rvar, &op.s_mean, &op.s_invstd, &op.s_k2, &op.s_k3})
         *s = take(op.cout_p * 4);
+      op.s_keep = take(op.cout_p * 8);
       op.s2d = stem_s2d(c, (int)(&bp - &c->net[1][0]), op);
       if (op.s2d) op.w2 = take((size_t)op.d.c_out * kS2dK * es);
       // transposed copy for backward-data of dense convolutions that need it
@@ -723,6 +725,26 @@ int pool_reader(const BlockPlan& bp, int j, int batch) {
       if (q.in[i] == j + 1) { ++uses; reader = k; }
   }
   return uses == 1 && bp.ops[reader].d.type == OP_POOL ? reader : -1;
+}
+
+// For student layer j: the index of a depthwise layer that is the only reader of j's output and runs on the matrix cores
+// (it then normalises and rectifies j's convolution output as it stages it, forward and in its weight gradient, and the
+// normalised tensor is not written), else -1.  Bit for bit the values of the separate pass.  MobileNetV2's and the supernet's
+// expand layers, whose output is the block's largest tensor.
+int depthwise_reader(const pbd_ctx* c, const BlockPlan& bp, int j) {
+  const OpPlan& p = bp.ops[j];
+  if (c->o.precision != PBD_BF16 || c->o.force_direct || p.d.type != OP_CBA || (p.d.act != ACT_RELU && p.d.act != ACT_RELU6) ||
+      j + 2 == (int)bp.shapes.size() || short_column((long)c->o.batch * p.out.h * p.out.w)) return -1;
+  int reader = -1, uses = 0;
+  for (int k = j + 1; k < (int)bp.ops.size(); ++k) {
+    const OpD& q = bp.ops[k].d;
+    const int nin = q.type == OP_ADD || q.type == OP_MIX ? q.nin : 1;
+    for (int i = 0; i < nin; ++i)
+      if (q.in[i] == j + 1) { ++uses; reader = k; }
+  }
+  if (uses != 1 || bp.ops[reader].d.type != OP_CBA || !bp.ops[reader].dw) return -1;
+  const OpPlan& q = bp.ops[reader];
+  return dw_on_mfma(true, q.d.k, q.d.stride, q.d.pad, q.out.h, q.out.w) ? reader : -1;
 }
 
 template <class T> struct Exec {
@@ -1076,12 +1098,13 @@ template <class T> struct Exec {
     return (op.d.k == 3 || op.d.k == 5 || op.d.k == 7) && op.d.pad == op.d.k / 2 && (op.d.stride == 1 || op.d.stride == 2);
   }
   bool dw_mfma(const OpPlan& op) const { return dw_on_mfma(mfma(), op.d.k, op.d.stride, op.d.pad, op.out.h, op.out.w); }
-  void dw_fwd(const OpPlan& op, const T* x, const T* w, T* y, const float* a, const float* b, int act) {
+  // fold (optional; matrix-core kernels only): x is the producing layer's convolution output, normalised as it is staged
+  void dw_fwd(const OpPlan& op, const T* x, const T* w, T* y, const float* a, const float* b, int act, NormFold fold = NormFold{}) {
     const int N = c->o.batch, ncv = op.cout_p / 8;
     const long nvec = (long)N * op.out.h * op.out.w * ncv;
     // one profile class per kernel template: mfma (matrix cores), slide (registers), plain
     char cls[32];
-    snprintf(cls, sizeof cls, "dw_fwd%s_k%d", dw_mfma(op) ? "_mfma" : dw_slides(op) ? (op.d.stride == 1 ? "_slide" : "_slide_s2") : "", op.d.k);
+    snprintf(cls, sizeof cls, "dw_fwd%s_k%d", dw_mfma(op) ? (fold.mean ? "_mfma_bn" : "_mfma") : dw_slides(op) ? (op.d.stride == 1 ? "_slide" : "_slide_s2") : "", op.d.k);
     ProfScope ps(c, cls, bytes_of(op.in) + bytes_of(op.out), 2.0 * N * op.out.h * op.out.w * op.d.c_out * op.d.k * op.d.k,
                  net, blk, opi);
     const unsigned xe = (unsigned)((size_t)N * op.in.h * op.in.w * op.cin_p);
@@ -1089,7 +1112,8 @@ template <class T> struct Exec {
       if constexpr (sizeof(T) == 2) {
         DwArgs g = dw_args(N, op.out.h, op.out.w, op.cout_p, kDwFwdBlocks);
         g.stream = streams(op.out) ? 1 : 0;
-#define PBD_DWM(K_) launch(c, dw_mfma_kernel<K_, false>, dw_chunks(g) * g.groups, 256, 0, st, (const bf16_t*)x, (const bf16_t*)w, (bf16_t*)y, a, b, act, g)
+#define PBD_DWM(K_) launch(c, fold.mean ? dw_mfma_kernel<K_, false, true> : dw_mfma_kernel<K_, false>, dw_chunks(g) * g.groups, 256, 0, st, \
+    (const bf16_t*)x, (const bf16_t*)w, (bf16_t*)y, a, b, act, g, fold)
         if (op.d.k == 3) PBD_DWM(3); else if (op.d.k == 5) PBD_DWM(5); else PBD_DWM(7);
 #undef PBD_DWM
       }
@@ -1122,7 +1146,7 @@ template <class T> struct Exec {
         DwArgs g = dw_args(N, op.in.h, op.in.w, op.cin_p, kDwFwdBlocks);
         g.stream = streams(op.in) ? 1 : 0;
 #define PBD_DWM(K_) launch(c, dw_mfma_kernel<K_, true>, dw_chunks(g) * g.groups, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)w, (bf16_t*)dx, \
-    (const float*)nullptr, (const float*)nullptr, 0, g)
+    (const float*)nullptr, (const float*)nullptr, 0, g, NormFold{})
         if (op.d.k == 3) PBD_DWM(3); else if (op.d.k == 5) PBD_DWM(5); else PBD_DWM(7);
 #undef PBD_DWM
       }
@@ -1148,17 +1172,20 @@ template <class T> struct Exec {
     if (op.d.k == 3) PBD_DWD(9); else if (op.d.k == 5) PBD_DWD(25); else if (op.d.k == 7) PBD_DWD(49); else PBD_DWD(1);
 #undef PBD_DWD
   }
-  void dw_wgrad(const OpPlan& op, const T* dy, const T* x, float* dw) {
+  void dw_wgrad(const OpPlan& op, const T* dy, const T* x, float* dw, NormFold fold = NormFold{}) {
     const int N = c->o.batch;
     const DwWgradCfg cfg = dw_wgrad_cfg(mfma(), N, op.in.h, op.in.w, op.out.h, op.out.w, op.cout_p, op.d.k, op.d.stride, op.d.pad);
     {
       char cls[32];
-      snprintf(cls, sizeof cls, "dw_wgrad%s_k%d", cfg.mfma ? (op.d.stride == 2 ? "_s2_mfma" : "_mfma") : "", op.d.k <= 3 ? 3 : cfg.mfma ? op.d.k : 7);
+      snprintf(cls, sizeof cls, "dw_wgrad%s_k%d", cfg.mfma ? (op.d.stride == 2 ? "_s2_mfma" : fold.mean ? "_mfma_bn" : "_mfma") : "", op.d.k <= 3 ? 3 : cfg.mfma ? op.d.k : 7);
       ProfScope ps(c, cls, bytes_of(op.in) + bytes_of(op.out),
                    2.0 * N * op.out.h * op.out.w * op.d.c_out * op.d.k * op.d.k, net, blk, opi);
       if (cfg.mfma) {
         if constexpr (sizeof(T) == 2) {
-#define PBD_DWW(K_) launch(c, op.d.stride == 2 ? dw_wgrad_s2_mfma_kernel<K_> : dw_wgrad_mfma_kernel<K_>, cfg.chunks * cfg.m.groups, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)x, parts(op), cfg.m)
+#define PBD_DWW(K_) do { const int n = cfg.chunks * cfg.m.groups; \
+    if (op.d.stride == 2) launch(c, dw_wgrad_s2_mfma_kernel<K_>, n, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)x, parts(op), cfg.m); \
+    else launch(c, fold.mean ? dw_wgrad_mfma_kernel<K_, true> : dw_wgrad_mfma_kernel<K_>, n, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)x, \
+                parts(op), cfg.m, fold); } while (0)
           if (op.d.k == 3) PBD_DWW(3); else if (op.d.k == 5) PBD_DWW(5); else PBD_DWW(7);
 #undef PBD_DWW
         }
@@ -1385,6 +1412,13 @@ template <class T> struct Exec {
     float* grad = wsf(bp.grad);
     const float* master = wsf(bp.master);
     const int nval = (int)bp.shapes.size();
+    // value v is normalised by the depthwise layer that reads it (as it stages the convolution output)
+    auto folds_into = [&](int v) { return v > 0 && depthwise_reader(c, bp, v - 1) >= 0; };
+    auto input_fold = [&](int v) -> NormFold {
+      if (!folds_into(v)) return NormFold{};
+      const OpPlan& p = bp.ops[v - 1];
+      return NormFold{wsf(p.s_mean), wsf(p.s_invstd), master + p.e_gamma, master + p.e_beta, p.d.act};
+    };
     auto mix_state = [&](const OpPlan& op) -> float* { return wsf(bp.mix) + (size_t)op.mix_slot * kMixState; };
 
     // ---- forward ----------------------------------------------------------
@@ -1397,8 +1431,9 @@ template <class T> struct Exec {
       const T* x = value(op.d.in[0]);
       if (op.d.type == OP_CBA) {
         T* y = ws(scr + op.y);
+        const int iv = op.d.in[0];
         const int stat_tiles = op.dw ? 0 : fused_stats_tiles(op);
-        if (op.dw) dw_fwd(op, x, wc + op.e_w, y, nullptr, nullptr, 0);
+        if (op.dw) dw_fwd(op, folds_into(iv) ? ws(scr + bp.ops[iv - 1].y) : x, wc + op.e_w, y, nullptr, nullptr, 0, input_fold(iv));
         else conv_fwd(op, x, wc + op.e_w, y, nullptr, nullptr, 0, nullptr, 0, stat_tiles ? red() : nullptr);
         const long M = (long)N * op.out.h * op.out.w;
         if (short_column(M)) {
@@ -1430,8 +1465,9 @@ template <class T> struct Exec {
           }
           launch(c, bn_finalize_kernel<T>, op.cout_p / kFinalizeChannels, 256, 0, st, 
               part, pivot, chunks, op.cout_p, (double)M, wsf(op.s_mean), wsf(op.s_invstd), wsf(op.s_rmean),
-              wsf(op.s_rvar), c->o.bn_eps, c->o.bn_momentum);
-          if (pool_reader(bp, (int)j, N) < 0) {
+              wsf(op.s_rvar), c->o.bn_eps, c->o.bn_momentum, master + op.e_gamma, master + op.e_beta,
+              folds_into((int)j + 1) ? wsf(op.s_keep) : (float*)nullptr);
+          if (pool_reader(bp, (int)j, N) < 0 && !folds_into((int)j + 1)) {
             const ColGrid ga = col_grid(M, op.cout_p, 8, 4096);   // elementwise pass: many short workgroups
             // a residual add that only reads this layer's output rides along: the normalised tensor itself
             // is never written (the backward pass needs y and the sum, not it)
@@ -1574,7 +1610,7 @@ template <class T> struct Exec {
         }
         const T* x = value(iv);
         if (!arch) {
-          if (op.dw) dw_wgrad(op, dz, x, grad + op.e_w);
+          if (op.dw) dw_wgrad(op, dz, folds_into(iv) ? ws(scr + bp.ops[iv - 1].y) : x, grad + op.e_w, input_fold(iv));
           else conv_wgrad(op, dz, x, grad + op.e_w);
         }
         if (wanted[iv]) {  // A_{i-1} is a constant: no backward-data for the block's first layer
@@ -2199,6 +2235,20 @@ int pbd_read_value(pbd_ctx* c, int32_t b, int32_t v, float* host, size_t n) {
   if (v > 0 && pool_reader(bp, v - 1, c->o.batch) >= 0)
     return fail(c, PBD_ESTATE, "value %d of block %d is not kept: the max-pool that reads it normalises the convolution output itself", v, b);
   const char* dev = v == 0 ? relay_ptr(c, b) : c->ws + bp.scr_off + bp.val[v];
+  if (v > 0 && depthwise_reader(c, bp, v - 1) >= 0) {
+    // the step does not write this tensor (its reader normalises the convolution output itself): formed now, with the
+    // gamma and beta that the step used
+    const OpPlan& p = bp.ops[v - 1];
+    const long M = (long)c->o.batch * s.h * s.w;
+    const ColGrid g = col_grid(M, p.cout_p, 8, 4096);
+    const float* keep = reinterpret_cast<const float*>(c->ws + p.s_keep);
+    bn_apply_kernel<bf16_t><<<dim3(g.slabs, g.chunks), 256, 0, c->stream>>>(
+        reinterpret_cast<const bf16_t*>(c->ws + bp.scr_off + p.y), reinterpret_cast<bf16_t*>(c->ws + bp.scr_off + bp.val[v]),
+        reinterpret_cast<const float*>(c->ws + p.s_mean), reinterpret_cast<const float*>(c->ws + p.s_invstd), keep, keep + p.cout_p, M, p.cout_p,
+        p.d.act, g, (const bf16_t*)nullptr, 0);
+    rc = after_launches(c);
+    if (rc) return rc;
+  }
   return download_act(c, dev, s, host);
 }
 

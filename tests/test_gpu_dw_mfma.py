@@ -46,3 +46,25 @@ def test_every_operation_of_a_small_block(n, h, w, c, k, stride):
     wl = W.Workload("dw_mfma", n, (8, h, w), [t], [b], "bf16", lr=0.05)
     worst = local_parity.run_and_check(wl, n)
     print(", ".join(f"{key} {e:.1e}" for key, e in sorted(worst.items())), flush=True)
+
+
+# (batch, h, w, channels, k, activation): more than 4096 pixels, so the layer in front leaves its normalisation to the
+# depthwise layer, its only reader
+FOLDED = [
+    (5, 33, 31, 40, 3, W.ACT_RELU6),
+    (6, 29, 27, 72, 5, W.ACT_RELU),
+    (17, 17, 16, 24, 7, W.ACT_RELU6),
+    (100, 7, 7, 48, 5, W.ACT_RELU6),
+]
+
+
+@pytest.mark.parametrize("n,h,w,c,k,act", FOLDED)
+def test_normalisation_in_the_staging(n, h, w, c, k, act):
+    t, b = W.Block(), W.Block()
+    t.cba(0, 16, 1, act=W.ACT_NONE)
+    v = b.cba(0, c, 1, act=act)
+    v = b.cba(v, c, k, groups=c, act=W.ACT_RELU6)
+    b.cba(v, 16, 1, act=W.ACT_NONE)
+    wl = W.Workload("dw_folded", n, (8, h, w), [t], [b], "bf16", lr=0.05)
+    worst = local_parity.run_and_check(wl, n)     # (reads the value between the two layers: formed on request, after the update)
+    print(", ".join(f"{key} {e:.1e}" for key, e in sorted(worst.items())), flush=True)
