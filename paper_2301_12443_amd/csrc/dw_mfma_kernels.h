@@ -106,6 +106,7 @@ struct DwArgs {
   int groups, per_block;        // channel groups, tiles per workgroup
   unsigned bytes;               // of the input tensor (and of the output: the shapes agree at stride 1)
   int stream;                   // nontemporal stores
+  float* stats;                 // forward, STATS: [2 x chunks][3][8 ncv] mean, sum of squares about it, pixels
   int P, Q;                     // stride 2: height, width and bytes of dy (tiles are counted over it)
   unsigned dy_bytes;
 };
@@ -117,7 +118,7 @@ struct DwArgs {
 // the vector ALUs: 7 x 7 72 -> 37 us, 5 x 5 40 -> 30, 3 x 3 24.4 -> 24.7 (and MobileNetV2's at batch 33: 11.6 -> 8.3).
 // Slower: the next tile's loads in flight behind the products (K = 7 40 us, K = 5 31: the registers cost a workgroup per
 // compute unit); 64 channels a workgroup (K = 5 31 us, batch 33 12.6 against 11.4).
-template <int K, bool FLIP, bool FOLD = false>
+template <int K, bool FLIP, bool FOLD = false, bool STATS = false>
 __global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
                                                          bf16_t* __restrict__ dst, const float* __restrict__ a,
                                                          const float* __restrict__ b, int act, DwArgs g, NormFold fold) {
@@ -177,6 +178,9 @@ __global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16
   }
   float ea = 1.f, eb = 0.f;
   if (a && cv0 * 8 + ch < g.ncv * 8) { ea = a[cv0 * 8 + ch]; eb = b[cv0 * 8 + ch]; }
+  // STATS: this lane's sums of (y - pivot) and (y - pivot)^2 over the stored outputs of its channel, the pivot being the wave's first
+  // output of the channel (no cancellation when |mean| is far above the deviation)
+  float pivot = 0.f, s1 = 0.f, s2 = 0.f, cnt = 0.f;
 
   for (int tile = tile_begin; tile < tile_end; ++tile) {
     int t_ = tile;
@@ -244,6 +248,26 @@ __global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16
 #pragma unroll
           for (int m = 0; m < 4; ++m) acc[o][q][m] = apply_act(fmaf(acc[o][q][m], ea, eb), act);
     }
+    if (STATS) {
+      if (tile == tile_begin) pivot = as_stored<bf16_t>(__shfl(acc[0][0][0], lane & ~3, 64));
+      const int rows = min(4, g.H - h0 - 4 * strip);     // of this lane's outputs (none or negative: below the image)
+      const int cols = min(8, g.W - w0 - half * 8);      // (the same for the whole wave)
+#pragma unroll
+      for (int o = 0; o < 4; ++o) {
+        const bool row_in = o < rows;
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int m = 0; m < 4; ++m) {
+            const float v = as_stored<bf16_t>(acc[o][q][m]) - pivot;
+            const float d = row_in && q * 4 + m < cols ? v : 0.f;
+            s1 += d;
+            s2 = fmaf(d, d, s2);
+          }
+        __builtin_amdgcn_sched_barrier(0);               // (one row's temporaries at a time)
+      }
+      cnt += (float)(max(rows, 0) * max(cols, 0));
+    }
     __syncthreads();                                     // every wave has read the input tile
     // lanes 4 apart hold neighbouring channels: the even channel packs columns 0 and 1 of both, the odd one columns 2 and 3
     unsigned char* so = smem + (ch >> 1) * 4 + ((ch & 1) * 2 + half * 8) * kDwOutP;
@@ -273,6 +297,21 @@ __global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16
       } else {
         *reinterpret_cast<uint4*>(out) = v;
       }
+    }
+  }
+  if (STATS) {
+#pragma unroll
+    for (int off = 1; off < 4; off <<= 1) {              // the four row strips of a channel
+      s1 += __shfl_xor(s1, off, 64);
+      s2 += __shfl_xor(s2, off, 64);
+      cnt += __shfl_xor(cnt, off, 64);
+    }
+    if (strip == 0 && cv0 * 8 + ch < g.ncv * 8) {
+      const float shift = cnt > 0.f ? s1 / cnt : 0.f;
+      float* p = g.stats + (size_t)((wg / g.groups) * 2 + half) * 3 * (g.ncv * 8) + cv0 * 8 + ch;
+      p[0] = pivot + shift;
+      p[g.ncv * 8] = fmaxf(s2 - s1 * shift, 0.f);
+      p[2 * g.ncv * 8] = cnt;
     }
   }
 }

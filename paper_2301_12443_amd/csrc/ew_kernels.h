@@ -428,7 +428,10 @@ __global__ __launch_bounds__(256) void bn_stats_kernel(const T* __restrict__ y, 
 // chunks l, l+32, ... in order, the 8 lanes of a channel inside one wave are added by a butterfly and
 // the 4 waves in a fixed order (fixed association, independent of scheduling).  Few chunks per lane
 // keep the chain of dependent loads short: these kernels sit between two passes over the tensor.
+// GROUPS: the chunks hold a mean, a sum of squares about it and a number of rows each (part[chunk][3][Cp]) instead of two
+// sums; s1 and s2 come out as the sums of y and y^2, in double.
 constexpr int kFinalizeChannels = 8;
+template <bool GROUPS = false>
 __device__ __forceinline__ void finalize_sums(const float* __restrict__ part, int chunks, int Cp, int c,
                                               int lane, double& s1, double& s2) {
   __shared__ double red1[4][kFinalizeChannels], red2[4][kFinalizeChannels];
@@ -437,8 +440,15 @@ __device__ __forceinline__ void finalize_sums(const float* __restrict__ part, in
   if (c < Cp) {
 #pragma unroll 4
     for (int k = lane; k < chunks; k += 32) {
-      a += (double)part[(long)k * 2 * Cp + c];
-      b += (double)part[(long)k * 2 * Cp + Cp + c];
+      if (GROUPS) {
+        const float* p = part + (long)k * 3 * Cp + c;
+        const double mu = (double)p[0], n = (double)p[2 * Cp];
+        a += n * mu;
+        b += (double)p[Cp] + n * mu * mu;
+      } else {
+        a += (double)part[(long)k * 2 * Cp + c];
+        b += (double)part[(long)k * 2 * Cp + Cp + c];
+      }
     }
   }
 #pragma unroll
@@ -459,13 +469,13 @@ __device__ __forceinline__ void finalize_sums(const float* __restrict__ part, in
 //   rm <- (1-rho) rm + rho mean,  rv <- (1-rho) rv + rho var m/(m-1)
 // keep (optional): [2][Cp] copies of gamma and beta as the step's normalisation uses them (the update overwrites both),
 // for a normalised tensor that is not written and may be asked for later
-template <class T>
+template <class T, bool GROUPS = false>
 __global__ void bn_finalize_kernel(const float* __restrict__ part, const T* __restrict__ y, int chunks,
                                    int Cp, double m, float* mean, float* invstd, float* rmean,
                                    float* rvar, float eps, float rho, const float* gamma, const float* beta, float* keep) {
   const int c = blockIdx.x * kFinalizeChannels + (threadIdx.x & (kFinalizeChannels - 1)), lane = threadIdx.x >> 3;
   double s1, s2;
-  finalize_sums(part, chunks, Cp, c, lane, s1, s2);
+  finalize_sums<GROUPS>(part, chunks, Cp, c, lane, s1, s2);
   if (c >= Cp || lane != 0) return;
   const double shift = s1 / m;
   const double mu = (y ? (double)(float)y[c] : 0.0) + shift;     // y: the pivot row the sums were shifted by, if any

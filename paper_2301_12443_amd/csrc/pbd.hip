@@ -282,6 +282,9 @@ inline DwArgs dw_args(int N, int h, int w, int Cp, int blocks, int tile_h = kDwT
   return g;
 }
 inline int dw_chunks(const DwArgs& g) { return (g.tiles + g.per_block - 1) / g.per_block; }
+constexpr int kDwFwdBlocks = 2048;      // two rounds of the four workgroups that a compute unit holds
+// groups of outputs whose batch-norm statistics the forward kernel delivers: the two column halves of each workgroup
+inline int dw_stat_groups(int N, int h, int w, int Cp) { return 2 * dw_chunks(dw_args(N, h, w, Cp, kDwFwdBlocks)); }
 
 // Partial results of a depthwise backward-weight: row chunks of the column-grid kernel, or workgroups of
 // dw_wgrad_mfma_kernel (three resident workgroups per compute unit; it also wins on 8-wide images, unlike the forward kernel)
@@ -608,6 +611,8 @@ int plan(pbd_ctx* c) {
           const DwWgradCfg gw = dw_wgrad_cfg(bf && !c->o.force_direct, c->o.batch, op.in.h, op.in.w, op.out.h, op.out.w,
                                              op.cout_p, op.d.k, op.d.stride, op.d.pad);
           need_red((size_t)gw.chunks * op.d.k * op.d.k * op.cout_p * 4);
+          if (dw_on_mfma(bf && !c->o.force_direct, op.d.k, op.d.stride, op.d.pad, op.out.h, op.out.w))
+            need_red((size_t)dw_stat_groups(c->o.batch, op.out.h, op.out.w, op.cout_p) * 3 * op.cout_p * 4);
           defer(op, gw.chunks);
         } else if (bf && !c->o.force_direct) {
           const WgradCfg w = op.s2d ? wgrad_cfg(M, op.d.c_out, kS2dK, 16) : wgrad_cfg(M, op.d.c_out, op.d.k * op.d.k * op.cin_p, op.d.k * op.d.k);
@@ -1093,13 +1098,19 @@ template <class T> struct Exec {
   // ---- depthwise ----------------------------------------------------------
   // sliding-window depthwise kernels: odd k in {3,5,7} with "same" padding, 4 outputs per thread
   static constexpr int kDwSlide = 4;
-  static constexpr int kDwFwdBlocks = 2048;      // two rounds of the four workgroups that a compute unit holds
   static bool dw_slides(const OpPlan& op) {
     return (op.d.k == 3 || op.d.k == 5 || op.d.k == 7) && op.d.pad == op.d.k / 2 && (op.d.stride == 1 || op.d.stride == 2);
   }
+  // groups whose statistics the forward kernel leaves of a long column (0: a pass of its own)
+  int dw_stat_rows(const OpPlan& op) const {
+    if (!op.dw || !dw_mfma(op) || short_column((long)c->o.batch * op.out.h * op.out.w)) return 0;
+    return dw_stat_groups(c->o.batch, op.out.h, op.out.w, op.cout_p);
+  }
   bool dw_mfma(const OpPlan& op) const { return dw_on_mfma(mfma(), op.d.k, op.d.stride, op.d.pad, op.out.h, op.out.w); }
-  // fold (optional; matrix-core kernels only): x is the producing layer's convolution output, normalised as it is staged
-  void dw_fwd(const OpPlan& op, const T* x, const T* w, T* y, const float* a, const float* b, int act, NormFold fold = NormFold{}) {
+  // stats (optional; matrix-core kernels only): a mean, a sum of squares about it and a number of pixels per channel and
+  // dw_stat_rows(op) groups of outputs; fold (ditto): x is the producing layer's convolution output, normalised as it is staged
+  void dw_fwd(const OpPlan& op, const T* x, const T* w, T* y, const float* a, const float* b, int act, NormFold fold = NormFold{},
+              float* stats = nullptr) {
     const int N = c->o.batch, ncv = op.cout_p / 8;
     const long nvec = (long)N * op.out.h * op.out.w * ncv;
     // one profile class per kernel template: mfma (matrix cores), slide (registers), plain
@@ -1112,7 +1123,9 @@ template <class T> struct Exec {
       if constexpr (sizeof(T) == 2) {
         DwArgs g = dw_args(N, op.out.h, op.out.w, op.cout_p, kDwFwdBlocks);
         g.stream = streams(op.out) ? 1 : 0;
-#define PBD_DWM(K_) launch(c, fold.mean ? dw_mfma_kernel<K_, false, true> : dw_mfma_kernel<K_, false>, dw_chunks(g) * g.groups, 256, 0, st, \
+        g.stats = stats;
+#define PBD_DWM(K_) launch(c, fold.mean ? dw_mfma_kernel<K_, false, true, true> : stats ? dw_mfma_kernel<K_, false, false, true> : \
+    dw_mfma_kernel<K_, false>, dw_chunks(g) * g.groups, 256, 0, st, \
     (const bf16_t*)x, (const bf16_t*)w, (bf16_t*)y, a, b, act, g, fold)
         if (op.d.k == 3) PBD_DWM(3); else if (op.d.k == 5) PBD_DWM(5); else PBD_DWM(7);
 #undef PBD_DWM
@@ -1433,7 +1446,9 @@ template <class T> struct Exec {
         T* y = ws(scr + op.y);
         const int iv = op.d.in[0];
         const int stat_tiles = op.dw ? 0 : fused_stats_tiles(op);
-        if (op.dw) dw_fwd(op, folds_into(iv) ? ws(scr + bp.ops[iv - 1].y) : x, wc + op.e_w, y, nullptr, nullptr, 0, input_fold(iv));
+        const int dw_rows = dw_stat_rows(op);
+        if (op.dw) dw_fwd(op, folds_into(iv) ? ws(scr + bp.ops[iv - 1].y) : x, wc + op.e_w, y, nullptr, nullptr, 0, input_fold(iv),
+                          dw_rows ? red() : nullptr);
         else conv_fwd(op, x, wc + op.e_w, y, nullptr, nullptr, 0, nullptr, 0, stat_tiles ? red() : nullptr);
         const long M = (long)N * op.out.h * op.out.w;
         if (short_column(M)) {
@@ -1456,6 +1471,8 @@ template <class T> struct Exec {
               launch(c, regroup_partials_kernel, dim3((n + 255) / 256, groups), 256, 0, st, part, out, chunks, n, per);
               part = out; chunks = groups;
             }
+          } else if (dw_rows) {
+            chunks = dw_rows;
           } else {
             const ColGrid g = bn_stats_grid(M, op.cout_p);
             ProfScope ps(c, streams(op.out) ? "bn_stats_nt" : "bn_stats", bytes_of(op.out), 0, net, blk, opi);
@@ -1463,7 +1480,8 @@ template <class T> struct Exec {
                    256 * 16 * sizeof(float), st, y, red(), M, op.cout_p, g);
             chunks = g.chunks;
           }
-          launch(c, bn_finalize_kernel<T>, op.cout_p / kFinalizeChannels, 256, 0, st, 
+          if (dw_rows) pivot = nullptr;
+          launch(c, dw_rows ? bn_finalize_kernel<T, true> : bn_finalize_kernel<T>, op.cout_p / kFinalizeChannels, 256, 0, st, 
               part, pivot, chunks, op.cout_p, (double)M, wsf(op.s_mean), wsf(op.s_invstd), wsf(op.s_rmean),
               wsf(op.s_rvar), c->o.bn_eps, c->o.bn_momentum, master + op.e_gamma, master + op.e_beta,
               folds_into((int)j + 1) ? wsf(op.s_keep) : (float*)nullptr);
