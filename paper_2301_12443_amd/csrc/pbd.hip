@@ -419,7 +419,9 @@ DmaCfg dma_cfg(long M, int NC, int Kred, int CA, int num_cu, int epi) {
     const int bn = kBN[i];
     if (narrow && bn > 128) continue;
     const long tn = (NC + bn - 1) / bn, T = tm * tn;
-    const long slots = (bn <= 128 && T > num_cu ? 2 : 1) * (long)num_cu;       // (narrow tiles: two resident workgroups per unit)
+    // narrow tiles: two resident workgroups per unit, unless the launch does not give every unit one (then each runs alone:
+    // 16660 rows, 384 -> 384, 3 x 3: 396 tiles of 64 columns 55.8 us, 198 of 128 columns 46.8)
+    const long slots = (bn <= 128 && T > num_cu ? 2 : 1) * (long)num_cu;
     const long full = T / slots, r = T % slots;
     double rounds = (double)full;
     if (r) rounds += (full >= 1 && r <= slots / 4) ? 0.66 : 1.0;
@@ -428,9 +430,11 @@ DmaCfg dma_cfg(long M, int NC, int Kred, int CA, int num_cu, int epi) {
   }
   // K step 64 (128-byte rows) for the wide tiles; the narrow ones take 32, whose three stages fit twice in a
   // compute unit's LDS, so that two workgroups hide each other's fill, barriers and store
-  // (256 x 56 x 56 x 64 -> 64, 3 x 3: 129 -> 113 us; 256 -> 96, 1 x 1: 152 -> 124 us)
-  d.BK = CA % 64 == 0 && d.BN >= 192 ? 64 : 32;
+  // (256 x 56 x 56 x 64 -> 64, 3 x 3: 129 -> 113 us; 256 -> 96, 1 x 1: 152 -> 124 us).  A launch of at most one tile per unit
+  // has nobody to hide behind: 128 columns take the longer step then (resnet50_x1.5 block 3 at batch 85 3594 -> 3482 us; with
+  // 96 and 64 columns too the same block stays at 3504 against 3508 and the whole step at batch 64 loses 9.49 -> 9.56 ms).
   const long T = tm * d.tiles_n;
+  d.BK = CA % 64 == 0 && (d.BN >= 192 || (d.BN == 128 && T <= num_cu)) ? 64 : 32;
   if (T < num_cu * 7 / 10) return d;       // (use stays false)
   d.use = true;
   d.big_m = (int)tm;
