@@ -1,213 +1,311 @@
-// float32 dense convolutions on the fp32 matrix cores (v_mfma_f32_32x32x2_f32: fp32 products and fp32 sums, twice the
-// vector ALUs' rate), channel-last tensors.
+// float32 dense convolutions on the fp32 matrix cores, channel-last tensors, bit for bit the results of the direct kernels
+// (conv_direct_* in conv_kernels.h).
 //
-// An MFMA of this shape takes ONE float per lane and operand, lanes 0..31 one reduction element of the 32 rows,
-// lanes 32..63 another, and which reduction element that is does not matter as long as both operands agree.  So
-// both operands go from memory straight to registers, with no LDS staging and no transposition:
-//  * igemm_f32_kernel (forward, backward-data): a lane loads 16 bytes, four consecutive channels of its pixel; half 0 the first
-//    four of a run of eight, half 1 the other four; four MFMAs use them up.
-//  * wgrad_f32_kernel (backward-weight): a lane loads 8 bytes of one pixel, two neighbouring channels; the even
-//    and the odd rows / columns of a 64 x 64 tile are separate MFMAs.
-// 64 cycles per MFMA against 8 to 16 bytes per lane: what a wave loads costs the L1 path a quarter of the time
-// its matrix instructions take.  What bounds the small layers this precision is used on is latency, so the
-// reduction is cut over the eight waves of a workgroup, each with a batch of loads in flight while the one before
-// is multiplied, and the partial tiles meet in LDS in a fixed order (bit-reproducible).
-//  Against one thread per result (conv_direct_*): VGG-16 at 64 x 32 x 32, forward 2516 -> 27 us a layer (72 TFLOP/s on
-// the 64-wide tiles), backward-weight 3968 -> 9.6, backward-data 97 -> 9.7; its whole step 90.8 -> 1.53 ms, the
-// four-layer network at 8 x 32 x 32 1943 -> 258 us.  Each result is also closer to the exact sum (eight shorter
-// chains instead of one): relative error of a 64-channel 3 x 3 layer 4.1e-7 -> 1.6e-7.
+// v_mfma_f32_32x32x2_f32 and v_mfma_f32_16x16x4_f32 add their two / four products to the accumulator one after the other, in
+// the order of the lanes that hold them, as fused multiply-adds that round each time, subnormals included (checked against
+// fmaf over chains of up to 4096).  One result's chain therefore stays ONE chain in the order of the direct kernels: no cut of
+// the reduction over waves or workgroups, and the lanes 0..31 / 32..63 (or the four groups of sixteen) of an operand hold
+// CONSECUTIVE reduction elements.  A tap outside the image, which the direct kernels leave out, is a product with zero and
+// changes no chain of finite numbers; a result that comes out as NaN is formed once more the direct way, so an infinity or NaN in a
+// weight that the image's edge never meets stays there.
+//   Why the order matters: a rectifier's mask, and everything behind it, hangs on the last bit of some pre-activations, so another
+// order of summation, closer to the exact sum or not, moves single gradients by percents and a few steps' results with them.
+//
+// An MFMA takes one float per lane and operand: 64 cycles for 32 x 32 results and two reduction elements, 32 cycles for 16 x 16 and
+// four.  Both run at the same rate, but a chain of n elements takes 32 n cycles on the one and 8 n on the other, and the
+// small layers this precision is used on are bound by the length of the chain.  So the 16-wide tiles are taken wherever the
+// 32-wide ones would not give every compute unit a workgroup.
+//
+// Measured, VGG-16 at 64 x 32 x 32: against one thread per result the whole step takes 1.77 ms instead of 91.1, the four-layer
+// network's at 8 x 32 x 32 0.24 instead of 1.94 ms.  Forward 64 -> 64, 3 x 3, 65536 pixels 57 us (84 TFLOP/s), 512 -> 512 at 1024
+// pixels 81 us (60), the weight gradient of a 1 x 1 layer over 65536 pixels 440 us.  Cutting a reduction over eight waves and
+// adding the parts (other bits) took 1.50 ms a step.
 #pragma once
 #include "conv_kernels.h"
 
 namespace pbd {
 
-constexpr int kF32Threads = 512;                  // eight waves
-constexpr int kF32Pitch = 36;                     // floats per staged row of 32: 16-byte accesses of neighbouring rows spread over the banks
-
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f32x4 buffer_load_f4(__amdgpu_buffer_rsrc_t r, unsigned byte_off) {
   return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)byte_off, 0, 0));
 }
-__device__ __forceinline__ f32x2 buffer_load_f2(__amdgpu_buffer_rsrc_t r, unsigned byte_off) {
-  return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)byte_off, 0, 0));
+
+// exchange of lane rows of two registers: odd rows of 16 of `a` with even rows of `b`; lanes 32..63 of `a` with 0..31 of `b`
+__device__ __forceinline__ void swap_rows16(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
 }
-__device__ __forceinline__ float buffer_load_f1(__amdgpu_buffer_rsrc_t r, unsigned byte_off) {
-  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)byte_off, 0, 0));
+__device__ __forceinline__ void swap_rows32(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
 }
+
+template <int TILE> struct F32Tile;
+template <> struct F32Tile<32> {
+  typedef f32x16 Acc;
+  static constexpr int GROUPS = 2, VALUES = 16;       // reduction elements per MFMA, results per lane
+  static constexpr int COLP = 64;                     // floats per reduction element staged [element][channel]
+  // tile row of a lane's four results 4 q .. 4 q + 3
+  static __device__ __forceinline__ int row(int q, int group) { return 8 * q + 4 * group; }
+  static __device__ __forceinline__ Acc mfma(float a, float b, Acc c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+  // v[e] of lane group g = element 4 g + e of a run of eight -> element 2 e + g
+  static __device__ __forceinline__ void in_order(float (&v)[4]) {
+    swap_rows32(v[0], v[1]);                          // 0 1 | 4 5
+    swap_rows32(v[2], v[3]);                          // 2 3 | 6 7
+    const float t = v[1]; v[1] = v[2]; v[2] = t;
+  }
+};
+template <> struct F32Tile<16> {
+  typedef f32x4 Acc;
+  static constexpr int GROUPS = 4, VALUES = 4;
+  static constexpr int COLP = 48;                     // (two elements that a half wave reads lie on different banks)
+  static __device__ __forceinline__ int row(int, int group) { return 4 * group; }
+  static __device__ __forceinline__ Acc mfma(float a, float b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+  // element 4 g + e of a run of sixteen -> element 4 e + g: a 4 x 4 transposition
+  static __device__ __forceinline__ void in_order(float (&v)[4]) {
+    swap_rows16(v[0], v[1]); swap_rows16(v[2], v[3]);
+    swap_rows32(v[0], v[2]); swap_rows32(v[1], v[3]);
+  }
+};
+
+// The product both kernels share.  A workgroup of four waves owns EDGE x EDGE = 2 x 2 tiles of Out[p][q] = sum_e P[p][e] Q[q][e] and
+// their whole reduction, in stages of BK elements (sixteen MFMAs).  Two passes of all threads load a stage of an operand, four
+// floats each, into registers and from there into LDS:
+//  * ROWS: the operand's memory is contiguous along the reduction; staged [p][element], ROWP = BK + 4 floats a row, a lane
+//    reads four elements of its row at once and neighbouring lane groups exchange them;
+//  * else contiguous along p (or q): staged [element][p], a lane reads one element at a time.
+// While stage t is multiplied from registers, stage t + 1 goes from LDS to the other register set, stage t + 2 from
+// registers to LDS, and t + 3 to t + 6 are on their way from memory.  Sixteen dependent 16-wide products take 512 cycles, a stage of
+// the 65536-pixel weight gradient about 1030: the barrier, the LDS reads behind it and the products' own latency are what is left
+// (1570 before the staging was dealt out between the products and the waits counted loads exactly).
+template <int TILE> struct F32Gemm {
+  typedef F32Tile<TILE> F;
+  static constexpr int EDGE = 2 * TILE, BK = 16 * F::GROUPS, ROWP = BK + 4, COLP = F::COLP;    // 32 and 64, 64 and 32
+  template <bool ROWS> static constexpr int floats = ROWS ? EDGE * ROWP : BK * COLP;             // per stage in LDS
+  // what thread tid stages in pass i: row / element, and the first of its four elements / rows
+  static constexpr int PER = 256 / (BK / 4), PER_COL = 256 / (EDGE / 4);
+  template <bool ROWS> static __device__ __forceinline__ int major(int tid, int i) { return ROWS ? tid / (BK / 4) + i * PER : tid / (EDGE / 4) + i * PER_COL; }
+  template <bool ROWS> static __device__ __forceinline__ int minor(int tid) { return (ROWS ? tid % (BK / 4) : tid % (EDGE / 4)) * 4; }
+  static_assert(2 * PER == EDGE && 2 * PER_COL == BK, "two passes stage a stage");
+
+  template <bool ROWS> static __device__ __forceinline__ void put(float* buf, f32x4 v, int i, int tid) {
+    *reinterpret_cast<f32x4*>(buf + major<ROWS>(tid, i) * (ROWS ? ROWP : COLP) + minor<ROWS>(tid)) = v;
+  }
+  // operands 4 v .. 4 v + 3 of the lane whose tile row is `at`
+  template <bool ROWS> static __device__ __forceinline__ void get(const float* buf, float (&f)[4], int v, int at, int group) {
+    if constexpr (ROWS) {
+      const f32x4 q = *reinterpret_cast<const f32x4*>(buf + at * ROWP + v * 4 * F::GROUPS + 4 * group);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f[e] = q[e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f[e] = buf[((4 * v + e) * F::GROUPS + group) * COLP + at];
+    }
+  }
+  // load_p(i), load_q(i): pass i = 0, 1 of the next stage of an operand
+  template <bool P_ROWS, bool Q_ROWS, class LP, class LQ>
+  static __device__ __forceinline__ void run(LP&& load_p, LQ&& load_q, typename F::Acc& acc, int stages, int tid) {
+    __shared__ __attribute__((aligned(16))) float sp[2][floats<P_ROWS>], sq[2][floats<Q_ROWS>];
+    const int lane = tid & 63, group = lane / TILE, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int at_p = (wave >> 1) * TILE + lane % TILE, at_q = (wave & 1) * TILE + lane % TILE;
+    f32x4 gp[4][2], gq[4][2];                          // stage n waits in set n % 4 and goes through LDS buffer n % 2
+    float fp[2][4][4], fq[2][4][4];
+    // quarter v of a stage's staging: one pass of one operand.  (No branch around a load, and the order pinned: the compiler
+    // then knows how many loads are younger than the one it waits for.)
+    auto load = [&](auto set, int v) {
+      constexpr int S_ = decltype(set)::value;
+      if (v < 2) gp[S_][v] = load_p(v); else gq[S_][v - 2] = load_q(v - 2);
+    };
+    auto store = [&](auto set, int v) {
+      constexpr int S_ = decltype(set)::value;
+      if (v < 2) put<P_ROWS>(sp[S_ & 1], gp[S_][v], v, tid); else put<Q_ROWS>(sq[S_ & 1], gq[S_][v - 2], v - 2, tid);
+    };
+    auto order = [&](int set, int v) {
+      if (P_ROWS) F::in_order(fp[set][v]);
+      if (Q_ROWS) F::in_order(fq[set][v]);
+    };
+    auto turn = [&](auto set) {
+      constexpr int S_ = decltype(set)::value, CUR = S_ & 1, NXT = CUR ^ 1;
+      const std::integral_constant<int, (S_ + 2) & 3> ahead{};
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        get<P_ROWS>(sp[NXT], fp[NXT][v], v, at_p, group);
+        get<Q_ROWS>(sq[NXT], fq[NXT][v], v, at_q, group);
+        order(v < 3 ? CUR : NXT, (v + 1) & 3);         // (what the next four products read)
+        store(ahead, v);
+        load(ahead, v);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = F::mfma(fp[CUR][v][e], fq[CUR][v][e], acc);
+        // addresses and LDS traffic of the coming stages issue between the products, which wait for each other
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                              // an MFMA
+          __builtin_amdgcn_sched_group_barrier(0x100, P_ROWS || Q_ROWS ? 2 : 1, 0);       // LDS reads
+          __builtin_amdgcn_sched_group_barrier(0x006, 12, 0);                             // vector and scalar ALU
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __syncthreads();
+    };
+    using S0 = std::integral_constant<int, 0>;
+    using S1 = std::integral_constant<int, 1>;
+    using S2 = std::integral_constant<int, 2>;
+    using S3 = std::integral_constant<int, 3>;
+    auto load_all = [&](auto set) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) load(set, v);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto store_all = [&](auto set) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) store(set, v);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    load_all(S0{}); load_all(S1{}); load_all(S2{}); load_all(S3{});
+    store_all(S0{});
+    load_all(S0{});
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < 4; ++v) { get<P_ROWS>(sp[0], fp[0][v], v, at_p, group); get<Q_ROWS>(sq[0], fq[0][v], v, at_q, group); }
+    order(0, 0);
+    store_all(S1{});
+    load_all(S1{});
+    __syncthreads();
+    // (whole rounds of the four sets in a loop without exits; what is staged behind the last stage, zeros, is not multiplied)
+    for (int t = 0; t < stages >> 2; ++t) { turn(S0{}); turn(S1{}); turn(S2{}); turn(S3{}); }
+    if (stages & 3) {
+      turn(S0{});
+      if ((stages & 3) > 1) turn(S1{});
+      if ((stages & 3) > 2) turn(S2{});
+    }
+  }
+};
 
 // Same view as igemm_kernel: Out[m][j] = sum_kk Agather(m, kk) * W(j, kk), rows m = pixels of an [N][HO][WO] grid,
 // kk = (r*S + s)*CA + c.  MODE 0 reads the weights as they lie, [NC][R][S][CA]; MODE 1 reads the forward filter
-// [CA][R][S][NC] (the 32 columns of a tile are then contiguous), so there is no transposed copy to keep.
-//   A wave owns MT x NT tiles of 32 pixels x 32 channels; of the eight waves KW share a tile and cut its reduction,
-// the others take the next rows.  The workgroup's tile is (8 / KW) * 32 * MT rows x 32 * NT columns.
-struct F32Args {
-  IgemmArgs g;
-  int kw_log2;            // 1, 2, 4 or 8 waves per tile
-  int accumulate;         // Out += (backward-data into a value that already has a gradient)
-};
-
-template <int MODE, int MT, int NT>
-__global__ __launch_bounds__(kF32Threads) void igemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ Bw,
-                                                               float* __restrict__ Out, const float* __restrict__ ep_a,
-                                                               const float* __restrict__ ep_b, int act, F32Args fa) {
-  // reduction runs of 8 channels per batch: two batches in registers, the next one in flight
-  constexpr int UNR = MT * NT == 1 ? 4 : 2;
-  const IgemmArgs& g = fa.g;
-  __shared__ __attribute__((aligned(16))) float part[8][32 * kF32Pitch];
-  const int tid = threadIdx.x, lane = tid & 63, row = lane & 31, half = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int kw = 1 << fa.kw_log2, ks = wave & (kw - 1), mw = wave >> fa.kw_log2, rows_wg = (8 >> fa.kw_log2) * 32 * MT;
+// [CA][R][S][NC], so there is no transposed copy to keep.
+template <int MODE, int TILE>
+__global__ __launch_bounds__(256) void igemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ Bw,
+                                                       float* Out, const float* __restrict__ ep_a,
+                                                       const float* __restrict__ ep_b, int act, int accumulate, IgemmArgs g) {
+  typedef F32Tile<TILE> F;
+  typedef F32Gemm<TILE> G;
+  constexpr bool W_ROWS = MODE == 0;
+  const int tid = threadIdx.x, lane = tid & 63, group = lane / TILE, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tile = xcd_contiguous(blockIdx.x, g.tiles_m * g.tiles_n);
-  const int m0 = tile / g.tiles_n * rows_wg, n0 = tile % g.tiles_n * 32 * NT;
+  const int m0 = tile / g.tiles_n * G::EDGE, n0 = tile % g.tiles_n * G::EDGE;
   const int sh = g.stride == 2 ? 1 : 0, smask = g.stride - 1;
+  const __amdgpu_buffer_rsrc_t ra = tensor_rsrc(A, g.a_bytes), rb = tensor_rsrc(Bw, g.b_bytes);
+  const int RS = g.R * g.S;
 
-  int rbase[MT], rh[MT], rw[MT];
+  // a thread's reduction element kk = tap * CA + c, moved on by a stage at a time (CA % 8 == 0: its four elements share a tap)
+  struct Tap { int kk, c, r, s; };
+  auto tap_of = [&](int kk) {
+    const int rs = kk / g.CA;
+    return Tap{kk, kk - rs * g.CA, rs / g.S, rs % g.S};
+  };
+  const int dtap = G::BK / g.CA, dc = G::BK % g.CA, dr = dtap / g.S, ds = dtap % g.S;   // BK in the mixed radix of (r, s, c)
+  auto next_stage = [&](Tap& t) {
+    t.kk += G::BK;
+    const int c = t.c + dc, c1 = c >= g.CA ? 1 : 0, s = t.s + ds + c1, c2 = s >= g.S ? 1 : 0;
+    t.c = c - (c1 ? g.CA : 0);
+    t.s = s - (c2 ? g.S : 0);
+    t.r += dr + c2;
+  };
+  // pixels: two rows of four elements a stage
+  Tap ta = tap_of(G::template minor<true>(tid));
+  int rbase[2], rh[2], rw[2];
 #pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    const int m = m0 + (mw * MT + i) * 32 + row;
-    const int mm = m < g.M ? m : 0;
+  for (int i = 0; i < 2; ++i) {
+    const int m = m0 + G::template major<true>(tid, i), mm = m < g.M ? m : 0;
     const int b_ = mm % g.WO, t = mm / g.WO, a_ = t % g.HO;
     rbase[i] = (t / g.HO) * g.HA * g.WA;
     rh[i] = MODE == 0 ? a_ * g.stride - g.pad : a_ + g.pad;
     rw[i] = MODE == 0 ? b_ * g.stride - g.pad : b_ + g.pad;
-    if (m >= g.M) rh[i] = -(1 << 24);             // (fails every range test)
+    if (m >= g.M) rh[i] = -(1 << 24);                  // (fails every range test)
   }
-  const __amdgpu_buffer_rsrc_t ra = tensor_rsrc(A, g.a_bytes), rb = tensor_rsrc(Bw, g.b_bytes);
-  const int RS = g.R * g.S;
-  unsigned bbase[NT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    const int col = n0 + j * 32 + row;
-    bbase[j] = col >= g.NC ? kOutOfRange : (unsigned)(MODE == 0 ? col * g.Kred + 4 * half : 4 * half * RS * g.NC + col) * 4u;
-  }
-
-  // this wave's runs of 8: [run0, run1) of Kred / 8; the tap of a run is the same for all lanes
-  const int runs = g.Kred >> 3, per = (runs + kw - 1) >> fa.kw_log2;
-  const int run0 = min(runs, ks * per), run1 = min(runs, run0 + per);
-  int r, s, c;
-  {
-    const int kk = run0 * 8, rs = kk / g.CA;
-    c = kk - rs * g.CA; r = rs / g.S; s = rs - r * g.S;
-  }
-  f32x4 av[2][UNR][MT], bv[2][UNR][NT];
-  int at = run0;
-  auto load = [&](auto stage) {
-    constexpr int S_ = decltype(stage)::value;
-#pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      const bool live = at < run1;
-#pragma unroll
-      for (int i = 0; i < MT; ++i) {
-        int h = MODE == 0 ? rh[i] + r : rh[i] - r, w = MODE == 0 ? rw[i] + s : rw[i] - s;
-        bool ok = live;
-        if (MODE == 1) { ok = ok && ((h | w) & smask) == 0; h >>= sh; w >>= sh; }
-        ok = ok && (unsigned)h < (unsigned)g.HA && (unsigned)w < (unsigned)g.WA;
-        const unsigned off = (unsigned)((rbase[i] + h * g.WA + w) * g.CA + c + 4 * half) * 4u;
-        av[S_][u][i] = buffer_load_f4(ra, ok ? off : kOutOfRange);
-      }
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        if (MODE == 0) {
-          bv[S_][u][j] = buffer_load_f4(rb, live ? bbase[j] + (unsigned)at * 32u : kOutOfRange);
-        } else {
-          // channels c .. c + 3 (+ 4 in half 1) of the reduction: one row of the forward filter each
-          const unsigned step = (unsigned)(RS * g.NC) * 4u;
-          const unsigned off = live ? bbase[j] + (unsigned)((c * RS + r * g.S + s) * g.NC) * 4u : kOutOfRange;
-          bv[S_][u][j].x = buffer_load_f1(rb, off);
-          bv[S_][u][j].y = buffer_load_f1(rb, live ? off + step : kOutOfRange);
-          bv[S_][u][j].z = buffer_load_f1(rb, live ? off + 2 * step : kOutOfRange);
-          bv[S_][u][j].w = buffer_load_f1(rb, live ? off + 3 * step : kOutOfRange);
-        }
-      }
-      ++at;
-      c += 8;
-      if (c >= g.CA) { c = 0; if (++s == g.S) { s = 0; ++r; } }
-    }
+  auto load_pixels = [&](int i) {
+    int h = MODE == 0 ? rh[i] + ta.r : rh[i] - ta.r, w = MODE == 0 ? rw[i] + ta.s : rw[i] - ta.s;
+    bool ok = ta.kk < g.Kred;
+    if (MODE == 1) { ok &= ((h | w) & smask) == 0; h >>= sh; w >>= sh; }
+    ok &= ((unsigned)h < (unsigned)g.HA) & ((unsigned)w < (unsigned)g.WA);
+    const unsigned off = (unsigned)((rbase[i] + h * g.WA + w) * g.CA + ta.c) * 4u;
+    if (i == 1) next_stage(ta);
+    return buffer_load_f4(ra, ok ? off : kOutOfRange);
   };
-  f32x16 acc[MT][NT];
+  // weights: MODE 0 two channels' four elements, MODE 1 two elements' four channels (NC % 8 == 0: in or out as a whole)
+  Tap tb[2];
+  int bat[2];
 #pragma unroll
-  for (int i = 0; i < MT; ++i)
+  for (int i = 0; i < 2; ++i) {
+    tb[i] = tap_of(MODE == 0 ? G::template minor<true>(tid) : G::template major<false>(tid, i));
+    bat[i] = n0 + (MODE == 0 ? G::template major<true>(tid, i) : G::template minor<false>(tid));
+  }
+  auto load_weights = [&](int i) {
+    const bool ok = (bat[i] < g.NC) & (tb[i].kk < g.Kred);
+    const unsigned off = MODE == 0 ? (unsigned)(bat[i] * g.Kred + tb[i].kk) * 4u
+                                   : (unsigned)((tb[i].c * RS + tb[i].r * g.S + tb[i].s) * g.NC + bat[i]) * 4u;
+    if (MODE == 0) tb[i].kk += G::BK; else next_stage(tb[i]);
+    return buffer_load_f4(rb, ok ? off : kOutOfRange);
+  };
+
+  // a lane holds runs of four consecutive channels of one pixel (NC % 8 == 0: in or out as a whole)
+  const int m = m0 + (wave & 1) * TILE + lane % TILE, col0 = n0 + (wave >> 1) * TILE;
+  typename F::Acc acc;
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
+  for (int q = 0; q < F::VALUES / 4; ++q) {
+    // the direct kernel's chain starts from the value that is added to
+    const int col = col0 + F::row(q, group);
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (accumulate && m < g.M && col < g.NC) o = *reinterpret_cast<const float4*>(Out + (size_t)m * g.NC + col);
+    acc[4 * q] = o.x; acc[4 * q + 1] = o.y; acc[4 * q + 2] = o.z; acc[4 * q + 3] = o.w;
+  }
+  G::template run<W_ROWS, true>(load_weights, load_pixels, acc, (g.Kred + G::BK - 1) / G::BK, tid);
+
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  auto multiply = [&](auto stage) {
-    constexpr int S_ = decltype(stage)::value;
+  for (int q = 0; q < F::VALUES / 4; ++q) {
+    const int col = col0 + F::row(q, group);
+    if (m >= g.M || col >= g.NC) continue;
+    float4* dst = reinterpret_cast<float4*>(Out + (size_t)m * g.NC + col);
+    float o[4];
 #pragma unroll
-    for (int u = 0; u < UNR; ++u)
+    for (int e = 0; e < 4; ++e) o[e] = acc[4 * q + e];
+    if (o[0] != o[0] || o[1] != o[1] || o[2] != o[2] || o[3] != o[3]) {
+      const int b_ = m % g.WO, t = m / g.WO, a_ = t % g.HO, n = t / g.HO;
+      const ConvGeom d = MODE == 0 ? ConvGeom{g.N, g.HA, g.WA, g.CA, g.HO, g.WO, g.NC, g.R, g.S, g.stride, g.pad}
+                                   : ConvGeom{g.N, g.HO, g.WO, g.NC, g.HA, g.WA, g.CA, g.R, g.S, g.stride, g.pad};
+      const float4 old = accumulate ? *dst : make_float4(0.f, 0.f, 0.f, 0.f);
+      const float init[4] = {old.x, old.y, old.z, old.w};
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-          for (int j = 0; j < NT; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[S_][u][j][e], av[S_][u][i][e], acc[i][j], 0, 0, 0);
-  };
-  using S0 = std::integral_constant<int, 0>;
-  using S1 = std::integral_constant<int, 1>;
-  const int batches = (run1 - run0 + UNR - 1) / UNR;
-  if (batches > 0) load(S0{});
-  for (int t = 0; t < batches; t += 2) {
-    if (t + 1 < batches) load(S1{});
-    __builtin_amdgcn_sched_barrier(0);            // (the loads above are in flight while the batch before is multiplied)
-    multiply(S0{});
-    if (t + 1 >= batches) break;
-    if (t + 2 < batches) load(S0{});
-    __builtin_amdgcn_sched_barrier(0);
-    multiply(S1{});
-  }
-
-  // a tile at a time: the KW partial tiles side by side in LDS, added in wave order, stored as whole rows
-#pragma unroll
-  for (int i = 0; i < MT; ++i)
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      if (i + j > 0) __syncthreads();
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        *reinterpret_cast<float4*>(&part[wave][row * kF32Pitch + 8 * q + 4 * half]) =
-            make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-      __syncthreads();
-      for (int t = tid; t < (8 >> fa.kw_log2) * 256; t += kF32Threads) {
-        const int w0 = t >> 8, px = (t >> 3) & 31, ch = (t & 7) * 4;
-        const int m = m0 + (w0 * MT + i) * 32 + px, col = n0 + j * 32 + ch;
-        if (m >= g.M || col >= g.NC) continue;    // NC % 8 == 0: a group of four is in or out as a whole
-        float o[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int k = 0; k < kw; ++k) {
-          const float4 p = *reinterpret_cast<const float4*>(&part[(w0 << fa.kw_log2) + k][px * kF32Pitch + ch]);
-          o[0] += p.x; o[1] += p.y; o[2] += p.z; o[3] += p.w;
-        }
-        float4* dst = reinterpret_cast<float4*>(Out + (size_t)m * g.NC + col);
-        if (ep_a) {
-          const float4 ea = *reinterpret_cast<const float4*>(ep_a + col), eb = *reinterpret_cast<const float4*>(ep_b + col);
-          o[0] = apply_act(fmaf(o[0], ea.x, eb.x), act); o[1] = apply_act(fmaf(o[1], ea.y, eb.y), act);
-          o[2] = apply_act(fmaf(o[2], ea.z, eb.z), act); o[3] = apply_act(fmaf(o[3], ea.w, eb.w), act);
-        } else if (fa.accumulate) {
-          const float4 p = *dst;
-          o[0] += p.x; o[1] += p.y; o[2] += p.z; o[3] += p.w;
-        }
-        *dst = make_float4(o[0], o[1], o[2], o[3]);
-      }
+        o[e] = MODE == 0 ? conv_direct_fwd_at(A, Bw, d, n, a_, b_, col + e) : conv_direct_dgrad_at(A, Bw, d, n, a_, b_, col + e, init[e]);
     }
+    if (MODE == 0) {
+      if (ep_a) {
+        const float4 ea = *reinterpret_cast<const float4*>(ep_a + col), eb = *reinterpret_cast<const float4*>(ep_b + col);
+        o[0] = fmaf(o[0], ea.x, eb.x); o[1] = fmaf(o[1], ea.y, eb.y); o[2] = fmaf(o[2], ea.z, eb.z); o[3] = fmaf(o[3], ea.w, eb.w);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = apply_act(o[e], act);
+    }
+    *dst = make_float4(o[0], o[1], o[2], o[3]);
+  }
 }
 
-// dW[k][j] = sum over pixels of dy[m][k] * xcol[m][j]: 64 x 64 tiles, the pixels of a split dealt to the eight waves
-// in turns of 2 * UNR, partial tiles added in LDS in wave order; `part` gets one [K][J] matrix per split.
-template <int UNR>
-__global__ __launch_bounds__(kF32Threads) void wgrad_f32_kernel(const float* __restrict__ dy, const float* __restrict__ x,
-                                                               float* __restrict__ part, WgradTrArgs g) {
-  constexpr int PITCH = 68;
-  __shared__ __attribute__((aligned(16))) float red[8][32 * PITCH];
-  const int tid = threadIdx.x, lane = tid & 63, row = lane & 31, half = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int tile = xcd_contiguous(blockIdx.x, g.tiles_k * g.tiles_j * g.splits);
-  const int slice = tile / (g.tiles_k * g.tiles_j);
-  const int k0 = ((tile / g.tiles_j) % g.tiles_k) * 64, j0 = (tile % g.tiles_j) * 64;
-  const int mbeg = slice * g.pix_per_split, mend = min(g.M, mbeg + g.pix_per_split);
+// dW[k][j] = sum over pixels of dy[m][k] * xcol[m][j], in pixel order (so bound by the chain on layers of many pixels and few
+// weights: 16 cycles a pixel, 8 of them the products').  Both operands are contiguous along their channels; a gathered pixel is addressed once per
+// four channels of a tap.
+template <int TILE>
+__global__ __launch_bounds__(256) void wgrad_f32_kernel(const float* __restrict__ dy, const float* __restrict__ x,
+                                                       float* __restrict__ dw, WgradTrArgs g) {
+  typedef F32Tile<TILE> F;
+  typedef F32Gemm<TILE> G;
+  const int tid = threadIdx.x, lane = tid & 63, group = lane / TILE, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tile = xcd_contiguous(blockIdx.x, g.tiles_k * g.tiles_j);
+  const int k0 = (tile / g.tiles_j) * G::EDGE, j0 = (tile % g.tiles_j) * G::EDGE;
   const __amdgpu_buffer_rsrc_t rd = tensor_rsrc(dy, g.dy_bytes), rx = tensor_rsrc(x, g.x_bytes);
 
-  const int kcol = k0 + 2 * row, jcol = j0 + 2 * row;             // (both even: a pair is in or out as a whole)
+  const int kcol = k0 + G::template minor<false>(tid), jcol = j0 + G::template minor<false>(tid);   // (K, J, C are multiples of 8: four are in or out)
   const bool k_ok = kcol < g.K, j_ok = jcol < g.J;
   int br, bs, bc;
   {
@@ -217,84 +315,56 @@ __global__ __launch_bounds__(kF32Threads) void wgrad_f32_kernel(const float* __r
     bs = rs - br * g.S;
   }
   br -= g.pad; bs -= g.pad;
-  // pixel of load u: mbeg + (turn * 8 + wave) * 2 UNR + 2 u + half, advanced by 16 UNR pixels a turn without divisions
-  int pm[UNR], pn[UNR], pp[UNR], pq[UNR];
+  int dm[2], pm[2], pn[2], pp[2], pq[2];               // the two pixels of the next stage: of dy, of x
 #pragma unroll
-  for (int u = 0; u < UNR; ++u) {
-    pm[u] = mbeg + wave * 2 * UNR + 2 * u + half;
-    pq[u] = pm[u] % g.Q;
-    const int t = pm[u] / g.Q;
-    pp[u] = t % g.P;
-    pn[u] = t / g.P;
+  for (int i = 0; i < 2; ++i) {
+    dm[i] = pm[i] = G::template major<false>(tid, i);
+    pq[i] = pm[i] % g.Q;
+    const int t = pm[i] / g.Q;
+    pp[i] = t % g.P;
+    pn[i] = t / g.P;
   }
-  f32x2 dv[2][UNR], xv[2][UNR];
-  auto load = [&](auto stage) {
-    constexpr int S_ = decltype(stage)::value;
-#pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      const bool live = pm[u] < mend;
-      const int h = pp[u] * g.stride + br, w = pq[u] * g.stride + bs;
-      const bool ok = live && j_ok && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;
-      dv[S_][u] = buffer_load_f2(rd, live && k_ok ? (unsigned)(pm[u] * g.K + kcol) * 4u : kOutOfRange);
-      xv[S_][u] = buffer_load_f2(rx, ok ? (unsigned)(((pn[u] * g.H + h) * g.W + w) * g.C + bc) * 4u : kOutOfRange);
-      pm[u] += 16 * UNR;
-      int q = pq[u] + g.dq;
-      const int c1 = q >= g.Q ? 1 : 0;
-      pq[u] = q - (c1 ? g.Q : 0);
-      int p = pp[u] + g.dp + c1;
-      const int c2 = p >= g.P ? 1 : 0;
-      pp[u] = p - (c2 ? g.P : 0);
-      pn[u] += g.dn + c2;
-    }
+  auto load_dy = [&](int i) {
+    const unsigned off = (unsigned)(dm[i] * g.K + kcol) * 4u;
+    const bool ok = (dm[i] < g.M) & k_ok;
+    dm[i] += G::BK;
+    return buffer_load_f4(rd, ok ? off : kOutOfRange);
   };
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-  auto multiply = [&](auto stage) {
-    constexpr int S_ = decltype(stage)::value;
-#pragma unroll
-    for (int u = 0; u < UNR; ++u)
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(dv[S_][u][a], xv[S_][u][b], acc[a][b], 0, 0, 0);
+  auto load_x = [&](int i) {
+    const int h = pp[i] * g.stride + br, w = pq[i] * g.stride + bs;
+    const bool ok = (pm[i] < g.M) & j_ok & ((unsigned)h < (unsigned)g.H) & ((unsigned)w < (unsigned)g.W);
+    const unsigned off = (unsigned)(((pn[i] * g.H + h) * g.W + w) * g.C + bc) * 4u;
+    pm[i] += G::BK;
+    int q = pq[i] + g.dq;
+    const int c1 = q >= g.Q ? 1 : 0;
+    pq[i] = q - (c1 ? g.Q : 0);
+    int p = pp[i] + g.dp + c1;
+    const int c2 = p >= g.P ? 1 : 0;
+    pp[i] = p - (c2 ? g.P : 0);
+    pn[i] += g.dn + c2;
+    return buffer_load_f4(rx, ok ? off : kOutOfRange);
   };
-  using S0 = std::integral_constant<int, 0>;
-  using S1 = std::integral_constant<int, 1>;
-  const int turns = (mend - mbeg + 16 * UNR - 1) / (16 * UNR);
-  load(S0{});
-  for (int t = 0; t < turns; t += 2) {
-    if (t + 1 < turns) load(S1{});
-    __builtin_amdgcn_sched_barrier(0);
-    multiply(S0{});
-    if (t + 1 >= turns) break;
-    if (t + 2 < turns) load(S0{});
-    __builtin_amdgcn_sched_barrier(0);
-    multiply(S1{});
-  }
-  // even channels of the 64, then the odd ones: rows k0 + 2 i + a, all 64 columns
-  float* out = part + (size_t)slice * g.K * g.J;
+  typename F::Acc acc;
 #pragma unroll
-  for (int a = 0; a < 2; ++a) {
-    if (a) __syncthreads();
+  for (int v = 0; v < F::VALUES; ++v) acc[v] = 0.f;
+  G::template run<false, false>(load_x, load_dy, acc, (g.M + G::BK - 1) / G::BK, tid);
+
+  // lane: row k of dW, runs of four columns
+  const int k = k0 + (wave & 1) * TILE + lane % TILE;
 #pragma unroll
-    for (int v = 0; v < 16; ++v)
-      *reinterpret_cast<float2*>(&red[wave][(8 * (v >> 2) + 4 * half + (v & 3)) * PITCH + 2 * row]) = make_float2(acc[a][0][v], acc[a][1][v]);
-    __syncthreads();
-    const int i = tid >> 4, col = (tid & 15) * 4;                 // 512 threads: 32 rows x 16 groups of four columns
-    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int q = 0; q < F::VALUES / 4; ++q) {
+    const int j = j0 + (wave >> 1) * TILE + F::row(q, group);
+    if (k >= g.K || j >= g.J) continue;
+    float o[4];
 #pragma unroll
-    for (int w = 0; w < 8; ++w) {
-      const float4 p = *reinterpret_cast<const float4*>(&red[w][i * PITCH + col]);
-      o.x += p.x; o.y += p.y; o.z += p.z; o.w += p.w;
+    for (int e = 0; e < 4; ++e) o[e] = acc[4 * q + e];
+    if (o[0] != o[0] || o[1] != o[1] || o[2] != o[2] || o[3] != o[3]) {
+      const ConvGeom d{g.N, g.H, g.W, g.C, g.P, g.Q, g.K, g.R, g.S, g.stride, g.pad};
+      const int rs = j / g.C;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = conv_direct_wgrad_at(dy, x, d, k, rs / g.S, rs % g.S, j - rs * g.C + e);
     }
-    const int k = k0 + 2 * i + a, j = j0 + col;
-    if (k < g.K && j < g.J) *reinterpret_cast<float4*>(out + (size_t)k * g.J + j) = o;
+    *reinterpret_cast<float4*>(dw + (size_t)k * g.J + j) = make_float4(o[0], o[1], o[2], o[3]);
   }
 }
 

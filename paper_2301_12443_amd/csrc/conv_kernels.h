@@ -30,9 +30,26 @@ struct ConvGeom {
 };
 
 // ---------------------------------------------------------------------------
-// direct kernels (fp32 accumulate)
+// direct kernels (fp32 accumulate): one result is one chain of fused multiply-adds in the order written here, over the taps
+// that lie in the image.  The float32 matrix-core kernels (conv_f32_kernels.h) keep that order and those bits.
 // ---------------------------------------------------------------------------
 // y[m][k] = sum_{r,s,c} x[n, p*st+r-pad, q*st+s-pad, c] * w[k][r][s][c]
+template <class T, class WT>
+__device__ __forceinline__ float conv_direct_fwd_at(const T* __restrict__ x, const WT* __restrict__ w, const ConvGeom& g, int n, int p, int q, int k) {
+  float acc = 0.f;
+  for (int r = 0; r < g.R; ++r) {
+    const int h = p * g.stride + r - g.pad;
+    if (h < 0 || h >= g.H) continue;
+    for (int s = 0; s < g.S; ++s) {
+      const int ww = q * g.stride + s - g.pad;
+      if (ww < 0 || ww >= g.W) continue;
+      const T* xp = x + (((long)n * g.H + h) * g.W + ww) * g.C;
+      const WT* wp = w + (((long)k * g.R + r) * g.S + s) * g.C;
+      for (int c = 0; c < g.C; ++c) acc = fmaf((float)xp[c], (float)wp[c], acc);
+    }
+  }
+  return acc;
+}
 template <class T, class WT>
 __global__ void conv_direct_fwd_kernel(const T* __restrict__ x, const WT* __restrict__ w,
                                        T* __restrict__ y, const float* __restrict__ a,
@@ -44,24 +61,34 @@ __global__ void conv_direct_fwd_kernel(const T* __restrict__ x, const WT* __rest
     const int q = (int)(pix % g.Q); pix /= g.Q;
     const int p = (int)(pix % g.P);
     const int n = (int)(pix / g.P);
-    float acc = 0.f;
-    for (int r = 0; r < g.R; ++r) {
-      const int h = p * g.stride + r - g.pad;
-      if (h < 0 || h >= g.H) continue;
-      for (int s = 0; s < g.S; ++s) {
-        const int ww = q * g.stride + s - g.pad;
-        if (ww < 0 || ww >= g.W) continue;
-        const T* xp = x + (((long)n * g.H + h) * g.W + ww) * g.C;
-        const WT* wp = w + (((long)k * g.R + r) * g.S + s) * g.C;
-        for (int c = 0; c < g.C; ++c) acc = fmaf((float)xp[c], (float)wp[c], acc);
-      }
-    }
+    float acc = conv_direct_fwd_at(x, w, g, n, p, q, k);
     if (a) acc = fmaf(acc, a[k], b[k]);
     y[i] = (T)apply_act(acc, act);
   }
 }
 
-// dx[n,h,w,c] (+)= sum_{k,r,s} dy[n,(h+pad-r)/st,(w+pad-s)/st,k] * w[k][r][s][c]
+// dx[n,h,w,c] = init + sum_{k,r,s} dy[n,(h+pad-r)/st,(w+pad-s)/st,k] * w[k][r][s][c]   (init: what dx holds, or 0)
+template <class T, class WT>
+__device__ __forceinline__ float conv_direct_dgrad_at(const T* __restrict__ dy, const WT* __restrict__ w, const ConvGeom& g, int n, int h, int ww, int c,
+                                                      float init) {
+  float acc = init;
+  for (int r = 0; r < g.R; ++r) {
+    const int ph = h + g.pad - r;
+    if (ph < 0 || ph % g.stride) continue;
+    const int p = ph / g.stride;
+    if (p >= g.P) continue;
+    for (int s = 0; s < g.S; ++s) {
+      const int qw = ww + g.pad - s;
+      if (qw < 0 || qw % g.stride) continue;
+      const int q = qw / g.stride;
+      if (q >= g.Q) continue;
+      const T* dp = dy + (((long)n * g.P + p) * g.Q + q) * g.K;
+      for (int k = 0; k < g.K; ++k)
+        acc = fmaf((float)dp[k], (float)w[(((long)k * g.R + r) * g.S + s) * g.C + c], acc);
+    }
+  }
+  return acc;
+}
 template <class T, class WT>
 __global__ void conv_direct_dgrad_kernel(const T* __restrict__ dy, const WT* __restrict__ w,
                                          T* __restrict__ dx, int accumulate, ConvGeom g) {
@@ -72,27 +99,27 @@ __global__ void conv_direct_dgrad_kernel(const T* __restrict__ dy, const WT* __r
     const int ww = (int)(pix % g.W); pix /= g.W;
     const int h = (int)(pix % g.H);
     const int n = (int)(pix / g.H);
-    float acc = accumulate ? (float)dx[i] : 0.f;
-    for (int r = 0; r < g.R; ++r) {
-      const int ph = h + g.pad - r;
-      if (ph < 0 || ph % g.stride) continue;
-      const int p = ph / g.stride;
-      if (p >= g.P) continue;
-      for (int s = 0; s < g.S; ++s) {
-        const int qw = ww + g.pad - s;
-        if (qw < 0 || qw % g.stride) continue;
-        const int q = qw / g.stride;
-        if (q >= g.Q) continue;
-        const T* dp = dy + (((long)n * g.P + p) * g.Q + q) * g.K;
-        for (int k = 0; k < g.K; ++k)
-          acc = fmaf((float)dp[k], (float)w[(((long)k * g.R + r) * g.S + s) * g.C + c], acc);
-      }
-    }
-    dx[i] = (T)acc;
+    dx[i] = (T)conv_direct_dgrad_at(dy, w, g, n, h, ww, c, accumulate ? (float)dx[i] : 0.f);
   }
 }
 
 // dw[k][r][s][c] = sum_{n,p,q} dy[n,p,q,k] * x[n, p*st+r-pad, q*st+s-pad, c]
+template <class T>
+__device__ __forceinline__ float conv_direct_wgrad_at(const T* __restrict__ dy, const T* __restrict__ x, const ConvGeom& g, int k, int r, int s, int c) {
+  float acc = 0.f;
+  for (int n = 0; n < g.N; ++n)
+    for (int p = 0; p < g.P; ++p) {
+      const int h = p * g.stride + r - g.pad;
+      if (h < 0 || h >= g.H) continue;
+      for (int q = 0; q < g.Q; ++q) {
+        const int ww = q * g.stride + s - g.pad;
+        if (ww < 0 || ww >= g.W) continue;
+        acc = fmaf((float)dy[(((long)n * g.P + p) * g.Q + q) * g.K + k],
+                   (float)x[(((long)n * g.H + h) * g.W + ww) * g.C + c], acc);
+      }
+    }
+  return acc;
+}
 template <class T>
 __global__ void conv_direct_wgrad_kernel(const T* __restrict__ dy, const T* __restrict__ x,
                                          float* __restrict__ dw, ConvGeom g) {
@@ -103,19 +130,7 @@ __global__ void conv_direct_wgrad_kernel(const T* __restrict__ dy, const T* __re
     const int s = (int)(t % g.S); t /= g.S;
     const int r = (int)(t % g.R);
     const int k = (int)(t / g.R);
-    float acc = 0.f;
-    for (int n = 0; n < g.N; ++n)
-      for (int p = 0; p < g.P; ++p) {
-        const int h = p * g.stride + r - g.pad;
-        if (h < 0 || h >= g.H) continue;
-        for (int q = 0; q < g.Q; ++q) {
-          const int ww = q * g.stride + s - g.pad;
-          if (ww < 0 || ww >= g.W) continue;
-          acc = fmaf((float)dy[(((long)n * g.P + p) * g.Q + q) * g.K + k],
-                     (float)x[(((long)n * g.H + h) * g.W + ww) * g.C + c], acc);
-        }
-      }
-    dw[i] = acc;
+    dw[i] = conv_direct_wgrad_at(dy, x, g, k, r, s, c);
   }
 }
 

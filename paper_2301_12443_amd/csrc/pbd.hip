@@ -449,39 +449,11 @@ DmaCfg dma_cfg(long M, int NC, int Kred, int CA, int num_cu, int epi) {
   return d;
 }
 
-// Launch shape of igemm_f32_kernel.  A layer with at least 256 tiles of 64 x 64 takes them (half the operand bytes per
-// product of a 32 x 32 tile); the others take 32 x 32 tiles.  The reduction is cut over as many of a workgroup's
-// eight waves as it takes to have eight waves per compute unit, but leaves each at least two runs of eight channels.
-struct F32Cfg { int mt, kw_log2, tiles_m, tiles_n; };
-F32Cfg f32_cfg(long M, int NC, int Kred) {
-  F32Cfg c;
-  c.mt = NC >= 64 && ((M + 63) / 64) * ((NC + 63) / 64) >= 256 ? 2 : 1;
-  const int edge = 32 * c.mt;
-  c.tiles_n = (NC + edge - 1) / edge;
-  const long tiles = (M + edge - 1) / edge * c.tiles_n;
-  c.kw_log2 = 0;
-  while (c.kw_log2 < 3 && (tiles << c.kw_log2) < 2048 && (Kred / 8) >> (c.kw_log2 + 1) >= 2) ++c.kw_log2;
-  const int rows = (8 >> c.kw_log2) * edge;
-  c.tiles_m = (int)((M + rows - 1) / rows);
-  return c;
-}
-// wgrad_f32_kernel: 64 x 64 tiles, the pixels cut so that about 256 workgroups result (their partial sums are then at
-// most 8 MB whatever the layer), at least two turns of 64 pixels each.
-constexpr int kF32WgradUnr = 4;
-WgradCfg wgrad_f32_cfg(long M, int K, int J) {
-  WgradCfg w{};
-  w.TM = w.TN = 64;
-  w.BKP = 16 * kF32WgradUnr;
-  w.tiles_k = (K + 63) / 64;
-  w.tiles_j = (J + 63) / 64;
-  const long tiles = (long)w.tiles_k * w.tiles_j;
-  long splits = std::max(1L, std::min((256 + tiles - 1) / tiles, M / (2 * w.BKP)));
-  long pps = (M + splits - 1) / splits;
-  pps = (pps + w.BKP - 1) / w.BKP * w.BKP;
-  w.pix_per_split = (int)pps;
-  w.splits = (int)((M + pps - 1) / pps);
-  return w;
-}
+// Tile width of the float32 kernels (a workgroup owns 2 x 2 of them): 32 (half the operand bytes per product) where
+// 64 x 64 results a workgroup still give every compute unit one, else 16 (a quarter of the chain).  Dense layers of a step in us
+// with the line at 128 / 256 / 512 workgroups: VGG-16 at batch 64 2277 / 2189 / 2249, at batch 16 920 / 901 / 918, ResNet-50
+// x1.5 at batch 8 10.5 / 10.6 / 10.7 ms.
+inline int f32_tile(long rows, long cols) { return (rows + 63) / 64 * ((cols + 63) / 64) >= 256 ? 32 : 16; }
 
 constexpr int kMseBlocks = 1024;
 
@@ -629,10 +601,6 @@ int plan(pbd_ctx* c) {
           need_red((size_t)igemm_splits(M, op.d.c_out, op.d.k * op.d.k * op.cin_p, op.cin_p) * M * op.d.c_out * 4);
           if (op.s2d) need_red((size_t)igemm_splits(M, op.d.c_out, kS2dK, 16) * M * op.d.c_out * 4);
           need_red((size_t)igemm_splits(Min, op.cin_p, op.d.k * op.d.k * op.d.c_out, op.d.c_out) * Min * op.cin_p * 4);
-        } else if (!bf && !c->o.force_direct) {
-          const WgradCfg w = wgrad_f32_cfg(M, op.d.c_out, op.d.k * op.d.k * op.cin_p);
-          if (w.splits > 1) need_red((size_t)w.splits * op.wn * 4);
-          defer(op, w.splits);
         }
       } else if (op.d.type == OP_POOL) {
         op.idx = s; s += align_up((size_t)M * op.cout_p);
@@ -788,6 +756,8 @@ template <class T> struct Exec {
   }
   double bytes_of(Shape s) const { return (double)c->o.batch * s.h * s.w * round8(s.c) * sizeof(T); }
   bool mfma() const { return sizeof(T) == 2 && !c->o.force_direct; }
+  // (tensors end below 2 GiB; the float32 kernels address the weights with 32-bit byte offsets as well)
+  bool mfma_f32(const OpPlan& op) const { return sizeof(T) == 4 && !c->o.force_direct && op.wn < ((size_t)1 << 29) - 1024; }
   // The batch-norm passes over a tensor of this shape use nontemporal loads and stores (bf16 tensors far larger than
   // L2: what they stream through would only push out the lines that convolutions running beside them reuse).
   // From 64 MiB on (measured 8 ... 200 MiB on the four large configurations: ResNet-50 x1.5 30.40 -> 29.74 ms per step,
@@ -846,12 +816,12 @@ template <class T> struct Exec {
         launch_igemm<0>(g, (const bf16_t*)x, (const bf16_t*)w, (bf16_t*)y, a, b, act, a ? EPI_AFFINE_ACT : EPI_STORE,
                         bytes_run, flops);
       }
-    } else if (!c->o.force_direct) {
+    } else if (mfma_f32(op)) {
       if constexpr (sizeof(T) == 4) {
-        F32Args f{{N, op.in.h, op.in.w, op.cin_p, op.out.h, op.out.w, op.d.c_out, op.d.k, op.d.k, op.d.stride, op.d.pad,
-                   N * op.out.h * op.out.w, op.d.k * op.d.k * op.cin_p, 0,
-                   (unsigned)((size_t)N * op.in.h * op.in.w * op.cin_p * 4), (unsigned)(op.wn * 4)}};
-        launch_igemm_f32<0>(f, x, w, y, a, b, act, bytes, flops);
+        const IgemmArgs g{N, op.in.h, op.in.w, op.cin_p, op.out.h, op.out.w, op.d.c_out, op.d.k, op.d.k, op.d.stride, op.d.pad,
+                          N * op.out.h * op.out.w, op.d.k * op.d.k * op.cin_p, 0,
+                          (unsigned)((size_t)N * op.in.h * op.in.w * op.cin_p * 4), (unsigned)(op.wn * 4)};
+        launch_igemm_f32<0>(g, x, w, y, a, b, act, false, bytes, flops);
       }
     } else {
       ConvGeom g{N, op.in.h, op.in.w, op.cin_p, op.out.h, op.out.w, op.d.c_out, op.d.k, op.d.k, op.d.stride, op.d.pad};
@@ -861,16 +831,15 @@ template <class T> struct Exec {
   }
 
   template <int MODE>
-  void launch_igemm_f32(F32Args f, const float* A, const float* Bw, float* out, const float* a, const float* b, int act,
+  void launch_igemm_f32(IgemmArgs g, const float* A, const float* Bw, float* out, const float* a, const float* b, int act, bool accumulate,
                         double bytes, double flops) {
-    const F32Cfg cfg = f32_cfg(f.g.M, f.g.NC, f.g.Kred);
-    f.g.tiles_m = cfg.tiles_m; f.g.tiles_n = cfg.tiles_n;
-    f.kw_log2 = cfg.kw_log2;
-    const dim3 grid(cfg.tiles_m * cfg.tiles_n);
+    const int tile = f32_tile(g.M, g.NC), edge = 2 * tile;
+    g.tiles_m = (g.M + edge - 1) / edge; g.tiles_n = (g.NC + edge - 1) / edge;
     char name[32];
-    snprintf(name, sizeof name, "igemm_f32_%s_%d", MODE ? "dgrad" : "fwd", 32 * cfg.mt);
+    snprintf(name, sizeof name, "igemm_f32_%s_%d", MODE ? "dgrad" : "fwd", edge);
     ProfScope ps(c, name, bytes, flops, net, blk, opi);
-    launch(c, cfg.mt == 2 ? igemm_f32_kernel<MODE, 2, 2> : igemm_f32_kernel<MODE, 1, 1>, grid, kF32Threads, 0, st, A, Bw, out, a, b, act, f);
+    launch(c, tile == 32 ? igemm_f32_kernel<MODE, 32> : igemm_f32_kernel<MODE, 16>, g.tiles_m * g.tiles_n, 256, 0, st, A, Bw, out, a, b, act,
+           accumulate ? 1 : 0, g);
   }
 
   template <int MODE>
@@ -986,13 +955,12 @@ template <class T> struct Exec {
         launch_igemm<1>(g, (const bf16_t*)dy, (const bf16_t*)wt, (bf16_t*)dx, nullptr, nullptr, 0,
                         accumulate ? EPI_ACCUM : EPI_STORE, bytes, flops);
       }
-    } else if (!c->o.force_direct) {
+    } else if (mfma_f32(op)) {
       if constexpr (sizeof(T) == 4) {
-        F32Args f{{N, op.out.h, op.out.w, op.d.c_out, op.in.h, op.in.w, op.cin_p, op.d.k, op.d.k, op.d.stride, op.d.pad,
-                   N * op.in.h * op.in.w, op.d.k * op.d.k * op.d.c_out, 0,
-                   (unsigned)((size_t)N * op.out.h * op.out.w * op.d.c_out * 4), (unsigned)(op.wn * 4)}};
-        f.accumulate = accumulate ? 1 : 0;
-        launch_igemm_f32<1>(f, dy, w, dx, nullptr, nullptr, 0, bytes, flops);
+        const IgemmArgs g{N, op.out.h, op.out.w, op.d.c_out, op.in.h, op.in.w, op.cin_p, op.d.k, op.d.k, op.d.stride, op.d.pad,
+                          N * op.in.h * op.in.w, op.d.k * op.d.k * op.d.c_out, 0,
+                          (unsigned)((size_t)N * op.out.h * op.out.w * op.d.c_out * 4), (unsigned)(op.wn * 4)};
+        launch_igemm_f32<1>(g, dy, w, dx, nullptr, nullptr, 0, accumulate, bytes, flops);
       }
     } else {
       ConvGeom g{N, op.in.h, op.in.w, op.cin_p, op.out.h, op.out.w, op.d.c_out, op.d.k, op.d.k, op.d.stride, op.d.pad};
@@ -1055,24 +1023,16 @@ template <class T> struct Exec {
         if (op.s2d)
           launch(c, unpack_stem_grad_kernel, (op.d.c_out * 392 + 255) / 256, 256, 0, st, dw_run, dw, op.d.c_out, op.in.c);
       }
-    } else if (!c->o.force_direct) {
+    } else if (mfma_f32(op)) {
       if constexpr (sizeof(T) == 4) {
-        const WgradCfg w = wgrad_f32_cfg(M, op.d.c_out, J);
-        const int pq = op.out.h * op.out.w;
-        WgradTrArgs g{N, op.in.h, op.in.w, op.cin_p, op.out.h, op.out.w, op.d.c_out, op.d.k, op.d.k,
-                      op.d.stride, op.d.pad, (int)M, J, w.pix_per_split,
-                      w.BKP / pq, (w.BKP % pq) / op.out.w, w.BKP % op.out.w,
-                      (unsigned)(M * op.d.c_out * 4), (unsigned)((size_t)N * op.in.h * op.in.w * op.cin_p * 4),
-                      w.tiles_k, w.tiles_j, w.splits};
-        float* part = w.splits == 1 ? dw : parts(op);
-        {
-          ProfScope ps(c, "wgrad_f32", bytes, flops, net, blk, opi);
-          launch(c, wgrad_f32_kernel<kF32WgradUnr>, w.tiles_k * w.tiles_j * w.splits, kF32Threads, 0, st, dy, x, part, g);
-        }
-        if (w.splits > 1 && !deferred(op)) {
-          ProfScope ps(c, "sum_partials", (double)(w.splits + 1) * op.wn * 4, 0, net, blk, opi);
-          sum_partials(part, dw, (long)op.wn, w.splits);
-        }
+        const int tile = f32_tile(op.d.c_out, J), edge = 2 * tile;
+        const int px = tile == 32 ? F32Gemm<32>::BK : F32Gemm<16>::BK, pq = op.out.h * op.out.w;
+        const WgradTrArgs g{N, op.in.h, op.in.w, op.cin_p, op.out.h, op.out.w, op.d.c_out, op.d.k, op.d.k,
+                            op.d.stride, op.d.pad, (int)M, J, (int)M, px / pq, (px % pq) / op.out.w, px % op.out.w,
+                            (unsigned)(M * op.d.c_out * 4), (unsigned)((size_t)N * op.in.h * op.in.w * op.cin_p * 4),
+                            (op.d.c_out + edge - 1) / edge, (J + edge - 1) / edge, 1};
+        ProfScope ps(c, tile == 32 ? "wgrad_f32_64" : "wgrad_f32_32", bytes, flops, net, blk, opi);
+        launch(c, tile == 32 ? wgrad_f32_kernel<32> : wgrad_f32_kernel<16>, g.tiles_k * g.tiles_j, 256, 0, st, dy, x, dw, g);
       }
     } else {
       ConvGeom g{N, op.in.h, op.in.w, op.cin_p, op.out.h, op.out.w, op.d.c_out, op.d.k, op.d.k, op.d.stride, op.d.pad};
