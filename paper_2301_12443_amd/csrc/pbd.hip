@@ -566,8 +566,14 @@ int plan(pbd_ctx* c) {
   for (BlockPlan& bp : c->net[1]) {
     size_t s = 0, parts = 0;      // (parts: elements of the deferred partial sums)
     red = kMseBlocks * sizeof(float);
+    // ops that the weight round back-propagates to; one whose value leads nowhere keeps the zero gradient it was bound with
+    std::vector<char> reached(bp.shapes.size(), 0);
+    reached.back() = 1;
+    for (size_t j = bp.ops.size(); j-- > 0;)
+      if (reached[j + 1])
+        for (int i = 0; i < bp.ops[j].d.nin; ++i) reached[bp.ops[j].d.in[i]] = 1;
     auto defer = [&](OpPlan& op, int splits) {
-      if (splits < 2 || (size_t)splits * op.wn > kDeferredElems) return;
+      if (splits < 2 || (size_t)splits * op.wn > kDeferredElems || !reached[&op - bp.ops.data() + 1]) return;
       op.e_part = (long)parts;
       bp.stable.push_back({(long)parts, (long)op.e_w, (long)op.wn, splits, 0});
       parts += (size_t)splits * op.wn;

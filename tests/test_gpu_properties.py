@@ -182,3 +182,44 @@ def test_profile_records_every_launch(batch, bn):
         assert any(n.startswith(prefix) for n in names), (prefix, names)
     assert any(n.startswith("igemm_fwd_") and n.endswith("_affine") for n in names)      # teacher: fused BN + ReLU
     assert all(p["ms"] > 0 for p in prof) and all(p["bytes"] > 0 for p in prof)
+
+
+@pytest.mark.parametrize("call", ["student_step", "student_step_static", "distill_step"])
+@pytest.mark.parametrize("precision", ["bf16", "f32"])
+def test_a_value_that_nobody_reads_trains_nothing(precision, call):
+    """Layers whose values lead nowhere get no gradient: their weights and momenta stay as they were, whatever the
+    memory behind the parameters held when the workspace was bound."""
+    import torch
+    t, s = W.Block(), W.Block()
+    t.cba(0, 24, 3)
+    v = s.cba(0, 32, 1)
+    dangling = [s.cba(v, 40, 3), s.cba(v, 32, 3, groups=32), s.cba(v, 32, 5, 2, groups=32)]
+    dangling.append(s.cba(dangling[0], 48, 1))
+    s.cba(v, 24, 3)
+    wl = W.Workload("dangling", 8, (8, 20, 20), [t], [s], precision, lr=0.05)
+    d = pbd.Distiller(wl)
+    d.bind("cuda:0")
+    d._ws.fill_(255)                                   # NaN in every type
+    torch.cuda.synchronize()
+    base = (d._ws.data_ptr() + 255) // 256 * 256
+    assert pbd.lib().pbd_bind(d.h, base, d.workspace_bytes(), d._stream.cuda_stream) == 0
+    d.load_params()
+    x = torch.from_numpy(W.make_input(wl)).cuda()
+    for _ in range(2):
+        if call == "distill_step":
+            d.distill_step(x, wl.lr)
+        else:
+            d.teacher_relay(x)
+            getattr(d, call)(1, wl.lr)
+    d.sync()
+    assert np.isfinite(d.losses.cpu().numpy()).all()
+    for (j, slot), shape in W.param_shapes(wl, W.NET_STUDENT, 0).items():
+        if slot > W.P_BETA:
+            continue
+        got = d.read_tensor(pbd.PBD_PARAM, 1, 0, j, slot, shape)
+        start = W.make_param(wl, W.NET_STUDENT, 0, j, slot, shape)
+        moved = not np.array_equal(got, start)
+        assert np.isfinite(got).all() and moved == (j + 1 not in dangling), (j, slot)
+        if j + 1 in dangling:
+            for kind in (pbd.PBD_GRAD, pbd.PBD_MOMENTUM):
+                assert not d.read_tensor(kind, 1, 0, j, slot, shape).any(), (j, slot, kind)
