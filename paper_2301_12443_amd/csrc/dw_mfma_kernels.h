@@ -179,8 +179,9 @@ __global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16
   float ea = 1.f, eb = 0.f;
   if (a && cv0 * 8 + ch < g.ncv * 8) { ea = a[cv0 * 8 + ch]; eb = b[cv0 * 8 + ch]; }
   // STATS: this lane's sums of (y - pivot) and (y - pivot)^2 over the stored outputs of its channel, the pivot being the wave's first
-  // output of the channel (no cancellation when |mean| is far above the deviation)
+  // output of the channel that lies in the image (no cancellation when |mean| is far above the deviation)
   float pivot = 0.f, s1 = 0.f, s2 = 0.f, cnt = 0.f;
+  bool pivoted = false;                                  // (the same for the whole wave)
 
   for (int tile = tile_begin; tile < tile_end; ++tile) {
     int t_ = tile;
@@ -249,9 +250,12 @@ __global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16
           for (int m = 0; m < 4; ++m) acc[o][q][m] = apply_act(fmaf(acc[o][q][m], ea, eb), act);
     }
     if (STATS) {
-      if (tile == tile_begin) pivot = as_stored<bf16_t>(__shfl(acc[0][0][0], lane & ~3, 64));
       const int rows = min(4, g.H - h0 - 4 * strip);     // of this lane's outputs (none or negative: below the image)
-      const int cols = min(8, g.W - w0 - half * 8);      // (the same for the whole wave)
+      const int cols = min(8, g.W - w0 - half * 8);      // (the same for the whole wave; none where a row's last tile ends in the left half)
+      if (!pivoted && cols > 0) {
+        pivot = as_stored<bf16_t>(__shfl(acc[0][0][0], lane & ~3, 64));
+        pivoted = true;
+      }
 #pragma unroll
       for (int o = 0; o < 4; ++o) {
         const bool row_in = o < rows;

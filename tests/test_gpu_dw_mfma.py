@@ -4,9 +4,12 @@ primitives on the tensors that the library read (local_parity.py).  Its bounds: 
 it, 2e-2 of the largest allowed) forward and backward-data; the weight gradient is float32, a sum of n products of
 bfloat16 numbers, off by at most n 2^-24 of the sum of their magnitudes - a wrong tap, shift or mask is off by the size of
 the result."""
+import numpy as np
 import pytest
+import torch
 
 import local_parity
+import parity
 from paper_2301_12443_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -68,3 +71,41 @@ def test_normalisation_in_the_staging(n, h, w, c, k, act):
     wl = W.Workload("dw_folded", n, (8, h, w), [t], [b], "bf16", lr=0.05)
     worst = local_parity.run_and_check(wl, n)     # (reads the value between the two layers: formed on request, after the update)
     print(", ".join(f"{key} {e:.1e}" for key, e in sorted(worst.items())), flush=True)
+
+
+@pytest.mark.parametrize("folded", [False, True])
+@pytest.mark.parametrize("k", [3, 5, 7])
+def test_statistics_of_channels_far_from_zero(k, folded):
+    """Batch statistics from the forward kernel where a workgroup begins with a tile whose right half is empty (40 columns:
+    tiles of 16, 16 and 8; 17 tiles a workgroup).  Every channel is a checkerboard of two numbers up to 500 deviations from
+    zero and the filter is its middle tap, so about any pixel of the image all sums are small whole numbers, exact in float32.
+    About zero instead, a lane's 352 squares need more than its 24 bits, and the lost ones are a quarter of the variance and more."""
+    n, h, w = 11000, 16, 40
+    top = np.array([251, 241, 231, 221, 201, 191, 181, 171], dtype=np.float32)
+    c = top.size
+    tiles, groups = n * ((h + 15) // 16) * ((w + 15) // 16), (c + 31) // 32
+    assert -(-tiles * groups // 2048) == 17                    # tiles a workgroup
+    t, b = W.Block(), W.Block()
+    t.cba(0, 16, 1, act=W.ACT_NONE)
+    v = b.cba(0, c, 1, act=W.ACT_RELU) if folded else 0        # (a rectified value is normalised in the staging: top - 1 +- 1)
+    v = b.cba(v, c, k, groups=c, act=W.ACT_NONE)
+    b.cba(v, 16, 1, act=W.ACT_NONE)
+    op = 1 if folded else 0
+    wl = W.Workload("dw_far", n, (c, h, w), [t], [b], "bf16", lr=0.05)
+    d = parity.make_distiller(wl, n, "bf16")
+    middle = np.zeros((c, 1, k, k), dtype=np.float32)
+    middle[:, :, k // 2, k // 2] = 1.0
+    d.load_param(W.NET_STUDENT, 0, op, W.P_WEIGHT, middle)
+    if folded:
+        d.load_param(W.NET_STUDENT, 0, 0, W.P_WEIGHT, np.eye(c, dtype=np.float32).reshape(c, c, 1, 1))
+        d.load_param(W.NET_STUDENT, 0, 0, W.P_BETA, top - 1)
+    board = np.indices((h, w)).sum(axis=0) % 2
+    x = torch.from_numpy(top[:, None, None] - board.astype(np.float32)).cuda().expand(n, c, h, w).contiguous()
+    torch.cuda.synchronize()                                   # (the library works on a stream of its own)
+    d.teacher_relay(x)
+    d.student_step(1, wl.lr)
+    d.sync()
+    mean, invstd = d.read_batch_stats(0, op)
+    print("variance + 1e-5:", invstd.astype(np.float64) ** -2, flush=True)
+    np.testing.assert_array_equal(mean, top - 1 if folded else top - 0.5)
+    np.testing.assert_allclose(invstd, ((1.0 if folded else 0.25) + 1e-5) ** -0.5, rtol=2.0 ** -23)
