@@ -118,8 +118,10 @@ struct DwArgs {
 // the vector ALUs: 7 x 7 72 -> 37 us, 5 x 5 40 -> 30, 3 x 3 24.4 -> 24.7 (and MobileNetV2's at batch 33: 11.6 -> 8.3).
 // Slower: the next tile's loads in flight behind the products (K = 7 40 us, K = 5 31: the registers cost a workgroup per
 // compute unit); 64 channels a workgroup (K = 5 31 us, batch 33 12.6 against 11.4).
-template <int K, bool FLIP, bool FOLD = false, bool STATS = false>
-__global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
+// ACC (backward-data into a value that already has a gradient): the result is added to what dst holds, in float32, and rounded
+// once.  What dst holds is loaded ahead of the products and passes through LDS the way the result does.
+template <int K, bool FLIP, bool FOLD = false, bool STATS = false, bool ACC = false>
+__global__ __launch_bounds__(256, K == 7 || ACC ? 3 : 4) void dw_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
                                                          bf16_t* __restrict__ dst, const float* __restrict__ a,
                                                          const float* __restrict__ b, int act, DwArgs g, NormFold fold) {
   typedef DwGeom<K> G;
@@ -215,6 +217,25 @@ __global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16
     }
     __syncthreads();
 
+    // this thread's chunks of the output: 8 channels of a pixel each
+    constexpr int NOUT = kDwTile * kDwTile * (kDwCh / 8) / 256;
+    auto chunk = [&](int i, int& at, size_t& out) {      // its place in LDS and in dst; whether it lies in the image
+      const int c = tid + i * 256;
+      const int cvl = c % (kDwCh / 8), col = (c / (kDwCh / 8)) % kDwTile, row = c / (kDwCh / 8) / kDwTile;
+      const int h = h0 + row, w_ = w0 + col;
+      at = row * kDwOutRow + col * kDwOutP + cvl * 16;
+      out = ((((size_t)n * g.H + h) * g.W + w_) * g.ncv + cv0 + cvl) * 8;
+      return h < g.H && w_ < g.W && cv0 + cvl < g.ncv;
+    };
+    uint4 old[ACC ? NOUT : 1];
+    if constexpr (ACC) {
+#pragma unroll
+      for (int i = 0; i < NOUT; ++i) {
+        int at; size_t out;
+        old[i] = chunk(i, at, out) ? *reinterpret_cast<const uint4*>(dst + out) : make_uint4(0u, 0u, 0u, 0u);
+      }
+    }
+
     // ---- products: acc[rho][q] = output rows 4 strip + rho, output columns 8 half + 4 q + 0..3 ----
     dw_f32x4 acc[4][2];
 #pragma unroll
@@ -273,6 +294,15 @@ __global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16
       cnt += (float)(max(rows, 0) * max(cols, 0));
     }
     __syncthreads();                                     // every wave has read the input tile
+    if constexpr (ACC) {
+#pragma unroll
+      for (int i = 0; i < NOUT; ++i) {
+        int at; size_t out;
+        chunk(i, at, out);
+        *reinterpret_cast<uint4*>(smem + at) = old[i];
+      }
+      __syncthreads();
+    }
     // lanes 4 apart hold neighbouring channels: the even channel packs columns 0 and 1 of both, the odd one columns 2 and 3
     unsigned char* so = smem + (ch >> 1) * 4 + ((ch & 1) * 2 + half * 8) * kDwOutP;
 #pragma unroll
@@ -284,22 +314,21 @@ __global__ __launch_bounds__(256, K == 7 ? 3 : 4) void dw_mfma_kernel(const bf16
           const int v0 = __float_as_int(acc[o][q][m]), v2 = __float_as_int(acc[o][q][m + 2]);
           const int lo = __builtin_amdgcn_update_dpp(v0, v2, 0x114, 0xf, 0xa, false);   // row_shr:4 into the odd channels
           const int hi = __builtin_amdgcn_update_dpp(v2, v0, 0x104, 0xf, 0x5, false);   // row_shl:4 into the even channels
-          *reinterpret_cast<unsigned*>(so + (4 * strip + o) * kDwOutRow + (q * 4 + m) * kDwOutP) = pack_bf2(__int_as_float(lo), __int_as_float(hi));
+          unsigned* slot = reinterpret_cast<unsigned*>(so + (4 * strip + o) * kDwOutRow + (q * 4 + m) * kDwOutP);
+          if constexpr (ACC) *slot = pack_bf2(__int_as_float(lo) + bf_lo(*slot), __int_as_float(hi) + bf_hi(*slot));
+          else *slot = pack_bf2(__int_as_float(lo), __int_as_float(hi));
         }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kDwTile * kDwTile * (kDwCh / 8) / 256; ++i) {
-      const int c = tid + i * 256;
-      const int cvl = c % (kDwCh / 8), col = (c / (kDwCh / 8)) % kDwTile, row = c / (kDwCh / 8) / kDwTile;
-      const int h = h0 + row, w_ = w0 + col;
-      if (h >= g.H || w_ >= g.W || cv0 + cvl >= g.ncv) continue;
-      const uint4 v = *reinterpret_cast<const uint4*>(smem + row * kDwOutRow + col * kDwOutP + cvl * 16);
-      bf16_t* out = dst + ((((size_t)n * g.H + h) * g.W + w_) * g.ncv + cv0 + cvl) * 8;
+    for (int i = 0; i < NOUT; ++i) {
+      int at; size_t out;
+      if (!chunk(i, at, out)) continue;
+      const uint4 v = *reinterpret_cast<const uint4*>(smem + at);
       if (g.stream) {
         const u32x4 q = {v.x, v.y, v.z, v.w};
-        __builtin_nontemporal_store(q, reinterpret_cast<u32x4*>(out));
+        __builtin_nontemporal_store(q, reinterpret_cast<u32x4*>(dst + out));
       } else {
-        *reinterpret_cast<uint4*>(out) = v;
+        *reinterpret_cast<uint4*>(dst + out) = v;
       }
     }
   }

@@ -1119,16 +1119,20 @@ template <class T> struct Exec {
   void dw_dgrad(const OpPlan& op, const T* dy, const T* w, T* dx, bool accumulate) {
     const int N = c->o.batch, ncv = op.cout_p / 8;
     const long nvec = (long)N * op.in.h * op.in.w * ncv;
+    // adding to what dx holds costs the matrix-core kernel a pass through LDS more: images of 7 x 7 stay on the sliding windows then
+    // (7 x 7 x 960, batch 64: 5 x 5 14.0 against 14.3 us, 7 x 7 14.3 against 18.7; 14 x 14 x 576: 5 x 5 28 against 12.1, 3 x 3 15.8
+    // against 11.1; 56 x 56 x 144: 3 x 3 59 against 42, 5 x 5 89 against 48, 7 x 7 101 against 56)
+    const bool on_mfma = dw_mfma(op) && (!accumulate || (op.in.h >= 8 && op.in.w >= 12));
     char cls[32];
-    snprintf(cls, sizeof cls, "dw_dgrad%s_k%d", dw_mfma(op) && !accumulate ? "_mfma" : dw_slides(op) ? (op.d.stride == 1 ? "_slide" : "_s2") : "", op.d.k);
+    snprintf(cls, sizeof cls, "dw_dgrad%s_k%d", on_mfma ? (accumulate ? "_mfma_acc" : "_mfma") : dw_slides(op) ? (op.d.stride == 1 ? "_slide" : "_s2") : "", op.d.k);
     ProfScope ps(c, cls, bytes_of(op.in) + bytes_of(op.out), 2.0 * N * op.out.h * op.out.w * op.d.c_out * op.d.k * op.d.k,
                  net, blk, opi);
     const unsigned de = (unsigned)((size_t)N * op.out.h * op.out.w * op.cout_p);
-    if (dw_mfma(op) && !accumulate) {          // mirrored filter over dy
+    if (on_mfma) {                             // mirrored filter over dy
       if constexpr (sizeof(T) == 2) {
         DwArgs g = dw_args(N, op.in.h, op.in.w, op.cin_p, kDwFwdBlocks);
         g.stream = streams(op.in) ? 1 : 0;
-#define PBD_DWM(K_) launch(c, dw_mfma_kernel<K_, true>, dw_chunks(g) * g.groups, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)w, (bf16_t*)dx, \
+#define PBD_DWM(K_) launch(c, accumulate ? dw_mfma_kernel<K_, true, false, false, true> : dw_mfma_kernel<K_, true>, dw_chunks(g) * g.groups, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)w, (bf16_t*)dx, \
     (const float*)nullptr, (const float*)nullptr, 0, g, NormFold{})
         if (op.d.k == 3) PBD_DWM(3); else if (op.d.k == 5) PBD_DWM(5); else PBD_DWM(7);
 #undef PBD_DWM

@@ -109,3 +109,21 @@ def test_statistics_of_channels_far_from_zero(k, folded):
     print("variance + 1e-5:", invstd.astype(np.float64) ** -2, flush=True)
     np.testing.assert_array_equal(mean, top - 1 if folded else top - 0.5)
     np.testing.assert_allclose(invstd, ((1.0 if folded else 0.25) + 1e-5) ** -0.5, rtol=2.0 ** -23)
+
+
+def test_a_second_reader_keeps_the_matrix_cores():
+    """Backward-data that adds to a gradient already there runs on the same kernel as the first one."""
+    t, b = W.Block(), W.Block()
+    t.cba(0, 16, 1, act=W.ACT_NONE)
+    v = b.cba(0, 40, 1, act=W.ACT_NONE)
+    outs = [b.cba(v, 40, k, groups=40, act=W.ACT_NONE) for k in (3, 5, 7, 3)]
+    b.cba(b.add(b.add(outs[0], outs[1]), b.add(outs[2], outs[3])), 16, 1, act=W.ACT_NONE)
+    wl = W.Workload("dw_readers", 3, (8, 17, 21), [t], [b], "bf16", lr=0.05)
+    d = parity.make_distiller(wl, 3, "bf16")
+    d.teacher_relay(torch.from_numpy(W.make_input(wl, batch=3)).cuda())
+    d.sync()
+    d.set_profile(True)
+    d.student_step(1, wl.lr)
+    names = sorted(p["name"] for p in d.get_profile() if p["name"].startswith("dw_dgrad"))
+    assert names == ["dw_dgrad_mfma_acc_k3", "dw_dgrad_mfma_acc_k5", "dw_dgrad_mfma_acc_k7", "dw_dgrad_mfma_k3"], names
+    local_parity.run_and_check(wl, 3)
