@@ -105,7 +105,6 @@ struct DwArgs {
   int tiles_h, tiles_w, tiles;  // tiles = N * tiles_h * tiles_w
   int groups, per_block;        // channel groups, tiles per workgroup
   unsigned bytes;               // of the input tensor (and of the output: the shapes agree at stride 1)
-  int stream;                   // nontemporal stores
   float* stats;                 // forward, STATS: [2 x chunks][3][8 ncv] mean, sum of squares about it, pixels
   int P, Q;                     // stride 2: height, width and bytes of dy (tiles are counted over it)
   unsigned dy_bytes;
@@ -116,6 +115,9 @@ struct DwArgs {
 // Bound by the latency of load - stage - multiply - stage - store at three to four workgroups per compute unit (no unit is
 // busy all the time).  Launch averages over the supernet step (batch 64, 96 MB in and out each) against a tile kernel on
 // the vector ALUs: 7 x 7 72 -> 37 us, 5 x 5 40 -> 30, 3 x 3 24.4 -> 24.7 (and MobileNetV2's at batch 33: 11.6 -> 8.3).
+// Stores go through the caches whatever the tensor's size: a workgroup writes 64 of the 128 bytes of a line, its neighbour the
+// others, and past the caches the halves reach memory one by one (128 x 56 x 56 x 144, 3 x 3: backward-data 97 us nontemporal, 60
+// through the caches; 128 x 40 x 40 x 384, 7 x 7 120 and 111; the supernet step 41.21 and 41.03 ms).
 // Slower: the next tile's loads in flight behind the products (K = 7 40 us, K = 5 31: the registers cost a workgroup per
 // compute unit); 64 channels a workgroup (K = 5 31 us, batch 33 12.6 against 11.4).
 // ACC (backward-data into a value that already has a gradient): the result is added to what dst holds, in float32, and rounded
@@ -323,13 +325,7 @@ __global__ __launch_bounds__(256, K == 7 || ACC ? 3 : 4) void dw_mfma_kernel(con
     for (int i = 0; i < NOUT; ++i) {
       int at; size_t out;
       if (!chunk(i, at, out)) continue;
-      const uint4 v = *reinterpret_cast<const uint4*>(smem + at);
-      if (g.stream) {
-        const u32x4 q = {v.x, v.y, v.z, v.w};
-        __builtin_nontemporal_store(q, reinterpret_cast<u32x4*>(dst + out));
-      } else {
-        *reinterpret_cast<uint4*>(dst + out) = v;
-      }
+      *reinterpret_cast<uint4*>(dst + out) = *reinterpret_cast<const uint4*>(smem + at);
     }
   }
   if (STATS) {

@@ -1092,7 +1092,6 @@ template <class T> struct Exec {
     if (dw_mfma(op)) {
       if constexpr (sizeof(T) == 2) {
         DwArgs g = dw_args(N, op.out.h, op.out.w, op.cout_p, kDwFwdBlocks);
-        g.stream = streams(op.out) ? 1 : 0;
         g.stats = stats;
 #define PBD_DWM(K_) launch(c, fold.mean ? dw_mfma_kernel<K_, false, true, true> : stats ? dw_mfma_kernel<K_, false, false, true> : \
     dw_mfma_kernel<K_, false>, dw_chunks(g) * g.groups, 256, 0, st, \
@@ -1130,8 +1129,7 @@ template <class T> struct Exec {
     const unsigned de = (unsigned)((size_t)N * op.out.h * op.out.w * op.cout_p);
     if (on_mfma) {                             // mirrored filter over dy
       if constexpr (sizeof(T) == 2) {
-        DwArgs g = dw_args(N, op.in.h, op.in.w, op.cin_p, kDwFwdBlocks);
-        g.stream = streams(op.in) ? 1 : 0;
+        const DwArgs g = dw_args(N, op.in.h, op.in.w, op.cin_p, kDwFwdBlocks);
 #define PBD_DWM(K_) launch(c, accumulate ? dw_mfma_kernel<K_, true, false, false, true> : dw_mfma_kernel<K_, true>, dw_chunks(g) * g.groups, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)w, (bf16_t*)dx, \
     (const float*)nullptr, (const float*)nullptr, 0, g, NormFold{})
         if (op.d.k == 3) PBD_DWM(3); else if (op.d.k == 5) PBD_DWM(5); else PBD_DWM(7);
