@@ -1593,6 +1593,134 @@ __global__ __launch_bounds__(256) void dw_slide_kernel(const T* __restrict__ x, 
   }
 }
 
+// LDS-tiled stride-1 3 x 3 depthwise convolution on the vector ALUs (bf16): a block stages the (8+K-1) x (16+K-1) input
+// pixels x 64 channels behind an 8 x 16 output tile in LDS with ONE round of global loads (all in
+// flight together), then every thread slides over 4 outputs reading LDS.  Each input element is
+// fetched once per tile instead of ~K*K/2 times, which takes the kernel off the vector-memory
+// pipeline and onto HBM.  LDS pixel pitch 160 B: the two 4-pixel segments of a 16-lane group land
+// 128 B apart modulo the 256 B bank span.  FLIP / accumulate as in dw_slide_kernel.
+//  Whole 128-byte lines of whole 64-channel groups, read and written (nontemporally: the tensors are far larger than the
+// caches) by one workgroup: bound by memory on tensors the caches do not hold, where dw_mfma_kernel's workgroups of 32 channels share
+// each line with a neighbour and lose to it.  Backward-data in us against dw_mfma_kernel: 128 x 56 x 56 x 192 64 and 77,
+// 64 x 56 x 56 x 192 35 and 40, 128 x 40 x 40 x 384 68 and 83, 128 x 28 x 28 x 384 37 and 40, 128 x 24 x 24 x 960 65 and 72,
+// 64 x 112 x 112 x 64 40 and 48; on smaller tensors or channel counts that leave a group part empty it is the other way round (64 x 28
+// x 28 x 192 13 and 10, 128 x 14 x 14 x 960 24 and 20, 128 x 56 x 56 x 144 76 and 60).
+constexpr int kDwTileH = 8, kDwTileW = 16, kDwTileCv = 8, kDwTilePitch = kDwTileCv * 16 + 32;
+
+template <bool FLIP>
+__global__ __launch_bounds__(256) void dw_tile_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
+                                                      bf16_t* dst, const float* __restrict__ a,
+                                                      const float* __restrict__ b, int act, int accumulate,
+                                                      int N, int H, int W, int ncv, int tiles_h, int tiles_w,
+                                                      unsigned x_bytes) {
+  constexpr int K = 3, TH = kDwTileH, TW = kDwTileW, WS = 4, CVB = kDwTileCv, PIXB = kDwTilePitch;
+  constexpr int IH = TH + K - 1, IW = TW + K - 1, NIN = WS + K - 1, pad = K / 2;
+  constexpr int TOTAL = IH * IW * CVB, NLOAD = (TOTAL + 255) / 256;
+  __shared__ __attribute__((aligned(16))) unsigned char tile[IH * IW * PIXB];
+  __shared__ __attribute__((aligned(16))) float wl[K * K * CVB * 8];   // the block's filters, unpacked once
+  const int tid = threadIdx.x;
+  int t = blockIdx.x;
+  const int tw = t % tiles_w; t /= tiles_w;
+  const int th_ = t % tiles_h;
+  const int n = t / tiles_h;
+  const int h0 = th_ * TH, w0 = tw * TW, cv0 = blockIdx.y * CVB;
+  const __amdgpu_buffer_rsrc_t xr = tensor_rsrc(x, x_bytes);
+
+  uint4 raw[NLOAD];
+#pragma unroll
+  for (int i = 0; i < NLOAD; ++i) {
+    const int c = tid + i * 256;
+    const int pix = c / CVB, cvl = c % CVB;
+    const int ih = pix / IW, iw = pix % IW;
+    const int h = h0 - pad + ih, ww = w0 - pad + iw;
+    const bool ok = c < TOTAL && (unsigned)h < (unsigned)H && (unsigned)ww < (unsigned)W && cv0 + cvl < ncv;
+    raw[i] = buffer_load16(xr, ok ? (unsigned)(((n * H + h) * W + ww) * ncv + cv0 + cvl) * 16u : kOutOfRange);
+  }
+  constexpr int NW = (K * K * CVB + 255) / 256;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    const int c = tid + i * 256;
+    if (c < K * K * CVB) {
+      const int tap = c / CVB, wcv = cv0 + c % CVB;
+      float f[8];
+      if (wcv < ncv) IO<bf16_t>::ld(w + ((long)tap * ncv + wcv) * 8, f);
+      else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f[e] = 0.f;
+      }
+      float* dstw = &wl[((FLIP ? K * K - 1 - tap : tap) * CVB + c % CVB) * 8];
+      *reinterpret_cast<float4*>(dstw) = make_float4(f[0], f[1], f[2], f[3]);
+      *reinterpret_cast<float4*>(dstw + 4) = make_float4(f[4], f[5], f[6], f[7]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NLOAD; ++i) {
+    const int c = tid + i * 256;
+    if (c < TOTAL) *reinterpret_cast<uint4*>(&tile[(c / CVB) * PIXB + (c % CVB) * 16]) = raw[i];
+  }
+  __syncthreads();
+
+  const int cvl = tid % CVB, seg = (tid / CVB) % (TW / WS), th = tid / (CVB * (TW / WS));
+  const int cv = cv0 + cvl;
+  if (cv >= ncv) return;
+  float ea[8], eb[8];                  // folded BN terms, fetched ahead of the taps they follow
+  if (a) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { ea[e] = a[cv * 8 + e]; eb[e] = b[cv * 8 + e]; }
+  }
+  float acc[WS][8];
+#pragma unroll
+  for (int o = 0; o < WS; ++o)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[o][e] = 0.f;
+#pragma unroll 1
+  for (int r = 0; r < K; ++r) {
+    const unsigned char* rowp = &tile[((th + r) * IW + seg * WS) * PIXB + cvl * 16];
+    uint4 in[NIN];
+#pragma unroll
+    for (int j = 0; j < NIN; ++j) in[j] = *reinterpret_cast<const uint4*>(rowp + j * PIXB);
+    float f[K][8];
+#pragma unroll
+    for (int tt = 0; tt < K; ++tt) {
+      const float* wr = &wl[((r * K + tt) * CVB + cvl) * 8];
+      const float4 lo = *reinterpret_cast<const float4*>(wr), hi = *reinterpret_cast<const float4*>(wr + 4);
+      f[tt][0] = lo.x; f[tt][1] = lo.y; f[tt][2] = lo.z; f[tt][3] = lo.w;
+      f[tt][4] = hi.x; f[tt][5] = hi.y; f[tt][6] = hi.z; f[tt][7] = hi.w;
+    }
+#pragma unroll
+    for (int j = 0; j < NIN; ++j) {
+      float v[8];
+      BufIO<bf16_t>::unpack(in[j], v);
+#pragma unroll
+      for (int o = 0; o < WS; ++o) {
+        const int tt = j - o;
+        if (tt < 0 || tt >= K) continue;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[o][e] = fmaf(v[e], f[tt][e], acc[o][e]);
+      }
+    }
+  }
+  const int h = h0 + th;
+  if (h >= H) return;
+#pragma unroll
+  for (int o = 0; o < WS; ++o) {
+    const int ww = w0 + seg * WS + o;
+    if (ww >= W) continue;
+    bf16_t* out = dst + ((((long)n * H + h) * W + ww) * ncv + cv) * 8;
+    if (a) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[o][e] = apply_act(fmaf(acc[o][e], ea[e], eb[e]), act);
+    }
+    if (accumulate) {
+      float old[8];
+      IO<bf16_t>::ld(out, old);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[o][e] += old[e];
+    }
+    IO<bf16_t>::st_t<true>(out, acc[o]);
+  }
+}
+
 // Backward-data in gather form: dx[h,w] (+)= sum_taps dy[(h+pad-r)/st, (w+pad-s)/st] * w[r][s]
 template <class T, int KK>
 __global__ __launch_bounds__(256) void dw_dgrad_kernel(const T* __restrict__ dy, const T* __restrict__ w,

@@ -1077,18 +1077,30 @@ template <class T> struct Exec {
     return dw_stat_groups(c->o.batch, op.out.h, op.out.w, op.cout_p);
   }
   bool dw_mfma(const OpPlan& op) const { return dw_on_mfma(mfma(), op.d.k, op.d.stride, op.d.pad, op.out.h, op.out.w); }
+  // 3 x 3 layers on tensors far larger than the caches with whole 64-channel groups: dw_tile_kernel (not where the forward kernel
+  // also delivers the statistics: 128 x 56 x 56 x 192 80 us against 64 and a pass of 29)
+  bool dw_tiles(const OpPlan& op) const { return dw_mfma(op) && op.d.k == 3 && op.cout_p % 64 == 0 && streams(op.out); }
   // stats (optional; matrix-core kernels only): a mean, a sum of squares about it and a number of pixels per channel and
   // dw_stat_rows(op) groups of outputs; fold (ditto): x is the producing layer's convolution output, normalised as it is staged
   void dw_fwd(const OpPlan& op, const T* x, const T* w, T* y, const float* a, const float* b, int act, NormFold fold = NormFold{},
               float* stats = nullptr) {
     const int N = c->o.batch, ncv = op.cout_p / 8;
     const long nvec = (long)N * op.out.h * op.out.w * ncv;
-    // one profile class per kernel template: mfma (matrix cores), slide (registers), plain
+    // one profile class per kernel template: mfma (matrix cores), tile (LDS), slide (registers), plain
+    const bool tiles = dw_tiles(op) && !stats && !fold.mean;
     char cls[32];
-    snprintf(cls, sizeof cls, "dw_fwd%s_k%d", dw_mfma(op) ? (fold.mean ? "_mfma_bn" : "_mfma") : dw_slides(op) ? (op.d.stride == 1 ? "_slide" : "_slide_s2") : "", op.d.k);
+    snprintf(cls, sizeof cls, "dw_fwd%s_k%d", tiles ? "_tile" : dw_mfma(op) ? (fold.mean ? "_mfma_bn" : "_mfma") : dw_slides(op) ? (op.d.stride == 1 ? "_slide" : "_slide_s2") : "", op.d.k);
     ProfScope ps(c, cls, bytes_of(op.in) + bytes_of(op.out), 2.0 * N * op.out.h * op.out.w * op.d.c_out * op.d.k * op.d.k,
                  net, blk, opi);
     const unsigned xe = (unsigned)((size_t)N * op.in.h * op.in.w * op.cin_p);
+    if (tiles) {
+      if constexpr (sizeof(T) == 2) {
+        const int th = (op.out.h + kDwTileH - 1) / kDwTileH, tw = (op.out.w + kDwTileW - 1) / kDwTileW;
+        launch(c, dw_tile_kernel<false>, dim3(N * th * tw, ncv / kDwTileCv), 256, 0, st, (const bf16_t*)x, (const bf16_t*)w, (bf16_t*)y, a, b, act, 0,
+               N, op.in.h, op.in.w, ncv, th, tw, xe * 2u);
+      }
+      return;
+    }
     if (dw_mfma(op)) {
       if constexpr (sizeof(T) == 2) {
         DwArgs g = dw_args(N, op.out.h, op.out.w, op.cout_p, kDwFwdBlocks);
@@ -1123,11 +1135,19 @@ template <class T> struct Exec {
     // against 11.1; 56 x 56 x 144: 3 x 3 59 against 42, 5 x 5 89 against 48, 7 x 7 101 against 56)
     const bool on_mfma = dw_mfma(op) && (!accumulate || (op.in.h >= 8 && op.in.w >= 12));
     char cls[32];
-    snprintf(cls, sizeof cls, "dw_dgrad%s_k%d", on_mfma ? (accumulate ? "_mfma_acc" : "_mfma") : dw_slides(op) ? (op.d.stride == 1 ? "_slide" : "_s2") : "", op.d.k);
+    snprintf(cls, sizeof cls, "dw_dgrad%s_k%d", dw_tiles(op) ? "_tile" : on_mfma ? (accumulate ? "_mfma_acc" : "_mfma") : dw_slides(op) ? (op.d.stride == 1 ? "_slide" : "_s2") : "", op.d.k);
     ProfScope ps(c, cls, bytes_of(op.in) + bytes_of(op.out), 2.0 * N * op.out.h * op.out.w * op.d.c_out * op.d.k * op.d.k,
                  net, blk, opi);
     const unsigned de = (unsigned)((size_t)N * op.out.h * op.out.w * op.cout_p);
-    if (on_mfma) {                             // mirrored filter over dy
+    if (dw_tiles(op)) {                        // mirrored filter over dy
+      if constexpr (sizeof(T) == 2) {
+        const int th = (op.in.h + kDwTileH - 1) / kDwTileH, tw = (op.in.w + kDwTileW - 1) / kDwTileW;
+        launch(c, dw_tile_kernel<true>, dim3(N * th * tw, ncv / kDwTileCv), 256, 0, st, (const bf16_t*)dy, (const bf16_t*)w, (bf16_t*)dx,
+               (const float*)nullptr, (const float*)nullptr, 0, accumulate ? 1 : 0, N, op.out.h, op.out.w, ncv, th, tw, de * 2u);
+      }
+      return;
+    }
+    if (on_mfma) {                             // the same on the matrix cores
       if constexpr (sizeof(T) == 2) {
         const DwArgs g = dw_args(N, op.in.h, op.in.w, op.cin_p, kDwFwdBlocks);
 #define PBD_DWM(K_) launch(c, accumulate ? dw_mfma_kernel<K_, true, false, false, true> : dw_mfma_kernel<K_, true>, dw_chunks(g) * g.groups, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)w, (bf16_t*)dx, \

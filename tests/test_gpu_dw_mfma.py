@@ -127,3 +127,30 @@ def test_a_second_reader_keeps_the_matrix_cores():
     names = sorted(p["name"] for p in d.get_profile() if p["name"].startswith("dw_dgrad"))
     assert names == ["dw_dgrad_mfma_acc_k3", "dw_dgrad_mfma_acc_k5", "dw_dgrad_mfma_acc_k7", "dw_dgrad_mfma_k3"], names
     local_parity.run_and_check(wl, 3)
+
+
+@pytest.mark.parametrize("n,h,w,c", [(57, 97, 101, 64),        # ragged tiles of 8 x 16, one group of 64 channels
+                                     (68, 56, 72, 128)])       # whole ones, two groups
+def test_three_by_three_on_tensors_beyond_the_caches(n, h, w, c):
+    """From 64 MiB on, whole 64-channel groups: forward without statistics (teacher) and backward-data, storing and adding,
+    run on the tile kernel."""
+    assert n * h * w * c * 2 >= 64 << 20
+    t, b = W.Block(), W.Block()
+    v = t.cba(0, c, 1, act=W.ACT_RELU6)
+    v = t.cba(v, c, 3, groups=c, act=W.ACT_RELU6)
+    t.cba(v, 8, 1, act=W.ACT_NONE)
+    v = b.cba(0, c, 1, act=W.ACT_RELU6)
+    d1 = b.cba(v, c, 3, groups=c, act=W.ACT_RELU6)
+    d2 = b.cba(v, c, 3, groups=c, act=W.ACT_NONE)
+    b.cba(b.add(d1, d2), 8, 1, act=W.ACT_NONE)
+    wl = W.Workload("dw_large", n, (8, h, w), [t], [b], "bf16", lr=0.05)
+    d = parity.make_distiller(wl, n, "bf16")
+    d.set_profile(True)
+    d.teacher_relay(torch.from_numpy(W.make_input(wl, batch=n)).cuda())
+    d.student_step(1, wl.lr)
+    d.sync()
+    names = [p["name"] for p in d.get_profile() if p["name"].startswith(("dw_fwd", "dw_dgrad"))]
+    assert names == ["dw_fwd_tile_k3", "dw_fwd_mfma_k3", "dw_fwd_mfma_k3", "dw_dgrad_tile_k3", "dw_dgrad_tile_k3"], names
+    err = local_parity.teacher_block_error(d, wl, 0, (0, n // 2 + 1, n - 1))
+    assert err < local_parity.TOL_BF16, err
+    local_parity.run_and_check(wl, n, {0: ({1}, {1})})         # one depthwise forward, and the value that both read
