@@ -269,7 +269,9 @@ inline ColGrid bn_bwd_grid(long M, int Cp) { return col_grid(M, Cp, 8, 1024); }
 inline bool dw_on_mfma(bool bf16, int k, int stride, int pad, int h_out, int w_out) {
   return bf16 && (k == 3 || k == 5 || k == 7) && pad == k / 2 && stride == 1 && (k > 3 || (h_out >= 8 && w_out >= 12));
 }
-// Tiles and channel groups of a launch, and how many tiles a workgroup takes so that about `blocks` workgroups result.
+// Tiles and channel groups of a launch, and how many tiles a workgroup takes so that at most `blocks` workgroups result (or one
+// per group).  Not a few more, which would run behind the others on an empty chip: backward-weight of 128 x 17 x 17 x 960, where
+// 30 groups make 780 workgroups of 768, 3 x 3 94 us, 5 x 5 160, 7 x 7 185; 750 of them 81, 127, 145.
 inline DwArgs dw_args(int N, int h, int w, int Cp, int blocks, int tile_h = kDwTile) {
   DwArgs g{};
   g.N = N; g.H = h; g.W = w; g.ncv = Cp / 8;
@@ -277,7 +279,8 @@ inline DwArgs dw_args(int N, int h, int w, int Cp, int blocks, int tile_h = kDwT
   g.tiles_w = (w + kDwTile - 1) / kDwTile;
   g.tiles = N * g.tiles_h * g.tiles_w;
   g.groups = (Cp + kDwCh - 1) / kDwCh;
-  g.per_block = (int)std::max(1L, ((long)g.tiles * g.groups + blocks - 1) / blocks);
+  const int chunks = std::max(1, blocks / g.groups);
+  g.per_block = (g.tiles + chunks - 1) / chunks;
   g.bytes = (unsigned)((size_t)N * h * w * Cp * 2);
   return g;
 }

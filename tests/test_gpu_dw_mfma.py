@@ -154,3 +154,18 @@ def test_three_by_three_on_tensors_beyond_the_caches(n, h, w, c):
     err = local_parity.teacher_block_error(d, wl, 0, (0, n // 2 + 1, n - 1))
     assert err < local_parity.TOL_BF16, err
     local_parity.run_and_check(wl, n, {0: ({1}, {1})})         # one depthwise forward, and the value that both read
+
+
+@pytest.mark.parametrize("k,stride", [(3, 1), (5, 1), (7, 1), (5, 2)])
+def test_many_channel_groups_divide_the_workgroups(k, stride):
+    """Thirty groups of channels, ragged tiles, several tiles a workgroup: the weight gradient against its definition."""
+    n, h, w, c = 60, 17, 19, 960
+    t, b = W.Block(), W.Block()
+    t.cba(0, 16, 1, act=W.ACT_NONE)
+    v = b.cba(0, c, 1, act=W.ACT_RELU6)
+    v = b.cba(v, c, k, stride, groups=c, act=W.ACT_RELU6)
+    b.cba(v, 16, 1, act=W.ACT_NONE)
+    if stride == 2:
+        t.cba(1, 16, 3, 2, act=W.ACT_NONE)
+    wl = W.Workload("dw_groups", n, (8, h, w), [t], [b], "bf16", lr=0.05)
+    local_parity.run_and_check(wl, n, {0: ({1}, {2})})
