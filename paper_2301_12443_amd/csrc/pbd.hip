@@ -263,12 +263,6 @@ ColGrid col_grid(long M, int Cp, int rows_per_thread = 8, int max_blocks = 512) 
 inline ColGrid bn_stats_grid(long M, int Cp) { return col_grid(M, Cp, 8, 1024); }
 inline ColGrid bn_bwd_grid(long M, int Cp) { return col_grid(M, Cp, 8, 1024); }
 
-// Depthwise layers on the matrix cores (bf16, stride 1).  3 x 3: images of at least 8 x 12 (below that a 16 x 16 tile is mostly
-// padding and the sliding-window kernels win: 7 x 7 x 960, batch 128: 12.5 against 18 us; 8 x 8 x 256, batch 256: 6.3 against 9.6);
-// 5 x 5 and 7 x 7: all images (7 x 7 x 640, 5 x 5, batch 33: 6.1 us against 15 on the sliding windows, backward-weight 9.4 against 23).
-inline bool dw_on_mfma(bool bf16, int k, int stride, int pad, int h_out, int w_out) {
-  return bf16 && (k == 3 || k == 5 || k == 7) && pad == k / 2 && stride == 1 && (k > 3 || (h_out >= 8 && w_out >= 12));
-}
 // Tiles and channel groups of a launch, and how many tiles a workgroup takes so that at most `blocks` workgroups result (or one
 // per group).  Not a few more, which would run behind the others on an empty chip: backward-weight of 128 x 17 x 17 x 960, where
 // 30 groups make 780 workgroups of 768, 3 x 3 94 us, 5 x 5 160, 7 x 7 185; 750 of them 81, 127, 145.
@@ -289,14 +283,45 @@ constexpr int kDwFwdBlocks = 2048;      // two rounds of the four workgroups tha
 // groups of outputs whose batch-norm statistics the forward kernel delivers: the two column halves of each workgroup
 inline int dw_stat_groups(int N, int h, int w, int Cp) { return 2 * dw_chunks(dw_args(N, h, w, Cp, kDwFwdBlocks)); }
 
+// Depthwise layers on the matrix cores (bf16, stride 1).  A tile of 16 x 16 costs the same however much of it lies in the image, so
+// small images lose once there are more tiles x groups than the chip holds (below that the launch is as long as one of them, and
+// shorter than on the sliding windows).  3 x 3: images of at least 8 x 12 (7 x 7 x 960, batch 128: 12.5 us on the sliding windows,
+// 18 here; 8 x 8 x 256, batch 256: 6.3 and 9.6).  5 x 5 and 7 x 7, batch 128, backward-data in us on the sliding windows / here:
+//             4 x 4        5 x 5        6 x 6        7 x 7        8 x 8        10 x 10      17 x 17
+//   960, 5:   11.3 / 16.2  14.2 / 16.7  15.6 / 17.2  24.6 / 17.5  25.5 / 17.9  39.6 / 18.9  98 / 59
+//   384, 5:    9.1 /  7.9               11.5 /  8.7  12.3 /  9.0  12.8 /  9.4  15.6 / 10.1  40 / 27
+//   960, 7:   10.5 / 26.7  20.2 / 27.4  20.7 / 28.0  23.5 / 28.6  24.5 / 28.8  45.1 / 29.4  118 / 92
+//   384, 7:    9.6 / 12.7               12.2 / 13.4  12.3 / 13.7  12.5 / 13.9  20.6 / 14.8  47 / 43
+// (192 channels at batch 64: 8.5 to 10 us / 4 to 7).  The forward pass saves the statistics' and the normalisation's passes
+// besides, which decides for 5 x 5 on 6 x 6.
+struct DwLoad { long items; double fill; };       // tiles x channel groups; part of the tiles that lies in the image
+inline DwLoad dw_load(int N, int h, int w, int Cp) {
+  const DwArgs g = dw_args(N, h, w, Cp, 1);
+  return {(long)g.tiles * g.groups, (double)h * w / ((double)g.tiles_h * g.tiles_w * kDwTile * kDwTile)};
+}
+inline bool dw_on_mfma(bool bf16, int N, int h, int w, int Cp, int k, int stride, int pad) {
+  if (!bf16 || pad != k / 2 || stride != 1) return false;
+  const DwLoad l = dw_load(N, h, w, Cp);
+  return k == 3 ? h >= 8 && w >= 12 : k == 5 ? l.items <= 2048 || l.fill >= 1.0 / 8 : k == 7 ? l.items <= 1024 || l.fill > 1.0 / 4 : false;
+}
+// Their backward-weight, which also wins on 3 x 3 images of 8 x 8 but for many of them (128 x 8 x 8 x 960 24.5 against 21.6 us on the
+// column grid; 384 channels 10 against 13), and on smaller ones but for the smallest (2 x 2: 33 x 640, 5 x 5 9.0 against 6.0, 7 x 7 10.6
+// against 8.0; 128 x 4 x 4 x 960, 5 x 5 37 against 32.5, 7 x 7 43 against 41; 128 x 5 x 5 x 960, 5 x 5 36 against 32; 128 x 6 x 6 x
+// 960, 5 x 5 36 against 39; 128 x 4 x 4 x 384, 5 x 5 15 against 24).
+inline bool dw_wgrad_on_mfma(bool bf16, int N, int h, int w, int Cp, int k, int stride, int pad) {
+  if (!bf16 || pad != k / 2 || stride != 1 || (k != 3 && k != 5 && k != 7)) return false;
+  const DwLoad l = dw_load(N, h, w, Cp);
+  if (k == 3) return h >= 8 && w >= 8 && (w >= 12 || l.items <= 2048 || l.fill >= 0.3);
+  return l.fill >= 1.0 / 32 && (l.items <= 2048 || l.fill >= 1.0 / 10);
+}
+
 // Partial results of a depthwise backward-weight: row chunks of the column-grid kernel, or workgroups of
-// dw_wgrad_mfma_kernel (three resident workgroups per compute unit; it also wins on 8-wide images, unlike the forward kernel)
-// or, at stride 2, of dw_wgrad_s2_mfma_kernel.
+// dw_wgrad_mfma_kernel (three resident workgroups per compute unit) or, at stride 2, of dw_wgrad_s2_mfma_kernel.
 struct DwWgradCfg { bool mfma; int chunks; DwArgs m; ColGrid g; };
 inline DwWgradCfg dw_wgrad_cfg(bool bf16, int N, int h_in, int w_in, int h_out, int w_out, int Cp, int k, int stride, int pad) {
   DwWgradCfg w{};
   const long M = (long)N * h_out * w_out;
-  w.mfma = dw_on_mfma(bf16, k, stride, pad, h_out, std::max(w_out, w_out >= 8 ? 12 : 0));
+  w.mfma = dw_wgrad_on_mfma(bf16, N, h_out, w_out, Cp, k, stride, pad);
   if (w.mfma) {
     w.m = dw_args(N, h_out, w_out, Cp, 768);
     w.chunks = dw_chunks(w.m);
@@ -596,7 +621,7 @@ int plan(pbd_ctx* c) {
           const DwWgradCfg gw = dw_wgrad_cfg(bf && !c->o.force_direct, c->o.batch, op.in.h, op.in.w, op.out.h, op.out.w,
                                              op.cout_p, op.d.k, op.d.stride, op.d.pad);
           need_red((size_t)gw.chunks * op.d.k * op.d.k * op.cout_p * 4);
-          if (dw_on_mfma(bf && !c->o.force_direct, op.d.k, op.d.stride, op.d.pad, op.out.h, op.out.w))
+          if (dw_on_mfma(bf && !c->o.force_direct, c->o.batch, op.out.h, op.out.w, op.cout_p, op.d.k, op.d.stride, op.d.pad))
             need_red((size_t)dw_stat_groups(c->o.batch, op.out.h, op.out.w, op.cout_p) * 3 * op.cout_p * 4);
           defer(op, gw.chunks);
         } else if (bf && !c->o.force_direct) {
@@ -730,7 +755,9 @@ int depthwise_reader(const pbd_ctx* c, const BlockPlan& bp, int j) {
   }
   if (uses != 1 || bp.ops[reader].d.type != OP_CBA || !bp.ops[reader].dw) return -1;
   const OpPlan& q = bp.ops[reader];
-  return dw_on_mfma(true, q.d.k, q.d.stride, q.d.pad, q.out.h, q.out.w) ? reader : -1;
+  const int N = c->o.batch;     // (both its passes that read the tensor form it as they stage it)
+  return dw_on_mfma(true, N, q.out.h, q.out.w, q.cout_p, q.d.k, q.d.stride, q.d.pad) &&
+         dw_wgrad_on_mfma(true, N, q.out.h, q.out.w, q.cout_p, q.d.k, q.d.stride, q.d.pad) ? reader : -1;
 }
 
 template <class T> struct Exec {
@@ -1079,7 +1106,7 @@ template <class T> struct Exec {
     if (!op.dw || !dw_mfma(op) || short_column((long)c->o.batch * op.out.h * op.out.w)) return 0;
     return dw_stat_groups(c->o.batch, op.out.h, op.out.w, op.cout_p);
   }
-  bool dw_mfma(const OpPlan& op) const { return dw_on_mfma(mfma(), op.d.k, op.d.stride, op.d.pad, op.out.h, op.out.w); }
+  bool dw_mfma(const OpPlan& op) const { return dw_on_mfma(mfma(), c->o.batch, op.out.h, op.out.w, op.cout_p, op.d.k, op.d.stride, op.d.pad); }
   // 3 x 3 layers on tensors far larger than the caches with whole 64-channel groups: dw_tile_kernel (not where the forward kernel
   // also delivers the statistics: 128 x 56 x 56 x 192 80 us against 64 and a pass of 29)
   bool dw_tiles(const OpPlan& op) const { return dw_mfma(op) && op.d.k == 3 && op.cout_p % 64 == 0 && streams(op.out); }

@@ -169,3 +169,35 @@ def test_many_channel_groups_divide_the_workgroups(k, stride):
         t.cba(1, 16, 3, 2, act=W.ACT_NONE)
     wl = W.Workload("dw_groups", n, (8, h, w), [t], [b], "bf16", lr=0.05)
     local_parity.run_and_check(wl, n, {0: ({1}, {2})})
+
+
+# (batch, h, w, channels, k) where the forward, the folded and the backward-weight kernel part ways: small images, few or many tiles
+@pytest.mark.parametrize("n,h,w,c,k,fwd,wgrad", [
+    (128, 4, 4, 960, 5, "slide", "wgrad"),             # 3840 tiles x groups, 1/16 of them in the image
+    (128, 4, 4, 384, 5, "mfma", "mfma"),               # 1536
+    (128, 5, 5, 960, 7, "slide", "wgrad"),
+    (128, 5, 6, 960, 7, "slide", "mfma"),
+    (100, 7, 8, 384, 7, "slide", "mfma"),              # more than 4096 pixels, and yet the layer in front is not folded
+    (33, 7, 8, 384, 7, "mfma", "mfma"),
+    (9, 2, 2, 40, 5, "mfma", "wgrad"),
+    (1100, 2, 2, 32, 5, "mfma", "wgrad"),              # more than 4096 pixels on the matrix cores, weight gradient not: not folded
+    (128, 6, 6, 960, 5, "mfma_bn", "mfma_bn"),
+    (128, 8, 8, 640, 3, "slide", "wgrad"),
+    (33, 8, 8, 384, 3, "slide", "mfma"),
+])
+def test_small_images(n, h, w, c, k, fwd, wgrad):
+    t, b = W.Block(), W.Block()
+    t.cba(0, 16, 1, act=W.ACT_NONE)
+    v = b.cba(0, c, 1, act=W.ACT_RELU6)
+    v = b.cba(v, c, k, groups=c, act=W.ACT_RELU6)
+    b.cba(v, 16, 1, act=W.ACT_NONE)
+    wl = W.Workload("dw_small", n, (8, h, w), [t], [b], "bf16", lr=0.05)
+    d = parity.make_distiller(wl, n, "bf16")
+    d.teacher_relay(torch.from_numpy(W.make_input(wl, batch=n)).cuda())
+    d.sync()
+    d.set_profile(True)
+    d.student_step(1, wl.lr)
+    names = {p["name"] for p in d.get_profile()}
+    assert f"dw_fwd_{fwd}_k{k}" in names, names
+    assert (f"dw_wgrad_{wgrad}_k{k}" if wgrad != "wgrad" else f"dw_wgrad_k{3 if k == 3 else 7}") in names, names
+    local_parity.run_and_check(wl, n)
