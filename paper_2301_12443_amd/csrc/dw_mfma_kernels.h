@@ -511,7 +511,8 @@ __global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __r
 // x in the tile, A[i][k] = x[y][parity][4 c + i + k] (s = 2 i + parity), B[k][j] = dy[(y >> 1) - j][4 c + k] (r = 2 j + (y & 1)).
 // Tile: 8 x 16 pixels of dy, 32 channels; wave = (16 channels) x (column parity), so no two waves share a tap.
 // Bound by the shifts (vector ALUs) and LDS reads at 8 waves per compute unit; against one thread per 8 channels and filter
-// row (dw_wgrad_kernel): 5 x 5, MobileNetV2 batch 128 69 -> 41 us a launch, batch 33 28 -> 13; 7 x 7, supernet 52 -> 30.
+// row (dw_wgrad_kernel): 5 x 5, MobileNetV2 batch 128 69 -> 41 us a launch, batch 33 28 -> 13; 7 x 7, supernet 52 -> 30.  3 x 3 only
+// wins on few tiles (a third of the products are real there, and the shifts cost the same).
 constexpr int kDwS2TileH = 8;
 template <int K>
 __global__ __launch_bounds__(256, 2) void dw_wgrad_s2_mfma_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,

@@ -295,9 +295,9 @@ inline int dw_stat_groups(int N, int h, int w, int Cp) { return 2 * dw_chunks(dw
 // (192 channels at batch 64: 8.5 to 10 us / 4 to 7).  The forward pass saves the statistics' and the normalisation's passes
 // besides, which decides for 5 x 5 on 6 x 6.
 struct DwLoad { long items; double fill; };       // tiles x channel groups; part of the tiles that lies in the image
-inline DwLoad dw_load(int N, int h, int w, int Cp) {
-  const DwArgs g = dw_args(N, h, w, Cp, 1);
-  return {(long)g.tiles * g.groups, (double)h * w / ((double)g.tiles_h * g.tiles_w * kDwTile * kDwTile)};
+inline DwLoad dw_load(int N, int h, int w, int Cp, int tile_h = kDwTile) {
+  const DwArgs g = dw_args(N, h, w, Cp, 1, tile_h);
+  return {(long)g.tiles * g.groups, (double)h * w / ((double)g.tiles_h * g.tiles_w * tile_h * kDwTile)};
 }
 inline bool dw_on_mfma(bool bf16, int N, int h, int w, int Cp, int k, int stride, int pad) {
   if (!bf16 || pad != k / 2 || stride != 1) return false;
@@ -314,6 +314,15 @@ inline bool dw_wgrad_on_mfma(bool bf16, int N, int h, int w, int Cp, int k, int 
   if (k == 3) return h >= 8 && w >= 8 && (w >= 12 || l.items <= 2048 || l.fill >= 0.3);
   return l.fill >= 1.0 / 32 && (l.items <= 2048 || l.fill >= 1.0 / 10);
 }
+// Backward-weight at stride 2 (h, w of the output; tiles of 8 x 16).  3 x 3 has nine taps to the column grid's three passes over the
+// image and only wins while the launch is latency: 33 x 25 x 25 x 192 8.0 against 10.0 us, but 128 x 112 x 112 x 96 113 against 81,
+// 128 x 56 x 56 x 144 50 and 30, 128 x 14 x 14 x 960 33 and 20.  5 x 5 and 7 x 7 win but on many tiny images: 128 x 14 x 14 x 960 35
+// against 49 and 39 against 65; 128 x 7 x 7 x 960 35 against 28 and 39 against 38; 128 x 4 x 4 x 960 36 against 23 and 40 against 31.
+inline bool dw_wgrad_s2_on_mfma(bool bf16, int N, int h, int w, int Cp, int k, int stride, int pad) {
+  if (!bf16 || pad != k / 2 || stride != 2 || (k != 3 && k != 5 && k != 7)) return false;
+  const DwLoad l = dw_load(N, h, w, Cp, kDwS2TileH);
+  return k == 3 ? l.items <= 512 : l.items <= 2048 || l.fill >= 1.0 / 6;
+}
 
 // Partial results of a depthwise backward-weight: row chunks of the column-grid kernel, or workgroups of
 // dw_wgrad_mfma_kernel (three resident workgroups per compute unit) or, at stride 2, of dw_wgrad_s2_mfma_kernel.
@@ -325,7 +334,7 @@ inline DwWgradCfg dw_wgrad_cfg(bool bf16, int N, int h_in, int w_in, int h_out, 
   if (w.mfma) {
     w.m = dw_args(N, h_out, w_out, Cp, 768);
     w.chunks = dw_chunks(w.m);
-  } else if (bf16 && (k == 3 || k == 5 || k == 7) && pad == k / 2 && stride == 2) {
+  } else if (dw_wgrad_s2_on_mfma(bf16, N, h_out, w_out, Cp, k, stride, pad)) {
     w.mfma = true;
     w.m = dw_args(N, h_out, w_out, Cp, 512, kDwS2TileH);      // (two resident workgroups per compute unit)
     w.m.P = h_out; w.m.Q = w_out; w.m.dy_bytes = w.m.bytes;

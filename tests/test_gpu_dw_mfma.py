@@ -201,3 +201,28 @@ def test_small_images(n, h, w, c, k, fwd, wgrad):
     assert f"dw_fwd_{fwd}_k{k}" in names, names
     assert (f"dw_wgrad_{wgrad}_k{k}" if wgrad != "wgrad" else f"dw_wgrad_k{3 if k == 3 else 7}") in names, names
     local_parity.run_and_check(wl, n)
+
+
+# (batch, h, w, channels, k, kernel class of the stride-2 weight gradient): both sides of its rule
+@pytest.mark.parametrize("n,h,w,c,k,wgrad", [
+    (5, 25, 25, 192, 3, "dw_wgrad_s2_mfma_k3"),
+    (33, 49, 33, 40, 3, "dw_wgrad_k3"),
+    (33, 49, 33, 40, 5, "dw_wgrad_s2_mfma_k5"),
+    (128, 4, 4, 640, 5, "dw_wgrad_k7"),
+    (128, 9, 11, 640, 7, "dw_wgrad_s2_mfma_k7"),
+])
+def test_stride_two_weight_gradient(n, h, w, c, k, wgrad):
+    t, b = W.Block(), W.Block()
+    t.cba(0, 16, 1, 2, act=W.ACT_NONE)
+    v = b.cba(0, c, 1, act=W.ACT_RELU6)
+    v = b.cba(v, c, k, 2, groups=c, act=W.ACT_RELU6)
+    b.cba(v, 16, 1, act=W.ACT_NONE)
+    wl = W.Workload("dw_s2", n, (8, h, w), [t], [b], "bf16", lr=0.05)
+    d = parity.make_distiller(wl, n, "bf16")
+    d.teacher_relay(torch.from_numpy(W.make_input(wl, batch=n)).cuda())
+    d.sync()
+    d.set_profile(True)
+    d.student_step(1, wl.lr)
+    names = {p["name"] for p in d.get_profile()}
+    assert wgrad in names, names
+    local_parity.run_and_check(wl, n)
