@@ -6,9 +6,12 @@
 // so four output columns meet K + 3 input columns in NT = ceil((K + 3) / 4) products per filter row: 28 of 48
 // multiply-adds are real at K = 7, 20 of 32 at K = 5, 12 of 32 at K = 3, at 128 multiply-adds a cycle and SIMD against
 // 16 of the vector ALUs.  Products of bf16 numbers are exact in float32 and sums are kept there, as in the kernels on the
-// vector ALUs.  (A tap outside the filter is a product with zero: an infinity or NaN among the inputs can reach
-// outputs up to three columns further than the filter does.  Inputs of these layers are outputs of a rectifier or of a
-// normalisation over the batch, where it would have spread to the whole channel.)
+// vector ALUs.
+//  A tap outside the filter is a product with zero, which an infinity or NaN among the inputs turns into NaN, up to three columns
+// further than the filter reaches.  The forward pass of a layer whose normalisation is folded in (the frozen teacher's, with
+// running statistics) therefore forms every result that came out as NaN once more from the filter's own taps.  In a student's
+// layer the value goes into the batch statistics, and the whole channel is NaN either way; so is, in its backward pass, the
+// gradient of the whole channel.
 //
 // Layout.  An operand lane holds four consecutive pixels of ONE channel, so tiles lie in LDS channel by channel,
 // [channel][row][column]; the 4 pixels x 8 channels that a thread loads (four 16-byte chunks) are transposed in
@@ -262,6 +265,34 @@ __global__ __launch_bounds__(256, K == 7 || ACC ? 3 : 4) void dw_mfma_kernel(con
           }
         }
       }
+
+    if constexpr (!FLIP && !FOLD && !STATS) {
+      float s = 0.f;                                     // NaN if any of them is (or infinities cancel)
+#pragma unroll
+      for (int o = 0; o < 4; ++o)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int m = 0; m < 4; ++m) s += acc[o][q][m];
+      if (s != s && cv0 * 8 + ch < g.ncv * 8) {
+#pragma unroll
+        for (int o = 0; o < 4; ++o)
+#pragma unroll
+          for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+              if (acc[o][q][m] == acc[o][q][m]) continue;
+              float v = 0.f;
+#pragma unroll 1
+              for (int i = 0; i < K * K; ++i) {
+                const int r = i / K, t = i % K;
+                v = fmaf((float)*reinterpret_cast<const bf16_t*>(in + (o + r) * G::ROWP + (4 * q + m + t) * 2),
+                         (float)w[(size_t)i * g.ncv * 8 + cv0 * 8 + ch], v);
+              }
+              acc[o][q][m] = v;
+            }
+      }
+    }
 
     // ---- output through LDS: pixel-major, then 16-byte stores ----
     if (a) {                                             // folded inference-mode BN + activation (teacher)

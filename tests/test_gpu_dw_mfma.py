@@ -226,3 +226,31 @@ def test_stride_two_weight_gradient(n, h, w, c, k, wgrad):
     names = {p["name"] for p in d.get_profile()}
     assert wgrad in names, names
     local_parity.run_and_check(wl, n)
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("k", [3, 5, 7])
+def test_a_non_finite_input_stays_within_the_filter(k, bad):
+    """One infinity or NaN per image in what a frozen teacher's depthwise layer reads reaches the k x k outputs around it and
+    no other, as in the plain kernels (force_direct): at tile edges, at the image's edge, inside."""
+    n, h, w, c = 6, 18, 35, 40
+    t, s = W.Block(), W.Block()
+    t.cba(0, c, k, groups=c, act=W.ACT_NONE)
+    s.cba(0, c, 1, act=W.ACT_NONE)
+    wl = W.Workload("dw_inf", n, (c, h, w), [t], [s], "bf16", lr=0.05)
+    x = W.make_input(wl, batch=n).copy()
+    near = np.zeros((n, c, h, w), dtype=bool)
+    for i, (p, q) in enumerate([(0, 0), (7, 7), (15, 16), (17, 34), (16, 31), (9, 20)]):
+        x[i, 3 + i, p, q] = bad
+        near[i, 3 + i, max(0, p - k // 2):p + k // 2 + 1, max(0, q - k // 2):q + k // 2 + 1] = True
+    out = []
+    for direct in (True, False):
+        d = parity.make_distiller(wl, n, "bf16", force_direct=direct)
+        d.teacher_relay(torch.from_numpy(x).cuda())
+        d.sync()
+        out.append(d.read_act(1))
+    ref, got = out
+    np.testing.assert_array_equal(~np.isfinite(ref), near)
+    np.testing.assert_array_equal(got[near], ref[near])
+    assert np.isfinite(got[~near]).all()
+    assert local_parity._max_rel(got[~near], ref[~near]) < 2.0 ** -7       # (two roundings to bfloat16 of float32 sums)
