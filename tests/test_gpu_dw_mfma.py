@@ -1,9 +1,8 @@
 """Depthwise convolutions on the matrix cores (dw_mfma_kernel, dw_wgrad_mfma_kernel, dw_wgrad_s2_mfma_kernel) at the edges
 of their tiles of 16 x 16 or 8 x 16 pixels x 32 channels: every operation of a one-block step, and the teacher's folded form, against the plain fp64 oracle
 primitives on the tensors that the library read (local_parity.py).  Its bounds: one bfloat16 rounding of a result (2^-9 of
-it, 2e-2 of the largest allowed) forward and backward-data; the weight gradient is float32, a sum of n products of
-bfloat16 numbers, off by at most n 2^-24 of the sum of their magnitudes - a wrong tap, shift or mask is off by the size of
-the result."""
+it, 2e-2 of the largest allowed) forward and backward-data; the weight gradient is a float32 sum of products of bfloat16 numbers
+(exact), held to TOL_DW - a wrong tap, shift or mask is off by the size of the result."""
 import numpy as np
 import pytest
 import torch
@@ -14,6 +13,21 @@ from paper_2301_12443_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
+# A weight gradient sums n products in chains of at most d = 400 additions (176 of a tile, the tiles of a workgroup, a lane's share
+# of the workgroups), so it is off by at most d 2^-24 of the sum of the products' magnitudes.  With random signs that sum is
+# at most 0.4 sqrt(n) times the largest of a layer's components (mean magnitude of a product 0.64, the largest of some hundred
+# sums 2 sqrt(n) and more): 400 x 6e-8 x 0.4 x sqrt(n), 3e-3 at the 3e5 pixels of the largest layer here.  A lost or doubled
+# part of 1 % of the pixels shows as sqrt(0.01) = 10 %, of 0.01 % as 1 %.
+TOL_DW = 3e-3
+
+
+def _tiles_per_workgroup(n, h, w, c, blocks, tile_h=16):
+    """How many tiles one workgroup of a launch of at most `blocks` takes (2048 forward and backward-data, 768 weight gradient, 512
+    weight gradient at stride 2)."""
+    tiles, chunks = n * -(-h // tile_h) * -(-w // 16), max(1, blocks // -(-c // 32))
+    return -(-tiles // chunks)
+
+
 # (batch, h, w, channels, k, stride)
 SHAPES = [
     (1, 8, 12, 8, 3, 1),         # the smallest image, one vector of channels
@@ -22,7 +36,10 @@ SHAPES = [
     (1, 15, 31, 32, 3, 1),       # one short of a tile both ways
     (2, 14, 14, 144, 5, 1),      # the late layers: one ragged tile
     (1, 49, 13, 24, 7, 1),       # three tiles and a row
-    (40, 32, 20, 96, 7, 1),      # several tiles per workgroup, forward and backward
+    (40, 32, 20, 96, 7, 1),      # three groups, an empty right half
+    (260, 33, 37, 8, 3, 1),      # several tiles per workgroup, forward and backward, ragged both ways
+    (260, 33, 37, 8, 5, 1),
+    (260, 33, 37, 8, 7, 1),
     (3, 9, 8, 64, 3, 1),         # 8 wide: only the weight gradient takes the matrix cores
     (2, 31, 47, 16, 5, 1),       # half a channel group
     (5, 4, 5, 40, 5, 1),      # a corner of a tile
@@ -46,8 +63,12 @@ def test_every_operation_of_a_small_block(n, h, w, c, k, stride):
     d1 = b.cba(v, c, k, stride, groups=c, act=W.ACT_RELU6)
     d2 = b.cba(v, c, 3, stride, groups=c, act=W.ACT_NONE)
     b.cba(b.add(d1, d2), 16, 1, act=W.ACT_NONE)
+    if n == 260:
+        assert _tiles_per_workgroup(n, h, w, c, 2048) == 2 and _tiles_per_workgroup(n, h, w, c, 768) == 4
+    if n == 60:
+        assert _tiles_per_workgroup(n, (h + 1) // 2, (w + 1) // 2, c, 512, 8) == 3
     wl = W.Workload("dw_mfma", n, (8, h, w), [t], [b], "bf16", lr=0.05)
-    worst = local_parity.run_and_check(wl, n)
+    worst = local_parity.run_and_check(wl, n, tol_dw=TOL_DW)
     print(", ".join(f"{key} {e:.1e}" for key, e in sorted(worst.items())), flush=True)
 
 
@@ -58,6 +79,9 @@ FOLDED = [
     (6, 29, 27, 72, 5, W.ACT_RELU),
     (17, 17, 16, 24, 7, W.ACT_RELU6),
     (100, 7, 7, 48, 5, W.ACT_RELU6),
+    (250, 35, 40, 24, 3, W.ACT_RELU),      # several tiles per workgroup, ragged, the last ones' right half empty
+    (250, 35, 40, 24, 5, W.ACT_RELU6),
+    (250, 35, 40, 24, 7, W.ACT_RELU6),
 ]
 
 
@@ -68,8 +92,10 @@ def test_normalisation_in_the_staging(n, h, w, c, k, act):
     v = b.cba(0, c, 1, act=act)
     v = b.cba(v, c, k, groups=c, act=W.ACT_RELU6)
     b.cba(v, 16, 1, act=W.ACT_NONE)
+    if n == 250:
+        assert _tiles_per_workgroup(n, h, w, c, 2048) == 2 and _tiles_per_workgroup(n, h, w, c, 768) == 3
     wl = W.Workload("dw_folded", n, (8, h, w), [t], [b], "bf16", lr=0.05)
-    worst = local_parity.run_and_check(wl, n)     # (reads the value between the two layers: formed on request, after the update)
+    worst = local_parity.run_and_check(wl, n, tol_dw=TOL_DW)     # (reads the value between the two layers: formed on request, after the update)
     print(", ".join(f"{key} {e:.1e}" for key, e in sorted(worst.items())), flush=True)
 
 
@@ -83,8 +109,7 @@ def test_statistics_of_channels_far_from_zero(k, folded):
     n, h, w = 11000, 16, 40
     top = np.array([251, 241, 231, 221, 201, 191, 181, 171], dtype=np.float32)
     c = top.size
-    tiles, groups = n * ((h + 15) // 16) * ((w + 15) // 16), (c + 31) // 32
-    assert -(-tiles * groups // 2048) == 17                    # tiles a workgroup
+    assert _tiles_per_workgroup(n, h, w, c, 2048) == 17
     t, b = W.Block(), W.Block()
     t.cba(0, 16, 1, act=W.ACT_NONE)
     v = b.cba(0, c, 1, act=W.ACT_RELU) if folded else 0        # (a rectified value is normalised in the staging: top - 1 +- 1)
@@ -126,7 +151,7 @@ def test_a_second_reader_keeps_the_matrix_cores():
     d.student_step(1, wl.lr)
     names = sorted(p["name"] for p in d.get_profile() if p["name"].startswith("dw_dgrad"))
     assert names == ["dw_dgrad_mfma_acc_k3", "dw_dgrad_mfma_acc_k5", "dw_dgrad_mfma_acc_k7", "dw_dgrad_mfma_k3"], names
-    local_parity.run_and_check(wl, 3)
+    local_parity.run_and_check(wl, 3, tol_dw=TOL_DW)
 
 
 @pytest.mark.parametrize("n,h,w,c", [(57, 97, 101, 64),        # ragged tiles of 8 x 16, one group of 64 channels
@@ -158,7 +183,7 @@ def test_three_by_three_on_tensors_beyond_the_caches(n, h, w, c):
 
 @pytest.mark.parametrize("k,stride", [(3, 1), (5, 1), (7, 1), (5, 2)])
 def test_many_channel_groups_divide_the_workgroups(k, stride):
-    """Thirty groups of channels, ragged tiles, several tiles a workgroup: the weight gradient against its definition."""
+    """Thirty groups of channels, ragged tiles, several tiles a workgroup: one layer, forward and backward."""
     n, h, w, c = 60, 17, 19, 960
     t, b = W.Block(), W.Block()
     t.cba(0, 16, 1, act=W.ACT_NONE)
@@ -168,7 +193,7 @@ def test_many_channel_groups_divide_the_workgroups(k, stride):
     if stride == 2:
         t.cba(1, 16, 3, 2, act=W.ACT_NONE)
     wl = W.Workload("dw_groups", n, (8, h, w), [t], [b], "bf16", lr=0.05)
-    local_parity.run_and_check(wl, n, {0: ({1}, {2})})
+    local_parity.run_and_check(wl, n, {0: ({1}, {1, 2})}, tol_dw=TOL_DW)
 
 
 # (batch, h, w, channels, k) where the forward, the folded and the backward-weight kernel part ways: small images, few or many tiles
@@ -200,7 +225,7 @@ def test_small_images(n, h, w, c, k, fwd, wgrad):
     names = {p["name"] for p in d.get_profile()}
     assert f"dw_fwd_{fwd}_k{k}" in names, names
     assert (f"dw_wgrad_{wgrad}_k{k}" if wgrad != "wgrad" else f"dw_wgrad_k{3 if k == 3 else 7}") in names, names
-    local_parity.run_and_check(wl, n)
+    local_parity.run_and_check(wl, n, tol_dw=TOL_DW)
 
 
 # (batch, h, w, channels, k, kernel class of the stride-2 weight gradient): both sides of its rule
@@ -225,7 +250,7 @@ def test_stride_two_weight_gradient(n, h, w, c, k, wgrad):
     d.student_step(1, wl.lr)
     names = {p["name"] for p in d.get_profile()}
     assert wgrad in names, names
-    local_parity.run_and_check(wl, n)
+    local_parity.run_and_check(wl, n, tol_dw=TOL_DW)
 
 
 @pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
