@@ -17,6 +17,7 @@ PEAK_BF16_TFLOPS = 2500.0    # MI355X dense bf16 MFMA
 # fp32 vector FMA without packed instructions (this build must compile them out): 256 CUs x 4 SIMDs
 # x 16 lanes x 2 flop x 2.4 GHz; the published 157.3 TFLOP/s counts the packed form
 PEAK_FP32_VALU_TFLOPS = 78.6
+PEAK_FP32_MFMA_TFLOPS = 157.3  # fp32 MFMA: 256 CUs x 4 SIMDs x 64 flop x 2.4 GHz
 LR_ALPHA = 0.005          # learning rate of the architecture parameters in the arch / two_round modes
 
 # HBM bytes per launch (mean over a kernel class's launches in one step) from rocprofv3 --pmc
@@ -41,22 +42,29 @@ HBM_TRAFFIC_PER_LAUNCH = {
 CPU_BASELINE_BATCH = {"tiny_cnn": 8, "vgg16_dsconv": 256, "mbv2_mbconv_k5e4": 8, "mbv2_supernet": 2, "resnet50_x1.5": 2}
 
 CONV_PREFIXES = ("igemm_", "wgrad_")
+
+
+def mfma_peak(name):
+    """Peak of the matrix cores for a convolution class, by the type of its operands."""
+    return PEAK_FP32_MFMA_TFLOPS if name.startswith(("igemm_f32_", "wgrad_f32_")) else PEAK_BF16_TFLOPS
+
+
 # the bandwidth-bound families: normalisation, depthwise, joins, pooling, loss, update, casts, partial sums
 EW_PREFIXES = ("bn_", "dw_", "join_", "maxpool_", "mse_", "sgd_", "cast_", "sum_partials", "splitk_", "transpose_", "mix_")
 
 
 def family_fractions(prof, steps):
     """The two halves of the metric besides samples/s: the convolutions (implicit GEMM forward / backward-data
-    and backward-weight launches) as a time-weighted TFLOP/s against the bf16 MFMA peak, and the bandwidth-bound
+    and backward-weight launches) as a time-weighted TFLOP/s against the MFMA peak of their type, and the bandwidth-bound
     families (normalisation, depthwise, joins, pooling, loss, update) as GB/s of algorithmic bytes against the
     HBM peak.  Convolutions are given three ways: all launches, those whose own arithmetic intensity is above
     the MFMA ridge (the matrix-core-bound ones, which the 50 % target is about) and those below it (bandwidth-
     bound 1x1 layers and stems, as GB/s)."""
-    ridge = PEAK_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9)
     acc = {k: dict(ms=0.0, bytes=0.0, flops=0.0, n=0) for k in ("conv", "conv_hi", "conv_lo", "ew")}
     for p in prof:
         keys = []
         if p["name"].startswith(CONV_PREFIXES):
+            ridge = mfma_peak(p["name"]) * 1e12 / (PEAK_HBM_GBS * 1e9)
             keys = ["conv", "conv_hi" if p["bytes"] and p["flops"] / p["bytes"] >= ridge else "conv_lo"]
         elif p["name"].startswith(EW_PREFIXES):
             keys = ["ew"]
@@ -70,9 +78,12 @@ def family_fractions(prof, steps):
     def gb(a):
         return a["bytes"] / (a["ms"] * 1e-3) / 1e9 if a["ms"] else 0.0
 
+    # (a workload's convolutions are all of one type)
+    peak = next((mfma_peak(p["name"]) for p in prof if p["name"].startswith(CONV_PREFIXES)), PEAK_BF16_TFLOPS)
+
     def conv_entry(a):
         return dict(ms_per_step=round(a["ms"] / steps, 4), launches_per_step=a["n"] // steps,
-                    TFLOPs=round(tf(a), 2), frac_of_mfma_peak=round(tf(a) / PEAK_BF16_TFLOPS, 4),
+                    TFLOPs=round(tf(a), 2), frac_of_mfma_peak=round(tf(a) / peak, 4),
                     GBs=round(gb(a), 1), frac_of_hbm_peak=round(gb(a) / PEAK_HBM_GBS, 4))
     conv = conv_entry(acc["conv"])
     conv["above_ridge"] = conv_entry(acc["conv_hi"])
@@ -86,17 +97,18 @@ def family_fractions(prof, steps):
 def roofline_from_profile(prof, steps):
     """Aggregate the library's per-launch HIP-event timings by kernel class; report the class that
     takes the most time against the roofline that bounds it."""
-    ridge_mfma = PEAK_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9)
     ridge_alu = PEAK_FP32_VALU_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9)
 
     def bound_of(p):
         # contractions (implicit GEMM, weight gradient) run on the matrix cores; depthwise kernels do
-        # their multiply-adds on the vector ALUs; everything else only moves bytes.  A launch counts
-        # against the compute peak only when its own arithmetic intensity lies above the ridge.
+        # their multiply-adds on the vector ALUs, except the *_mfma classes, whose small matrix products have
+        # a peak (0.63 PFLOP/s, products by zero included) that no filter of 7 x 7 and less reaches before
+        # memory does; everything else only moves bytes.  A launch counts against the compute peak only
+        # when its own arithmetic intensity lies above the ridge.
         ai = p["flops"] / p["bytes"] if p["bytes"] else 0.0
-        if p["name"].startswith(("igemm_", "wgrad_")) and ai >= ridge_mfma:
+        if p["name"].startswith(CONV_PREFIXES) and ai >= mfma_peak(p["name"]) * 1e12 / (PEAK_HBM_GBS * 1e9):
             return "mfma"
-        if p["name"].startswith("dw_") and ai >= ridge_alu:
+        if p["name"].startswith("dw_") and "_mfma" not in p["name"] and ai >= ridge_alu:
             return "alu"
         return "hbm"
 
@@ -112,7 +124,7 @@ def roofline_from_profile(prof, steps):
     bound, a = max(((k[1], v) for k, v in groups.items() if k[0] == name), key=lambda kv: kv[1]["ms"])
     avg_s = a["ms"] / a["n"] * 1e-3
     if bound == "mfma":
-        achieved, peak, unit = a["flops"] / a["n"] / avg_s / 1e12, PEAK_BF16_TFLOPS, "TFLOP/s"
+        achieved, peak, unit = a["flops"] / a["n"] / avg_s / 1e12, mfma_peak(name), "TFLOP/s"
     elif bound == "alu":
         achieved, peak, unit = a["flops"] / a["n"] / avg_s / 1e12, PEAK_FP32_VALU_TFLOPS, "TFLOP/s"
     else:

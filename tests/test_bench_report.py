@@ -44,12 +44,31 @@ def test_contraction_counts_against_mfma_only_above_the_ridge():
 
 def test_depthwise_counts_against_the_vector_alu_peak():
     ridge = bench.PEAK_FP32_VALU_TFLOPS * 1e12 / (bench.PEAK_HBM_GBS * 1e9)
-    k7 = _entry("dw_fwd_tile_k7", 0.070, 100e6, 100e6 * ridge * 2.5)
+    k7 = _entry("dw_fwd_slide_k7", 0.070, 100e6, 100e6 * ridge * 2.5)
     k3 = _entry("dw_fwd_tile_k3", 0.030, 100e6, 100e6 * ridge * 0.4)
     roof, _, _ = bench.roofline_from_profile([k7, k3], 1)
-    assert roof["kernel"] == "dw_fwd_tile_k7" and roof["bound"] == "alu" and roof["peak"] == bench.PEAK_FP32_VALU_TFLOPS
+    assert roof["kernel"] == "dw_fwd_slide_k7" and roof["bound"] == "alu" and roof["peak"] == bench.PEAK_FP32_VALU_TFLOPS
     roof, _, _ = bench.roofline_from_profile([k3], 1)
     assert roof["bound"] == "hbm"
+
+
+@pytest.mark.parametrize("name", ["dw_fwd_mfma_k7", "dw_fwd_mfma_bn_k7", "dw_dgrad_mfma_acc_k7", "dw_wgrad_s2_mfma_k7"])
+def test_depthwise_on_the_matrix_cores_counts_against_hbm(name):
+    # 96 MB in and out, 49 multiply-adds an element, in 37 us: 1.6 times the vector ALUs' peak
+    e = _entry(name, 0.037, 192e6, 96e6 / 2 * 49 * 2)
+    roof, _, _ = bench.roofline_from_profile([e], 1)
+    assert roof["bound"] == "hbm" and roof["frac"] == pytest.approx(192e6 / 37e-6 / 1e9 / bench.PEAK_HBM_GBS, abs=1e-4)
+
+
+@pytest.mark.parametrize("name", ["igemm_f32_fwd_64", "igemm_f32_dgrad_32", "wgrad_f32_32"])
+def test_float32_convolutions_count_against_the_fp32_matrix_cores(name):
+    ridge = bench.PEAK_FP32_MFMA_TFLOPS * 1e12 / (bench.PEAK_HBM_GBS * 1e9)
+    e = _entry(name, 0.060, 10e6, 10e6 * ridge * 8)                # (far below the bf16 ridge)
+    roof, _, _ = bench.roofline_from_profile([e], 1)
+    assert roof["bound"] == "mfma" and roof["peak"] == bench.PEAK_FP32_MFMA_TFLOPS
+    conv, _ = bench.family_fractions([e], 1)
+    assert conv["above_ridge"]["launches_per_step"] == 1
+    assert conv["frac_of_mfma_peak"] == pytest.approx(conv["TFLOPs"] / bench.PEAK_FP32_MFMA_TFLOPS, abs=1e-4)
 
 
 def test_more_than_one_gpu_is_refused(monkeypatch, capsys):
@@ -100,7 +119,7 @@ def test_family_fractions_split_convolutions_at_the_ridge():
     hi = _entry("igemm_fwd_128x128_store", 0.200, 100e6, 100e6 * ridge * 4)
     lo = _entry("wgrad_128x128", 0.100, 400e6, 400e6 * ridge / 4)
     bn = _entry("bn_apply", 0.050, 300e6)
-    dw = _entry("dw_fwd_tile_k5", 0.150, 500e6, 1e9)
+    dw = _entry("dw_fwd_mfma_k5", 0.150, 500e6, 1e9)
     other = _entry("unknown_kernel", 1.0, 1e6)
     conv, ew = bench.family_fractions([hi, lo, bn, dw, other] * 2, 2)
     assert conv["launches_per_step"] == 2 and conv["ms_per_step"] == pytest.approx(0.300)
