@@ -116,8 +116,9 @@ struct DwArgs {
 // y = x * w (FLIP: mirrored filter, the backward-data pass of the same layer), optionally a folded batch norm and
 // activation behind it.
 // Bound by the latency of load - stage - multiply - stage - store at three to four workgroups per compute unit (no unit is
-// busy all the time).  Launch averages over the supernet step (batch 64, 96 MB in and out each) against a tile kernel on
-// the vector ALUs: 7 x 7 72 -> 37 us, 5 x 5 40 -> 30, 3 x 3 24.4 -> 24.7 (and MobileNetV2's at batch 33: 11.6 -> 8.3).
+// busy all the time).  Launch averages over the supernet step (batch 64) against a tile kernel on the vector ALUs: backward-data
+// 7 x 7 72 -> 34 us, 5 x 5 41 -> 24, 3 x 3 26 -> 20; forward with FOLD and STATS, two passes over the tensor less beside it,
+// 73 -> 44, 41 -> 34, 25 -> 31 (MobileNetV2's teacher at batch 33, plain 3 x 3 forward: 11.1 -> 8.5).
 // Stores go through the caches whatever the tensor's size: a workgroup writes 64 of the 128 bytes of a line, its neighbour the
 // others, and past the caches the halves reach memory one by one (128 x 56 x 56 x 144, 3 x 3: backward-data 97 us nontemporal, 60
 // through the caches; 128 x 40 x 40 x 384, 7 x 7 120 and 111; the supernet step 41.21 and 41.03 ms).
@@ -383,8 +384,8 @@ __global__ __launch_bounds__(256, K == 7 || ACC ? 3 : 4) void dw_mfma_kernel(con
 // x and dy are read once for all taps.  A shifted quad of x meets dy's quads c (it = 0) and c - 1 (it = 1).  Rows of dy
 // outside the tile are a row of zeros.  A workgroup walks per_block tiles with its accumulators in registers; the two
 // column halves meet in LDS at the end; one partial result per workgroup as in the other kernels.  Bound by the shifts and
-// LDS reads.  Launch averages over the supernet step against a tile kernel on the vector ALUs: 7 x 7 90 -> 39 us, 5 x 5
-// 72 -> 35, 3 x 3 37 -> 26.
+// LDS reads.  Launch averages over the supernet step, with FOLD, against a tile kernel on the vector ALUs that read the
+// normalised tensor: 7 x 7 91 -> 47 us, 5 x 5 72 -> 41, 3 x 3 37 -> 32.
 template <int K, bool FOLD = false>
 __global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
                                                                float* __restrict__ part, DwArgs g, NormFold fold) {

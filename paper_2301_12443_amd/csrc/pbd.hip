@@ -457,7 +457,8 @@ DmaCfg dma_cfg(long M, int NC, int Kred, int CA, int num_cu, int epi) {
     if (narrow && bn > 128) continue;
     const long tn = (NC + bn - 1) / bn, T = tm * tn;
     // narrow tiles: two resident workgroups per unit, unless the launch does not give every unit one (then each runs alone:
-    // 16660 rows, 384 -> 384, 3 x 3: 396 tiles of 64 columns 55.8 us, 198 of 128 columns 46.8)
+    // 16660 rows, 384 -> 384, 3 x 3: 396 tiles of 64 columns 55.8 us, 198 of 128 columns 46.8; resnet50_x1.5 block 3 at batch 85
+    // 3617 -> 3570 us, its whole step at batch 64 9.31 -> 9.21 ms)
     const long slots = (bn <= 128 && T > num_cu ? 2 : 1) * (long)num_cu;
     const long full = T / slots, r = T % slots;
     double rounds = (double)full;
@@ -468,8 +469,9 @@ DmaCfg dma_cfg(long M, int NC, int Kred, int CA, int num_cu, int epi) {
   // K step 64 (128-byte rows) for the wide tiles; the narrow ones take 32, whose three stages fit twice in a
   // compute unit's LDS, so that two workgroups hide each other's fill, barriers and store
   // (256 x 56 x 56 x 64 -> 64, 3 x 3: 129 -> 113 us; 256 -> 96, 1 x 1: 152 -> 124 us).  A launch of at most one tile per unit
-  // has nobody to hide behind: 128 columns take the longer step then (resnet50_x1.5 block 3 at batch 85 3594 -> 3482 us; with
-  // 96 and 64 columns too the same block stays at 3504 against 3508 and the whole step at batch 64 loses 9.49 -> 9.56 ms).
+  // has nobody to hide behind: 128 columns take the longer step then (the same block 3570 -> 3470 us, the teacher's relay at batch
+  // 256 4.74 -> 4.70 ms, both sides in turn on one machine; with 96 and 64 columns too the block stays and the whole step at
+  // batch 64 loses 0.7 %).
   const long T = tm * d.tiles_n;
   d.BK = CA % 64 == 0 && (d.BN >= 192 || (d.BN == 128 && T <= num_cu)) ? 64 : 32;
   if (T < num_cu * 7 / 10) return d;       // (use stays false)
