@@ -456,10 +456,16 @@ DmaCfg dma_cfg(long M, int NC, int Kred, int CA, int num_cu, int epi) {
     const int bn = kBN[i];
     if (narrow && bn > 128) continue;
     const long tn = (NC + bn - 1) / bn, T = tm * tn;
-    // narrow tiles: two resident workgroups per unit, unless the launch does not give every unit one (then each runs alone:
-    // 16660 rows, 384 -> 384, 3 x 3: 396 tiles of 64 columns 55.8 us, 198 of 128 columns 46.8; resnet50_x1.5 block 3 at batch 85
-    // 3617 -> 3570 us, its whole step at batch 64 9.31 -> 9.21 ms)
-    const long slots = (bn <= 128 && T > num_cu ? 2 : 1) * (long)num_cu;
+    // narrow tiles: two resident workgroups per unit, unless the launch gives most units one and none a second (each then runs
+    // alone: 16660 rows, 384 -> 384, 3 x 3: 396 tiles of 64 columns 55.8 us, 198 of 128 columns 46.8; resnet50_x1.5 block 3 at
+    // batch 85 3617 -> 3570 us, its whole step at batch 64 9.31 -> 9.21 ms).  From 768 reduction elements on: below, two
+    // short workgroups a unit hide each other's fill and store (in us, two narrow / one wide: 6272 rows, 256 -> 1024, affine 14.8 /
+    // 17.8, 512 -> 1024 20.0 / 22.1; 51200 rows, 64 -> 128, 3 x 3, affine 20.9 / 23.0; 12544 rows, 576 -> 128, affine 10.1 / 11.9, 128
+    // -> 384, backward-data 9.2 / 10.7), above, the wide one wins (16660 rows, 1024 -> 384 28.6 / 24.9, 51200 rows, 128 -> 128, 3 x 3
+    // 33.0 / 31.1).  And not where the launch would then fall below what this kernel takes at all (37632 rows, 128 -> 128, 3 x 3, 294
+    // narrow tiles or 147: 28.7 us here, 33.2 on the 64-row kernel).
+    const bool alone = T <= num_cu && T >= num_cu * 7 / 10 && Kred >= 768;
+    const long slots = (bn <= 128 && !alone ? 2 : 1) * (long)num_cu;
     const long full = T / slots, r = T % slots;
     double rounds = (double)full;
     if (r) rounds += (full >= 1 && r <= slots / 4) ? 0.66 : 1.0;

@@ -223,3 +223,26 @@ def test_a_value_that_nobody_reads_trains_nothing(precision, call):
         if j + 1 in dangling:
             for kind in (pbd.PBD_GRAD, pbd.PBD_MOMENTUM):
                 assert not d.read_tensor(kind, 1, 0, j, slot, shape).any(), (j, slot, kind)
+
+
+@pytest.mark.parametrize("n,hw,classes", [
+    # 51200 rows, 400 tiles of 128 columns or 200: the short reduction (576) keeps two narrow workgroups a unit, 1152 takes the wide one
+    (200, 16, ["igemm_fwd_256x64x32_affine", "igemm_fwd_256x128x64_affine"]),
+    # 37632 rows: 147 wide tiles would be too few for the 256-row kernel, 294 narrow ones are not
+    (48, 28, ["igemm_fwd_256x64x32_affine", "igemm_fwd_256x64x32_affine"]),
+])
+def test_tiles_of_a_launch_that_does_not_fill_the_chip_twice(n, hw, classes):
+    import torch
+
+    import local_parity
+    t, s = W.Block(), W.Block()
+    v = t.cba(0, 128, 3); t.cba(v, 128, 3)
+    s.cba(0, 128, 1)
+    wl = W.Workload("one_round", n, (64, hw, hw), [t], [s], "bf16", lr=0.05)
+    d = parity.make_distiller(wl, n, "bf16")
+    d.set_profile(True)
+    d.teacher_relay(torch.from_numpy(W.make_input(wl, batch=n)).cuda())
+    d.sync()
+    assert [p["name"] for p in d.get_profile() if p["name"].startswith("igemm_")] == classes
+    err = local_parity.teacher_block_error(d, wl, 0, (0, n // 2 + 1, n - 1))
+    assert err < 2e-2, err
