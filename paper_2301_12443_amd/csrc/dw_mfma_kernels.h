@@ -537,6 +537,374 @@ __global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __r
     }
 }
 
+// The whole backward pass of a stride-1 layer between two batch norms, y1 -> z1 = act(bn(y1)) -> y2 = z1 * w -> z2 = act(bn(y2)), in one
+// pass over the tensors: reads dz2, y2 (with the filter's halo) and y1, forms dy2 from dz2 and y2 as it stages them (bn_bwd_apply_kernel's
+// arithmetic and rounding), and from that one tile the gradient of z1 (stored), the filter's (one partial result per workgroup) and the two
+// sums of y1's batch-norm backward pass (bn_bwd_reduce_kernel's; one pair per workgroup and channel).  As passes of their own these read and
+// write the layer's tensor ten times (apply 3, backward-data 2, backward-weight 2, reduce 2, and dy2's halo), here it is four.
+// The weight gradient is taken over the pixels p of x = z1 so that x needs no halo and dy2's tile serves both products:
+// dW[r][s] = sum over p of x[p] dy2[p + pad - (r, s)], i.e. dw_wgrad_mfma_kernel with the operands' roles changed and the taps mirrored.
+// Bound by the vector ALUs (73 % of their cycles at 3 x 3 and 5 x 5, 60 % at 7 x 7, whose tile leaves room for two workgroups a
+// compute unit): a third of the instructions form dy2, halo included (1.3, 1.6 and 1.9 elements for one).  Against the passes it replaces,
+// 64 x 56 x 56 x 144: 3 x 3 115 -> 76 us, 5 x 5 134 -> 91, 7 x 7 158 -> 134; 64 x 14 x 14 x 384: 33 -> 20, 35 -> 24, 40 -> 31; 128 x 6 x 6 x 960,
+// 5 x 5, 77 -> 69; all such layers of a supernet step at batch 64 11.6 -> 7.9 ms.  Tried: the filters' Toeplitz rows held in registers
+// (20 of them at 5 x 5, spilled), x shifted by selects instead of by its LDS address (13 instructions a row more).
+struct BnBwd { const float* mean; const float* invstd; const float* gamma; const float* beta; const float* k2; const float* k3; int act; };
+struct DwBnBwd { float mu[kDwCh], a[kDwCh], b[kDwCh], p[kDwCh], q[kDwCh]; };   // dy = a dpre + (p (y - mu) + q)
+__device__ __forceinline__ unsigned dw_word(const uint4& v, int m) { return m == 0 ? v.x : m == 1 ? v.y : m == 2 ? v.z : v.w; }
+// all ones where bit i is set (a conditional expression on it becomes a branch around the arithmetic)
+__device__ __forceinline__ unsigned dw_bit(unsigned v, int i) { return (unsigned)((int)(v << (31 - i)) >> 31); }
+// act_pass as one integer comparison (0 < v, 0 < v < 6, always: positive floats order like their bits, NaN lies above infinity);
+// the two float comparisons meet in scalar registers, which a chain of them waits for
+__device__ __forceinline__ unsigned dw_pass_limit(int act) {
+  return act == ACT_RELU6 ? 0x40bfffffu - 1u : act == ACT_RELU ? 0x7f800000u - 1u : ~0u;
+}
+__device__ __forceinline__ float dw_pass(float v, float d, unsigned limit) { return __float_as_uint(v) - 1u <= limit ? d : 0.f; }
+__device__ __forceinline__ float2 dw_pair(const float* p) { return *reinterpret_cast<const float2*>(p); }
+// Four pixels x 8 channels of dz2 and y2 -> dy2, transposed into the tile; bit i of ok: pixel i lies in the image (elsewhere dy2 is
+// zero).  Two channels at a time: their coefficients are few enough to leave three workgroups a compute unit.
+template <int CH_PITCH>
+__device__ __forceinline__ void dw_bn_bwd_store(unsigned char* dst, const uint4 (&d)[4], const uint4 (&y)[4], const DwBnBwd& f, int c8, unsigned ok, unsigned limit,
+                                                bool store) {
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    const float2 mu = dw_pair(f.mu + c8 + 2 * m), a = dw_pair(f.a + c8 + 2 * m), b = dw_pair(f.b + c8 + 2 * m),
+                 fp = dw_pair(f.p + c8 + 2 * m), fq = dw_pair(f.q + c8 + 2 * m);
+    unsigned o[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const unsigned dw = dw_word(d[i], m), yw = dw_word(y[i], m);
+      const float y0 = bf_lo(yw) - mu.x, y1 = bf_hi(yw) - mu.y;
+      const float d0 = dw_pass(fmaf(y0, a.x, b.x), bf_lo(dw), limit), d1 = dw_pass(fmaf(y1, a.y, b.y), bf_hi(dw), limit);
+      const float t0 = fmaf(a.x, d0, fmaf(fp.x, y0, fq.x)), t1 = fmaf(a.y, d1, fmaf(fp.y, y1, fq.y));
+      o[i] = pack_bf2(t0, t1) & dw_bit(ok, i);
+    }
+    if (store) {
+      *reinterpret_cast<uint2*>(dst + (2 * m) * CH_PITCH) = make_uint2(dw_lo2(o[0], o[1]), dw_lo2(o[2], o[3]));
+      *reinterpret_cast<uint2*>(dst + (2 * m + 1) * CH_PITCH) = make_uint2(dw_hi2(o[0], o[1]), dw_hi2(o[2], o[3]));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+// the same for x = z1 from y1 (dw_fold_apply's arithmetic)
+template <int CH_PITCH>
+__device__ __forceinline__ void dw_fold_store(unsigned char* dst, const uint4 (&y)[4], const DwFold& f, int c8, unsigned ok, float hi) {
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    const float2 mu = dw_pair(f.mu + c8 + 2 * m), a = dw_pair(f.a + c8 + 2 * m), b = dw_pair(f.b + c8 + 2 * m);
+    unsigned o[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const unsigned yw = dw_word(y[i], m);
+      const float z0 = fminf(fmaxf(fmaf(bf_lo(yw) - mu.x, a.x, b.x), 0.f), hi), z1 = fminf(fmaxf(fmaf(bf_hi(yw) - mu.y, a.y, b.y), 0.f), hi);
+      o[i] = pack_bf2(z0, z1) & dw_bit(ok, i);
+    }
+    *reinterpret_cast<uint2*>(dst + (2 * m) * CH_PITCH) = make_uint2(dw_lo2(o[0], o[1]), dw_lo2(o[2], o[3]));
+    *reinterpret_cast<uint2*>(dst + (2 * m + 1) * CH_PITCH) = make_uint2(dw_hi2(o[0], o[1]), dw_hi2(o[2], o[3]));
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// WGRAD false: the architecture round, which leaves the filters alone.
+template <int K, bool WGRAD>
+__global__ __launch_bounds__(256, WGRAD ? (K == 7 ? 2 : 3) : (K == 7 ? 3 : 4)) void dw_bwd_mfma_kernel(
+    const bf16_t* __restrict__ dz, const bf16_t* __restrict__ y2, const bf16_t* __restrict__ y1, const bf16_t* __restrict__ w,
+    bf16_t* __restrict__ dx, float* __restrict__ wpart, float* __restrict__ spart, DwArgs g, BnBwd f2, NormFold f1) {
+  typedef DwGeom<K> G;
+  constexpr int NT = G::NT, pad = K / 2, NIT = K == 3 ? 1 : 2, QS = K == 3 ? 2 : 1;
+  constexpr int DY = G::CHP * kDwCh > kDwOutRow * kDwTile ? G::CHP * kDwCh : kDwOutRow * kDwTile;   // dy2's tile, then dz1's
+  constexpr int ROWD = kDwTile * 2, CHD = kDwTile * ROWD + 8;                        // x: 16 x 16 pixels a channel
+  constexpr int ZERO = DY + (WGRAD ? CHD * kDwCh : 0);                               // a row of zeros
+  __shared__ __attribute__((aligned(16))) unsigned char smem[ZERO + ROWD];
+  __shared__ __attribute__((aligned(16))) unsigned char filt[kDwCh * K * G::WROW];
+  __shared__ __attribute__((aligned(16))) DwBnBwd c2;
+  __shared__ __attribute__((aligned(16))) DwFold c1;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int slice = wave & 1, half = wave >> 1;
+  const int wg = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int cv0 = (wg % g.groups) * (kDwCh / 8), chunk = wg / g.groups, C = g.ncv * 8;
+  const int tile_begin = chunk * g.per_block, tile_end = min(g.tiles, tile_begin + g.per_block);
+  const __amdgpu_buffer_rsrc_t zr = tensor_rsrc(dz, g.bytes), y2r = tensor_rsrc(y2, g.bytes), y1r = tensor_rsrc(y1, g.bytes);
+  int ch = slice * 16 + (lane >> 2), n4 = lane & 3;          // n4: output row strip, column of the filter operand, tap offset
+  const float hi1 = f1.act == ACT_RELU6 ? 6.f : __builtin_inff();
+  const unsigned limit1 = dw_pass_limit(f1.act), limit2 = dw_pass_limit(f2.act);
+
+  if (tid < kDwCh) {
+    const int c = cv0 * 8 + tid;
+    const bool in = c < C;
+    const float a = in ? f2.gamma[c] * f2.invstd[c] : 0.f;
+    c2.mu[tid] = in ? f2.mean[c] : 0.f;
+    c2.a[tid] = a;
+    c2.b[tid] = in ? f2.beta[c] : 0.f;
+    c2.p[tid] = in ? -a * (f2.invstd[c] * f2.k3[c]) : 0.f;
+    c2.q[tid] = in ? -a * f2.k2[c] : 0.f;
+  }
+  dw_fold_load(c1, f1, cv0 * 8, C, tid);
+  if (tid < ROWD / 8) *reinterpret_cast<uint2*>(smem + ZERO + tid * 8) = make_uint2(0u, 0u);
+
+  // ---- mirrored filters: [channel][filter row][tap] in LDS, from where every tile forms its Toeplitz rows anew ----
+  for (int i = tid; i < K * K * (kDwCh / 2); i += 256) {
+    const int tap = i / (kDwCh / 2), cc = i % (kDwCh / 2), t = K * K - 1 - tap;
+    unsigned v = 0;
+    if (cv0 * 8 + 2 * cc < C) v = *reinterpret_cast<const unsigned*>(w + (size_t)tap * C + cv0 * 8 + 2 * cc);
+    unsigned short* p = reinterpret_cast<unsigned short*>(filt + (2 * cc * K + t / K) * G::WROW) + t % K;
+    p[0] = (unsigned short)v;
+    p[K * G::WROW / 2] = (unsigned short)(v >> 16);
+  }
+  dw_f32x4 wsum[NIT][NIT];                               // over the tiles, each summed on its own first
+#pragma unroll
+  for (int i = 0; i < NIT; ++i)
+#pragma unroll
+    for (int j = 0; j < NIT; ++j) wsum[i][j] = dw_f32x4{0.f, 0.f, 0.f, 0.f};
+  float sb[8], sg[8];                                    // this thread's channels: sum dpre1, sum dpre1 (y1 - mean1)
+#pragma unroll
+  for (int e = 0; e < 8; ++e) sb[e] = sg[e] = 0.f;
+  // this thread's four pixels of the tile (of x, and of the stored gradient): columns 4 xq .. 4 xq + 3 of row xrow
+  const int cvl = tid % (kDwCh / 8), xq = (tid / (kDwCh / 8)) % 4, xrow = tid / (kDwCh / 8) / 4;
+
+  for (int tile = tile_begin; tile < tile_end; ++tile) {
+    int t_ = tile;
+    const int tw = t_ % g.tiles_w; t_ /= g.tiles_w;
+    const int th = t_ % g.tiles_h, n = t_ / g.tiles_h;
+    const int h0 = th * kDwTile, w0 = tw * kDwTile;
+    // ---- all loads of the tile in flight together ----
+    uint4 rz[G::NLOAD][4], ry[G::NLOAD][4], rx[4];
+    unsigned ok = 0;                                     // bit 4 i + p: pixel p of item i lies in the image
+    // (places formed anew in every phase: kept over the tile they cost the registers that the loads in flight need)
+    int at0 = tid;
+    asm volatile("" : "+v"(at0));
+#pragma unroll
+    for (int i = 0; i < G::NLOAD; ++i) {
+      const int c = at0 + i * 256, quad = (c / (kDwCh / 8)) % G::NQ, row = c / (kDwCh / 8) / G::NQ;
+      const int h = h0 - pad + row, w_ = w0 - pad + 4 * quad;
+      const bool rok = c < G::ITEMS && (unsigned)h < (unsigned)g.H && cv0 + cvl < g.ncv;
+      const unsigned off = (unsigned)(((n * g.H + h) * g.W + w_) * g.ncv + cv0 + cvl) * 16u;
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const bool in = rok && 4 * quad + p < G::IN && (unsigned)(w_ + p) < (unsigned)g.W;
+        const unsigned at = in ? off + (unsigned)(p * g.ncv) * 16u : kOutOfRange;
+        rz[i][p] = buffer_load16(zr, at);
+        ry[i][p] = buffer_load16(y2r, at);
+        ok |= (in ? 1u : 0u) << (4 * i + p);
+      }
+    }
+    unsigned xok = 0;                                    // bit p: pixel p of x lies in the image
+    const unsigned xoff = (unsigned)(((n * g.H + h0 + xrow) * g.W + w0 + 4 * xq) * g.ncv + cv0 + cvl) * 16u;
+    asm volatile("" : "+v"(at0), "+v"(n4), "+v"(ch));
+    __syncthreads();                                     // the previous tile's result (or the filters) has been read
+#pragma unroll
+    for (int i = 0; i < G::NLOAD; ++i) {
+      const int c = at0 + i * 256, quad = (c / (kDwCh / 8)) % G::NQ, row = c / (kDwCh / 8) / G::NQ;
+      unsigned char* dst = smem + cvl * 8 * G::CHP + row * G::ROWP + quad * 8;
+      if (__builtin_amdgcn_ballot_w64((ok >> (4 * i) & 15u) != 0u))
+        dw_bn_bwd_store<G::CHP>(dst, rz[i], ry[i], c2, cvl * 8, ok >> (4 * i), limit2, c < G::ITEMS);
+      else if (c < G::ITEMS) {                           // rows outside the image: a third of the tile on a 14 x 14 image
+#pragma unroll
+        for (int e = 0; e < 8; ++e) *reinterpret_cast<uint2*>(dst + e * G::CHP) = make_uint2(0u, 0u);
+      }
+      if (i == 0) {                                      // (in flight behind the other items, in the first one's registers)
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const bool in = h0 + xrow < g.H && w0 + 4 * xq + p < g.W && cv0 + cvl < g.ncv;
+          rx[p] = buffer_load16(y1r, in ? xoff + (unsigned)(p * g.ncv) * 16u : kOutOfRange);
+          xok |= (in ? 1u : 0u) << p;
+        }
+      }
+    }
+    if constexpr (WGRAD) dw_fold_store<CHD>(smem + DY + cvl * 8 * CHD + xrow * ROWD + xq * 8, rx, c1, cvl * 8, xok, hi1);
+    __syncthreads();
+
+    // ---- weight gradient (dw_wgrad_mfma_kernel, dy2 in the role of x): D[r'][s'] = sum x[p] dy2tile[p + (r', s')] ----
+    if constexpr (WGRAD) {
+      const unsigned odd = n4 & 1 ? kDwSelMid : kDwSelLow;
+      // (a lane's whole pairs of shift are in the address: LDS reads of two words)
+      const unsigned char* xp = smem + ch * G::CHP + half * 16 + (n4 >> 1) * 4;
+      const unsigned char* dp = smem + DY + ch * CHD + half * 16 - n4 * ROWD;
+      const unsigned char* zp = smem + ZERO + half * 16;
+      dw_f32x4 acc[NIT][NIT][QS];
+#pragma unroll
+      for (int i = 0; i < NIT; ++i)
+#pragma unroll
+        for (int j = 0; j < NIT; ++j)
+#pragma unroll
+          for (int q = 0; q < QS; ++q) acc[i][j][q] = dw_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int y = 0; y < G::IN; ++y) {
+        // row y - n4 - 4 jt of x, n4 = 0..3: none, some or all of the four lie in the tile
+        dw_s16x4 d[NIT][2];
+#pragma unroll
+        for (int jt = 0; jt < NIT; ++jt) {
+          const int top = y - 4 * jt;
+          const unsigned char* db = dp + top * ROWD;
+          if (top < 3) db = n4 <= top ? db : zp;
+          if (top > kDwTile - 1) db = n4 > top - kDwTile ? db : zp;
+          if (top < 0 || top > kDwTile + 2) continue;
+#pragma unroll
+          for (int q = 0; q < 2; ++q) d[jt][q] = *reinterpret_cast<const dw_s16x4*>(db + q * 8);
+        }
+        unsigned E[2 * (NIT + 1) + 1];
+#pragma unroll
+        for (int i = 0; i < 2 * (NIT + 1) + 1; ++i) E[i] = *reinterpret_cast<const unsigned*>(xp + y * G::ROWP + i * 4);
+#pragma unroll
+        for (int c = 0; c < NIT + 1; ++c) {
+          const dw_s16x4 xs = __builtin_bit_cast(dw_s16x4, make_uint2(__builtin_amdgcn_perm(E[2 * c + 1], E[2 * c], odd),
+                                                                      __builtin_amdgcn_perm(E[2 * c + 2], E[2 * c + 1], odd)));
+#pragma unroll
+          for (int it = 0; it < NIT; ++it) {
+            const int q = c - it;
+            if (q < 0 || q > 1) continue;
+#pragma unroll
+            for (int jt = 0; jt < NIT; ++jt)
+              if (y - 4 * jt >= 0 && y - 4 * jt <= kDwTile + 2)
+                acc[it][jt][q % QS] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(xs, d[jt][q], acc[it][jt][q % QS], 0, 0, 0);
+          }
+        }
+        if (y % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int i = 0; i < NIT; ++i)
+#pragma unroll
+        for (int j = 0; j < NIT; ++j) wsum[i][j] += QS == 2 ? acc[i][j][0] + acc[i][j][QS - 1] : acc[i][j][0];
+      __builtin_amdgcn_sched_barrier(0);
+    }
+
+    // ---- backward-data (dw_mfma_kernel, FLIP): acc[o][q] = rows 4 n4 + o, columns 8 half + 4 q + 0..3 ----
+    dw_s16x4 wt[K][NT];                                  // (not held over the tile: 20 registers at 5 x 5)
+    {
+      const unsigned far = n4 >= 2 ? ~0u : 0u, odd = n4 & 1 ? kDwSelMid : kDwSelHigh;
+#pragma unroll
+      for (int r = 0; r < K; ++r) {
+        unsigned P[2 * NT + 2];
+#pragma unroll
+        for (int i = 0; i < 2 * NT + 2; ++i) P[i] = 0u;
+        const unsigned char* row = filt + (ch * K + r) * G::WROW;
+        const uint2 q0 = *reinterpret_cast<const uint2*>(row);
+        P[2] = q0.x; P[3] = K == 3 ? q0.y & 0xffffu : q0.y;
+        if (K > 3) {
+          const uint2 q1 = *reinterpret_cast<const uint2*>(row + 8);
+          P[4] = K == 5 ? q1.x & 0xffffu : q1.x;
+          if (K > 5) P[5] = q1.y & 0xffffu;
+        }
+        unsigned E[2 * NT + 1];
+#pragma unroll
+        for (int i = 0; i < 2 * NT + 1; ++i) E[i] = dw_sel(far, P[i], P[i + 1]);
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          wt[r][t] = __builtin_bit_cast(dw_s16x4, make_uint2(__builtin_amdgcn_perm(E[2 * t + 1], E[2 * t], odd),
+                                                             __builtin_amdgcn_perm(E[2 * t + 2], E[2 * t + 1], odd)));
+      }
+    }
+    dw_f32x4 acc[4][2];
+#pragma unroll
+    for (int o = 0; o < 4; ++o)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) acc[o][q] = dw_f32x4{0.f, 0.f, 0.f, 0.f};
+    const unsigned char* in = smem + ch * G::CHP + 4 * n4 * G::ROWP + half * 16;
+#pragma unroll
+    for (int c = 0; c < NT + 1; ++c)
+#pragma unroll
+      for (int y = 0; y < K + 3; ++y) {
+        const dw_s16x4 d = *reinterpret_cast<const dw_s16x4*>(in + y * G::ROWP + c * 8);
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+          const int r = y - o;
+          if (r < 0 || r >= K) continue;
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const int t = c - q;
+            if (t < 0 || t >= NT) continue;
+            acc[o][q] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(wt[r][t], d, acc[o][q], 0, 0, 0);
+          }
+        }
+        if (K > 3 && y % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // (not every read of the tile in registers at once)
+      }
+    __syncthreads();                                     // every wave has read dy2's tile
+    unsigned char* so = smem + (ch >> 1) * 4 + ((ch & 1) * 2 + half * 8) * kDwOutP;
+#pragma unroll
+    for (int o = 0; o < 4; ++o)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          const int v0 = __float_as_int(acc[o][q][m]), v2 = __float_as_int(acc[o][q][m + 2]);
+          const int lo = __builtin_amdgcn_update_dpp(v0, v2, 0x114, 0xf, 0xa, false);   // row_shr:4 into the odd channels
+          const int hi = __builtin_amdgcn_update_dpp(v2, v0, 0x104, 0xf, 0x5, false);   // row_shl:4 into the even channels
+          *reinterpret_cast<unsigned*>(so + (4 * n4 + o) * kDwOutRow + (q * 4 + m) * kDwOutP) = pack_bf2(__int_as_float(lo), __int_as_float(hi));
+        }
+    __syncthreads();
+    // ---- store, and the sums of y1's batch-norm backward pass over what was stored ----
+    uint4 out[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      out[p] = *reinterpret_cast<const uint4*>(smem + xrow * kDwOutRow + (4 * xq + p) * kDwOutP + cvl * 16);
+      if ((xok >> p) & 1u) *reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(dx) + xoff + (unsigned)(p * g.ncv) * 16u) = out[p];
+      else out[p] = make_uint4(0u, 0u, 0u, 0u);
+    }
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const float2 mu = dw_pair(c1.mu + cvl * 8 + 2 * m), a = dw_pair(c1.a + cvl * 8 + 2 * m), b = dw_pair(c1.b + cvl * 8 + 2 * m);
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const unsigned dw = dw_word(out[p], m), yw = dw_word(rx[p], m);
+        const float y0 = bf_lo(yw) - mu.x, y1_ = bf_hi(yw) - mu.y;
+        const float d0 = dw_pass(fmaf(y0, a.x, b.x), bf_lo(dw), limit1), d1 = dw_pass(fmaf(y1_, a.y, b.y), bf_hi(dw), limit1);
+        sb[2 * m] += d0;
+        sb[2 * m + 1] += d1;
+        sg[2 * m] = fmaf(d0, y0, sg[2 * m]);
+        sg[2 * m + 1] = fmaf(d1, y1_, sg[2 * m + 1]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  // ---- sums: lanes 4 apart hold the same channels; then the four waves ----
+  __syncthreads();
+  float* red = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+#pragma unroll
+    for (int off = 4; off < 64; off <<= 1) {
+      sb[e] += __shfl_xor(sb[e], off, 64);
+      sg[e] += __shfl_xor(sg[e], off, 64);
+    }
+  if (lane < kDwCh / 8) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      red[(wave * 2) * kDwCh + lane * 8 + e] = sb[e];
+      red[(wave * 2 + 1) * kDwCh + lane * 8 + e] = sg[e];
+    }
+  }
+  __syncthreads();
+  if (tid < 2 * kDwCh && cv0 * 8 + tid % kDwCh < C) {
+    const int c = cv0 * 8 + tid % kDwCh;
+    const float v = (red[tid] + red[2 * kDwCh + tid]) + (red[4 * kDwCh + tid] + red[6 * kDwCh + tid]);
+    spart[((size_t)chunk * 2 + tid / kDwCh) * C + c] = tid < kDwCh ? v : v * f1.invstd[c];
+  }
+  if constexpr (!WGRAD) return;
+  // ---- the two column halves of a slice meet; lane 4 c + j holds taps (r' = 4 jt + j, s' = 4 it + v) of channel c, mirrored ----
+  __syncthreads();
+  if (half) {
+#pragma unroll
+    for (int it = 0; it < NIT; ++it)
+#pragma unroll
+      for (int jt = 0; jt < NIT; ++jt)
+        *reinterpret_cast<dw_f32x4*>(red + ((slice * NIT * NIT + it * NIT + jt) * 64 + lane) * 4) = wsum[it][jt];
+  }
+  __syncthreads();
+  if (half || cv0 * 8 + ch >= C) return;
+#pragma unroll
+  for (int it = 0; it < NIT; ++it)
+#pragma unroll
+    for (int jt = 0; jt < NIT; ++jt) {
+      const dw_f32x4 o = *reinterpret_cast<const dw_f32x4*>(red + ((slice * NIT * NIT + it * NIT + jt) * 64 + lane) * 4);
+      const int r = K - 1 - (4 * jt + n4);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int s = K - 1 - (4 * it + v);
+        if (r >= 0 && s >= 0) wpart[((size_t)chunk * K * K + r * K + s) * C + cv0 * 8 + ch] = wsum[it][jt][v] + o[v];
+      }
+    }
+}
+
 // Backward-weight of a stride-2 layer, dW[r][s] = sum x[2 p + r - pad][2 q + s - pad] dy[p][q].  Columns (and rows) of x of one
 // parity are a stride-1 problem with at most (K + 1) / 2 <= 4 taps, so one product covers all taps of a parity pair: the four
 // pixels a thread loads lie two columns apart, LDS holds [channel][row][column parity][column], and with y the row of

@@ -347,6 +347,10 @@ inline DwWgradCfg dw_wgrad_cfg(bool bf16, int N, int h_in, int w_in, int h_out, 
   return w;
 }
 
+// The backward pass in one kernel (dw_bwd_mfma_kernel): as many workgroups as are resident, three a compute unit, two at 7 x 7; one
+// more each without the weight gradient (arch).
+inline DwArgs dw_bwd_args(int N, int h, int w, int Cp, int k, bool arch) { return dw_args(N, h, w, Cp, (k == 7 ? 512 : 768) + (arch ? 256 : 0)); }
+
 struct WgradCfg { int TM, TN, BKP, tiles_k, tiles_j, splits, pix_per_split; bool dma; };
 // taps = R * S of the layer (J = taps * C).  Layers with a filter (taps > 1), whole 64- or 96-channel groups and a
 // long pixel range take wgrad_dma_kernel: TM x 256 tiles, one workgroup per compute unit, the pixel range cut
@@ -514,6 +518,8 @@ bool stem_s2d(const pbd_ctx* c, int block, const OpPlan& op) {
          op.d.in[0] == 0 && op.d.k == 7 && op.d.stride == 2 && op.d.pad == 3 && op.in.c <= 4 && op.cin_p == 8 &&
          op.in.h % 2 == 0 && op.in.w % 2 == 0 && op.out.h == op.in.h / 2 && op.out.w == op.in.w / 2;
 }
+int depthwise_reader(const pbd_ctx* c, const BlockPlan& bp, int j);
+bool dw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j);
 constexpr int kS2dK = 256;     // reduction length of such a stem: 4 x 4 taps x 16 lanes
 
 int plan(pbd_ctx* c) {
@@ -640,7 +646,13 @@ int plan(pbd_ctx* c) {
           need_red((size_t)gw.chunks * op.d.k * op.d.k * op.cout_p * 4);
           if (dw_on_mfma(bf && !c->o.force_direct, c->o.batch, op.out.h, op.out.w, op.cout_p, op.d.k, op.d.stride, op.d.pad))
             need_red((size_t)dw_stat_groups(c->o.batch, op.out.h, op.out.w, op.cout_p) * 3 * op.cout_p * 4);
-          defer(op, gw.chunks);
+          int chunks = gw.chunks;
+          if (dw_bwd_fused(c, bp, (int)v - 1)) {
+            chunks = dw_chunks(dw_bwd_args(c->o.batch, op.in.h, op.in.w, op.cout_p, op.d.k, false));
+            need_red((size_t)chunks * (op.d.k * op.d.k + 2) * op.cout_p * 4);
+            need_red((size_t)dw_chunks(dw_bwd_args(c->o.batch, op.in.h, op.in.w, op.cout_p, op.d.k, true)) * 2 * op.cout_p * 4);
+          }
+          defer(op, chunks);
         } else if (bf && !c->o.force_direct) {
           const WgradCfg w = op.s2d ? wgrad_cfg(M, op.d.c_out, kS2dK, 16) : wgrad_cfg(M, op.d.c_out, op.d.k * op.d.k * op.cin_p, op.d.k * op.d.k);
           // (the stem on the space-to-depth input: partial sums and their sum in the repacked layout, then unpacked)
@@ -775,6 +787,13 @@ int depthwise_reader(const pbd_ctx* c, const BlockPlan& bp, int j) {
   const int N = c->o.batch;     // (both its passes that read the tensor form it as they stage it)
   return dw_on_mfma(true, N, q.out.h, q.out.w, q.cout_p, q.d.k, q.d.stride, q.d.pad) &&
          dw_wgrad_on_mfma(true, N, q.out.h, q.out.w, q.cout_p, q.d.k, q.d.stride, q.d.pad) ? reader : -1;
+}
+
+// The backward pass of student layer j in one kernel: a depthwise layer that normalises the layer in front as it stages it
+// (depthwise_reader) and whose own gradient arrives as a tensor (no residual add rides in its batch norm).
+bool dw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j) {
+  const OpPlan& op = bp.ops[j];
+  return op.d.type == OP_CBA && op.dw && op.d.in[0] > 0 && depthwise_reader(c, bp, op.d.in[0] - 1) == j && residual_reader(bp, j) < 0;
 }
 
 template <class T> struct Exec {
@@ -1229,7 +1248,7 @@ template <class T> struct Exec {
     const DwWgradCfg cfg = dw_wgrad_cfg(mfma(), N, op.in.h, op.in.w, op.out.h, op.out.w, op.cout_p, op.d.k, op.d.stride, op.d.pad);
     {
       char cls[32];
-      snprintf(cls, sizeof cls, "dw_wgrad%s_k%d", cfg.mfma ? (op.d.stride == 2 ? "_s2_mfma" : fold.mean ? "_mfma_bn" : "_mfma") : "", op.d.k <= 3 ? 3 : cfg.mfma ? op.d.k : 7);
+      snprintf(cls, sizeof cls, "dw_wgrad%s_k%d", cfg.mfma ? (op.d.stride == 2 ? "_s2_mfma" : fold.mean ? "_mfma_fold" : "_mfma") : "", op.d.k <= 3 ? 3 : cfg.mfma ? op.d.k : 7);
       ProfScope ps(c, cls, bytes_of(op.in) + bytes_of(op.out),
                    2.0 * N * op.out.h * op.out.w * op.d.c_out * op.d.k * op.d.k, net, blk, opi);
       if (cfg.mfma) {
@@ -1257,6 +1276,36 @@ template <class T> struct Exec {
     if (deferred(op)) return;
     ProfScope ps(c, "sum_partials", (double)(cfg.chunks + 1) * op.wn * 4, 0, net, blk, opi);
     sum_partials(parts(op), dw, (long)op.wn, cfg.chunks);
+  }
+
+  // op's whole backward pass (dw_bwd_fused): from dz, the gradient of its normalised output, to the gradient dx of the normalised output
+  // of p, the layer in front, op's filter gradient (arch: not that) and the sums of p's batch-norm backward pass, which are finished here.
+  void dw_bwd(const OpPlan& op, const OpPlan& p, const T* dz, const T* y, const T* y_in, const T* w, T* dx, bool arch) {
+    const BlockPlan& bp = c->net[1][blk];
+    const float* master = wsf(bp.master);
+    float* grad = wsf(bp.grad);
+    const DwArgs g = dw_bwd_args(c->o.batch, op.in.h, op.in.w, op.cout_p, op.d.k, arch);
+    const int chunks = dw_chunks(g);
+    float* wpart = parts(op);
+    float* spart = red() + (arch || deferred(op) ? 0 : (size_t)chunks * op.wn);
+    {
+      char cls[32];
+      snprintf(cls, sizeof cls, "dw_%s_mfma_bn_k%d", arch ? "dgrad" : "wgrad", op.d.k);   // (the weight gradient is formed nowhere else)
+      ProfScope ps(c, cls, 4 * bytes_of(op.out), (arch ? 2.0 : 4.0) * c->o.batch * op.out.h * op.out.w * op.d.c_out * op.d.k * op.d.k, net, blk, opi);
+      if constexpr (sizeof(T) == 2) {
+        const BnBwd f2{wsf(op.s_mean), wsf(op.s_invstd), master + op.e_gamma, master + op.e_beta, wsf(op.s_k2), wsf(op.s_k3), op.d.act};
+        const NormFold f1{wsf(p.s_mean), wsf(p.s_invstd), master + p.e_gamma, master + p.e_beta, p.d.act};
+#define PBD_DWB(K_) launch(c, arch ? dw_bwd_mfma_kernel<K_, false> : dw_bwd_mfma_kernel<K_, true>, chunks * g.groups, 256, 0, st, \
+    (const bf16_t*)dz, (const bf16_t*)y, (const bf16_t*)y_in, (const bf16_t*)w, (bf16_t*)dx, wpart, spart, g, f2, f1)
+        if (op.d.k == 3) PBD_DWB(3); else if (op.d.k == 5) PBD_DWB(5); else PBD_DWB(7);
+#undef PBD_DWB
+      }
+    }
+    launch(c, bn_bwd_finalize_kernel, p.cout_p / kFinalizeChannels, 256, 0, st, spart, chunks, p.cout_p, (double)c->o.batch * p.out.h * p.out.w,
+           grad + p.e_gamma, grad + p.e_beta, wsf(p.s_k2), wsf(p.s_k3));
+    if (arch || deferred(op)) return;
+    ProfScope ps(c, "sum_partials", (double)(chunks + 1) * op.wn * 4, 0, net, blk, opi);
+    sum_partials(wpart, grad + op.e_w, (long)op.wn, chunks);
   }
 
   // ---- joins / pool -------------------------------------------------------
@@ -1523,7 +1572,7 @@ template <class T> struct Exec {
           launch(c, dw_rows ? bn_finalize_kernel<T, true> : bn_finalize_kernel<T>, op.cout_p / kFinalizeChannels, 256, 0, st, 
               part, pivot, chunks, op.cout_p, (double)M, wsf(op.s_mean), wsf(op.s_invstd), wsf(op.s_rmean),
               wsf(op.s_rvar), c->o.bn_eps, c->o.bn_momentum, master + op.e_gamma, master + op.e_beta,
-              folds_into((int)j + 1) ? wsf(op.s_keep) : (float*)nullptr);
+              folds_into((int)j + 1) || dw_bwd_fused(c, bp, (int)j) ? wsf(op.s_keep) : (float*)nullptr);
           if (pool_reader(bp, (int)j, N) < 0 && !folds_into((int)j + 1)) {
             const ColGrid ga = col_grid(M, op.cout_p, 8, 4096);   // elementwise pass: many short workgroups
             // a residual add that only reads this layer's output rides along: the normalised tensor itself
@@ -1600,6 +1649,7 @@ template <class T> struct Exec {
     // gradient, masks it and stores the result once, where the add's other input collects its gradient.
     struct AddBwd { const T* dz; const T* z; int act; T* dstore; bool loss; };
     std::vector<AddBwd> add_bwd(bp.ops.size(), AddBwd{nullptr, nullptr, 0, nullptr, false});
+    std::vector<char> summed(bp.ops.size(), 0);     // layers whose batch-norm sums the backward pass of their depthwise reader took
     for (int j = (int)bp.ops.size() - 1; j >= 0; --j) {
       const OpPlan& op = bp.ops[j];
       opi = j;
@@ -1631,7 +1681,8 @@ template <class T> struct Exec {
                  op.cout_p, op.d.act, (unsigned)(M * op.cout_p * sizeof(T)));
         } else {
           const ColGrid g = bn_bwd_grid(M, op.cout_p);
-          if (ab.loss) {
+          if (summed[j]) {
+          } else if (ab.loss) {
             float* loss_part = red() + (size_t)g.chunks * 2 * op.cout_p;
             {
               ProfScope ps(c, streams(op.out) ? "bn_bwd_reduce_add_mse_nt" : "bn_bwd_reduce_add_mse", 4 * bytes_of(op.out), 0, net, blk, opi);
@@ -1654,9 +1705,16 @@ template <class T> struct Exec {
                 (const T*)dz, y, master + op.e_gamma, master + op.e_beta, wsf(op.s_mean), wsf(op.s_invstd), red(), M, op.cout_p,
                 op.d.act, g, (const T*)nullptr, 0, (T*)nullptr, (float*)nullptr, 0.f);
           }
-          launch(c, bn_bwd_finalize_kernel, op.cout_p / kFinalizeChannels, 256, 0, st, red(), g.chunks, op.cout_p, (double)M,
-                                                                           grad + op.e_gamma, grad + op.e_beta,
-                                                                           wsf(op.s_k2), wsf(op.s_k3));
+          if (!summed[j])
+            launch(c, bn_bwd_finalize_kernel, op.cout_p / kFinalizeChannels, 256, 0, st, red(), g.chunks, op.cout_p, (double)M,
+                                                                             grad + op.e_gamma, grad + op.e_beta,
+                                                                             wsf(op.s_k2), wsf(op.s_k3));
+          if (dw_bwd_fused(c, bp, j)) {
+            dw_bwd(op, bp.ops[iv - 1], dz, y, ws(scr + bp.ops[iv - 1].y), wc + op.e_w, dvalue(iv), arch);
+            summed[iv - 1] = 1;
+            have[iv] = 1;
+            continue;
+          }
           {
             const ColGrid ga = col_grid(M, op.cout_p, 8, 4096);
             ProfScope ps(c, streams(op.out) ? "bn_bwd_apply_nt" : "bn_bwd_apply", 3 * bytes_of(op.out), 0, net, blk, opi);
@@ -2351,6 +2409,20 @@ int pbd_read_grad_value(pbd_ctx* c, int32_t b, int32_t v, float* host, size_t n)
       !short_column((long)c->o.batch * s.h * s.w))
     return fail(c, PBD_ESTATE, "the gradient of the output of block %d is not stored: the batch-norm reduction that does the last add's "
                 "backward pass forms it from the block's output and the teacher's activation", b);
+  const OpPlan& op = bp.ops[v - 1];
+  if (dw_bwd_fused(c, bp, v - 1)) {
+    // the step does not write this tensor (the layer's backward kernel forms it as it stages the gradient of the normalised output):
+    // formed now, in the place of the layer's normalised input, which is not kept either
+    const long M = (long)c->o.batch * s.h * s.w;
+    const ColGrid g = col_grid(M, op.cout_p, 8, 4096);
+    auto f = [&](size_t off) { return reinterpret_cast<const float*>(c->ws + off); };
+    bf16_t* dy = reinterpret_cast<bf16_t*>(c->ws + bp.scr_off + bp.val[op.d.in[0]]);
+    bn_bwd_apply_kernel<bf16_t><<<dim3(g.slabs, g.chunks), 256, 0, c->stream>>>(
+        reinterpret_cast<const bf16_t*>(c->ws + bp.scr_off + bp.dval[v]), dy, reinterpret_cast<const bf16_t*>(c->ws + bp.scr_off + op.y),
+        f(op.s_keep), f(op.s_keep) + op.cout_p, f(op.s_mean), f(op.s_invstd), f(op.s_k2), f(op.s_k3), M, op.cout_p, op.d.act, g);
+    rc = after_launches(c);
+    return rc ? rc : download_act(c, reinterpret_cast<const char*>(dy), s, host);
+  }
   return download_act(c, c->ws + bp.scr_off + bp.dval[v], s, host);
 }
 

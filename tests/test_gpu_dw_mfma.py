@@ -99,6 +99,45 @@ def test_normalisation_in_the_staging(n, h, w, c, k, act):
     print(", ".join(f"{key} {e:.1e}" for key, e in sorted(worst.items())), flush=True)
 
 
+# (batch, h, w, channels, k, activation in front, activation behind): the backward pass of such a layer in one kernel
+BACKWARD = [
+    (17, 16, 16, 8, 5, W.ACT_RELU, W.ACT_NONE),        # exactly one tile, one vector of channels
+    (30, 14, 14, 40, 7, W.ACT_RELU6, W.ACT_RELU6),     # one ragged tile, a channel group and a quarter
+    (5, 33, 31, 72, 3, W.ACT_RELU6, W.ACT_RELU),       # one row into the next tiles, one column short of them
+    (3, 49, 37, 24, 7, W.ACT_RELU, W.ACT_NONE),
+    (70, 8, 12, 136, 3, W.ACT_RELU, W.ACT_RELU6),
+    (90, 50, 20, 8, 5, W.ACT_RELU6, W.ACT_RELU6),      # several tiles a workgroup in neither round
+    (290, 35, 40, 16, 7, W.ACT_RELU6, W.ACT_RELU),     # several in both, the last ones' right half empty
+]
+
+
+@pytest.mark.parametrize("n,h,w,c,k,front,behind", BACKWARD)
+def test_backward_in_one_kernel(n, h, w, c, k, front, behind):
+    """Every operation against the oracle; and the architecture round, where the kernel leaves the filter alone, against the weight
+    round: the same gradients up to the last bit of a stored bfloat16 number (the sums over the batch are grouped differently)."""
+    t, b = W.Block(), W.Block()
+    t.cba(0, 16, 1, act=W.ACT_NONE)
+    v = b.mix([b.cba(0, 16, 1, act=W.ACT_NONE), b.cba(0, 16, 1, act=W.ACT_NONE)], [0.5, 0.5])
+    v = b.cba(v, c, 1, act=front)
+    v = b.cba(v, c, k, groups=c, act=behind)
+    b.cba(v, 16, 1, act=W.ACT_NONE)
+    wl = W.Workload("dw_backward", n, (8, h, w), [t], [b], "bf16", lr=0.05)
+    worst = local_parity.run_and_check(wl, n, tol_dw=TOL_DW)
+    print(", ".join(f"{key} {e:.1e}" for key, e in sorted(worst.items())), flush=True)
+    grads = []
+    for arch in (False, True):
+        d = parity.make_distiller(wl, n, "bf16")
+        d.teacher_relay(torch.from_numpy(W.make_input(wl, batch=n)).cuda())
+        d.set_profile(True)
+        (d.arch_step if arch else d.student_step)(1, wl.lr)
+        names = {p["name"] for p in d.get_profile()}
+        assert f"dw_{'dgrad' if arch else 'wgrad'}_mfma_bn_k{k}" in names, names
+        d.set_profile(False)
+        grads.append([d.read_grad_value(0, i) for i in (3, 4, 5)])       # of the mix, the layer in front and the depthwise one
+    for x, y in zip(*grads):
+        assert np.max(np.abs(x - y)) < 2.0 ** -7 * np.max(np.abs(x))
+
+
 @pytest.mark.parametrize("folded", [False, True])
 @pytest.mark.parametrize("k", [3, 5, 7])
 def test_statistics_of_channels_far_from_zero(k, folded):
