@@ -435,7 +435,7 @@ __device__ __forceinline__ void dma_tile(unsigned char* smem, float* ep_s, const
 // fastest, then class, then row tile: the classes of one row range read the same rows of A, and every XCD
 // gets the same mix of heavy and light classes.
 template <int MODE, int BN, int BK, int EPI>
-__global__ __launch_bounds__(kDmaThreads) void igemm_dma_kernel(const bf16_t* __restrict__ A,
+__device__ __forceinline__ void igemm_dma_block(const Blk& blk, const bf16_t* __restrict__ A,
                                                                 const bf16_t* __restrict__ Bw,
                                                                 bf16_t* __restrict__ Out,
                                                                 const float* __restrict__ ep_a,
@@ -443,8 +443,8 @@ __global__ __launch_bounds__(kDmaThreads) void igemm_dma_kernel(const bf16_t* __
                                                                 IgemmArgs g) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[dma_lds_bytes(BN, BK, EPI == EPI_ACCUM)];
   __shared__ __attribute__((aligned(16))) float ep_s[EPI == EPI_AFFINE_ACT ? 2 * BN : 4];
-  if ((int)blockIdx.x < g.big_tiles) {
-    const int tile = xcd_contiguous(blockIdx.x, g.big_tiles);
+  if ((int)blk.x < g.big_tiles) {
+    const int tile = xcd_contiguous(blk.x, g.big_tiles);
     const int tile_n = tile % g.tiles_n;
     int tile_m = tile / g.tiles_n, cls = -1;
     if (MODE == 1 && g.par_classes) {
@@ -453,11 +453,17 @@ __global__ __launch_bounds__(kDmaThreads) void igemm_dma_kernel(const bf16_t* __
     }
     dma_tile<MODE, kDmaBM, BN, BK, dma_waves_m(BN), EPI>(smem, ep_s, A, Bw, Out, ep_a, ep_b, act, g, tile_m * kDmaBM, tile_n * BN, tile_m, cls);
   } else {
-    const int tile = blockIdx.x - g.big_tiles;
+    const int tile = blk.x - g.big_tiles;
     const int tile_n = tile % g.tiles_n, tile_m = tile / g.tiles_n;
     dma_tile<MODE, kDmaTailBM, BN, BK, 1, EPI>(smem, ep_s, A, Bw, Out, ep_a, ep_b, act, g, g.tail_m0 + tile_m * kDmaTailBM,
                                                tile_n * BN, g.big_tiles / g.tiles_n + tile_m);
   }
+}
+template <int MODE, int BN, int BK, int EPI>
+__global__ __launch_bounds__(kDmaThreads) void igemm_dma_kernel(
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ Bw, bf16_t* __restrict__ Out, const float* __restrict__ ep_a,
+    const float* __restrict__ ep_b, int act, IgemmArgs g) {
+  igemm_dma_block<MODE, BN, BK, EPI>(one_block(), A, Bw, Out, ep_a, ep_b, act, g);
 }
 
 // ---------------------------------------------------------------------------

@@ -195,8 +195,8 @@ __device__ __forceinline__ int xcd_contiguous(int w, int total) {
 // UNI: the channel count of the gathered tensor is a multiple of the 32-element K step, so a step
 // lies inside one filter tap and (r, s, c0) are the same for the whole workgroup: they live in
 // scalar registers and a load costs a lane two adds, two compares, an add and a select.
-template <int MODE, int BM, int BN, int EPI, bool UNI, int BK = IG_BK>
-__global__ __launch_bounds__(256) void igemm_kernel(const bf16_t* __restrict__ A,
+template <int MODE, int BM, int BN, int EPI, bool UNI, int BK>
+__device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __restrict__ A,
                                                     const bf16_t* __restrict__ Bw,
                                                     bf16_t* __restrict__ Out,
                                                     const float* __restrict__ ep_a,
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(256) void igemm_kernel(const bf16_t* __restrict__ A
   // an XCD works through a contiguous run of tiles (column tiles of one row tile next to each other,
   // then the next row tile): the 3x3 halo rows and the rows shared by column tiles are then re-read
   // from that XCD's L2 instead of crossing the fabric once per tap.
-  const int tile = xcd_contiguous(blockIdx.x, g.tiles_m * g.tiles_n * g.splits);
+  const int tile = xcd_contiguous(blk.x, g.tiles_m * g.tiles_n * g.splits);
   const int tile_n = tile % g.tiles_n, tile_m = (tile / g.tiles_n) % g.tiles_m, kslice = tile / (g.tiles_n * g.tiles_m);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const int chunk = tid % CPR, prow = tid / CPR;
@@ -608,12 +608,18 @@ __global__ __launch_bounds__(256) void igemm_kernel(const bf16_t* __restrict__ A
       }
   }
 }
+template <int MODE, int BM, int BN, int EPI, bool UNI, int BK = IG_BK>
+__global__ __launch_bounds__(256) void igemm_kernel(
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ Bw, bf16_t* __restrict__ Out, const float* __restrict__ ep_a,
+    const float* __restrict__ ep_b, int act, IgemmArgs g) {
+  igemm_block<MODE, BM, BN, EPI, UNI, BK>(one_block(), A, Bw, Out, ep_a, ep_b, act, g);
+}
 
 // Second stage of a split-K launch: out = epilogue(sum_s part[s]) in split order.
-__global__ void splitk_epilogue_kernel(const float* __restrict__ part, bf16_t* __restrict__ out,
+__device__ __forceinline__ void splitk_epilogue_block(const Blk& blk, const float* __restrict__ part, bf16_t* __restrict__ out,
                                        const float* __restrict__ ep_a, const float* __restrict__ ep_b,
                                        int act, int epi, long nvec, int ncv, int splits) {
-  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < nvec; i += (long)gridDim.x * blockDim.x) {
+  for (long i = blk.x * (long)blockDim.x + threadIdx.x; i < nvec; i += (long)blk.gx * blockDim.x) {
     const int c0 = (int)(i % ncv) * 8;
     float acc[8];
 #pragma unroll
@@ -635,6 +641,10 @@ __global__ void splitk_epilogue_kernel(const float* __restrict__ part, bf16_t* _
     }
     IO<bf16_t>::st(out + i * 8, acc);
   }
+}
+__global__ void splitk_epilogue_kernel(const float* __restrict__ part, bf16_t* __restrict__ out, const float* __restrict__ ep_a,
+    const float* __restrict__ ep_b, int act, int epi, long nvec, int ncv, int splits) {
+  splitk_epilogue_block(one_block(), part, out, ep_a, ep_b, act, epi, nvec, ncv, splits);
 }
 
 // ---------------------------------------------------------------------------
@@ -674,7 +684,7 @@ __device__ __forceinline__ bf16x8 lds_read_tr8(const bf16_t* p, int row_pitch) {
 }
 
 template <int TM, int TN>
-__global__ __launch_bounds__(256) void wgrad_tr_kernel(const bf16_t* __restrict__ dy,
+__device__ __forceinline__ void wgrad_tr_block(const Blk& blk, const bf16_t* __restrict__ dy,
                                                        const bf16_t* __restrict__ x,
                                                        float* __restrict__ part, WgradTrArgs g) {
   constexpr int BKP = 32;
@@ -690,7 +700,7 @@ __global__ __launch_bounds__(256) void wgrad_tr_kernel(const bf16_t* __restrict_
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   // all tiles of one pixel slice read the same rows of dy and x: keep them on one XCD (one L2)
-  const int tile = xcd_contiguous(blockIdx.x, g.tiles_k * g.tiles_j * g.splits);
+  const int tile = xcd_contiguous(blk.x, g.tiles_k * g.tiles_j * g.splits);
   const int slice = tile / (g.tiles_k * g.tiles_j);
   const int k0 = ((tile / g.tiles_j) % g.tiles_k) * TM, j0 = (tile % g.tiles_j) * TN;
   const int mbeg = slice * g.pix_per_split;
@@ -811,6 +821,11 @@ __global__ __launch_bounds__(256) void wgrad_tr_kernel(const bf16_t* __restrict_
         if (row < g.K) out[(size_t)row * g.J + col] = acc[i][j][v];
       }
   }
+}
+template <int TM, int TN>
+__global__ __launch_bounds__(256) void wgrad_tr_kernel(const bf16_t* __restrict__ dy,
+    const bf16_t* __restrict__ x, float* __restrict__ part, WgradTrArgs g) {
+  wgrad_tr_block<TM, TN>(one_block(), dy, x, part, g);
 }
 
 }  // namespace pbd

@@ -126,8 +126,8 @@ struct DwArgs {
 // compute unit); 64 channels a workgroup (K = 5 31 us, batch 33 12.6 against 11.4).
 // ACC (backward-data into a value that already has a gradient): the result is added to what dst holds, in float32, and rounded
 // once.  What dst holds is loaded ahead of the products and passes through LDS the way the result does.
-template <int K, bool FLIP, bool FOLD = false, bool STATS = false, bool ACC = false>
-__global__ __launch_bounds__(256, K == 7 || ACC ? 3 : 4) void dw_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
+template <int K, bool FLIP, bool FOLD, bool STATS, bool ACC>
+__device__ __forceinline__ void dw_mfma_block(const Blk& blk, const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
                                                          bf16_t* __restrict__ dst, const float* __restrict__ a,
                                                          const float* __restrict__ b, int act, DwArgs g, NormFold fold) {
   typedef DwGeom<K> G;
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(256, K == 7 || ACC ? 3 : 4) void dw_mfma_kernel(con
   __shared__ __attribute__((aligned(16))) DwFold folded;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slice = wave & 1, half = wave >> 1;
-  const int wg = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int wg = xcd_contiguous(blk.x, blk.gx);
   const int cv0 = (wg % g.groups) * (kDwCh / 8);
   const int tile_begin = (wg / g.groups) * g.per_block, tile_end = min(g.tiles, tile_begin + g.per_block);
   const __amdgpu_buffer_rsrc_t xr = tensor_rsrc(x, g.bytes);
@@ -376,6 +376,12 @@ __global__ __launch_bounds__(256, K == 7 || ACC ? 3 : 4) void dw_mfma_kernel(con
     }
   }
 }
+template <int K, bool FLIP, bool FOLD = false, bool STATS = false, bool ACC = false>
+__global__ __launch_bounds__(256, K == 7 || ACC ? 3 : 4) void dw_mfma_kernel(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ w, bf16_t* __restrict__ dst, const float* __restrict__ a,
+    const float* __restrict__ b, int act, DwArgs g, NormFold fold) {
+  dw_mfma_block<K, FLIP, FOLD, STATS, ACC>(one_block(), x, w, dst, a, b, act, g, fold);
+}
 
 // Backward-weight of the same layers: dW[r][s] = sum over pixels of x[p + r][q + s] dy[p][q], per channel.
 // A product takes four neighbouring columns of one input row: A[i][k] = x[y][4 c + i + k] (s = i + 4 it: the four lanes of a
@@ -386,8 +392,8 @@ __global__ __launch_bounds__(256, K == 7 || ACC ? 3 : 4) void dw_mfma_kernel(con
 // column halves meet in LDS at the end; one partial result per workgroup as in the other kernels.  Bound by the shifts and
 // LDS reads.  Launch averages over the supernet step, with FOLD, against a tile kernel on the vector ALUs that read the
 // normalised tensor: 7 x 7 91 -> 47 us, 5 x 5 72 -> 41, 3 x 3 37 -> 32.
-template <int K, bool FOLD = false>
-__global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
+template <int K, bool FOLD>
+__device__ __forceinline__ void dw_wgrad_mfma_block(const Blk& blk, const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
                                                                float* __restrict__ part, DwArgs g, NormFold fold) {
   typedef DwGeom<K> G;
   constexpr int pad = K / 2, NIT = K == 3 ? 1 : 2, QS = K == 7 ? 1 : 2;    // (QS: accumulators per tap block, one per quad column where registers allow)
@@ -398,7 +404,7 @@ __global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __r
   __shared__ __attribute__((aligned(16))) DwFold folded;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slice = wave & 1, half = wave >> 1;
-  const int wg = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int wg = xcd_contiguous(blk.x, blk.gx);
   const int cv0 = (wg % g.groups) * (kDwCh / 8), chunk = wg / g.groups;
   const int tile_begin = chunk * g.per_block, tile_end = min(g.tiles, tile_begin + g.per_block);
   const __amdgpu_buffer_rsrc_t xr = tensor_rsrc(x, g.bytes), dr = tensor_rsrc(dy, g.bytes);
@@ -536,6 +542,11 @@ __global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __r
       }
     }
 }
+template <int K, bool FOLD = false>
+__global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __restrict__ dy,
+    const bf16_t* __restrict__ x, float* __restrict__ part, DwArgs g, NormFold fold) {
+  dw_wgrad_mfma_block<K, FOLD>(one_block(), dy, x, part, g, fold);
+}
 
 // The whole backward pass of a stride-1 layer between two batch norms, y1 -> z1 = act(bn(y1)) -> y2 = z1 * w -> z2 = act(bn(y2)), in one
 // pass over the tensors: reads dz2, y2 (with the filter's halo) and y1, forms dy2 from dz2 and y2 as it stages them (bn_bwd_apply_kernel's
@@ -607,8 +618,7 @@ __device__ __forceinline__ void dw_fold_store(unsigned char* dst, const uint4 (&
 
 // WGRAD false: the architecture round, which leaves the filters alone.
 template <int K, bool WGRAD>
-__global__ __launch_bounds__(256, WGRAD ? (K == 7 ? 2 : 3) : (K == 7 ? 3 : 4)) void dw_bwd_mfma_kernel(
-    const bf16_t* __restrict__ dz, const bf16_t* __restrict__ y2, const bf16_t* __restrict__ y1, const bf16_t* __restrict__ w,
+__device__ __forceinline__ void dw_bwd_mfma_block(const Blk& blk, const bf16_t* __restrict__ dz, const bf16_t* __restrict__ y2, const bf16_t* __restrict__ y1, const bf16_t* __restrict__ w,
     bf16_t* __restrict__ dx, float* __restrict__ wpart, float* __restrict__ spart, DwArgs g, BnBwd f2, NormFold f1) {
   typedef DwGeom<K> G;
   constexpr int NT = G::NT, pad = K / 2, NIT = K == 3 ? 1 : 2, QS = K == 3 ? 2 : 1;
@@ -621,7 +631,7 @@ __global__ __launch_bounds__(256, WGRAD ? (K == 7 ? 2 : 3) : (K == 7 ? 3 : 4)) v
   __shared__ __attribute__((aligned(16))) DwFold c1;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slice = wave & 1, half = wave >> 1;
-  const int wg = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int wg = xcd_contiguous(blk.x, blk.gx);
   const int cv0 = (wg % g.groups) * (kDwCh / 8), chunk = wg / g.groups, C = g.ncv * 8;
   const int tile_begin = chunk * g.per_block, tile_end = min(g.tiles, tile_begin + g.per_block);
   const __amdgpu_buffer_rsrc_t zr = tensor_rsrc(dz, g.bytes), y2r = tensor_rsrc(y2, g.bytes), y1r = tensor_rsrc(y1, g.bytes);
@@ -904,6 +914,12 @@ __global__ __launch_bounds__(256, WGRAD ? (K == 7 ? 2 : 3) : (K == 7 ? 3 : 4)) v
       }
     }
 }
+template <int K, bool WGRAD>
+__global__ __launch_bounds__(256, WGRAD ? (K == 7 ? 2 : 3) : (K == 7 ? 3 : 4)) void dw_bwd_mfma_kernel(
+    const bf16_t* __restrict__ dz, const bf16_t* __restrict__ y2, const bf16_t* __restrict__ y1, const bf16_t* __restrict__ w,
+    bf16_t* __restrict__ dx, float* __restrict__ wpart, float* __restrict__ spart, DwArgs g, BnBwd f2, NormFold f1) {
+  dw_bwd_mfma_block<K, WGRAD>(one_block(), dz, y2, y1, w, dx, wpart, spart, g, f2, f1);
+}
 
 // Backward-weight of a stride-2 layer, dW[r][s] = sum x[2 p + r - pad][2 q + s - pad] dy[p][q].  Columns (and rows) of x of one
 // parity are a stride-1 problem with at most (K + 1) / 2 <= 4 taps, so one product covers all taps of a parity pair: the four
@@ -915,7 +931,7 @@ __global__ __launch_bounds__(256, WGRAD ? (K == 7 ? 2 : 3) : (K == 7 ? 3 : 4)) v
 // wins on few tiles (a third of the products are real there, and the shifts cost the same).
 constexpr int kDwS2TileH = 8;
 template <int K>
-__global__ __launch_bounds__(256, 2) void dw_wgrad_s2_mfma_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
+__device__ __forceinline__ void dw_wgrad_s2_mfma_block(const Blk& blk, const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
                                                                   float* __restrict__ part, DwArgs g) {
   constexpr int pad = K / 2, IH = 2 * kDwS2TileH - 2 + K, NQ = 5, CVB = kDwCh / 8;
   constexpr int ROWX = 2 * NQ * 8, CHX = (IH * ROWX + 31) / 32 * 32 + 8;
@@ -926,7 +942,7 @@ __global__ __launch_bounds__(256, 2) void dw_wgrad_s2_mfma_kernel(const bf16_t* 
   __shared__ __attribute__((aligned(16))) unsigned char smem[ZERO + ROWD];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slice = wave & 1, par = wave >> 1;
-  const int wg = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int wg = xcd_contiguous(blk.x, blk.gx);
   const int cv0 = (wg % g.groups) * CVB, chunk = wg / g.groups;
   const int tile_begin = chunk * g.per_block, tile_end = min(g.tiles, tile_begin + g.per_block);
   const __amdgpu_buffer_rsrc_t xr = tensor_rsrc(x, g.bytes), dr = tensor_rsrc(dy, g.dy_bytes);
@@ -1018,6 +1034,11 @@ __global__ __launch_bounds__(256, 2) void dw_wgrad_s2_mfma_kernel(const bf16_t* 
       const int r = 2 * n4 + e, s = 2 * v + par;
       if (r < K && s < K) part[((size_t)chunk * K * K + r * K + s) * (g.ncv * 8) + cv0 * 8 + ch] = sum[e][v];
     }
+}
+template <int K>
+__global__ __launch_bounds__(256, 2) void dw_wgrad_s2_mfma_kernel(const bf16_t* __restrict__ dy,
+    const bf16_t* __restrict__ x, float* __restrict__ part, DwArgs g) {
+  dw_wgrad_s2_mfma_block<K>(one_block(), dy, x, part, g);
 }
 
 }  // namespace pbd

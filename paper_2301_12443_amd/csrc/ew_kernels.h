@@ -11,6 +11,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "many.h"
+
 namespace pbd {
 
 typedef __bf16 bf16_t;
@@ -308,8 +310,8 @@ template <> __device__ __forceinline__ float as_stored<bf16_t>(float v) { return
 
 // res (optional): a residual add fused into the pass, z = res_act(stored(act(bn(y))) + res): the same
 // numbers as storing the normalised tensor and adding in a second kernel, without that tensor
-template <class T, bool STREAM = false>
-__global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ y, T* __restrict__ z,
+template <class T, bool STREAM>
+__device__ __forceinline__ void bn_apply_block(const Blk& blk, const T* __restrict__ y, T* __restrict__ z,
                                                        const float* __restrict__ mean,
                                                        const float* __restrict__ invstd,
                                                        const float* __restrict__ gamma,
@@ -317,9 +319,9 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ y, 
                                                        int act, ColGrid g, const T* __restrict__ res, int res_act) {
   const int ncv = Cp / 8;
   const int cv_lane = threadIdx.x % g.cvl, row_lane = threadIdx.x / g.cvl, rl = 256 / g.cvl;
-  const int cv = blockIdx.x * g.cvl + cv_lane;
+  const int cv = blk.x * g.cvl + cv_lane;
   if (cv >= ncv || row_lane >= rl) return;
-  const long r0 = blockIdx.y * g.rows_per_chunk;
+  const long r0 = blk.y * g.rows_per_chunk;
   const long r1 = min(M, r0 + g.rows_per_chunk);
   float mu[8], a[8], b[8];
 #pragma unroll
@@ -366,18 +368,24 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ y, 
     IO<T>::template st_t<STREAM>(z + (r * ncv + cv) * 8, v);
   }
 }
+template <class T, bool STREAM = false>
+__global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ y,
+    T* __restrict__ z, const float* __restrict__ mean, const float* __restrict__ invstd, const float* __restrict__ gamma,
+    const float* __restrict__ beta, long M, int Cp, int act, ColGrid g, const T* __restrict__ res, int res_act) {
+  bn_apply_block<T, STREAM>(one_block(), y, z, mean, invstd, gamma, beta, M, Cp, act, g, res, res_act);
+}
 
 // part[chunk][0][c] = sum (y - piv), part[chunk][1][c] = sum (y - piv)^2 with the pivot
 // piv[c] = y[row 0][c]: shifting by a sample of the channel keeps the variance free of the
 // cancellation that  E[y^2] - mean^2  suffers when |mean| >> std
-template <class T, bool STREAM = false>
-__global__ __launch_bounds__(256) void bn_stats_kernel(const T* __restrict__ y, float* __restrict__ part,
+template <class T, bool STREAM>
+__device__ __forceinline__ void bn_stats_block(const Blk& blk, const T* __restrict__ y, float* __restrict__ part,
                                                        long M, int Cp, ColGrid g) {
   extern __shared__ float smem[];
   const int ncv = Cp / 8;
   const int cv_lane = threadIdx.x % g.cvl, row_lane = threadIdx.x / g.cvl, rl = 256 / g.cvl;
-  const int cv = blockIdx.x * g.cvl + cv_lane;
-  const long r0 = blockIdx.y * g.rows_per_chunk;
+  const int cv = blk.x * g.cvl + cv_lane;
+  const long r0 = blk.y * g.rows_per_chunk;
   const long r1 = min(M, r0 + g.rows_per_chunk);
   float acc[16];
 #pragma unroll
@@ -418,10 +426,15 @@ __global__ __launch_bounds__(256) void bn_stats_kernel(const T* __restrict__ y, 
   bool owner;
   block_col_reduce<16>(acc, smem, g.cvl, cv_lane, row_lane, out, owner);
   if (owner && cv < ncv) {
-    float* p = part + (long)blockIdx.y * 2 * Cp + cv * 8;
+    float* p = part + (long)blk.y * 2 * Cp + cv * 8;
 #pragma unroll
     for (int k = 0; k < 8; ++k) { p[k] = out[k]; p[Cp + k] = out[8 + k]; }
   }
+}
+template <class T, bool STREAM = false>
+__global__ __launch_bounds__(256) void bn_stats_kernel(const T* __restrict__ y,
+    float* __restrict__ part, long M, int Cp, ColGrid g) {
+  bn_stats_block<T, STREAM>(one_block(), y, part, M, Cp, g);
 }
 
 // Finalize kernels run 8 channels x 32 lanes per block (thread = lane * 8 + channel): lane l adds
@@ -469,11 +482,11 @@ __device__ __forceinline__ void finalize_sums(const float* __restrict__ part, in
 //   rm <- (1-rho) rm + rho mean,  rv <- (1-rho) rv + rho var m/(m-1)
 // keep (optional): [2][Cp] copies of gamma and beta as the step's normalisation uses them (the update overwrites both),
 // for a normalised tensor that is not written and may be asked for later
-template <class T, bool GROUPS = false>
-__global__ void bn_finalize_kernel(const float* __restrict__ part, const T* __restrict__ y, int chunks,
+template <class T, bool GROUPS>
+__device__ __forceinline__ void bn_finalize_block(const Blk& blk, const float* __restrict__ part, const T* __restrict__ y, int chunks,
                                    int Cp, double m, float* mean, float* invstd, float* rmean,
                                    float* rvar, float eps, float rho, const float* gamma, const float* beta, float* keep) {
-  const int c = blockIdx.x * kFinalizeChannels + (threadIdx.x & (kFinalizeChannels - 1)), lane = threadIdx.x >> 3;
+  const int c = blk.x * kFinalizeChannels + (threadIdx.x & (kFinalizeChannels - 1)), lane = threadIdx.x >> 3;
   double s1, s2;
   finalize_sums<GROUPS>(part, chunks, Cp, c, lane, s1, s2);
   if (c >= Cp || lane != 0) return;
@@ -487,17 +500,26 @@ __global__ void bn_finalize_kernel(const float* __restrict__ part, const T* __re
   rmean[c] = (1.f - rho) * rmean[c] + rho * (float)mu;
   rvar[c] = (1.f - rho) * rvar[c] + rho * (float)(var * m / (m - 1.0));
 }
+template <class T, bool GROUPS = false>
+__global__ void bn_finalize_kernel(const float* __restrict__ part, const T* __restrict__ y,
+    int chunks, int Cp, double m, float* mean, float* invstd, float* rmean, float* rvar, float eps, float rho, const float* gamma,
+    const float* beta, float* keep) {
+  bn_finalize_block<T, GROUPS>(one_block(), part, y, chunks, Cp, m, mean, invstd, rmean, rvar, eps, rho, gamma, beta, keep);
+}
 
 // out[g][i] = sum of part[k][i] over the `per` chunks of group g, in order: shortens the list of partial
 // sums that a finalize kernel walks through when a convolution's row tiles delivered thousands of them
 constexpr int kStatGroupsMax = 1024;   // partial sums a batch-norm finalize walks through at most
-__global__ void regroup_partials_kernel(const float* __restrict__ part, float* __restrict__ out, int chunks, int n, int per) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void regroup_partials_block(const Blk& blk, const float* __restrict__ part, float* __restrict__ out, int chunks, int n, int per) {
+  const int i = blk.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const int k0 = blockIdx.y * per, k1 = min(chunks, k0 + per);
+  const int k0 = blk.y * per, k1 = min(chunks, k0 + per);
   float s = 0.f;
   for (int k = k0; k < k1; ++k) s += part[(long)k * n + i];
-  out[(long)blockIdx.y * n + i] = s;
+  out[(long)blk.y * n + i] = s;
+}
+__global__ void regroup_partials_kernel(const float* __restrict__ part, float* __restrict__ out, int chunks, int n, int per) {
+  regroup_partials_block(one_block(), part, out, chunks, n, per);
 }
 
 // BN backward, stage 1: with xhat = (y - mean)*invstd, pre = gamma*xhat + beta and
@@ -509,20 +531,19 @@ __global__ void regroup_partials_kernel(const float* __restrict__ part, float* _
 // LOSS (with RES and zres): the add's output is the block's output S.  dz is then the teacher's activation A,
 // the gradient of the add's output is 2 (S - A) / M rounded as it would be stored (Sec. II-A, the loss of the
 // block's output), and loss_part[workgroup] = sum (S - A)^2 over the workgroup's elements.
-template <class T, bool RES = false, bool LOSS = false, bool STREAM = false>
-__global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(
-    const T* __restrict__ dz, const T* __restrict__ y, const float* __restrict__ gamma,
+template <class T, bool RES, bool LOSS, bool STREAM>
+__device__ __forceinline__ void bn_bwd_reduce_block(const Blk& blk, const T* __restrict__ dz, const T* __restrict__ y, const float* __restrict__ gamma,
     const float* __restrict__ beta, const float* __restrict__ mean, const float* __restrict__ invstd,
-    float* __restrict__ part, long M, int Cp, int act, ColGrid g, const T* __restrict__ zres = nullptr,
-    int res_act = 0, T* __restrict__ dstore = nullptr, float* __restrict__ loss_part = nullptr,
-    float two_over_m = 0.f) {
+    float* __restrict__ part, long M, int Cp, int act, ColGrid g, const T* __restrict__ zres,
+    int res_act, T* __restrict__ dstore, float* __restrict__ loss_part,
+    float two_over_m) {
   static_assert(RES || !LOSS, "the loss rides only where the add does");
   float lacc = 0.f;
   extern __shared__ float smem[];
   const int ncv = Cp / 8;
   const int cv_lane = threadIdx.x % g.cvl, row_lane = threadIdx.x / g.cvl, rl = 256 / g.cvl;
-  const int cv = blockIdx.x * g.cvl + cv_lane;
-  const long r0 = blockIdx.y * g.rows_per_chunk;
+  const int cv = blk.x * g.cvl + cv_lane;
+  const long r0 = blk.y * g.rows_per_chunk;
   const long r1 = min(M, r0 + g.rows_per_chunk);
   float acc[16];
 #pragma unroll
@@ -614,7 +635,7 @@ __global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(
   bool owner;
   block_col_reduce<16>(acc, smem, g.cvl, cv_lane, row_lane, out, owner);
   if (owner && cv < ncv) {
-    float* p = part + (long)blockIdx.y * 2 * Cp + cv * 8;
+    float* p = part + (long)blk.y * 2 * Cp + cv * 8;
 #pragma unroll
     for (int k = 0; k < 8; ++k) { p[k] = out[k]; p[Cp + k] = out[8 + k]; }
   }
@@ -626,15 +647,23 @@ __global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(
       if ((int)threadIdx.x < h) smem[threadIdx.x] += smem[threadIdx.x + h];
       __syncthreads();
     }
-    if (threadIdx.x == 0) loss_part[blockIdx.y * gridDim.x + blockIdx.x] = smem[0];
+    if (threadIdx.x == 0) loss_part[blk.y * blk.gx + blk.x] = smem[0];
   }
+}
+template <class T, bool RES = false, bool LOSS = false, bool STREAM = false>
+__global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(
+    const T* __restrict__ dz, const T* __restrict__ y, const float* __restrict__ gamma, const float* __restrict__ beta,
+    const float* __restrict__ mean, const float* __restrict__ invstd, float* __restrict__ part, long M, int Cp, int act, ColGrid g,
+    const T* __restrict__ zres = nullptr, int res_act = 0, T* __restrict__ dstore = nullptr, float* __restrict__ loss_part = nullptr,
+    float two_over_m = 0.f) {
+  bn_bwd_reduce_block<T, RES, LOSS, STREAM>(one_block(), dz, y, gamma, beta, mean, invstd, part, M, Cp, act, g, zres, res_act, dstore, loss_part, two_over_m);
 }
 
 // stage 2: dbeta, dgamma (the parameter gradients) and the per-channel terms
 // k2 = dbeta/m, k3 = dgamma/m of  dy = gamma*invstd*(dpre - k2 - xhat*k3)
-__global__ void bn_bwd_finalize_kernel(const float* __restrict__ part, int chunks, int Cp, double m,
+__device__ __forceinline__ void bn_bwd_finalize_block(const Blk& blk, const float* __restrict__ part, int chunks, int Cp, double m,
                                        float* g_gamma, float* g_beta, float* k2, float* k3) {
-  const int c = blockIdx.x * kFinalizeChannels + (threadIdx.x & (kFinalizeChannels - 1)), lane = threadIdx.x >> 3;
+  const int c = blk.x * kFinalizeChannels + (threadIdx.x & (kFinalizeChannels - 1)), lane = threadIdx.x >> 3;
   double sb, sg;
   finalize_sums(part, chunks, Cp, c, lane, sb, sg);
   if (c >= Cp || lane != 0) return;
@@ -643,19 +672,22 @@ __global__ void bn_bwd_finalize_kernel(const float* __restrict__ part, int chunk
   k2[c] = (float)(sb / m);
   k3[c] = (float)(sg / m);
 }
+__global__ void bn_bwd_finalize_kernel(const float* __restrict__ part, int chunks, int Cp, double m, float* g_gamma, float* g_beta,
+    float* k2, float* k3) {
+  bn_bwd_finalize_block(one_block(), part, chunks, Cp, m, g_gamma, g_beta, k2, k3);
+}
 
 // stage 3: gradient w.r.t. the convolution output, written to dy (dy == dz: in place; column-grid launch, each
 // thread reads its elements before it writes them)
-template <class T, bool STREAM = false>
-__global__ __launch_bounds__(256) void bn_bwd_apply_kernel(
-    const T* dz, T* dy, const T* __restrict__ y, const float* __restrict__ gamma,
+template <class T, bool STREAM>
+__device__ __forceinline__ void bn_bwd_apply_block(const Blk& blk, const T* dz, T* dy, const T* __restrict__ y, const float* __restrict__ gamma,
     const float* __restrict__ beta, const float* __restrict__ mean, const float* __restrict__ invstd,
     const float* __restrict__ k2, const float* __restrict__ k3, long M, int Cp, int act, ColGrid g) {
   const int ncv = Cp / 8;
   const int cv_lane = threadIdx.x % g.cvl, row_lane = threadIdx.x / g.cvl, rl = 256 / g.cvl;
-  const int cv = blockIdx.x * g.cvl + cv_lane;
+  const int cv = blk.x * g.cvl + cv_lane;
   if (cv >= ncv || row_lane >= rl) return;
-  const long r0 = blockIdx.y * g.rows_per_chunk;
+  const long r0 = blk.y * g.rows_per_chunk;
   const long r1 = min(M, r0 + g.rows_per_chunk);
   float mu[8], a[8], b[8], is[8], c2[8], c3[8];
 #pragma unroll
@@ -699,6 +731,12 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(
     }
     IO<T>::template st_t<STREAM>(dy + (r * ncv + cv) * 8, d);
   }
+}
+template <class T, bool STREAM = false>
+__global__ __launch_bounds__(256) void bn_bwd_apply_kernel(const T* dz, T* dy,
+    const T* __restrict__ y, const float* __restrict__ gamma, const float* __restrict__ beta, const float* __restrict__ mean,
+    const float* __restrict__ invstd, const float* __restrict__ k2, const float* __restrict__ k3, long M, int Cp, int act, ColGrid g) {
+  bn_bwd_apply_block<T, STREAM>(one_block(), dz, dy, y, gamma, beta, mean, invstd, k2, k3, M, Cp, act, g);
 }
 
 // ---------------------------------------------------------------------------
@@ -750,13 +788,12 @@ __device__ __forceinline__ void block_sum16(const float (&v)[16], double (&out)[
 // y -> batch statistics (pivot-shifted sums as in bn_stats_kernel), running statistics, then
 // z = act((y - mean) * (gamma*invstd) + beta)
 template <class T>
-__global__ __launch_bounds__(kSmallThreads) void bn_small_fwd_kernel(
-    const T* __restrict__ y, T* __restrict__ z, const float* __restrict__ gamma, const float* __restrict__ beta,
+__device__ __forceinline__ void bn_small_fwd_block(const Blk& blk, const T* __restrict__ y, T* __restrict__ z, const float* __restrict__ gamma, const float* __restrict__ beta,
     float* __restrict__ mean, float* __restrict__ invstd, float* __restrict__ rmean, float* __restrict__ rvar,
     int M, int Cp, float eps, float rho, int act, unsigned bytes) {
   __shared__ float red[kSmallThreads / 64][16];
   __shared__ double tot[16];
-  const int ncv = Cp / 8, cv = xcd_slab(blockIdx.x, ncv), tid = threadIdx.x;
+  const int ncv = Cp / 8, cv = xcd_slab(blk.x, ncv), tid = threadIdx.x;
   const __amdgpu_buffer_rsrc_t ry = tensor_rsrc(y, bytes);
   typename BufIO<T>::Raw raw[kSmallRows];
 #pragma unroll
@@ -822,17 +859,22 @@ __global__ __launch_bounds__(kSmallThreads) void bn_small_fwd_kernel(
     IO<T>::st(z + ((long)r * ncv + cv) * 8, v);
   }
 }
+template <class T>
+__global__ __launch_bounds__(kSmallThreads) void bn_small_fwd_kernel(const T* __restrict__ y, T* __restrict__ z,
+    const float* __restrict__ gamma, const float* __restrict__ beta, float* __restrict__ mean, float* __restrict__ invstd,
+    float* __restrict__ rmean, float* __restrict__ rvar, int M, int Cp, float eps, float rho, int act, unsigned bytes) {
+  bn_small_fwd_block<T>(one_block(), y, z, gamma, beta, mean, invstd, rmean, rvar, M, Cp, eps, rho, act, bytes);
+}
 
 // BN backward in one launch: sums of dpre and dpre*xhat, the parameter gradients, then
 // dy = gamma*invstd*(dpre - dbeta/m - xhat*dgamma/m) over dz in place
 template <class T>
-__global__ __launch_bounds__(kSmallThreads) void bn_small_bwd_kernel(
-    T* dz, const T* __restrict__ y, const float* __restrict__ gamma, const float* __restrict__ beta,
+__device__ __forceinline__ void bn_small_bwd_block(const Blk& blk, T* dz, const T* __restrict__ y, const float* __restrict__ gamma, const float* __restrict__ beta,
     const float* __restrict__ mean, const float* __restrict__ invstd, float* __restrict__ g_gamma,
     float* __restrict__ g_beta, int M, int Cp, int act, unsigned bytes) {
   __shared__ float red[kSmallThreads / 64][16];
   __shared__ double tot[16];
-  const int ncv = Cp / 8, cv = xcd_slab(blockIdx.x, ncv), tid = threadIdx.x;
+  const int ncv = Cp / 8, cv = xcd_slab(blk.x, ncv), tid = threadIdx.x;
   const __amdgpu_buffer_rsrc_t ry = tensor_rsrc(y, bytes), rd = tensor_rsrc(dz, bytes);
   typename BufIO<T>::Raw rawd[kSmallRows], rawy[kSmallRows];
 #pragma unroll
@@ -897,6 +939,12 @@ __global__ __launch_bounds__(kSmallThreads) void bn_small_bwd_kernel(
     }
     IO<T>::st(dz + ((long)r * ncv + cv) * 8, d);
   }
+}
+template <class T>
+__global__ __launch_bounds__(kSmallThreads) void bn_small_bwd_kernel(T* dz, const T* __restrict__ y,
+    const float* __restrict__ gamma, const float* __restrict__ beta, const float* __restrict__ mean, const float* __restrict__ invstd,
+    float* __restrict__ g_gamma, float* __restrict__ g_beta, int M, int Cp, int act, unsigned bytes) {
+  bn_small_bwd_block<T>(one_block(), dz, y, gamma, beta, mean, invstd, g_gamma, g_beta, M, Cp, act, bytes);
 }
 
 // ---------------------------------------------------------------------------
@@ -1407,12 +1455,12 @@ __global__ __launch_bounds__(256) void transpose_weights_kernel(const T* __restr
 // loads in flight), then the SL lane sums are added in order, so the result does not depend on
 // scheduling.  SL = 8 for a few partials of a large tensor, 32 for many partials of a small one.
 template <int SL>
-__device__ __forceinline__ void sum_partials_body(const float* __restrict__ part, float* __restrict__ out, long n, int splits,
+__device__ __forceinline__ void sum_partials_body(const Blk& blk, const float* __restrict__ part, float* __restrict__ out, long n, int splits,
                                                   float4* red /*[256]*/) {
   constexpr int NO = 256 / SL;
   const int o = threadIdx.x % NO, l = threadIdx.x / NO;
   const long n4 = n / 4;
-  for (long base = (long)blockIdx.x * NO; base < n4; base += (long)gridDim.x * NO) {
+  for (long base = (long)blk.x * NO; base < n4; base += (long)blk.gx * NO) {
     const long i = base + o;
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
     if (i < n4) {
@@ -1445,9 +1493,14 @@ __device__ __forceinline__ void sum_partials_body(const float* __restrict__ part
 }
 constexpr int kManySplits = 64;       // from here on SL = 32
 template <int SL>
-__global__ __launch_bounds__(256) void sum_partials_kernel(const float* __restrict__ part, float* __restrict__ out, long n, int splits) {
+__device__ __forceinline__ void sum_partials_block(const Blk& blk, const float* __restrict__ part, float* __restrict__ out, long n, int splits) {
   __shared__ float4 red[256];
-  sum_partials_body<SL>(part, out, n, splits, red);
+  sum_partials_body<SL>(blk, part, out, n, splits, red);
+}
+template <int SL>
+__global__ __launch_bounds__(256) void sum_partials_kernel(const float* __restrict__ part, float* __restrict__ out,
+    long n, int splits) {
+  sum_partials_block<SL>(one_block(), part, out, n, splits);
 }
 // The same for many layers in one launch, blockIdx.y = layer: the weight gradients of a student block, whose partial
 // sums wait side by side until the update reads them.  A launch of its own per layer is 4 us for a few microseconds' worth of
@@ -1457,8 +1510,8 @@ __global__ __launch_bounds__(256) void sum_partials_batch_kernel(const float* __
                                                                  const SumEntry* __restrict__ table) {
   __shared__ float4 red[256];
   const SumEntry e = table[blockIdx.y];
-  if (e.splits >= kManySplits) sum_partials_body<32>(parts + e.part, outs + e.out, e.n, e.splits, red);
-  else sum_partials_body<8>(parts + e.part, outs + e.out, e.n, e.splits, red);
+  if (e.splits >= kManySplits) sum_partials_body<32>(one_block(), parts + e.part, outs + e.out, e.n, e.splits, red);
+  else sum_partials_body<8>(one_block(), parts + e.part, outs + e.out, e.n, e.splits, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -1520,7 +1573,7 @@ __global__ __launch_bounds__(256) void dw_fwd_kernel(const T* __restrict__ x, co
 // FLIP: read the filter mirrored (backward-data of a stride-1 convolution is the same sliding
 // sum with taps (K-1-r, K-1-s)); `accumulate` then adds to what dst holds.
 template <class T, int K, int STRIDE, int WS, bool FLIP>
-__global__ __launch_bounds__(256) void dw_slide_kernel(const T* __restrict__ x, const T* __restrict__ w,
+__device__ __forceinline__ void dw_slide_block(const Blk& blk, const T* __restrict__ x, const T* __restrict__ w,
                                                        T* dst, const float* __restrict__ a,
                                                        const float* __restrict__ b, int act, int accumulate,
                                                        int N, int H, int W, int P, int Q, int ncv, int pad,
@@ -1529,7 +1582,7 @@ __global__ __launch_bounds__(256) void dw_slide_kernel(const T* __restrict__ x, 
   const int QS = (Q + WS - 1) / WS;
   const long nitem = (long)N * P * QS * ncv;
   const __amdgpu_buffer_rsrc_t xr = tensor_rsrc(x, x_elems * (unsigned)sizeof(T));
-  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < nitem; i += (long)gridDim.x * blockDim.x) {
+  for (long i = blk.x * (long)blockDim.x + threadIdx.x; i < nitem; i += (long)blk.gx * blockDim.x) {
     const int cv = (int)(i % ncv);
     long seg = i / ncv;
     const int qs = (int)(seg % QS); seg /= QS;
@@ -1591,6 +1644,12 @@ __global__ __launch_bounds__(256) void dw_slide_kernel(const T* __restrict__ x, 
       IO<T>::st(out, acc[o]);
     }
   }
+}
+template <class T, int K, int STRIDE, int WS, bool FLIP>
+__global__ __launch_bounds__(256) void dw_slide_kernel(const T* __restrict__ x,
+    const T* __restrict__ w, T* dst, const float* __restrict__ a, const float* __restrict__ b, int act, int accumulate, int N, int H,
+    int W, int P, int Q, int ncv, int pad, unsigned x_elems) {
+  dw_slide_block<T, K, STRIDE, WS, FLIP>(one_block(), x, w, dst, a, b, act, accumulate, N, H, W, P, Q, ncv, pad, x_elems);
 }
 
 // LDS-tiled stride-1 3 x 3 depthwise convolution on the vector ALUs (bf16): a block stages the (8+K-1) x (16+K-1) input
@@ -1773,13 +1832,13 @@ __global__ __launch_bounds__(256) void dw_dgrad_kernel(const T* __restrict__ dy,
 // parity matches its own, (K+1)/2 per dimension, so only those are visited (K*K/4 instead of K*K
 // masked loads).
 template <class T, int K>
-__global__ __launch_bounds__(256) void dw_dgrad_s2_kernel(const T* __restrict__ dy, const T* __restrict__ w,
+__device__ __forceinline__ void dw_dgrad_s2_block(const Blk& blk, const T* __restrict__ dy, const T* __restrict__ w,
                                                           T* __restrict__ dx, int N, int H, int W, int P, int Q,
                                                           int ncv, int pad, int accumulate, unsigned dy_elems) {
   constexpr int HK = (K + 1) / 2;
   const long nvec = (long)N * H * W * ncv;
   const __amdgpu_buffer_rsrc_t dr = tensor_rsrc(dy, dy_elems * (unsigned)sizeof(T));
-  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < nvec; i += (long)gridDim.x * blockDim.x) {
+  for (long i = blk.x * (long)blockDim.x + threadIdx.x; i < nvec; i += (long)blk.gx * blockDim.x) {
     const int cv = (int)(i % ncv);
     long pix = i / ncv;
     const int ww = (int)(pix % W); pix /= W;
@@ -1816,22 +1875,27 @@ __global__ __launch_bounds__(256) void dw_dgrad_s2_kernel(const T* __restrict__ 
     IO<T>::st(dx + i * 8, acc);
   }
 }
+template <class T, int K>
+__global__ __launch_bounds__(256) void dw_dgrad_s2_kernel(const T* __restrict__ dy, const T* __restrict__ w,
+    T* __restrict__ dx, int N, int H, int W, int P, int Q, int ncv, int pad, int accumulate, unsigned dy_elems) {
+  dw_dgrad_s2_block<T, K>(one_block(), dy, w, dx, N, H, W, P, Q, ncv, pad, accumulate, dy_elems);
+}
 
 // dW[r][t][c] = sum over output pixels dY * X(shifted).  ROWS tap rows per block: 3x3 filters keep all
 // 9 x 8 accumulators in registers and read dY / X once; larger filters take one tap row per
 // blockIdx.z (grid = (slabs, chunks, k / ROWS)).  All taps of a pixel are requested before use.
 template <class T, int KMAX, int ROWS>
-__global__ __launch_bounds__(256) void dw_wgrad_kernel(const T* __restrict__ dy, const T* __restrict__ x,
+__device__ __forceinline__ void dw_wgrad_block(const Blk& blk, const T* __restrict__ dy, const T* __restrict__ x,
                                                        float* __restrict__ part, int N, int H, int W,
                                                        int P, int Q, int Cp, int k, int stride, int pad,
                                                        ColGrid g, unsigned x_elems) {
   extern __shared__ float smem[];
   const int ncv = Cp / 8;
   const int cv_lane = threadIdx.x % g.cvl, row_lane = threadIdx.x / g.cvl, rl = 256 / g.cvl;
-  const int cv = blockIdx.x * g.cvl + cv_lane;
-  const int rbase = blockIdx.z * ROWS;
+  const int cv = blk.x * g.cvl + cv_lane;
+  const int rbase = blk.z * ROWS;
   const long M = (long)N * P * Q;
-  const long r0 = blockIdx.y * g.rows_per_chunk;
+  const long r0 = blk.y * g.rows_per_chunk;
   const long r1 = min(M, r0 + g.rows_per_chunk);
   const __amdgpu_buffer_rsrc_t xr = tensor_rsrc(x, x_elems * (unsigned)sizeof(T));
   float acc[ROWS][KMAX * 8];
@@ -1885,12 +1949,18 @@ __global__ __launch_bounds__(256) void dw_wgrad_kernel(const T* __restrict__ dy,
 #pragma unroll
       for (int t = 0; t < KMAX; ++t) {
         if (t >= k) continue;
-        float* pp = part + ((long)blockIdx.y * k * k + (rbase + a) * k + t) * Cp + cv * 8;
+        float* pp = part + ((long)blk.y * k * k + (rbase + a) * k + t) * Cp + cv * 8;
 #pragma unroll
         for (int e = 0; e < 8; ++e) pp[e] = out[t * 8 + e];
       }
     }
   }
+}
+template <class T, int KMAX, int ROWS>
+__global__ __launch_bounds__(256) void dw_wgrad_kernel(const T* __restrict__ dy,
+    const T* __restrict__ x, float* __restrict__ part, int N, int H, int W, int P, int Q, int Cp, int k, int stride, int pad, ColGrid g,
+    unsigned x_elems) {
+  dw_wgrad_block<T, KMAX, ROWS>(one_block(), dy, x, part, N, H, W, P, Q, Cp, k, stride, pad, g, x_elems);
 }
 
 }  // namespace pbd

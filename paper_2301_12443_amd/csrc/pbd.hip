@@ -16,6 +16,8 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <new>
+#include <unordered_map>
 #include <utility>
 #include <vector>
 
@@ -90,8 +92,15 @@ struct OpPlan {
   size_t w2 = 0;
 };
 
+// The inputs of a mix op that are chains of layers over one value, the candidates of a mixed layer: ops first .. join - 1, whose
+// launches go out together (Lanes).  root: the value that all of them read.
+struct LaneGroup { int first, join, root; };
+
 struct BlockPlan {
   std::vector<OpPlan> ops;
+  std::vector<LaneGroup> groups;
+  std::vector<int> group_of, lane_of;   // per op: its group and its lane there (-1: none)
+  int lanes = 1;                        // regions of reduction scratch: the most lanes of a group
   std::vector<Shape> shapes;     // values, 0 = block input
   std::vector<size_t> val;       // scratch byte offset of each value (>=1)
   std::vector<size_t> dval;      // scratch byte offset of each value's gradient (student)
@@ -114,8 +123,29 @@ struct BlockPlan {
 
 }  // namespace
 
+// A launch that waits for those of the other lanes.
+struct LaneLaunch {
+  const void* kern;              // the kernel on its own
+  void (*one)(pbd_ctx*, hipStream_t, const LaneLaunch&);
+  dim3 grid, block;
+  size_t smem;
+  int lane, stage;               // stage: how many ops of the lane came before
+  bool serial;                   // adds to what another lane writes: after all others, in order
+  bool labelled;                 // profile entry
+  pbd_prof_entry label;
+  alignas(8) unsigned char args[448];
+};
+struct Lanes {
+  bool on = false, serial = false, labelled = false;
+  int lane = 0;
+  std::vector<int> stage;
+  std::vector<LaneLaunch> rec;
+  pbd_prof_entry label{};
+};
+
 struct pbd_ctx {
   pbd_opts o{};
+  Lanes lanes;
   int B = 0;
   Shape in{};
   std::vector<double> pool;
@@ -522,6 +552,42 @@ int depthwise_reader(const pbd_ctx* c, const BlockPlan& bp, int j);
 bool dw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j);
 constexpr int kS2dK = 256;     // reduction length of such a stem: 4 x 4 taps x 16 lanes
 
+// Also for tensors far beyond the 256 MiB last-level cache, which a kernel's output would have survived in for the next kernel of the
+// same candidate: with groups of at most 0 / 128 / 512 / 2000 / 20000 MB of layer outputs the supernet's step at batch 64 takes 37.7 / 36.4 /
+// 35.7 / 35.5 / 35.1 ms, its search step at batch 16 25.0 / 21.6 / 19.7 / 19.2 / 19.2 (one machine).
+void find_lanes(pbd_ctx* c, BlockPlan& bp) {
+  const int nops = (int)bp.ops.size();
+  bp.group_of.assign(nops, -1);
+  bp.lane_of.assign(nops, -1);
+  if (c->o.precision != PBD_BF16 || c->o.force_direct) return;
+  std::vector<int> readers(nops + 1, 0);
+  readers[nops] = 1;                                  // (the loss)
+  for (const OpPlan& op : bp.ops)
+    for (int i = 0; i < op.d.nin; ++i) ++readers[op.d.in[i]];
+  for (int j = 0; j < nops; ++j) {
+    const OpD& o = bp.ops[j].d;
+    if (o.type != OP_MIX || o.nin < 2 || o.nin > kManyMax) continue;
+    std::vector<int> lane(nops, -1);
+    int first = j, root = -1, members = 0;
+    bool ok = true;
+    for (int k = 0; k < o.nin; ++k) {
+      int v = o.in[k];
+      while (v > 0 && readers[v] == 1 && bp.ops[v - 1].d.type == OP_CBA) {
+        lane[v - 1] = k;
+        first = std::min(first, v - 1);
+        ++members;
+        v = bp.ops[v - 1].d.in[0];
+      }
+      ok = ok && (root < 0 || v == root);
+      root = v;
+    }
+    if (!ok || members != j - first || root > first) continue;   // (members: nothing else lies between)
+    for (int i = first; i < j; ++i) { bp.group_of[i] = (int)bp.groups.size(); bp.lane_of[i] = lane[i]; }
+    bp.groups.push_back({first, j, root});
+    bp.lanes = std::max(bp.lanes, o.nin);
+  }
+}
+
 int plan(pbd_ctx* c) {
   const size_t es = c->esz;
   const bool bf = c->o.precision == PBD_BF16;
@@ -674,8 +740,9 @@ int plan(pbd_ctx* c) {
     bp.parts = s;
     bp.scratch_bytes = align_up(s + parts * 4);
     bp.red_bytes = align_up(red);
-    smax = std::max(smax, bp.scratch_bytes + bp.red_bytes);
-    ssum += bp.scratch_bytes + bp.red_bytes;
+    find_lanes(c, bp);
+    smax = std::max(smax, bp.scratch_bytes + bp.red_bytes * bp.lanes);
+    ssum += bp.scratch_bytes + bp.red_bytes * bp.lanes;
   }
   c->r_tred = cur; cur += teacher_red;
   // Blocks are independent (Sec. IV-B): when the sum of their scratch fits comfortably in HBM each
@@ -685,7 +752,7 @@ int plan(pbd_ctx* c) {
   for (BlockPlan& bp : c->net[1]) {
     bp.scr_off = at;
     bp.red_off = at + bp.scratch_bytes;
-    if (c->concurrent) at += bp.scratch_bytes + bp.red_bytes;
+    if (c->concurrent) at += bp.scratch_bytes + bp.red_bytes * bp.lanes;
   }
   cur = c->concurrent ? at : cur + smax;
   c->total = cur;
@@ -707,29 +774,167 @@ struct ProfScope {
     pbd_prof_entry e{};
     snprintf(e.name, sizeof e.name, "%s", name);
     e.bytes = bytes; e.flops = flops; e.net = net; e.block = block; e.op = op;
+    if (c->lanes.on) { c->lanes.label = e; c->lanes.labelled = true; return; }
     c->prof.push_back(e);
     const size_t need = c->prof.size() * 2;
     while (c->ev.size() < need) { hipEvent_t ev; (void)hipEventCreate(&ev); c->ev.push_back(ev); }
     c->pend_start = c->ev[need - 2]; c->pend_stop = c->ev[need - 1];   // the scope's first launch takes them
   }
-  ~ProfScope() { if (on) c->pend_start = c->pend_stop = nullptr; }
+  ~ProfScope() { if (on) { c->pend_start = c->pend_stop = nullptr; c->lanes.labelled = false; } }
 };
 
 // Launch through one place.  A profiled launch attaches its two events to the dispatch itself, so
 // their distance is the kernel's own run time (what a kernel trace reports), not the gap between
-// two markers in the stream.  The lambda converts every argument to the kernel's parameter type.
+// two markers in the stream.
+template <class... KA>
+inline void launch_now(pbd_ctx* c, void (*kern)(KA...), dim3 grid, dim3 block, size_t smem, hipStream_t st, KA... ka) {
+  void* argv[] = {(void*)&ka...};
+  if (c->pend_start) {
+    (void)hipExtLaunchKernel((const void*)kern, grid, block, argv, smem, st, c->pend_start, c->pend_stop, 0);
+    c->pend_start = c->pend_stop = nullptr;
+  } else {
+    (void)hipLaunchKernel((const void*)kern, grid, block, argv, smem, st);
+  }
+}
+template <class... KA> void launch_recorded(pbd_ctx* c, hipStream_t st, const LaneLaunch& r) {
+  unpack_to([&](const KA&... a) { launch_now<KA...>(c, (void (*)(KA...))r.kern, r.grid, r.block, r.smem, st, a...); },
+            *reinterpret_cast<const Pack<KA...>*>(r.args));
+}
+// Every argument is converted to the kernel's parameter type.  Between the lanes of a mixed layer the launch waits for the others'
+// (flush_lanes).
 template <class... KA, class... A>
 inline void launch(pbd_ctx* c, void (*kern)(KA...), dim3 grid, dim3 block, size_t smem, hipStream_t st, A&&... a) {
   static_assert(sizeof...(KA) == sizeof...(A), "argument count differs from the kernel's");
-  [&](KA... ka) {
-    void* argv[] = {(void*)&ka...};
-    if (c->pend_start) {
-      (void)hipExtLaunchKernel((const void*)kern, grid, block, argv, smem, st, c->pend_start, c->pend_stop, 0);
-      c->pend_start = c->pend_stop = nullptr;
-    } else {
-      (void)hipLaunchKernel((const void*)kern, grid, block, argv, smem, st);
+  if (!c->lanes.on) {
+    launch_now<KA...>(c, kern, grid, block, smem, st, std::forward<A>(a)...);
+    return;
+  }
+  static_assert(sizeof(Pack<KA...>) <= sizeof(LaneLaunch::args), "the arguments fit the record");
+  Lanes& l = c->lanes;
+  l.rec.emplace_back();
+  LaneLaunch& r = l.rec.back();
+  r.kern = (const void*)kern; r.one = launch_recorded<KA...>; r.grid = grid; r.block = block; r.smem = smem;
+  r.lane = l.lane; r.stage = l.stage[l.lane]; r.serial = l.serial; r.labelled = l.labelled; r.label = l.label;
+  l.labelled = false;                                    // (the scope's first launch takes it)
+  pack_up(*new (r.args) Pack<KA...>, KA(std::forward<A>(a))...);
+}
+
+// ---- lanes: launches of the same kernel for several candidates of a mixed layer in one (many.h) ----
+typedef void (*ManyFn)(pbd_ctx*, hipStream_t, const LaneLaunch* const*, int);
+typedef std::unordered_map<const void*, ManyFn> ManyTable;
+template <auto Block, int THREADS, int WAVES, class... KA>
+void launch_many(pbd_ctx* c, hipStream_t st, const LaneLaunch* const* r, int n) {
+  typedef Pack<KA...> P;
+  Many<P> m{};
+  static_assert(sizeof m <= 4096, "kernel arguments");
+  m.n = n;
+  int w = 0;
+  for (int i = 0; i < n; ++i) {
+    m.start[i] = w;
+    m.size[i] = (int)(r[i]->grid.x * r[i]->grid.y * r[i]->grid.z);
+    m.gx[i] = (int)r[i]->grid.x; m.gy[i] = (int)r[i]->grid.y;
+    m.args[i] = *reinterpret_cast<const P*>(r[i]->args);
+    w += (m.size[i] + 7) / 8 * 8;
+  }
+  m.start[n] = w;
+  launch_now<Many<P>>(c, many_kernel<Block, THREADS, WAVES, P>, w, THREADS, r[0]->smem, st, m);
+}
+template <auto Block, int THREADS, int WAVES, class... KA> void put(ManyTable& t, void (*kern)(KA...)) {
+  t[(const void*)kern] = launch_many<Block, THREADS, WAVES, KA...>;
+}
+// The kernels of mixed layers (bfloat16); one that is not here is launched lane by lane.
+const ManyTable& many_table() {
+  static const ManyTable table = [] {
+    ManyTable t;
+    typedef bf16_t B;
+#define PBD_MANY(WAVES_, NAME_, ...) put<&NAME_##_block<__VA_ARGS__>, 256, WAVES_>(t, NAME_##_kernel<__VA_ARGS__>)
+#define PBD_MANY_IG(MODE_, BM_, BN_, EPI_) PBD_MANY(1, igemm, MODE_, BM_, BN_, EPI_, true, 64); PBD_MANY(1, igemm, MODE_, BM_, BN_, EPI_, true, 32); \
+    PBD_MANY(1, igemm, MODE_, BM_, BN_, EPI_, false, 32)
+#define PBD_MANY_MODE(MODE_) PBD_MANY_IG(MODE_, 64, 128, EPI_STORE); PBD_MANY_IG(MODE_, 64, 64, EPI_STORE); PBD_MANY_IG(MODE_, 64, 32, EPI_STORE); \
+    PBD_MANY_IG(MODE_, 128, 128, EPI_STORE); PBD_MANY_IG(MODE_, 128, 64, EPI_STORE); PBD_MANY_IG(MODE_, 128, 32, EPI_STORE); \
+    PBD_MANY_IG(MODE_, 64, 128, EPI_PARTIAL); \
+    put<&igemm_dma_block<MODE_, 64, 32, EPI_STORE>, kDmaThreads, 2>(t, igemm_dma_kernel<MODE_, 64, 32, EPI_STORE>)
+    PBD_MANY_MODE(0); PBD_MANY_MODE(1);
+    PBD_MANY(1, wgrad_tr, 128, 128); PBD_MANY(1, wgrad_tr, 128, 64); PBD_MANY(1, wgrad_tr, 64, 128); PBD_MANY(1, wgrad_tr, 64, 64);
+    put<&splitk_epilogue_block, 256, 1>(t, splitk_epilogue_kernel);
+    put<&regroup_partials_block, 256, 1>(t, regroup_partials_kernel);
+    put<&bn_bwd_finalize_block, 256, 1>(t, bn_bwd_finalize_kernel);
+    PBD_MANY(1, bn_finalize, B, false); PBD_MANY(1, bn_finalize, B, true);
+    PBD_MANY(1, bn_stats, B, false);
+    PBD_MANY(1, bn_apply, B, false);
+    PBD_MANY(1, bn_bwd_reduce, B, false, false, false);
+    PBD_MANY(1, bn_bwd_apply, B, false);
+    put<&bn_small_fwd_block<B>, kSmallThreads, 2>(t, bn_small_fwd_kernel<B>);
+    put<&bn_small_bwd_block<B>, kSmallThreads, 2>(t, bn_small_bwd_kernel<B>);
+    PBD_MANY(1, sum_partials, 32); PBD_MANY(1, sum_partials, 8);
+    PBD_MANY(1, dw_wgrad, B, 3, 3); PBD_MANY(1, dw_wgrad, B, 7, 1);
+#define PBD_MANY_DW(K_) PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, false, false, false, false); PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, false, false, true, false); \
+    PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, false, true, true, false); PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, true, false, false, false); \
+    PBD_MANY(3, dw_wgrad_mfma, K_, false); PBD_MANY((K_ == 7 ? 2 : 3), dw_bwd_mfma, K_, true); PBD_MANY((K_ == 7 ? 3 : 4), dw_bwd_mfma, K_, false); \
+    PBD_MANY(2, dw_wgrad_s2_mfma, K_); PBD_MANY(1, dw_slide, B, K_, 1, 4, false); PBD_MANY(1, dw_slide, B, K_, 2, 4, false); \
+    PBD_MANY(1, dw_slide, B, K_, 1, 4, true); PBD_MANY(1, dw_dgrad_s2, B, K_)
+    PBD_MANY_DW(3); PBD_MANY_DW(5); PBD_MANY_DW(7);
+#undef PBD_MANY_DW
+#undef PBD_MANY_MODE
+#undef PBD_MANY_IG
+#undef PBD_MANY
+    return t;
+  }();
+  return table;
+}
+
+// Send out what the lanes recorded: each lane's launches in their order, launches of one kernel that several lanes have come to in one.
+// A kernel that another lane reaches a little later (in the same op of its chain) waits for it.  Launches that add to the value all lanes read
+// come last, one by one in lane order, as without lanes.
+void flush_lanes(pbd_ctx* c, hipStream_t st) {
+  Lanes& l = c->lanes;
+  l.on = false;
+  const int nl = (int)l.stage.size();
+  std::vector<std::vector<const LaneLaunch*>> q(nl);
+  for (const LaneLaunch& r : l.rec)
+    if (!r.serial) q[r.lane].push_back(&r);
+  std::vector<size_t> head(nl, 0);
+  auto emit = [&](const LaneLaunch* const* r, int n) {
+    ProfScope* ps = nullptr;
+    if (r[0]->labelled) {
+      double bytes = 0, flops = 0;
+      for (int i = 0; i < n; ++i) { bytes += r[i]->label.bytes; flops += r[i]->label.flops; }
+      const pbd_prof_entry& e = r[0]->label;
+      ps = new ProfScope(c, e.name, bytes, flops, e.net, e.block, e.op);
     }
-  }(std::forward<A>(a)...);
+    if (n == 1) r[0]->one(c, st, *r[0]);
+    else many_table().at(r[0]->kern)(c, st, r, n);
+    delete ps;
+  };
+  for (;;) {
+    const LaneLaunch* pick = nullptr;
+    for (int a = 0; a < nl; ++a) {
+      if (head[a] == q[a].size()) continue;
+      const LaneLaunch* h = q[a][head[a]];
+      bool wait = false;
+      for (int b = 0; b < nl && !wait; ++b) {
+        if (head[b] == q[b].size() || q[b][head[b]]->kern == h->kern || q[b][head[b]]->stage > h->stage) continue;
+        for (size_t i = head[b] + 1; i < q[b].size() && q[b][i]->stage <= h->stage; ++i) wait |= q[b][i]->kern == h->kern;
+      }
+      if (!wait) { pick = h; break; }
+      if (!pick) pick = h;                               // (lanes that wait for each other: the first one goes)
+    }
+    if (!pick) break;
+    const LaneLaunch* r[kManyMax];
+    int n = 0;
+    const bool many = many_table().count(pick->kern) != 0;
+    for (int a = 0; a < nl; ++a) {
+      if (head[a] == q[a].size()) continue;
+      const LaneLaunch* h = q[a][head[a]];
+      if (h != pick && !(many && h->kern == pick->kern && h->block.x == pick->block.x && h->smem == pick->smem)) continue;
+      r[n++] = h;
+      ++head[a];
+    }
+    emit(r, n);
+  }
+  for (const LaneLaunch& r : l.rec)
+    if (r.serial) { const LaneLaunch* p = &r; emit(&p, 1); }
+  l.rec.clear();
 }
 
 // For op j of a block: the index of an add op that (a) is the only reader of j's output, (b) has two
@@ -819,7 +1024,21 @@ template <class T> struct Exec {
     if (!op.s2d) return op.cin_p;
     return dma_for((long)c->o.batch * op.out.h * op.out.w, op.d.c_out, kS2dK, 64).use ? 64 : 16;
   }
-  float* red() const { return red_static ? red_static : wsf(red_off); }
+  float* red() const {
+    return red_static ? red_static : wsf(red_off + (c->lanes.on ? (size_t)c->lanes.lane * c->net[1][blk].red_bytes : 0));
+  }
+  // before op j of a student block's forward or backward pass: its launches go to its lane, or out at once
+  void lane_of_op(const BlockPlan& bp, int j, int& group) {
+    Lanes& l = c->lanes;
+    const int g = red_static || j < 0 ? -1 : bp.group_of[j];
+    if (g != group && l.on) flush_lanes(c, st);
+    if (g >= 0) {
+      if (g != group) { l.on = true; l.stage.assign(kManyMax, 0); }
+      l.lane = bp.lane_of[j];
+      ++l.stage[l.lane];
+    }
+    group = g;
+  }
   // where a layer's weight-gradient partial sums go, and whether they are added with the whole block's (the caller
   // that brings its own scratch has them added at once: same association, same bits)
   bool deferred(const OpPlan& op) const { return op.e_part >= 0 && !red_static; }
@@ -1524,9 +1743,11 @@ template <class T> struct Exec {
 
     // ---- forward ----------------------------------------------------------
     std::vector<char> fused(bp.ops.size(), 0);      // adds that rode in their producer's normalisation pass
+    int group = -1;                                 // the mixed layer whose candidates are at work
     for (size_t j = 0; j < bp.ops.size(); ++j) {
       const OpPlan& op = bp.ops[j];
       opi = (int)j;
+      lane_of_op(bp, (int)j, group);
       if (fused[j]) continue;
       T* z = value((int)j + 1);
       const T* x = value(op.d.in[0]);
@@ -1613,6 +1834,8 @@ template <class T> struct Exec {
       }
     }
 
+    lane_of_op(bp, -1, group);
+
     // ---- loss and its gradient (fused) -----------------------------------
     // A block that ends in an add whose backward pass rides in a batch-norm reduction (below): that reduction also
     // forms the loss and its gradient from the block's output and the teacher's activation.
@@ -1653,6 +1876,7 @@ template <class T> struct Exec {
     for (int j = (int)bp.ops.size() - 1; j >= 0; --j) {
       const OpPlan& op = bp.ops[j];
       opi = j;
+      lane_of_op(bp, j, group);
       if (!have[j + 1]) continue;
       T* dz = dvalue(j + 1);
       const int iv = op.d.in[0];
@@ -1729,8 +1953,10 @@ template <class T> struct Exec {
           else conv_wgrad(op, dz, x, grad + op.e_w);
         }
         if (wanted[iv]) {  // A_{i-1} is a constant: no backward-data for the block's first layer
+          c->lanes.serial = group >= 0 && iv == bp.groups[group].root;     // (every lane adds to that one)
           if (op.dw) dw_dgrad(op, dz, wc + op.e_w, dvalue(iv), have[iv]);
           else conv_dgrad(op, dz, wc + op.e_w, op.e_wt >= 0 ? ws(bp.wt) + op.e_wt : nullptr, dvalue(iv), have[iv]);
+          c->lanes.serial = false;
           have[iv] = 1;
         }
       } else if (op.d.type == OP_POOL) {
@@ -1776,6 +2002,8 @@ template <class T> struct Exec {
           launch(c, mix_alpha_update_kernel, 1, 256, 0, st, red(), nb, mix_state(op), op.d.nin, wsf(c->lr_off), c->o.momentum, 1);
       }
     }
+
+    lane_of_op(bp, -1, group);
 
     // ---- decoupled update of this block only -----------------------------
     if (!arch) {
