@@ -173,7 +173,21 @@ struct IgemmArgs {
   // the staged stores of the output, and the loads of what they combine with (a fused residual, the gradient an
   // accumulating launch adds to), are nontemporal (tensors far larger than the caches)
   int stream_out;
+  // FOLD: A is the convolution output of the layer in front, normalised and rectified on its way to LDS (igemm_kernel, 1 x 1)
+  NormFold fold;
 };
+
+// The producing layer's batch norm and rectifier on one 16-byte chunk: bn_apply_kernel's arithmetic and rounding.  (The clamp is one
+// v_med3_f32, which like apply_act makes zero of a NaN.)
+__device__ __forceinline__ uint4 fold_chunk(const uint4& q, const float (&mu)[8], const float (&a)[8], const float (&b)[8], float hi) {
+  float v[8];
+  IO<bf16_t>::unpack(q, v);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = __builtin_amdgcn_fmed3f(fmaf(v[e] - mu[e], a[e], b[e]), 0.f, hi);
+  return make_uint4(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7]));
+}
+// dynamic LDS of a FOLD launch: mean, gamma * invstd and beta of the reduction's channels (zeros behind them)
+inline int fold_lds(int channels) { return 3 * 4 * ((channels + 63) / 64 * 64); }
 
 // EPI_PARTIAL: raw fp32 partial tile of a split-K launch, summed by splitk_epilogue_kernel
 enum { EPI_STORE = 0, EPI_AFFINE_ACT = 1, EPI_ACCUM = 2, EPI_PARTIAL = 3 };
@@ -195,7 +209,11 @@ __device__ __forceinline__ int xcd_contiguous(int w, int total) {
 // UNI: the channel count of the gathered tensor is a multiple of the 32-element K step, so a step
 // lies inside one filter tap and (r, s, c0) are the same for the whole workgroup: they live in
 // scalar registers and a load costs a lane two adds, two compares, an add and a select.
-template <int MODE, int BM, int BN, int EPI, bool UNI, int BK>
+//
+// FOLD (1 x 1, stride 1, forward): the narrow layers behind MobileNetV2's and the supernet's depthwise layers, N <= 32, so that every
+// element of A is staged once.  ~40 vector operations a chunk beside a kernel that waits for memory; bn_apply_kernel's pass over the
+// block's largest tensor, one read and one write, goes.
+template <int MODE, int BM, int BN, int EPI, bool UNI, int BK, bool FOLD>
 __device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __restrict__ A,
                                                     const bf16_t* __restrict__ Bw,
                                                     bf16_t* __restrict__ Out,
@@ -286,6 +304,19 @@ __device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __rest
     for (int i = 0; i < B_LOADS; ++i) bbase[i] = brow[i] >= 0 ? (unsigned)(brow[i] + chunk * 8) * 2u : kOutOfRange;
   }
 
+  extern __shared__ __attribute__((aligned(16))) float fold_s[];
+  const int fold_c = FOLD ? (g.CA + 63) / 64 * 64 : 0;
+  const float fold_hi = FOLD && g.fold.act == ACT_RELU6 ? 6.f : __builtin_inff();
+  if constexpr (FOLD) {
+    static_assert(MODE == 0, "the layer in front of a forward pass");
+    for (int i = tid; i < fold_c; i += 256) {
+      const bool in = i < g.CA;
+      fold_s[i] = in ? g.fold.mean[i] : 0.f;
+      fold_s[fold_c + i] = in ? g.fold.gamma[i] * g.fold.invstd[i] : 0.f;
+      fold_s[2 * fold_c + i] = in ? g.fold.beta[i] : 0.f;
+    }
+  }
+
   // two register stages: tile kt+2 is requested while tile kt is multiplied and tile kt+1 moves to LDS
   uint4 areg[2][A_LOADS], breg[2][B_LOADS];
   const __amdgpu_buffer_rsrc_t a_rsrc = tensor_rsrc(A, g.a_bytes), b_rsrc = tensor_rsrc(Bw, g.b_bytes);
@@ -352,8 +383,22 @@ __device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __rest
       }
     }
   };
-  auto store_tile = [&](auto stage, int buf) {
+  auto store_tile = [&](auto stage, int buf, int kt) {
     constexpr int S_ = decltype(stage)::value;
+    if constexpr (FOLD) {
+      float mu[8], a[8], b[8];
+      const float* f = fold_s + kt * BK + chunk * 8;
+#pragma unroll
+      for (int e = 0; e < 8; e += 4) {
+        const float4 m4 = *reinterpret_cast<const float4*>(f + e), a4 = *reinterpret_cast<const float4*>(f + fold_c + e),
+                     b4 = *reinterpret_cast<const float4*>(f + 2 * fold_c + e);
+        mu[e] = m4.x; mu[e + 1] = m4.y; mu[e + 2] = m4.z; mu[e + 3] = m4.w;
+        a[e] = a4.x; a[e + 1] = a4.y; a[e + 2] = a4.z; a[e + 3] = a4.w;
+        b[e] = b4.x; b[e + 1] = b4.y; b[e + 2] = b4.z; b[e + 3] = b4.w;
+      }
+#pragma unroll
+      for (int i = 0; i < A_LOADS; ++i) areg[S_][i] = fold_chunk(areg[S_][i], mu, a, b, fold_hi);   // (rows past M: neither stored nor summed)
+    }
 #pragma unroll
     for (int i = 0; i < A_LOADS; ++i)
       *reinterpret_cast<uint4*>(&As[buf][(prow + RPP * i) * PITCH + chunk * 8]) = areg[S_][i];
@@ -380,7 +425,8 @@ __device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __rest
   using S1 = std::integral_constant<int, 1>;
   load_tile(S0{});
   if (nk > 1) load_tile(S1{});
-  store_tile(S0{}, 0);
+  if (FOLD) __syncthreads();                         // the terms are in LDS
+  store_tile(S0{}, 0, 0);
   __syncthreads();
   auto iteration = [&](int kt, auto cur) {
     constexpr int C_ = decltype(cur)::value;
@@ -406,7 +452,7 @@ __device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __rest
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
       }
     }
-    if (kt + 1 < nk) store_tile(Nxt{}, 1 - C_);
+    if (kt + 1 < nk) store_tile(Nxt{}, 1 - C_, kt + 1);
     __syncthreads();
   };
   for (int kt = 0; kt < nk; kt += 2) {
@@ -608,11 +654,11 @@ __device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __rest
       }
   }
 }
-template <int MODE, int BM, int BN, int EPI, bool UNI, int BK = IG_BK>
+template <int MODE, int BM, int BN, int EPI, bool UNI, int BK = IG_BK, bool FOLD = false>
 __global__ __launch_bounds__(256) void igemm_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ Bw, bf16_t* __restrict__ Out, const float* __restrict__ ep_a,
     const float* __restrict__ ep_b, int act, IgemmArgs g) {
-  igemm_block<MODE, BM, BN, EPI, UNI, BK>(one_block(), A, Bw, Out, ep_a, ep_b, act, g);
+  igemm_block<MODE, BM, BN, EPI, UNI, BK, FOLD>(one_block(), A, Bw, Out, ep_a, ep_b, act, g);
 }
 
 // Second stage of a split-K launch: out = epilogue(sum_s part[s]) in split order.
@@ -670,6 +716,7 @@ struct WgradTrArgs {
   int dn, dp, dq;     // 32 pixels = dn images + dp rows + dq columns (mixed radix P, Q)
   unsigned dy_bytes, x_bytes;
   int tiles_k, tiles_j, splits;   // the 1-D grid holds tiles_k * tiles_j * splits workgroups
+  NormFold fold;                  // FOLD: x is the convolution output of the layer in front (wgrad_tr_kernel, 1 x 1)
 };
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -683,7 +730,8 @@ __device__ __forceinline__ bf16x8 lds_read_tr8(const bf16_t* p, int row_pitch) {
   return __builtin_bit_cast(bf16x8, v);
 }
 
-template <int TM, int TN>
+// FOLD: x is normalised and rectified on its way to LDS; a thread's channels are the same in every step.
+template <int TM, int TN, bool FOLD>
 __device__ __forceinline__ void wgrad_tr_block(const Blk& blk, const bf16_t* __restrict__ dy,
                                                        const bf16_t* __restrict__ x,
                                                        float* __restrict__ part, WgradTrArgs g) {
@@ -739,8 +787,21 @@ __device__ __forceinline__ void wgrad_tr_block(const Blk& blk, const bf16_t* __r
     bn[i] = t / g.P;
   }
 
+  float f_mu[8], f_a[8], f_b[8];
+  const float f_hi = FOLD && g.fold.act == ACT_RELU6 ? 6.f : __builtin_inff();
+  if constexpr (FOLD) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      f_mu[e] = g.fold.mean[bc + e];
+      f_a[e] = g.fold.gamma[bc + e] * g.fold.invstd[bc + e];
+      f_b[e] = g.fold.beta[bc + e];
+    }
+  }
+
   uint4 ra[A_N], rb[B_N];
+  unsigned b_in = 0;                                    // FOLD: which of rb exist (the others stay zero)
   auto load_step = [&]() {
+    b_in = 0;
 #pragma unroll
     for (int i = 0; i < A_N; ++i) {
       ra[i] = buffer_load16(rdy, a_off[i]);
@@ -752,6 +813,7 @@ __device__ __forceinline__ void wgrad_tr_block(const Blk& blk, const bf16_t* __r
       const bool ok = b_ok && bm[i] < mend && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;
       const unsigned off = (unsigned)(((bn[i] * g.H + h) * g.W + w) * g.C + bc) * 2u;
       rb[i] = buffer_load16(rx, ok ? off : kOutOfRange);
+      if (FOLD) b_in |= ok ? 1u << i : 0u;
       bm[i] += BKP;
       int q = bq[i] + g.dq;
       const int c1 = q >= g.Q ? 1 : 0;
@@ -763,6 +825,14 @@ __device__ __forceinline__ void wgrad_tr_block(const Blk& blk, const bf16_t* __r
     }
   };
   auto store_step = [&](int buf) {
+    if constexpr (FOLD) {
+#pragma unroll
+      for (int i = 0; i < B_N; ++i) {
+        const uint4 v = fold_chunk(rb[i], f_mu, f_a, f_b, f_hi);
+        const unsigned in = (unsigned)((int)(b_in << (31 - i)) >> 31);
+        rb[i] = make_uint4(v.x & in, v.y & in, v.z & in, v.w & in);
+      }
+    }
 #pragma unroll
     for (int i = 0; i < A_N; ++i)
       *reinterpret_cast<uint4*>(&As[buf][(a_row + i * A_RSTEP) * PA + a_cc * 8]) = ra[i];
@@ -822,10 +892,10 @@ __device__ __forceinline__ void wgrad_tr_block(const Blk& blk, const bf16_t* __r
       }
   }
 }
-template <int TM, int TN>
+template <int TM, int TN, bool FOLD = false>
 __global__ __launch_bounds__(256) void wgrad_tr_kernel(const bf16_t* __restrict__ dy,
     const bf16_t* __restrict__ x, float* __restrict__ part, WgradTrArgs g) {
-  wgrad_tr_block<TM, TN>(one_block(), dy, x, part, g);
+  wgrad_tr_block<TM, TN, FOLD>(one_block(), dy, x, part, g);
 }
 
 }  // namespace pbd

@@ -829,7 +829,9 @@ void launch_many(pbd_ctx* c, hipStream_t st, const LaneLaunch* const* r, int n) 
   static_assert(sizeof m <= 4096, "kernel arguments");
   m.n = n;
   int w = 0;
+  size_t smem = 0;
   for (int i = 0; i < n; ++i) {
+    smem = std::max(smem, r[i]->smem);
     m.start[i] = w;
     m.size[i] = (int)(r[i]->grid.x * r[i]->grid.y * r[i]->grid.z);
     m.gx[i] = (int)r[i]->grid.x; m.gy[i] = (int)r[i]->grid.y;
@@ -837,7 +839,7 @@ void launch_many(pbd_ctx* c, hipStream_t st, const LaneLaunch* const* r, int n) 
     w += (m.size[i] + 7) / 8 * 8;
   }
   m.start[n] = w;
-  launch_now<Many<P>>(c, many_kernel<Block, THREADS, WAVES, P>, w, THREADS, r[0]->smem, st, m);
+  launch_now<Many<P>>(c, many_kernel<Block, THREADS, WAVES, P>, w, THREADS, smem, st, m);
 }
 template <auto Block, int THREADS, int WAVES, class... KA> void put(ManyTable& t, void (*kern)(KA...)) {
   t[(const void*)kern] = launch_many<Block, THREADS, WAVES, KA...>;
@@ -848,14 +850,18 @@ const ManyTable& many_table() {
     ManyTable t;
     typedef bf16_t B;
 #define PBD_MANY(WAVES_, NAME_, ...) put<&NAME_##_block<__VA_ARGS__>, 256, WAVES_>(t, NAME_##_kernel<__VA_ARGS__>)
-#define PBD_MANY_IG(MODE_, BM_, BN_, EPI_) PBD_MANY(1, igemm, MODE_, BM_, BN_, EPI_, true, 64); PBD_MANY(1, igemm, MODE_, BM_, BN_, EPI_, true, 32); \
-    PBD_MANY(1, igemm, MODE_, BM_, BN_, EPI_, false, 32)
+#define PBD_MANY_IG(MODE_, BM_, BN_, EPI_) PBD_MANY(1, igemm, MODE_, BM_, BN_, EPI_, true, 64, false); PBD_MANY(1, igemm, MODE_, BM_, BN_, EPI_, true, 32, false); \
+    PBD_MANY(1, igemm, MODE_, BM_, BN_, EPI_, false, 32, false)
 #define PBD_MANY_MODE(MODE_) PBD_MANY_IG(MODE_, 64, 128, EPI_STORE); PBD_MANY_IG(MODE_, 64, 64, EPI_STORE); PBD_MANY_IG(MODE_, 64, 32, EPI_STORE); \
     PBD_MANY_IG(MODE_, 128, 128, EPI_STORE); PBD_MANY_IG(MODE_, 128, 64, EPI_STORE); PBD_MANY_IG(MODE_, 128, 32, EPI_STORE); \
     PBD_MANY_IG(MODE_, 64, 128, EPI_PARTIAL); \
     put<&igemm_dma_block<MODE_, 64, 32, EPI_STORE>, kDmaThreads, 2>(t, igemm_dma_kernel<MODE_, 64, 32, EPI_STORE>)
     PBD_MANY_MODE(0); PBD_MANY_MODE(1);
-    PBD_MANY(1, wgrad_tr, 128, 128); PBD_MANY(1, wgrad_tr, 128, 64); PBD_MANY(1, wgrad_tr, 64, 128); PBD_MANY(1, wgrad_tr, 64, 64);
+    PBD_MANY(1, igemm, 0, 128, 32, EPI_STORE, true, 64, true); PBD_MANY(1, igemm, 0, 128, 32, EPI_STORE, true, 32, true);
+    PBD_MANY(1, igemm, 0, 128, 32, EPI_STORE, false, 32, true); PBD_MANY(1, igemm, 0, 64, 32, EPI_STORE, true, 64, true);
+    PBD_MANY(1, igemm, 0, 64, 32, EPI_STORE, true, 32, true); PBD_MANY(1, igemm, 0, 64, 32, EPI_STORE, false, 32, true);
+    PBD_MANY(1, wgrad_tr, 128, 128, false); PBD_MANY(1, wgrad_tr, 128, 64, false); PBD_MANY(1, wgrad_tr, 64, 128, false);
+    PBD_MANY(1, wgrad_tr, 64, 64, false); PBD_MANY(1, wgrad_tr, 64, 128, true); PBD_MANY(1, wgrad_tr, 64, 64, true);
     put<&splitk_epilogue_block, 256, 1>(t, splitk_epilogue_kernel);
     put<&regroup_partials_block, 256, 1>(t, regroup_partials_kernel);
     put<&bn_bwd_finalize_block, 256, 1>(t, bn_bwd_finalize_kernel);
@@ -926,7 +932,7 @@ void flush_lanes(pbd_ctx* c, hipStream_t st) {
     for (int a = 0; a < nl; ++a) {
       if (head[a] == q[a].size()) continue;
       const LaneLaunch* h = q[a][head[a]];
-      if (h != pick && !(many && h->kern == pick->kern && h->block.x == pick->block.x && h->smem == pick->smem)) continue;
+      if (h != pick && !(many && h->kern == pick->kern && h->block.x == pick->block.x)) continue;
       r[n++] = h;
       ++head[a];
     }
@@ -996,10 +1002,38 @@ int depthwise_reader(const pbd_ctx* c, const BlockPlan& bp, int j) {
 
 // The backward pass of student layer j in one kernel: a depthwise layer that normalises the layer in front as it stages it
 // (depthwise_reader) and whose own gradient arrives as a tensor (no residual add rides in its batch norm).
+// For student layer j: the index of a dense 1 x 1 layer with at most 32 outputs that is the only reader of j's output (it then normalises
+// and rectifies j's convolution output as it stages it, forward and in its weight gradient, and the normalised tensor is not written),
+// else -1.  MobileNetV2's and the supernet's depthwise layers on the large images: supernet step at batch 64 34.06 -> 32.82 ms (its
+// bn_apply launches 2.76 -> 1.01 ms, the readers 1.50 -> 1.69, their weight gradients as before), search step 18.63 -> 17.99, MobileNetV2
+// 24.17 -> 23.52 ms for four batches, 1.879 -> 1.838 at batch 33.  Up to 64 or 128 outputs, which are the small images' layers (most of
+// them on the direct-to-LDS kernel, which has no registers to form the tensor in): within 0.3 % of this line everywhere.
+constexpr int kFoldChannels = 1024;       // terms that fit in a workgroup's LDS beside its tiles
+int dense_reader(const pbd_ctx* c, const BlockPlan& bp, int j) {
+  const OpPlan& p = bp.ops[j];
+  if (c->o.precision != PBD_BF16 || c->o.force_direct || p.d.type != OP_CBA || (p.d.act != ACT_RELU && p.d.act != ACT_RELU6) ||
+      j + 2 == (int)bp.shapes.size() || p.cout_p > kFoldChannels || short_column((long)c->o.batch * p.out.h * p.out.w)) return -1;
+  int reader = -1, uses = 0;
+  for (int k = j + 1; k < (int)bp.ops.size(); ++k) {
+    const OpD& q = bp.ops[k].d;
+    const int nin = q.type == OP_ADD || q.type == OP_MIX ? q.nin : 1;
+    for (int i = 0; i < nin; ++i)
+      if (q.in[i] == j + 1) { ++uses; reader = k; }
+  }
+  if (uses != 1 || bp.ops[reader].d.type != OP_CBA || bp.ops[reader].dw) return -1;
+  const OpPlan& q = bp.ops[reader];
+  if (q.d.k != 1 || q.d.stride != 1 || q.d.c_out > 32) return -1;
+  const IgemmCfg cfg = igemm_cfg((long)c->o.batch * q.out.h * q.out.w, q.d.c_out, q.cin_p, q.cin_p);
+  return cfg.splits == 1 && cfg.BN == 32 ? reader : -1;
+}
+
 bool dw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j) {
   const OpPlan& op = bp.ops[j];
   return op.d.type == OP_CBA && op.dw && op.d.in[0] > 0 && depthwise_reader(c, bp, op.d.in[0] - 1) == j && residual_reader(bp, j) < 0;
 }
+
+// layer j's normalised output is formed by its reader and not written
+bool value_folded(const pbd_ctx* c, const BlockPlan& bp, int j) { return depthwise_reader(c, bp, j) >= 0 || dense_reader(c, bp, j) >= 0; }
 
 template <class T> struct Exec {
   pbd_ctx* c;
@@ -1083,7 +1117,7 @@ template <class T> struct Exec {
   // res (optional): a residual join fused into the store, y = res_act(conv result + res); only where
   // fuses_residual(op) holds.  stats (optional): per row tile sums of y and y^2, where fused_stats_tiles(op) > 0
   void conv_fwd(const OpPlan& op, const T* x, const T* w, T* y, const float* a, const float* b, int act,
-                const T* res = nullptr, int res_act = 0, float* stats = nullptr) {
+                const T* res = nullptr, int res_act = 0, float* stats = nullptr, NormFold fold = NormFold{}) {
     const int N = c->o.batch;
     const double flops = 2.0 * N * op.out.h * op.out.w * op.d.c_out * op.d.k * op.d.k * op.in.c;
     const double bytes = bytes_of(op.in) + bytes_of(op.out) * (res ? 2 : 1) + (double)op.wn * sizeof(T);
@@ -1103,7 +1137,7 @@ template <class T> struct Exec {
           w = reinterpret_cast<const T*>(c->ws + op.w2);
           bytes_run = (double)g.a_bytes + bytes_of(op.out) * (res ? 2 : 1) + (double)g.b_bytes;
         }
-        g.res = res; g.res_act = res_act; g.stats = stats;
+        g.res = res; g.res_act = res_act; g.stats = stats; g.fold = fold;
         launch_igemm<0>(g, (const bf16_t*)x, (const bf16_t*)w, (bf16_t*)y, a, b, act, a ? EPI_AFFINE_ACT : EPI_STORE,
                         bytes_run, flops);
       }
@@ -1197,7 +1231,17 @@ template <class T> struct Exec {
     // a rocprofv3 kernel trace: igemm_<fwd|dgrad>_<BM>x<BN>_<epilogue>
     static const char* const kEpi[] = {"store", "affine", "accum", "partial"};
     char name[32];
-    snprintf(name, sizeof name, "igemm_%s_%dx%d_%s", MODE ? "dgrad" : "fwd", cfg.BM, cfg.BN, kEpi[g.splits > 1 ? 3 : epi]);
+    snprintf(name, sizeof name, "igemm_%s_%dx%d_%s", MODE ? "dgrad" : "fwd", cfg.BM, cfg.BN, g.fold.mean ? "bn_store" : kEpi[g.splits > 1 ? 3 : epi]);
+    if constexpr (MODE == 0) {
+      if (g.fold.mean) {                     // (dense_reader: 32 columns, no split)
+        ProfScope ps(c, name, bytes, flops, net, blk, opi);
+#define PBD_IGF(BM_, UNI_, BK_) launch(c, igemm_kernel<0, BM_, 32, EPI_STORE, UNI_, BK_, true>, grid, 256, fold_lds(g.CA), st, A, Bw, out, a, b, act, g)
+        if (cfg.BM == 128) { if (cfg.BK == 64) PBD_IGF(128, true, 64); else if (g.CA % IG_BK == 0) PBD_IGF(128, true, 32); else PBD_IGF(128, false, 32); }
+        else { if (cfg.BK == 64) PBD_IGF(64, true, 64); else if (g.CA % IG_BK == 0) PBD_IGF(64, true, 32); else PBD_IGF(64, false, 32); }
+#undef PBD_IGF
+        return;
+      }
+    }
     if (g.splits > 1) {
       {
         ProfScope ps(c, name, bytes, flops, net, blk, opi);
@@ -1261,7 +1305,7 @@ template <class T> struct Exec {
   }
 
   // ---- convolution backward-weight (dense) -------------------------------
-  void conv_wgrad(const OpPlan& op, const T* dy, const T* x, float* dw) {
+  void conv_wgrad(const OpPlan& op, const T* dy, const T* x, float* dw, NormFold fold = NormFold{}) {
     const int N = c->o.batch;
     const long M = (long)N * op.out.h * op.out.w;
     const int J = op.d.k * op.d.k * op.cin_p;
@@ -1275,7 +1319,7 @@ template <class T> struct Exec {
                       op.d.stride, op.d.pad, (int)M, J, w.pix_per_split,
                       w.BKP / pq, (w.BKP % pq) / op.out.w, w.BKP % op.out.w,
                       (unsigned)(M * op.d.c_out * 2), (unsigned)((size_t)N * op.in.h * op.in.w * op.cin_p * 2),
-                      w.tiles_k, w.tiles_j, w.splits};
+                      w.tiles_k, w.tiles_j, w.splits, fold};
         const dim3 grid(w.tiles_k * w.tiles_j * w.splits);
         float* part = w.splits == 1 ? dw : parts(op);
         long wn_run = (long)op.wn;
@@ -1294,15 +1338,16 @@ template <class T> struct Exec {
         }
         {
           char name[32];
-          snprintf(name, sizeof name, "wgrad_%dx%d", w.TM, w.TN);
+          snprintf(name, sizeof name, "wgrad_%dx%d%s", w.TM, w.TN, fold.mean ? "_bn" : "");
           ProfScope ps(c, name, bytes_run, flops, net, blk, opi);
           if (w.dma) {
 #define PBD_WGD(TM_) launch(c, wgrad_dma_kernel<TM_>, grid, kDmaThreads, 0, st, (const bf16_t*)dy, (const bf16_t*)x, part, g)
             if (w.TM == 256) PBD_WGD(256); else PBD_WGD(192);
 #undef PBD_WGD
           } else {
-#define PBD_WG(TM_, TN_) launch(c, wgrad_tr_kernel<TM_, TN_>, grid, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)x, part, g)
-            if (w.TM == 128) { if (w.TN == 128) PBD_WG(128, 128); else PBD_WG(128, 64); }
+#define PBD_WG(TM_, ...) launch(c, wgrad_tr_kernel<TM_, __VA_ARGS__>, grid, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)x, part, g)
+            if (fold.mean) { if (w.TN == 128) PBD_WG(64, 128, true); else PBD_WG(64, 64, true); }    // (dense_reader: 32 rows at most)
+            else if (w.TM == 128) { if (w.TN == 128) PBD_WG(128, 128); else PBD_WG(128, 64); }
             else { if (w.TN == 128) PBD_WG(64, 128); else PBD_WG(64, 64); }
 #undef PBD_WG
           }
@@ -1732,8 +1777,8 @@ template <class T> struct Exec {
     float* grad = wsf(bp.grad);
     const float* master = wsf(bp.master);
     const int nval = (int)bp.shapes.size();
-    // value v is normalised by the depthwise layer that reads it (as it stages the convolution output)
-    auto folds_into = [&](int v) { return v > 0 && depthwise_reader(c, bp, v - 1) >= 0; };
+    // value v is normalised by the layer that reads it (as it stages the convolution output)
+    auto folds_into = [&](int v) { return v > 0 && value_folded(c, bp, v - 1); };
     auto input_fold = [&](int v) -> NormFold {
       if (!folds_into(v)) return NormFold{};
       const OpPlan& p = bp.ops[v - 1];
@@ -1758,7 +1803,8 @@ template <class T> struct Exec {
         const int dw_rows = dw_stat_rows(op);
         if (op.dw) dw_fwd(op, folds_into(iv) ? ws(scr + bp.ops[iv - 1].y) : x, wc + op.e_w, y, nullptr, nullptr, 0, input_fold(iv),
                           dw_rows ? red() : nullptr);
-        else conv_fwd(op, x, wc + op.e_w, y, nullptr, nullptr, 0, nullptr, 0, stat_tiles ? red() : nullptr);
+        else conv_fwd(op, folds_into(iv) ? ws(scr + bp.ops[iv - 1].y) : x, wc + op.e_w, y, nullptr, nullptr, 0, nullptr, 0, stat_tiles ? red() : nullptr,
+                      input_fold(iv));
         const long M = (long)N * op.out.h * op.out.w;
         if (short_column(M)) {
           ProfScope ps(c, "bn_small_fwd", 3 * bytes_of(op.out), 0, net, blk, opi);
@@ -1950,7 +1996,7 @@ template <class T> struct Exec {
         const T* x = value(iv);
         if (!arch) {
           if (op.dw) dw_wgrad(op, dz, folds_into(iv) ? ws(scr + bp.ops[iv - 1].y) : x, grad + op.e_w, input_fold(iv));
-          else conv_wgrad(op, dz, x, grad + op.e_w);
+          else conv_wgrad(op, dz, folds_into(iv) ? ws(scr + bp.ops[iv - 1].y) : x, grad + op.e_w, input_fold(iv));
         }
         if (wanted[iv]) {  // A_{i-1} is a constant: no backward-data for the block's first layer
           c->lanes.serial = group >= 0 && iv == bp.groups[group].root;     // (every lane adds to that one)
@@ -2578,7 +2624,7 @@ int pbd_read_value(pbd_ctx* c, int32_t b, int32_t v, float* host, size_t n) {
   if (v > 0 && pool_reader(bp, v - 1, c->o.batch) >= 0)
     return fail(c, PBD_ESTATE, "value %d of block %d is not kept: the max-pool that reads it normalises the convolution output itself", v, b);
   const char* dev = v == 0 ? relay_ptr(c, b) : c->ws + bp.scr_off + bp.val[v];
-  if (v > 0 && depthwise_reader(c, bp, v - 1) >= 0) {
+  if (v > 0 && value_folded(c, bp, v - 1)) {
     // the step does not write this tensor (its reader normalises the convolution output itself): formed now, with the
     // gamma and beta that the step used
     const OpPlan& p = bp.ops[v - 1];
