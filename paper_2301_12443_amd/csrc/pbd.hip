@@ -14,6 +14,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <string>
 #include <new>
@@ -27,6 +28,7 @@
 #include "conv_f32_kernels.h"
 #include "dw_mfma_kernels.h"
 #include "ew_kernels.h"
+#include "pw_bwd_kernels.h"
 
 using namespace pbd;
 
@@ -550,6 +552,8 @@ bool stem_s2d(const pbd_ctx* c, int block, const OpPlan& op) {
 }
 int depthwise_reader(const pbd_ctx* c, const BlockPlan& bp, int j);
 bool dw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j);
+bool pw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j);
+inline int pw_blocks(long M) { return (int)std::min<long>(256, ((M + kPwPix - 1) / kPwPix + kPwWaves - 1) / kPwWaves); }
 constexpr int kS2dK = 256;     // reduction length of such a stem: 4 x 4 taps x 16 lanes
 
 // Also for tensors far beyond the 256 MiB last-level cache, which a kernel's output would have survived in for the next kernel of the
@@ -723,7 +727,9 @@ int plan(pbd_ctx* c) {
           const WgradCfg w = op.s2d ? wgrad_cfg(M, op.d.c_out, kS2dK, 16) : wgrad_cfg(M, op.d.c_out, op.d.k * op.d.k * op.cin_p, op.d.k * op.d.k);
           // (the stem on the space-to-depth input: partial sums and their sum in the repacked layout, then unpacked)
           need_red(op.s2d ? ((size_t)w.splits + 1) * op.d.c_out * kS2dK * 4 : (size_t)w.splits * op.wn * 4);
-          if (!op.s2d) defer(op, w.splits);
+          const bool pw = pw_bwd_fused(c, bp, (int)v - 1);
+          if (pw) need_red((size_t)pw_blocks(M) * op.wn * 4);
+          if (!op.s2d) defer(op, pw ? pw_blocks(M) : w.splits);
           // per-row-tile batch-norm sums from the convolution's store (64-row tiles at most), and their regrouping
           need_red(((size_t)(M + 63) / 64 + kStatGroupsMax + 1) * 2 * op.cout_p * 4);
           const long Min = (long)c->o.batch * op.in.h * op.in.w;
@@ -1030,6 +1036,15 @@ int dense_reader(const pbd_ctx* c, const BlockPlan& bp, int j) {
 bool dw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j) {
   const OpPlan& op = bp.ops[j];
   return op.d.type == OP_CBA && op.dw && op.d.in[0] > 0 && depthwise_reader(c, bp, op.d.in[0] - 1) == j && residual_reader(bp, j) < 0;
+}
+
+// The same for an expand layer (pw_bwd_kernel).  From kPwMinPixels pixels on: below, a wave has a single tile of 32 pixels or none.
+constexpr long kPwMinPixels = 16384;
+bool pw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j) {
+  const OpPlan& op = bp.ops[j];
+  return c->o.precision == PBD_BF16 && !c->o.force_direct && op.d.type == OP_CBA && !op.dw && op.d.k == 1 && op.d.stride == 1 && op.d.pad == 0 &&
+         op.cin_p <= kPwMaxIn && op.d.c_out > kPwMaxIn && op.d.c_out <= kPwMaxOut && op.d.c_out % 8 == 0 &&
+         (long)c->o.batch * op.out.h * op.out.w >= kPwMinPixels && residual_reader(bp, j) < 0;
 }
 
 // layer j's normalised output is formed by its reader and not written
@@ -1572,6 +1587,37 @@ template <class T> struct Exec {
     sum_partials(wpart, grad + op.e_w, (long)op.wn, chunks);
   }
 
+  // op's whole backward pass (pw_bwd_fused): from dz, the gradient of its normalised output, to the gradient dx of its input (null: not
+  // wanted) and, but for the architecture round, the filter's
+  void pw_bwd(const OpPlan& op, const T* dz, const T* y, const T* x, const T* w, T* dx, bool accumulate, bool arch) {
+    const BlockPlan& bp = c->net[1][blk];
+    const float* master = wsf(bp.master);
+    const long M = (long)c->o.batch * op.out.h * op.out.w;
+    const int blocks = pw_blocks(M);
+    float* wpart = parts(op);
+    {
+      ProfScope ps(c, arch ? "pw_dgrad_bn" : "pw_bwd_bn", 2 * bytes_of(op.out) + bytes_of(op.in) * ((arch ? 0 : 1) + (dx ? (accumulate ? 2 : 1) : 0)) + (double)op.wn * 6,
+                   2.0 * M * op.d.c_out * op.in.c * ((arch ? 0 : 1) + (dx ? 1 : 0)), net, blk, opi);
+      if constexpr (sizeof(T) == 2) {
+        const PwBwdArgs g{(int)M, op.d.c_out, op.cin_p, (int)((M + kPwPix - 1) / kPwPix), accumulate ? 1 : 0,
+                          (unsigned)(M * op.d.c_out * 2), (unsigned)(M * op.cin_p * 2), dx ? (unsigned)(M * op.cin_p * 2) : 0u};
+        const BnBwd f{wsf(op.s_mean), wsf(op.s_invstd), master + op.e_gamma, master + op.e_beta, wsf(op.s_k2), wsf(op.s_k3), op.d.act};
+#define PBD_PWB(NC_) launch(c, arch ? pw_bwd_kernel<NC_, false> : pw_bwd_kernel<NC_, true>, blocks, kPwThreads, 0, st, \
+    (const bf16_t*)dz, (const bf16_t*)y, (const bf16_t*)x, (const bf16_t*)w, (bf16_t*)dx, wpart, g, f)
+        switch ((op.d.c_out + 31) / 32) {
+          case 2: PBD_PWB(2); break;
+          case 3: PBD_PWB(3); break;
+          case 4: PBD_PWB(4); break;
+          default: PBD_PWB(6); break;
+        }
+#undef PBD_PWB
+      }
+    }
+    if (arch || deferred(op)) return;
+    ProfScope ps(c, "sum_partials", (double)(blocks + 1) * op.wn * 4, 0, net, blk, opi);
+    sum_partials(wpart, wsf(bp.grad) + op.e_w, (long)op.wn, blocks);
+  }
+
   // ---- joins / pool -------------------------------------------------------
   void join_fwd(const OpPlan& op, const Join& j, T* z) {
     const long nvec = (long)c->o.batch * op.out.h * op.out.w * op.cout_p / 8;
@@ -1839,7 +1885,7 @@ template <class T> struct Exec {
           launch(c, dw_rows ? bn_finalize_kernel<T, true> : bn_finalize_kernel<T>, op.cout_p / kFinalizeChannels, 256, 0, st, 
               part, pivot, chunks, op.cout_p, (double)M, wsf(op.s_mean), wsf(op.s_invstd), wsf(op.s_rmean),
               wsf(op.s_rvar), c->o.bn_eps, c->o.bn_momentum, master + op.e_gamma, master + op.e_beta,
-              folds_into((int)j + 1) || dw_bwd_fused(c, bp, (int)j) ? wsf(op.s_keep) : (float*)nullptr);
+              folds_into((int)j + 1) || dw_bwd_fused(c, bp, (int)j) || pw_bwd_fused(c, bp, (int)j) ? wsf(op.s_keep) : (float*)nullptr);
           if (pool_reader(bp, (int)j, N) < 0 && !folds_into((int)j + 1)) {
             const ColGrid ga = col_grid(M, op.cout_p, 8, 4096);   // elementwise pass: many short workgroups
             // a residual add that only reads this layer's output rides along: the normalised tensor itself
@@ -1983,6 +2029,13 @@ template <class T> struct Exec {
             dw_bwd(op, bp.ops[iv - 1], dz, y, ws(scr + bp.ops[iv - 1].y), wc + op.e_w, dvalue(iv), arch);
             summed[iv - 1] = 1;
             have[iv] = 1;
+            continue;
+          }
+          if (pw_bwd_fused(c, bp, j)) {
+            c->lanes.serial = group >= 0 && iv == bp.groups[group].root;
+            pw_bwd(op, dz, y, value(iv), wc + op.e_w, wanted[iv] ? dvalue(iv) : nullptr, have[iv], arch);
+            c->lanes.serial = false;
+            if (wanted[iv]) have[iv] = 1;
             continue;
           }
           {
@@ -2684,18 +2737,35 @@ int pbd_read_grad_value(pbd_ctx* c, int32_t b, int32_t v, float* host, size_t n)
     return fail(c, PBD_ESTATE, "the gradient of the output of block %d is not stored: the batch-norm reduction that does the last add's "
                 "backward pass forms it from the block's output and the teacher's activation", b);
   const OpPlan& op = bp.ops[v - 1];
-  if (dw_bwd_fused(c, bp, v - 1)) {
+  const bool dw = dw_bwd_fused(c, bp, v - 1);
+  if (dw || pw_bwd_fused(c, bp, v - 1)) {
     // the step does not write this tensor (the layer's backward kernel forms it as it stages the gradient of the normalised output):
-    // formed now, in the place of the layer's normalised input, which is not kept either
+    // formed now, of a depthwise layer in the place of its normalised input, which is not kept either, of an expand layer in place, the
+    // gradient of the normalised output put back afterwards
     const long M = (long)c->o.batch * s.h * s.w;
     const ColGrid g = col_grid(M, op.cout_p, 8, 4096);
     auto f = [&](size_t off) { return reinterpret_cast<const float*>(c->ws + off); };
-    bf16_t* dy = reinterpret_cast<bf16_t*>(c->ws + bp.scr_off + bp.val[op.d.in[0]]);
+    char* const dz = c->ws + bp.scr_off + bp.dval[v];
+    const size_t bytes = (size_t)M * op.cout_p * 2;
+    void* kept = dw ? nullptr : std::malloc(bytes);
+    if (!dw) {
+      if (!kept) return fail(c, PBD_EINVAL, "%zu bytes of host memory are not to be had", bytes);
+      hipError_t e = hipStreamSynchronize(c->stream);
+      if (e == hipSuccess) e = hipMemcpy(kept, dz, bytes, hipMemcpyDeviceToHost);
+      if (e != hipSuccess) { std::free(kept); HIP_TRY(c, e); }
+    }
+    bf16_t* dy = reinterpret_cast<bf16_t*>(dw ? c->ws + bp.scr_off + bp.val[op.d.in[0]] : dz);
     bn_bwd_apply_kernel<bf16_t><<<dim3(g.slabs, g.chunks), 256, 0, c->stream>>>(
-        reinterpret_cast<const bf16_t*>(c->ws + bp.scr_off + bp.dval[v]), dy, reinterpret_cast<const bf16_t*>(c->ws + bp.scr_off + op.y),
+        reinterpret_cast<const bf16_t*>(dz), dy, reinterpret_cast<const bf16_t*>(c->ws + bp.scr_off + op.y),
         f(op.s_keep), f(op.s_keep) + op.cout_p, f(op.s_mean), f(op.s_invstd), f(op.s_k2), f(op.s_k3), M, op.cout_p, op.d.act, g);
     rc = after_launches(c);
-    return rc ? rc : download_act(c, reinterpret_cast<const char*>(dy), s, host);
+    if (!rc) rc = download_act(c, reinterpret_cast<const char*>(dy), s, host);
+    if (kept) {
+      const hipError_t e = hipMemcpy(dz, kept, bytes, hipMemcpyHostToDevice);
+      std::free(kept);
+      if (!rc) HIP_TRY(c, e);
+    }
+    return rc;
   }
   return download_act(c, c->ws + bp.scr_off + bp.dval[v], s, host);
 }
