@@ -553,7 +553,13 @@ bool stem_s2d(const pbd_ctx* c, int block, const OpPlan& op) {
 int depthwise_reader(const pbd_ctx* c, const BlockPlan& bp, int j);
 bool dw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j);
 bool pw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j);
+bool pj_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j);
 inline int pw_blocks(long M) { return (int)std::min<long>(256, ((M + kPwPix - 1) / kPwPix + kPwWaves - 1) / kPwWaves); }
+inline PjBwdArgs pj_args(long M, int C, int K) {      // two workgroups a compute unit
+  PjBwdArgs g{(int)M, C, K, (int)((M + kPwPix - 1) / kPwPix), (C + kPjCh - 1) / kPjCh, 0, (unsigned)(M * C * 2), (unsigned)(M * K * 2)};
+  g.pblocks = std::max(1, std::min(512 / g.groups, (g.tiles + kPjWaves - 1) / kPjWaves));
+  return g;
+}
 constexpr int kS2dK = 256;     // reduction length of such a stem: 4 x 4 taps x 16 lanes
 
 // Also for tensors far beyond the 256 MiB last-level cache, which a kernel's output would have survived in for the next kernel of the
@@ -729,7 +735,10 @@ int plan(pbd_ctx* c) {
           need_red(op.s2d ? ((size_t)w.splits + 1) * op.d.c_out * kS2dK * 4 : (size_t)w.splits * op.wn * 4);
           const bool pw = pw_bwd_fused(c, bp, (int)v - 1);
           if (pw) need_red((size_t)pw_blocks(M) * op.wn * 4);
-          if (!op.s2d) defer(op, pw ? pw_blocks(M) : w.splits);
+          const bool pj = pj_bwd_fused(c, bp, (int)v - 1);
+          const int pblocks = pj ? pj_args(M, op.cin_p, op.d.c_out).pblocks : 0;
+          if (pj) need_red((size_t)pblocks * (op.wn + 2 * op.cin_p) * 4);
+          if (!op.s2d) defer(op, pj ? pblocks : pw ? pw_blocks(M) : w.splits);
           // per-row-tile batch-norm sums from the convolution's store (64-row tiles at most), and their regrouping
           need_red(((size_t)(M + 63) / 64 + kStatGroupsMax + 1) * 2 * op.cout_p * 4);
           const long Min = (long)c->o.batch * op.in.h * op.in.w;
@@ -878,6 +887,7 @@ const ManyTable& many_table() {
     PBD_MANY(1, bn_bwd_apply, B, false);
     put<&bn_small_fwd_block<B>, kSmallThreads, 2>(t, bn_small_fwd_kernel<B>);
     put<&bn_small_bwd_block<B>, kSmallThreads, 2>(t, bn_small_bwd_kernel<B>);
+    PBD_MANY(2, pj_bwd, true); PBD_MANY(2, pj_bwd, false);
     PBD_MANY(1, sum_partials, 32); PBD_MANY(1, sum_partials, 8);
     PBD_MANY(1, dw_wgrad, B, 3, 3); PBD_MANY(1, dw_wgrad, B, 7, 1);
 #define PBD_MANY_DW(K_) PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, false, false, false, false); PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, false, false, true, false); \
@@ -1045,6 +1055,15 @@ bool pw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j) {
   return c->o.precision == PBD_BF16 && !c->o.force_direct && op.d.type == OP_CBA && !op.dw && op.d.k == 1 && op.d.stride == 1 && op.d.pad == 0 &&
          op.cin_p <= kPwMaxIn && op.d.c_out > kPwMaxIn && op.d.c_out <= kPwMaxOut && op.d.c_out % 8 == 0 &&
          (long)c->o.batch * op.out.h * op.out.w >= kPwMinPixels && residual_reader(bp, j) < 0;
+}
+
+// Backward-data and the weight gradient of a projection that normalises the layer in front itself (dense_reader), with the sums of that
+// layer's batch norm, in one kernel (pj_bwd_kernel).  From kPjMinPixels pixels on, as above.
+constexpr long kPjMinPixels = 16384;
+bool pj_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j) {
+  const OpPlan& op = bp.ops[j];
+  return op.d.type == OP_CBA && !op.dw && op.d.in[0] > 0 && (long)c->o.batch * op.out.h * op.out.w >= kPjMinPixels &&
+         dense_reader(c, bp, op.d.in[0] - 1) == j;
 }
 
 // layer j's normalised output is formed by its reader and not written
@@ -1618,6 +1637,32 @@ template <class T> struct Exec {
     sum_partials(wpart, wsf(bp.grad) + op.e_w, (long)op.wn, blocks);
   }
 
+  // op's weight gradient (but for the architecture round) and the gradient dx of the normalised output of the layer p in front, with that
+  // layer's batch-norm sums (pj_bwd_fused).  dy: gradient of op's convolution output
+  void pj_bwd(const OpPlan& op, const OpPlan& p, const T* dy, const T* y_in, const T* wt, T* dx, bool arch) {
+    const BlockPlan& bp = c->net[1][blk];
+    const float* master = wsf(bp.master);
+    float* grad = wsf(bp.grad);
+    const long M = (long)c->o.batch * op.out.h * op.out.w;
+    const PjBwdArgs g = pj_args(M, op.cin_p, op.d.c_out);
+    float* wpart = parts(op);
+    float* spart = red() + (arch || deferred(op) ? 0 : (size_t)g.pblocks * op.wn);
+    {
+      ProfScope ps(c, arch ? "pj_dgrad_bn" : "pj_bwd_bn", 2 * bytes_of(op.in) + bytes_of(op.out) + (double)op.wn * 6,
+                   (arch ? 2.0 : 4.0) * M * op.d.c_out * op.in.c, net, blk, opi);
+      if constexpr (sizeof(T) == 2) {
+        const NormFold f{wsf(p.s_mean), wsf(p.s_invstd), master + p.e_gamma, master + p.e_beta, p.d.act};
+        launch(c, arch ? pj_bwd_kernel<false> : pj_bwd_kernel<true>, g.pblocks * g.groups, kPjThreads, 0, st, (const bf16_t*)dy, (const bf16_t*)y_in,
+               (const bf16_t*)wt, (bf16_t*)dx, wpart, spart, g, f);
+      }
+    }
+    launch(c, bn_bwd_finalize_kernel, p.cout_p / kFinalizeChannels, 256, 0, st, spart, g.pblocks, p.cout_p, (double)M,
+           grad + p.e_gamma, grad + p.e_beta, wsf(p.s_k2), wsf(p.s_k3));
+    if (arch || deferred(op)) return;
+    ProfScope ps(c, "sum_partials", (double)(g.pblocks + 1) * op.wn * 4, 0, net, blk, opi);
+    sum_partials(wpart, grad + op.e_w, (long)op.wn, g.pblocks);
+  }
+
   // ---- joins / pool -------------------------------------------------------
   void join_fwd(const OpPlan& op, const Join& j, T* z) {
     const long nvec = (long)c->o.batch * op.out.h * op.out.w * op.cout_p / 8;
@@ -2045,6 +2090,12 @@ template <class T> struct Exec {
                 dz_in, dz, y, master + op.e_gamma, master + op.e_beta, wsf(op.s_mean), wsf(op.s_invstd), wsf(op.s_k2),
                 wsf(op.s_k3), M, op.cout_p, op.d.act, ga);
           }
+        }
+        if (pj_bwd_fused(c, bp, j)) {
+          pj_bwd(op, bp.ops[iv - 1], dz, ws(scr + bp.ops[iv - 1].y), ws(bp.wt) + op.e_wt, dvalue(iv), arch);
+          summed[iv - 1] = 1;
+          have[iv] = 1;
+          continue;
         }
         const T* x = value(iv);
         if (!arch) {
