@@ -560,6 +560,11 @@ inline PjBwdArgs pj_args(long M, int C, int K) {      // two workgroups a comput
   g.pblocks = std::max(1, std::min(512 / g.groups, (g.tiles + kPjWaves - 1) / kPjWaves));
   return g;
 }
+inline PwFwdArgs pw_fwd_args(long M, int K, int C) {  // three workgroups a compute unit
+  PwFwdArgs g{(int)M, K, C, (int)((M + kPwPix - 1) / kPwPix), (C + kPjCh - 1) / kPjCh, 0, (unsigned)(M * K * 2), (unsigned)(M * C * 2)};
+  g.pblocks = std::max(1, std::min(768 / g.groups, (g.tiles + kPwfWaves - 1) / kPwfWaves));
+  return g;
+}
 constexpr int kS2dK = 256;     // reduction length of such a stem: 4 x 4 taps x 16 lanes
 
 // Also for tensors far beyond the 256 MiB last-level cache, which a kernel's output would have survived in for the next kernel of the
@@ -887,7 +892,7 @@ const ManyTable& many_table() {
     PBD_MANY(1, bn_bwd_apply, B, false);
     put<&bn_small_fwd_block<B>, kSmallThreads, 2>(t, bn_small_fwd_kernel<B>);
     put<&bn_small_bwd_block<B>, kSmallThreads, 2>(t, bn_small_bwd_kernel<B>);
-    PBD_MANY(2, pj_bwd, true); PBD_MANY(2, pj_bwd, false);
+    PBD_MANY(2, pj_bwd, true); PBD_MANY(2, pj_bwd, false); PBD_MANY(3, pw_fwd, false);
     PBD_MANY(1, sum_partials, 32); PBD_MANY(1, sum_partials, 8);
     PBD_MANY(1, dw_wgrad, B, 3, 3); PBD_MANY(1, dw_wgrad, B, 7, 1);
 #define PBD_MANY_DW(K_) PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, false, false, false, false); PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, false, false, true, false); \
@@ -1050,11 +1055,14 @@ bool dw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j) {
 
 // The same for an expand layer (pw_bwd_kernel).  From kPwMinPixels pixels on: below, a wave has a single tile of 32 pixels or none.
 constexpr long kPwMinPixels = 16384;
-bool pw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j) {
-  const OpPlan& op = bp.ops[j];
+bool expands(const pbd_ctx* c, const OpPlan& op) {
   return c->o.precision == PBD_BF16 && !c->o.force_direct && op.d.type == OP_CBA && !op.dw && op.d.k == 1 && op.d.stride == 1 && op.d.pad == 0 &&
          op.cin_p <= kPwMaxIn && op.d.c_out > kPwMaxIn && op.d.c_out <= kPwMaxOut && op.d.c_out % 8 == 0 &&
-         (long)c->o.batch * op.out.h * op.out.w >= kPwMinPixels && residual_reader(bp, j) < 0;
+         (long)c->o.batch * op.out.h * op.out.w >= kPwMinPixels;
+}
+bool pw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j) {
+  const OpPlan& op = bp.ops[j];
+  return expands(c, op) && residual_reader(bp, j) < 0;
 }
 
 // Backward-data and the weight gradient of a projection that normalises the layer in front itself (dense_reader), with the sums of that
@@ -1142,6 +1150,7 @@ template <class T> struct Exec {
   // vectors, and a column long enough for the chunked normalisation path.
   int fused_stats_tiles(const OpPlan& op) const {
     const long M = (long)c->o.batch * op.out.h * op.out.w;
+    if (expands(c, op)) return pw_fwd_args(M, op.cin_p, op.d.c_out).pblocks;
     if (!fuses_residual(op) || op.d.c_out % 8 != 0 || short_column(M)) return 0;
     const DmaCfg d = dma_for(M, op.d.c_out, kred_of(op), ca_of(op));
     if (d.use) return d.big_m + d.tail_m;
@@ -1149,13 +1158,21 @@ template <class T> struct Exec {
     return (int)((M + cfg.BM - 1) / cfg.BM);
   }
   // res (optional): a residual join fused into the store, y = res_act(conv result + res); only where
-  // fuses_residual(op) holds.  stats (optional): per row tile sums of y and y^2, where fused_stats_tiles(op) > 0
+  // fuses_residual(op) holds.  stats (optional): per row tile sums of y and y^2, where fused_stats_tiles(op) > 0 (an expand layer: of
+  // y - y0 and its square, y0 the first pixel's)
   void conv_fwd(const OpPlan& op, const T* x, const T* w, T* y, const float* a, const float* b, int act,
                 const T* res = nullptr, int res_act = 0, float* stats = nullptr, NormFold fold = NormFold{}) {
     const int N = c->o.batch;
     const double flops = 2.0 * N * op.out.h * op.out.w * op.d.c_out * op.d.k * op.d.k * op.in.c;
     const double bytes = bytes_of(op.in) + bytes_of(op.out) * (res ? 2 : 1) + (double)op.wn * sizeof(T);
-    if (mfma()) {
+    if (!res && !fold.mean && (a || stats) && expands(c, op)) {
+      if constexpr (sizeof(T) == 2) {
+        const PwFwdArgs g = pw_fwd_args((long)N * op.out.h * op.out.w, op.cin_p, op.d.c_out);
+        ProfScope ps(c, a ? "pw_fwd_affine" : "pw_fwd_store", bytes, flops, net, blk, opi);
+        launch(c, a ? pw_fwd_kernel<true> : pw_fwd_kernel<false>, g.pblocks * g.groups, kPwfThreads, 0, st, (const bf16_t*)x, (const bf16_t*)w,
+               (bf16_t*)y, a, b, act, stats, g);
+      }
+    } else if (mfma()) {
       if constexpr (sizeof(T) == 2) {
         IgemmArgs g{N, op.in.h, op.in.w, op.cin_p, op.out.h, op.out.w, op.d.c_out, op.d.k, op.d.k,
                     op.d.stride, op.d.pad, N * op.out.h * op.out.w, op.d.k * op.d.k * op.cin_p, 0,
@@ -1907,9 +1924,9 @@ template <class T> struct Exec {
           const T* pivot = y;                       // the pass of its own shifts by the first row
           int chunks = stat_tiles;
           if (stat_tiles) {
-            // the convolution's store left one pair of sums per row tile (no pivot); thousands of them are
+            // the convolution's store left one pair of sums per row tile (an expand layer's shifted likewise, else no pivot); thousands of them are
             // first summed in groups so that the finalize kernel's walk stays short
-            pivot = nullptr;
+            if (!expands(c, op)) pivot = nullptr;
             if (chunks > kStatGroupsMax) {
               const int per = (chunks + kStatGroupsMax - 1) / kStatGroupsMax, n = 2 * op.cout_p;
               float* out = red() + (size_t)chunks * n;
