@@ -41,7 +41,7 @@ HBM_TRAFFIC_PER_LAUNCH = {
 # image size (its samples/s do not depend on the batch to first order: every loop is linear in it).
 CPU_BASELINE_BATCH = {"tiny_cnn": 8, "vgg16_dsconv": 256, "mbv2_mbconv_k5e4": 8, "mbv2_supernet": 2, "resnet50_x1.5": 2}
 
-CONV_PREFIXES = ("igemm_", "wgrad_")
+CONV_PREFIXES = ("igemm_", "wgrad_", "pw_", "pj_")
 
 
 def mfma_peak(name):
