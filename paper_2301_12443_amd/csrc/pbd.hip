@@ -1068,8 +1068,8 @@ bool pw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j) {
 }
 
 // Backward-data and the weight gradient of a projection that normalises the layer in front itself (dense_reader), with the sums of that
-// layer's batch norm, in one kernel (pj_bwd_kernel).  From kPjMinPixels pixels on, as above: at 16464 pixels, 128 -> 32, 13 to 17 us against 17 to
-// 25 for three launches, at 32928 13.5 against 17.7.
+// layer's batch norm, in one kernel (pj_bwd_kernel).  From kPjMinPixels pixels on, as above: at 16464 pixels, 128 -> 32, 12 to 17 us against 17 to
+// 28 for three launches, at 32928 13.5 against 17.7.
 constexpr long kPjMinPixels = 16384;
 bool pj_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j) {
   const OpPlan& op = bp.ops[j];
