@@ -103,6 +103,7 @@ struct BlockPlan {
   std::vector<LaneGroup> groups;
   std::vector<int> group_of, lane_of;   // per op: its group and its lane there (-1: none)
   int lanes = 1;                        // regions of reduction scratch: the most lanes of a group
+  size_t lane_bytes = 0;                // the regions of the lanes behind the first: what an op of a group needs
   std::vector<Shape> shapes;     // values, 0 = block input
   std::vector<size_t> val;       // scratch byte offset of each value (>=1)
   std::vector<size_t> dval;      // scratch byte offset of each value's gradient (student)
@@ -603,13 +604,32 @@ void find_lanes(pbd_ctx* c, BlockPlan& bp) {
   }
 }
 
+// A block's reduction scratch: one region for the ops that go out by themselves and for the first lane, and for every further lane one of
+// what the ops of a lane group need (the supernet's at batch 64: 6 x 39 MB a block at most).
+inline size_t all_red(const BlockPlan& bp) { return bp.red_bytes + bp.lane_bytes * (bp.lanes - 1); }
+
 int plan(pbd_ctx* c) {
   const size_t es = c->esz;
   const bool bf = c->o.precision == PBD_BF16;
   size_t p = 0;  // parameter region cursor
   auto take = [&](size_t bytes) { size_t o = p; p += align_up(bytes); return o; };
   size_t red = kMseBlocks * sizeof(float);  // reduction scratch of the block being planned
-  auto need_red = [&](size_t bytes) { red = std::max(red, bytes); };
+  size_t lane_red = 0;                      // ... and of its ops that belong to a lane group
+  bool in_lane = false;
+  auto need_red = [&](size_t bytes) {
+    red = std::max(red, bytes);
+    if (in_lane) lane_red = std::max(lane_red, bytes);
+  };
+  // partial sums of op's weight gradient: a deferred op leaves its own elsewhere, but for the step that brings its own scratch, without lanes
+  auto need_parts = [&](const OpPlan& op, size_t bytes) {
+    red = std::max(red, bytes);
+    if (in_lane && op.e_part < 0) lane_red = std::max(lane_red, bytes);
+  };
+  // partial tiles of an implicit GEMM whose reduction is cut (launch_igemm; one that is not cut stores its result itself)
+  auto need_split = [&](long M, int NC, int Kred, int CA) {
+    const int splits = igemm_splits(M, NC, Kred, CA);
+    if (splits > 1) need_red((size_t)splits * M * NC * 4);
+  };
 
   // teacher parameters
   for (BlockPlan& bp : c->net[0])
@@ -617,14 +637,13 @@ int plan(pbd_ctx* c) {
       if (op.d.type != OP_CBA) continue;
       if (!op.dw && bf) {
         const long M = (long)c->o.batch * op.out.h * op.out.w;
-        need_red((size_t)igemm_splits(M, op.d.c_out, op.d.k * op.d.k * op.cin_p, op.cin_p) * M * op.d.c_out * 4);
+        need_split(M, op.d.c_out, op.d.k * op.d.k * op.cin_p, op.cin_p);
       }
       op.t_w = take(op.wn * es);
       op.s2d = stem_s2d(c, (int)(&bp - &c->net[0][0]), op);
       if (op.s2d) {
         op.w2 = take((size_t)op.d.c_out * kS2dK * es);
-        const long M = (long)c->o.batch * op.out.h * op.out.w;
-        need_red((size_t)igemm_splits(M, op.d.c_out, kS2dK, 16) * M * op.d.c_out * 4);
+        need_split((long)c->o.batch * op.out.h * op.out.w, op.d.c_out, kS2dK, 16);
       }
       op.t_gamma = take(op.cout_p * 4); op.t_beta = take(op.cout_p * 4);
       op.t_rmean = take(op.cout_p * 4); op.t_rvar = take(op.cout_p * 4);
@@ -698,6 +717,8 @@ int plan(pbd_ctx* c) {
   for (BlockPlan& bp : c->net[1]) {
     size_t s = 0, parts = 0;      // (parts: elements of the deferred partial sums)
     red = kMseBlocks * sizeof(float);
+    lane_red = 0;
+    find_lanes(c, bp);
     // ops that the weight round back-propagates to; one whose value leads nowhere keeps the zero gradient it was bound with
     std::vector<char> reached(bp.shapes.size(), 0);
     reached.back() = 1;
@@ -716,6 +737,7 @@ int plan(pbd_ctx* c) {
       bp.val[v] = s; s += tensor_bytes(c, bp.shapes[v]);
       bp.dval[v] = s; s += tensor_bytes(c, bp.shapes[v]);
       OpPlan& op = bp.ops[v - 1];
+      in_lane = bp.group_of[v - 1] >= 0;
       const long M = (long)c->o.batch * op.out.h * op.out.w;
       if (op.d.type == OP_CBA) {
         op.y = s; s += tensor_bytes(c, op.out);
@@ -724,32 +746,39 @@ int plan(pbd_ctx* c) {
         if (op.dw) {
           const DwWgradCfg gw = dw_wgrad_cfg(bf && !c->o.force_direct, c->o.batch, op.in.h, op.in.w, op.out.h, op.out.w,
                                              op.cout_p, op.d.k, op.d.stride, op.d.pad);
-          need_red((size_t)gw.chunks * op.d.k * op.d.k * op.cout_p * 4);
           if (dw_on_mfma(bf && !c->o.force_direct, c->o.batch, op.out.h, op.out.w, op.cout_p, op.d.k, op.d.stride, op.d.pad))
             need_red((size_t)dw_stat_groups(c->o.batch, op.out.h, op.out.w, op.cout_p) * 3 * op.cout_p * 4);
-          int chunks = gw.chunks;
           if (dw_bwd_fused(c, bp, (int)v - 1)) {
-            chunks = dw_chunks(dw_bwd_args(c->o.batch, op.in.h, op.in.w, op.cout_p, op.d.k, false));
-            need_red((size_t)chunks * (op.d.k * op.d.k + 2) * op.cout_p * 4);
+            const int chunks = dw_chunks(dw_bwd_args(c->o.batch, op.in.h, op.in.w, op.cout_p, op.d.k, false));
+            defer(op, chunks);
+            need_parts(op, (size_t)chunks * (op.d.k * op.d.k + 2) * op.cout_p * 4);
+            need_red((size_t)chunks * 2 * op.cout_p * 4);
             need_red((size_t)dw_chunks(dw_bwd_args(c->o.batch, op.in.h, op.in.w, op.cout_p, op.d.k, true)) * 2 * op.cout_p * 4);
+          } else {
+            defer(op, gw.chunks);
+            need_parts(op, (size_t)gw.chunks * op.d.k * op.d.k * op.cout_p * 4);
           }
-          defer(op, chunks);
         } else if (bf && !c->o.force_direct) {
           const WgradCfg w = op.s2d ? wgrad_cfg(M, op.d.c_out, kS2dK, 16) : wgrad_cfg(M, op.d.c_out, op.d.k * op.d.k * op.cin_p, op.d.k * op.d.k);
-          // (the stem on the space-to-depth input: partial sums and their sum in the repacked layout, then unpacked)
-          need_red(op.s2d ? ((size_t)w.splits + 1) * op.d.c_out * kS2dK * 4 : (size_t)w.splits * op.wn * 4);
-          const bool pw = pw_bwd_fused(c, bp, (int)v - 1);
-          if (pw) need_red((size_t)pw_blocks(M) * op.wn * 4);
-          const bool pj = pj_bwd_fused(c, bp, (int)v - 1);
-          const int pblocks = pj ? pj_args(M, op.cin_p, op.d.c_out).pblocks : 0;
-          if (pj) need_red((size_t)pblocks * (op.wn + 2 * op.cin_p) * 4);
-          if (!op.s2d) defer(op, pj ? pblocks : pw ? pw_blocks(M) : w.splits);
-          // per-row-tile batch-norm sums from the convolution's store (64-row tiles at most), and their regrouping
-          need_red(((size_t)(M + 63) / 64 + kStatGroupsMax + 1) * 2 * op.cout_p * 4);
+          if (op.s2d) {               // partial sums on the space-to-depth input and their sum in the repacked layout, then unpacked
+            need_red(((size_t)w.splits + 1) * op.d.c_out * kS2dK * 4);
+          } else if (pj_bwd_fused(c, bp, (int)v - 1)) {
+            const int blocks = pj_args(M, op.cin_p, op.d.c_out).pblocks;
+            defer(op, blocks);
+            need_parts(op, (size_t)blocks * (op.wn + 2 * op.cin_p) * 4);
+            need_red((size_t)blocks * 2 * op.cin_p * 4);
+          } else {
+            const int splits = pw_bwd_fused(c, bp, (int)v - 1) ? pw_blocks(M) : w.splits;
+            defer(op, splits);
+            need_parts(op, (size_t)splits * op.wn * 4);
+          }
+          // per-row-tile batch-norm sums from the convolution's store (64-row tiles at least), and their regrouping where they are many
+          const long stat_tiles = (M + 63) / 64;
+          need_red((size_t)(stat_tiles + (stat_tiles > kStatGroupsMax ? kStatGroupsMax : 0) + 1) * 2 * op.cout_p * 4);
           const long Min = (long)c->o.batch * op.in.h * op.in.w;
-          need_red((size_t)igemm_splits(M, op.d.c_out, op.d.k * op.d.k * op.cin_p, op.cin_p) * M * op.d.c_out * 4);
-          if (op.s2d) need_red((size_t)igemm_splits(M, op.d.c_out, kS2dK, 16) * M * op.d.c_out * 4);
-          need_red((size_t)igemm_splits(Min, op.cin_p, op.d.k * op.d.k * op.d.c_out, op.d.c_out) * Min * op.cin_p * 4);
+          need_split(M, op.d.c_out, op.d.k * op.d.k * op.cin_p, op.cin_p);
+          if (op.s2d) need_split(M, op.d.c_out, kS2dK, 16);
+          need_split(Min, op.cin_p, op.d.k * op.d.k * op.d.c_out, op.d.c_out);
         }
       } else if (op.d.type == OP_POOL) {
         op.idx = s; s += align_up((size_t)M * op.cout_p);
@@ -760,9 +789,9 @@ int plan(pbd_ctx* c) {
     bp.parts = s;
     bp.scratch_bytes = align_up(s + parts * 4);
     bp.red_bytes = align_up(red);
-    find_lanes(c, bp);
-    smax = std::max(smax, bp.scratch_bytes + bp.red_bytes * bp.lanes);
-    ssum += bp.scratch_bytes + bp.red_bytes * bp.lanes;
+    bp.lane_bytes = align_up(lane_red);
+    smax = std::max(smax, bp.scratch_bytes + all_red(bp));
+    ssum += bp.scratch_bytes + all_red(bp);
   }
   c->r_tred = cur; cur += teacher_red;
   // Blocks are independent (Sec. IV-B): when the sum of their scratch fits comfortably in HBM each
@@ -772,7 +801,7 @@ int plan(pbd_ctx* c) {
   for (BlockPlan& bp : c->net[1]) {
     bp.scr_off = at;
     bp.red_off = at + bp.scratch_bytes;
-    if (c->concurrent) at += bp.scratch_bytes + bp.red_bytes * bp.lanes;
+    if (c->concurrent) at += bp.scratch_bytes + all_red(bp);
   }
   cur = c->concurrent ? at : cur + smax;
   c->total = cur;
@@ -1104,7 +1133,10 @@ template <class T> struct Exec {
     return dma_for((long)c->o.batch * op.out.h * op.out.w, op.d.c_out, kS2dK, 64).use ? 64 : 16;
   }
   float* red() const {
-    return red_static ? red_static : wsf(red_off + (c->lanes.on ? (size_t)c->lanes.lane * c->net[1][blk].red_bytes : 0));
+    if (red_static) return red_static;
+    const int lane = c->lanes.on ? c->lanes.lane : 0;
+    const BlockPlan& bp = c->net[1][blk];
+    return wsf(red_off + (lane ? bp.red_bytes + (size_t)(lane - 1) * bp.lane_bytes : 0));
   }
   // before op j of a student block's forward or backward pass: its launches go to its lane, or out at once
   void lane_of_op(const BlockPlan& bp, int j, int& group) {

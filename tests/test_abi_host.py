@@ -93,6 +93,19 @@ def test_workspace_sizes_and_unbound_calls():
     assert pbd.lib().pbd_sync(None) == -1
 
 
+def test_workspace_of_the_supernet_holds_what_is_used():
+    """Reduction scratch is reserved for what is written to it: no partial tiles for implicit GEMMs that are not cut, and for the second to
+    last candidate of a mixed layer a region of what a candidate's layers need.  Both as whole copies of a layer's float32 output took
+    43.8 GiB at batch 64 and 129.4 at 192, and at batch 268 the blocks no longer lay side by side (the sum dropped to 108 GiB, the
+    blocks ran one after another and kept no values for read_value)."""
+    size = {b: pbd.Distiller(W.mbv2_supernet(b, 224, "bf16")).workspace_bytes() / 2**30 for b in (2, 64, 192, 268)}
+    assert size[2] < 1.85 and size[64] < 38.35 and size[192] < 113.3
+    assert size[192] < size[268] < 160
+    # (the other networks have no mixed layers: less than with whole copies for every layer)
+    assert pbd.Distiller(W.CONFIGS["mbv2_mbconv_k5e4"](128, 224, "bf16")).workspace_bytes() / 2**30 < 7.0
+    assert pbd.Distiller(W.CONFIGS["resnet50_x1.5"](256, 224, "bf16")).workspace_bytes() / 2**30 < 31.0
+
+
 def test_binding_rejects_a_wrong_input_tensor_before_any_launch():
     """The ABI carries no size for x_dev (a bare device pointer to batch x C0 x H0 x W0 float32), so the
     binding checks dtype, shape, device and contiguity itself and raises before the library is called."""
