@@ -14,7 +14,6 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
-#include <cstdlib>
 #include <cstring>
 #include <string>
 #include <new>
@@ -2327,25 +2326,22 @@ int upload(pbd_ctx* c, const TensorRef& t, const OpPlan& op, const float* host) 
   return PBD_OK;
 }
 
-// NHWC (Cp) device tensor -> NCHW float host
-int download_act(pbd_ctx* c, const char* dev, Shape s, float* host) {
-  const int N = c->o.batch, cp = round8(s.c);
-  const size_t n = (size_t)N * s.h * s.w * cp;
-  std::vector<float> f(n);
-  if (c->esz == 2) {
-    std::vector<uint16_t> h16(n);
-    HIP_TRY(c, hipMemcpyAsync(h16.data(), dev, n * 2, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    for (size_t i = 0; i < n; ++i) f[i] = bf2f(h16[i]);
-  } else {
-    HIP_TRY(c, hipMemcpyAsync(f.data(), dev, n * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-  }
-  const size_t hw = (size_t)s.h * s.w;
-  for (int nn = 0; nn < N; ++nn)
+// NHWC (Cp) elements -> NCHW float; at(i): element i as float
+template <class F> void to_nchw(const pbd_ctx* c, Shape s, float* host, F&& at) {
+  const size_t hw = (size_t)s.h * s.w, cp = round8(s.c);
+  for (int nn = 0; nn < c->o.batch; ++nn)
     for (size_t p = 0; p < hw; ++p)
       for (int ch = 0; ch < s.c; ++ch)
-        host[((size_t)nn * s.c + ch) * hw + p] = f[((size_t)nn * hw + p) * cp + ch];
+        host[((size_t)nn * s.c + ch) * hw + p] = at(((size_t)nn * hw + p) * cp + ch);
+}
+// NHWC (Cp) device tensor -> NCHW float host
+int download_act(pbd_ctx* c, const char* dev, Shape s, float* host) {
+  const size_t n = (size_t)c->o.batch * s.h * s.w * round8(s.c);
+  std::vector<char> raw(n * c->esz);
+  HIP_TRY(c, hipMemcpyAsync(raw.data(), dev, raw.size(), hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  if (c->esz == 2) to_nchw(c, s, host, [&](size_t i) { return bf2f(reinterpret_cast<const uint16_t*>(raw.data())[i]); });
+  else to_nchw(c, s, host, [&](size_t i) { return reinterpret_cast<const float*>(raw.data())[i]; });
   return PBD_OK;
 }
 
@@ -2840,35 +2836,29 @@ int pbd_read_grad_value(pbd_ctx* c, int32_t b, int32_t v, float* host, size_t n)
     return fail(c, PBD_ESTATE, "the gradient of the output of block %d is not stored: the batch-norm reduction that does the last add's "
                 "backward pass forms it from the block's output and the teacher's activation", b);
   const OpPlan& op = bp.ops[v - 1];
-  const bool dw = dw_bwd_fused(c, bp, v - 1);
-  if (dw || pw_bwd_fused(c, bp, v - 1)) {
-    // the step does not write this tensor (the layer's backward kernel forms it as it stages the gradient of the normalised output):
-    // formed now, of a depthwise layer in the place of its normalised input, which is not kept either, of an expand layer in place, the
-    // gradient of the normalised output put back afterwards
-    const long M = (long)c->o.batch * s.h * s.w;
-    const ColGrid g = col_grid(M, op.cout_p, 8, 4096);
+  if (dw_bwd_fused(c, bp, v - 1) || pw_bwd_fused(c, bp, v - 1)) {
+    // the step does not write this tensor (the layer's backward kernel forms it as it stages the gradient of the normalised output): formed
+    // now, as many rows at a time as the block's reduction scratch holds, which is free between calls
+    const long M = (long)c->o.batch * s.h * s.w, cp = op.cout_p, rows = (long)bp.red_bytes / (cp * 2);
     auto f = [&](size_t off) { return reinterpret_cast<const float*>(c->ws + off); };
-    char* const dz = c->ws + bp.scr_off + bp.dval[v];
-    const size_t bytes = (size_t)M * op.cout_p * 2;
-    void* kept = dw ? nullptr : std::malloc(bytes);
-    if (!dw) {
-      if (!kept) return fail(c, PBD_EINVAL, "%zu bytes of host memory are not to be had", bytes);
-      hipError_t e = hipStreamSynchronize(c->stream);
-      if (e == hipSuccess) e = hipMemcpy(kept, dz, bytes, hipMemcpyDeviceToHost);
-      if (e != hipSuccess) { std::free(kept); HIP_TRY(c, e); }
+    const bf16_t* const dz = reinterpret_cast<const bf16_t*>(c->ws + bp.scr_off + bp.dval[v]);
+    const bf16_t* const y = reinterpret_cast<const bf16_t*>(c->ws + bp.scr_off + op.y);
+    bf16_t* const dy = reinterpret_cast<bf16_t*>(c->ws + bp.red_off);
+    std::vector<uint16_t> h16((size_t)M * cp);
+    hipError_t e = hipSuccess;
+    for (long m = 0; m < M && e == hipSuccess; m += rows) {
+      const long n = std::min(rows, M - m);
+      const ColGrid g = col_grid(n, (int)cp, 8, 4096);
+      bn_bwd_apply_kernel<bf16_t><<<dim3(g.slabs, g.chunks), 256, 0, c->stream>>>(
+          dz + m * cp, dy, y + m * cp, f(op.s_keep), f(op.s_keep) + cp, f(op.s_mean), f(op.s_invstd), f(op.s_k2), f(op.s_k3), n, (int)cp, op.d.act, g);
+      e = hipGetLastError();
+      if (e == hipSuccess) e = hipMemcpyAsync(h16.data() + m * cp, dy, (size_t)n * cp * 2, hipMemcpyDeviceToHost, c->stream);
     }
-    bf16_t* dy = reinterpret_cast<bf16_t*>(dw ? c->ws + bp.scr_off + bp.val[op.d.in[0]] : dz);
-    bn_bwd_apply_kernel<bf16_t><<<dim3(g.slabs, g.chunks), 256, 0, c->stream>>>(
-        reinterpret_cast<const bf16_t*>(dz), dy, reinterpret_cast<const bf16_t*>(c->ws + bp.scr_off + op.y),
-        f(op.s_keep), f(op.s_keep) + op.cout_p, f(op.s_mean), f(op.s_invstd), f(op.s_k2), f(op.s_k3), M, op.cout_p, op.d.act, g);
-    rc = after_launches(c);
-    if (!rc) rc = download_act(c, reinterpret_cast<const char*>(dy), s, host);
-    if (kept) {
-      const hipError_t e = hipMemcpy(dz, kept, bytes, hipMemcpyHostToDevice);
-      std::free(kept);
-      if (!rc) HIP_TRY(c, e);
-    }
-    return rc;
+    const hipError_t done = hipStreamSynchronize(c->stream);     // (also after an error: copies may be on their way)
+    HIP_TRY(c, e);
+    HIP_TRY(c, done);
+    to_nchw(c, s, host, [&](size_t i) { return bf2f(h16[i]); });
+    return PBD_OK;
   }
   return download_act(c, c->ws + bp.scr_off + bp.dval[v], s, host);
 }

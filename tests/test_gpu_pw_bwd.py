@@ -63,6 +63,33 @@ def test_expand_layer(n, h, w, c_in, c, act, k, stride, first):
     np.testing.assert_array_equal(d.read_grad_value(0, v), d.read_grad_value(0, v))
 
 
+def test_reading_a_gradient_waits_for_the_bound_stream_alone():
+    """read_grad_value of an expand layer and of a depthwise one, whose gradient is formed on request, while another stream (the legacy
+    default one) is busy for some hundred times as long as the read takes."""
+    n, h, w = 16, 32, 32
+    t = W.Block()
+    t.cba(0, 16, 1, act=W.ACT_NONE)
+    wl = W.Workload("pw_bwd", n, (16, h, w), [t], [_block(16, 96, W.ACT_RELU6, 3, 1, True)], "bf16", lr=0.05)
+    d = parity.make_distiller(wl, n, "bf16")
+    d.teacher_relay(torch.from_numpy(W.make_input(wl, batch=n)).cuda())
+    assert {"pw_bwd_bn", "dw_wgrad_mfma_bn_k3"} <= set(_classes(d, wl))
+    d.sync()
+    a = torch.randn(8192, 8192, device="cuda", dtype=torch.bfloat16)
+    out = a @ a
+    torch.cuda.synchronize()
+    for v in (1, 2):
+        want = d.read_grad_value(0, v)
+        for _ in range(600):                           # 0.4 s and more
+            torch.matmul(a, a, out=out)
+        end = torch.cuda.Event()
+        end.record()
+        got = d.read_grad_value(0, v)
+        busy = not end.query()
+        torch.cuda.synchronize()
+        assert busy, f"value {v}"
+        np.testing.assert_array_equal(got, want)
+
+
 def test_other_layers_keep_the_separate_passes():
     def fused(n, c_in, c, k, stride, residual=False):
         b = W.Block()
