@@ -549,8 +549,8 @@ __global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __r
 }
 
 // The whole backward pass of a stride-1 layer between two batch norms, y1 -> z1 = act(bn(y1)) -> y2 = z1 * w -> z2 = act(bn(y2)), in one
-// pass over the tensors: reads dz2, y2 (with the filter's halo) and y1, forms dy2 from dz2 and y2 as it stages them (bn_bwd_apply_kernel's
-// arithmetic and rounding), and from that one tile the gradient of z1 (stored), the filter's (one partial result per workgroup) and the two
+// pass over the tensors: reads dz2, y2 (with the filter's halo) and y1, forms dy2 from dz2 and y2 as it stages them (bn_bwd_dy), and from
+// that one tile the gradient of z1 (stored), the filter's (one partial result per workgroup) and the two
 // sums of y1's batch-norm backward pass (bn_bwd_reduce_kernel's; one pair per workgroup and channel).  As passes of their own these read and
 // write the layer's tensor ten times (apply 3, backward-data 2, backward-weight 2, reduce 2, and dy2's halo), here it is four.
 // The weight gradient is taken over the pixels p of x = z1 so that x needs no halo and dy2's tile serves both products:
@@ -561,7 +561,16 @@ __global__ __launch_bounds__(256, 3) void dw_wgrad_mfma_kernel(const bf16_t* __r
 // 5 x 5, 77 -> 69; all such layers of a supernet step at batch 64 11.6 -> 7.9 ms.  Tried: the filters' Toeplitz rows held in registers
 // (20 of them at 5 x 5, spilled), x shifted by selects instead of by its LDS address (13 instructions a row more).
 struct BnBwd { const float* mean; const float* invstd; const float* gamma; const float* beta; const float* k2; const float* k3; int act; };
-struct DwBnBwd { float mu[kDwCh], a[kDwCh], b[kDwCh], p[kDwCh], q[kDwCh]; };   // dy = a dpre + (p (y - mu) + q)
+struct DwBnBwd { float mu[kDwCh], a[kDwCh], b[kDwCh], p[kDwCh], q[kDwCh]; };   // (BnBwdTerms of the channels)
+// The last stage of a batch norm's backward pass as every kernel has it that forms dy as it stages it, and bn_bwd_form_kernel, which forms the
+// tensor for those who ask for it: dy = a dpre + (p (y - mu) + q), dpre = dz where the activation passes, two roundings an element
+// (bn_bwd_apply_kernel: a (dpre - k2 - (y - mu) invstd k3), the same to within their last bits).
+struct BnBwdTerms { float mu, a, b, p, q; };
+__device__ __forceinline__ BnBwdTerms bn_bwd_terms(const BnBwd& f, int c) {
+  const float is = f.invstd[c], a = f.gamma[c] * is;
+  return {f.mean[c], a, f.beta[c], -a * (is * f.k3[c]), -a * f.k2[c]};
+}
+__device__ __forceinline__ float bn_bwd_dy(float yc, float dpre, float a, float p, float q) { return fmaf(a, dpre, fmaf(p, yc, q)); }
 __device__ __forceinline__ unsigned dw_word(const uint4& v, int m) { return m == 0 ? v.x : m == 1 ? v.y : m == 2 ? v.z : v.w; }
 // all ones where bit i is set (a conditional expression on it becomes a branch around the arithmetic)
 __device__ __forceinline__ unsigned dw_bit(unsigned v, int i) { return (unsigned)((int)(v << (31 - i)) >> 31); }
@@ -587,7 +596,7 @@ __device__ __forceinline__ void dw_bn_bwd_store(unsigned char* dst, const uint4 
       const unsigned dw = dw_word(d[i], m), yw = dw_word(y[i], m);
       const float y0 = bf_lo(yw) - mu.x, y1 = bf_hi(yw) - mu.y;
       const float d0 = dw_pass(fmaf(y0, a.x, b.x), bf_lo(dw), limit), d1 = dw_pass(fmaf(y1, a.y, b.y), bf_hi(dw), limit);
-      const float t0 = fmaf(a.x, d0, fmaf(fp.x, y0, fq.x)), t1 = fmaf(a.y, d1, fmaf(fp.y, y1, fq.y));
+      const float t0 = bn_bwd_dy(y0, d0, a.x, fp.x, fq.x), t1 = bn_bwd_dy(y1, d1, a.y, fp.y, fq.y);
       o[i] = pack_bf2(t0, t1) & dw_bit(ok, i);
     }
     if (store) {
@@ -595,6 +604,25 @@ __device__ __forceinline__ void dw_bn_bwd_store(unsigned char* dst, const uint4 
       *reinterpret_cast<uint2*>(dst + (2 * m + 1) * CH_PITCH) = make_uint2(dw_hi2(o[0], o[1]), dw_hi2(o[2], o[3]));
     }
     __builtin_amdgcn_sched_barrier(0);
+  }
+}
+// dy as a tensor, bit for bit what the kernels form (pbd_read_grad_value)
+__global__ __launch_bounds__(256) void bn_bwd_form_kernel(const bf16_t* __restrict__ dz, const bf16_t* __restrict__ y, bf16_t* __restrict__ dy, long nvec,
+                                                          int ncv, BnBwd f) {
+  const unsigned limit = dw_pass_limit(f.act);
+  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < nvec; i += (long)gridDim.x * blockDim.x) {
+    const uint4 d = *reinterpret_cast<const uint4*>(dz + i * 8), v = *reinterpret_cast<const uint4*>(y + i * 8);
+    unsigned o[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int c = (int)(i % ncv) * 8 + 2 * m;
+      const BnBwdTerms t0 = bn_bwd_terms(f, c), t1 = bn_bwd_terms(f, c + 1);
+      const unsigned dw = dw_word(d, m), yw = dw_word(v, m);
+      const float y0 = bf_lo(yw) - t0.mu, y1 = bf_hi(yw) - t1.mu;
+      const float d0 = dw_pass(fmaf(y0, t0.a, t0.b), bf_lo(dw), limit), d1 = dw_pass(fmaf(y1, t1.a, t1.b), bf_hi(dw), limit);
+      o[m] = pack_bf2(bn_bwd_dy(y0, d0, t0.a, t0.p, t0.q), bn_bwd_dy(y1, d1, t1.a, t1.p, t1.q));
+    }
+    *reinterpret_cast<uint4*>(dy + i * 8) = make_uint4(o[0], o[1], o[2], o[3]);
   }
 }
 // the same for x = z1 from y1 (dw_fold_apply's arithmetic)
@@ -641,13 +669,8 @@ __device__ __forceinline__ void dw_bwd_mfma_block(const Blk& blk, const bf16_t* 
 
   if (tid < kDwCh) {
     const int c = cv0 * 8 + tid;
-    const bool in = c < C;
-    const float a = in ? f2.gamma[c] * f2.invstd[c] : 0.f;
-    c2.mu[tid] = in ? f2.mean[c] : 0.f;
-    c2.a[tid] = a;
-    c2.b[tid] = in ? f2.beta[c] : 0.f;
-    c2.p[tid] = in ? -a * (f2.invstd[c] * f2.k3[c]) : 0.f;
-    c2.q[tid] = in ? -a * f2.k2[c] : 0.f;
+    const BnBwdTerms t = c < C ? bn_bwd_terms(f2, c) : BnBwdTerms{};
+    c2.mu[tid] = t.mu; c2.a[tid] = t.a; c2.b[tid] = t.b; c2.p[tid] = t.p; c2.q[tid] = t.q;
   }
   dw_fold_load(c1, f1, cv0 * 8, C, tid);
   if (tid < ROWD / 8) *reinterpret_cast<uint2*>(smem + ZERO + tid * 8) = make_uint2(0u, 0u);

@@ -2844,13 +2844,13 @@ int pbd_read_grad_value(pbd_ctx* c, int32_t b, int32_t v, float* host, size_t n)
     const bf16_t* const dz = reinterpret_cast<const bf16_t*>(c->ws + bp.scr_off + bp.dval[v]);
     const bf16_t* const y = reinterpret_cast<const bf16_t*>(c->ws + bp.scr_off + op.y);
     bf16_t* const dy = reinterpret_cast<bf16_t*>(c->ws + bp.red_off);
+    const BnBwd terms{f(op.s_mean), f(op.s_invstd), f(op.s_keep), f(op.s_keep) + cp, f(op.s_k2), f(op.s_k3), op.d.act};
     std::vector<uint16_t> h16((size_t)M * cp);
     hipError_t e = hipSuccess;
     for (long m = 0; m < M && e == hipSuccess; m += rows) {
       const long n = std::min(rows, M - m);
-      const ColGrid g = col_grid(n, (int)cp, 8, 4096);
-      bn_bwd_apply_kernel<bf16_t><<<dim3(g.slabs, g.chunks), 256, 0, c->stream>>>(
-          dz + m * cp, dy, y + m * cp, f(op.s_keep), f(op.s_keep) + cp, f(op.s_mean), f(op.s_invstd), f(op.s_k2), f(op.s_k3), n, (int)cp, op.d.act, g);
+      const long nvec = n * cp / 8;
+      bn_bwd_form_kernel<<<grid_for(nvec), 256, 0, c->stream>>>(dz + m * cp, y + m * cp, dy, nvec, (int)cp / 8, terms);
       e = hipGetLastError();
       if (e == hipSuccess) e = hipMemcpyAsync(h16.data() + m * cp, dy, (size_t)n * cp * 2, hipMemcpyDeviceToHost, c->stream);
     }

@@ -40,7 +40,7 @@ __global__ __launch_bounds__(kPwThreads, 2) void pw_bwd_kernel(const bf16_t* __r
   constexpr int D = NC > 4 ? 3 : NC;                 // chunks in flight (divides NC: a chunk's registers are known at compile time)
   constexpr int CP = NC * 32, WP = CP + 8;            // row of the transposed filter in LDS: no conflicts
   __shared__ __attribute__((aligned(16))) bf16_t wt[32 * WP];
-  __shared__ __attribute__((aligned(16))) float cf[5 * CP];                         // mu, a, b, p, q:  dy = a dpre + (p (y - mu) + q)
+  __shared__ __attribute__((aligned(16))) float cf[5 * CP];                         // mu, a, b, p, q of bn_bwd_terms
   __shared__ __attribute__((aligned(16))) bf16_t tile_s[kPwWaves * 2 * kPwPix * kPwPitch];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   bf16_t* const ds = tile_s + wave * 2 * kPwPix * kPwPitch;                         // dy: 32 pixels x 32 channels
@@ -48,13 +48,8 @@ __global__ __launch_bounds__(kPwThreads, 2) void pw_bwd_kernel(const bf16_t* __r
   static_assert(kPwWaves * 2 * kPwPix * kPwPitch * 2 >= kPwWaves * 1024 * 4, "the waves' 32 x 32 sums fit where the tiles were");
 
   for (int i = tid; i < CP; i += kPwThreads) {
-    const bool in = i < g.C;
-    const float is = in ? f.invstd[i] : 0.f, a = in ? f.gamma[i] * is : 0.f;
-    cf[i] = in ? f.mean[i] : 0.f;
-    cf[CP + i] = a;
-    cf[2 * CP + i] = in ? f.beta[i] : 0.f;
-    cf[3 * CP + i] = in ? -(a * is * f.k3[i]) : 0.f;
-    cf[4 * CP + i] = in ? -(a * f.k2[i]) : 0.f;
+    const BnBwdTerms t = i < g.C ? bn_bwd_terms(f, i) : BnBwdTerms{};
+    cf[i] = t.mu; cf[CP + i] = t.a; cf[2 * CP + i] = t.b; cf[3 * CP + i] = t.p; cf[4 * CP + i] = t.q;
   }
   for (int i = tid; i < 4 * CP; i += kPwThreads) {    // 8 inputs of an output channel at a time
     const int c = i >> 2, ci = (i & 3) * 8;
@@ -149,7 +144,7 @@ __global__ __launch_bounds__(kPwThreads, 2) void pw_bwd_kernel(const bf16_t* __r
           const unsigned dw = dw_word(zq[slot][i], h), yw = dw_word(yq[slot][i], h);
           const float y0 = bf_lo(yw) - mu.x, y1 = bf_hi(yw) - mu.y;
           const float d0 = dw_pass(fmaf(y0, a.x, b.x), bf_lo(dw), limit), d1 = dw_pass(fmaf(y1, a.y, b.y), bf_hi(dw), limit);
-          const unsigned v = pack_bf2(fmaf(a.x, d0, fmaf(fp.x, y0, fq.x)), fmaf(a.y, d1, fmaf(fp.y, y1, fq.y))) & (i ? in1 : in0);
+          const unsigned v = pack_bf2(bn_bwd_dy(y0, d0, a.x, fp.x, fq.x), bn_bwd_dy(y1, d1, a.y, fp.y, fq.y)) & (i ? in1 : in0);
           if (h == 0) o[i].x = v; else if (h == 1) o[i].y = v; else if (h == 2) o[i].z = v; else o[i].w = v;
         }
       }

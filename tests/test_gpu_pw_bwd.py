@@ -63,6 +63,32 @@ def test_expand_layer(n, h, w, c_in, c, act, k, stride, first):
     np.testing.assert_array_equal(d.read_grad_value(0, v), d.read_grad_value(0, v))
 
 
+@pytest.mark.parametrize("c,act", [(96, W.ACT_RELU6), (144, W.ACT_RELU), (40, W.ACT_NONE)])
+@pytest.mark.parametrize("last", [False, True])
+def test_the_gradient_read_is_the_one_the_kernel_used(c, act, last):
+    """A filter that copies 16 of the outputs' channels' gradients to the inputs (one weight of one a row and column): backward-data then
+    hands out the gradient of the convolution output as the kernel formed it, every bit.  The value in front is a max-pool's, whose
+    gradient is kept as it arrives."""
+    n, c_in = 16, 16
+    t, b = W.Block(), W.Block()
+    t.cba(0, 16, 3, 2, act=W.ACT_NONE)
+    e = b.cba(b.pool(0, 2, 2), c, 1, act=act)
+    b.cba(e, 16, 1, act=W.ACT_NONE)
+    wl = W.Workload("pw_bwd", n, (c_in, 64, 64), [t], [b], "bf16", lr=0.05)
+    first = c - c_in if last else 0
+    w = np.zeros((c, c_in, 1, 1), dtype=np.float32)
+    w[first:first + c_in, :, 0, 0] = np.eye(c_in)
+    d = parity.make_distiller(wl, n, "bf16")
+    d.load_param(W.NET_STUDENT, 0, e - 1, W.P_WEIGHT, w)
+    d.teacher_relay(torch.from_numpy(W.make_input(wl, batch=n)).cuda())
+    d.set_profile(True)
+    d.student_step(1, wl.lr)
+    assert "pw_bwd_bn" in {p["name"] for p in d.get_profile()}
+    dy = d.read_grad_value(0, e)[:, first:first + c_in]
+    assert np.count_nonzero(dy) > dy.size // 2
+    np.testing.assert_array_equal(d.read_grad_value(0, e - 1), dy)
+
+
 def test_reading_a_gradient_waits_for_the_bound_stream_alone():
     """read_grad_value of an expand layer and of a depthwise one, whose gradient is formed on request, while another stream (the legacy
     default one) is busy for some hundred times as long as the read takes."""
