@@ -552,6 +552,7 @@ bool stem_s2d(const pbd_ctx* c, int block, const OpPlan& op) {
 }
 int depthwise_reader(const pbd_ctx* c, const BlockPlan& bp, int j);
 bool dw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j);
+bool expands(const pbd_ctx* c, const OpPlan& op);
 bool pw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j);
 bool pj_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j);
 inline int pw_blocks(long M) { return (int)std::min<long>(256, ((M + kPwPix - 1) / kPwPix + kPwWaves - 1) / kPwWaves); }
@@ -774,6 +775,7 @@ int plan(pbd_ctx* c) {
           // per-row-tile batch-norm sums from the convolution's store (64-row tiles at least), and their regrouping where they are many
           const long stat_tiles = (M + 63) / 64;
           need_red((size_t)(stat_tiles + (stat_tiles > kStatGroupsMax ? kStatGroupsMax : 0) + 1) * 2 * op.cout_p * 4);
+          if (expands(c, op)) need_red((size_t)pw_fwd_args(M, op.cin_p, op.d.c_out).pblocks * 3 * op.cout_p * 4);
           const long Min = (long)c->o.batch * op.in.h * op.in.w;
           need_split(M, op.d.c_out, op.d.k * op.d.k * op.cin_p, op.cin_p);
           if (op.s2d) need_split(M, op.d.c_out, kS2dK, 16);
@@ -1192,8 +1194,8 @@ template <class T> struct Exec {
     return (int)((M + cfg.BM - 1) / cfg.BM);
   }
   // res (optional): a residual join fused into the store, y = res_act(conv result + res); only where
-  // fuses_residual(op) holds.  stats (optional): per row tile sums of y and y^2, where fused_stats_tiles(op) > 0 (an expand layer: of
-  // y - y0 and its square, y0 the first pixel's)
+  // fuses_residual(op) holds.  stats (optional): per row tile sums of y and y^2, where fused_stats_tiles(op) > 0 (an expand layer: a
+  // mean, a sum of squares about it and a count per workgroup)
   void conv_fwd(const OpPlan& op, const T* x, const T* w, T* y, const float* a, const float* b, int act,
                 const T* res = nullptr, int res_act = 0, float* stats = nullptr, NormFold fold = NormFold{}) {
     const int N = c->o.batch;
@@ -1957,19 +1959,21 @@ template <class T> struct Exec {
           const float* part = red();
           const T* pivot = y;                       // the pass of its own shifts by the first row
           int chunks = stat_tiles;
-          if (stat_tiles) {
-            // the convolution's store left one pair of sums per row tile (an expand layer's shifted likewise, else no pivot); thousands of them are
+          const bool groups = dw_rows || expands(c, op);   // a mean, a sum of squares and a count each
+          if (groups) {
+            pivot = nullptr;
+            if (dw_rows) chunks = dw_rows;
+          } else if (stat_tiles) {
+            // the convolution's store left one pair of sums per row tile (no pivot); thousands of them are
             // first summed in groups so that the finalize kernel's walk stays short
-            if (!expands(c, op)) pivot = nullptr;
+            pivot = nullptr;
             if (chunks > kStatGroupsMax) {
               const int per = (chunks + kStatGroupsMax - 1) / kStatGroupsMax, n = 2 * op.cout_p;
               float* out = red() + (size_t)chunks * n;
-              const int groups = (chunks + per - 1) / per;
-              launch(c, regroup_partials_kernel, dim3((n + 255) / 256, groups), 256, 0, st, part, out, chunks, n, per);
-              part = out; chunks = groups;
+              const int sums = (chunks + per - 1) / per;
+              launch(c, regroup_partials_kernel, dim3((n + 255) / 256, sums), 256, 0, st, part, out, chunks, n, per);
+              part = out; chunks = sums;
             }
-          } else if (dw_rows) {
-            chunks = dw_rows;
           } else {
             const ColGrid g = bn_stats_grid(M, op.cout_p);
             ProfScope ps(c, streams(op.out) ? "bn_stats_nt" : "bn_stats", bytes_of(op.out), 0, net, blk, opi);
@@ -1977,8 +1981,7 @@ template <class T> struct Exec {
                    256 * 16 * sizeof(float), st, y, red(), M, op.cout_p, g);
             chunks = g.chunks;
           }
-          if (dw_rows) pivot = nullptr;
-          launch(c, dw_rows ? bn_finalize_kernel<T, true> : bn_finalize_kernel<T>, op.cout_p / kFinalizeChannels, 256, 0, st, 
+          launch(c, groups ? bn_finalize_kernel<T, true> : bn_finalize_kernel<T>, op.cout_p / kFinalizeChannels, 256, 0, st, 
               part, pivot, chunks, op.cout_p, (double)M, wsf(op.s_mean), wsf(op.s_invstd), wsf(op.s_rmean),
               wsf(op.s_rvar), c->o.bn_eps, c->o.bn_momentum, master + op.e_gamma, master + op.e_beta,
               folds_into((int)j + 1) || dw_bwd_fused(c, bp, (int)j) || pw_bwd_fused(c, bp, (int)j) ? wsf(op.s_keep) : (float*)nullptr);

@@ -400,8 +400,10 @@ __global__ __launch_bounds__(kPjThreads, 2) void pj_bwd_kernel(const bf16_t* __r
 // What bounds it: memory, the writes of y.  The implicit GEMM walks through such a layer as load, one reduction step, staged store, one after the
 // other, its tiles two or three a compute unit; here a workgroup keeps its 64 channels' filter in registers and walks the pixels, a wave works
 // alone on 32 of them, its store (whole cache lines, through LDS rows of its own) beside the next tile's products.
-// AFFINE (the teacher): the folded batch norm and the rectifier on the way out.  Else: sums of y - y0 and its square over the pixels, y0 the
-// first pixel's output (as stored), one pair a workgroup and channel.
+// AFFINE (the teacher): the folded batch norm and the rectifier on the way out.  Else the batch norm's statistics of y as stored: a mean, a sum
+// of squares about it and a count for each workgroup and channel, as bn_finalize_kernel<T, true> merges them.  A workgroup sums y - y0 and its
+// square, y0 the output at its own first pixel: a pixel far from the others costs the precision of its own workgroup's share (M pixels with
+// one of them as everybody's y0, on blank images, M times a rounding error of the variance).
 //
 // Measured against igemm_kernel (2.2 to 2.8 TB/s on these layers), same machine, alternating: supernet step 28.96 -> 28.33 ms, search step
 // 16.71 -> 16.30, MobileNetV2 21.75 -> 21.35 ms for four batches, 1.762 -> 1.737 at batch 33.
@@ -475,8 +477,8 @@ __device__ __forceinline__ void pw_fwd_block(const Blk& blk, const bf16_t* __res
 
   uint4 xq[2][2];
   float y0[8], s1[8], s2[8];
-  if constexpr (!AFFINE) {                            // the first pixel's outputs, in every row
-    load(xq[0], 0, true);
+  if constexpr (!AFFINE) {                            // the outputs at the workgroup's first pixel, in every row
+    load(xq[0], pb * kPwfWaves * kPwPix, true);
     product(xq[0]);
     __builtin_amdgcn_wave_barrier();
     IO<bf16_t>::unpack(*reinterpret_cast<const uint4*>(ys + lcol), y0);
@@ -527,12 +529,23 @@ __device__ __forceinline__ void pw_fwd_block(const Blk& blk, const bf16_t* __res
     float* const sums = reinterpret_cast<float*>(tile_s);
     __syncthreads();
     wave_channel_sums(s1, s2, sums + wave * 128, lane);
-    __syncthreads();
-    if (tid < 128 && c0 + (tid & 63) < g.C) {
-      float s = sums[tid];
+    if (tid < 8) {
 #pragma unroll
-      for (int k = 1; k < kPwfWaves; ++k) s += sums[k * 128 + tid];
-      spart[(size_t)pb * 2 * g.C + (tid >> 6) * g.C + c0 + (tid & 63)] = s;
+      for (int e = 0; e < 8; ++e) sums[kPwfWaves * 128 + tid * 8 + e] = y0[e];
+    }
+    __syncthreads();
+    if (tid < 64 && c0 + tid < g.C) {
+      float a = sums[tid], b = sums[64 + tid];
+#pragma unroll
+      for (int k = 1; k < kPwfWaves; ++k) { a += sums[k * 128 + tid]; b += sums[k * 128 + 64 + tid]; }
+      // the workgroup's tiles (tile t is that of workgroup t / waves mod pblocks), the last of all perhaps not full
+      const int own = g.tiles / stride * kPwfWaves + min(max(g.tiles % stride - pb * kPwfWaves, 0), kPwfWaves);
+      const int missing = (g.tiles - 1) / kPwfWaves % g.pblocks == pb ? g.tiles * kPwPix - g.M : 0;
+      const float n = (float)(own * kPwPix - missing), shift = a / n;
+      float* const out = spart + (size_t)pb * 3 * g.C + c0 + tid;
+      out[0] = sums[kPwfWaves * 128 + tid] + shift;
+      out[g.C] = fmaxf(b - a * shift, 0.f);
+      out[2 * g.C] = n;
     }
   }
 }
