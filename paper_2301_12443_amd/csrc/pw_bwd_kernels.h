@@ -30,6 +30,13 @@ struct PwBwdArgs {
   unsigned y_bytes, x_bytes, dx_bytes;   // dx_bytes 0: no dx (the layer reads the block's input)
 };
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+// Between a wave's accesses to LDS rows of its own that its lanes exchange data through.  The hardware carries out a wave's LDS accesses in
+// order; the fence keeps the compiler from changing that order and costs no instruction.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
 
 // NC: chunks of 32 output channels.  WGRAD false: the architecture round.
 // (No branch in the loop: loads and stores that a launch or a lane has no use for go out of range, which keeps the number of loads in flight
@@ -114,7 +121,7 @@ __global__ __launch_bounds__(kPwThreads, 2) void pw_bwd_kernel(const bf16_t* __r
 #pragma unroll
       for (int i = 0; i < 2; ++i) *reinterpret_cast<uint4*>(xs + (lrow + 16 * i) * kPwPitch + lcol) = xq[i];
       load_x(t + stride);
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_fence();
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) xf[ks] = lds_read_tr8(xs + tr_frag + ks * 16 * kPwPitch, kPwPitch);
     }
@@ -152,7 +159,7 @@ __global__ __launch_bounds__(kPwThreads, 2) void pw_bwd_kernel(const bf16_t* __r
       for (int i = 0; i < 2; ++i) *reinterpret_cast<uint4*>(ds + (lrow + 16 * i) * kPwPitch + lcol) = o[i];
       load(slot, kc + kD < NC ? t : t + stride, (kc + kD) % NC);
       __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_wave_barrier();                // (a wave's LDS accesses are carried out in order)
+      wave_lds_fence();
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         const bf16x8 df = *reinterpret_cast<const bf16x8*>(ds + row_frag + ks * 16);
@@ -164,7 +171,7 @@ __global__ __launch_bounds__(kPwThreads, 2) void pw_bwd_kernel(const bf16_t* __r
         for (int ks = 0; ks < 2; ++ks)
           acc[kc] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_read_tr8(ds + tr_frag + ks * 16 * kPwPitch, kPwPitch), xf[ks], acc[kc], 0, 0, 0);
       }
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_fence();
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -323,7 +330,7 @@ __device__ __forceinline__ void pj_bwd_block(const Blk& blk, const bf16_t* __res
       }
       load_dy(slot, tt + 2 * stride);
       __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_wave_barrier();                // (a wave's LDS accesses are carried out in order)
+      wave_lds_fence();
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         uint4* const at = reinterpret_cast<uint4*>(zs + (lrow + 8 * i) * kPjPitch + lcol);
@@ -346,7 +353,7 @@ __device__ __forceinline__ void pj_bwd_block(const Blk& blk, const bf16_t* __res
       }
       load_y(slot, tt + 2 * stride);
       __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_fence();
       if constexpr (WGRAD) {
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
@@ -355,7 +362,7 @@ __device__ __forceinline__ void pj_bwd_block(const Blk& blk, const bf16_t* __res
           for (int i = 0; i < 2; ++i)
             acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(df, lds_read_tr8(zs + (tr_row + ks * 16) * kPjPitch + i * 32 + tr_col, kPjPitch), acc[i], 0, 0, 0);
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_fence();
       }
     }
   }
@@ -480,9 +487,9 @@ __device__ __forceinline__ void pw_fwd_block(const Blk& blk, const bf16_t* __res
   if constexpr (!AFFINE) {                            // the outputs at the workgroup's first pixel, in every row
     load(xq[0], pb * kPwfWaves * kPwPix, true);
     product(xq[0]);
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_fence();
     IO<bf16_t>::unpack(*reinterpret_cast<const uint4*>(ys + lcol), y0);
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_fence();
 #pragma unroll
     for (int e = 0; e < 8; ++e) s1[e] = s2[e] = 0.f;
   }
@@ -501,7 +508,7 @@ __device__ __forceinline__ void pw_fwd_block(const Blk& blk, const bf16_t* __res
       product(xq[slot]);
       load_tile(xq[slot], tt + 2 * stride);
       __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_wave_barrier();                // (a wave's LDS accesses are carried out in order)
+      wave_lds_fence();
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const uint4 v = *reinterpret_cast<const uint4*>(ys + (lrow + 8 * i) * kPjPitch + lcol);
@@ -522,7 +529,7 @@ __device__ __forceinline__ void pw_fwd_block(const Blk& blk, const bf16_t* __res
           }
         }
       }
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_fence();
     }
   }
   if constexpr (!AFFINE) {
