@@ -1,7 +1,9 @@
 """The candidates of a mixed layer go out together, launches of one kernel in one grid (many_kernel): the same kernels with the same
 arguments as one candidate after the other, so every bit is the same.  pbd_student_step_static, whose scratch has no room for several
 candidates at a time, is the one-by-one form.  Kernels that only some candidates use, several mixed layers on top of each other, chains of
-one to three layers, a candidate that is the input itself, and sizes on every path of the batch norms."""
+one to three layers, a candidate that is the input itself, and sizes on every path of the batch norms and of the kernels that take an
+expand or projection layer whole (their weight-gradient sums lie in the lane's scratch, and the candidates' gradients of the shared input are
+added in order)."""
 import numpy as np
 import pytest
 import torch
@@ -26,6 +28,8 @@ CASES = [
     (70, 9, 8, 1, [(5, 3), (3, 3), (5, 5)], "dense"),                                     # a dense 3 x 3, a single 1 x 1
     (20, 16, 16, 1, [(3, 3), (5, 3)], "identity"),
     (7, 28, 28, 1, [(3, 6), (5, 6), (7, 6), (3, 3), (5, 3), (7, 3), (3, 2), (5, 2)], "none"),   # as many as one launch takes
+    (17, 31, 32, 1, [(3, 3), (5, 6), (7, 3), (3, 6), (5, 3), (7, 6)], "none"),            # expand and projection layers in kernels of their own
+    (72, 31, 33, 2, [(3, 6), (5, 3), (7, 6)], "identity"),                                # ... behind a stride-2 layer, and beside the input itself
 ]
 
 
@@ -65,3 +69,7 @@ def test_candidates_together_and_one_by_one(n, h, w, stride, candidates, more):
     a.set_profile(False)
     # the six 1 x 1 layers in front and behind alone would be two launches a candidate and mixed layer
     assert sum(p["name"].startswith("igemm_fwd") for p in entries) < 2 * 2 * len(candidates)
+    if n * h * w >= 16384:
+        names = [p["name"] for p in entries]
+        assert {"pw_fwd_store", "pw_bwd_bn", "pj_bwd_bn"} <= set(names), names
+        assert names.count("pw_bwd_bn") >= len(candidates) > names.count("pw_fwd_store")      # one after the other, and together
