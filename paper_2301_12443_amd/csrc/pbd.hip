@@ -81,7 +81,7 @@ struct OpPlan {
   // student: element offsets in the block's flat arena; byte offsets for statistics
   size_t e_w = 0, e_gamma = 0, e_beta = 0;
   size_t s_rmean = 0, s_rvar = 0, s_mean = 0, s_invstd = 0, s_k2 = 0, s_k3 = 0;
-  size_t s_keep = 0;        // gamma and beta of the last step, where the normalised output is not written (depthwise_reader)
+  size_t s_keep = 0;        // gamma and beta of the last step, where the normalised output or the gradient dy is not written
   long e_wt = -1;           // element offset in the block's transposed-weight arena
   long e_part = -1;         // element offset of the weight gradient's partial sums among the block's deferred ones (-1: summed at once)
   // scratch byte offsets
@@ -1051,8 +1051,6 @@ int depthwise_reader(const pbd_ctx* c, const BlockPlan& bp, int j) {
          dw_wgrad_on_mfma(true, N, q.out.h, q.out.w, q.cout_p, q.d.k, q.d.stride, q.d.pad) ? reader : -1;
 }
 
-// The backward pass of student layer j in one kernel: a depthwise layer that normalises the layer in front as it stages it
-// (depthwise_reader) and whose own gradient arrives as a tensor (no residual add rides in its batch norm).
 // For student layer j: the index of a dense 1 x 1 layer with at most 32 outputs that is the only reader of j's output (it then normalises
 // and rectifies j's convolution output as it stages it, forward and in its weight gradient, and the normalised tensor is not written),
 // else -1.  MobileNetV2's and the supernet's depthwise layers on the large images: supernet step at batch 64 34.06 -> 32.82 ms (its
@@ -1078,14 +1076,24 @@ int dense_reader(const pbd_ctx* c, const BlockPlan& bp, int j) {
   return cfg.splits == 1 && cfg.BN == 32 ? reader : -1;
 }
 
+// The backward pass of student layer j in one kernel: a depthwise layer that normalises the layer in front as it stages it
+// (depthwise_reader) and whose own gradient arrives as a tensor (no residual add rides in its batch norm).
 bool dw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j) {
   const OpPlan& op = bp.ops[j];
   return op.d.type == OP_CBA && op.dw && op.d.in[0] > 0 && depthwise_reader(c, bp, op.d.in[0] - 1) == j && residual_reader(bp, j) < 0;
 }
 
-// The same for an expand layer (pw_bwd_kernel).  From kPwMinPixels pixels on: at 16464 pixels, 32 -> 128 (MobileNetV2's third block, 21 images)
-// 11 to 13 us against 16 to 19 for the three separate launches, at 32928 12 against 16; below, a wave has a single tile of 32 pixels or
-// none and both sides are launches on tensors that lie in L2.  (pw_fwd_kernel there: 6.0 us against 6.1 to 6.8, 7.3 against 6.7 to 7.5.)
+// The same for an expand layer (pw_bwd_kernel, and pw_fwd_kernel forward), from kPwMinPixels pixels on.  Kernel times in us of a layer by
+// itself, pw_bwd_kernel / apply, weight gradient and backward-data, then pw_fwd_kernel / implicit GEMM:
+//   pixels        4704          6272          8624          12544         16464         32928        forward: 4704, 12544, 16464, 32928
+//   32 ->  96   8.5 / 13.0    8.5 / 13.3    8.5 / 13.6    8.8 / 14.4    8.8 / 15.8    9.6 / 17.6     5.1 / 5.2   5.7 / 6.1   6.3 / 6.6    8.4 / 8.2
+//   32 -> 192  12.4 / 14.9   12.4 / 15.1   12.6 / 15.7   13.0 / 15.7   13.5 / 17.4   14.4 / 21.7     5.7 / 6.0   7.3 / 7.2   8.2 / 7.7   10.2 / 9.1
+//   24 -> 144  12.2 / 13.8   12.3 / 14.5   12.3 / 14.3   12.5 / 16.0   13.0 / 16.2   14.1 / 19.5     5.6 / 5.6   6.6 / 6.9   7.6 / 7.4   10.3 / 8.9
+// Backward the kernel is ahead on both sides of the line and forward the two are level; what lies between decides little: with this line and
+// kPjMinPixels at 4096 the supernet's search step at batch 16 (layers of 12544 pixels) takes 16.11 instead of 16.20 ms, and every other
+// network's step is within 0.2 %, also with the forward line alone at 4096 or 65536.  (The candidates of a mixed layer run pw_bwd_kernel one after
+// the other, the separate passes together.)  Far above the line it decides: without pw_fwd_kernel supernet 28.4 -> 29.0 ms, search step
+// 16.2 -> 16.6, MobileNetV2 21.3 -> 21.7 ms for four batches.
 constexpr long kPwMinPixels = 16384;
 bool expands(const pbd_ctx* c, const OpPlan& op) {
   return c->o.precision == PBD_BF16 && !c->o.force_direct && op.d.type == OP_CBA && !op.dw && op.d.k == 1 && op.d.stride == 1 && op.d.pad == 0 &&
@@ -1098,8 +1106,13 @@ bool pw_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j) {
 }
 
 // Backward-data and the weight gradient of a projection that normalises the layer in front itself (dense_reader), with the sums of that
-// layer's batch norm, in one kernel (pj_bwd_kernel).  From kPjMinPixels pixels on, as above: at 16464 pixels, 128 -> 32, 12 to 17 us against 17 to
-// 28 for three launches, at 32928 13.5 against 17.7.
+// layer's batch norm, in one kernel (pj_bwd_kernel), from kPjMinPixels pixels on.  In us, against the weight gradient, backward-data and the
+// reduction of the batch norm in front:
+//   pixels        4704          8624          12544         16464         32928
+//    96 -> 32   8.9 / 14.6    9.0 / 15.7    9.1 / 16.0   12.2 / 17.4   14.0 / 20.3
+//   192 -> 32   9.2 / 15.9    9.6 / 17.7   13.2 / 18.5   13.8 / 20.2   14.6 / 25.8
+//   144 -> 24   8.8 / 15.0    9.1 / 16.9   12.2 / 17.8   13.3 / 18.5   14.3 / 23.3
+// Ahead on both sides of the line too; for what the line is worth see kPwMinPixels.
 constexpr long kPjMinPixels = 16384;
 bool pj_bwd_fused(const pbd_ctx* c, const BlockPlan& bp, int j) {
   const OpPlan& op = bp.ops[j];
@@ -2063,7 +2076,7 @@ template <class T> struct Exec {
     // gradient, masks it and stores the result once, where the add's other input collects its gradient.
     struct AddBwd { const T* dz; const T* z; int act; T* dstore; bool loss; };
     std::vector<AddBwd> add_bwd(bp.ops.size(), AddBwd{nullptr, nullptr, 0, nullptr, false});
-    std::vector<char> summed(bp.ops.size(), 0);     // layers whose batch-norm sums the backward pass of their depthwise reader took
+    std::vector<char> summed(bp.ops.size(), 0);     // layers whose batch-norm sums the backward pass of their reader took (dw_bwd, pj_bwd)
     for (int j = (int)bp.ops.size() - 1; j >= 0; --j) {
       const OpPlan& op = bp.ops[j];
       opi = j;
