@@ -16,10 +16,17 @@
 //    swz(r) = (r >> 1) & 7 for 128-byte rows and (r >> 2) & 3 for 64-byte rows: the 16 lanes that one
 //    ds_read_b128 cycle serves (16 consecutive rows, one chunk index) then hit 16 different 16-byte bank groups.
 //    An out-of-range lane (padding, ragged tile) gets the descriptor's zeros written.
-//  * A ring of NS stages with ONE barrier per reduction step: at step kt a wave waits for its own loads of
-//    stage kt (s_waitcnt vmcnt), passes the barrier (now every wave's part of stage kt is in LDS, and every
-//    wave has finished reading stage kt-1), issues the loads of stage kt+NS-1 into the buffer of stage kt-1,
-//    and multiplies stage kt.
+//  * A ring of NS stages with ONE barrier per reduction step, ahead of the step's last sub-step, whose fragments are in registers by
+//    then: a wave waits for its own loads of stage kt+1 (s_waitcnt vmcnt), passes the barrier (now every wave's part of stage kt+1 is
+//    in LDS, and every wave has read stage kt), requests the first fragments of stage kt+1 and issues the last products of
+//    stage kt with the loads of stage kt+NS, into the buffer of stage kt, one behind each product.  So the matrix cores have work
+//    while the fragments and the loads are on their way.
+//  * A load costs two vector operations: a row's offset is fixed, the tap's is a scalar, and whether the tap lies in the image is a
+//    bit of a mask that is set up once per tile.  Forming and testing the coordinates for every load, all of them at the head of the
+//    step, kept the matrix cores waiting for ~430 of a step's ~4300 cycles in each of a SIMD's two waves.  Before and after (both points), same
+//    bits, us: 384 -> 384, 3 x 3, 50176 pixels 165 -> 144 (805 -> 925 TFLOP/s), 768 -> 768, 12544 180 -> 159, 192 -> 192, 200704
+//    163 -> 147, 256 -> 256, 200704 257 -> 240; 1024 -> 384, 1 x 1 62 -> 56; memory-bound 1 x 1 layers as before.  Raised wave
+//    priority around the products and four or five stages of the 32-wide step gave nothing.
 //  * Fragment reads are ds_read_b128 in inline assembly with their own s_waitcnt lgkmcnt: the compiler
 //    would otherwise order every LDS read behind ALL outstanding direct-to-LDS loads (it cannot tell the
 //    stages apart) and the prefetch would be lost.  Fragments of sub-step ks+1 are requested before the
@@ -35,6 +42,8 @@
 //    64-element tap, and each 16-byte chunk is range-tested against the pixel it belongs to.
 // Needs CA % BK == 0 (a reduction step lies inside one filter tap: taps are uniform over the block).
 #pragma once
+#include <type_traits>
+
 #include "conv_kernels.h"
 
 
@@ -42,9 +51,9 @@ namespace pbd {
 
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
-__device__ __forceinline__ void dma_load16(__amdgpu_buffer_rsrc_t r, unsigned char* lds_wave_base, unsigned byte_off) {
-  // lane l's 16 bytes land at lds_wave_base + 16 l (the base must be uniform over the wavefront)
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_ptr)lds_wave_base, 16, (int)byte_off, 0, 0, 0);
+__device__ __forceinline__ void dma_load16(__amdgpu_buffer_rsrc_t r, unsigned char* lds_wave_base, unsigned byte_off, unsigned uniform_off = 0) {
+  // lane l's 16 bytes land at lds_wave_base + 16 l (the base and uniform_off must be uniform over the wavefront)
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_ptr)lds_wave_base, 16, (int)byte_off, (int)uniform_off, 0, 0);
 }
 
 // Wait until at most N of this wave's vector-memory operations are outstanding.  The "memory" clobbers keep
@@ -89,6 +98,8 @@ __device__ __forceinline__ void wait_vmcnt_dyn(int n) {
   }
 }
 
+constexpr unsigned kDmaSkip = 0xC0000000u;   // an offset that is out of range, also with a scalar offset of up to 1 GiB added
+constexpr int kDmaMaxTaps = 32;              // bits of a row's tap mask
 constexpr int kDmaThreads = 512;
 constexpr int kDmaBM = 256;      // rows of a big tile
 constexpr int kDmaTailBM = 64;   // rows of a tail tile
@@ -130,7 +141,7 @@ __device__ __forceinline__ void dma_tile(unsigned char* smem, float* ep_s, const
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // uniform, and known to the compiler as such
   const int wm = wave / WAVES_N_MAX, wn = wave % WAVES_N_MAX;
-  const bool active = wn < WAVES_N;
+  const bool active = WAVES_N == WAVES_N_MAX || wn < WAVES_N;
   const int sh = g.stride == 2 ? 1 : 0, smask = g.stride - 1;
   const bool par = MODE == 1 && cls >= 0;
   const int ph = par ? cls >> 1 : 0, pw = par ? cls & 1 : 0;
@@ -150,12 +161,20 @@ __device__ __forceinline__ void dma_tile(unsigned char* smem, float* ep_s, const
   // slot = lane % CPR is where the chunk lands in its row; the global chunk it fetches is slot ^ swz(row)
   const int lrow = lane / CPR, slot = lane % CPR;
   auto swz = [](int row) { return BK == 64 ? (row >> 1) & 7 : (row >> 2) & 3; };
-  unsigned abase[A_INSTR];
-  int rh[A_INSTR], rw[A_INSTR], kc8[A_INSTR];
+  // A lane's address is its row's, a_off, plus what the tap and channel add, which is the same for the whole block and rides in the
+  // load's scalar offset (never negative: the descriptor begins `before` elements ahead of the tensor).  Whether the tap lies in the image is
+  // a bit of `skip`, set up once per tile: two vector operations a load where forming and testing the coordinates took about ten, which the
+  // matrix cores waited for at the head of every step.
+  unsigned a_off[A_INSTR], skip[A_INSTR];
   // elements between neighbouring pixels of A: the channel count, except for a tap that spans several pixels
   // (g.pix_shift > 0: CA = a run of CA >> pix_shift-wide pixels, each range-tested on its own)
   const int pitch = MODE == 0 && g.pix_shift ? g.CA >> g.pix_shift : g.CA;
-  const int pshift = MODE == 0 && g.pix_shift ? 31 - __builtin_clz(pitch) : 31;     // (x >> 31 = 0: one pixel per tap)
+  const bool runs = MODE == 0 && g.pix_shift != 0;
+  const int pshift = runs ? 31 - __builtin_clz(pitch) : 0;
+  const int row_bits = runs ? g.CA / BK : g.S;   // a run is tested step by step, S = 1
+  const int before = MODE == 0 ? g.pad * (g.WA + 1) * pitch : ((g.R - 1) * g.WA + g.S - 1) * g.CA >> sh;
+  const unsigned hlim = MODE == 0 ? (unsigned)g.HA : (unsigned)g.HA << sh;
+  const unsigned wlim = MODE == 0 ? (unsigned)g.WA : (unsigned)g.WA << sh;
   int a_cnt = 0, b_cnt = 0;                      // loads this WAVE issues per stage (uniform)
 #pragma unroll
   for (int i = 0; i < A_INSTR; ++i) {
@@ -170,12 +189,19 @@ __device__ __forceinline__ void dma_tile(unsigned char* smem, float* ep_s, const
     const int nbase = (t / HOr) * g.HA * g.WA;
     const int h0 = MODE == 0 ? a_ * g.stride - g.pad : (par ? 2 * a_ + ph : a_) + g.pad;
     const int w0 = MODE == 0 ? b_ * g.stride - g.pad : (par ? 2 * b_ + pw : b_) + g.pad;
-    const int kc = slot ^ swz(row);
-    kc8[i] = kc * 8;
-    if (MODE == 0) abase[i] = (unsigned)(((nbase + h0 * g.WA + w0) * pitch + kc * 8) * 2);
-    else abase[i] = (unsigned)((nbase * g.CA + ((h0 * g.WA + w0) * g.CA >> sh) + kc * 8) * 2);
-    rh[i] = valid ? h0 : -(1 << 24);             // rows past the end fail every range test
-    rw[i] = w0;
+    const int kc8 = (slot ^ swz(row)) * 8;
+    if (MODE == 0) a_off[i] = (unsigned)(((nbase + h0 * g.WA + w0) * pitch + kc8 + before) * 2);
+    else a_off[i] = (unsigned)((nbase * g.CA + ((h0 * g.WA + w0) * g.CA >> sh) + kc8) * 2);
+    unsigned cols = 0, take = 0;
+    for (int j = 0; j < row_bits; ++j) {
+      const int w = MODE == 1 ? w0 - j : runs ? w0 + ((j * BK + kc8) >> pshift) : w0 + j;
+      cols |= ((unsigned)w < wlim && (MODE == 0 || (w & smask) == 0) ? 1u : 0u) << j;
+    }
+    for (int j = 0; j < g.R; ++j) {
+      const int h = MODE == 0 ? h0 + j : h0 - j;
+      take |= ((unsigned)h < hlim && (MODE == 0 || (h & smask) == 0) ? cols : 0u) << (j * row_bits);
+    }
+    skip[i] = valid ? ~take : ~0u;
   }
   unsigned bbase[B_INSTR];
 #pragma unroll
@@ -183,44 +209,51 @@ __device__ __forceinline__ void dma_tile(unsigned char* smem, float* ep_s, const
     if ((i * 8 + wave) * 64 < B_CHUNKS) ++b_cnt;
     const int row = (i * 8 + wave) * RPI + lrow;
     const int kc = slot ^ swz(row);
-    bbase[i] = row < BN && n0 + row < g.NC ? (unsigned)((n0 + row) * g.Kred + kc * 8) * 2u : kOutOfRange;
+    bbase[i] = row < BN && n0 + row < g.NC ? (unsigned)((n0 + row) * g.Kred + kc * 8) * 2u : kDmaSkip;
   }
   const int lps = a_cnt + b_cnt;
   constexpr int LPS_MAX = A_INSTR + B_INSTR;
-  const __amdgpu_buffer_rsrc_t a_rsrc = tensor_rsrc(A, g.a_bytes), b_rsrc = tensor_rsrc(Bw, g.b_bytes);
+  const __amdgpu_buffer_rsrc_t a_rsrc = tensor_rsrc(A - before, g.a_bytes + (unsigned)before * 2u), b_rsrc = tensor_rsrc(Bw, g.b_bytes);
 
   // reduction position of the next stage to be loaded: kk = (r*S + s)*CA + c, uniform over the block
   int r = r0, s = s0, c = 0;
-  auto issue_stage = [&](int stage) {
-    unsigned char* sa = smem + stage * STAGE + wave * 1024;
-    const int tap = MODE == 0 ? r * g.WA + s : -(r * g.WA + s);
-    const unsigned delta = (unsigned)(((tap * (MODE == 0 ? pitch : g.CA)) >> (MODE == 1 ? sh : 0)) + c) * 2u;
-    const unsigned hlim = MODE == 0 ? (unsigned)g.HA : (unsigned)g.HA << sh;
-    const unsigned wlim = MODE == 0 ? (unsigned)g.WA : (unsigned)g.WA << sh;
-    const unsigned kk = (unsigned)((r * g.S + s) * g.CA + c);
-#pragma unroll
-    for (int i = 0; i < A_INSTR; ++i) {
-      if ((i * 8 + wave) * 64 >= A_CHUNKS) continue;        // (uniform over the wave)
-      const int h = MODE == 0 ? rh[i] + r : rh[i] - r, w = MODE == 0 ? rw[i] + s : rw[i] - s;
-      bool ok = (unsigned)h < hlim && (unsigned)(w + ((c + kc8[i]) >> pshift)) < wlim;
-      if (MODE == 1) ok = ok && ((h | w) & smask) == 0;
-      dma_load16(a_rsrc, sa + i * 8 * 1024, ok ? abase[i] + delta : kOutOfRange);
-    }
-#pragma unroll
-    for (int i = 0; i < B_INSTR; ++i) {
-      if ((i * 8 + wave) * 64 >= B_CHUNKS) continue;
-      dma_load16(b_rsrc, sa + A_BYTES + i * 8 * 1024, bbase[i] == kOutOfRange ? kOutOfRange : bbase[i] + kk * 2u);
-    }
-    c += BK;
-    const bool wrap = c >= g.CA;
-    c = wrap ? 0 : c;
-    s += wrap ? tstep : 0;
-    const bool wrap2 = s >= g.S;
-    s = wrap2 ? s0 : s;
-    r += wrap2 ? tstep : 0;
+  unsigned a_uni = 0, b_uni = 0, bit = 0;        // scalar offsets and bit of that position
+  auto place = [&] {
+    const int tap = r * g.WA + s;
+    a_uni = MODE == 0 ? (unsigned)(tap * pitch + c) * 2u : (unsigned)(before - (tap * g.CA >> sh) + c) * 2u;
+    b_uni = (unsigned)((r * g.S + s) * g.CA + c) * 2u;
+    bit = (unsigned)(r * row_bits + (runs ? c / BK : s));
   };
-  // wait until this wave's loads of stage kt have landed: up to NS - 2 younger stages may stay in flight
-  auto wait_stage = [&](int younger) { wait_vmcnt_dyn(min(NS - 2, younger) * lps); };
+  auto advance = [&] {
+    c += BK; a_uni += 2 * BK; b_uni += 2 * BK;
+    if (runs) ++bit;
+    if (c >= g.CA) {                             // the next tap
+      c = 0;
+      s += tstep;
+      if (s >= g.S) { s = s0; r += tstep; }
+      place();
+    }
+  };
+  place();
+  // load u of a stage, u = 0 .. LPS_MAX - 1
+  auto issue = [&](int stage, int u) {
+    unsigned char* sa = smem + stage * STAGE + wave * 1024;
+    if (u < A_INSTR) {
+      if (A_CHUNKS % kDmaThreads == 0 || (u * 8 + wave) * 64 < A_CHUNKS)        // (uniform over the wave)
+        dma_load16(a_rsrc, sa + u * 8 * 1024, (skip[u] >> bit) & 1u ? kDmaSkip : a_off[u], a_uni);
+    } else if (B_CHUNKS % kDmaThreads == 0 || ((u - A_INSTR) * 8 + wave) * 64 < B_CHUNKS) {
+      dma_load16(b_rsrc, sa + A_BYTES + (u - A_INSTR) * 8 * 1024, bbase[u - A_INSTR], b_uni);
+    }
+  };
+  auto issue_stage = [&](int stage) {
+#pragma unroll
+    for (int u = 0; u < LPS_MAX; ++u) issue(stage, u);
+    advance();
+  };
+  // wait until this wave's loads of a stage have landed; `younger`: stages behind it, of which up to `ahead` have been requested
+  auto wait_stage = [&](int younger, int ahead) {
+    if (ahead == 0) wait_vmcnt<0>(); else wait_vmcnt_dyn(min(ahead, younger) * lps);
+  };
 
   // ---- fragment addresses: row = lane % 32 (+ 32 i), chunk = 2 ks + lane / 32, slot = chunk ^ swz(row) ----
   const int frow = lane & 31, fhi = lane >> 5;
@@ -254,37 +287,77 @@ __device__ __forceinline__ void dma_tile(unsigned char* smem, float* ep_s, const
     for (int j = 0; j < TN; ++j) pin(f.b[j]);
   };
 
-  // ---- the ring ----
+  auto multiply = [&](Frag& f) {
 #pragma unroll
-  for (int st = 0; st < NS - 1; ++st)
-    if (st < nk) issue_stage(st);
-  int stage = 0, next = NS - 1;                 // buffer of step kt, buffer the next loads go to
-  for (int kt = 0; kt < nk; ++kt) {
-    wait_stage(nk - 1 - kt);
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[j], f.a[i], acc[i][j], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);          // keep the next group's reads behind these MFMAs' issue, not ahead of the wait
+  };
+
+  // ---- the ring (waves without columns of their own only load) ----
+  static_assert(KS % 2 == 0, "the first and the last sub-step of a stage use different fragment registers");
+  auto ring = [&](auto multiplies) {
+    constexpr bool MUL = decltype(multiplies)::value;
+#pragma unroll
+    for (int st = 0; st < NS; ++st)
+      if (st < nk) issue_stage(st);
+    wait_stage(nk - 1, NS - 1);
     block_barrier();
-    // every wave is past step kt-1: its buffer takes the loads of step kt+NS-1
-    if (kt + NS - 1 < nk) issue_stage(next);
-    if (active) {
-      const unsigned sbase = (unsigned)(stage * STAGE);
-      Frag f[2];
-      read_frag(f[0], fa[0] + sbase, fb[0] + sbase);
+    Frag f[2];
+    auto substeps = [&](unsigned sbase) {       // all but the last, whose fragments are in registers at the end
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        if (ks + 1 < KS) read_frag(f[(ks + 1) & 1], fa[ks + 1] + sbase, fb[ks + 1] + sbase);
-        Frag& cur = f[ks & 1];
-        // LDS reads return in order: the older group is complete once at most the newer group's reads are pending
-        if (ks + 1 < KS) wait_lgkmcnt<TM + TN>(); else wait_lgkmcnt<0>();
-        pin_frag(cur);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.b[j], cur.a[i], acc[i][j], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);      // keep the next group's reads behind these MFMAs' issue, not ahead of the wait
+      for (int ks = 0; ks + 1 < KS; ++ks) {
+        read_frag(f[(ks + 1) & 1], fa[ks + 1] + sbase, fb[ks + 1] + sbase);
+        if (ks) {                               // LDS reads return in order: complete once at most the newer group's are pending
+          wait_lgkmcnt<TM + TN>();
+          pin_frag(f[ks & 1]);
+        }
+        multiply(f[ks & 1]);
       }
+      wait_lgkmcnt<0>();
+      pin_frag(f[(KS - 1) & 1]);
+    };
+    if constexpr (MUL) {
+      read_frag(f[0], fa[0], fb[0]);
+      wait_lgkmcnt<0>();
+      pin_frag(f[0]);
     }
-    stage = stage + 1 == NS ? 0 : stage + 1;
-    next = next + 1 == NS ? 0 : next + 1;
+    int stage = 0, kt = 0;                      // buffer of step kt
+    auto step = [&](auto loads) {
+      constexpr bool LOADS = decltype(loads)::value;
+      const int next = stage + 1 == NS ? 0 : stage + 1;
+      if constexpr (MUL) substeps((unsigned)(stage * STAGE));
+      wait_stage(nk - 2 - kt, NS - 2);
+      block_barrier();                          // stage kt+1 is in LDS, stage kt has been read by everyone
+      if constexpr (MUL) {
+        read_frag(f[0], fa[0] + (unsigned)(next * STAGE), fb[0] + (unsigned)(next * STAGE));
+        __builtin_amdgcn_sched_barrier(0);      // (on their way behind the products of the last sub-step)
+        Frag& cur = f[(KS - 1) & 1];
+#pragma unroll
+        for (int u = 0; u < (TM * TN > LPS_MAX ? TM * TN : LPS_MAX); ++u) {     // a load behind each product
+          if (u < TM * TN) acc[u / TN][u % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.b[u % TN], cur.a[u / TN], acc[u / TN][u % TN], 0, 0, 0);
+          if (LOADS && u < LPS_MAX) issue(stage, u);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (LOADS) advance();
+        wait_lgkmcnt<0>();                      // (and complete where the loop closes: the compiler may move them there)
+        pin_frag(f[0]);
+      } else if (LOADS) {
+        issue_stage(stage);
+      }
+      stage = next;
+    };
+    for (; kt + NS < nk; ++kt) step(std::true_type{});
+    for (; kt + 1 < nk; ++kt) step(std::false_type{});
+    if constexpr (MUL) {
+      substeps((unsigned)(stage * STAGE));
+      multiply(f[(KS - 1) & 1]);
+    }
+  };
+  if (nk > 0) {                                 // (a parity class that no tap reaches holds zeros)
+    if (active) ring(std::true_type{}); else ring(std::false_type{});
   }
   wait_vmcnt<0>();
   __syncthreads();                              // the ring is dead: LDS now stages the output tile
@@ -469,14 +542,16 @@ __global__ __launch_bounds__(kDmaThreads) void igemm_dma_kernel(
 // ---------------------------------------------------------------------------
 // Weight gradient for the 3 x 3 layers: 256-column tiles, eight wavefronts, direct-to-LDS loads.
 //   dW[k][j] = sum_m dy[m][k] * xcol[m][j],  j = (r*S + s)*C + c          (same as wgrad_tr_kernel)
-// Tile TM (output channels k: 256 / 192 / 128 / 96 / 64) x 256 (columns j), reduction over pixels in steps of
+// Tile TM (output channels k) x TN (columns j), 192 x 256, 256 x 256 or 256 x 192, reduction over pixels in steps of
 // 32, ring of four stages, one barrier a step.  Tiles lie in LDS as they lie in memory (rows = pixels) and the
 // MFMA fragments come out of the transposing read ds_read_b64_tr_b16, as in wgrad_tr_kernel; what changes is
 // that a stage is written by buffer_load ... lds (no register round trip), so rows are unpadded and bank
 // conflicts of the transposing reads are avoided by a swizzle: one read cycle serves 32 lanes = 4 pixel rows x
 // 64 contiguous bytes, so the 64-byte blocks of a row are permuted by the row number such that four consecutive
 // rows land in four different 16-bank groups (which permutation depends on the row pitch modulo 256 bytes).
-// Reads are inline assembly with their own waits, for the reason given at igemm_dma_kernel.
+// Reads are inline assembly with their own waits, for the reason given at igemm_dma_kernel, and the barrier lies between the two halves of a
+// step, the next loads behind the products of the second one, as there; the pixels' offsets are advanced by additions (WgradPixel).  Before and
+// after, us: 192 channels, 200704 pixels 185 -> 161 (730 -> 826 TFLOP/s), 384, 50176 187 -> 160, 768, 12544 171 -> 142.
 // ---------------------------------------------------------------------------
 // XOR mask on the 16-byte chunk index of a row of `elems` bf16 elements
 __device__ __forceinline__ constexpr int tr_swizzle(int elems, int row) {
@@ -491,16 +566,15 @@ __device__ __forceinline__ s16x4_t lds_read_tr4_async(unsigned addr) {
 }
 __device__ __forceinline__ void pin4(s16x4_t& v) { asm volatile("" : "+v"(v)); }
 
-constexpr int kWgradTN = 256;
 constexpr int kWgradStages = 4;
-constexpr int wgrad_dma_lds_bytes(int TM) { return kWgradStages * 32 * (TM + kWgradTN) * 2; }
+constexpr int wgrad_dma_lds_bytes(int TM, int TN) { return kWgradStages * 32 * (TM + TN) * 2; }
 
-template <int TM>
+template <int TM, int TN>
 __global__ __launch_bounds__(kDmaThreads) void wgrad_dma_kernel(const bf16_t* __restrict__ dy,
                                                                 const bf16_t* __restrict__ x,
                                                                 float* __restrict__ part, WgradTrArgs g) {
-  constexpr int TN = kWgradTN, BKP = 32, NS = kWgradStages;
-  constexpr int WK = TM >= 128 ? 2 : 1, WJ = 8 / WK;              // wave grid: channels x columns
+  constexpr int BKP = 32, NS = kWgradStages;
+  constexpr int WK = TN == 192 ? 4 : 2, WJ = 8 / WK;              // wave grid: channels x columns
   constexpr int WTM = TM / WK, WTN = TN / WJ;                      // a wave's part of the tile
   constexpr int TWM = WTM / 32, TWN = WTN / 32;
   static_assert(TWM * 32 * WK == TM && TWN * 32 * WJ == TN, "wave grid");
@@ -508,9 +582,9 @@ __global__ __launch_bounds__(kDmaThreads) void wgrad_dma_kernel(const bf16_t* __
   constexpr int PA = TM * 2, PB = TN * 2;                          // row pitch, bytes
   constexpr int A_BYTES = BKP * PA, STAGE = BKP * (PA + PB);
   constexpr int A_INSTR_ALL = BKP * CPA / 64, B_INSTR_ALL = BKP * CPB / 64;   // wave instructions per stage
-  constexpr int A_INSTR = (A_INSTR_ALL + 7) / 8, B_INSTR = B_INSTR_ALL / 8;   // ... per wave (A: at most)
-  static_assert(B_INSTR_ALL % 8 == 0 && (BKP * CPA) % 64 == 0, "whole wave instructions");
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[wgrad_dma_lds_bytes(TM)];
+  constexpr int A_INSTR = (A_INSTR_ALL + 7) / 8, B_INSTR = (B_INSTR_ALL + 7) / 8;   // ... per wave, at most
+  static_assert((BKP * CPB) % 64 == 0 && (BKP * CPA) % 64 == 0, "whole wave instructions");
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[wgrad_dma_lds_bytes(TM, TN)];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // uniform, and known to the compiler as such
@@ -538,48 +612,34 @@ __global__ __launch_bounds__(kDmaThreads) void wgrad_dma_kernel(const bf16_t* __
   }
   const unsigned a_step = (unsigned)(BKP * g.K) * 2u;
   // ---- x chunks: the column chunk fixes the tap (br, bs) and first channel bc; the pixel advances by 32 a step ----
-  const int b_slot = lane % CPB;                                   // (CPB = 32: the same slot for both instructions)
-  int bn[B_INSTR], bp[B_INSTR], bq[B_INSTR], bm[B_INSTR], br[B_INSTR], bs[B_INSTR], bc[B_INSTR];
-  bool b_ok[B_INSTR];
+  const WgradSteps steps = wgrad_steps(g);
+  WgradPixel px[B_INSTR];
+  int b_cnt = 0;
 #pragma unroll
   for (int i = 0; i < B_INSTR; ++i) {
-    const int ci = (i * 8 + wave) * 64 + lane, row = ci / CPB;
-    const int jcol = j0 + ((b_slot ^ tr_swizzle(TN, row)) * 8);
-    b_ok[i] = jcol < g.J;
-    const int rs = b_ok[i] ? jcol / g.C : 0;
-    bc[i] = b_ok[i] ? jcol - rs * g.C : 0;
-    br[i] = rs / g.S;
-    bs[i] = rs - br[i] * g.S;
-    bm[i] = mbeg + row;
-    bq[i] = bm[i] % g.Q;
-    const int t = bm[i] / g.Q;
-    bp[i] = t % g.P;
-    bn[i] = t / g.P;
+    if (i * 8 + wave < B_INSTR_ALL) ++b_cnt;
+    const int ci = (i * 8 + wave) * 64 + lane, row = ci / CPB, slot = ci % CPB;
+    px[i].init(g, j0 + (slot ^ tr_swizzle(TN, row)) * 8, mbeg + row);
   }
-  const int lps = a_cnt + B_INSTR;
-
-  auto issue_stage = [&](int stage) {
+  constexpr int LPS_MAX = A_INSTR + B_INSTR;
+  const int lps = a_cnt + b_cnt;
+  // load u of the next stage, u = 0 .. LPS_MAX - 1, into buffer `stage`
+  auto issue = [&](int stage, int u) {
     unsigned char* sa = smem + stage * STAGE + wave * 1024;
-#pragma unroll
-    for (int i = 0; i < A_INSTR; ++i) {
-      if (i * 8 + wave >= A_INSTR_ALL) continue;                  // (uniform over the wave)
-      dma_load16(rdy, sa + i * 8 * 1024, a_off[i]);
-      a_off[i] += a_off[i] == kOutOfRange ? 0u : a_step;
+    if (u < A_INSTR) {
+      if (A_INSTR_ALL % 8 != 0 && u * 8 + wave >= A_INSTR_ALL) return;   // (uniform over the wave)
+      dma_load16(rdy, sa + u * 8 * 1024, a_off[u]);
+      a_off[u] += a_off[u] == kOutOfRange ? 0u : a_step;
+      return;
     }
+    const int i = u - A_INSTR;
+    if (B_INSTR_ALL % 8 != 0 && i * 8 + wave >= B_INSTR_ALL) return;
+    dma_load16(rx, sa + A_BYTES + i * 8 * 1024, px[i].in_image(steps) ? px[i].off : kOutOfRange);
+    px[i].advance(steps);
+  };
+  auto issue_stage = [&](int stage) {
 #pragma unroll
-    for (int i = 0; i < B_INSTR; ++i) {
-      const int h = bp[i] * g.stride + br[i] - g.pad, w = bq[i] * g.stride + bs[i] - g.pad;
-      const bool ok = b_ok[i] && bm[i] < mend && (unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W;
-      dma_load16(rx, sa + A_BYTES + i * 8 * 1024, ok ? (unsigned)(((bn[i] * g.H + h) * g.W + w) * g.C + bc[i]) * 2u : kOutOfRange);
-      bm[i] += BKP;
-      const int q = bq[i] + g.dq;
-      const int c1 = q >= g.Q ? 1 : 0;
-      bq[i] = q - (c1 ? g.Q : 0);
-      const int pp = bp[i] + g.dp + c1;
-      const int c2 = pp >= g.P ? 1 : 0;
-      bp[i] = pp - (c2 ? g.P : 0);
-      bn[i] += g.dn + c2;
-    }
+    for (int u = 0; u < LPS_MAX; ++u) issue(stage, u);
   };
 
   // ---- fragment addresses: 16-lane group gl reads channels 16 (gl & 1) .. +15 of pixels 8 (gl >> 1) .. +3 (and +4) ----
@@ -619,47 +679,66 @@ __global__ __launch_bounds__(kDmaThreads) void wgrad_dma_kernel(const bf16_t* __
       f.b[j][1] = lds_read_tr4_async(base + fb[j] + ks * 16 * PB + 4 * PB);
     }
   };
-  auto mfma_frag = [&](Frag& f) {
+  auto pin_frag = [&](Frag& f) {
+#pragma unroll
+    for (int i = 0; i < TWM; ++i) { pin4(f.a[i][0]); pin4(f.a[i][1]); }
+#pragma unroll
+    for (int j = 0; j < TWN; ++j) { pin4(f.b[j][0]); pin4(f.b[j][1]); }
+  };
+  // the products of a fragment; LOADS: the loads of the next stage, one behind each
+  auto multiply = [&](Frag& f, auto loads, int stage) {
+    constexpr bool LOADS = decltype(loads)::value;
     bf16x8 af[TWM], bfr[TWN];
 #pragma unroll
-    for (int i = 0; i < TWM; ++i) {
-      pin4(f.a[i][0]); pin4(f.a[i][1]);
-      af[i] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(f.a[i][0], f.a[i][1], 0, 1, 2, 3, 4, 5, 6, 7));
+    for (int i = 0; i < TWM; ++i) af[i] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(f.a[i][0], f.a[i][1], 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+    for (int j = 0; j < TWN; ++j) bfr[j] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(f.b[j][0], f.b[j][1], 0, 1, 2, 3, 4, 5, 6, 7));
+    static_assert(TWM * TWN >= LPS_MAX, "a product for each load");
+#pragma unroll
+    for (int u = 0; u < TWM * TWN; ++u) {
+      acc[u / TWN][u % TWN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[u / TWN], bfr[u % TWN], acc[u / TWN][u % TWN], 0, 0, 0);
+      if constexpr (LOADS) {
+        if (u < LPS_MAX) issue(stage, u);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
-#pragma unroll
-    for (int j = 0; j < TWN; ++j) {
-      pin4(f.b[j][0]); pin4(f.b[j][1]);
-      bfr[j] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(f.b[j][0], f.b[j][1], 0, 1, 2, 3, 4, 5, 6, 7));
-    }
-#pragma unroll
-    for (int i = 0; i < TWM; ++i)
-#pragma unroll
-      for (int j = 0; j < TWN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
   };
 
 #pragma unroll
-  for (int st = 0; st < NS - 1; ++st)
+  for (int st = 0; st < NS; ++st)
     if (st < nsteps) issue_stage(st);
-  int stage = 0, next = NS - 1;
-  for (int st = 0; st < nsteps; ++st) {
-    // younger stages whose loads may stay in flight: up to NS - 2
-    wait_vmcnt_dyn(min(NS - 2, nsteps - 1 - st) * lps);
-    block_barrier();
-    if (st + NS - 1 < nsteps) issue_stage(next);
-    const unsigned sbase = (unsigned)(stage * STAGE);
-    Frag f0, f1;
-    read_frag(f0, sbase, 0);
-    read_frag(f1, sbase, 1);
-    wait_lgkmcnt<2 * (TWM + TWN)>();            // LDS reads return in order: the first group is complete
-    mfma_frag(f0);
+  wait_vmcnt_dyn(min(NS - 1, nsteps - 1) * lps);
+  block_barrier();
+  Frag f0, f1;
+  read_frag(f0, 0u, 0);
+  wait_lgkmcnt<0>();
+  pin_frag(f0);
+  int stage = 0, st = 0;
+  auto step = [&](auto loads) {
+    const int next = stage + 1 == NS ? 0 : stage + 1;
+    read_frag(f1, (unsigned)(stage * STAGE), 1);
     __builtin_amdgcn_sched_barrier(0);
+    multiply(f0, std::false_type{}, 0);
     wait_lgkmcnt<0>();
-    mfma_frag(f1);
-    __builtin_amdgcn_sched_barrier(0);
-    stage = stage + 1 == NS ? 0 : stage + 1;
-    next = next + 1 == NS ? 0 : next + 1;
-  }
+    pin_frag(f1);
+    wait_vmcnt_dyn(min(NS - 2, nsteps - 2 - st) * lps);
+    block_barrier();                            // stage st+1 is in LDS, stage st has been read by everyone
+    read_frag(f0, (unsigned)(next * STAGE), 0);
+    __builtin_amdgcn_sched_barrier(0);          // (on their way behind the products of the second half)
+    multiply(f1, loads, stage);
+    wait_lgkmcnt<0>();                          // (and complete where the loop closes: the compiler may move them there)
+    pin_frag(f0);
+    stage = next;
+  };
+  for (; st + NS < nsteps; ++st) step(std::true_type{});
+  for (; st + 1 < nsteps; ++st) step(std::false_type{});
+  read_frag(f1, (unsigned)(stage * STAGE), 1);
+  __builtin_amdgcn_sched_barrier(0);
+  multiply(f0, std::false_type{}, 0);
+  wait_lgkmcnt<0>();
+  pin_frag(f1);
+  multiply(f1, std::false_type{}, 0);
   wait_vmcnt<0>();
 
   float* out = part + (size_t)slice * g.K * g.J;

@@ -391,12 +391,12 @@ struct WgradCfg { int TM, TN, BKP, tiles_k, tiles_j, splits, pix_per_split; bool
 WgradCfg wgrad_cfg(long M, int K, int J, int taps) {
   WgradCfg w;
   w.dma = false;
-  // (measured on the 3 x 3 layers of ResNet-50 x1.5 at batch 256: 192 channels 274 -> 184 us, 768 channels 265 -> 166 us,
-  // 384 channels 204 -> 190 us; tiles of 128, 96 or 64 channels are no faster than wgrad_tr_kernel and stay with it)
+  // (measured on the 3 x 3 layers of ResNet-50 x1.5 at batch 256: 192 channels 274 -> 161 us, 768 channels 265 -> 142 us,
+  // 384 channels 204 -> 160 us; tiles of 128, 96 or 64 channels are no faster than wgrad_tr_kernel and stay with it)
   if (taps > 1 && M >= 8192 && J >= 512 && (K % 256 == 0 || K % 192 == 0) && (J / taps) % 8 == 0) {
     w.dma = true;
     w.TM = K % 256 == 0 ? 256 : 192;
-    w.TN = kWgradTN;
+    w.TN = 256;
     w.BKP = 32;
     w.tiles_k = K / w.TM;
     w.tiles_j = (J + w.TN - 1) / w.TN;
@@ -461,8 +461,8 @@ int igemm_splits(long M, int NC, int Kred, int CA) { return igemm_cfg(M, NC, Kre
 
 // Launch shape of igemm_dma_kernel (256-row tiles, operands straight into LDS) for one dense layer, or use = false
 // when the layer keeps igemm_kernel: channel counts that are no multiple of 32, fewer tiles than most of the
-// compute units (there 128- and 64-row tiles and split-K fill the chip better), and reductions shorter than 256
-// (one or two steps per tile: nothing to pipeline).
+// compute units (there 128- and 64-row tiles and split-K fill the chip better), reductions shorter than 256
+// (one or two steps per tile: nothing to pipeline), and filters of more taps than a row's mask has bits (6 x 6 and larger).
 struct DmaCfg { bool use; int BN, BK, tiles_n, big_m, tail_m; };
 // epi: what the store does (EPI_AFFINE_ACT: a folded batch norm and activation, the frozen teacher's layers)
 DmaCfg dma_cfg(long M, int NC, int Kred, int CA, int num_cu, int epi) {
@@ -473,7 +473,7 @@ DmaCfg dma_cfg(long M, int NC, int Kred, int CA, int num_cu, int epi) {
   // student 96 -> 256 at 56 x 56 178 -> 162 us, 192 -> 512 at 28 x 28 126 -> 96 us; teacher 64 -> 256 with the fused
   // residual 233 -> 183 us, 128 -> 512 140 -> 105 us on the narrow tiles chosen below); filters from 256 reduction
   // elements on.
-  if (Kred < (Kred == CA ? 64 : 256)) return d;
+  if (Kred < (Kred == CA ? 64 : 256) || Kred / CA > kDmaMaxTaps) return d;
   const long tm = (M + kDmaBM - 1) / kDmaBM;
   // One workgroup per compute unit is resident: time ~ rounds x columns of the tile (a little more per column for
   // narrow tiles, whose fragments feed fewer MFMAs).  A last round that fills at most a quarter of the units is
@@ -1441,7 +1441,7 @@ template <class T> struct Exec {
           snprintf(name, sizeof name, "wgrad_%dx%d%s", w.TM, w.TN, fold.mean ? "_bn" : "");
           ProfScope ps(c, name, bytes_run, flops, net, blk, opi);
           if (w.dma) {
-#define PBD_WGD(TM_) launch(c, wgrad_dma_kernel<TM_>, grid, kDmaThreads, 0, st, (const bf16_t*)dy, (const bf16_t*)x, part, g)
+#define PBD_WGD(TM_) launch(c, wgrad_dma_kernel<TM_, 256>, grid, kDmaThreads, 0, st, (const bf16_t*)dy, (const bf16_t*)x, part, g)
             if (w.TM == 256) PBD_WGD(256); else PBD_WGD(192);
 #undef PBD_WGD
           } else {
