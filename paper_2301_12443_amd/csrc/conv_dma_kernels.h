@@ -540,7 +540,7 @@ __global__ __launch_bounds__(kDmaThreads) void igemm_dma_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Weight gradient for the 3 x 3 layers: 256-column tiles, eight wavefronts, direct-to-LDS loads.
+// Weight gradient of the layers whose channels fill wide tiles: eight wavefronts, direct-to-LDS loads.
 //   dW[k][j] = sum_m dy[m][k] * xcol[m][j],  j = (r*S + s)*C + c          (same as wgrad_tr_kernel)
 // Tile TM (output channels k) x TN (columns j), 192 x 256, 256 x 256 or 256 x 192, reduction over pixels in steps of
 // 32, ring of four stages, one barrier a step.  Tiles lie in LDS as they lie in memory (rows = pixels) and the

@@ -385,21 +385,28 @@ inline DwArgs dw_bwd_args(int N, int h, int w, int Cp, int k, bool arch) { retur
 
 struct WgradCfg { int TM, TN, BKP, tiles_k, tiles_j, splits, pix_per_split; bool dma; };
 // taps = R * S of the layer (J = taps * C).  Layers with a filter (taps > 1), whole 64- or 96-channel groups and a
-// long pixel range take wgrad_dma_kernel: TM x 256 tiles, one workgroup per compute unit, the pixel range cut
-// so that about 256 workgroups result.  Everything else (1 x 1 layers, which are bound by memory, stems) keeps
-// wgrad_tr_kernel.
+// long pixel range take wgrad_dma_kernel: TM x TN tiles, one workgroup per compute unit, the pixel range cut
+// so that about 256 workgroups result.  So do 1 x 1 layers whose channels fill such tiles, where a workgroup gets kWgradDmaPixels
+// pixels or more.  Everything else (short or narrow 1 x 1 layers, stems) keeps wgrad_tr_kernel.
+// In us, wgrad_tr_kernel / wgrad_dma_kernel (pixels a workgroup of the latter):
+//   256 -> 192, 802816 pixels  172 / 147 (3136)     192 -> 512, 200704  81 / 65 (1568)     1024 -> 384, 50176  56 / 53 (1568)
+//   256 -> 192, 200704          39 / 35 (784)       192 -> 512, 50176   26 / 23 (392)      1024 -> 384, 12544  21.7 / 22.8 (392)
+//   768 -> 2048, 12544          56 / 52 (1568)      768 -> 2048, 3136   22.3 / 22.5 (392)  512 -> 512, 3136   10.6 / 13.6 (49)
+// A line at 512 takes in layers of 520 to 784 pixels a workgroup, and ResNet-50 x1.5's block 3 at batch 85 goes from 2438 to 2564 us, its step at batch
+// 64 from 8.80 to 8.95 ms: the tiles leave no room on a unit for the other branches' kernels, and their partial sums are more.
+constexpr long kWgradDmaPixels = 1024;
 WgradCfg wgrad_cfg(long M, int K, int J, int taps) {
   WgradCfg w;
-  w.dma = false;
-  // (measured on the 3 x 3 layers of ResNet-50 x1.5 at batch 256: 192 channels 274 -> 161 us, 768 channels 265 -> 142 us,
-  // 384 channels 204 -> 160 us; tiles of 128, 96 or 64 channels are no faster than wgrad_tr_kernel and stay with it)
-  if (taps > 1 && M >= 8192 && J >= 512 && (K % 256 == 0 || K % 192 == 0) && (J / taps) % 8 == 0) {
-    w.dma = true;
-    w.TM = K % 256 == 0 ? 256 : 192;
-    w.TN = 256;
-    w.BKP = 32;
-    w.tiles_k = K / w.TM;
-    w.tiles_j = (J + w.TN - 1) / w.TN;
+  // (measured on the 3 x 3 layers of ResNet-50 x1.5 at batch 256, against wgrad_tr_kernel: 192 channels 274 -> 161 us, 768 channels
+  // 265 -> 142 us; 96 channels on 96 x 256 tiles 242 us as with wgrad_tr_kernel, which keeps them)
+  w.TM = K % 256 == 0 ? 256 : 192;
+  w.TN = taps > 1 || J % 256 == 0 ? 256 : 192;
+  w.BKP = 32;
+  w.tiles_k = K / w.TM;
+  w.tiles_j = (J + w.TN - 1) / w.TN;
+  w.dma = K % w.TM == 0 && (taps > 1 ? M >= 8192 && J >= 512 && (J / taps) % 8 == 0
+                                     : J % w.TN == 0 && w.TM + w.TN > 384 && M * w.tiles_k * w.tiles_j >= 256 * kWgradDmaPixels);
+  if (w.dma) {
     const long tiles = (long)w.tiles_k * w.tiles_j;
     long splits = std::max(1L, 256 / tiles);
     splits = std::min(splits, std::max(1L, (long)(256u << 20) / ((long)K * J * 4)));
@@ -412,7 +419,6 @@ WgradCfg wgrad_cfg(long M, int K, int J, int taps) {
   }
   w.TM = K > 64 ? 128 : 64;       // a 128-wide tile that is 3/4 full still beats two 64-wide ones
   w.TN = J > 64 ? 128 : 64;
-  w.BKP = 32;
   w.tiles_k = (K + w.TM - 1) / w.TM;
   w.tiles_j = (J + w.TN - 1) / w.TN;
   const long tiles = (long)w.tiles_k * w.tiles_j;
@@ -1441,8 +1447,8 @@ template <class T> struct Exec {
           snprintf(name, sizeof name, "wgrad_%dx%d%s", w.TM, w.TN, fold.mean ? "_bn" : "");
           ProfScope ps(c, name, bytes_run, flops, net, blk, opi);
           if (w.dma) {
-#define PBD_WGD(TM_) launch(c, wgrad_dma_kernel<TM_, 256>, grid, kDmaThreads, 0, st, (const bf16_t*)dy, (const bf16_t*)x, part, g)
-            if (w.TM == 256) PBD_WGD(256); else PBD_WGD(192);
+#define PBD_WGD(TM_, TN_) launch(c, wgrad_dma_kernel<TM_, TN_>, grid, kDmaThreads, 0, st, (const bf16_t*)dy, (const bf16_t*)x, part, g)
+            if (w.TN == 192) PBD_WGD(256, 192); else if (w.TM == 256) PBD_WGD(256, 256); else PBD_WGD(192, 256);
 #undef PBD_WGD
           } else {
 #define PBD_WG(TM_, ...) launch(c, wgrad_tr_kernel<TM_, __VA_ARGS__>, grid, 256, 0, st, (const bf16_t*)dy, (const bf16_t*)x, part, g)
