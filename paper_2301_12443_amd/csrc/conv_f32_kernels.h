@@ -296,12 +296,12 @@ __global__ __launch_bounds__(256) void igemm_f32_kernel(const float* __restrict_
 // weights: 16 cycles a pixel, 8 of them the products').  Both operands are contiguous along their channels; a gathered pixel is addressed once per
 // four channels of a tap.
 template <int TILE>
-__global__ __launch_bounds__(256) void wgrad_f32_kernel(const float* __restrict__ dy, const float* __restrict__ x,
-                                                       float* __restrict__ dw, WgradTrArgs g) {
+__device__ __forceinline__ void wgrad_f32_block(const Blk& blk, const float* __restrict__ dy, const float* __restrict__ x,
+                                                float* __restrict__ dw, WgradTrArgs g) {
   typedef F32Tile<TILE> F;
   typedef F32Gemm<TILE> G;
   const int tid = threadIdx.x, lane = tid & 63, group = lane / TILE, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int tile = xcd_contiguous(blockIdx.x, g.tiles_k * g.tiles_j);
+  const int tile = xcd_contiguous(blk.x, g.tiles_k * g.tiles_j);
   const int k0 = (tile / g.tiles_j) * G::EDGE, j0 = (tile % g.tiles_j) * G::EDGE;
   const __amdgpu_buffer_rsrc_t rd = tensor_rsrc(dy, g.dy_bytes), rx = tensor_rsrc(x, g.x_bytes);
 
@@ -366,6 +366,11 @@ __global__ __launch_bounds__(256) void wgrad_f32_kernel(const float* __restrict_
     }
     *reinterpret_cast<float4*>(dw + (size_t)k * g.J + j) = make_float4(o[0], o[1], o[2], o[3]);
   }
+}
+template <int TILE>
+__global__ __launch_bounds__(256) void wgrad_f32_kernel(const float* __restrict__ dy, const float* __restrict__ x,
+                                                       float* __restrict__ dw, WgradTrArgs g) {
+  wgrad_f32_block<TILE>(one_block(), dy, x, dw, g);
 }
 
 }  // namespace pbd

@@ -83,6 +83,7 @@ struct OpPlan {
   size_t s_rmean = 0, s_rvar = 0, s_mean = 0, s_invstd = 0, s_k2 = 0, s_k3 = 0;
   size_t s_keep = 0;        // gamma and beta of the last step, where the normalised output or the gradient dy is not written
   long e_wt = -1;           // element offset in the block's transposed-weight arena
+  bool late = false;        // the weight gradient goes out with the block's others (find_late)
   long e_part = -1;         // element offset of the weight gradient's partial sums among the block's deferred ones (-1: summed at once)
   // scratch byte offsets
   size_t y = 0, idx = 0;
@@ -147,7 +148,7 @@ struct Lanes {
 
 struct pbd_ctx {
   pbd_opts o{};
-  Lanes lanes;
+  Lanes lanes, late;                    // launches that wait for those of other lanes; weight gradients that wait for their block's
   int B = 0;
   Shape in{};
   std::vector<double> pool;
@@ -544,6 +545,11 @@ inline int f32_tile(long rows, long cols) { return (rows + 63) / 64 * ((cols + 6
 
 constexpr int kMseBlocks = 1024;
 
+// The launch shape of op's weight gradient (bf16, not a space-to-depth stem)
+WgradCfg wgrad_of(const OpPlan& op, long M) {
+  return wgrad_cfg(M, op.d.c_out, op.d.k * op.d.k * op.cin_p, op.d.k * op.d.k);
+}
+
 // Partial sums of a weight gradient of up to 4 MB wait for the block's one summing launch; larger ones, whose sum is memory
 // traffic rather than a launch, are added at once while the caches hold them (ResNet-50 x1.5 at batch 256: 53 sums of 46 MB on
 // average at 5.2 TB/s).
@@ -613,6 +619,38 @@ void find_lanes(pbd_ctx* c, BlockPlan& bp) {
 // A block's reduction scratch: one region for the ops that go out by themselves and for the first lane, and for every further lane one of
 // what the ops of a lane group need (the supernet's at batch 64: 6 x 39 MB a block at most).
 inline size_t all_red(const BlockPlan& bp) { return bp.red_bytes + bp.lane_bytes * (bp.lanes - 1); }
+
+// Weight gradients of a block that wait for its end and go out together, those of one kernel in one grid (many.h): no later op of the
+// backward pass reads them, and on small layers each is a launch of its own that leaves most of the chip idle.  Every layer keeps its cut of
+// the pixels, and with it its bits.  reached: values whose gradient the weight round forms.  Layers that another kernel forms on the way stay with
+// it, those of wgrad_dma_kernel fill the chip by themselves.
+// Of up to kLateBytes of input and output and kLateElems partial sums, which are read again from the caches or nearly so.  us a step, none late / 4 M
+// partial sums and 32 MB / 160 MB / 16 M and 160 MB: VGG-16 at batch 256, pipelined, 1284 / 1219 / 1223 / 1224, at batch 85 999 / 908 / 916 / 918,
+// MobileNetV2 at batch 33 1853 / 1773 / 1778 / 1783 (with 1 M: 1261, 952, 1841); ResNet-50 x1.5 at batch 64 and 256 level.  One cut for all of a block's
+// layers, of fewer and longer sums, was faster still (VGG-16 at batch 85 -1 %, ResNet-50 x1.5 at batch 64 -4 %), but its gradients were up to 4 times
+// as far from 64-bit sums.
+constexpr double kLateBytes = 64.0 * 1048576.0;
+constexpr size_t kLateElems = (size_t)1 << 22;
+void find_late(pbd_ctx* c, BlockPlan& bp, const std::vector<char>& reached) {
+  if (c->o.force_direct) return;
+  const bool bf = c->o.precision == PBD_BF16;
+  std::vector<OpPlan*> late;
+  for (int j = 0; j < (int)bp.ops.size(); ++j) {
+    OpPlan& op = bp.ops[j];
+    if (op.d.type != OP_CBA || op.s2d || !reached[j + 1] || bp.group_of[j] >= 0) continue;
+    if (dw_bwd_fused(c, bp, j) || pw_bwd_fused(c, bp, j) || pj_bwd_fused(c, bp, j)) continue;
+    const double bytes = (double)c->o.batch * ((double)op.in.h * op.in.w * op.cin_p + (double)op.out.h * op.out.w * op.cout_p) * c->esz;
+    const long M = (long)c->o.batch * op.out.h * op.out.w;
+    if (bytes > kLateBytes || (bf && !op.dw && wgrad_of(op, M).dma)) continue;
+    // (the partial sums need a place of their own; depthwise layers always leave some)
+    const int splits = op.dw ? dw_wgrad_cfg(bf, c->o.batch, op.in.h, op.in.w, op.out.h, op.out.w, op.cout_p, op.d.k, op.d.stride, op.d.pad).chunks
+                             : bf ? wgrad_of(op, M).splits : 1;
+    if ((op.dw && splits < 2) || (size_t)splits * op.wn > kLateElems) continue;
+    late.push_back(&op);
+  }
+  if (late.size() < 2) return;
+  for (OpPlan* op : late) op->late = true;
+}
 
 int plan(pbd_ctx* c) {
   const size_t es = c->esz;
@@ -731,8 +769,9 @@ int plan(pbd_ctx* c) {
     for (size_t j = bp.ops.size(); j-- > 0;)
       if (reached[j + 1])
         for (int i = 0; i < bp.ops[j].d.nin; ++i) reached[bp.ops[j].d.in[i]] = 1;
+    find_late(c, bp, reached);
     auto defer = [&](OpPlan& op, int splits) {
-      if (splits < 2 || (size_t)splits * op.wn > kDeferredElems || !reached[&op - bp.ops.data() + 1]) return;
+      if (splits < 2 || (size_t)splits * op.wn > (op.late ? kLateElems : kDeferredElems) || !reached[&op - bp.ops.data() + 1]) return;
       op.e_part = (long)parts;
       bp.stable.push_back({(long)parts, (long)op.e_w, (long)op.wn, splits, 0});
       parts += (size_t)splits * op.wn;
@@ -765,7 +804,7 @@ int plan(pbd_ctx* c) {
             need_parts(op, (size_t)gw.chunks * op.d.k * op.d.k * op.cout_p * 4);
           }
         } else if (bf && !c->o.force_direct) {
-          const WgradCfg w = op.s2d ? wgrad_cfg(M, op.d.c_out, kS2dK, 16) : wgrad_cfg(M, op.d.c_out, op.d.k * op.d.k * op.cin_p, op.d.k * op.d.k);
+          const WgradCfg w = op.s2d ? wgrad_cfg(M, op.d.c_out, kS2dK, 16) : wgrad_of(op, M);
           if (op.s2d) {               // partial sums on the space-to-depth input and their sum in the repacked layout, then unpacked
             need_red(((size_t)w.splits + 1) * op.d.c_out * kS2dK * 4);
           } else if (pj_bwd_fused(c, bp, (int)v - 1)) {
@@ -822,6 +861,9 @@ inline int grid_for(long n, int block = 256, int cap = 256 * 32) {
   return (int)std::max(1L, std::min<long>((n + block - 1) / block, cap));
 }
 
+// what takes down launches instead of sending them out (null: nothing does)
+inline Lanes* recorder(pbd_ctx* c) { return c->late.on ? &c->late : c->lanes.on ? &c->lanes : nullptr; }
+
 struct ProfScope {
   pbd_ctx* c;
   bool on;
@@ -830,13 +872,13 @@ struct ProfScope {
     pbd_prof_entry e{};
     snprintf(e.name, sizeof e.name, "%s", name);
     e.bytes = bytes; e.flops = flops; e.net = net; e.block = block; e.op = op;
-    if (c->lanes.on) { c->lanes.label = e; c->lanes.labelled = true; return; }
+    if (Lanes* l = recorder(c)) { l->label = e; l->labelled = true; return; }
     c->prof.push_back(e);
     const size_t need = c->prof.size() * 2;
     while (c->ev.size() < need) { hipEvent_t ev; (void)hipEventCreate(&ev); c->ev.push_back(ev); }
     c->pend_start = c->ev[need - 2]; c->pend_stop = c->ev[need - 1];   // the scope's first launch takes them
   }
-  ~ProfScope() { if (on) { c->pend_start = c->pend_stop = nullptr; c->lanes.labelled = false; } }
+  ~ProfScope() { if (on) { c->pend_start = c->pend_stop = nullptr; c->lanes.labelled = c->late.labelled = false; } }
 };
 
 // Launch through one place.  A profiled launch attaches its two events to the dispatch itself, so
@@ -857,20 +899,21 @@ template <class... KA> void launch_recorded(pbd_ctx* c, hipStream_t st, const La
             *reinterpret_cast<const Pack<KA...>*>(r.args));
 }
 // Every argument is converted to the kernel's parameter type.  Between the lanes of a mixed layer the launch waits for the others'
-// (flush_lanes).
+// (flush_lanes), a late weight gradient's for the end of its block (flush_late).
 template <class... KA, class... A>
 inline void launch(pbd_ctx* c, void (*kern)(KA...), dim3 grid, dim3 block, size_t smem, hipStream_t st, A&&... a) {
   static_assert(sizeof...(KA) == sizeof...(A), "argument count differs from the kernel's");
-  if (!c->lanes.on) {
+  Lanes* const to = recorder(c);
+  if (!to) {
     launch_now<KA...>(c, kern, grid, block, smem, st, std::forward<A>(a)...);
     return;
   }
   static_assert(sizeof(Pack<KA...>) <= sizeof(LaneLaunch::args), "the arguments fit the record");
-  Lanes& l = c->lanes;
+  Lanes& l = *to;
   l.rec.emplace_back();
   LaneLaunch& r = l.rec.back();
   r.kern = (const void*)kern; r.one = launch_recorded<KA...>; r.grid = grid; r.block = block; r.smem = smem;
-  r.lane = l.lane; r.stage = l.stage[l.lane]; r.serial = l.serial; r.labelled = l.labelled; r.label = l.label;
+  r.lane = l.lane; r.stage = l.stage.empty() ? 0 : l.stage[l.lane]; r.serial = l.serial; r.labelled = l.labelled; r.label = l.label;
   l.labelled = false;                                    // (the scope's first launch takes it)
   pack_up(*new (r.args) Pack<KA...>, KA(std::forward<A>(a))...);
 }
@@ -900,7 +943,7 @@ void launch_many(pbd_ctx* c, hipStream_t st, const LaneLaunch* const* r, int n) 
 template <auto Block, int THREADS, int WAVES, class... KA> void put(ManyTable& t, void (*kern)(KA...)) {
   t[(const void*)kern] = launch_many<Block, THREADS, WAVES, KA...>;
 }
-// The kernels of mixed layers (bfloat16); one that is not here is launched lane by lane.
+// The kernels of mixed layers and of late weight gradients; one that is not here is launched by itself.
 const ManyTable& many_table() {
   static const ManyTable table = [] {
     ManyTable t;
@@ -931,6 +974,8 @@ const ManyTable& many_table() {
     PBD_MANY(2, pj_bwd, true); PBD_MANY(2, pj_bwd, false); PBD_MANY(3, pw_fwd, false);
     PBD_MANY(1, sum_partials, 32); PBD_MANY(1, sum_partials, 8);
     PBD_MANY(1, dw_wgrad, B, 3, 3); PBD_MANY(1, dw_wgrad, B, 7, 1);
+    PBD_MANY(1, dw_wgrad, float, 3, 3); PBD_MANY(1, dw_wgrad, float, 7, 1);
+    PBD_MANY(1, wgrad_f32, 16); PBD_MANY(1, wgrad_f32, 32);
 #define PBD_MANY_DW(K_) PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, false, false, false, false); PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, false, false, true, false); \
     PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, false, true, true, false); PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, true, false, false, false); \
     PBD_MANY(3, dw_wgrad_mfma, K_, false); PBD_MANY((K_ == 7 ? 2 : 3), dw_bwd_mfma, K_, true); PBD_MANY((K_ == 7 ? 3 : 4), dw_bwd_mfma, K_, false); \
@@ -946,6 +991,36 @@ const ManyTable& many_table() {
   return table;
 }
 
+// n recorded launches of one kernel (more than one: of one that is in the table) in one grid
+void send_recorded(pbd_ctx* c, hipStream_t st, const LaneLaunch* const* r, int n) {
+  ProfScope* ps = nullptr;
+  if (r[0]->labelled) {
+    double bytes = 0, flops = 0;
+    for (int i = 0; i < n; ++i) { bytes += r[i]->label.bytes; flops += r[i]->label.flops; }
+    const pbd_prof_entry& e = r[0]->label;
+    ps = new ProfScope(c, e.name, bytes, flops, e.net, e.block, e.op);
+  }
+  if (n == 1) r[0]->one(c, st, *r[0]);
+  else many_table().at(r[0]->kern)(c, st, r, n);
+  delete ps;
+}
+
+// Send out a block's late weight gradients: up to kManyMax of one kernel in a grid, in the order in which the backward pass came to them.
+void flush_late(pbd_ctx* c, hipStream_t st) {
+  std::vector<LaneLaunch>& rec = c->late.rec;
+  std::vector<char> sent(rec.size(), 0);
+  for (size_t i = 0; i < rec.size(); ++i) {
+    if (sent[i]) continue;
+    const LaneLaunch* r[kManyMax] = {&rec[i]};
+    int n = 1;
+    if (many_table().count(rec[i].kern))
+      for (size_t k = i + 1; k < rec.size() && n < kManyMax; ++k)
+        if (!sent[k] && rec[k].kern == rec[i].kern && rec[k].block.x == rec[i].block.x) { r[n++] = &rec[k]; sent[k] = 1; }
+    send_recorded(c, st, r, n);
+  }
+  rec.clear();
+}
+
 // Send out what the lanes recorded: each lane's launches in their order, launches of one kernel that several lanes have come to in one.
 // A kernel that another lane reaches a little later (in the same op of its chain) waits for it.  Launches that add to the value all lanes read
 // come last, one by one in lane order, as without lanes.
@@ -957,18 +1032,6 @@ void flush_lanes(pbd_ctx* c, hipStream_t st) {
   for (const LaneLaunch& r : l.rec)
     if (!r.serial) q[r.lane].push_back(&r);
   std::vector<size_t> head(nl, 0);
-  auto emit = [&](const LaneLaunch* const* r, int n) {
-    ProfScope* ps = nullptr;
-    if (r[0]->labelled) {
-      double bytes = 0, flops = 0;
-      for (int i = 0; i < n; ++i) { bytes += r[i]->label.bytes; flops += r[i]->label.flops; }
-      const pbd_prof_entry& e = r[0]->label;
-      ps = new ProfScope(c, e.name, bytes, flops, e.net, e.block, e.op);
-    }
-    if (n == 1) r[0]->one(c, st, *r[0]);
-    else many_table().at(r[0]->kern)(c, st, r, n);
-    delete ps;
-  };
   for (;;) {
     const LaneLaunch* pick = nullptr;
     for (int a = 0; a < nl; ++a) {
@@ -993,10 +1056,10 @@ void flush_lanes(pbd_ctx* c, hipStream_t st) {
       r[n++] = h;
       ++head[a];
     }
-    emit(r, n);
+    send_recorded(c, st, r, n);
   }
   for (const LaneLaunch& r : l.rec)
-    if (r.serial) { const LaneLaunch* p = &r; emit(&p, 1); }
+    if (r.serial) { const LaneLaunch* p = &r; send_recorded(c, st, &p, 1); }
   l.rec.clear();
 }
 
@@ -1419,7 +1482,7 @@ template <class T> struct Exec {
     const double bytes = bytes_of(op.in) + bytes_of(op.out) + (double)op.wn * 4;
     if (mfma()) {
       if constexpr (sizeof(T) == 2) {
-        const WgradCfg w = op.s2d ? wgrad_cfg(M, op.d.c_out, kS2dK, 16) : wgrad_cfg(M, op.d.c_out, J, op.d.k * op.d.k);
+        const WgradCfg w = op.s2d ? wgrad_cfg(M, op.d.c_out, kS2dK, 16) : wgrad_of(op, M);
         const int pq = op.out.h * op.out.w;
         WgradTrArgs g{N, op.in.h, op.in.w, op.cin_p, op.out.h, op.out.w, op.d.c_out, op.d.k, op.d.k,
                       op.d.stride, op.d.pad, (int)M, J, w.pix_per_split,
@@ -2172,8 +2235,10 @@ template <class T> struct Exec {
         }
         const T* x = value(iv);
         if (!arch) {
+          c->late.on = op.late && !red_static;
           if (op.dw) dw_wgrad(op, dz, folds_into(iv) ? ws(scr + bp.ops[iv - 1].y) : x, grad + op.e_w, input_fold(iv));
           else conv_wgrad(op, dz, folds_into(iv) ? ws(scr + bp.ops[iv - 1].y) : x, grad + op.e_w, input_fold(iv));
+          c->late.on = false;
         }
         if (wanted[iv]) {  // A_{i-1} is a constant: no backward-data for the block's first layer
           c->lanes.serial = group >= 0 && iv == bp.groups[group].root;     // (every lane adds to that one)
@@ -2231,6 +2296,7 @@ template <class T> struct Exec {
     // ---- decoupled update of this block only -----------------------------
     if (!arch) {
       opi = -1;
+      flush_late(c, st);
       sum_deferred(bp);
       const long n4 = (long)bp.arena_elems / 4;
       ProfScope ps(c, "sgd_momentum", (double)bp.arena_elems * (20 + (sizeof(T) == 2 ? 2 : 0)), 0, net, blk, opi);
