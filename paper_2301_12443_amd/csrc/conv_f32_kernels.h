@@ -199,29 +199,35 @@ __global__ __launch_bounds__(256) void igemm_f32_kernel(const float* __restrict_
   const int RS = g.R * g.S;
 
   // a thread's reduction element kk = tap * CA + c, moved on by a stage at a time (CA % 8 == 0: its four elements share a tap)
-  struct Tap { int kk, c, r, s; };
+  // off: what the tap and channel add to an element's offset, advanced by additions like the rest
+  struct Tap { int kk, c, r, s, off; };
   auto tap_of = [&](int kk) {
-    const int rs = kk / g.CA;
-    return Tap{kk, kk - rs * g.CA, rs / g.S, rs % g.S};
+    const int rs = kk / g.CA, r = rs / g.S, q = rs % g.S, c = kk - rs * g.CA;
+    return Tap{kk, c, r, q, MODE == 0 ? (r * g.WA + q) * g.CA + c : c - ((r * g.WA + q) * g.CA >> sh)};
   };
   const int dtap = G::BK / g.CA, dc = G::BK % g.CA, dr = dtap / g.S, ds = dtap % g.S;   // BK in the mixed radix of (r, s, c)
+  // (a channel count run out is the next tap of the row: the same offset at MODE 0.  MODE 1 forms it anew: with stride 2 the taps of a row are
+  // half a pixel apart)
+  const int d_off = (dr * g.WA + ds) * g.CA + dc, row_off = (g.WA - g.S) * g.CA;
   auto next_stage = [&](Tap& t) {
     t.kk += G::BK;
     const int c = t.c + dc, c1 = c >= g.CA ? 1 : 0, s = t.s + ds + c1, c2 = s >= g.S ? 1 : 0;
     t.c = c - (c1 ? g.CA : 0);
     t.s = s - (c2 ? g.S : 0);
     t.r += dr + c2;
+    if (MODE == 0) t.off += d_off + (c2 ? row_off : 0);
+    else t.off = t.c - ((t.r * g.WA + t.s) * g.CA >> sh);
   };
   // pixels: two rows of four elements a stage
   Tap ta = tap_of(G::template minor<true>(tid));
-  int rbase[2], rh[2], rw[2];
+  int at[2], rh[2], rw[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int m = m0 + G::template major<true>(tid, i), mm = m < g.M ? m : 0;
     const int b_ = mm % g.WO, t = mm / g.WO, a_ = t % g.HO;
-    rbase[i] = (t / g.HO) * g.HA * g.WA;
     rh[i] = MODE == 0 ? a_ * g.stride - g.pad : a_ + g.pad;
     rw[i] = MODE == 0 ? b_ * g.stride - g.pad : b_ + g.pad;
+    at[i] = (t / g.HO) * g.HA * g.WA * g.CA + ((rh[i] * g.WA + rw[i]) * g.CA >> (MODE == 1 ? sh : 0));
     if (m >= g.M) rh[i] = -(1 << 24);                  // (fails every range test)
   }
   auto load_pixels = [&](int i) {
@@ -229,24 +235,35 @@ __global__ __launch_bounds__(256) void igemm_f32_kernel(const float* __restrict_
     bool ok = ta.kk < g.Kred;
     if (MODE == 1) { ok &= ((h | w) & smask) == 0; h >>= sh; w >>= sh; }
     ok &= ((unsigned)h < (unsigned)g.HA) & ((unsigned)w < (unsigned)g.WA);
-    const unsigned off = (unsigned)((rbase[i] + h * g.WA + w) * g.CA + ta.c) * 4u;
+    const unsigned off = (unsigned)(at[i] + ta.off) * 4u;
     if (i == 1) next_stage(ta);
     return buffer_load_f4(ra, ok ? off : kOutOfRange);
   };
-  // weights: MODE 0 two channels' four elements, MODE 1 two elements' four channels (NC % 8 == 0: in or out as a whole)
-  Tap tb[2];
-  int bat[2];
+  // weights: MODE 0 two channels' four elements, MODE 1 two elements' four channels (NC % 8 == 0: in or out as a whole).  Offsets of the elements
+  // kk and, MODE 1, channel and tap of each, advanced by additions; an element past the last is out of range there or not asked for.
+  int wk[2], wc[2], woff[2];
+  bool w_in[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    tb[i] = tap_of(MODE == 0 ? G::template minor<true>(tid) : G::template major<false>(tid, i));
-    bat[i] = n0 + (MODE == 0 ? G::template major<true>(tid, i) : G::template minor<false>(tid));
+    wk[i] = MODE == 0 ? G::template minor<true>(tid) : G::template major<false>(tid, i);
+    const int bat = n0 + (MODE == 0 ? G::template major<true>(tid, i) : G::template minor<false>(tid));
+    w_in[i] = bat < g.NC;
+    wc[i] = wk[i] % g.CA;
+    woff[i] = MODE == 0 ? bat * g.Kred + wk[i] : (wc[i] * RS + wk[i] / g.CA) * g.NC + bat;
   }
+  const int w_step = (dc * RS + dtap) * g.NC, w_wrap = (1 - g.CA * RS) * g.NC;
   auto load_weights = [&](int i) {
-    const bool ok = (bat[i] < g.NC) & (tb[i].kk < g.Kred);
-    const unsigned off = MODE == 0 ? (unsigned)(bat[i] * g.Kred + tb[i].kk) * 4u
-                                   : (unsigned)((tb[i].c * RS + tb[i].r * g.S + tb[i].s) * g.NC + bat[i]) * 4u;
-    if (MODE == 0) tb[i].kk += G::BK; else next_stage(tb[i]);
-    return buffer_load_f4(rb, ok ? off : kOutOfRange);
+    const unsigned off = w_in[i] & (wk[i] < g.Kred) ? (unsigned)woff[i] * 4u : kOutOfRange;
+    wk[i] += G::BK;
+    if (MODE == 0) {
+      woff[i] += G::BK;
+    } else {
+      const int c = wc[i] + dc;
+      const bool wrap = c >= g.CA;
+      wc[i] = c - (wrap ? g.CA : 0);
+      woff[i] += w_step + (wrap ? w_wrap : 0);
+    }
+    return buffer_load_f4(rb, off);
   };
 
   // a lane holds runs of four consecutive channels of one pixel (NC % 8 == 0: in or out as a whole)
@@ -306,43 +323,27 @@ __device__ __forceinline__ void wgrad_f32_block(const Blk& blk, const float* __r
   const __amdgpu_buffer_rsrc_t rd = tensor_rsrc(dy, g.dy_bytes), rx = tensor_rsrc(x, g.x_bytes);
 
   const int kcol = k0 + G::template minor<false>(tid), jcol = j0 + G::template minor<false>(tid);   // (K, J, C are multiples of 8: four are in or out)
-  const bool k_ok = kcol < g.K, j_ok = jcol < g.J;
-  int br, bs, bc;
-  {
-    const int rs = j_ok ? jcol / g.C : 0;
-    bc = j_ok ? jcol - rs * g.C : 0;
-    br = rs / g.S;
-    bs = rs - br * g.S;
-  }
-  br -= g.pad; bs -= g.pad;
-  int dm[2], pm[2], pn[2], pp[2], pq[2];               // the two pixels of the next stage: of dy, of x
+  const bool k_ok = kcol < g.K;
+  // the two pixels of the next stage: of dy, of x, both advanced by additions (pixels past the end lie past both tensors: zeros)
+  const WgradSteps steps = wgrad_steps<4>(g);
+  WgradPixel px[2];
+  unsigned dm[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    dm[i] = pm[i] = G::template major<false>(tid, i);
-    pq[i] = pm[i] % g.Q;
-    const int t = pm[i] / g.Q;
-    pp[i] = t % g.P;
-    pn[i] = t / g.P;
+    const int m = G::template major<false>(tid, i);
+    px[i].template init<4>(g, jcol, m);
+    dm[i] = (unsigned)(m * g.K + kcol) * 4u;
   }
+  const unsigned d_step = (unsigned)(G::BK * g.K) * 4u;
   auto load_dy = [&](int i) {
-    const unsigned off = (unsigned)(dm[i] * g.K + kcol) * 4u;
-    const bool ok = (dm[i] < g.M) & k_ok;
-    dm[i] += G::BK;
-    return buffer_load_f4(rd, ok ? off : kOutOfRange);
+    const unsigned off = dm[i];
+    dm[i] += d_step;
+    return buffer_load_f4(rd, k_ok ? off : kOutOfRange);
   };
   auto load_x = [&](int i) {
-    const int h = pp[i] * g.stride + br, w = pq[i] * g.stride + bs;
-    const bool ok = (pm[i] < g.M) & j_ok & ((unsigned)h < (unsigned)g.H) & ((unsigned)w < (unsigned)g.W);
-    const unsigned off = (unsigned)(((pn[i] * g.H + h) * g.W + w) * g.C + bc) * 4u;
-    pm[i] += G::BK;
-    int q = pq[i] + g.dq;
-    const int c1 = q >= g.Q ? 1 : 0;
-    pq[i] = q - (c1 ? g.Q : 0);
-    int p = pp[i] + g.dp + c1;
-    const int c2 = p >= g.P ? 1 : 0;
-    pp[i] = p - (c2 ? g.P : 0);
-    pn[i] += g.dn + c2;
-    return buffer_load_f4(rx, ok ? off : kOutOfRange);
+    const unsigned off = px[i].in_image(steps) ? px[i].off : kOutOfRange;
+    px[i].advance(steps);
+    return buffer_load_f4(rx, off);
   };
   typename F::Acc acc;
 #pragma unroll

@@ -730,25 +730,26 @@ __device__ __forceinline__ bf16x8 lds_read_tr8(const bf16_t* p, int row_pitch) {
   return __builtin_bit_cast(bf16x8, v);
 }
 
-// The chunk of x that a thread of the weight-gradient kernels stages: its tap and first channel are fixed, its pixel of dy advances by 32 a
-// step.  Row and column of x under the tap, and the byte offset, are advanced by additions: the products of the full form (four 32-bit
+// The chunk of x that a thread of the weight-gradient kernels stages: its tap and first channel are fixed, its pixel of dy advances by as many a
+// step as dn, dp and dq stand for (32; F32Gemm::BK).  Row and column of x under the tap, and the byte offset, are advanced by additions: the products of the full form (four 32-bit
 // multiplications, 16 cycles each) cost as much as the step's matrix instructions.  Measured beside the loads behind the products:
 // wgrad_dma_kernel 188 -> 160 us (192 channels, 3 x 3, 200704 pixels), 171 -> 141 us (768 channels, 12544 pixels).
 struct WgradSteps {                      // the same for every thread
   int H, W, dq, dp, stride, wrap_w, wrap_h;
-  unsigned step, row, image;             // bytes: 32 pixels on; from one row of dy, and from one image, to the next
+  unsigned step, row, image;             // bytes: a step's pixels on; from one row of dy, and from one image, to the next
 };
+template <int ES = 2>                    // bytes of an element
 __device__ __forceinline__ WgradSteps wgrad_steps(const WgradTrArgs& g) {
   const int dq = g.dq * g.stride, dp = g.dp * g.stride, ww = g.Q * g.stride, wh = g.P * g.stride;
-  return WgradSteps{g.H, g.W, dq, dp, g.stride, ww, wh, (unsigned)((g.dn * g.H * g.W + dp * g.W + dq) * g.C) * 2u,
-                    (unsigned)((g.stride * g.W - ww) * g.C) * 2u, (unsigned)((g.H - wh) * g.W * g.C) * 2u};
+  return WgradSteps{g.H, g.W, dq, dp, g.stride, ww, wh, (unsigned)((g.dn * g.H * g.W + dp * g.W + dq) * g.C) * ES,
+                    (unsigned)((g.stride * g.W - ww) * g.C) * ES, (unsigned)((g.H - wh) * g.W * g.C) * ES};
 }
 struct WgradPixel {
   int h, w, hend, wend;                  // row and column of x; their limits
   unsigned off;                          // byte offset, meaningful where row and column lie in the image
   bool col;                              // the column of the gradient exists
   // column chunk jcol (elements) of pixel m
-  __device__ __forceinline__ void init(const WgradTrArgs& g, int jcol, int m) {
+  template <int ES = 2> __device__ __forceinline__ void init(const WgradTrArgs& g, int jcol, int m) {
     col = jcol < g.J;
     const int rs = col ? jcol / g.C : 0, c = col ? jcol - rs * g.C : 0;
     const int r = rs / g.S, s = rs - r * g.S;
@@ -758,7 +759,7 @@ struct WgradPixel {
     w = q * g.stride + s - g.pad;
     hend = g.P * g.stride + r - g.pad;
     wend = g.Q * g.stride + s - g.pad;
-    off = (unsigned)(((n * g.H + h) * g.W + w) * g.C + c) * 2u;
+    off = (unsigned)(((n * g.H + h) * g.W + w) * g.C + c) * ES;
   }
   // (a pixel past the last lies past the end of x as well: the descriptor turns it into zeros)
   __device__ __forceinline__ bool in_image(const WgradSteps& t) const { return col && (unsigned)h < (unsigned)t.H && (unsigned)w < (unsigned)t.W; }
