@@ -311,25 +311,8 @@ template <> __device__ __forceinline__ float as_stored<bf16_t>(float v) { return
 // res (optional): a residual add fused into the pass, z = res_act(stored(act(bn(y))) + res): the same
 // numbers as storing the normalised tensor and adding in a second kernel, without that tensor
 template <class T, bool STREAM>
-__device__ __forceinline__ void bn_apply_block(const Blk& blk, const T* __restrict__ y, T* __restrict__ z,
-                                                       const float* __restrict__ mean,
-                                                       const float* __restrict__ invstd,
-                                                       const float* __restrict__ gamma,
-                                                       const float* __restrict__ beta, long M, int Cp,
-                                                       int act, ColGrid g, const T* __restrict__ res, int res_act) {
-  const int ncv = Cp / 8;
-  const int cv_lane = threadIdx.x % g.cvl, row_lane = threadIdx.x / g.cvl, rl = 256 / g.cvl;
-  const int cv = blk.x * g.cvl + cv_lane;
-  if (cv >= ncv || row_lane >= rl) return;
-  const long r0 = blk.y * g.rows_per_chunk;
-  const long r1 = min(M, r0 + g.rows_per_chunk);
-  float mu[8], a[8], b[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const int c = cv * 8 + k;
-    mu[k] = mean[c]; a[k] = gamma[c] * invstd[c]; b[k] = beta[c];
-  }
-  long r = r0 + row_lane;
+__device__ __forceinline__ void bn_apply_rows(const T* __restrict__ y, T* __restrict__ z, const float (&mu)[8], const float (&a)[8], const float (&b)[8],
+                                              int cv, int ncv, long r, long r1, int rl, int act, const T* __restrict__ res, int res_act) {
   for (; r + 3 * rl < r1; r += 4 * rl) {             // four rows (with a residual: eight loads) in flight
     typename IO<T>::Raw yr[4], sr[4];
 #pragma unroll
@@ -367,6 +350,27 @@ __device__ __forceinline__ void bn_apply_block(const Blk& blk, const T* __restri
     }
     IO<T>::template st_t<STREAM>(z + (r * ncv + cv) * 8, v);
   }
+}
+template <class T, bool STREAM>
+__device__ __forceinline__ void bn_apply_block(const Blk& blk, const T* __restrict__ y, T* __restrict__ z,
+                                                       const float* __restrict__ mean,
+                                                       const float* __restrict__ invstd,
+                                                       const float* __restrict__ gamma,
+                                                       const float* __restrict__ beta, long M, int Cp,
+                                                       int act, ColGrid g, const T* __restrict__ res, int res_act) {
+  const int ncv = Cp / 8;
+  const int cv_lane = threadIdx.x % g.cvl, row_lane = threadIdx.x / g.cvl, rl = 256 / g.cvl;
+  const int cv = blk.x * g.cvl + cv_lane;
+  if (cv >= ncv || row_lane >= rl) return;
+  const long r0 = blk.y * g.rows_per_chunk;
+  const long r1 = min(M, r0 + g.rows_per_chunk);
+  float mu[8], a[8], b[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int c = cv * 8 + k;
+    mu[k] = mean[c]; a[k] = gamma[c] * invstd[c]; b[k] = beta[c];
+  }
+  bn_apply_rows<T, STREAM>(y, z, mu, a, b, cv, ncv, r0 + row_lane, r1, rl, act, res, res_act);
 }
 template <class T, bool STREAM = false>
 __global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ y,
@@ -520,6 +524,83 @@ __device__ __forceinline__ void regroup_partials_block(const Blk& blk, const flo
 }
 __global__ void regroup_partials_kernel(const float* __restrict__ part, float* __restrict__ out, int chunks, int n, int per) {
   regroup_partials_block(one_block(), part, out, chunks, n, per);
+}
+
+// The elementwise passes of small tensors add the partial sums themselves: no finalize launch between the reduction and them, and instead of the
+// whole-column kernels where a column is long.  A workgroup has at most 64 channels (whole 128-byte lines of bf16) and adds their sums,
+// kSumChunksMax partial sums at most, in double: thread = (lane, channel), lane l adds chunks l, l + lanes, ... and the lanes are added in order.
+// All workgroups of a slab come to the same numbers; those of the first row chunk store them.
+// What bounds them is the launch: 8 MB tensors stream in ~2 us, the sums of 64 chunks are two rounds of loads from the caches.
+constexpr int kSumChunksMax = 128, kSumChannels = 64;
+struct SlabSums { double part[2][256]; float co[2][kSumChannels]; };
+__device__ __forceinline__ void slab_sums(SlabSums& s, const float* __restrict__ part, int chunks, int Cp, int c0, int n, double& s1, double& s2) {
+  const int ch = threadIdx.x % n, lane = threadIdx.x / n, lanes = 256 / n;
+  double a = 0.0, b = 0.0;
+  if (c0 + ch < Cp && lane < lanes) {
+    const float* p = part + c0 + ch;
+    for (int k = lane; k < chunks; k += 8 * lanes) {
+      float u[8], v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {                  // (past the last chunk: the last one, not added)
+        const long at = (long)min(k + i * lanes, chunks - 1) * 2 * Cp;
+        u[i] = p[at]; v[i] = p[at + Cp];
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const bool in = k + i * lanes < chunks;
+        a += in ? (double)u[i] : 0.0;
+        b += in ? (double)v[i] : 0.0;
+      }
+    }
+  }
+  s.part[0][threadIdx.x] = a;
+  s.part[1][threadIdx.x] = b;
+  __syncthreads();
+  s1 = s2 = 0.0;
+  if ((int)threadIdx.x < n)
+    for (int l = 0; l < lanes; ++l) { s1 += s.part[0][l * n + threadIdx.x]; s2 += s.part[1][l * n + threadIdx.x]; }
+}
+// bn_finalize_kernel and bn_apply_kernel (pivot: the row that the sums were shifted by, if any)
+template <class T>
+__device__ __forceinline__ void bn_apply_sums_block(const Blk& blk, const T* __restrict__ y, T* __restrict__ z, const float* __restrict__ part,
+    const T* __restrict__ pivot, int chunks, double m, float* mean, float* invstd, float* rmean, float* rvar, float eps, float rho,
+    const float* __restrict__ gamma, const float* __restrict__ beta, long M, int Cp, int act, ColGrid g, const T* __restrict__ res, int res_act) {
+  __shared__ SlabSums sh;
+  const int n = g.cvl * 8, c0 = blk.x * n, t = threadIdx.x;
+  double s1, s2;
+  slab_sums(sh, part, chunks, Cp, c0, n, s1, s2);
+  if (t < n && c0 + t < Cp) {
+    const int c = c0 + t;
+    const double shift = s1 / m, mu = (pivot ? (double)(float)pivot[c] : 0.0) + shift;
+    double var = s2 / m - shift * shift;
+    if (var < 0.0) var = 0.0;
+    const float is = (float)(1.0 / sqrt(var + (double)eps));
+    sh.co[0][t] = (float)mu;
+    sh.co[1][t] = is;
+    if (blk.y == 0) {
+      mean[c] = (float)mu;
+      invstd[c] = is;
+      rmean[c] = (1.f - rho) * rmean[c] + rho * (float)mu;
+      rvar[c] = (1.f - rho) * rvar[c] + rho * (float)(var * m / (m - 1.0));
+    }
+  }
+  __syncthreads();
+  const int ncv = Cp / 8, cv_lane = t % g.cvl, row_lane = t / g.cvl, rl = 256 / g.cvl, cv = blk.x * g.cvl + cv_lane;
+  if (cv >= ncv || row_lane >= rl) return;
+  const long r0 = blk.y * g.rows_per_chunk;
+  float mu[8], a[8], b[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int c = cv * 8 + k;
+    mu[k] = sh.co[0][cv_lane * 8 + k]; a[k] = gamma[c] * sh.co[1][cv_lane * 8 + k]; b[k] = beta[c];
+  }
+  bn_apply_rows<T, false>(y, z, mu, a, b, cv, ncv, r0 + row_lane, min(M, r0 + g.rows_per_chunk), rl, act, res, res_act);
+}
+template <class T>
+__global__ __launch_bounds__(256) void bn_apply_sums_kernel(const T* __restrict__ y, T* __restrict__ z, const float* __restrict__ part,
+    const T* __restrict__ pivot, int chunks, double m, float* mean, float* invstd, float* rmean, float* rvar, float eps, float rho,
+    const float* __restrict__ gamma, const float* __restrict__ beta, long M, int Cp, int act, ColGrid g, const T* __restrict__ res, int res_act) {
+  bn_apply_sums_block<T>(one_block(), y, z, part, pivot, chunks, m, mean, invstd, rmean, rvar, eps, rho, gamma, beta, M, Cp, act, g, res, res_act);
 }
 
 // BN backward, stage 1: with xhat = (y - mean)*invstd, pre = gamma*xhat + beta and
@@ -679,24 +760,10 @@ __global__ void bn_bwd_finalize_kernel(const float* __restrict__ part, int chunk
 
 // stage 3: gradient w.r.t. the convolution output, written to dy (dy == dz: in place; column-grid launch, each
 // thread reads its elements before it writes them)
+struct BnBwdCoef { float mu[8], a[8], b[8], is[8], c2[8], c3[8]; };
 template <class T, bool STREAM>
-__device__ __forceinline__ void bn_bwd_apply_block(const Blk& blk, const T* dz, T* dy, const T* __restrict__ y, const float* __restrict__ gamma,
-    const float* __restrict__ beta, const float* __restrict__ mean, const float* __restrict__ invstd,
-    const float* __restrict__ k2, const float* __restrict__ k3, long M, int Cp, int act, ColGrid g) {
-  const int ncv = Cp / 8;
-  const int cv_lane = threadIdx.x % g.cvl, row_lane = threadIdx.x / g.cvl, rl = 256 / g.cvl;
-  const int cv = blk.x * g.cvl + cv_lane;
-  if (cv >= ncv || row_lane >= rl) return;
-  const long r0 = blk.y * g.rows_per_chunk;
-  const long r1 = min(M, r0 + g.rows_per_chunk);
-  float mu[8], a[8], b[8], is[8], c2[8], c3[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const int c = cv * 8 + k;
-    mu[k] = mean[c]; is[k] = invstd[c]; a[k] = gamma[c] * is[k]; b[k] = beta[c];
-    c2[k] = k2[c]; c3[k] = k3[c];
-  }
-  long r = r0 + row_lane;
+__device__ __forceinline__ void bn_bwd_apply_rows(const T* dz, T* dy, const T* __restrict__ y, const BnBwdCoef& f, int cv, int ncv, long r, long r1, int rl, int act) {
+  const auto &mu = f.mu, &a = f.a, &b = f.b, &is = f.is, &c2 = f.c2, &c3 = f.c3;
   for (; r + 3 * rl < r1; r += 4 * rl) {             // four rows (eight loads) in flight
     typename IO<T>::Raw dr[4], yr[4];
 #pragma unroll
@@ -731,6 +798,65 @@ __device__ __forceinline__ void bn_bwd_apply_block(const Blk& blk, const T* dz, 
     }
     IO<T>::template st_t<STREAM>(dy + (r * ncv + cv) * 8, d);
   }
+}
+template <class T, bool STREAM>
+__device__ __forceinline__ void bn_bwd_apply_block(const Blk& blk, const T* dz, T* dy, const T* __restrict__ y, const float* __restrict__ gamma,
+    const float* __restrict__ beta, const float* __restrict__ mean, const float* __restrict__ invstd,
+    const float* __restrict__ k2, const float* __restrict__ k3, long M, int Cp, int act, ColGrid g) {
+  const int ncv = Cp / 8;
+  const int cv_lane = threadIdx.x % g.cvl, row_lane = threadIdx.x / g.cvl, rl = 256 / g.cvl;
+  const int cv = blk.x * g.cvl + cv_lane;
+  if (cv >= ncv || row_lane >= rl) return;
+  const long r0 = blk.y * g.rows_per_chunk;
+  const long r1 = min(M, r0 + g.rows_per_chunk);
+  BnBwdCoef f;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int c = cv * 8 + k;
+    f.mu[k] = mean[c]; f.is[k] = invstd[c]; f.a[k] = gamma[c] * f.is[k]; f.b[k] = beta[c];
+    f.c2[k] = k2[c]; f.c3[k] = k3[c];
+  }
+  bn_bwd_apply_rows<T, STREAM>(dz, dy, y, f, cv, ncv, r0 + row_lane, r1, rl, act);
+}
+// bn_bwd_finalize_kernel and bn_bwd_apply_kernel
+template <class T>
+__device__ __forceinline__ void bn_bwd_apply_sums_block(const Blk& blk, const T* dz, T* dy, const T* __restrict__ y, const float* __restrict__ part, int chunks,
+    double m, float* g_gamma, float* g_beta, const float* __restrict__ gamma, const float* __restrict__ beta, const float* __restrict__ mean,
+    const float* __restrict__ invstd, float* k2, float* k3, long M, int Cp, int act, ColGrid g) {
+  __shared__ SlabSums sh;
+  const int n = g.cvl * 8, c0 = blk.x * n, t = threadIdx.x;
+  double sb, sg;
+  slab_sums(sh, part, chunks, Cp, c0, n, sb, sg);
+  if (t < n && c0 + t < Cp) {
+    const int c = c0 + t;
+    const float v2 = (float)(sb / m), v3 = (float)(sg / m);
+    sh.co[0][t] = v2;
+    sh.co[1][t] = v3;
+    if (blk.y == 0) {
+      g_beta[c] = (float)sb;
+      g_gamma[c] = (float)sg;
+      k2[c] = v2;
+      k3[c] = v3;
+    }
+  }
+  __syncthreads();
+  const int ncv = Cp / 8, cv_lane = t % g.cvl, row_lane = t / g.cvl, rl = 256 / g.cvl, cv = blk.x * g.cvl + cv_lane;
+  if (cv >= ncv || row_lane >= rl) return;
+  const long r0 = blk.y * g.rows_per_chunk;
+  BnBwdCoef f;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int c = cv * 8 + k;
+    f.mu[k] = mean[c]; f.is[k] = invstd[c]; f.a[k] = gamma[c] * f.is[k]; f.b[k] = beta[c];
+    f.c2[k] = sh.co[0][cv_lane * 8 + k]; f.c3[k] = sh.co[1][cv_lane * 8 + k];
+  }
+  bn_bwd_apply_rows<T, false>(dz, dy, y, f, cv, ncv, r0 + row_lane, min(M, r0 + g.rows_per_chunk), rl, act);
+}
+template <class T>
+__global__ __launch_bounds__(256) void bn_bwd_apply_sums_kernel(const T* dz, T* dy, const T* __restrict__ y, const float* __restrict__ part, int chunks,
+    double m, float* g_gamma, float* g_beta, const float* __restrict__ gamma, const float* __restrict__ beta, const float* __restrict__ mean,
+    const float* __restrict__ invstd, float* k2, float* k3, long M, int Cp, int act, ColGrid g) {
+  bn_bwd_apply_sums_block<T>(one_block(), dz, dy, y, part, chunks, m, g_gamma, g_beta, gamma, beta, mean, invstd, k2, k3, M, Cp, act, g);
 }
 template <class T, bool STREAM = false>
 __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(const T* dz, T* dy,

@@ -295,6 +295,17 @@ ColGrid col_grid(long M, int Cp, int rows_per_thread = 8, int max_blocks = 512) 
 // on tensors of 100 MB and more (statistics 2.0 -> 1.5 ms, backward sums 3.4 -> 2.9 ms per ResNet-50 step)
 inline ColGrid bn_stats_grid(long M, int Cp) { return col_grid(M, Cp, 8, 1024); }
 inline ColGrid bn_bwd_grid(long M, int Cp) { return col_grid(M, Cp, 8, 1024); }
+// slabs of at most 64 channels, four rows a thread
+inline ColGrid slab_grid(long M, int Cp) {
+  ColGrid g;
+  const int ncv = Cp / 8;
+  g.slabs = (ncv + 7) / 8;
+  g.cvl = (ncv + g.slabs - 1) / g.slabs;
+  g.slabs = (ncv + g.cvl - 1) / g.cvl;
+  g.rows_per_chunk = (long)(256 / g.cvl) * 4;
+  g.chunks = (int)((M + g.rows_per_chunk - 1) / g.rows_per_chunk);
+  return g;
+}
 
 // Tiles and channel groups of a launch, and how many tiles a workgroup takes so that at most `blocks` workgroups result (or one
 // per group).  Not a few more, which would run behind the others on an empty chip: backward-weight of 128 x 17 x 17 x 960, where
@@ -788,6 +799,8 @@ int plan(pbd_ctx* c) {
         op.y = s; s += tensor_bytes(c, op.out);
         const ColGrid g = bn_bwd_grid(M, op.cout_p);   // the larger of the two reductions' grids
         need_red(((size_t)g.chunks * 2 * op.cout_p + (size_t)g.slabs * g.chunks) * 4);   // (+ one loss partial a workgroup)
+        const ColGrid gs = slab_grid(M, op.cout_p);
+        if (gs.chunks <= kSumChunksMax) need_red(((size_t)gs.chunks * 2 * op.cout_p + (size_t)gs.slabs * gs.chunks) * 4);
         if (op.dw) {
           const DwWgradCfg gw = dw_wgrad_cfg(bf && !c->o.force_direct, c->o.batch, op.in.h, op.in.w, op.out.h, op.out.w,
                                              op.cout_p, op.d.k, op.d.stride, op.d.pad);
@@ -966,7 +979,7 @@ const ManyTable& many_table() {
     put<&bn_bwd_finalize_block, 256, 1>(t, bn_bwd_finalize_kernel);
     PBD_MANY(1, bn_finalize, B, false); PBD_MANY(1, bn_finalize, B, true);
     PBD_MANY(1, bn_stats, B, false);
-    PBD_MANY(1, bn_apply, B, false);
+    PBD_MANY(1, bn_apply, B, false); PBD_MANY(1, bn_apply_sums, B); PBD_MANY(1, bn_bwd_apply_sums, B);
     PBD_MANY(1, bn_bwd_reduce, B, false, false, false);
     PBD_MANY(1, bn_bwd_apply, B, false);
     put<&bn_small_fwd_block<B>, kSmallThreads, 2>(t, bn_small_fwd_kernel<B>);
@@ -1083,6 +1096,15 @@ int residual_reader(const BlockPlan& bp, int j) {
 }
 // few enough rows for the whole-column BN kernels (one block per 8-channel slab)
 inline bool short_column(long M) { return M <= (long)kSmallThreads * kSmallRows; }
+// The batch norm of a student layer with M rows of Cp channels takes the elementwise passes that add their partial sums themselves
+// (bn_apply_sums_kernel, bn_bwd_apply_sums_kernel): of long columns in both directions, where a finalize launch is 4 us of its block's
+// chain, of columns from kColumnRows to 4096 rows on the way back, where the whole-column kernel pays a 128-byte line for every 16 bytes it
+// uses (512 channels: 16.7 us).  Their reductions add four rows a thread before the lanes, half of what the wide ones do.
+constexpr long kColumnRows = 2048;
+constexpr double kSumsBytes = 8.0 * 1048576.0;
+template <class T> inline bool adds_sums(long M, int Cp) {
+  return M > kColumnRows && (double)M * Cp * sizeof(T) <= kSumsBytes && slab_grid(M, Cp).chunks <= kSumChunksMax;
+}
 // For student layer j: the index of a max-pool that is the only reader of j's output (the pool then normalises what
 // it reads and the normalised tensor is never written), else -1.
 int pool_reader(const BlockPlan& bp, int j, int batch) {
@@ -2042,9 +2064,13 @@ template <class T> struct Exec {
           const T* pivot = y;                       // the pass of its own shifts by the first row
           int chunks = stat_tiles;
           const bool groups = dw_rows || expands(c, op);   // a mean, a sum of squares and a count each
+          const bool applies = pool_reader(bp, (int)j, N) < 0 && !folds_into((int)j + 1);
+          const bool adds = adds_sums<T>(M, op.cout_p) && applies && !groups;
           if (groups) {
             pivot = nullptr;
             if (dw_rows) chunks = dw_rows;
+          } else if (stat_tiles && adds && stat_tiles <= kSumChunksMax) {
+            pivot = nullptr;
           } else if (stat_tiles) {
             // the convolution's store left one pair of sums per row tile (no pivot); thousands of them are
             // first summed in groups so that the finalize kernel's walk stays short
@@ -2057,18 +2083,20 @@ template <class T> struct Exec {
               part = out; chunks = sums;
             }
           } else {
-            const ColGrid g = bn_stats_grid(M, op.cout_p);
+            const ColGrid g = adds ? slab_grid(M, op.cout_p) : bn_stats_grid(M, op.cout_p);
             ProfScope ps(c, streams(op.out) ? "bn_stats_nt" : "bn_stats", bytes_of(op.out), 0, net, blk, opi);
             launch(c, streams(op.out) ? bn_stats_kernel<T, true> : bn_stats_kernel<T, false>, dim3(g.slabs, g.chunks), 256,
                    256 * 16 * sizeof(float), st, y, red(), M, op.cout_p, g);
             chunks = g.chunks;
           }
-          launch(c, groups ? bn_finalize_kernel<T, true> : bn_finalize_kernel<T>, op.cout_p / kFinalizeChannels, 256, 0, st, 
+          const bool self = adds && chunks <= kSumChunksMax;
+          if (!self)
+            launch(c, groups ? bn_finalize_kernel<T, true> : bn_finalize_kernel<T>, op.cout_p / kFinalizeChannels, 256, 0, st, 
               part, pivot, chunks, op.cout_p, (double)M, wsf(op.s_mean), wsf(op.s_invstd), wsf(op.s_rmean),
               wsf(op.s_rvar), c->o.bn_eps, c->o.bn_momentum, master + op.e_gamma, master + op.e_beta,
               folds_into((int)j + 1) || dw_bwd_fused(c, bp, (int)j) || pw_bwd_fused(c, bp, (int)j) ? wsf(op.s_keep) : (float*)nullptr);
-          if (pool_reader(bp, (int)j, N) < 0 && !folds_into((int)j + 1)) {
-            const ColGrid ga = col_grid(M, op.cout_p, 8, 4096);   // elementwise pass: many short workgroups
+          if (applies) {
+            const ColGrid ga = self ? slab_grid(M, op.cout_p) : col_grid(M, op.cout_p, 8, 4096);   // elementwise pass: many short workgroups
             // a residual add that only reads this layer's output rides along: the normalised tensor itself
             // is never written (the backward pass needs y and the sum, not it)
             const int rd = residual_reader(bp, (int)j);
@@ -2080,6 +2108,12 @@ template <class T> struct Exec {
               res_act = q.act;
               z = value(rd + 1);
               fused[rd] = 1;
+            }
+            if (self) {
+              ProfScope ps(c, res ? "bn_apply_add" : "bn_apply", (res ? 3 : 2) * bytes_of(op.out), 0, net, blk, opi);
+              launch(c, bn_apply_sums_kernel<T>, dim3(ga.slabs, ga.chunks), 256, 0, st, y, z, part, pivot, chunks, (double)M, wsf(op.s_mean), wsf(op.s_invstd),
+                     wsf(op.s_rmean), wsf(op.s_rvar), c->o.bn_eps, c->o.bn_momentum, master + op.e_gamma, master + op.e_beta, M, op.cout_p, op.d.act, ga, res, res_act);
+              continue;
             }
             const bool nt = streams(op.out);    // (profile classes: one per kernel instantiation)
             ProfScope ps(c, res ? (nt ? "bn_apply_add_nt" : "bn_apply_add") : (nt ? "bn_apply_nt" : "bn_apply"), (res ? 3 : 2) * bytes_of(op.out), 0, net, blk, opi);
@@ -2171,13 +2205,14 @@ template <class T> struct Exec {
         const long M = (long)N * op.out.h * op.out.w;
         const AddBwd ab = add_bwd[j];
         const T* dz_in = ab.dz ? ab.dstore : dz;     // what the last stage reads (dz: in place)
-        if (short_column(M)) {
+        if (short_column(M) && !adds_sums<T>(M, op.cout_p)) {
           ProfScope ps(c, "bn_small_bwd", 5 * bytes_of(op.out), 0, net, blk, opi);
           launch(c, bn_small_bwd_kernel<T>, op.cout_p / 8, kSmallThreads, 0, st, dz, y, master + op.e_gamma,
                  master + op.e_beta, wsf(op.s_mean), wsf(op.s_invstd), grad + op.e_gamma, grad + op.e_beta, (int)M,
                  op.cout_p, op.d.act, (unsigned)(M * op.cout_p * sizeof(T)));
         } else {
-          const ColGrid g = bn_bwd_grid(M, op.cout_p);
+          const bool self = adds_sums<T>(M, op.cout_p) && !summed[j] && !dw_bwd_fused(c, bp, j) && !pw_bwd_fused(c, bp, j);
+          const ColGrid g = self ? slab_grid(M, op.cout_p) : bn_bwd_grid(M, op.cout_p);
           if (summed[j]) {
           } else if (ab.loss) {
             float* loss_part = red() + (size_t)g.chunks * 2 * op.cout_p;
@@ -2202,7 +2237,7 @@ template <class T> struct Exec {
                 (const T*)dz, y, master + op.e_gamma, master + op.e_beta, wsf(op.s_mean), wsf(op.s_invstd), red(), M, op.cout_p,
                 op.d.act, g, (const T*)nullptr, 0, (T*)nullptr, (float*)nullptr, 0.f);
           }
-          if (!summed[j])
+          if (!summed[j] && !self)
             launch(c, bn_bwd_finalize_kernel, op.cout_p / kFinalizeChannels, 256, 0, st, red(), g.chunks, op.cout_p, (double)M,
                                                                              grad + op.e_gamma, grad + op.e_beta,
                                                                              wsf(op.s_k2), wsf(op.s_k3));
@@ -2219,7 +2254,12 @@ template <class T> struct Exec {
             if (wanted[iv]) have[iv] = 1;
             continue;
           }
-          {
+          if (self) {
+            const ColGrid ga = slab_grid(M, op.cout_p);
+            ProfScope ps(c, "bn_bwd_apply", 3 * bytes_of(op.out), 0, net, blk, opi);
+            launch(c, bn_bwd_apply_sums_kernel<T>, dim3(ga.slabs, ga.chunks), 256, 0, st, dz_in, dz, y, red(), g.chunks, (double)M, grad + op.e_gamma, grad + op.e_beta,
+                   master + op.e_gamma, master + op.e_beta, wsf(op.s_mean), wsf(op.s_invstd), wsf(op.s_k2), wsf(op.s_k3), M, op.cout_p, op.d.act, ga);
+          } else {
             const ColGrid ga = col_grid(M, op.cout_p, 8, 4096);
             ProfScope ps(c, streams(op.out) ? "bn_bwd_apply_nt" : "bn_bwd_apply", 3 * bytes_of(op.out), 0, net, blk, opi);
             launch(c, streams(op.out) ? bn_bwd_apply_kernel<T, true> : bn_bwd_apply_kernel<T, false>, dim3(ga.slabs, ga.chunks), 256, 0, st,
