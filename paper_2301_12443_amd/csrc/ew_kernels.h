@@ -443,7 +443,7 @@ __global__ __launch_bounds__(256) void bn_stats_kernel(const T* __restrict__ y,
 
 // Finalize kernels run 8 channels x 32 lanes per block (thread = lane * 8 + channel): lane l adds
 // chunks l, l+32, ... in order, the 8 lanes of a channel inside one wave are added by a butterfly and
-// the 4 waves in a fixed order (fixed association, independent of scheduling).  Few chunks per lane
+// the 4 waves in a fixed order (fixed association, independent of scheduling).  Few chunks per lane, eight of them requested at a time,
 // keep the chain of dependent loads short: these kernels sit between two passes over the tensor.
 // GROUPS: the chunks hold a mean, a sum of squares about it and a number of rows each (part[chunk][3][Cp]) instead of two
 // sums; s1 and s2 come out as the sums of y and y^2, in double.
@@ -455,16 +455,29 @@ __device__ __forceinline__ void finalize_sums(const float* __restrict__ part, in
   const int cl = threadIdx.x & (kFinalizeChannels - 1);
   double a = 0.0, b = 0.0;
   if (c < Cp) {
-#pragma unroll 4
-    for (int k = lane; k < chunks; k += 32) {
-      if (GROUPS) {
-        const float* p = part + (long)k * 3 * Cp + c;
-        const double mu = (double)p[0], n = (double)p[2 * Cp];
-        a += n * mu;
-        b += (double)p[Cp] + n * mu * mu;
-      } else {
-        a += (double)part[(long)k * 2 * Cp + c];
-        b += (double)part[(long)k * 2 * Cp + Cp + c];
+    // (a batch of loads in flight before the first addition; past the last chunk: the last one, not added)
+    constexpr int U = 8, W = GROUPS ? 3 : 2;
+    for (int k0 = lane; k0 < chunks; k0 += 32 * U) {
+      float v[U][W];
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        const float* p = part + (long)min(k0 + 32 * i, chunks - 1) * W * Cp + c;
+#pragma unroll
+        for (int w = 0; w < W; ++w) v[i][w] = p[(long)w * Cp];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        const bool in = k0 + 32 * i < chunks;
+        if (GROUPS) {
+          const double mu = (double)v[i][0], n = (double)v[i][W - 1];
+          const double a1 = n * mu, b1 = (double)v[i][1] + n * mu * mu;
+          a += in ? a1 : 0.0;
+          b += in ? b1 : 0.0;
+        } else {
+          a += in ? (double)v[i][0] : 0.0;
+          b += in ? (double)v[i][1] : 0.0;
+        }
       }
     }
   }
@@ -492,17 +505,19 @@ __device__ __forceinline__ void bn_finalize_block(const Blk& blk, const float* _
                                    float* rvar, float eps, float rho, const float* gamma, const float* beta, float* keep) {
   const int c = blk.x * kFinalizeChannels + (threadIdx.x & (kFinalizeChannels - 1)), lane = threadIdx.x >> 3;
   double s1, s2;
+  const int cl = min(c, Cp - 1);                     // (what the end needs besides the sums, requested ahead of them)
+  const float pivot = y ? (float)y[cl] : 0.f, ga = gamma[cl], be = beta[cl], rm = rmean[cl], rv = rvar[cl];   // y: the row the sums were shifted by, if any
   finalize_sums<GROUPS>(part, chunks, Cp, c, lane, s1, s2);
   if (c >= Cp || lane != 0) return;
   const double shift = s1 / m;
-  const double mu = (y ? (double)(float)y[c] : 0.0) + shift;     // y: the pivot row the sums were shifted by, if any
+  const double mu = (double)pivot + shift;
   double var = s2 / m - shift * shift;
   if (var < 0.0) var = 0.0;
-  if (keep) { keep[c] = gamma[c]; keep[Cp + c] = beta[c]; }
+  if (keep) { keep[c] = ga; keep[Cp + c] = be; }
   mean[c] = (float)mu;
   invstd[c] = (float)(1.0 / sqrt(var + (double)eps));
-  rmean[c] = (1.f - rho) * rmean[c] + rho * (float)mu;
-  rvar[c] = (1.f - rho) * rvar[c] + rho * (float)(var * m / (m - 1.0));
+  rmean[c] = (1.f - rho) * rm + rho * (float)mu;
+  rvar[c] = (1.f - rho) * rv + rho * (float)(var * m / (m - 1.0));
 }
 template <class T, bool GROUPS = false>
 __global__ void bn_finalize_kernel(const float* __restrict__ part, const T* __restrict__ y,
