@@ -499,11 +499,10 @@ DmaCfg dma_cfg(long M, int NC, int Kred, int CA, int num_cu, int epi) {
   // weight tile: measured 275.7 -> 252.6 us on 256 x 28 x 28 x 256 -> 256, 3 x 3, 784 tiles).
   // Short reductions behind a store without batch-norm sums (the teacher's, the accumulating backward-data ones)
   // run faster as two narrow workgroups per compute unit than as one wide one: one fills while the other stores
-  // (1024 -> 256 at 14 x 14, affine: 91 -> 66 us; 256 -> 96 accumulating at 56 x 56: 198 -> 176 us).  Measured per layer inside
-  // the ResNet-50 x1.5 step.  With the sums in the store up to 256 reduction elements, us wide / narrow at batch 256 and 64: 64 -> 256 at 56 x 56
-  // 120 / 102, 33.6 / 28.2; 96 -> 256 131 / 118, 38.0 / 32.2; 192 -> 512 at 28 x 28 83 / 75, 28.4 / 27.7; 256 -> 512 92 / 85, 31.1 / 31.1; above, 384 ->
-  // 1024 at 14 x 14 60.5 / 58.3, 20.3 / 21.8.  Whole 128-column tiles: 256 -> 192 at 56 x 56 on 96 columns 197 / 200.
-  const bool narrow = epi == EPI_STORE ? Kred <= 256 && NC % 128 == 0 : Kred <= 512 || (affine && Kred <= 1024 && NC >= 512);
+  // (1024 -> 256 at 14 x 14, affine: 91 -> 66 us; 256 -> 96 accumulating at 56 x 56: 198 -> 176 us); with the sums
+  // in the store the wide tile stays ahead (192 -> 512 at 28 x 28: 97 against 103 us).  Measured per layer inside
+  // the ResNet-50 x1.5 step.
+  const bool narrow = (epi == EPI_AFFINE_ACT || epi == EPI_ACCUM) && (Kred <= 512 || (affine && Kred <= 1024 && NC >= 512));
   static const int kBN[5] = {256, 192, 128, 96, 64};
   static const double kCost[5] = {1.0, 1.05, 1.15, 1.25, 1.4};
   double best = 1e30;
