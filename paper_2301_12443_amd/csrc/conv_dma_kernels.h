@@ -213,7 +213,9 @@ __device__ __forceinline__ void dma_tile(unsigned char* smem, float* ep_s, const
   }
   const int lps = a_cnt + b_cnt;
   constexpr int LPS_MAX = A_INSTR + B_INSTR;
-  const __amdgpu_buffer_rsrc_t a_rsrc = tensor_rsrc(A - before, g.a_bytes + (unsigned)before * 2u), b_rsrc = tensor_rsrc(Bw, g.b_bytes);
+  // (every offset is a valid one or kDmaSkip: a range beyond any scalar offset, which the range check subtracts from it; an image of a single
+  // row ends before the taps two rows further down begin)
+  const __amdgpu_buffer_rsrc_t a_rsrc = tensor_rsrc(A - before, kDmaSkip), b_rsrc = tensor_rsrc(Bw, g.b_bytes);
 
   // reduction position of the next stage to be loaded: kk = (r*S + s)*CA + c, uniform over the block
   int r = r0, s = s0, c = 0;

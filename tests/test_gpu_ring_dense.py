@@ -23,6 +23,8 @@ CASES = [
     (20, 21, 20, 128, 512, 1, 1),        # two
     (360, 5, 5, 64, 512, 3, 1),          # more than an image a step of the weight gradient
     (180, 7, 7, 64, 384, 3, 1),
+    (1, 1, 8200, 64, 512, 3, 1),         # one row: two of three filter rows lie outside, and beyond the end of the tensor
+    (1, 2, 4200, 64, 256, 5, 1),
     # 1 x 1 weight gradients on 192 x 256, 256 x 192 and 256 x 256 tiles, a ragged last step
     (73, 61, 59, 256, 192, 1, 1),
     (33, 65, 63, 192, 512, 1, 1),
