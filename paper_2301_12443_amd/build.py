@@ -10,7 +10,8 @@ LIB = os.path.join(HERE, "libpbd.so")
 SOURCES = [os.path.join(HERE, "csrc", "pbd.hip")]
 HEADERS = [os.path.join(HERE, "csrc", "ew_kernels.h"), os.path.join(HERE, "csrc", "conv_kernels.h"),
            os.path.join(HERE, "csrc", "conv_dma_kernels.h"), os.path.join(HERE, "csrc", "conv_f32_kernels.h"),
-           os.path.join(HERE, "csrc", "dw_mfma_kernels.h"), os.path.join(HERE, "csrc", "many.h"), os.path.join(HERE, "csrc", "pw_bwd_kernels.h"),
+           os.path.join(HERE, "csrc", "gather.h"), os.path.join(HERE, "csrc", "dw_mfma_kernels.h"),
+           os.path.join(HERE, "csrc", "many.h"), os.path.join(HERE, "csrc", "pw_bwd_kernels.h"),
            os.path.join(ROOT, "include", "pbd.h")]
 
 

@@ -45,6 +45,7 @@
 #include <type_traits>
 
 #include "conv_kernels.h"
+#include "gather.h"
 
 
 namespace pbd {
@@ -98,7 +99,6 @@ __device__ __forceinline__ void wait_vmcnt_dyn(int n) {
   }
 }
 
-constexpr unsigned kDmaSkip = 0xC0000000u;   // an offset that is out of range, also with a scalar offset of up to 1 GiB added
 constexpr int kDmaMaxTaps = 32;              // bits of a row's tap mask
 constexpr int kDmaThreads = 512;
 constexpr int kDmaBM = 256;      // rows of a big tile
@@ -162,7 +162,7 @@ __device__ __forceinline__ void dma_tile(unsigned char* smem, float* ep_s, const
   const int lrow = lane / CPR, slot = lane % CPR;
   auto swz = [](int row) { return BK == 64 ? (row >> 1) & 7 : (row >> 2) & 3; };
   // A lane's address is its row's, a_off, plus what the tap and channel add, which is the same for the whole block and rides in the
-  // load's scalar offset (never negative: the descriptor begins `before` elements ahead of the tensor).  Whether the tap lies in the image is
+  // load's scalar offset (gather.h).  Whether the tap lies in the image is
   // a bit of `skip`, set up once per tile: two vector operations a load where forming and testing the coordinates took about ten, which the
   // matrix cores waited for at the head of every step.
   unsigned a_off[A_INSTR], skip[A_INSTR];
@@ -172,7 +172,7 @@ __device__ __forceinline__ void dma_tile(unsigned char* smem, float* ep_s, const
   const bool runs = MODE == 0 && g.pix_shift != 0;
   const int pshift = runs ? 31 - __builtin_clz(pitch) : 0;
   const int row_bits = runs ? g.CA / BK : g.S;   // a run is tested step by step, S = 1
-  const int before = MODE == 0 ? g.pad * (g.WA + 1) * pitch : ((g.R - 1) * g.WA + g.S - 1) * g.CA >> sh;
+  const Gather gather{MODE == 0, g.R, g.S, g.pad, g.WA, MODE == 1 ? g.CA >> sh : pitch};
   const unsigned hlim = MODE == 0 ? (unsigned)g.HA : (unsigned)g.HA << sh;
   const unsigned wlim = MODE == 0 ? (unsigned)g.WA : (unsigned)g.WA << sh;
   int a_cnt = 0, b_cnt = 0;                      // loads this WAVE issues per stage (uniform)
@@ -190,8 +190,7 @@ __device__ __forceinline__ void dma_tile(unsigned char* smem, float* ep_s, const
     const int h0 = MODE == 0 ? a_ * g.stride - g.pad : (par ? 2 * a_ + ph : a_) + g.pad;
     const int w0 = MODE == 0 ? b_ * g.stride - g.pad : (par ? 2 * b_ + pw : b_) + g.pad;
     const int kc8 = (slot ^ swz(row)) * 8;
-    if (MODE == 0) a_off[i] = (unsigned)(((nbase + h0 * g.WA + w0) * pitch + kc8 + before) * 2);
-    else a_off[i] = (unsigned)((nbase * g.CA + ((h0 * g.WA + w0) * g.CA >> sh) + kc8) * 2);
+    a_off[i] = gather.row((unsigned)nbase * pitch, h0, w0, kc8);
     unsigned cols = 0, take = 0;
     for (int j = 0; j < row_bits; ++j) {
       const int w = MODE == 1 ? w0 - j : runs ? w0 + ((j * BK + kc8) >> pshift) : w0 + j;
@@ -209,20 +208,19 @@ __device__ __forceinline__ void dma_tile(unsigned char* smem, float* ep_s, const
     if ((i * 8 + wave) * 64 < B_CHUNKS) ++b_cnt;
     const int row = (i * 8 + wave) * RPI + lrow;
     const int kc = slot ^ swz(row);
-    bbase[i] = row < BN && n0 + row < g.NC ? (unsigned)((n0 + row) * g.Kred + kc * 8) * 2u : kDmaSkip;
+    bbase[i] = row < BN && n0 + row < g.NC ? (unsigned)((n0 + row) * g.Kred + kc * 8) * 2u : kGatherRange;
   }
   const int lps = a_cnt + b_cnt;
   constexpr int LPS_MAX = A_INSTR + B_INSTR;
-  // (every offset is a valid one or kDmaSkip: a range beyond any scalar offset, which the range check subtracts from it; an image of a single
-  // row ends before the taps two rows further down begin)
-  const __amdgpu_buffer_rsrc_t a_rsrc = tensor_rsrc(A - before, kDmaSkip), b_rsrc = tensor_rsrc(Bw, g.b_bytes);
+  // (every offset is a valid one or kGatherRange; the host has checked Gather::in_range.  The tensor's own end would not do: an image of a
+  // single row ends before the taps two rows further down begin)
+  const __amdgpu_buffer_rsrc_t a_rsrc = tensor_rsrc(A - gather.before(), kGatherRange), b_rsrc = tensor_rsrc(Bw, g.b_bytes);
 
   // reduction position of the next stage to be loaded: kk = (r*S + s)*CA + c, uniform over the block
   int r = r0, s = s0, c = 0;
   unsigned a_uni = 0, b_uni = 0, bit = 0;        // scalar offsets and bit of that position
   auto place = [&] {
-    const int tap = r * g.WA + s;
-    a_uni = MODE == 0 ? (unsigned)(tap * pitch + c) * 2u : (unsigned)(before - (tap * g.CA >> sh) + c) * 2u;
+    a_uni = gather.tap(r, s, c);
     b_uni = (unsigned)((r * g.S + s) * g.CA + c) * 2u;
     bit = (unsigned)(r * row_bits + (runs ? c / BK : s));
   };
@@ -242,7 +240,7 @@ __device__ __forceinline__ void dma_tile(unsigned char* smem, float* ep_s, const
     unsigned char* sa = smem + stage * STAGE + wave * 1024;
     if (u < A_INSTR) {
       if (A_CHUNKS % kDmaThreads == 0 || (u * 8 + wave) * 64 < A_CHUNKS)        // (uniform over the wave)
-        dma_load16(a_rsrc, sa + u * 8 * 1024, (skip[u] >> bit) & 1u ? kDmaSkip : a_off[u], a_uni);
+        dma_load16(a_rsrc, sa + u * 8 * 1024, (skip[u] >> bit) & 1u ? kGatherRange : a_off[u], a_uni);
     } else if (B_CHUNKS % kDmaThreads == 0 || ((u - A_INSTR) * 8 + wave) * 64 < B_CHUNKS) {
       dma_load16(b_rsrc, sa + A_BYTES + (u - A_INSTR) * 8 * 1024, bbase[u - A_INSTR], b_uni);
     }

@@ -1233,10 +1233,7 @@ template <class T> struct Exec {
   // reduction length and gathered channels of a dense convolution as it is run
   static int kred_of(const OpPlan& op) { return op.s2d ? kS2dK : op.d.k * op.d.k * op.cin_p; }
   // (a space-to-depth stem: 64 where the direct-to-LDS kernel takes it, which gathers a filter row at a time)
-  int ca_of(const OpPlan& op) const {
-    if (!op.s2d) return op.cin_p;
-    return dma_for((long)c->o.batch * op.out.h * op.out.w, op.d.c_out, kS2dK, 64).use ? 64 : 16;
-  }
+  int ca_of(const OpPlan& op) const { return !op.s2d ? op.cin_p : dma_fwd(op).use ? 64 : 16; }
   float* red() const {
     if (red_static) return red_static;
     const int lane = c->lanes.on ? c->lanes.lane : 0;
@@ -1279,11 +1276,18 @@ template <class T> struct Exec {
     const IgemmCfg cfg = igemm_cfg((long)c->o.batch * op.out.h * op.out.w, op.d.c_out, kred_of(op), ca_of(op));
     return cfg.splits == 1 && !(cfg.BM == 64 && cfg.BN == 32);      // (the 256-row kernel, where it is used, fuses it too)
   }
-  // the 256-row, direct-to-LDS kernel takes a launch when its tile count fills the chip and no split-K is wanted
-  DmaCfg dma_for(long M, int NC, int Kred, int CA, int epi = EPI_STORE) const {
+  // the 256-row, direct-to-LDS kernel takes a launch when its tile count fills the chip, no split-K is wanted and its offsets reach
+  // (a_bytes: of the gathered tensor)
+  DmaCfg dma_for(long M, int NC, int Kred, int CA, const Gather& gather, long a_bytes, int epi) const {
     DmaCfg d = dma_cfg(M, NC, Kred, CA, c->num_cu, epi);
-    if (d.use && igemm_cfg(M, NC, Kred, CA).splits != 1) d.use = false;
+    if (d.use && (igemm_cfg(M, NC, Kred, CA).splits != 1 || !gather.in_range(a_bytes, CA))) d.use = false;
     return d;
+  }
+  // ... of op's forward pass
+  DmaCfg dma_fwd(const OpPlan& op, int epi = EPI_STORE) const {
+    const Gather gather = op.s2d ? Gather{true, 4, 1, 2, op.in.w / 2, 16} : Gather{true, op.d.k, op.d.k, op.d.pad, op.in.w, op.cin_p};
+    const long a_bytes = (long)c->o.batch * op.in.h * op.in.w * (op.s2d ? 4 : op.cin_p) * 2;
+    return dma_for((long)c->o.batch * op.out.h * op.out.w, op.d.c_out, kred_of(op), op.s2d ? 64 : op.cin_p, gather, a_bytes, epi);
   }
   // Row tiles whose staged store also delivers the batch-norm sums of the convolution's output (0: the
   // layer takes its statistics in a pass of its own).  Same conditions as fuses_residual, whole channel
@@ -1292,7 +1296,7 @@ template <class T> struct Exec {
     const long M = (long)c->o.batch * op.out.h * op.out.w;
     if (expands(c, op)) return pw_fwd_args(M, op.cin_p, op.d.c_out).pblocks;
     if (!fuses_residual(op) || op.d.c_out % 8 != 0 || short_column(M)) return 0;
-    const DmaCfg d = dma_for(M, op.d.c_out, kred_of(op), ca_of(op));
+    const DmaCfg d = dma_fwd(op);
     if (d.use) return d.big_m + d.tail_m;
     const IgemmCfg cfg = igemm_cfg(M, op.d.c_out, kred_of(op), ca_of(op));
     return (int)((M + cfg.BM - 1) / cfg.BM);
@@ -1322,7 +1326,7 @@ template <class T> struct Exec {
           // 4 x 4, stride 1, two rows / columns of padding in front, over the space-to-depth copy of the input
           g.HA = op.in.h / 2; g.WA = op.in.w / 2; g.CA = 16; g.R = g.S = 4; g.stride = 1; g.pad = 2; g.Kred = kS2dK;
           // the four taps of a filter row are 64 contiguous elements: one tap of four pixels to the direct-to-LDS kernel
-          if (dma_for(g.M, g.NC, kS2dK, 64, a ? EPI_AFFINE_ACT : EPI_STORE).use) { g.CA = 64; g.S = 1; g.pix_shift = 2; }
+          if (dma_fwd(op, a ? EPI_AFFINE_ACT : EPI_STORE).use) { g.CA = 64; g.S = 1; g.pix_shift = 2; }
           g.a_bytes = (unsigned)((size_t)N * g.HA * g.WA * 16 * 2); g.b_bytes = (unsigned)(op.d.c_out * kS2dK * 2);
           x = s2d_input();
           w = reinterpret_cast<const T*>(c->ws + op.w2);
@@ -1361,7 +1365,8 @@ template <class T> struct Exec {
   template <int MODE>
   void launch_igemm(IgemmArgs g, const bf16_t* A, const bf16_t* Bw, bf16_t* out, const float* a,
                     const float* b, int act, int epi, double bytes, double flops) {
-    DmaCfg dc = dma_for(g.M, g.NC, g.Kred, g.CA, epi);
+    const Gather gather{MODE == 0, g.R, g.S, g.pad, g.WA, MODE == 1 && g.stride == 2 ? g.CA / 2 : g.CA >> g.pix_shift};
+    DmaCfg dc = dma_for(g.M, g.NC, g.Kred, g.CA, gather, g.a_bytes, epi);
     g.stream_out = (double)g.M * g.NC * 2.0 >= 64.0 * 1048576.0;   // (as for the batch-norm passes: see streams())
     if (MODE == 1 && g.par_classes) {
       // parity classes: par_classes x ceil(rows of a class / 256) row tiles, no tail tiles
