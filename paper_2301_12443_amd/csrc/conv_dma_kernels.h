@@ -21,11 +21,12 @@
 //    in LDS, and every wave has read stage kt), requests the first fragments of stage kt+1 and issues the last products of
 //    stage kt with the loads of stage kt+NS, into the buffer of stage kt, one behind each product.  So the matrix cores have work
 //    while the fragments and the loads are on their way.
-//  * A load costs two vector operations: a row's offset is fixed, the tap's is a scalar, and whether the tap lies in the image is a
-//    bit of a mask that is set up once per tile.  Forming and testing the coordinates for every load, all of them at the head of the
+//  * A load costs two vector operations: a row's offset is fixed, the tap's is a scalar, and whether the tap lies in the image is
+//    in a mask that is set up once per tile.  Forming and testing the coordinates for every load, all of them at the head of the
 //    step, kept the matrix cores waiting for ~430 of a step's ~4300 cycles in each of a SIMD's two waves.  Before and after (both points), same
 //    bits, us: 384 -> 384, 3 x 3, 50176 pixels 165 -> 144 (805 -> 925 TFLOP/s), 768 -> 768, 12544 180 -> 159, 192 -> 192, 200704
-//    163 -> 147, 256 -> 256, 200704 257 -> 240; 1024 -> 384, 1 x 1 62 -> 56; memory-bound 1 x 1 layers as before.  Raised wave
+//    163 -> 147, 256 -> 256, 200704 257 -> 240; 1024 -> 384, 1 x 1 62 -> 56; 256 -> 256, 7 x 7, 50176 338 -> 286 (445 on the 128-row
+//    kernel), 128 -> 128 115 -> 102 (153); memory-bound 1 x 1 layers as before.  Raised wave
 //    priority around the products and four or five stages of the 32-wide step gave nothing.
 //  * Fragment reads are ds_read_b128 in inline assembly with their own s_waitcnt lgkmcnt: the compiler
 //    would otherwise order every LDS read behind ALL outstanding direct-to-LDS loads (it cannot tell the
@@ -99,7 +100,6 @@ __device__ __forceinline__ void wait_vmcnt_dyn(int n) {
   }
 }
 
-constexpr int kDmaMaxTaps = 32;              // bits of a row's tap mask
 constexpr int kDmaThreads = 512;
 constexpr int kDmaBM = 256;      // rows of a big tile
 constexpr int kDmaTailBM = 64;   // rows of a tail tile
@@ -163,15 +163,15 @@ __device__ __forceinline__ void dma_tile(unsigned char* smem, float* ep_s, const
   auto swz = [](int row) { return BK == 64 ? (row >> 1) & 7 : (row >> 2) & 3; };
   // A lane's address is its row's, a_off, plus what the tap and channel add, which is the same for the whole block and rides in the
   // load's scalar offset (gather.h).  Whether the tap lies in the image is
-  // a bit of `skip`, set up once per tile: two vector operations a load where forming and testing the coordinates took about ten, which the
-  // matrix cores waited for at the head of every step.
+  // two bits of `skip`, its row's and its column's (of filters of up to 7 x 7), set up once per tile: a load tests them with one scalar mask, where
+  // forming and testing the coordinates took about ten vector operations, which the matrix cores waited for at the head of every step.
   unsigned a_off[A_INSTR], skip[A_INSTR];
   // elements between neighbouring pixels of A: the channel count, except for a tap that spans several pixels
   // (g.pix_shift > 0: CA = a run of CA >> pix_shift-wide pixels, each range-tested on its own)
   const int pitch = MODE == 0 && g.pix_shift ? g.CA >> g.pix_shift : g.CA;
   const bool runs = MODE == 0 && g.pix_shift != 0;
   const int pshift = runs ? 31 - __builtin_clz(pitch) : 0;
-  const int row_bits = runs ? g.CA / BK : g.S;   // a run is tested step by step, S = 1
+  const int col_bits = runs ? g.CA / BK : g.S;   // a run is tested step by step, S = 1
   const Gather gather{MODE == 0, g.R, g.S, g.pad, g.WA, MODE == 1 ? g.CA >> sh : pitch};
   const unsigned hlim = MODE == 0 ? (unsigned)g.HA : (unsigned)g.HA << sh;
   const unsigned wlim = MODE == 0 ? (unsigned)g.WA : (unsigned)g.WA << sh;
@@ -191,16 +191,16 @@ __device__ __forceinline__ void dma_tile(unsigned char* smem, float* ep_s, const
     const int w0 = MODE == 0 ? b_ * g.stride - g.pad : (par ? 2 * b_ + pw : b_) + g.pad;
     const int kc8 = (slot ^ swz(row)) * 8;
     a_off[i] = gather.row((unsigned)nbase * pitch, h0, w0, kc8);
-    unsigned cols = 0, take = 0;
-    for (int j = 0; j < row_bits; ++j) {
+    unsigned cols = 0, rows = 0;
+    for (int j = 0; j < col_bits; ++j) {
       const int w = MODE == 1 ? w0 - j : runs ? w0 + ((j * BK + kc8) >> pshift) : w0 + j;
       cols |= ((unsigned)w < wlim && (MODE == 0 || (w & smask) == 0) ? 1u : 0u) << j;
     }
     for (int j = 0; j < g.R; ++j) {
       const int h = MODE == 0 ? h0 + j : h0 - j;
-      take |= ((unsigned)h < hlim && (MODE == 0 || (h & smask) == 0) ? cols : 0u) << (j * row_bits);
+      rows |= ((unsigned)h < hlim && (MODE == 0 || (h & smask) == 0) ? 1u : 0u) << j;
     }
-    skip[i] = valid ? ~take : ~0u;
+    skip[i] = valid ? ~(cols | rows << col_bits) : ~0u;
   }
   unsigned bbase[B_INSTR];
 #pragma unroll
@@ -218,15 +218,15 @@ __device__ __forceinline__ void dma_tile(unsigned char* smem, float* ep_s, const
 
   // reduction position of the next stage to be loaded: kk = (r*S + s)*CA + c, uniform over the block
   int r = r0, s = s0, c = 0;
-  unsigned a_uni = 0, b_uni = 0, bit = 0;        // scalar offsets and bit of that position
+  unsigned a_uni = 0, b_uni = 0, here = 0;       // scalar offsets and bits of that position
   auto place = [&] {
     a_uni = gather.tap(r, s, c);
     b_uni = (unsigned)((r * g.S + s) * g.CA + c) * 2u;
-    bit = (unsigned)(r * row_bits + (runs ? c / BK : s));
+    here = 1u << (runs ? c / BK : s) | 1u << (col_bits + r);
   };
   auto advance = [&] {
     c += BK; a_uni += 2 * BK; b_uni += 2 * BK;
-    if (runs) ++bit;
+    if (runs) here += here & ((1u << col_bits) - 1);   // (the column's bit moves on)
     if (c >= g.CA) {                             // the next tap
       c = 0;
       s += tstep;
@@ -240,7 +240,7 @@ __device__ __forceinline__ void dma_tile(unsigned char* smem, float* ep_s, const
     unsigned char* sa = smem + stage * STAGE + wave * 1024;
     if (u < A_INSTR) {
       if (A_CHUNKS % kDmaThreads == 0 || (u * 8 + wave) * 64 < A_CHUNKS)        // (uniform over the wave)
-        dma_load16(a_rsrc, sa + u * 8 * 1024, (skip[u] >> bit) & 1u ? kGatherRange : a_off[u], a_uni);
+        dma_load16(a_rsrc, sa + u * 8 * 1024, skip[u] & here ? kGatherRange : a_off[u], a_uni);
     } else if (B_CHUNKS % kDmaThreads == 0 || ((u - A_INSTR) * 8 + wave) * 64 < B_CHUNKS) {
       dma_load16(b_rsrc, sa + A_BYTES + (u - A_INSTR) * 8 * 1024, bbase[u - A_INSTR], b_uni);
     }

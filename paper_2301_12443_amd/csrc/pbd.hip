@@ -479,8 +479,8 @@ int igemm_splits(long M, int NC, int Kred, int CA) { return igemm_cfg(M, NC, Kre
 
 // Launch shape of igemm_dma_kernel (256-row tiles, operands straight into LDS) for one dense layer, or use = false
 // when the layer keeps igemm_kernel: channel counts that are no multiple of 32, fewer tiles than most of the
-// compute units (there 128- and 64-row tiles and split-K fill the chip better), reductions shorter than 256
-// (one or two steps per tile: nothing to pipeline), and filters of more taps than a row's mask has bits (6 x 6 and larger).
+// compute units (there 128- and 64-row tiles and split-K fill the chip better), and reductions shorter than 256
+// (one or two steps per tile: nothing to pipeline).
 struct DmaCfg { bool use; int BN, BK, tiles_n, big_m, tail_m; };
 // epi: what the store does (EPI_AFFINE_ACT: a folded batch norm and activation, the frozen teacher's layers)
 DmaCfg dma_cfg(long M, int NC, int Kred, int CA, int num_cu, int epi) {
@@ -491,7 +491,7 @@ DmaCfg dma_cfg(long M, int NC, int Kred, int CA, int num_cu, int epi) {
   // student 96 -> 256 at 56 x 56 178 -> 162 us, 192 -> 512 at 28 x 28 126 -> 96 us; teacher 64 -> 256 with the fused
   // residual 233 -> 183 us, 128 -> 512 140 -> 105 us on the narrow tiles chosen below); filters from 256 reduction
   // elements on.
-  if (Kred < (Kred == CA ? 64 : 256) || Kred / CA > kDmaMaxTaps) return d;
+  if (Kred < (Kred == CA ? 64 : 256)) return d;
   const long tm = (M + kDmaBM - 1) / kDmaBM;
   // One workgroup per compute unit is resident: time ~ rounds x columns of the tile (a little more per column for
   // narrow tiles, whose fragments feed fewer MFMAs).  A last round that fills at most a quarter of the units is

@@ -4,8 +4,10 @@ parity class and by pixel; reductions of fewer steps than the ring has stages; r
 images of more and of less than a step of 32.  Every operation of the block against the plain fp64 oracle primitives on the tensors that the
 library read, at the bounds of local_parity.py (a wrong tap or pixel is off by the size of the result)."""
 import pytest
+import torch
 
 import local_parity
+import parity
 from paper_2301_12443_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -32,12 +34,36 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("n,h,w,ci,co,k,s", CASES)
-def test_addresses_of_the_direct_to_lds_kernels(n, h, w, ci, co, k, s):
+def _layer(n, h, w, ci, co, k, s):
     t, b = W.Block(), W.Block()
     t.cba(0, co, k, s, act=W.ACT_NONE)
     v = b.cba(0, ci, 1, act=W.ACT_RELU)
     b.cba(v, co, k, s, act=W.ACT_NONE)
-    wl = W.Workload("dense_ring", n, (ci, h, w), [t], [b], "bf16", lr=0.05)
-    worst = local_parity.run_and_check(wl, n)
+    return W.Workload("dense_ring", n, (ci, h, w), [t], [b], "bf16", lr=0.05)
+
+
+def _check(wl):
+    worst = local_parity.run_and_check(wl, wl.batch)
     print(", ".join(f"{key} {e:.1e}" for key, e in sorted(worst.items())), flush=True)
+
+
+def _classes(wl):
+    """The profile classes of the layer's launches, student and teacher."""
+    d = parity.make_distiller(wl, wl.batch, "bf16")
+    x = torch.from_numpy(W.make_input(wl)).cuda()
+    d.set_profile(True)
+    d.teacher_relay(x)
+    d.student_step(1, wl.lr)
+    return [p["name"] for p in d.get_profile() if (p["net"], p["op"]) in ((1, 1), (0, 0))]
+
+
+@pytest.mark.parametrize("n,h,w,ci,co,k,s", CASES)
+def test_addresses_of_the_direct_to_lds_kernels(n, h, w, ci, co, k, s):
+    _check(_layer(n, h, w, ci, co, k, s))
+
+
+@pytest.mark.parametrize("k", [6, 7])
+def test_filters_of_more_taps_than_a_word_has_bits(k):
+    wl = _layer(30, 39, 40, 64, 64, k, 1)
+    assert {"igemm_fwd_256x64x32_store", "igemm_fwd_256x64x32_affine", "igemm_dgrad_256x64x32_store"} <= set(_classes(wl))
+    _check(wl)
