@@ -2115,7 +2115,7 @@ template <class T> struct Exec {
               fused[rd] = 1;
             }
             if (self) {
-              ProfScope ps(c, res ? "bn_apply_add" : "bn_apply", (res ? 3 : 2) * bytes_of(op.out), 0, net, blk, opi);
+              ProfScope ps(c, res ? "bn_apply_sums_add" : "bn_apply_sums", (res ? 3 : 2) * bytes_of(op.out), 0, net, blk, opi);
               launch(c, bn_apply_sums_kernel<T>, dim3(ga.slabs, ga.chunks), 256, 0, st, y, z, part, pivot, chunks, (double)M, wsf(op.s_mean), wsf(op.s_invstd),
                      wsf(op.s_rmean), wsf(op.s_rvar), c->o.bn_eps, c->o.bn_momentum, master + op.e_gamma, master + op.e_beta, M, op.cout_p, op.d.act, ga, res, res_act);
               continue;
@@ -2261,7 +2261,7 @@ template <class T> struct Exec {
           }
           if (self) {
             const ColGrid ga = slab_grid(M, op.cout_p);
-            ProfScope ps(c, "bn_bwd_apply", 3 * bytes_of(op.out), 0, net, blk, opi);
+            ProfScope ps(c, "bn_bwd_apply_sums", 3 * bytes_of(op.out), 0, net, blk, opi);
             launch(c, bn_bwd_apply_sums_kernel<T>, dim3(ga.slabs, ga.chunks), 256, 0, st, dz_in, dz, y, red(), g.chunks, (double)M, grad + op.e_gamma, grad + op.e_beta,
                    master + op.e_gamma, master + op.e_beta, wsf(op.s_mean), wsf(op.s_invstd), wsf(op.s_k2), wsf(op.s_k3), M, op.cout_p, op.d.act, ga);
           } else {
