@@ -89,6 +89,30 @@ def test_the_gradient_read_is_the_one_the_kernel_used(c, act, last):
     np.testing.assert_array_equal(d.read_grad_value(0, e - 1), dy)
 
 
+def _beside_the_default_stream(make, busy):
+    """A distiller whose stream does not share a hardware queue with the legacy default stream: streams are dealt out to a few queues in the
+    order in which the process made them, and what waits in one queue runs in order whatever its stream.  make() brings a new one on a stream of its own,
+    busy() keeps the default stream at work for a while."""
+    made = []
+    for _ in range(8):
+        d = make()
+        made.append(d)
+        one = torch.zeros(1, device="cuda")
+        torch.cuda.synchronize()
+        busy()
+        end, done = torch.cuda.Event(), torch.cuda.Event()
+        end.record()
+        with torch.cuda.stream(d._stream):
+            one.add_(1)
+            done.record()
+        done.synchronize()
+        beside = not end.query()
+        torch.cuda.synchronize()
+        if beside:
+            return d
+    pytest.fail("every stream shares the default stream's hardware queue")
+
+
 def test_reading_a_gradient_waits_for_the_bound_stream_alone():
     """read_grad_value of an expand layer and of a depthwise one, whose gradient is formed on request, while another stream (the legacy
     default one) is busy for some hundred times as long as the read takes."""
@@ -96,17 +120,20 @@ def test_reading_a_gradient_waits_for_the_bound_stream_alone():
     t = W.Block()
     t.cba(0, 16, 1, act=W.ACT_NONE)
     wl = W.Workload("pw_bwd", n, (16, h, w), [t], [_block(16, 96, W.ACT_RELU6, 3, 1, True)], "bf16", lr=0.05)
-    d = parity.make_distiller(wl, n, "bf16")
-    d.teacher_relay(torch.from_numpy(W.make_input(wl, batch=n)).cuda())
-    assert {"pw_bwd_bn", "dw_wgrad_mfma_bn_k3"} <= set(_classes(d, wl))
-    d.sync()
     a = torch.randn(8192, 8192, device="cuda", dtype=torch.bfloat16)
     out = a @ a
     torch.cuda.synchronize()
+
+    def keep_busy(products):
+        for _ in range(products):
+            torch.matmul(a, a, out=out)
+    d = _beside_the_default_stream(lambda: parity.make_distiller(wl, n, "bf16"), lambda: keep_busy(60))
+    d.teacher_relay(torch.from_numpy(W.make_input(wl, batch=n)).cuda())
+    assert {"pw_bwd_bn", "dw_wgrad_mfma_bn_k3"} <= set(_classes(d, wl))
+    d.sync()
     for v in (1, 2):
         want = d.read_grad_value(0, v)
-        for _ in range(600):                           # 0.4 s and more
-            torch.matmul(a, a, out=out)
+        keep_busy(600)                                 # 0.4 s and more
         end = torch.cuda.Event()
         end.record()
         got = d.read_grad_value(0, v)
