@@ -64,6 +64,18 @@ def test_together_and_one_by_one(n, h, w, build, stride, precision):
                                               err_msg=f"step {step}, op {j}, slot {slot}, kind {kind}")
 
 
+@pytest.mark.parametrize("precision", ["bf16", "f32"])
+@pytest.mark.parametrize("n,h,w,build,stride", CASES)
+def test_fewer_launches_than_layers(n, h, w, build, stride, precision):
+    wl = _workload(n, h, w, build, stride, precision)
+    d = parity.make_distiller(wl, n, precision)
+    d.teacher_relay(torch.from_numpy(W.make_input(wl, batch=n)).cuda())
+    d.set_profile(True)
+    d.student_step(1, wl.lr)
+    launches = [p["name"] for p in d.get_profile() if p["name"].startswith("wgrad_")]
+    assert len(launches) < sum(op.type == W.OP_CBA and op.groups == 1 for op in wl.student[0].ops), launches
+
+
 @pytest.mark.parametrize("n,h,w,build,stride", CASES[:3])
 def test_against_the_oracle(n, h, w, build, stride):
     wl = _workload(n, h, w, build, stride, "bf16")
