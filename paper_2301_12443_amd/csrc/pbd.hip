@@ -396,7 +396,7 @@ inline DwWgradCfg dw_wgrad_cfg(bool bf16, int N, int h_in, int w_in, int h_out, 
 inline DwArgs dw_bwd_args(int N, int h, int w, int Cp, int k, bool arch) { return dw_args(N, h, w, Cp, (k == 7 ? 512 : 768) + (arch ? 256 : 0)); }
 
 struct WgradCfg { int TM, TN, BKP, tiles_k, tiles_j, splits, pix_per_split; bool dma; };
-// taps = R * S of the layer (J = taps * C).  Layers with a filter (taps > 1), whole 64- or 96-channel groups and a
+// taps = R * S of the layer (J = taps * C).  Layers with a filter (taps > 1), output channels in multiples of 192 or 256 and a
 // long pixel range take wgrad_dma_kernel: TM x TN tiles, one workgroup per compute unit, the pixel range cut
 // so that about 256 workgroups result.  So do 1 x 1 layers whose channels fill such tiles, where a workgroup gets kWgradDmaPixels
 // pixels or more.  Everything else (short or narrow 1 x 1 layers, stems) keeps wgrad_tr_kernel.
@@ -499,9 +499,10 @@ DmaCfg dma_cfg(long M, int NC, int Kred, int CA, int num_cu, int epi) {
   // weight tile: measured 275.7 -> 252.6 us on 256 x 28 x 28 x 256 -> 256, 3 x 3, 784 tiles).
   // Short reductions behind a store without batch-norm sums (the teacher's, the accumulating backward-data ones)
   // run faster as two narrow workgroups per compute unit than as one wide one: one fills while the other stores
-  // (1024 -> 256 at 14 x 14, affine: 91 -> 66 us; 256 -> 96 accumulating at 56 x 56: 198 -> 176 us); with the sums
-  // in the store the wide tile stays ahead (192 -> 512 at 28 x 28: 97 against 103 us).  Measured per layer inside
-  // the ResNet-50 x1.5 step.
+  // (1024 -> 256 at 14 x 14, affine: 91 -> 66 us; 256 -> 96 accumulating at 56 x 56: 198 -> 176 us).  With the
+  // sums in the store they are faster too (64 -> 256 at 56 x 56 120 -> 102 us, 192 -> 512 at 28 x 28 83 -> 75), but the wide tile stays: the
+  // row tiles fix the order in which the batch norm's sums are added, and another order moves single rectifier bits of everything behind.
+  // Measured per layer inside the ResNet-50 x1.5 step.
   const bool narrow = (epi == EPI_AFFINE_ACT || epi == EPI_ACCUM) && (Kred <= 512 || (affine && Kred <= 1024 && NC >= 512));
   static const int kBN[5] = {256, 192, 128, 96, 64};
   static const double kCost[5] = {1.0, 1.05, 1.15, 1.25, 1.4};
@@ -636,8 +637,10 @@ inline size_t all_red(const BlockPlan& bp) { return bp.red_bytes + bp.lane_bytes
 // the pixels, and with it its bits.  reached: values whose gradient the weight round forms.  Layers that another kernel forms on the way stay with
 // it, those of wgrad_dma_kernel fill the chip by themselves.
 // Of up to kLateBytes of input and output and kLateElems partial sums, which are read again from the caches or nearly so.  us a step, none late / 4 M
-// partial sums and 32 MB / 160 MB / 16 M and 160 MB: VGG-16 at batch 256, pipelined, 1284 / 1219 / 1223 / 1224, at batch 85 999 / 908 / 916 / 918,
-// MobileNetV2 at batch 33 1853 / 1773 / 1778 / 1783 (with 1 M: 1261, 952, 1841); ResNet-50 x1.5 at batch 64 and 256 level.  One cut for all of a block's
+// partial sums and 32 MB / 16 M and 160 MB: VGG-16 at batch 256, pipelined, 1284 / 1219 / 1224, at batch 85 999 / 908 / 918,
+// MobileNetV2 at batch 33 1853 / 1773 / 1783 (with 1 M: 1261, 952, 1841); ResNet-50 x1.5 at batch 64 and 256 level.  The line in bytes is flat (4 M with
+// 32 / 64 / 160 MB, twice each in turn: 1174, 1174 / 1171, 1176 / 1169, 1170; 914, 916 / 914, 915 / 916, 915; 1760, 1759 / 1757, 1757 / 1759, 1758; float32
+// VGG-16 at batch 64 1692, 1687 / 1682, 1685 / 1687, 1681; ResNet-50 x1.5 at batch 64 9049, 8994 / 9044, 9004 / 9014, 9025).  One cut for all of a block's
 // layers, of fewer and longer sums, was faster still (VGG-16 at batch 85 -1 %, ResNet-50 x1.5 at batch 64 -4 %), but its gradients were up to 4 times
 // as far from 64-bit sums.
 constexpr double kLateBytes = 64.0 * 1048576.0;
@@ -2074,8 +2077,6 @@ template <class T> struct Exec {
           if (groups) {
             pivot = nullptr;
             if (dw_rows) chunks = dw_rows;
-          } else if (stat_tiles && adds && stat_tiles <= kSumChunksMax) {
-            pivot = nullptr;
           } else if (stat_tiles) {
             // the convolution's store left one pair of sums per row tile (no pivot); thousands of them are
             // first summed in groups so that the finalize kernel's walk stays short
