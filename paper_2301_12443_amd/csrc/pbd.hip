@@ -295,7 +295,7 @@ ColGrid col_grid(long M, int Cp, int rows_per_thread = 8, int max_blocks = 512) 
 // on tensors of 100 MB and more (statistics 2.0 -> 1.5 ms, backward sums 3.4 -> 2.9 ms per ResNet-50 step)
 inline ColGrid bn_stats_grid(long M, int Cp) { return col_grid(M, Cp, 8, 1024); }
 inline ColGrid bn_bwd_grid(long M, int Cp) { return col_grid(M, Cp, 8, 1024); }
-// slabs of at most 64 channels, four rows a thread
+// slabs of at most 64 channels, four rows a thread (up to 1024 a chunk, where the separate passes' 256 chunks have as few as 32: the lanes in double)
 inline ColGrid slab_grid(long M, int Cp) {
   ColGrid g;
   const int ncv = Cp / 8;
@@ -304,6 +304,7 @@ inline ColGrid slab_grid(long M, int Cp) {
   g.slabs = (ncv + g.cvl - 1) / g.cvl;
   g.rows_per_chunk = (long)(256 / g.cvl) * 4;
   g.chunks = (int)((M + g.rows_per_chunk - 1) / g.rows_per_chunk);
+  g.join64 = true;
   return g;
 }
 
@@ -1102,7 +1103,7 @@ inline bool short_column(long M) { return M <= (long)kSmallThreads * kSmallRows;
 // The batch norm of a student layer with M rows of Cp channels takes the elementwise passes that add their partial sums themselves
 // (bn_apply_sums_kernel, bn_bwd_apply_sums_kernel): of long columns in both directions, where a finalize launch is 4 us of its block's
 // chain, of columns from kColumnRows to 4096 rows on the way back, where the whole-column kernel pays a 128-byte line for every 16 bytes it
-// uses (512 channels: 16.7 us).  Their reductions add four rows a thread before the lanes, half of what the wide ones do.
+// uses (512 channels: 16.7 us).  Their reductions add four rows a thread, and the lanes in double.
 constexpr long kColumnRows = 2048;
 constexpr double kSumsBytes = 8.0 * 1048576.0;
 template <class T> inline bool adds_sums(long M, int Cp) {

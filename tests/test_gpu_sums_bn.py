@@ -2,6 +2,7 @@
 side of the rule's lines (2048 rows, 4096 for the adds that ride in the passes, 8 MB), one to many slabs of unequal width, sums from the convolution's
 store and from a pass of their own, a residual add in both passes, a block's loss.  Every operation against the plain fp64 oracle primitives on the
 tensors that the library read, at the bounds of local_parity.py; the profile classes say which kernels ran."""
+import numpy as np
 import pytest
 import torch
 
@@ -49,3 +50,35 @@ def test_elementwise_passes_that_add_the_sums(n, h, w, c, precision):
     assert ("bn_bwd_apply_sums" in names) == (small and m > 2048), names
     few = precision == "f32" or -(-m // 64) <= 128                # (bfloat16: as many partial sums as the convolution's store has row tiles)
     assert (not names.isdisjoint({"bn_apply_sums", "bn_apply_sums_add"})) == (small and few and m > 4096), names
+
+
+@pytest.mark.parametrize("n,h,w,c", [(7, 33, 35, 48), (16, 31, 31, 40), (64, 16, 16, 64)])
+def test_float32_means_round_once_a_chunk(n, h, w, c):
+    """The mean's distance from its 64-bit value over the float32 differences from the pivot that the library adds, in standard deviations, 2-norm
+    over channels and seeds, against what the roundings on its way give: three additions in a thread, one at the end of a chunk, one of the
+    result, each up to half a unit in the last place (2^-24 of the value, over sqrt 3 as a 2-norm; less above a power of two).  Row lanes added in float, in
+    order, are beyond it (48 channels: 1.5e-8)."""
+    unit = 2.0 ** -24 / np.sqrt(3.0)
+    errors, bounds = [], []
+    for seed in range(6):
+        t, b = W.Block(), W.Block()
+        t.cba(0, c, 1, act=W.ACT_NONE)
+        b.cba(0, c, 1, act=W.ACT_NONE)
+        wl = W.Workload("bn_sums", n, (16, h, w), [t], [b], "f32", lr=0.05)
+        wl.seed = seed
+        d = parity.make_distiller(wl, n, "f32")
+        d.teacher_relay(torch.from_numpy(W.make_input(wl, batch=n)).cuda())
+        d.student_step(1, wl.lr)
+        y = d.read_conv_out(0, 0).transpose(0, 2, 3, 1).reshape(-1, c)
+        term = (y - y[0]).astype(np.float64)               # (float32 differences)
+        m, std = len(y), y.astype(np.float64).std(0)
+        mean = y[0].astype(np.float64) + term.mean(0)
+        errors.append((d.read_batch_stats(0, 0)[0] - mean) / std)
+        vectors = c // 8
+        lanes = 256 // -(-vectors // ((vectors + 7) // 8))
+        term = np.concatenate([term, np.zeros((-m % (4 * lanes), c))]).reshape(-1, 4, lanes, c)
+        roundings = [np.cumsum(term, axis=1)[:, 1:].reshape(-1, c), term.sum((1, 2))]
+        bounds.append((sum(((unit * r) ** 2).sum(0) for r in roundings) / m ** 2 + (unit * mean) ** 2) / std ** 2)
+    error, bound = np.sqrt(np.mean(np.square(errors))), np.sqrt(np.mean(bounds))
+    print(f"{error:.2e} of {bound:.2e}", flush=True)
+    assert error < bound
