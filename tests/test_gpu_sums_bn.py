@@ -82,3 +82,30 @@ def test_float32_means_round_once_a_chunk(n, h, w, c):
     error, bound = np.sqrt(np.mean(np.square(errors))), np.sqrt(np.mean(bounds))
     print(f"{error:.2e} of {bound:.2e}", flush=True)
     assert error < bound
+
+
+@pytest.mark.parametrize("n,h,w,c", [(7, 33, 35, 48), (16, 31, 31, 40), (64, 16, 16, 64)])
+def test_bfloat16_losses_round_once_a_chunk(n, h, w, c):
+    """The loss that rides in the reduction, relative to 64 bits on the tensors that the library read, 2-norm over 24 seeds: the result's rounding (its last
+    place, over sqrt 12) and one of each chunk's sum; a fifth more for what 24 draws of a rounding may be above their mean (two standard
+    deviations).  Rows and threads added in float are beyond it (40 channels: 4.5e-8)."""
+    errors, bounds = [], []
+    for seed in range(24):
+        t, b = W.Block(), W.Block()
+        t.cba(0, c, 1, act=W.ACT_NONE)
+        v = b.cba(0, c, 1, act=W.ACT_RELU)
+        b.add(v, b.cba(v, c, 1, act=W.ACT_NONE), act=W.ACT_RELU)
+        wl = W.Workload("bn_sums", n, (16, h, w), [t], [b], "bf16", lr=0.05)
+        wl.seed = seed
+        d = parity.make_distiller(wl, n, "bf16")
+        d.teacher_relay(torch.from_numpy(W.make_input(wl, batch=n)).cuda())
+        d.student_step(1, wl.lr)
+        d.sync()
+        s, a = d.read_value(0, 3).astype(np.float64), d.read_act(1).astype(np.float64)
+        loss = np.mean((s - a) ** 2)
+        chunks = -(-n * h * w // (256 // (c // 8) * 4))
+        errors.append(d.losses[0].item() / loss - 1.0)
+        bounds.append((np.spacing(np.float32(loss)) / loss) ** 2 / 12 + 2.0 ** -48 / 3 / chunks)
+    error, bound = np.sqrt(np.mean(np.square(errors))), 1.2 * np.sqrt(np.mean(bounds))
+    print(f"{error:.2e} of {bound:.2e}", flush=True)
+    assert error < bound
