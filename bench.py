@@ -25,14 +25,15 @@ LR_ALPHA = 0.005          # learning rate of the architecture parameters in the 
 # 256 MiB copy (fetch x2.000, write x1.000).  Counters cannot be read from inside the process: the
 # figures are CARRIED from the counter runs whose commands and full tables are in the named file
 # under profiles/ (the record says so under roofline.traffic_source), and apply only to the workload
-# and the kernel build they were measured on.
+# and the kernel build they were measured on: (bytes, launches of the class in a step then), and a class
+# that has more or fewer launches now gets no figure.
 HBM_TRAFFIC_PER_LAUNCH = {
     "resnet50_x1.5": ("profiles/resnet50_x1.5_step_hbm_traffic.md", {
-        "bn_bwd_apply_nt": 529362959, "bn_bwd_apply": 109015272, "bn_bwd_reduce_nt": 316315223, "bn_bwd_reduce": 68903370,
-        "bn_bwd_reduce_add_nt": 783209493, "bn_bwd_reduce_add_mse_nt": 961371582,
-        "wgrad_128x128": 305611219, "wgrad_192x256": 237289843, "wgrad_256x256": 218329889,
-        "igemm_fwd_256x192x64_store": 233869020, "igemm_dgrad_256x192x64_store": 166897786,
-        "igemm_fwd_256x256x64_affine": 111665417, "igemm_fwd_256x256x64_store": 212692777,
+        "bn_bwd_apply_nt": (529407386, 33), "bn_bwd_apply": (109004800, 20), "bn_bwd_reduce_nt": (316455936, 20),
+        "bn_bwd_reduce": (68914995, 17), "bn_bwd_reduce_add_nt": (783271629, 10), "bn_bwd_reduce_add_mse_nt": (961436160, 3),
+        "wgrad_128x128": (517230080, 8), "wgrad_192x256": (275603456, 20), "wgrad_256x256": (203073536, 12),
+        "wgrad_256x192": (248386765, 10), "igemm_fwd_256x192x64_store": (233527091, 26), "igemm_fwd_256x128x32_affine": (350143795, 30),
+        "igemm_dgrad_256x192x64_store": (166576128, 23), "igemm_fwd_256x256x64_affine": (111706726, 11), "igemm_fwd_256x256x64_store": (212673946, 17),
     }),
 }
 
@@ -141,6 +142,16 @@ def roofline_from_profile(prof, steps):
     return dict(bound=bound, achieved=round(achieved, 2), peak=peak, unit=unit, frac=round(achieved / peak, 4),
                 traffic=None, kernel=name, avg_launch_us=round(avg_s * 1e6, 2),
                 launches_per_step=a["n"] // steps, class_launches_per_step=agg[name]["n"] // steps), classes, totals
+
+
+def carry_traffic(roof, config):
+    """Put the counted HBM bytes of a launch beside the class that is reported, where the class is still what was counted: as
+    many launches a step, all of them on the reported side of the ridge (counters were averaged over the whole class)."""
+    src, table = HBM_TRAFFIC_PER_LAUNCH.get(config, (None, {}))
+    nbytes, launches = table.get(roof["kernel"], (None, None))
+    if nbytes and roof["launches_per_step"] == roof["class_launches_per_step"] == launches:
+        roof["traffic"] = nbytes
+        roof["traffic_source"] = f"carried from the rocprofv3 --pmc runs recorded in {src}, not measured in this run"
 
 
 def measure_peaks(torch):
@@ -339,10 +350,7 @@ def main():
     progress("event-timed step done")
     roof, classes, totals = roofline_from_profile(prof, psteps)
     conv, elementwise = family_fractions(prof, psteps)
-    src, table = HBM_TRAFFIC_PER_LAUNCH.get(args.config, (None, {}))
-    if roof["kernel"] in table and roof["launches_per_step"] == roof["class_launches_per_step"]:
-        roof["traffic"] = table[roof["kernel"]]          # counters were averaged over the whole class
-        roof["traffic_source"] = f"carried from the rocprofv3 --pmc runs recorded in {src}, not measured in this run"
+    carry_traffic(roof, args.config)
     if args.classes:
         for k, v in classes.items():
             print(f"{k:24s} {v}", file=sys.stderr)

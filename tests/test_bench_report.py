@@ -71,6 +71,24 @@ def test_float32_convolutions_count_against_the_fp32_matrix_cores(name):
     assert conv["frac_of_mfma_peak"] == pytest.approx(conv["TFLOPs"] / bench.PEAK_FP32_MFMA_TFLOPS, abs=1e-4)
 
 
+def test_counted_traffic_is_carried_only_while_the_class_is_what_was_counted():
+    name, (nbytes, launches) = next(iter(bench.HBM_TRAFFIC_PER_LAUNCH["resnet50_x1.5"][1].items()))
+
+    for config in ("resnet50_x1.5", "vgg16_dsconv"):
+        roof = dict(kernel=name, traffic=None, launches_per_step=launches, class_launches_per_step=launches)
+        bench.carry_traffic(roof, config)
+        assert roof["traffic"] == (nbytes if config == "resnet50_x1.5" else None)
+    for key, other in (("launches_per_step", launches - 1), ("class_launches_per_step", launches + 1), ("kernel", "unknown")):
+        roof = dict(kernel=name, traffic=None, launches_per_step=launches, class_launches_per_step=launches)
+        roof[key] = other
+        bench.carry_traffic(roof, "resnet50_x1.5")
+        assert roof["traffic"] is None and "traffic_source" not in roof
+    # (other layers have joined the class since)
+    roof = dict(kernel=name, traffic=None, launches_per_step=launches + 10, class_launches_per_step=launches + 10)
+    bench.carry_traffic(roof, "resnet50_x1.5")
+    assert roof["traffic"] is None
+
+
 def test_more_than_one_gpu_is_refused(monkeypatch, capsys):
     monkeypatch.setattr("sys.argv", ["bench.py", "--gpus", "2"])
     with pytest.raises(SystemExit) as e:
