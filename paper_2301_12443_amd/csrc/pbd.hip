@@ -1104,9 +1104,15 @@ inline bool short_column(long M) { return M <= (long)kSmallThreads * kSmallRows;
 // (bn_apply_sums_kernel, bn_bwd_apply_sums_kernel): of long columns in both directions, where a finalize launch is 4 us of its block's
 // chain, of columns from kColumnRows to 4096 rows on the way back, where the whole-column kernel pays a 128-byte line for every 16 bytes it
 // uses (512 channels: 16.7 us).  Their reductions add four rows a thread, and the lanes in double.
-constexpr long kColumnRows = 2048;
+// Short columns of narrower rows, of which a line holds several, stay with the whole-column kernel: all of those under 64 bytes, those under 128 up to
+// kNarrowRows.  Whole-column / sums, six 1 x 1 layers, of the block's step, at 2100, 3000 and 4090 rows: bfloat16 8 channels 0.85, 0.81, 0.88, 16
+// 0.88, 0.85, 0.93, 32 0.93, 0.98, 0.99, 48 0.95, 0.95, 1.10 (3600 rows: 1.06), 64 1.01, 1.09, 1.13; float32 8 channels 0.89, 0.84, 0.88, 16 0.96, 0.95,
+// 1.03 (3600: 1.06), 32 1.08, 1.14, 1.20.
+constexpr long kColumnRows = 2048, kNarrowRows = 3500;
 constexpr double kSumsBytes = 8.0 * 1048576.0;
 template <class T> inline bool adds_sums(long M, int Cp) {
+  const long row = (long)Cp * sizeof(T);
+  if (short_column(M) && (row < 64 || (row < 128 && M <= kNarrowRows))) return false;
   return M > kColumnRows && (double)M * Cp * sizeof(T) <= kSumsBytes && slab_grid(M, Cp).chunks <= kSumChunksMax;
 }
 // For student layer j: the index of a max-pool that is the only reader of j's output (the pool then normalises what

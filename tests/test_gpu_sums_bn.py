@@ -1,5 +1,5 @@
 """Batch norms whose elementwise passes add the partial sums themselves (bn_apply_sums_kernel, bn_bwd_apply_sums_kernel): column lengths on either
-side of the rule's lines (2048 rows, 4096 for the adds that ride in the passes, 8 MB), one to many slabs of unequal width, sums from the convolution's
+side of the rule's lines (2048 rows, 3500 and 4096 for narrow ones, 4096 for the adds that ride in the passes, 8 MB), one to many slabs of unequal width, sums from the convolution's
 store and from a pass of their own, a residual add in both passes, a block's loss.  Every operation against the plain fp64 oracle primitives on the
 tensors that the library read, at the bounds of local_parity.py; the profile classes say which kernels ran."""
 import numpy as np
@@ -15,7 +15,11 @@ pytestmark = pytest.mark.gpu
 # (batch, h, w, channels)
 CASES = [
     (1, 32, 64, 24),             # 2048 rows: the whole-column kernels
-    (3, 1, 683, 8),              # 2049 rows, one vector of channels
+    (3, 1, 683, 8),              # 2049 narrow rows: again
+    (1, 1, 3500, 24),            # the last of 48 and 96 bytes
+    (1, 1, 3501, 32),            # the first of 64; 128
+    (3, 1, 683, 64),             # 2049 rows
+    (3, 1, 1367, 8),             # 4101 rows, one vector of channels
     (5, 19, 23, 72),             # nine vectors: slabs of five and four
     (64, 8, 8, 136),             # 4096 rows
     (17, 13, 19, 520),           # 4199 rows, nine slabs
@@ -47,7 +51,9 @@ def test_elementwise_passes_that_add_the_sums(n, h, w, c, precision):
     slabs = (c // 8 + 7) // 8
     rows = 256 // -(-(c // 8) // slabs) * 4                        # a chunk: four rows a thread, a slab's vectors side by side
     small = m * c * (2 if precision == "bf16" else 4) <= 8 << 20 and -(-m // rows) <= 128
-    assert ("bn_bwd_apply_sums" in names) == (small and m > 2048), names
+    row = c * (2 if precision == "bf16" else 4)
+    columns = m > (2048 if row >= 128 else 3500 if row >= 64 else 4096)
+    assert ("bn_bwd_apply_sums" in names) == (small and columns), names
     few = precision == "f32" or -(-m // 64) <= 128                # (bfloat16: as many partial sums as the convolution's store has row tiles)
     assert (not names.isdisjoint({"bn_apply_sums", "bn_apply_sums_add"})) == (small and few and m > 4096), names
 
