@@ -29,11 +29,11 @@ LR_ALPHA = 0.005          # learning rate of the architecture parameters in the 
 # that has more or fewer launches now gets no figure.
 HBM_TRAFFIC_PER_LAUNCH = {
     "resnet50_x1.5": ("profiles/resnet50_x1.5_step_hbm_traffic.md", {
-        "bn_bwd_apply_nt": (529407386, 33), "bn_bwd_apply": (109004800, 20), "bn_bwd_reduce_nt": (316455936, 20),
-        "bn_bwd_reduce": (68914995, 17), "bn_bwd_reduce_add_nt": (783271629, 10), "bn_bwd_reduce_add_mse_nt": (961436160, 3),
-        "wgrad_128x128": (517230080, 8), "wgrad_192x256": (275603456, 20), "wgrad_256x256": (203073536, 12),
-        "wgrad_256x192": (248386765, 10), "igemm_fwd_256x192x64_store": (233527091, 26), "igemm_fwd_256x128x32_affine": (350143795, 30),
-        "igemm_dgrad_256x192x64_store": (166576128, 23), "igemm_fwd_256x256x64_affine": (111706726, 11), "igemm_fwd_256x256x64_store": (212673946, 17),
+        "bn_bwd_apply_nt": (529406669, 33), "bn_bwd_apply": (109010739, 20), "bn_bwd_reduce_nt": (316405146, 20),
+        "bn_bwd_reduce": (68914790, 17), "bn_bwd_reduce_add_nt": (783262208, 10), "bn_bwd_reduce_add_mse_nt": (961451315, 3),
+        "wgrad_128x128": (517549773, 8), "wgrad_192x256": (275614310, 20), "wgrad_256x256": (203078246, 12),
+        "wgrad_256x192": (248383693, 10), "igemm_fwd_256x192x64_store": (233592832, 26), "igemm_fwd_256x128x32_affine": (349974016, 30),
+        "igemm_dgrad_256x192x64_store": (166742221, 23), "igemm_fwd_256x256x64_affine": (111704269, 11), "igemm_fwd_256x256x64_store": (213144166, 17),
     }),
 }
 
