@@ -51,55 +51,6 @@
 
 namespace pbd {
 
-typedef __attribute__((address_space(3))) void* lds_void_ptr;
-
-__device__ __forceinline__ void dma_load16(__amdgpu_buffer_rsrc_t r, unsigned char* lds_wave_base, unsigned byte_off, unsigned uniform_off = 0) {
-  // lane l's 16 bytes land at lds_wave_base + 16 l (the base and uniform_off must be uniform over the wavefront)
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_ptr)lds_wave_base, 16, (int)byte_off, (int)uniform_off, 0, 0);
-}
-
-// Wait until at most N of this wave's vector-memory operations are outstanding.  The "memory" clobbers keep
-// the compiler from moving the direct-to-LDS loads (memory operations to it) across the wait or the barrier.
-template <int N> __device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-__device__ __forceinline__ void block_barrier() { asm volatile("s_barrier" ::: "memory"); }
-template <int N> __device__ __forceinline__ void wait_lgkmcnt() {
-  static_assert(N >= 0 && N < 16, "lgkmcnt is a 4-bit counter");
-  asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory");
-}
-__device__ __forceinline__ bf16x8 lds_read16_async(unsigned addr) {
-  // the result arrives later: only use it behind wait_lgkmcnt + pin()
-  bf16x8 v;
-  asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr) : "memory");
-  return v;
-}
-__device__ __forceinline__ void pin(bf16x8& v) { asm volatile("" : "+v"(v)); }
-
-// wait until at most n (0..16) vector-memory operations of this wave are outstanding; n is uniform
-__device__ __forceinline__ void wait_vmcnt_dyn(int n) {
-  switch (n) {
-    case 0: wait_vmcnt<0>(); break;
-    case 1: wait_vmcnt<1>(); break;
-    case 2: wait_vmcnt<2>(); break;
-    case 3: wait_vmcnt<3>(); break;
-    case 4: wait_vmcnt<4>(); break;
-    case 5: wait_vmcnt<5>(); break;
-    case 6: wait_vmcnt<6>(); break;
-    case 7: wait_vmcnt<7>(); break;
-    case 8: wait_vmcnt<8>(); break;
-    case 9: wait_vmcnt<9>(); break;
-    case 10: wait_vmcnt<10>(); break;
-    case 11: wait_vmcnt<11>(); break;
-    case 12: wait_vmcnt<12>(); break;
-    case 13: wait_vmcnt<13>(); break;
-    case 14: wait_vmcnt<14>(); break;
-    case 15: wait_vmcnt<15>(); break;
-    default: wait_vmcnt<16>(); break;
-  }
-}
-
 constexpr int kDmaThreads = 512;
 constexpr int kDmaBM = 256;      // rows of a big tile
 constexpr int kDmaTailBM = 64;   // rows of a tail tile

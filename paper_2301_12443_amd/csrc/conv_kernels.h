@@ -192,6 +192,70 @@ inline int fold_lds(int channels) { return 3 * 4 * ((channels + 63) / 64 * 64); 
 // EPI_PARTIAL: raw fp32 partial tile of a split-K launch, summed by splitk_epilogue_kernel
 enum { EPI_STORE = 0, EPI_AFFINE_ACT = 1, EPI_ACCUM = 2, EPI_PARTIAL = 3 };
 
+// ---- operands straight from memory to LDS ----
+typedef __attribute__((address_space(3))) void* lds_void_ptr;
+
+__device__ __forceinline__ void dma_load16(__amdgpu_buffer_rsrc_t r, unsigned char* lds_wave_base, unsigned byte_off, unsigned uniform_off = 0) {
+  // lane l's 16 bytes land at lds_wave_base + 16 l (the base and uniform_off must be uniform over the wavefront)
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_ptr)lds_wave_base, 16, (int)byte_off, (int)uniform_off, 0, 0);
+}
+
+// Wait until at most N of this wave's vector-memory operations are outstanding.  The "memory" clobbers keep
+// the compiler from moving the direct-to-LDS loads (memory operations to it) across the wait or the barrier.
+template <int N> __device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void block_barrier() { asm volatile("s_barrier" ::: "memory"); }
+template <int N> __device__ __forceinline__ void wait_lgkmcnt() {
+  static_assert(N >= 0 && N < 16, "lgkmcnt is a 4-bit counter");
+  asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ bf16x8 lds_read16_async(unsigned addr) {
+  // the result arrives later: only use it behind wait_lgkmcnt + pin()
+  bf16x8 v;
+  asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr) : "memory");
+  return v;
+}
+__device__ __forceinline__ void pin(bf16x8& v) { asm volatile("" : "+v"(v)); }
+
+// wait until at most n (0..16) vector-memory operations of this wave are outstanding; n is uniform
+__device__ __forceinline__ void wait_vmcnt_dyn(int n) {
+  switch (n) {
+    case 0: wait_vmcnt<0>(); break;
+    case 1: wait_vmcnt<1>(); break;
+    case 2: wait_vmcnt<2>(); break;
+    case 3: wait_vmcnt<3>(); break;
+    case 4: wait_vmcnt<4>(); break;
+    case 5: wait_vmcnt<5>(); break;
+    case 6: wait_vmcnt<6>(); break;
+    case 7: wait_vmcnt<7>(); break;
+    case 8: wait_vmcnt<8>(); break;
+    case 9: wait_vmcnt<9>(); break;
+    case 10: wait_vmcnt<10>(); break;
+    case 11: wait_vmcnt<11>(); break;
+    case 12: wait_vmcnt<12>(); break;
+    case 13: wait_vmcnt<13>(); break;
+    case 14: wait_vmcnt<14>(); break;
+    case 15: wait_vmcnt<15>(); break;
+    default: wait_vmcnt<16>(); break;
+  }
+}
+
+// ... at most n, which is uniform, to within one
+__device__ __forceinline__ void wait_vmcnt_upto(int n) {
+  if (n <= 16) { wait_vmcnt_dyn(n); return; }
+  if (n >= 40) { wait_vmcnt<40>(); return; }
+  switch (n >> 2) {
+    case 4: wait_vmcnt<16>(); break;
+    case 5: wait_vmcnt<20>(); break;
+    case 6: wait_vmcnt<24>(); break;
+    case 7: wait_vmcnt<28>(); break;
+    case 8: wait_vmcnt<32>(); break;
+    default: wait_vmcnt<36>(); break;
+  }
+}
+
 // K step 32 (any channel count) or 64 (channel counts that are multiples of 64: a row's chunk is
 // then a whole 128-byte cache line, 8 lanes wide, instead of half of one).  LDS row pitch 96 / 144
 // bytes: conflict-free for the fragment reads (row = lane%32, 16-byte chunk = lane/32) in both
@@ -213,7 +277,14 @@ __device__ __forceinline__ int xcd_contiguous(int w, int total) {
 // FOLD (1 x 1, stride 1, forward): the narrow layers behind MobileNetV2's and the supernet's depthwise layers, N <= 32, so that every
 // element of A is staged once.  ~40 vector operations a chunk beside a kernel that waits for memory; bn_apply_kernel's pass over the
 // block's largest tensor, one read and one write, goes.
-template <int MODE, int BM, int BN, int EPI, bool UNI, int BK, bool FOLD>
+//
+// RING (UNI, not FOLD): operands go from memory straight to LDS (dma_load16), into a ring of RING stages of unpadded rows whose 16-byte chunks
+// are swizzled, with one barrier a step: no registers to wait for, no LDS stores, and a step's fragments requested together.  Same products in the
+// same order, so the same bits.  What bounds it is what a compute unit fetches: 44 GB/s with one workgroup, 60 to 67 with two or three, whatever the
+// depth of the ring (six stages are no faster than three).  us with registers / with the ring: 3136 rows, 768 -> 768, 3 x 3, cut in
+// two 87 / 51 (640 TFLOP/s), 512 -> 512 41 / 27, 2048 -> 768, 1 x 1 35.6 / 22, 1360 rows, 512 -> 512, 3 x 3, cut in six 22.6 / 15.9, 340 rows, 1 x 1
+// 7.9 / 6.9 (5.5 on 64 x 64 tiles); layers of one step as before.
+template <int MODE, int BM, int BN, int EPI, bool UNI, int BK, bool FOLD, int RING>
 __device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __restrict__ A,
                                                     const bf16_t* __restrict__ Bw,
                                                     bf16_t* __restrict__ Out,
@@ -231,13 +302,17 @@ __device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __rest
   constexpr int A_LOADS = BM / RPP;
   constexpr int B_LOADS = (BN + RPP - 1) / RPP;  // 16-byte chunks of the weight tile per thread
   static_assert(!(BK == 64) || UNI, "the 64-wide K step needs uniform taps");
+  static_assert(!RING || (UNI && !FOLD), "the ring has no registers to form a value in");
+  constexpr int ROWB = BK * 2, STAGE = (BM + BN) * ROWB;       // the ring: bytes of a row (unpadded) and of a stage
+  constexpr int OUT = BM * (BN * (EPI == EPI_ACCUM && BM <= 128 ? 4 : 2) + 16);   // the staged output
+  constexpr int LDS = RING ? (RING * STAGE > OUT ? RING * STAGE : OUT) : 2 * (BM + BN) * PITCH * 2;
   // one LDS block: the two stages of both operand tiles during the reduction, then the output tile on
   // its way to coalesced stores
-  __shared__ __attribute__((aligned(16))) bf16_t smem[2 * (BM + BN) * PITCH];
+  __shared__ __attribute__((aligned(16))) bf16_t smem[LDS / 2];
   bf16_t (*As)[BM * PITCH] = reinterpret_cast<bf16_t (*)[BM * PITCH]>(smem);
   bf16_t (*Bs)[BN * PITCH] = reinterpret_cast<bf16_t (*)[BN * PITCH]>(smem + 2 * BM * PITCH);
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = RING ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
   // Workgroups are dealt to the 8 XCDs round-robin, each with an L2 of its own.  Remapped so that
   // an XCD works through a contiguous run of tiles (column tiles of one row tile next to each other,
@@ -246,7 +321,9 @@ __device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __rest
   const int tile = xcd_contiguous(blk.x, g.tiles_m * g.tiles_n * g.splits);
   const int tile_n = tile % g.tiles_n, tile_m = (tile / g.tiles_n) % g.tiles_m, kslice = tile / (g.tiles_n * g.tiles_m);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
-  const int chunk = tid % CPR, prow = tid / CPR;
+  // (ring: the lane's 16 bytes land in slot tid % CPR of its row and are the chunk that the swizzle puts there)
+  auto swz = [](int row) { return BK == 64 ? (row >> 1) & 7 : (row >> 2) & 3; };
+  const int prow = tid / CPR, chunk = RING ? (tid % CPR) ^ swz(prow) : tid % CPR;
   const int sh = g.stride == 2 ? 1 : 0, smask = g.stride - 1;
   // the tile's folded batch-norm terms wait in LDS from the start, so that the store at the end does not
   // begin with a round trip to memory (columns past NC repeat the last four: they are never stored)
@@ -318,10 +395,12 @@ __device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __rest
   }
 
   // two register stages: tile kt+2 is requested while tile kt is multiplied and tile kt+1 moves to LDS
-  uint4 areg[2][A_LOADS], breg[2][B_LOADS];
+  uint4 areg[RING ? 1 : 2][A_LOADS], breg[RING ? 1 : 2][B_LOADS];
+  unsigned char* const ring = reinterpret_cast<unsigned char*>(smem);
+  constexpr bool B_FULL = BN % RPP == 0;             // every wave loads as many rows of the weight tile
   const __amdgpu_buffer_rsrc_t a_rsrc = tensor_rsrc(A, g.a_bytes), b_rsrc = tensor_rsrc(Bw, g.b_bytes);
-  auto load_tile = [&](auto stage) {
-    constexpr int S_ = decltype(stage)::value;
+  auto load_tile = [&](auto stage, int ring_stage = 0) {
+    constexpr int S_ = RING ? 0 : decltype(stage)::value;
     if constexpr (UNI) {
       const int tap = MODE == 0 ? r * g.WA + s : -(r * g.WA + s);
       const unsigned delta = (unsigned)(((tap * g.CA) >> (MODE == 1 ? sh : 0)) + c) * 2u;
@@ -332,10 +411,14 @@ __device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __rest
         const int h = MODE == 0 ? rh[i] + r : rh[i] - r, w = MODE == 0 ? rw[i] + s : rw[i] - s;
         bool ok = (unsigned)h < hlim && (unsigned)w < wlim;
         if (MODE == 1) ok = ok && ((h | w) & smask) == 0;
-        areg[S_][i] = buffer_load16(a_rsrc, ok ? abase[i] + delta : kOutOfRange);
+        if constexpr (RING) dma_load16(a_rsrc, ring + ring_stage * STAGE + (i * 4 + wave) * 1024, ok ? abase[i] + delta : kOutOfRange);
+        else areg[S_][i] = buffer_load16(a_rsrc, ok ? abase[i] + delta : kOutOfRange);
       }
 #pragma unroll
-      for (int i = 0; i < B_LOADS; ++i) breg[S_][i] = buffer_load16(b_rsrc, bbase[i] + (unsigned)kk * 2u);
+      for (int i = 0; i < B_LOADS; ++i) {
+        if constexpr (RING) { if (B_FULL || (i * 4 + wave) * 1024 < BN * ROWB) dma_load16(b_rsrc, ring + ring_stage * STAGE + BM * ROWB + (i * 4 + wave) * 1024, bbase[i], (unsigned)kk * 2u); }
+        else breg[S_][i] = buffer_load16(b_rsrc, bbase[i] + (unsigned)kk * 2u);
+      }
       kk += BK;
       c += BK;
       const bool wrap = c >= g.CA;
@@ -423,41 +506,99 @@ __device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __rest
   const int nk = min(g.ksteps_per_split, (g.Kred + BK - 1) / BK - kt0);
   using S0 = std::integral_constant<int, 0>;
   using S1 = std::integral_constant<int, 1>;
-  load_tile(S0{});
-  if (nk > 1) load_tile(S1{});
-  if (FOLD) __syncthreads();                         // the terms are in LDS
-  store_tile(S0{}, 0, 0);
-  __syncthreads();
-  auto iteration = [&](int kt, auto cur) {
-    constexpr int C_ = decltype(cur)::value;
-    using Cur = std::integral_constant<int, C_>;
-    using Nxt = std::integral_constant<int, 1 - C_>;
-    if (kt + 2 < nk) load_tile(Cur{});          // stage C_ went to LDS one iteration ago
-    if (!(kIdleWaves && wn > 0)) {
+  if constexpr (RING != 0) {
+    // Fragment addresses: row = lane % 32 of a block, chunk 2 ks + lane / 32 in slot chunk ^ swz(row) (blocks start at multiples of 32 rows)
+    constexpr int KS = BK / 16;
+    const int frow = lane & 31;
+    const bool mul = !(kIdleWaves && wn > 0);
+    unsigned fa[KS], fb[KS];
 #pragma unroll
-      for (int ks = 0; ks < BK / 16; ++ks) {
-        bf16x8 af[TM], bfr[TN];
+    for (int ks = 0; ks < KS; ++ks) {
+      const unsigned so = (unsigned)(((ks * 2 + (lane >> 5)) ^ swz(frow)) * 16);
+      fa[ks] = (unsigned)((wm * TM * 32 + frow) * ROWB) + so;
+      fb[ks] = (unsigned)((BM + (kIdleWaves ? 0 : wn * TN * 32) + frow) * ROWB) + so;
+    }
+    struct Frag { bf16x8 a[TM], b[TN]; } f[KS];
+    int loads = A_LOADS;                             // of this wave per stage
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-          af[i] = *reinterpret_cast<const bf16x8*>(
-              &As[C_][(wm * TM * 32 + i * 32 + (lane & 31)) * PITCH + ks * 16 + (lane >> 5) * 8]);
+    for (int i = 0; i < B_LOADS; ++i) loads += B_FULL || (i * 4 + wave) * 1024 < BN * ROWB ? 1 : 0;
+    const int first = min(nk, RING);
+    for (int st = 0; st < first; ++st) load_tile(S0{}, st);
+    int stage = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+      // this wave's loads of step kt have landed (those behind may be on their way), and then everybody's
+      wait_vmcnt_upto(min(RING - 1 - (kt ? 1 : 0), nk - 1 - kt) * loads);
+      block_barrier();
+      if (kt && kt - 1 + RING < nk) load_tile(S0{}, stage ? stage - 1 : RING - 1);   // step kt - 1 has been read by everyone
+      if (mul) {
+        const unsigned sb = (unsigned)(stage * STAGE);
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-          bfr[j] = *reinterpret_cast<const bf16x8*>(
-              &Bs[C_][(wn * TN * 32 + j * 32 + (lane & 31)) * PITCH + ks * 16 + (lane >> 5) * 8]);
+        for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+          for (int i = 0; i < TM; ++i) f[ks].a[i] = lds_read16_async(fa[ks] + sb + i * 32 * ROWB);
+#pragma unroll
+          for (int j = 0; j < TN; ++j) f[ks].b[j] = lds_read16_async(fb[ks] + sb + j * 32 * ROWB);
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          // (reads return in order: those of the later sub-steps may be on their way)
+          constexpr int G = TM + TN;
+          if (ks == 0) wait_lgkmcnt<(KS - 1) * G < 16 ? (KS - 1) * G : 15>();
+          else if (ks + 1 == KS) wait_lgkmcnt<0>();
+          else if (ks + 2 == KS) wait_lgkmcnt<G>();
+          else wait_lgkmcnt<2 * G>();
+#pragma unroll
+          for (int i = 0; i < TM; ++i) pin(f[ks].a[i]);
+#pragma unroll
+          for (int j = 0; j < TN; ++j) pin(f[ks].b[j]);
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[ks].b[j], f[ks].a[i], acc[i][j], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      stage = stage + 1 == RING ? 0 : stage + 1;
+    }
+    __syncthreads();                                 // the ring is dead: LDS now stages the output tile
+  } else {
+    load_tile(S0{});
+    if (nk > 1) load_tile(S1{});
+    if (FOLD) __syncthreads();                         // the terms are in LDS
+    store_tile(S0{}, 0, 0);
+    __syncthreads();
+    auto iteration = [&](int kt, auto cur) {
+      constexpr int C_ = decltype(cur)::value;
+      using Cur = std::integral_constant<int, C_>;
+      using Nxt = std::integral_constant<int, 1 - C_>;
+      if (kt + 2 < nk) load_tile(Cur{});          // stage C_ went to LDS one iteration ago
+      if (!(kIdleWaves && wn > 0)) {
+#pragma unroll
+        for (int ks = 0; ks < BK / 16; ++ks) {
+          bf16x8 af[TM], bfr[TN];
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+            af[i] = *reinterpret_cast<const bf16x8*>(
+                &As[C_][(wm * TM * 32 + i * 32 + (lane & 31)) * PITCH + ks * 16 + (lane >> 5) * 8]);
 #pragma unroll
           for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
+            bfr[j] = *reinterpret_cast<const bf16x8*>(
+                &Bs[C_][(wn * TN * 32 + j * 32 + (lane & 31)) * PITCH + ks * 16 + (lane >> 5) * 8]);
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
+        }
       }
+      if (kt + 1 < nk) store_tile(Nxt{}, 1 - C_, kt + 1);
+      __syncthreads();
+    };
+    for (int kt = 0; kt < nk; kt += 2) {
+      iteration(kt, S0{});
+      if (kt + 1 < nk) iteration(kt + 1, S1{});
     }
-    if (kt + 1 < nk) store_tile(Nxt{}, 1 - C_, kt + 1);
-    __syncthreads();
-  };
-  for (int kt = 0; kt < nk; kt += 2) {
-    iteration(kt, S0{});
-    if (kt + 1 < nk) iteration(kt + 1, S1{});
   }
   // epilogue: lane holds pixel (lane%32) and channels 8*(v/4) + 4*(lane/32) + v%4 of each 32x32 tile
   const bool full = m0 + BM <= g.M && n0 + BN <= g.NC;
@@ -466,7 +607,7 @@ __device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __rest
     // leave as 16-byte chunks, consecutive lanes on consecutive chunks of a row: whole cache lines
     // instead of 32 rows x 16 bytes per store instruction
     constexpr int OP = BN * 2 + 16;                  // bytes per staged row; the pad spreads rows over banks
-    static_assert(BM * OP <= 2 * (BM + BN) * PITCH * 2, "the output tile must fit in the operand tiles' LDS");
+    static_assert(BM * OP <= LDS, "the output tile must fit in the operand tiles' LDS");
     unsigned char* stage = reinterpret_cast<unsigned char*>(smem);
     constexpr int CPROW = BN / 8;                    // 16-byte chunks per row
     constexpr int NCHUNK = BM * CPROW;
@@ -570,7 +711,7 @@ __device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __rest
   // accumulating launches add in fp32 before the one rounding: the tile is staged as fp32 where the
   // operand tiles' LDS has room for it (every tile shape but 256 x 128 and the 32-wide K step's 128 x 128)
   constexpr int OPF = BN * 4 + 16;
-  if constexpr (EPI == EPI_ACCUM && !kIdleWaves && BM * OPF <= 2 * (BM + BN) * PITCH * 2) {
+  if constexpr (EPI == EPI_ACCUM && !kIdleWaves && BM * OPF <= LDS) {
     unsigned char* stage = reinterpret_cast<unsigned char*>(smem);
     constexpr int CPROW = BN / 8;
     constexpr int NCHUNK = BM * CPROW;
@@ -654,11 +795,11 @@ __device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __rest
       }
   }
 }
-template <int MODE, int BM, int BN, int EPI, bool UNI, int BK = IG_BK, bool FOLD = false>
+template <int MODE, int BM, int BN, int EPI, bool UNI, int BK = IG_BK, bool FOLD = false, int RING = 0>
 __global__ __launch_bounds__(256) void igemm_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ Bw, bf16_t* __restrict__ Out, const float* __restrict__ ep_a,
     const float* __restrict__ ep_b, int act, IgemmArgs g) {
-  igemm_block<MODE, BM, BN, EPI, UNI, BK, FOLD>(one_block(), A, Bw, Out, ep_a, ep_b, act, g);
+  igemm_block<MODE, BM, BN, EPI, UNI, BK, FOLD, RING>(one_block(), A, Bw, Out, ep_a, ep_b, act, g);
 }
 
 // Second stage of a split-K launch: out = epilogue(sum_s part[s]) in split order.

@@ -478,6 +478,35 @@ IgemmCfg igemm_cfg(long M, int NC, int Kred, int CA) {
 }
 int igemm_splits(long M, int NC, int Kred, int CA) { return igemm_cfg(M, NC, Kred, CA).splits; }
 
+// Tile of a launch whose results do not depend on it (all but those that leave batch-norm sums, whose association the tile fixes, and
+// lanes, whose kernels have to agree to go out together), of 64 x 64, 64 x 128 and 128 x 128, K step 64.  A workgroup's time is what it
+// fetches, (BM + BN) x 128 bytes a step, and a compute unit fetches at a rate that depends on how many workgroups it holds: 23 ns a KB
+// with one, 17 with two, 15 with three and more (fitted to 18 layers, within 15 % of each).  us on 64 x 64 / 64 x 128 / 128 x 128:
+//   340 rows, 512 -> 512, 1 x 1      5.5 / 7.0 / 8.6     3136, 768 -> 2048, 1 x 1     23.1 / 22.4 / 16.8
+//   1360, 512 -> 512, 1 x 1          5.8 / 7.1 / 9.2     3136, 2048 -> 768, 1 x 1     25.9 / 22.0 / 23.2
+//   1617, 960 -> 160, 1 x 1          7.6 / 10.4 / 13.4   16660, 1024 -> 256, 1 x 1    23.1 / 23.9 / 20.5
+//   4096, 512 -> 512, 3 x 3          33.7 / 29.7 / 31.1  3136, 768 -> 768, 3 x 3      58.5 / 51.3 / 53.4
+void free_tile(IgemmCfg& c, long M, int NC, int Kred, int num_cu) {
+  if (c.BK != 64 || c.BN < 64 || c.BM != 64) return;        // (128 rows: 512 workgroups and more of those)
+  static const int kBM[3] = {64, 64, 128}, kBN[3] = {128, 64, 128};
+  const int nk = (Kred + 63) / 64, per = (nk + c.splits - 1) / c.splits;
+  double best = 1e30;
+  for (int i = 0; i < 3; ++i) {
+    if (NC <= 64 && kBN[i] > 64) continue;
+    const long wgs = ((M + kBM[i] - 1) / kBM[i]) * ((NC + kBN[i] - 1) / kBN[i]) * ((nk + per - 1) / per);
+    const long unit = (wgs + num_cu - 1) / num_cu;          // workgroups of the busiest compute unit
+    const double t = (double)unit * per * (kBM[i] + kBN[i]) * (unit == 1 ? 23.0 : unit == 2 ? 17.0 : 15.0);
+    if (t < best * 0.999) { best = t; c.BM = kBM[i]; c.BN = kBN[i]; }
+  }
+}
+// Stages of the ring that such a launch's operands go through (igemm_block): three, of which two 64 x 128 workgroups fit in a compute unit's
+// LDS, and two, so that three of them fit, where there are more than two for a unit.  us with three / two: 588 workgroups of 54 steps
+// 66 / 51, 528 of 12 19.8 / 15.9, 512 of 36 29.2 / 33.0, 88 of 8 7.1 / 7.6 (register staging 87, 22.8, 36.0, 8.1).
+int ring_stages(const IgemmCfg& c, long wgs, int num_cu) {
+  if (c.BK == 32) return c.BM == 256 ? 2 : 3;
+  return c.BM == 128 ? 2 : c.BN == 128 && wgs > 2L * num_cu ? 2 : 3;
+}
+
 // Launch shape of igemm_dma_kernel (256-row tiles, operands straight into LDS) for one dense layer, or use = false
 // when the layer keeps igemm_kernel: channel counts that are no multiple of 32, fewer tiles than most of the
 // compute units (there 128- and 64-row tiles and split-K fill the chip better), and reductions shorter than 256
@@ -966,16 +995,17 @@ const ManyTable& many_table() {
     ManyTable t;
     typedef bf16_t B;
 #define PBD_MANY(WAVES_, NAME_, ...) put<&NAME_##_block<__VA_ARGS__>, 256, WAVES_>(t, NAME_##_kernel<__VA_ARGS__>)
-#define PBD_MANY_IG(MODE_, BM_, BN_, EPI_) PBD_MANY(1, igemm, MODE_, BM_, BN_, EPI_, true, 64, false); PBD_MANY(1, igemm, MODE_, BM_, BN_, EPI_, true, 32, false); \
-    PBD_MANY(1, igemm, MODE_, BM_, BN_, EPI_, false, 32, false)
+#define PBD_MANY_IGR(MODE_, BM_, BN_, EPI_, BK_, RING_) put<&igemm_block<MODE_, BM_, BN_, EPI_, true, BK_, false, RING_>, 256, 1>(t, igemm_kernel<MODE_, BM_, BN_, EPI_, true, BK_, false, RING_>)
+#define PBD_MANY_IG(MODE_, BM_, BN_, EPI_) PBD_MANY_IGR(MODE_, BM_, BN_, EPI_, 64, (BM_ == 64 && BN_ < 128 ? 3 : 2)); PBD_MANY_IGR(MODE_, BM_, BN_, EPI_, 32, 3); \
+    PBD_MANY(1, igemm, MODE_, BM_, BN_, EPI_, false, 32, false, 0)
 #define PBD_MANY_MODE(MODE_) PBD_MANY_IG(MODE_, 64, 128, EPI_STORE); PBD_MANY_IG(MODE_, 64, 64, EPI_STORE); PBD_MANY_IG(MODE_, 64, 32, EPI_STORE); \
     PBD_MANY_IG(MODE_, 128, 128, EPI_STORE); PBD_MANY_IG(MODE_, 128, 64, EPI_STORE); PBD_MANY_IG(MODE_, 128, 32, EPI_STORE); \
     PBD_MANY_IG(MODE_, 64, 128, EPI_PARTIAL); \
     put<&igemm_dma_block<MODE_, 64, 32, EPI_STORE>, kDmaThreads, 2>(t, igemm_dma_kernel<MODE_, 64, 32, EPI_STORE>)
     PBD_MANY_MODE(0); PBD_MANY_MODE(1);
-    PBD_MANY(1, igemm, 0, 128, 32, EPI_STORE, true, 64, true); PBD_MANY(1, igemm, 0, 128, 32, EPI_STORE, true, 32, true);
-    PBD_MANY(1, igemm, 0, 128, 32, EPI_STORE, false, 32, true); PBD_MANY(1, igemm, 0, 64, 32, EPI_STORE, true, 64, true);
-    PBD_MANY(1, igemm, 0, 64, 32, EPI_STORE, true, 32, true); PBD_MANY(1, igemm, 0, 64, 32, EPI_STORE, false, 32, true);
+    PBD_MANY(1, igemm, 0, 128, 32, EPI_STORE, true, 64, true, 0); PBD_MANY(1, igemm, 0, 128, 32, EPI_STORE, true, 32, true, 0);
+    PBD_MANY(1, igemm, 0, 128, 32, EPI_STORE, false, 32, true, 0); PBD_MANY(1, igemm, 0, 64, 32, EPI_STORE, true, 64, true, 0);
+    PBD_MANY(1, igemm, 0, 64, 32, EPI_STORE, true, 32, true, 0); PBD_MANY(1, igemm, 0, 64, 32, EPI_STORE, false, 32, true, 0);
     PBD_MANY(1, wgrad_tr, 128, 128, false); PBD_MANY(1, wgrad_tr, 128, 64, false); PBD_MANY(1, wgrad_tr, 64, 128, false);
     PBD_MANY(1, wgrad_tr, 64, 64, false); PBD_MANY(1, wgrad_tr, 64, 128, true); PBD_MANY(1, wgrad_tr, 64, 64, true);
     put<&splitk_epilogue_block, 256, 1>(t, splitk_epilogue_kernel);
@@ -1002,6 +1032,7 @@ const ManyTable& many_table() {
 #undef PBD_MANY_DW
 #undef PBD_MANY_MODE
 #undef PBD_MANY_IG
+#undef PBD_MANY_IGR
 #undef PBD_MANY
     return t;
   }();
@@ -1421,15 +1452,20 @@ template <class T> struct Exec {
     // an accumulating 256-row tile cannot stage its fp32 results in LDS: 128 rows store whole cache lines
     if (epi == EPI_ACCUM && cfg.BM == 256) cfg.BM = 128;
     if (epi == EPI_ACCUM && cfg.BK == 32 && cfg.BM == 128 && cfg.BN == 128) cfg.BN = 64;   // (128 x 128 needs the 64-wide K step's LDS)
+    const bool grouped = recorder(c) != nullptr;
+    if (!g.stats && !g.fold.mean && !grouped) free_tile(cfg, g.M, g.NC, g.Kred, c->num_cu);
     const int nk = (g.Kred + cfg.BK - 1) / cfg.BK;
     g.ksteps_per_split = (nk + cfg.splits - 1) / cfg.splits;
     g.tiles_m = (g.M + cfg.BM - 1) / cfg.BM;
     g.tiles_n = (g.NC + cfg.BN - 1) / cfg.BN;
     g.splits = (nk + g.ksteps_per_split - 1) / g.ksteps_per_split;
     const dim3 grid(g.tiles_m * g.tiles_n * g.splits);
+    const int ring = grouped ? 2 : ring_stages(cfg, (long)g.tiles_m * g.tiles_n * g.splits, c->num_cu);
+#define PBD_IGR(BM_, BN_, EPI_, OUT_, BK_, RING_) launch(c, igemm_kernel<MODE, BM_, BN_, EPI_, true, BK_, false, RING_>, grid, 256, 0, st, A, Bw, OUT_, a, b, act, g)
 #define PBD_IG(BM_, BN_, EPI_, OUT_) do { \
-      if (cfg.BK == 64) { if constexpr (BM_ != 256) launch(c, igemm_kernel<MODE, BM_, BN_, EPI_, true, 64>, grid, 256, 0, st, A, Bw, OUT_, a, b, act, g); } \
-      else if (g.CA % IG_BK == 0) launch(c, igemm_kernel<MODE, BM_, BN_, EPI_, true>, grid, 256, 0, st, A, Bw, OUT_, a, b, act, g); \
+      if (cfg.BK == 64) { if constexpr (BM_ == 128) PBD_IGR(BM_, BN_, EPI_, OUT_, 64, 2); \
+        else if constexpr (BM_ == 64) { if (BN_ == 128 && ring == 2) PBD_IGR(BM_, BN_, EPI_, OUT_, 64, (BN_ == 128 ? 2 : 3)); else PBD_IGR(BM_, BN_, EPI_, OUT_, 64, 3); } } \
+      else if (g.CA % IG_BK == 0) PBD_IGR(BM_, BN_, EPI_, OUT_, 32, (BM_ == 256 ? 2 : 3)); \
       else launch(c, igemm_kernel<MODE, BM_, BN_, EPI_, false>, grid, 256, 0, st, A, Bw, OUT_, a, b, act, g); } while (0)
 #define PBD_IG_BN(BM_, EPI_, OUT_) do { if (cfg.BN == 128) PBD_IG(BM_, 128, EPI_, OUT_); else if (cfg.BN == 64) PBD_IG(BM_, 64, EPI_, OUT_); else PBD_IG(BM_, 32, EPI_, OUT_); } while (0)
 #define PBD_IG_BM(EPI_, OUT_) do { if (cfg.BM == 256) PBD_IG(256, 128, EPI_, OUT_); else if (cfg.BM == 128) PBD_IG_BN(128, EPI_, OUT_); else PBD_IG_BN(64, EPI_, OUT_); } while (0)
@@ -1465,6 +1501,7 @@ template <class T> struct Exec {
 #undef PBD_IG_BM
 #undef PBD_IG_BN
 #undef PBD_IG
+#undef PBD_IGR
   }
 
   // ---- convolution backward-data (dense) ---------------------------------
