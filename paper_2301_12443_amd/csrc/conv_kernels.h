@@ -511,12 +511,13 @@ __device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __rest
     constexpr int KS = BK / 16;
     const int frow = lane & 31;
     const bool mul = !(kIdleWaves && wn > 0);
+    const unsigned ring_at = (unsigned)(size_t)(lds_void_ptr)ring;
     unsigned fa[KS], fb[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       const unsigned so = (unsigned)(((ks * 2 + (lane >> 5)) ^ swz(frow)) * 16);
-      fa[ks] = (unsigned)((wm * TM * 32 + frow) * ROWB) + so;
-      fb[ks] = (unsigned)((BM + (kIdleWaves ? 0 : wn * TN * 32) + frow) * ROWB) + so;
+      fa[ks] = ring_at + (unsigned)((wm * TM * 32 + frow) * ROWB) + so;
+      fb[ks] = ring_at + (unsigned)((BM + (kIdleWaves ? 0 : wn * TN * 32) + frow) * ROWB) + so;
     }
     struct Frag { bf16x8 a[TM], b[TN]; } f[KS];
     int loads = A_LOADS;                             // of this wave per stage

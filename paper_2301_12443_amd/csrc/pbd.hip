@@ -1022,7 +1022,7 @@ const ManyTable& many_table() {
     PBD_MANY(1, sum_partials, 32); PBD_MANY(1, sum_partials, 8);
     PBD_MANY(1, dw_wgrad, B, 3, 3); PBD_MANY(1, dw_wgrad, B, 7, 1);
     PBD_MANY(1, dw_wgrad, float, 3, 3); PBD_MANY(1, dw_wgrad, float, 7, 1);
-    PBD_MANY(1, wgrad_f32, 16); PBD_MANY(1, wgrad_f32, 32);
+    put<&wgrad_f32_block<16>, F32Gemm<16>::THREADS, 2>(t, wgrad_f32_kernel<16>); put<&wgrad_f32_block<32>, F32Gemm<32>::THREADS, 2>(t, wgrad_f32_kernel<32>);
 #define PBD_MANY_DW(K_) PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, false, false, false, false); PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, false, false, true, false); \
     PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, false, true, true, false); PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, true, false, false, false); \
     PBD_MANY(3, dw_wgrad_mfma, K_, false); PBD_MANY((K_ == 7 ? 2 : 3), dw_bwd_mfma, K_, true); PBD_MANY((K_ == 7 ? 3 : 4), dw_bwd_mfma, K_, false); \
@@ -1399,7 +1399,7 @@ template <class T> struct Exec {
     char name[32];
     snprintf(name, sizeof name, "igemm_f32_%s_%d", MODE ? "dgrad" : "fwd", edge);
     ProfScope ps(c, name, bytes, flops, net, blk, opi);
-    launch(c, tile == 32 ? igemm_f32_kernel<MODE, 32> : igemm_f32_kernel<MODE, 16>, g.tiles_m * g.tiles_n, 256, 0, st, A, Bw, out, a, b, act,
+    launch(c, tile == 32 ? igemm_f32_kernel<MODE, 32> : igemm_f32_kernel<MODE, 16>, g.tiles_m * g.tiles_n, F32Gemm<16>::THREADS, 0, st, A, Bw, out, a, b, act,
            accumulate ? 1 : 0, g);
   }
 
@@ -1611,7 +1611,7 @@ template <class T> struct Exec {
                             (unsigned)(M * op.d.c_out * 4), (unsigned)((size_t)N * op.in.h * op.in.w * op.cin_p * 4),
                             (op.d.c_out + edge - 1) / edge, (J + edge - 1) / edge, 1};
         ProfScope ps(c, tile == 32 ? "wgrad_f32_64" : "wgrad_f32_32", bytes, flops, net, blk, opi);
-        launch(c, tile == 32 ? wgrad_f32_kernel<32> : wgrad_f32_kernel<16>, g.tiles_k * g.tiles_j, 256, 0, st, dy, x, dw, g);
+        launch(c, tile == 32 ? wgrad_f32_kernel<32> : wgrad_f32_kernel<16>, g.tiles_k * g.tiles_j, F32Gemm<16>::THREADS, 0, st, dy, x, dw, g);
       }
     } else {
       ConvGeom g{N, op.in.h, op.in.w, op.cin_p, op.out.h, op.out.w, op.d.c_out, op.d.k, op.d.k, op.d.stride, op.d.pad};
