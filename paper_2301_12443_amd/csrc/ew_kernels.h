@@ -108,6 +108,11 @@ template <> struct BufIO<bf16_t> {
   static __device__ __forceinline__ Raw issue(__amdgpu_buffer_rsrc_t r, unsigned elem, bool ok) {
     return buffer_load16(r, ok ? elem * 2u : kOutOfRange);
   }
+  static __device__ __forceinline__ Raw pack(const float v[8]) {
+    return make_uint4(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7]));
+  }
+  static __device__ __forceinline__ Raw slab_read(const uint4* s, int, int r) { return s[r]; }
+  static __device__ __forceinline__ void slab_write(uint4* s, int, int r, const Raw& u) { s[r] = u; }
   static __device__ __forceinline__ void unpack(const Raw& u, float v[8]) {
     v[0] = bf_lo(u.x); v[1] = bf_hi(u.x); v[2] = bf_lo(u.y); v[3] = bf_hi(u.y);
     v[4] = bf_lo(u.z); v[5] = bf_hi(u.z); v[6] = bf_lo(u.w); v[7] = bf_hi(u.w);
@@ -121,6 +126,13 @@ template <> struct BufIO<float> {
     q.b = buffer_load16(r, ok ? elem * 4u + 16u : kOutOfRange);
     return q;
   }
+  static __device__ __forceinline__ Raw pack(const float v[8]) {
+    return Raw{make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])),
+               make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7]))};
+  }
+  // (two planes: neighbouring lanes' rows lie 16 bytes apart in each)
+  static __device__ __forceinline__ Raw slab_read(const uint4* s, int plane, int r) { return Raw{s[r], s[plane + r]}; }
+  static __device__ __forceinline__ void slab_write(uint4* s, int plane, int r, const Raw& u) { s[r] = u.a; s[plane + r] = u.b; }
   static __device__ __forceinline__ void unpack(const Raw& u, float v[8]) {
     v[0] = __uint_as_float(u.a.x); v[1] = __uint_as_float(u.a.y); v[2] = __uint_as_float(u.a.z);
     v[3] = __uint_as_float(u.a.w); v[4] = __uint_as_float(u.b.x); v[5] = __uint_as_float(u.b.y);
@@ -970,29 +982,26 @@ __device__ __forceinline__ void block_sum16(const float (&v)[16], double (&out)[
   for (int k = 0; k < 16; ++k) out[k] = tot[k];
 }
 
-// y -> batch statistics (pivot-shifted sums as in bn_stats_kernel), running statistics, then
+struct SmallLds {
+  float red[kSmallThreads / 64][16];
+  double tot[16];
+  float coef[3][8];
+};
+struct ColFwd { const float *gamma, *beta; float *mean, *invstd, *rmean, *rvar; int act; };
+struct ColBwd { const float *gamma, *beta, *mean, *invstd; float *g_gamma, *g_beta; int act; };
+struct SmallTerms { float mu[8], a[8], b[8]; };
+
+// Batch statistics of a thread's rows (pivot-shifted sums as in bn_stats_kernel), running statistics, and the terms of
 // z = act((y - mean) * (gamma*invstd) + beta)
-template <class T>
-__device__ __forceinline__ void bn_small_fwd_block(const Blk& blk, const T* __restrict__ y, T* __restrict__ z, const float* __restrict__ gamma, const float* __restrict__ beta,
-    float* __restrict__ mean, float* __restrict__ invstd, float* __restrict__ rmean, float* __restrict__ rvar,
-    int M, int Cp, float eps, float rho, int act, unsigned bytes) {
-  __shared__ float red[kSmallThreads / 64][16];
-  __shared__ double tot[16];
-  const int ncv = Cp / 8, cv = xcd_slab(blk.x, ncv), tid = threadIdx.x;
-  const __amdgpu_buffer_rsrc_t ry = tensor_rsrc(y, bytes);
-  typename BufIO<T>::Raw raw[kSmallRows];
-#pragma unroll
-  for (int u = 0; u < kSmallRows; ++u) {
-    const int r = u * kSmallThreads + tid;
-    raw[u] = BufIO<T>::issue(ry, (unsigned)(r * ncv + cv) * 8u, r < M);
-  }
-  float piv[8];
-  IO<T>::ld(y + (long)cv * 8, piv);
+template <class T, int N>
+__device__ __forceinline__ void small_stats(const typename BufIO<T>::Raw (&raw)[N], const float (&piv)[8], const ColFwd& bn, SmallTerms& t,
+                                            SmallLds& lds, int cv, int M, float eps, float rho) {
+  const int tid = threadIdx.x;
   float acc[16];
 #pragma unroll
   for (int k = 0; k < 16; ++k) acc[k] = 0.f;
 #pragma unroll
-  for (int u = 0; u < kSmallRows; ++u) {
+  for (int u = 0; u < N; ++u) {
     if (u * kSmallThreads + (tid & ~63) >= M) continue;     // no lane of this wave owns the row
     const bool ok = u * kSmallThreads + tid < M;
     float v[8];
@@ -1005,10 +1014,9 @@ __device__ __forceinline__ void bn_small_fwd_block(const Blk& blk, const T* __re
     }
   }
   double sum[16];
-  block_sum16(acc, sum, red, tot);
+  block_sum16(acc, sum, lds.red, lds.tot);
   // thread k < 8 finalises channel k in double (once, not in every thread) and hands the float
   // coefficients to the block through LDS
-  __shared__ float coef[3][8];
   if (tid < 8) {
     const int c = cv * 8 + tid;
     const double m = (double)M;
@@ -1023,16 +1031,34 @@ __device__ __forceinline__ void bn_small_fwd_block(const Blk& blk, const T* __re
     if (var < 0.0) var = 0.0;
     const float is = (float)(1.0 / sqrt(var + (double)eps));
     const float muf = (float)mean_d;
-    mean[c] = muf;
-    invstd[c] = is;
-    rmean[c] = (1.f - rho) * rmean[c] + rho * muf;
-    rvar[c] = (1.f - rho) * rvar[c] + rho * (float)(var * m / (m - 1.0));
-    coef[0][tid] = muf; coef[1][tid] = gamma[c] * is; coef[2][tid] = beta[c];
+    bn.mean[c] = muf;
+    bn.invstd[c] = is;
+    bn.rmean[c] = (1.f - rho) * bn.rmean[c] + rho * muf;
+    bn.rvar[c] = (1.f - rho) * bn.rvar[c] + rho * (float)(var * m / (m - 1.0));
+    lds.coef[0][tid] = muf; lds.coef[1][tid] = bn.gamma[c] * is; lds.coef[2][tid] = bn.beta[c];
   }
   __syncthreads();
-  float mu[8], a[8], b[8];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) { mu[k] = coef[0][k]; a[k] = coef[1][k]; b[k] = coef[2][k]; }
+  for (int k = 0; k < 8; ++k) { t.mu[k] = lds.coef[0][k]; t.a[k] = lds.coef[1][k]; t.b[k] = lds.coef[2][k]; }
+}
+
+template <class T>
+__device__ __forceinline__ void bn_small_fwd_block(const Blk& blk, const T* __restrict__ y, T* __restrict__ z, const float* __restrict__ gamma, const float* __restrict__ beta,
+    float* __restrict__ mean, float* __restrict__ invstd, float* __restrict__ rmean, float* __restrict__ rvar,
+    int M, int Cp, float eps, float rho, int act, unsigned bytes) {
+  __shared__ SmallLds lds;
+  const int ncv = Cp / 8, cv = xcd_slab(blk.x, ncv), tid = threadIdx.x;
+  const __amdgpu_buffer_rsrc_t ry = tensor_rsrc(y, bytes);
+  typename BufIO<T>::Raw raw[kSmallRows];
+#pragma unroll
+  for (int u = 0; u < kSmallRows; ++u) {
+    const int r = u * kSmallThreads + tid;
+    raw[u] = BufIO<T>::issue(ry, (unsigned)(r * ncv + cv) * 8u, r < M);
+  }
+  float piv[8];
+  IO<T>::ld(y + (long)cv * 8, piv);
+  SmallTerms t;
+  small_stats<T>(raw, piv, ColFwd{gamma, beta, mean, invstd, rmean, rvar, act}, t, lds, cv, M, eps, rho);
 #pragma unroll
   for (int u = 0; u < kSmallRows; ++u) {
     const int r = u * kSmallThreads + tid;
@@ -1040,7 +1066,7 @@ __device__ __forceinline__ void bn_small_fwd_block(const Blk& blk, const T* __re
     float v[8];
     BufIO<T>::unpack(raw[u], v);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = apply_act(fmaf(v[k] - mu[k], a[k], b[k]), act);
+    for (int k = 0; k < 8; ++k) v[k] = apply_act(fmaf(v[k] - t.mu[k], t.a[k], t.b[k]), act);
     IO<T>::st(z + ((long)r * ncv + cv) * 8, v);
   }
 }
@@ -1051,14 +1077,74 @@ __global__ __launch_bounds__(kSmallThreads) void bn_small_fwd_kernel(const T* __
   bn_small_fwd_block<T>(one_block(), y, z, gamma, beta, mean, invstd, rmean, rvar, M, Cp, eps, rho, act, bytes);
 }
 
-// BN backward in one launch: sums of dpre and dpre*xhat, the parameter gradients, then
-// dy = gamma*invstd*(dpre - dbeta/m - xhat*dgamma/m) over dz in place
+// BN backward of a thread's rows: sums of dpre and dpre*xhat, the parameter gradients, then
+// dy = gamma*invstd*(dpre - dbeta/m - xhat*dgamma/m), handed out row by row (rows past M: dz = 0, they add nothing)
+template <class T, int N, class F>
+__device__ __forceinline__ void small_bwd(const typename BufIO<T>::Raw (&rawd)[N], const typename BufIO<T>::Raw (&rawy)[N], const ColBwd& bn,
+                                          SmallLds& lds, int cv, int M, F&& out) {
+  const int tid = threadIdx.x;
+  float mu[8], a[8], b[8], is[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int c = cv * 8 + k;
+    mu[k] = bn.mean[c]; is[k] = bn.invstd[c]; a[k] = bn.gamma[c] * is[k]; b[k] = bn.beta[c];
+  }
+  float acc[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) acc[k] = 0.f;
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    if (u * kSmallThreads + (tid & ~63) >= M) continue;     // no lane of this wave owns the row
+    float d[8], v[8];
+    BufIO<T>::unpack(rawd[u], d);
+    BufIO<T>::unpack(rawy[u], v);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const float yc = v[k] - mu[k];
+      const float dp = act_pass(fmaf(yc, a[k], b[k]), bn.act) ? d[k] : 0.f;
+      acc[k] += dp;
+      acc[8 + k] = fmaf(dp, yc * is[k], acc[8 + k]);
+    }
+  }
+  double sum[16];
+  block_sum16(acc, sum, lds.red, lds.tot);
+  if (tid < 8) {
+    double sb = 0.0, sg = 0.0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (k == tid) { sb = sum[k]; sg = sum[8 + k]; }
+    const double m = (double)M;
+    bn.g_beta[cv * 8 + tid] = (float)sb;
+    bn.g_gamma[cv * 8 + tid] = (float)sg;
+    lds.coef[0][tid] = (float)(sb / m);
+    lds.coef[1][tid] = (float)(sg / m);
+  }
+  __syncthreads();
+  float c2[8], c3[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) { c2[k] = lds.coef[0][k]; c3[k] = lds.coef[1][k]; }
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const int r = u * kSmallThreads + tid;
+    if (r >= M) continue;
+    float d[8], v[8];
+    BufIO<T>::unpack(rawd[u], d);
+    BufIO<T>::unpack(rawy[u], v);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const float yc = v[k] - mu[k];
+      const float dp = act_pass(fmaf(yc, a[k], b[k]), bn.act) ? d[k] : 0.f;
+      d[k] = a[k] * (dp - c2[k] - yc * is[k] * c3[k]);
+    }
+    out(u, r, d);
+  }
+}
+
 template <class T>
 __device__ __forceinline__ void bn_small_bwd_block(const Blk& blk, T* dz, const T* __restrict__ y, const float* __restrict__ gamma, const float* __restrict__ beta,
     const float* __restrict__ mean, const float* __restrict__ invstd, float* __restrict__ g_gamma,
     float* __restrict__ g_beta, int M, int Cp, int act, unsigned bytes) {
-  __shared__ float red[kSmallThreads / 64][16];
-  __shared__ double tot[16];
+  __shared__ SmallLds lds;
   const int ncv = Cp / 8, cv = xcd_slab(blk.x, ncv), tid = threadIdx.x;
   const __amdgpu_buffer_rsrc_t ry = tensor_rsrc(y, bytes), rd = tensor_rsrc(dz, bytes);
   typename BufIO<T>::Raw rawd[kSmallRows], rawy[kSmallRows];
@@ -1068,68 +1154,170 @@ __device__ __forceinline__ void bn_small_bwd_block(const Blk& blk, T* dz, const 
     rawd[u] = BufIO<T>::issue(rd, (unsigned)(r * ncv + cv) * 8u, r < M);
     rawy[u] = BufIO<T>::issue(ry, (unsigned)(r * ncv + cv) * 8u, r < M);
   }
-  float mu[8], a[8], b[8], is[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const int c = cv * 8 + k;
-    mu[k] = mean[c]; is[k] = invstd[c]; a[k] = gamma[c] * is[k]; b[k] = beta[c];
-  }
-  float acc[16];
-#pragma unroll
-  for (int k = 0; k < 16; ++k) acc[k] = 0.f;
-#pragma unroll
-  for (int u = 0; u < kSmallRows; ++u) {
-    if (u * kSmallThreads + (tid & ~63) >= M) continue;     // no lane of this wave owns the row
-    float d[8], v[8];                                // rows past M read as dz = 0: they add nothing
-    BufIO<T>::unpack(rawd[u], d);
-    BufIO<T>::unpack(rawy[u], v);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const float yc = v[k] - mu[k];
-      const float dp = act_pass(fmaf(yc, a[k], b[k]), act) ? d[k] : 0.f;
-      acc[k] += dp;
-      acc[8 + k] = fmaf(dp, yc * is[k], acc[8 + k]);
-    }
-  }
-  double sum[16];
-  block_sum16(acc, sum, red, tot);
-  __shared__ float coef[2][8];
-  if (tid < 8) {
-    double sb = 0.0, sg = 0.0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-      if (k == tid) { sb = sum[k]; sg = sum[8 + k]; }
-    const double m = (double)M;
-    g_beta[cv * 8 + tid] = (float)sb;
-    g_gamma[cv * 8 + tid] = (float)sg;
-    coef[0][tid] = (float)(sb / m);
-    coef[1][tid] = (float)(sg / m);
-  }
-  __syncthreads();
-  float c2[8], c3[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) { c2[k] = coef[0][k]; c3[k] = coef[1][k]; }
-#pragma unroll
-  for (int u = 0; u < kSmallRows; ++u) {
-    const int r = u * kSmallThreads + tid;
-    if (r >= M) continue;
-    float d[8], v[8];
-    BufIO<T>::unpack(rawd[u], d);
-    BufIO<T>::unpack(rawy[u], v);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const float yc = v[k] - mu[k];
-      const float dp = act_pass(fmaf(yc, a[k], b[k]), act) ? d[k] : 0.f;
-      d[k] = a[k] * (dp - c2[k] - yc * is[k] * c3[k]);
-    }
-    IO<T>::st(dz + ((long)r * ncv + cv) * 8, d);
-  }
+  small_bwd<T>(rawd, rawy, ColBwd{gamma, beta, mean, invstd, g_gamma, g_beta, act}, lds, cv, M,
+               [&](int, int r, const float (&d)[8]) { IO<T>::st(dz + ((long)r * ncv + cv) * 8, d); });
 }
 template <class T>
 __global__ __launch_bounds__(kSmallThreads) void bn_small_bwd_kernel(T* dz, const T* __restrict__ y,
     const float* __restrict__ gamma, const float* __restrict__ beta, const float* __restrict__ mean, const float* __restrict__ invstd,
     float* __restrict__ g_gamma, float* __restrict__ g_beta, int M, int Cp, int act, unsigned bytes) {
   bn_small_bwd_block<T>(one_block(), dz, y, gamma, beta, mean, invstd, g_gamma, g_beta, M, Cp, act, bytes);
+}
+
+// A 3 x 3 depthwise layer of a short column with the batch norms around it.  A workgroup of the whole-column kernels owns 8 channels of every
+// image, which is all that a depthwise layer needs of its input: so the normalisation in front (PRE), the convolution and the normalisation
+// behind it are one launch, with the column between them in LDS.
+//   forward:  y1 -> z1 (stored) -> y2 (stored) -> z2;   backward:  dz2, y2 -> dy2 (in place) -> dz1, y1 -> dy1
+// Bound by the launches, which follow one another in a block's chain: 4 to 6 us each, three of them here, of which the arithmetic is one or two.
+// Every value that went through memory is rounded as it was there, and the taps are added in dw_slide_kernel's order, zeros outside
+// the image included, so the bits are those of the separate launches.
+// Up to 2048 rows.  A step of VGG-16 at 32 x 32, whose last block has six of these layers at 4 x 4 and 2 x 2, separate / fused: batch 85 (1360
+// rows) 824 / 784 us, float32 at batch 64 (1024) 1277 / 1204.  Eight rows a thread, up to 4096 rows: batch 16 (256) 621 / 575, 85 825 / 804, 128 (2048) 938
+// / 935, four batches of 256 (4096) in a pipeline 4829 / 4850: there the rows of one workgroup take longer than the launches that they save.
+constexpr int kDwSmallRows = 4;                          // rows per thread
+template <class T> struct DwSmall {
+  static constexpr int ROWS = kDwSmallRows * kSmallThreads;
+  static constexpr int PLANE = ROWS + 1;                            // the last one is zeros: what lies outside the image
+  uint4 slab[PLANE * (int)sizeof(T) / 2];
+  uint4 first[2];
+  SmallLds lds;
+};
+
+// this thread's rows of a stride-1 3 x 3 convolution of the slab, rounded as a store rounds them (rows past M: zeros)
+template <class T, bool FLIP>
+__device__ __forceinline__ void dw_small_conv(typename BufIO<T>::Raw (&raw)[kDwSmallRows], const uint4* slab, const T* __restrict__ w, int cv, int ncv, int M, int H, int W) {
+  constexpr int ROWS = DwSmall<T>::ROWS, PLANE = DwSmall<T>::PLANE;
+  float f[9][8];
+#pragma unroll
+  for (int t = 0; t < 9; ++t) IO<T>::ld(w + ((long)(FLIP ? 8 - t : t) * ncv + cv) * 8, f[t]);
+  const int lane_row = threadIdx.x;
+#pragma unroll
+  for (int u = 0; u < kDwSmallRows; ++u) {
+    const int m = u * kSmallThreads + lane_row;
+    float acc[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+    if (m < M) {
+      const int q = m % W, h = (m / W) % H;
+#pragma unroll
+      for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+          const bool in = (unsigned)(h + r - 1) < (unsigned)H && (unsigned)(q + t - 1) < (unsigned)W;
+          float v[8];
+          BufIO<T>::unpack(BufIO<T>::slab_read(slab, PLANE, in ? m + (r - 1) * W + t - 1 : ROWS), v);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) acc[e] = fmaf(v[e], f[r * 3 + t][e], acc[e]);
+        }
+    }
+    raw[u] = BufIO<T>::pack(acc);
+  }
+}
+
+template <class T, bool PRE>
+__global__ __launch_bounds__(kSmallThreads) void dw_small_fwd_kernel(const T* __restrict__ x, T* __restrict__ z1, ColFwd pre, const T* __restrict__ w,
+    T* __restrict__ y2, T* __restrict__ z2, ColFwd bn, int M, int H, int W, int Cp, float eps, float rho, unsigned bytes) {
+  typedef BufIO<T> B;
+  typedef typename B::Raw Raw;
+  constexpr int ROWS = DwSmall<T>::ROWS, PLANE = DwSmall<T>::PLANE;
+  __shared__ DwSmall<T> sm;
+  const int ncv = Cp / 8, cv = xcd_slab(blockIdx.x, ncv), tid = threadIdx.x;
+  const __amdgpu_buffer_rsrc_t rx = tensor_rsrc(x, bytes);
+  Raw raw[kDwSmallRows];
+#pragma unroll
+  for (int u = 0; u < kDwSmallRows; ++u) {
+    const int r = u * kSmallThreads + tid;
+    raw[u] = B::issue(rx, (unsigned)(r * ncv + cv) * 8u, r < M);
+  }
+  auto at = [&](T* p, int r) { return reinterpret_cast<Raw*>(p + ((long)r * ncv + cv) * 8); };
+  float piv[8];
+  SmallTerms t;
+  if constexpr (PRE) {
+    IO<T>::ld(x + (long)cv * 8, piv);
+    small_stats<T>(raw, piv, pre, t, sm.lds, cv, M, eps, rho);
+  }
+#pragma unroll
+  for (int u = 0; u < kDwSmallRows; ++u) {
+    const int r = u * kSmallThreads + tid;
+    if (r >= M) continue;
+    if constexpr (PRE) {
+      float v[8];
+      B::unpack(raw[u], v);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = apply_act(fmaf(v[k] - t.mu[k], t.a[k], t.b[k]), pre.act);
+      raw[u] = B::pack(v);
+      *at(z1, r) = raw[u];
+    }
+    B::slab_write(sm.slab, PLANE, r, raw[u]);
+  }
+  const float zero[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (tid == 0) B::slab_write(sm.slab, PLANE, ROWS, B::pack(zero));
+  __syncthreads();
+  dw_small_conv<T, false>(raw, sm.slab, w, cv, ncv, M, H, W);
+  if (tid == 0) B::slab_write(sm.first, 1, 0, raw[0]);
+#pragma unroll
+  for (int u = 0; u < kDwSmallRows; ++u) {
+    const int r = u * kSmallThreads + tid;
+    if (r < M) *at(y2, r) = raw[u];
+  }
+  __syncthreads();
+  B::unpack(B::slab_read(sm.first, 1, 0), piv);
+  small_stats<T>(raw, piv, bn, t, sm.lds, cv, M, eps, rho);
+#pragma unroll
+  for (int u = 0; u < kDwSmallRows; ++u) {
+    const int r = u * kSmallThreads + tid;
+    if (r >= M) continue;
+    float v[8];
+    B::unpack(raw[u], v);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = apply_act(fmaf(v[k] - t.mu[k], t.a[k], t.b[k]), bn.act);
+    IO<T>::st(z2 + ((long)r * ncv + cv) * 8, v);
+  }
+}
+
+template <class T, bool PRE>
+__global__ __launch_bounds__(kSmallThreads) void dw_small_bwd_kernel(T* __restrict__ dz2, const T* __restrict__ y2, ColBwd bn, const T* __restrict__ w, T* __restrict__ dx,
+    const T* __restrict__ y1, ColBwd pre, int M, int H, int W, int Cp, unsigned bytes) {
+  typedef BufIO<T> B;
+  typedef typename B::Raw Raw;
+  constexpr int ROWS = DwSmall<T>::ROWS, PLANE = DwSmall<T>::PLANE;
+  __shared__ DwSmall<T> sm;
+  const int ncv = Cp / 8, cv = xcd_slab(blockIdx.x, ncv), tid = threadIdx.x;
+  const __amdgpu_buffer_rsrc_t rd = tensor_rsrc(dz2, bytes), ry = tensor_rsrc(y2, bytes);
+  Raw rawd[kDwSmallRows], rawy[kDwSmallRows];
+#pragma unroll
+  for (int u = 0; u < kDwSmallRows; ++u) {
+    const int r = u * kSmallThreads + tid;
+    rawd[u] = B::issue(rd, (unsigned)(r * ncv + cv) * 8u, r < M);
+    rawy[u] = B::issue(ry, (unsigned)(r * ncv + cv) * 8u, r < M);
+  }
+  auto at = [&](T* p, int r) { return reinterpret_cast<Raw*>(p + ((long)r * ncv + cv) * 8); };
+  small_bwd<T>(rawd, rawy, bn, sm.lds, cv, M, [&](int, int r, const float (&d)[8]) {
+    const Raw q = B::pack(d);
+    *at(dz2, r) = q;
+    B::slab_write(sm.slab, PLANE, r, q);
+  });
+  if constexpr (PRE) {                                   // in flight behind the convolution
+    const __amdgpu_buffer_rsrc_t rp = tensor_rsrc(y1, bytes);
+#pragma unroll
+    for (int u = 0; u < kDwSmallRows; ++u) {
+      const int r = u * kSmallThreads + tid;
+      rawy[u] = B::issue(rp, (unsigned)(r * ncv + cv) * 8u, r < M);
+    }
+  }
+  const float zero[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (tid == 0) B::slab_write(sm.slab, PLANE, ROWS, B::pack(zero));
+  __syncthreads();
+  dw_small_conv<T, true>(rawd, sm.slab, w, cv, ncv, M, H, W);
+  if constexpr (PRE) {
+    small_bwd<T>(rawd, rawy, pre, sm.lds, cv, M, [&](int, int r, const float (&d)[8]) { *at(dx, r) = B::pack(d); });
+  } else {
+#pragma unroll
+    for (int u = 0; u < kDwSmallRows; ++u) {
+      const int r = u * kSmallThreads + tid;
+      if (r < M) *at(dx, r) = rawd[u];
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------

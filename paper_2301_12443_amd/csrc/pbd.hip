@@ -1182,6 +1182,17 @@ template <class T> inline bool adds_sums(long M, int Cp) {
   if (short_column(M) && (row < 64 || (row < 128 && M <= kNarrowRows))) return false;
   return M > kColumnRows && (double)M * Cp * sizeof(T) <= kSumsBytes && slab_grid(M, Cp).chunks <= kSumChunksMax;
 }
+// The only reader of student layer j's output, -1 if there are several (a block's last value is read by the loss).
+int sole_reader(const BlockPlan& bp, int j) {
+  int reader = -1, uses = j + 2 == (int)bp.shapes.size() ? 1 : 0;
+  for (int k = j + 1; k < (int)bp.ops.size(); ++k) {
+    const OpD& q = bp.ops[k].d;
+    const int nin = q.type == OP_ADD || q.type == OP_MIX ? q.nin : 1;
+    for (int i = 0; i < nin; ++i)
+      if (q.in[i] == j + 1) { ++uses; reader = k; }
+  }
+  return uses == 1 ? reader : -1;
+}
 // For student layer j: the index of a max-pool that is the only reader of j's output (the pool then normalises what
 // it reads and the normalised tensor is never written), else -1.
 int pool_reader(const BlockPlan& bp, int j, int batch) {
@@ -1689,6 +1700,18 @@ template <class T> struct Exec {
   // 3 x 3 layers on tensors far larger than the caches with whole 64-channel groups: dw_tile_kernel (not where the forward kernel
   // also delivers the statistics: 128 x 56 x 56 x 192 80 us against 64 and a pass of 29)
   bool dw_tiles(const OpPlan& op) const { return dw_mfma(op) && op.d.k == 3 && op.cout_p % 64 == 0 && streams(op.out); }
+  // Layer j's launches of short columns: a 3 x 3 stride-1 depthwise layer on the sliding windows of a column short enough
+  // takes the batch norms around it along (dw_small_fwd_kernel, dw_small_bwd_kernel).  Not in a block with mixed layers, whose launches go
+  // out for several candidates at a time as it is.
+  bool dw_small(const BlockPlan& bp, const OpPlan& op) const {
+    return op.d.type == OP_CBA && op.dw && !c->o.force_direct && bp.groups.empty() && op.d.k == 3 && op.d.stride == 1 && dw_slides(op) && !dw_mfma(op) &&
+           (long)c->o.batch * op.out.h * op.out.w <= DwSmall<T>::ROWS;
+  }
+  // the dense layer right in front, whose normalised output layer j reads: index, else -1
+  int dw_small_pre(const BlockPlan& bp, int j) const {
+    const int p = bp.ops[j].d.in[0] - 1;
+    return p >= 0 && bp.ops[p].d.type == OP_CBA && !bp.ops[p].dw && dw_small(bp, bp.ops[j]) ? p : -1;
+  }
   // stats (optional; matrix-core kernels only): a mean, a sum of squares about it and a number of pixels per channel and
   // dw_stat_rows(op) groups of outputs; fold (ditto): x is the producing layer's convolution output, normalised as it is staged
   void dw_fwd(const OpPlan& op, const T* x, const T* w, T* y, const float* a, const float* b, int act, NormFold fold = NormFold{},
@@ -2117,6 +2140,7 @@ template <class T> struct Exec {
     // ---- forward ----------------------------------------------------------
     std::vector<char> fused(bp.ops.size(), 0);      // adds that rode in their producer's normalisation pass
     int group = -1;                                 // the mixed layer whose candidates are at work
+    bool pre_norm = false;                          // the last layer's batch norm is left to the next one (dw_small_pre)
     for (size_t j = 0; j < bp.ops.size(); ++j) {
       const OpPlan& op = bp.ops[j];
       opi = (int)j;
@@ -2129,12 +2153,30 @@ template <class T> struct Exec {
         const int iv = op.d.in[0];
         const int stat_tiles = op.dw ? 0 : fused_stats_tiles(op);
         const int dw_rows = dw_stat_rows(op);
+        const long M = (long)N * op.out.h * op.out.w;
+        auto bn_of = [&](const OpPlan& o) {
+          return ColFwd{master + o.e_gamma, master + o.e_beta, wsf(o.s_mean), wsf(o.s_invstd), wsf(o.s_rmean), wsf(o.s_rvar), o.d.act};
+        };
+        if (dw_small(bp, op) && !folds_into(iv)) {
+          const bool pre = pre_norm;
+          pre_norm = false;
+          const T* from = pre ? ws(scr + bp.ops[iv - 1].y) : x;
+          ProfScope ps(c, pre ? "dw_small_fwd_bn" : "dw_small_fwd", (pre ? 4 : 3) * bytes_of(op.out), 2.0 * M * op.d.c_out * 9, net, blk, opi);
+          launch(c, pre ? dw_small_fwd_kernel<T, true> : dw_small_fwd_kernel<T, false>, op.cout_p / 8, kSmallThreads, 0, st, from, value(iv),
+                 pre ? bn_of(bp.ops[iv - 1]) : ColFwd{}, wc + op.e_w, y, z, bn_of(op), (int)M, op.in.h, op.in.w, op.cout_p, c->o.bn_eps, c->o.bn_momentum,
+                 (unsigned)(M * op.cout_p * sizeof(T)));
+          continue;
+        }
         if (op.dw) dw_fwd(op, folds_into(iv) ? ws(scr + bp.ops[iv - 1].y) : x, wc + op.e_w, y, nullptr, nullptr, 0, input_fold(iv),
                           dw_rows ? red() : nullptr);
         else conv_fwd(op, folds_into(iv) ? ws(scr + bp.ops[iv - 1].y) : x, wc + op.e_w, y, nullptr, nullptr, 0, nullptr, 0, stat_tiles ? red() : nullptr,
                       input_fold(iv));
-        const long M = (long)N * op.out.h * op.out.w;
         if (short_column(M)) {
+          // (its reader right behind it does it)
+          if (!op.dw && j + 1 < bp.ops.size() && bp.ops[j + 1].d.type == OP_CBA && bp.ops[j + 1].d.in[0] == (int)j + 1 && dw_small_pre(bp, (int)j + 1) == (int)j) {
+            pre_norm = true;
+            continue;
+          }
           ProfScope ps(c, "bn_small_fwd", 3 * bytes_of(op.out), 0, net, blk, opi);
           launch(c, bn_small_fwd_kernel<T>, op.cout_p / 8, kSmallThreads, 0, st, y, z, master + op.e_gamma,
                  master + op.e_beta, wsf(op.s_mean), wsf(op.s_invstd), wsf(op.s_rmean), wsf(op.s_rvar), (int)M,
@@ -2257,6 +2299,7 @@ template <class T> struct Exec {
     // gradient, masks it and stores the result once, where the add's other input collects its gradient.
     struct AddBwd { const T* dz; const T* z; int act; T* dstore; bool loss; };
     std::vector<AddBwd> add_bwd(bp.ops.size(), AddBwd{nullptr, nullptr, 0, nullptr, false});
+    std::vector<char> normed(bp.ops.size(), 0);     // layers whose batch-norm backward pass their reader took (dw_small_bwd)
     std::vector<char> summed(bp.ops.size(), 0);     // layers whose batch-norm sums the backward pass of their reader took (dw_bwd, pj_bwd)
     for (int j = (int)bp.ops.size() - 1; j >= 0; --j) {
       const OpPlan& op = bp.ops[j];
@@ -2283,7 +2326,21 @@ template <class T> struct Exec {
         const long M = (long)N * op.out.h * op.out.w;
         const AddBwd ab = add_bwd[j];
         const T* dz_in = ab.dz ? ab.dstore : dz;     // what the last stage reads (dz: in place)
-        if (short_column(M) && !adds_sums<T>(M, op.cout_p)) {
+        auto bn_of = [&](const OpPlan& o) {
+          return ColBwd{master + o.e_gamma, master + o.e_beta, wsf(o.s_mean), wsf(o.s_invstd), grad + o.e_gamma, grad + o.e_beta, o.d.act};
+        };
+        bool passed = false;                            // backward-data has been taken care of
+        if (normed[j]) {
+        } else if (short_column(M) && !adds_sums<T>(M, op.cout_p) && dw_small(bp, op) && !arch && wanted[iv] && !have[iv]) {
+          const int p = dw_small_pre(bp, j);
+          const bool pre = p >= 0 && sole_reader(bp, p) == j;
+          ProfScope ps(c, pre ? "dw_small_bwd_bn" : "dw_small_bwd", (pre ? 5 : 4) * bytes_of(op.out), 2.0 * M * op.d.c_out * 9, net, blk, opi);
+          launch(c, pre ? dw_small_bwd_kernel<T, true> : dw_small_bwd_kernel<T, false>, op.cout_p / 8, kSmallThreads, 0, st, dz, y, bn_of(op), wc + op.e_w,
+                 dvalue(iv), pre ? ws(scr + bp.ops[p].y) : (const T*)nullptr, pre ? bn_of(bp.ops[p]) : ColBwd{}, (int)M, op.in.h, op.in.w, op.cout_p,
+                 (unsigned)(M * op.cout_p * sizeof(T)));
+          if (pre) normed[p] = 1;
+          passed = true;
+        } else if (short_column(M) && !adds_sums<T>(M, op.cout_p)) {
           ProfScope ps(c, "bn_small_bwd", 5 * bytes_of(op.out), 0, net, blk, opi);
           launch(c, bn_small_bwd_kernel<T>, op.cout_p / 8, kSmallThreads, 0, st, dz, y, master + op.e_gamma,
                  master + op.e_beta, wsf(op.s_mean), wsf(op.s_invstd), grad + op.e_gamma, grad + op.e_beta, (int)M,
@@ -2358,7 +2415,9 @@ template <class T> struct Exec {
           else conv_wgrad(op, dz, folds_into(iv) ? ws(scr + bp.ops[iv - 1].y) : x, grad + op.e_w, input_fold(iv));
           c->late.on = false;
         }
-        if (wanted[iv]) {  // A_{i-1} is a constant: no backward-data for the block's first layer
+        if (passed) {
+          have[iv] = 1;
+        } else if (wanted[iv]) {  // A_{i-1} is a constant: no backward-data for the block's first layer
           c->lanes.serial = group >= 0 && iv == bp.groups[group].root;     // (every lane adds to that one)
           if (op.dw) dw_dgrad(op, dz, wc + op.e_w, dvalue(iv), have[iv]);
           else conv_dgrad(op, dz, wc + op.e_w, op.e_wt >= 0 ? ws(bp.wt) + op.e_wt : nullptr, dvalue(iv), have[iv]);
