@@ -2704,14 +2704,16 @@ double block_us(const pbd_ctx* c, int net, int b, int* launches = nullptr) {
 }
 // Does the host bound the step's graph?  Launches of 6 us at most, by the estimate above.  Estimate, then us of a call with the branches in one graph / in
 // pieces: VGG-16 at 32 x 32, two to four batches in a pipeline, batch 32 5.2 us a launch 2573 / 2013; batch 85, one step 6.2 827 / 836; batch 256 9.8
-// 4800 / 4837; four-layer network at batch 8 4.6 220 / 179 (167 / 170 on another machine); MobileNetV2 in a pipeline at batch 16 6.4 5130 / 5170;
-// and where several contexts share the GPU the pieces of one stand in the way of the other's: VGG-16 at batch 85, three in turn, 773 / 840.
+// 4800 / 4837; MobileNetV2 in a pipeline at batch 16 6.4 5130 / 5170; and where several contexts share the GPU the pieces of one stand in the way of the
+// other's: VGG-16 at batch 85, three in turn, 773 / 840.
+// And sixteen launches or more a piece, which costs the host as much as eight of a graph with branches: the four-layer network (8 a piece) 220 / 177 us
+// on one machine and 167 / 170 on another, two batches of it in a pipeline with three contexts in turn 337 / 387.
 bool in_pieces(const pbd_ctx* c) {
   double us = 0;
   int n = 0;
   for (int net : {PBD_TEACHER, PBD_STUDENT})
     for (int b = 0; b < c->B; ++b) us += block_us(c, net, b, &n);
-  return us <= 6.0 * n;
+  return us <= 6.0 * n && n >= 16 * 2 * c->B;
 }
 
 constexpr int kSideStreams = 3, kSideTries = 8;
