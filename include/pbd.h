@@ -186,10 +186,7 @@ int pbd_student_step_static(pbd_ctx* ctx, int32_t i, const pbd_tensor* A_prev, c
  * losses_dev: device float32[B].  Same results as the two calls above.  When the bound
  * stream is a real (non-null) stream and profiling is off, the body of the step is
  * captured once into a HIP graph and replayed on later calls (it only touches
- * workspace addresses; x_dev, lr and losses_dev stay outside the graph).  A step of short
- * launches, which the host's cost of replaying that graph would bound, is captured block by
- * block instead and replayed on the bound stream and up to three streams of the context,
- * behind the bound stream's earlier work and before its later work. */
+ * workspace addresses; x_dev, lr and losses_dev stay outside the graph). */
 int pbd_distill_step(pbd_ctx* ctx, const float* x_dev, float lr, float* losses_dev);
 
 /* Architecture round of a supernet student (Sec. VI-A, neural architecture search: every step has a
@@ -222,7 +219,7 @@ int pbd_distill_arch_step(pbd_ctx* ctx, const float* x_dev, float lr_alpha, floa
  * leaves losses_dev alone.  pbd_pipeline_flush trains the students on the batch still waiting (nothing
  * if none) and writes its losses.  K calls and a flush leave the same parameters, statistics and losses,
  * bit for bit, as K calls of pbd_distill_step on the same batches.  x_dev is consumed by the call (it is
- * cast into the store).  Graph capture as for pbd_distill_step (one graph, or one of each block, per copy).  While a batch waits,
+ * cast into the store).  Graph capture as for pbd_distill_step (one graph per copy).  While a batch waits,
  * the one-step calls (relay, prefix, student, architecture and whole steps) return PBD_ESTATE, the views
  * and pbd_read_act show the waiting batch, and pbd_read_value has nothing to show until the flush.
  * Parameters loaded while a batch waits are the ones its students then train from.
@@ -233,9 +230,9 @@ int pbd_distill_arch_step(pbd_ctx* ctx, const float* x_dev, float lr_alpha, floa
 int pbd_pipeline_step(pbd_ctx* ctx, const float* x_dev, float lr, float* losses_dev);
 int pbd_pipeline_flush(pbd_ctx* ctx, float* losses_dev);
 
-/* Order in which pbd_pipeline_step captures or sends out its B+1 independent branches: a permutation of
+/* Order in which pbd_pipeline_step captures its B+1 independent branches into the graph: a permutation of
  * 0..B, where b < B is student block b (from 0) and B is the teacher's relay (Sec. IV-B: no block depends
- * on another, so every order computes the same bits).  The order decides how the branches share
+ * on another, so every order computes the same bits).  The order decides how the replayed branches share
  * the GPU's hardware queues and moves the step time by a few per cent; the best one depends on the
  * workload, so a caller times a few and keeps the fastest.  Default: 0, 1, .., B.  n must be B+1
  * (PBD_EINVAL otherwise, also for a non-permutation); PBD_ESTATE while a batch waits.  Host-only apart

@@ -163,10 +163,9 @@ __device__ __forceinline__ bool act_pass(float v, int act) {
 // ---------------------------------------------------------------------------
 template <class T>
 __global__ void cast_input_kernel(const float* __restrict__ x, T* __restrict__ out, int N, int C,
-                                  int HW, int Cp, float* lr_at, float lr) {
+                                  int HW, int Cp) {
   const long nvec = (long)N * HW * (Cp / 8);
   const int ncv = Cp / 8;
-  if (lr_at && blockIdx.x == 0 && threadIdx.x == 0) *lr_at = lr;
   for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < nvec; i += (long)gridDim.x * blockDim.x) {
     const int cv = (int)(i % ncv);
     const long pix = i / ncv;
@@ -1776,15 +1775,6 @@ __global__ void sgd_momentum_kernel(float* __restrict__ w, float* __restrict__ v
   }
 }
 
-__global__ void copy_floats_kernel(const float* __restrict__ src, float* __restrict__ dst, int n) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = src[i];
-}
-// Which streams share a hardware queue (share_a_queue): ~30 us on one lane, at most 2^14 looks at the clock, and nothing at all
-__global__ void queue_busy_kernel() {
-  const long long t0 = wall_clock64();
-  for (int i = 0; i < (1 << 14) && wall_clock64() - t0 < 3000; ++i) __builtin_amdgcn_s_sleep(1);
-}
-__global__ void queue_empty_kernel() {}
 __global__ void set_scalar_kernel(float* p, float v) { *p = v; }
 
 // compute copy <- rne(master) without an update (after parameters were loaded)

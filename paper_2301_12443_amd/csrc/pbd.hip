@@ -11,7 +11,6 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
-#include <memory>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -147,39 +146,6 @@ struct Lanes {
   pbd_prof_entry label{};
 };
 
-// A part of a step, captured on first use: launches that follow one another on one stream.
-struct Piece { hipGraphExec_t exec = nullptr; bool tried = false; };
-
-// The streams and events that captures branch out with, one of each a student block.  They stay with the context: the streams inside a graph are
-// dealt out to the hardware queues by how many each has, and without these the search step at batch 16 on three contexts in turn takes 16.06 instead of 15.78 ms.
-struct Fork {
-  std::vector<hipStream_t> side;
-  std::vector<hipEvent_t> forked, joined;
-  bool ok = true;
-  explicit Fork(int B) {
-    for (int b = 0; b < B && ok; ++b) {
-      hipStream_t s2 = nullptr; hipEvent_t e1 = nullptr, e2 = nullptr;
-      ok = hipStreamCreateWithFlags(&s2, hipStreamNonBlocking) == hipSuccess; if (s2) side.push_back(s2);
-      ok = ok && hipEventCreateWithFlags(&e1, hipEventDisableTiming) == hipSuccess; if (e1) forked.push_back(e1);
-      ok = ok && hipEventCreateWithFlags(&e2, hipEventDisableTiming) == hipSuccess; if (e2) joined.push_back(e2);
-    }
-  }
-  ~Fork() {
-    for (hipStream_t s2 : side) (void)hipStreamDestroy(s2);
-    for (hipEvent_t e : forked) (void)hipEventDestroy(e);
-    for (hipEvent_t e : joined) (void)hipEventDestroy(e);
-  }
-  void mark(int e, hipStream_t from) const { (void)hipEventRecord(forked[e], from); }
-  hipStream_t follow(int b, int e) const { (void)hipStreamWaitEvent(side[b], forked[e], 0); return side[b]; }
-  void join(hipStream_t to) const {
-    for (size_t b = 0; b < side.size(); ++b) {
-      (void)hipEventRecord(joined[b], side[b]);
-      (void)hipStreamWaitEvent(to, joined[b], 0);
-    }
-  }
-  Fork(const Fork&) = delete;
-};
-
 struct pbd_ctx {
   pbd_opts o{};
   Lanes lanes, late;                    // launches that wait for those of other lanes; weight gradients that wait for their block's
@@ -194,10 +160,8 @@ struct pbd_ctx {
   // regions (byte offsets from the workspace base)
   size_t r_param = 0, r_relay = 0, r_relay2 = 0, r_tscr = 0, r_tred = 0, total = 0;
   bool concurrent = false;              // student blocks own disjoint scratch and may overlap
-  // The branches of a step (student blocks, the teacher) beside each other: graphs without branches of their own, launched on the
-  // bound stream and these (at most kSideStreams), ordered by events.
-  std::vector<hipStream_t> side;
-  std::vector<hipEvent_t> ev_fork, ev_join;   // per block: its target is there; per side stream: its work of this step is done
+  std::vector<hipStream_t> side;        // one stream per student block (graph capture branches)
+  std::vector<hipEvent_t> ev_fork, ev_join;
   char* ws = nullptr;
   int num_cu = 256;                     // compute units of the bound device (tile-count heuristics)
   hipStream_t stream = nullptr;
@@ -206,19 +170,19 @@ struct pbd_ctx {
   std::string err;
   // profiling
   size_t lr_off = 0, loss_off = 0;      // device scalars: learning rate, per-block losses
-  bool pieces = false;                  // the blocks of a step go out as graphs of their own (in_pieces)
-  std::vector<Piece> g_teacher[3];      // teacher block b into copy 0; [1], [2]: the last one with the last student block behind it
-  std::unique_ptr<Fork> fork;
-  Piece g_step[2], g_pipe[2], g_drain[2];   // [round], [copy the teacher writes], [copy read]: graphs with the branches inside
-  Piece g_relay[2];                     // the whole relay into copy q
-  std::vector<Piece> g_student[3];      // student block b: weight round reading copy 0 / 1, architecture round reading copy 0
+  hipGraphExec_t gexec[2] = {nullptr, nullptr};   // the captured step: [0] weight round, [1] architecture round
+  bool graph_tried[2] = {false, false};
   // pipelined steps (pbd_pipeline_step): the relay store exists twice; `front` is the copy the teacher
   // wrote last (the one the views and read-backs show), `pending` says that its batch still waits for
-  // the students.
+  // the students.  gpipe[q]: captured body with the teacher writing copy q and the students reading 1-q.
   int front = 0;
   bool pending = false;
   float pending_lr = 0.f;
-  std::vector<int> pipe_order;                    // order in which the branches start (pbd_set_pipeline_order): block indices, B = the teacher
+  hipGraphExec_t gpipe[2] = {nullptr, nullptr};
+  bool gpipe_tried[2] = {false, false};
+  std::vector<int> pipe_order;                    // order in which the branches are captured: block indices, B = the teacher
+  hipGraphExec_t gdrain[2] = {nullptr, nullptr};  // the students alone, reading copy q (pbd_pipeline_flush)
+  bool gdrain_tried[2] = {false, false};
   bool prof_on = false;
   std::vector<hipEvent_t> ev;
   hipEvent_t pend_start = nullptr, pend_stop = nullptr;   // events waiting for the next launch
@@ -2009,23 +1973,21 @@ template <class T> struct Exec {
   void set_lr(float lr) { launch(c, set_scalar_kernel, 1, 1, 0, st, wsf(c->lr_off), lr); }
 
   // everything a step needs that depends on the caller's pointers or on freshly loaded parameters
-  void prepare(const float* x_dev, float lr) {
+  void prepare(const float* x_dev) {
     if (c->fold_dirty) fold_teacher_bn();
     for (int b = 0; b < c->B; ++b) {
       net = PBD_STUDENT; blk = b;
       if (c->net[1][b].dirty) refresh_compute_copies(c->net[1][b]);
     }
-    cast_input(x_dev, wsf(c->lr_off), lr);
+    cast_input(x_dev);
   }
-  // lr_at (optional): the learning rate goes there, one launch less at the head of a step
-  void cast_input(const float* x_dev, float* lr_at = nullptr, float lr = 0.f) {
+  void cast_input(const float* x_dev) {
     {
       const Shape s = c->act[0];
       const long nvec = (long)c->o.batch * s.h * s.w * round8(s.c) / 8;
       net = PBD_TEACHER; blk = -1; opi = -1;
       ProfScope ps(c, "cast_input", (double)c->o.batch * s.c * s.h * s.w * 4 + bytes_of(s), 0, net, blk, opi);
-      launch(c, cast_input_kernel<T>, grid_for(nvec), 256, 0, st, x_dev, trelay(0), c->o.batch, s.c, s.h * s.w, round8(s.c),
-             lr_at, lr);
+      launch(c, cast_input_kernel<T>, grid_for(nvec), 256, 0, st, x_dev, trelay(0), c->o.batch, s.c, s.h * s.w, round8(s.c));
     }
     if (c->s2d_off != (size_t)-1) {
       const Shape s = c->act[0];
@@ -2045,49 +2007,59 @@ template <class T> struct Exec {
     c->relayed_upto = upto;
   }
   // the pointer-independent body of a step: T_1..T_B once each, then every student block
-  // With `fork` (graph capture, disjoint scratch) student block b runs on its own stream as soon as T_b has produced its target, next to T_{b+1}:
-  // the one-device form of the overlap of Sec. IV-A.
-  void step_body(bool arch, const Fork* fork = nullptr) {
+  // With `fork` (graph capture, disjoint scratch) student block b runs on its own stream as soon as
+  // T_b has produced its target, next to T_{b+1}: the one-device form of the overlap of Sec. IV-A.
+  void step_body(bool fork, bool arch = false) {
     hipStream_t main = st;
     for (int b = 0; b < c->B; ++b) {
       teacher_block(b);
       if (fork) {
-        fork->mark(b, main);
-        st = fork->follow(b, b);
+        (void)hipEventRecord(c->ev_fork[b], main);
+        (void)hipStreamWaitEvent(c->side[b], c->ev_fork[b], 0);
+        st = c->side[b];
         student_block(b, wsf(c->loss_off) + b, arch);
+        (void)hipEventRecord(c->ev_join[b], st);
         st = main;
       }
     }
-    if (fork) fork->join(main);
-    else students(arch);
+    for (int b = 0; b < c->B; ++b) {
+      if (fork) (void)hipStreamWaitEvent(main, c->ev_join[b], 0);
+      else student_block(b, wsf(c->loss_off) + b, arch);
+    }
     c->relayed_upto = c->B;
   }
-  // One stage of the pipeline over steps (Sec. IV-A and IV-B: with the updates decoupled, the teacher goes on to the next batch while the students
-  // still train on the last one): nothing of one depends on the other, so every student block and the teacher chain start together.
-  void pipe_body(const Fork* fork, bool teacher) {
+  // One stage of the pipeline over steps (Sec. IV-A and IV-B: with the updates decoupled, the teacher
+  // goes on to the next batch while the students still train on the last one): the teacher relays the
+  // new batch into copy `tset` of the store; the students train on the batch in copy `sset`.  Nothing
+  // of one depends on the other, so with `fork` every student block and the teacher chain start together.
+  void pipe_body(bool fork, bool teacher = true) {
     hipStream_t main = st;
     if (fork) {
-      // Any order of capture gives the same results; it decides how the replayed graph's branches share the hardware queues.
-      fork->mark(0, main);
+      (void)hipEventRecord(c->ev_fork[0], main);
+      // The branches are independent, so any order of capture gives the same results; it decides how the
+      // replayed graph's branches share the hardware queues, and with that the step time (a few per cent).
       for (int i = 0; i <= c->B; ++i) {
-        const int b = c->pipe_order.empty() ? i : c->pipe_order[i];
-        if (b < c->B) {
-          st = fork->follow(b, 0);
-          student_block(b, wsf(c->loss_off) + b);
+        const int b = (int)c->pipe_order.size() == c->B + 1 ? c->pipe_order[i] : i;
+        if (b == c->B) {
           st = main;
-        } else if (teacher) {
-          for (int t = 0; t < c->B; ++t) teacher_block(t);
+          if (teacher)
+            for (int t = 0; t < c->B; ++t) teacher_block(t);
+          teacher = false;
+          continue;
         }
+        (void)hipStreamWaitEvent(c->side[b], c->ev_fork[0], 0);
+        st = c->side[b];
+        student_block(b, wsf(c->loss_off) + b);
+        (void)hipEventRecord(c->ev_join[b], st);
       }
-      fork->join(main);
-      return;
+      st = main;
     }
     if (teacher)
-      for (int t = 0; t < c->B; ++t) teacher_block(t);
-    students();
-  }
-  void students(bool arch = false) {
-    for (int b = 0; b < c->B; ++b) student_block(b, wsf(c->loss_off) + b, arch);
+      for (int b = 0; b < c->B; ++b) teacher_block(b);
+    for (int b = 0; b < c->B; ++b) {
+      if (fork) (void)hipStreamWaitEvent(main, c->ev_join[b], 0);
+      else student_block(b, wsf(c->loss_off) + b);
+    }
   }
 
   // =========================================================================
@@ -2678,243 +2650,19 @@ void fill_view(pbd_ctx* c, int i, pbd_tensor* t) {
   t->dtype = c->o.precision;
 }
 
-// ---- the branches of a step beside each other ----
-// Student blocks depend on nothing but their own two activations (Sec. IV-B), so they overlap with later teacher blocks and with each other: the
-// one-device form of the overlap of Sec. IV-A.  As a rule the whole step is one graph with these branches inside.  Replaying one costs 2.5 to 4 us of
-// host time a launch, though, while a graph whose launches follow one another is replayed as ready-made queue packets, ~20 us whatever its
-// length.  So a step of short launches, which the host would bound, goes out in pieces (in_pieces): every block a graph of its own, on four
-// streams, ordered by events.
-// Four streams, as many as a process has hardware queues, each on a queue of its own: two branches on one queue follow one another (VGG-16 at
-// batch 85, blocks 2 and 3 on one: 832 -> 1035 us).  The runtime deals queues out to streams by how many each has, and the caller's
-// and torch's streams come before these, so streams are created and tried until three are found that run beside the bound one and each other.
-
-// Rough time of a block in us and its launches: 4.5 us a launch, the tensors at 4.5 TB/s, dense products at 500 TFLOP/s (float32 60).
-double block_us(const pbd_ctx* c, int net, int b, int* launches = nullptr) {
-  const double rate = c->o.precision == PBD_BF16 ? 5e8 : 6e7;
-  double us = 0;
-  for (const OpPlan& op : c->net[net][b].ops) {
-    const double out = (double)c->o.batch * op.out.h * op.out.w * op.cout_p * c->esz, in = (double)c->o.batch * op.in.h * op.in.w * op.cin_p * c->esz;
-    const bool cba = op.d.type == OP_CBA, student = net == PBD_STUDENT;
-    const int n = !student ? 1 : cba ? 8 : 2;
-    if (launches) *launches += n;
-    us += 4.5 * n + (!student ? in + out : cba ? 3 * in + 11 * out : 2 * (in * op.d.nin + out)) / 4.5e6;
-    if (cba && !op.dw) us += (student ? 3 : 1) * 2.0 * c->o.batch * op.out.h * op.out.w * op.d.c_out * op.d.k * op.d.k * op.in.c / rate;
-  }
-  return us;
-}
-// Does the host bound the step's graph?  Launches of 6 us at most, by the estimate above.  Estimate, then us of a call with the branches in one graph / in
-// pieces: VGG-16 at 32 x 32, two to four batches in a pipeline, batch 32 5.2 us a launch 2573 / 2013; batch 85, one step 6.2 827 / 836; batch 256 9.8
-// 4800 / 4837; MobileNetV2 in a pipeline at batch 16 6.4 5130 / 5170; and where several contexts share the GPU the pieces of one stand in the way of the
-// other's: VGG-16 at batch 85, three in turn, 773 / 840.
-// And sixteen launches or more a piece, which costs the host as much as eight of a graph with branches: the four-layer network (8 a piece) 220 / 177 us
-// on one machine and 167 / 170 on another, two batches of it in a pipeline with three contexts in turn 337 / 387.
-bool in_pieces(const pbd_ctx* c) {
-  double us = 0;
-  int n = 0;
-  for (int net : {PBD_TEACHER, PBD_STUDENT})
-    for (int b = 0; b < c->B; ++b) us += block_us(c, net, b, &n);
-  return us <= 6.0 * n && n >= 16 * 2 * c->B;
-}
-
-constexpr int kSideStreams = 3, kSideTries = 8;
-
-// Does what is sent to b wait for what a has been given?  (On a queue that is busy with other work it may look so without being so.)
-bool share_a_queue(hipStream_t a, hipStream_t b, hipEvent_t ea, hipEvent_t eb) {
-  void* none[] = {nullptr};
-  if (hipLaunchKernel((const void*)queue_busy_kernel, dim3(1), dim3(1), none, 0, a) != hipSuccess || hipEventRecord(ea, a) != hipSuccess ||
-      hipLaunchKernel((const void*)queue_empty_kernel, dim3(1), dim3(1), none, 0, b) != hipSuccess || hipEventRecord(eb, b) != hipSuccess) return true;
-  if (hipEventSynchronize(eb) != hipSuccess) return true;
-  const bool shared = hipEventQuery(ea) == hipSuccess;
-  (void)hipGetLastError();                              // (not ready is no error)
-  (void)hipEventSynchronize(ea);
-  return shared;
-}
-void drop_streams(pbd_ctx* c) {
-  for (hipStream_t s2 : c->side) { (void)hipStreamSynchronize(s2); (void)hipStreamDestroy(s2); }
-  for (hipEvent_t e : c->ev_fork) (void)hipEventDestroy(e);
-  for (hipEvent_t e : c->ev_join) (void)hipEventDestroy(e);
-  c->side.clear(); c->ev_fork.clear(); c->ev_join.clear();
-}
-// The side streams and events of a context whose steps go out in pieces; none if they cannot all be had.
-void side_streams(pbd_ctx* c) {
-  if (!c->concurrent || !in_pieces(c) || !c->side.empty() || c->stream == nullptr || c->o.no_graph) return;
-  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(c->stream, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) { (void)hipGetLastError(); return; }
-  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;          // (another thread's capture is neither disturbed nor in the way)
-  (void)hipThreadExchangeStreamCaptureMode(&mode);
-  std::vector<hipStream_t> rejected;
-  hipEvent_t ea = nullptr, eb = nullptr;
-  bool ok = hipEventCreateWithFlags(&ea, hipEventDisableTiming) == hipSuccess && hipEventCreateWithFlags(&eb, hipEventDisableTiming) == hipSuccess;
-  const int want = std::min(kSideStreams, c->B);
-  for (int t = 0; ok && t < kSideTries && (int)c->side.size() < want; ++t) {
-    hipStream_t s2 = nullptr;
-    if (hipStreamCreateWithFlags(&s2, hipStreamNonBlocking) != hipSuccess) break;
-    (void)share_a_queue(s2, s2, ea, eb);                 // (the first launch on a stream takes longer)
-    bool shared = share_a_queue(c->stream, s2, ea, eb);
-    for (hipStream_t other : c->side) shared = shared || share_a_queue(other, s2, ea, eb);
-    hipEvent_t e = nullptr;
-    if (!shared && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess) { c->side.push_back(s2); c->ev_join.push_back(e); }
-    else rejected.push_back(s2);
-  }
-  for (hipStream_t s2 : rejected) (void)hipStreamDestroy(s2);
-  if (ea) (void)hipEventDestroy(ea);
-  if (eb) (void)hipEventDestroy(eb);
-  for (int b = 0; ok && b < c->B; ++b) {
-    hipEvent_t e = nullptr;
-    ok = hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
-    if (ok) c->ev_fork.push_back(e);
-  }
-  if (!ok || (int)c->side.size() < want) drop_streams(c);
-  (void)hipThreadExchangeStreamCaptureMode(&mode);
-  (void)hipGetLastError();
-}
-// Captured on first use.  Needs a real stream and no profiling events; false: the kernels are launched one by one.
-template <class F> bool ready(pbd_ctx* c, Piece& p, F&& body) {
-  if (!p.exec && !p.tried) {
-    p.tried = true;
-    hipGraph_t graph = nullptr;
-    if (hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed) == hipSuccess) {
-      dispatch(c, body);
-      const hipError_t ee = hipStreamEndCapture(c->stream, &graph);
-      if (ee == hipSuccess && graph && hipGraphInstantiate(&p.exec, graph, nullptr, nullptr, 0) != hipSuccess) p.exec = nullptr;
-      if (graph) (void)hipGraphDestroy(graph);
+// One stream and two events per student block for the forked capture; false if they cannot be had.
+bool side_streams(pbd_ctx* c) {
+  bool ok = c->concurrent;
+  if (ok && c->side.empty()) {
+    for (int b = 0; b < c->B && ok; ++b) {
+      hipStream_t s2; hipEvent_t e1, e2;
+      ok = hipStreamCreateWithFlags(&s2, hipStreamNonBlocking) == hipSuccess &&
+           hipEventCreateWithFlags(&e1, hipEventDisableTiming) == hipSuccess &&
+           hipEventCreateWithFlags(&e2, hipEventDisableTiming) == hipSuccess;
+      if (ok) { c->side.push_back(s2); c->ev_fork.push_back(e1); c->ev_join.push_back(e2); }
     }
-    (void)hipGetLastError();
   }
-  return p.exec != nullptr;
-}
-bool wants_graph(const pbd_ctx* c) { return c->stream != nullptr && !c->prof_on && !c->o.no_graph; }
-// The last block has the last student block behind it; tail: 1 / 2, its weight / architecture round
-bool teacher_ready(pbd_ctx* c, int tail) {
-  for (int b = 0; b < c->B; ++b) {
-    const int with = b == c->B - 1 ? tail : 0;
-    if (!ready(c, c->g_teacher[with][b], [&](auto& e) {
-          e.tset = e.sset = 0;
-          e.teacher_block(b);
-          if (with) e.student_block(b, e.wsf(c->loss_off) + b, with == 2);
-        })) return false;
-  }
-  return true;
-}
-bool relay_ready(pbd_ctx* c, int q) {
-  return ready(c, c->g_relay[q], [&](auto& e) { e.tset = q; for (int b = 0; b < c->B; ++b) e.teacher_block(b); });
-}
-// The first n student blocks; kind: 0, 1 the weight round reading that copy of the relay store, 2 the architecture round
-bool students_ready(pbd_ctx* c, int kind, int n) {
-  for (int b = 0; b < n; ++b)
-    if (!ready(c, c->g_student[kind][b], [&](auto& e) {
-          e.sset = kind == 1 ? 1 : 0;
-          e.student_block(b, e.wsf(c->loss_off) + b, kind == 2);
-        })) return false;
-  return true;
-}
-void drop_graphs(pbd_ctx* c) {
-  auto drop = [](Piece& p) { if (p.exec) (void)hipGraphExecDestroy(p.exec); p = Piece{}; };
-  for (auto& v : c->g_teacher) for (Piece& p : v) drop(p);
-  for (Piece& p : c->g_step) drop(p);
-  for (Piece& p : c->g_pipe) drop(p);
-  for (Piece& p : c->g_drain) drop(p);
-  for (Piece& p : c->g_relay) drop(p);
-  for (auto& v : c->g_student) for (Piece& p : v) drop(p);
-}
-
-// What is sent out on several streams; the first error is kept, and the bound stream waits for the others in any case.
-struct Branches {
-  pbd_ctx* c;
-  hipError_t err = hipSuccess;
-  std::vector<char> used;
-  explicit Branches(pbd_ctx* ctx) : c(ctx), used(ctx->side.size(), 0) {}
-  void keep(hipError_t e) { if (err == hipSuccess) err = e; }
-  void fork(int event) { keep(hipEventRecord(c->ev_fork[event], c->stream)); }
-  // lane 0: the bound stream; else a side stream, behind the event
-  void send(const Piece& p, int lane, int event) {
-    hipStream_t st = c->stream;
-    if (lane) {
-      st = c->side[lane - 1];
-      keep(hipStreamWaitEvent(st, c->ev_fork[event], 0));
-      used[lane - 1] = 1;
-    }
-    if (err == hipSuccess) keep(hipGraphLaunch(p.exec, st));
-  }
-  hipError_t join() {
-    for (size_t i = 0; i < used.size(); ++i)
-      if (used[i]) {
-        keep(hipEventRecord(c->ev_join[i], c->side[i]));
-        keep(hipStreamWaitEvent(c->stream, c->ev_join[i], 0));
-      }
-    return err;
-  }
-};
-
-// One graph with its branches inside (one after the other where the blocks share scratch).
-template <class F> bool ready_whole(pbd_ctx* c, Piece& p, F&& body) {
-  if (p.exec || p.tried) return p.exec != nullptr;
-  if (c->concurrent && !c->fork) c->fork.reset(new Fork(c->B));
-  return ready(c, p, [&](auto& e) { body(e, c->concurrent && c->fork->ok ? c->fork.get() : nullptr); });
-}
-
-// The teacher on the bound stream and every student block behind its target, as one graph or (c->pieces) on the side stream that is
-// expected to be free first; the last block then follows the teacher on its own stream.  arch: the architecture round.  False: it could not be captured.
-bool send_step(pbd_ctx* c, bool arch, hipError_t& err) {
-  if (!c->pieces) {
-    if (!ready_whole(c, c->g_step[arch], [&](auto& e, const Fork* f) { e.step_body(arch, f); })) return false;
-    err = hipGraphLaunch(c->g_step[arch].exec, c->stream);
-    return true;
-  }
-  const int kind = arch ? 2 : 0, tail = arch ? 2 : 1;
-  if (!teacher_ready(c, tail) || !students_ready(c, kind, c->B - 1)) return false;
-  Branches br(c);
-  std::vector<double> busy(c->side.size(), 0.0);
-  double teacher = 0;
-  for (int t = 0; t < c->B; ++t) {
-    const bool last = t == c->B - 1;
-    br.send(c->g_teacher[last ? tail : 0][t], 0, 0);
-    if (!last) br.fork(t);
-    if (t) {                                             // (the teacher is kept a block ahead of what the host sends beside it)
-      const int lane = (int)(std::min_element(busy.begin(), busy.end()) - busy.begin());
-      br.send(c->g_student[kind][t - 1], 1 + lane, t - 1);
-      busy[lane] = std::max(busy[lane], teacher) + block_us(c, PBD_STUDENT, t - 1);
-    }
-    teacher += block_us(c, PBD_TEACHER, t);
-  }
-  err = br.join();
-  return true;
-}
-
-// The students on the batch in copy q of the relay store and, with `teacher`, the relay into the other copy: nothing of one depends on
-// another.  In pieces they are dealt out to the streams in turn, in the order that the caller set or 0 .. B.
-bool send_pipelined(pbd_ctx* c, int q, bool teacher, hipError_t& err) {
-  if (!c->pieces) {
-    Piece& p = teacher ? c->g_pipe[1 - q] : c->g_drain[q];
-    if (!ready_whole(c, p, [&](auto& e, const Fork* f) { e.tset = 1 - q; e.sset = q; e.pipe_body(f, teacher); })) return false;
-    err = hipGraphLaunch(p.exec, c->stream);
-    return true;
-  }
-  if ((teacher && !relay_ready(c, 1 - q)) || !students_ready(c, q, c->B)) return false;
-  Branches br(c);
-  std::vector<int> order = c->pipe_order;
-  if (order.empty())
-    for (int b = 0; b <= c->B; ++b) order.push_back(b);
-  if (!teacher) order.erase(std::find(order.begin(), order.end(), c->B));
-  br.fork(0);
-  for (size_t i = 0; i < order.size(); ++i)
-    br.send(order[i] == c->B ? c->g_relay[1 - q] : c->g_student[q][order[i]], (int)(i % (1 + c->side.size())), 0);
-  err = br.join();
-  return true;
-}
-
-// A launch of ours where the losses lie on this device (a copy takes 4 us of host time more), a copy anywhere else.
-int hand_out_losses(pbd_ctx* c, float* losses_dev) {
-  const float* from = (const float*)(c->ws + c->loss_off);
-  hipPointerAttribute_t to{}, own{};
-  if (hipPointerGetAttributes(&to, losses_dev) == hipSuccess && hipPointerGetAttributes(&own, c->ws) == hipSuccess &&
-      to.type == hipMemoryTypeDevice && to.device == own.device) {
-    launch(c, copy_floats_kernel, 1, 64, 0, c->stream, from, losses_dev, c->B);
-    return PBD_OK;
-  }
-  (void)hipGetLastError();
-  HIP_TRY(c, hipMemcpyAsync(losses_dev, from, (size_t)c->B * 4, hipMemcpyDeviceToDevice, c->stream));
-  return PBD_OK;
+  return ok && (int)c->side.size() == c->B;
 }
 
 // The whole step in one of its two rounds (r = 0: weights, 1: architecture parameters).
@@ -2927,27 +2675,42 @@ int whole_step(pbd_ctx* c, const float* x_dev, float lr, float* losses_dev, int 
   if (r == 1)
     for (int b = 0; b < c->B; ++b)
       if ((rc = define_alpha(c, b))) return rc;
-  // The body of the step touches only workspace addresses, so its parts are captured once into HIP graphs and replayed: ~300 small
-  // launches per step would otherwise be bound by launch cost.
-  c->front = 0;        // the captured bodies address the first copy of the relay store
-  rc = dispatch(c, [&](auto& e) { e.prepare(x_dev, lr); });
+  // The body of the step touches only workspace addresses, so it is captured once into a HIP
+  // graph and replayed: ~300 small launches per step would otherwise be bound by launch cost.
+  // Capture needs a real stream and no profiling events; otherwise the kernels are launched directly.
+  const bool want_graph = c->stream != nullptr && !c->prof_on && !c->o.no_graph;
+  c->front = 0;        // the captured body addresses the first copy of the relay store
+  rc = dispatch(c, [&](auto& e) { e.set_lr(lr); e.prepare(x_dev); });
   if (rc) return rc;
-  hipError_t sent = hipSuccess;
-  if (wants_graph(c) && send_step(c, r == 1, sent)) {
-    HIP_TRY(c, sent);
+  if (want_graph && !c->gexec[r] && !c->graph_tried[r]) {
+    c->graph_tried[r] = true;
+    hipGraph_t graph = nullptr;
+    const bool fork = side_streams(c);
+    if (hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed) == hipSuccess) {
+      dispatch(c, [&](auto& e) { e.step_body(fork, r == 1); });
+      hipError_t ee = hipStreamEndCapture(c->stream, &graph);
+      if (ee == hipSuccess && graph && hipGraphInstantiate(&c->gexec[r], graph, nullptr, nullptr, 0) != hipSuccess)
+        c->gexec[r] = nullptr;
+      if (graph) (void)hipGraphDestroy(graph);
+    }
+    (void)hipGetLastError();
+  }
+  if (want_graph && c->gexec[r]) {
+    HIP_TRY(c, hipGraphLaunch(c->gexec[r], c->stream));
     c->relayed_upto = c->B;
     for (BlockPlan& bp : c->net[1]) bp.stepped = c->concurrent;
     c->net[1].back().stepped = true;
   } else {
-    rc = dispatch(c, [&](auto& e) { e.step_body(r == 1); });
+    rc = dispatch(c, [&](auto& e) { e.step_body(false, r == 1); });
     if (rc) return rc;
   }
-  if ((rc = hand_out_losses(c, losses_dev))) return rc;
+  HIP_TRY(c, hipMemcpyAsync(losses_dev, c->ws + c->loss_off, (size_t)c->B * 4, hipMemcpyDeviceToDevice, c->stream));
   return after_launches(c);
 }
 
 // The students' half of a pipelined step on the batch in the front copy, block after block.
 int pipeline_drain(pbd_ctx* c, float* losses_dev) {
+  const bool want_graph = c->stream != nullptr && !c->prof_on && !c->o.no_graph;
   const int q = c->front;
   int rc = dispatch(c, [&](auto& e) {
     e.set_lr(c->pending_lr);
@@ -2957,14 +2720,26 @@ int pipeline_drain(pbd_ctx* c, float* losses_dev) {
     }
   });
   if (rc) return rc;
-  hipError_t sent = hipSuccess;
-  if (wants_graph(c) && send_pipelined(c, q, false, sent)) {
-    HIP_TRY(c, sent);
+  if (want_graph && !c->gdrain[q] && !c->gdrain_tried[q]) {
+    c->gdrain_tried[q] = true;
+    hipGraph_t graph = nullptr;
+    const bool fork = side_streams(c);
+    if (hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed) == hipSuccess) {
+      dispatch(c, [&](auto& e) { e.pipe_body(fork, false); });
+      hipError_t ee = hipStreamEndCapture(c->stream, &graph);
+      if (ee == hipSuccess && graph && hipGraphInstantiate(&c->gdrain[q], graph, nullptr, nullptr, 0) != hipSuccess)
+        c->gdrain[q] = nullptr;
+      if (graph) (void)hipGraphDestroy(graph);
+    }
+    (void)hipGetLastError();
+  }
+  if (want_graph && c->gdrain[q]) {
+    HIP_TRY(c, hipGraphLaunch(c->gdrain[q], c->stream));
   } else {
-    rc = dispatch(c, [&](auto& e) { e.students(); });
+    rc = dispatch(c, [&](auto& e) { e.pipe_body(false, false); });
     if (rc) return rc;
   }
-  if ((rc = hand_out_losses(c, losses_dev))) return rc;
+  HIP_TRY(c, hipMemcpyAsync(losses_dev, c->ws + c->loss_off, (size_t)c->B * 4, hipMemcpyDeviceToDevice, c->stream));
   c->pending = false;
   for (BlockPlan& bp : c->net[1]) bp.stepped = c->concurrent;
   c->net[1].back().stepped = true;
@@ -2984,16 +2759,29 @@ int pipeline_step(pbd_ctx* c, const float* x_dev, float lr, float* losses_dev) {
     rc = dispatch(c, [&](auto& e) { e.relay_all(x_dev); });
     if (rc) return rc;
   } else {
-    rc = dispatch(c, [&](auto& e) { e.tset = tset; e.sset = 1 - tset; e.prepare(x_dev, c->pending_lr); });
+    const bool want_graph = c->stream != nullptr && !c->prof_on && !c->o.no_graph;
+    rc = dispatch(c, [&](auto& e) { e.tset = tset; e.sset = 1 - tset; e.set_lr(c->pending_lr); e.prepare(x_dev); });
     if (rc) return rc;
-    hipError_t sent = hipSuccess;
-    if (wants_graph(c) && send_pipelined(c, 1 - tset, true, sent)) {
-      HIP_TRY(c, sent);
+    if (want_graph && !c->gpipe[tset] && !c->gpipe_tried[tset]) {
+      c->gpipe_tried[tset] = true;
+      hipGraph_t graph = nullptr;
+      const bool fork = side_streams(c);
+      if (hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed) == hipSuccess) {
+        dispatch(c, [&](auto& e) { e.tset = tset; e.sset = 1 - tset; e.pipe_body(fork); });
+        hipError_t ee = hipStreamEndCapture(c->stream, &graph);
+        if (ee == hipSuccess && graph && hipGraphInstantiate(&c->gpipe[tset], graph, nullptr, nullptr, 0) != hipSuccess)
+          c->gpipe[tset] = nullptr;
+        if (graph) (void)hipGraphDestroy(graph);
+      }
+      (void)hipGetLastError();
+    }
+    if (want_graph && c->gpipe[tset]) {
+      HIP_TRY(c, hipGraphLaunch(c->gpipe[tset], c->stream));
     } else {
-      rc = dispatch(c, [&](auto& e) { e.tset = tset; e.sset = 1 - tset; e.pipe_body(nullptr, true); });
+      rc = dispatch(c, [&](auto& e) { e.tset = tset; e.sset = 1 - tset; e.pipe_body(false); });
       if (rc) return rc;
     }
-    if ((rc = hand_out_losses(c, losses_dev))) return rc;
+    HIP_TRY(c, hipMemcpyAsync(losses_dev, c->ws + c->loss_off, (size_t)c->B * 4, hipMemcpyDeviceToDevice, c->stream));
   }
   c->front = tset;
   c->relayed_upto = c->B;
@@ -3072,8 +2860,12 @@ int pbd_create(const int32_t* words, int32_t nwords, const double* pool, int32_t
 
 void pbd_destroy(pbd_ctx* c) {
   if (!c) return;
-  drop_streams(c);
-  drop_graphs(c);
+  for (hipGraphExec_t g : c->gexec) if (g) (void)hipGraphExecDestroy(g);
+  for (hipGraphExec_t g : c->gpipe) if (g) (void)hipGraphExecDestroy(g);
+  for (hipGraphExec_t g : c->gdrain) if (g) (void)hipGraphExecDestroy(g);
+  for (hipStream_t s2 : c->side) (void)hipStreamDestroy(s2);
+  for (hipEvent_t e : c->ev_fork) (void)hipEventDestroy(e);
+  for (hipEvent_t e : c->ev_join) (void)hipEventDestroy(e);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
   delete c;
 }
@@ -3100,12 +2892,14 @@ int pbd_bind(pbd_ctx* c, void* dev_ws, size_t bytes, void* hip_stream) {
   // parameters, optimiser state and statistics start at zero; the relay store too,
   // so that padded channels never hold stale bits
   HIP_TRY(c, hipMemsetAsync(c->ws, 0, c->r_tscr, c->stream));
-  drop_streams(c);          // (their queues were chosen beside the stream of the last binding)
-  drop_graphs(c);
-  side_streams(c);
-  c->pieces = !c->side.empty();
-  for (auto& v : c->g_student) v.resize(c->B);
-  for (auto& v : c->g_teacher) v.resize(c->B);
+  for (int r = 0; r < 2; ++r) {
+    if (c->gexec[r]) { (void)hipGraphExecDestroy(c->gexec[r]); c->gexec[r] = nullptr; }
+    c->graph_tried[r] = false;
+    if (c->gpipe[r]) { (void)hipGraphExecDestroy(c->gpipe[r]); c->gpipe[r] = nullptr; }
+    c->gpipe_tried[r] = false;
+    if (c->gdrain[r]) { (void)hipGraphExecDestroy(c->gdrain[r]); c->gdrain[r] = nullptr; }
+    c->gdrain_tried[r] = false;
+  }
   c->front = 0;
   c->pending = false;
   c->bound = true;
@@ -3380,9 +3174,10 @@ int pbd_set_pipeline_order(pbd_ctx* c, const int32_t* order, int32_t n) {
     seen[order[i]] = 1;
   }
   c->pipe_order.assign(order, order + n);
-  for (Piece& p : c->g_pipe) {        // captured with the old order: capture again on the next call
-    if (c->bound && p.exec) { (void)hipStreamSynchronize(c->stream); (void)hipGraphExecDestroy(p.exec); }
-    p = Piece{};
+  for (int q = 0; q < 2; ++q) {       // captured with the old order: capture again on the next call
+    if (c->bound && c->gpipe[q]) { (void)hipStreamSynchronize(c->stream); (void)hipGraphExecDestroy(c->gpipe[q]); }
+    c->gpipe[q] = nullptr;
+    c->gpipe_tried[q] = false;
   }
   return PBD_OK;
 }
@@ -3452,14 +3247,7 @@ int pbd_read_alpha(pbd_ctx* c, int32_t kind, int32_t b, int32_t opi, float* host
   return PBD_OK;
 }
 
-int pbd_uses_graph(const pbd_ctx* c) {
-  if (!c) return 0;
-  if (c->g_step[0].exec || c->g_step[1].exec || c->g_pipe[0].exec || c->g_pipe[1].exec) return 1;
-  for (const auto& v : c->g_student)
-    for (const Piece& p : v)
-      if (p.exec) return 1;
-  return 0;
-}
+int pbd_uses_graph(const pbd_ctx* c) { return c && (c->gexec[0] || c->gexec[1] || c->gpipe[0] || c->gpipe[1]) ? 1 : 0; }
 
 int pbd_sync(pbd_ctx* c) {
   int rc = check_ready(c);

@@ -1,7 +1,6 @@
-"""A step goes out as one graph with its branches inside or, where its launches are short (in_pieces), as a graph of each block on
-several streams.  VGG-16 on both sides of that rule: whole steps and pipelined steps in turn, nothing waited for between the calls but eager
-work of the caller on its own stream, twice on one workspace binding and once more on another, leave the bits that the launches
-leave when they are sent one by one."""
+"""Steps replayed from a graph: whole steps and pipelined steps in turn, nothing waited for between the calls but eager work of the caller
+on its own stream, twice on one workspace binding and once more on another, leave the bits that the launches leave when they are
+sent one by one.  Contexts that come and go, several at a time, leave nothing behind that the next ones trip over."""
 import dataclasses
 
 import numpy as np
@@ -21,7 +20,7 @@ def test_replays_leave_the_bits_of_single_launches(batch):
     for no_graph in (True, False):
         d = pbd.Distiller(wl, no_graph=no_graph)
         got = []
-        for _ in range(2):                                # (a new binding chooses its streams anew)
+        for _ in range(2):
             d.bind("cuda:0")
             d.load_params()
             torch.cuda.synchronize()
@@ -45,3 +44,29 @@ def test_replays_leave_the_bits_of_single_launches(batch):
     assert len(runs[0]) == len(runs[1])
     for a, b in zip(*runs):
         assert np.array_equal(a, b)
+
+
+def test_contexts_that_come_and_go():
+    """Three contexts at a time take turns and are dropped, again and again, at the batches of short launches."""
+    import torch
+    losses = {}
+    for again in range(2):
+        for batch in (8, 16, 32, 48, 64):
+            wl = W.vgg16_dsconv(batch)
+            x = torch.from_numpy(W.make_input(wl)).cuda()
+            contexts = []
+            for _ in range(3):
+                d = pbd.Distiller(wl)
+                d.bind("cuda:0")
+                d.load_params()
+                contexts.append(d)
+            torch.cuda.synchronize()
+            for _ in range(4):
+                for d in contexts:
+                    d.distill_step(x, wl.lr)
+            torch.cuda.synchronize()
+            for d in contexts:
+                assert d.uses_graph()
+                got = d.losses.cpu().numpy()
+                assert np.array_equal(got, losses.setdefault(batch, got.copy()))
+            del contexts, d
