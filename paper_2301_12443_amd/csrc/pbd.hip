@@ -499,12 +499,12 @@ void free_tile(IgemmCfg& c, long M, int NC, int Kred, int num_cu) {
     if (t < best * 0.999) { best = t; c.BM = kBM[i]; c.BN = kBN[i]; }
   }
 }
-// Stages of the ring that such a launch's operands go through (igemm_block): three, of which two 64 x 128 workgroups fit in a compute unit's
-// LDS, and two, so that three of them fit, where there are more than two for a unit.  us with three / two: 588 workgroups of 54 steps
-// 66 / 51, 528 of 12 19.8 / 15.9, 512 of 36 29.2 / 33.0, 88 of 8 7.1 / 7.6 (register staging 87, 22.8, 36.0, 8.1).
-int ring_stages(const IgemmCfg& c, long wgs, int num_cu) {
-  if (c.BK == 32) return c.BM == 256 ? 2 : 3;
-  return c.BM == 128 ? 2 : c.BN == 128 && wgs > 2L * num_cu ? 2 : 3;
+// Stages of the ring that a launch's operands go through (igemm_block): three, of which two 64 x 128 workgroups fit in a compute unit's
+// LDS, and two on wider tiles and, so that three 64 x 128 workgroups fit, where `shallow`: more than two of them for a unit, and lanes, whose kernels
+// have to agree.  us with three / two: 588 workgroups of 54 steps 66 / 51, 528 of 12 19.8 / 15.9, 512 of 36 29.2 / 33.0, 88 of 8 7.1 / 7.6
+// (register staging 87, 22.8, 36.0, 8.1).
+constexpr int ring_stages(int BM, int BN, int BK, bool shallow) {
+  return BK == 32 ? (BM == 256 ? 2 : 3) : BM == 128 || (BN == 128 && shallow) ? 2 : 3;
 }
 
 // Launch shape of igemm_dma_kernel (256-row tiles, operands straight into LDS) for one dense layer, or use = false
@@ -995,8 +995,9 @@ const ManyTable& many_table() {
     ManyTable t;
     typedef bf16_t B;
 #define PBD_MANY(WAVES_, NAME_, ...) put<&NAME_##_block<__VA_ARGS__>, 256, WAVES_>(t, NAME_##_kernel<__VA_ARGS__>)
-#define PBD_MANY_IGR(MODE_, BM_, BN_, EPI_, BK_, RING_) put<&igemm_block<MODE_, BM_, BN_, EPI_, true, BK_, false, RING_>, 256, 1>(t, igemm_kernel<MODE_, BM_, BN_, EPI_, true, BK_, false, RING_>)
-#define PBD_MANY_IG(MODE_, BM_, BN_, EPI_) PBD_MANY_IGR(MODE_, BM_, BN_, EPI_, 64, (BM_ == 64 && BN_ < 128 ? 3 : 2)); PBD_MANY_IGR(MODE_, BM_, BN_, EPI_, 32, 3); \
+#define PBD_MANY_IGR(MODE_, BM_, BN_, EPI_, BK_) put<&igemm_block<MODE_, BM_, BN_, EPI_, true, BK_, false, ring_stages(BM_, BN_, BK_, true)>, 256, 1>( \
+        t, igemm_kernel<MODE_, BM_, BN_, EPI_, true, BK_, false, ring_stages(BM_, BN_, BK_, true)>)
+#define PBD_MANY_IG(MODE_, BM_, BN_, EPI_) PBD_MANY_IGR(MODE_, BM_, BN_, EPI_, 64); PBD_MANY_IGR(MODE_, BM_, BN_, EPI_, 32); \
     PBD_MANY(1, igemm, MODE_, BM_, BN_, EPI_, false, 32, false, 0)
 #define PBD_MANY_MODE(MODE_) PBD_MANY_IG(MODE_, 64, 128, EPI_STORE); PBD_MANY_IG(MODE_, 64, 64, EPI_STORE); PBD_MANY_IG(MODE_, 64, 32, EPI_STORE); \
     PBD_MANY_IG(MODE_, 128, 128, EPI_STORE); PBD_MANY_IG(MODE_, 128, 64, EPI_STORE); PBD_MANY_IG(MODE_, 128, 32, EPI_STORE); \
@@ -1471,20 +1472,21 @@ template <class T> struct Exec {
     g.tiles_n = (g.NC + cfg.BN - 1) / cfg.BN;
     g.splits = (nk + g.ksteps_per_split - 1) / g.ksteps_per_split;
     const dim3 grid(g.tiles_m * g.tiles_n * g.splits);
-    const int ring = grouped ? 2 : ring_stages(cfg, (long)g.tiles_m * g.tiles_n * g.splits, c->num_cu);
-#define PBD_IGR(BM_, BN_, EPI_, OUT_, BK_, RING_) launch(c, igemm_kernel<MODE, BM_, BN_, EPI_, true, BK_, false, RING_>, grid, 256, 0, st, A, Bw, OUT_, a, b, act, g)
+    const bool shallow = grouped || (long)g.tiles_m * g.tiles_n * g.splits > 2L * c->num_cu;
+#define PBD_IGR(BM_, BN_, EPI_, OUT_, BK_, SHALLOW_) \
+      launch(c, igemm_kernel<MODE, BM_, BN_, EPI_, true, BK_, false, ring_stages(BM_, BN_, BK_, SHALLOW_)>, grid, 256, 0, st, A, Bw, OUT_, a, b, act, g)
 #define PBD_IG(BM_, BN_, EPI_, OUT_) do { \
-      if (cfg.BK == 64) { if constexpr (BM_ == 128) PBD_IGR(BM_, BN_, EPI_, OUT_, 64, 2); \
-        else if constexpr (BM_ == 64) { if (BN_ == 128 && ring == 2) PBD_IGR(BM_, BN_, EPI_, OUT_, 64, (BN_ == 128 ? 2 : 3)); else PBD_IGR(BM_, BN_, EPI_, OUT_, 64, 3); } } \
-      else if (g.CA % IG_BK == 0) PBD_IGR(BM_, BN_, EPI_, OUT_, 32, (BM_ == 256 ? 2 : 3)); \
+      if (cfg.BK == 64) { if constexpr (BM_ != 256) { if (shallow) PBD_IGR(BM_, BN_, EPI_, OUT_, 64, true); else PBD_IGR(BM_, BN_, EPI_, OUT_, 64, false); } } \
+      else if (g.CA % IG_BK == 0) PBD_IGR(BM_, BN_, EPI_, OUT_, 32, false); \
       else launch(c, igemm_kernel<MODE, BM_, BN_, EPI_, false>, grid, 256, 0, st, A, Bw, OUT_, a, b, act, g); } while (0)
 #define PBD_IG_BN(BM_, EPI_, OUT_) do { if (cfg.BN == 128) PBD_IG(BM_, 128, EPI_, OUT_); else if (cfg.BN == 64) PBD_IG(BM_, 64, EPI_, OUT_); else PBD_IG(BM_, 32, EPI_, OUT_); } while (0)
 #define PBD_IG_BM(EPI_, OUT_) do { if (cfg.BM == 256) PBD_IG(256, 128, EPI_, OUT_); else if (cfg.BM == 128) PBD_IG_BN(128, EPI_, OUT_); else PBD_IG_BN(64, EPI_, OUT_); } while (0)
     // profile entries are named after the kernel instantiation, so that each maps to one symbol of
-    // a rocprofv3 kernel trace: igemm_<fwd|dgrad>_<BM>x<BN>_<epilogue>
+    // a rocprofv3 kernel trace: igemm_<fwd|dgrad>_<BM>x<BN>[r<stages of the ring>]_<epilogue>
     static const char* const kEpi[] = {"store", "affine", "accum", "partial"};
-    char name[32];
-    snprintf(name, sizeof name, "igemm_%s_%dx%d_%s", MODE ? "dgrad" : "fwd", cfg.BM, cfg.BN, g.fold.mean ? "bn_store" : kEpi[g.splits > 1 ? 3 : epi]);
+    char ring[4] = "", name[32];
+    if (!g.fold.mean && g.CA % IG_BK == 0) snprintf(ring, sizeof ring, "r%d", ring_stages(cfg.BM, cfg.BN, cfg.BK, shallow));
+    snprintf(name, sizeof name, "igemm_%s_%dx%d%s_%s", MODE ? "dgrad" : "fwd", cfg.BM, cfg.BN, ring, g.fold.mean ? "bn_store" : kEpi[g.splits > 1 ? 3 : epi]);
     if constexpr (MODE == 0) {
       if (g.fold.mean) {                     // (dense_reader: 32 columns, no split)
         ProfScope ps(c, name, bytes, flops, net, blk, opi);
