@@ -710,7 +710,7 @@ __device__ __forceinline__ void igemm_block(const Blk& blk, const bf16_t* __rest
     return;
   }
   // accumulating launches add in fp32 before the one rounding: the tile is staged as fp32 where the
-  // operand tiles' LDS has room for it (every tile shape but 256 x 128 and the 32-wide K step's 128 x 128)
+  // operand tiles' LDS has room for it (every tile shape but 256 x 128 and, staged through registers, 128 x 128)
   constexpr int OPF = BN * 4 + 16;
   if constexpr (EPI == EPI_ACCUM && !kIdleWaves && BM * OPF <= LDS) {
     unsigned char* stage = reinterpret_cast<unsigned char*>(smem);

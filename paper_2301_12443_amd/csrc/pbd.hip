@@ -1463,7 +1463,9 @@ template <class T> struct Exec {
     IgemmCfg cfg = igemm_cfg(g.M, g.NC, g.Kred, g.CA);
     // an accumulating 256-row tile cannot stage its fp32 results in LDS: 128 rows store whole cache lines
     if (epi == EPI_ACCUM && cfg.BM == 256) cfg.BM = 128;
-    if (epi == EPI_ACCUM && cfg.BK == 32 && cfg.BM == 128 && cfg.BN == 128) cfg.BN = 64;   // (128 x 128 needs the 64-wide K step's LDS)
+    // ... and 32-deep ones take 64 columns, half the LDS for the staged float32 (and without the ring 128 have no room): us on 64 / 128, 2 x 2 layers
+    // to 32 channels, 25900 rows x 320 columns 10.4 / 15.5, 50200 x 256 14.7 / 17.0, 65600 x 512 33.4 / 40.4, 200700 x 128 23.5 / 30.1
+    if (epi == EPI_ACCUM && cfg.BK == 32 && cfg.BM == 128 && cfg.BN == 128) cfg.BN = 64;
     const bool grouped = recorder(c) != nullptr;
     if (!g.stats && !g.fold.mean && !grouped) free_tile(cfg, g.M, g.NC, g.Kred, c->num_cu);
     const int nk = (g.Kred + cfg.BK - 1) / cfg.BK;
