@@ -106,7 +106,7 @@ size_t pbd_workspace_bytes(const pbd_ctx* ctx);
 
 /* Adopt dev_ws (device, 256-byte aligned, >= pbd_workspace_bytes) and hip_stream
  * (a hipStream_t, may be null for the default stream).  Zero-fills parameters and
- * optimiser state, sets BN to the identity.  The caller keeps ownership. */
+ * optimiser state, sets BN to the identity; waits for the stream.  The caller keeps ownership. */
 int pbd_bind(pbd_ctx* ctx, void* dev_ws, size_t bytes, void* hip_stream);
 
 /* Copy one parameter tensor from host float32 (textbook layout) into the workspace,
