@@ -65,9 +65,10 @@ template <int N, class F> __device__ __forceinline__ void unrolled(F&& f) { unro
 // addresses and the exchange of lanes in the same waves a product took 64 cycles; here the chain has nothing between its
 // products but two LDS reads, all of whose addresses are a register and a constant.
 //  * ROWS: the operand's memory is contiguous along the reduction, [p][element] in LDS; else along p, [element][p].  A load brings a block of
-//    1 KiB: rows (elements) of 4 TILE .. bytes, their 16-byte chunks permuted so that the lanes of a read, one float each, lie on different
-//    banks (TILE 32, ROWS: on half of them).  ROWS: chunk c of row r in slot c ^ (r % 4 or r / 2 % 4), blocks 64 bytes apart; else chunk c of
-//    element e in slot c ^ half a row where element bit 1 (TILE 32: bit 0) is set.
+//    1 KiB: rows (elements) of 4 TILE .. bytes, their 16-byte chunks permuted.  ROWS: chunk c of row r in slot c ^ (r % 4 or r / 2 % 4), blocks 64
+//    bytes apart; else chunk c of element e in slot c ^ half a row where element bit 1 (TILE 32: bit 0) is set.  The lanes of a read, one float
+//    each, go 32 at a time to 32 banks; they lie on 16 of them (TILE 32, ROWS: on 8), so a read takes 4 (8) LDS cycles instead of 2 (counted:
+//    SQ_LDS_IDX_ACTIVE, 50 and 75 % of it conflicts).  Beside the 32 (64) of a product on each of four SIMDs that just fits.
 // A stage's barrier: the loaders have seen its loads land, the multiplying waves have read the stage before.  They read stage t while
 // they multiply stage t - 1.
 template <int TILE> struct F32Gemm {

@@ -280,8 +280,10 @@ __device__ __forceinline__ int xcd_contiguous(int w, int total) {
 //
 // RING (UNI, not FOLD): operands go from memory straight to LDS (dma_load16), into a ring of RING stages of unpadded rows whose 16-byte chunks
 // are swizzled, with one barrier a step: no registers to wait for, no LDS stores, and a step's fragments requested together.  Same products in the
-// same order, so the same bits.  What bounds it is what a compute unit fetches: 44 GB/s with one workgroup, 60 to 67 with two or three, whatever the
-// depth of the ring (six stages are no faster than three).  us with registers / with the ring: 3136 rows, 768 -> 768, 3 x 3, cut in
+// same order, so the same bits.  The time goes by what a compute unit fetches: 44 GB/s with one workgroup, 60 with two, 65 to 80 with three, whatever the
+// depth of the ring (six stages are no faster than three).  No unit is at its limit there (3136 rows, 768 -> 768, 3 x 3: matrix cores busy 27 %, LDS
+// reads 20 % and without conflicts, L2 hits 91 %): the waves wait for a counter or a barrier 37 % of the time and 30 % for their turn to issue.
+// us with registers / with the ring: 3136 rows, 768 -> 768, 3 x 3, cut in
 // two 87 / 51 (640 TFLOP/s), 512 -> 512 41 / 27, 2048 -> 768, 1 x 1 35.6 / 22, 1360 rows, 512 -> 512, 3 x 3, cut in six 22.6 / 15.9, 340 rows, 1 x 1
 // 7.9 / 6.9 (5.5 on 64 x 64 tiles); layers of one step as before.
 template <int MODE, int BM, int BN, int EPI, bool UNI, int BK, bool FOLD, int RING>
