@@ -71,13 +71,12 @@ template <int N, class F> __device__ __forceinline__ void unrolled(F&& f) { unro
 //    SQ_LDS_IDX_ACTIVE, 50 and 75 % of it conflicts).  Beside the 32 (64) of a product on each of four SIMDs that just fits.
 // A stage's barrier: the loaders have seen its loads land, the multiplying waves have read the stage before.  They read stage t while
 // they multiply stage t - 1.
-template <int TILE> struct F32Gemm {
+constexpr int kF32Threads = 512;
+constexpr int f32_stage(int tile) { return tile == 32 ? 32 : 64; }      // elements of the reduction a stage
+template <int TILE, int NS> struct F32Gemm {
   typedef F32Tile<TILE> F;
-  static constexpr int EDGE = 2 * TILE, BK = 16 * F::GROUPS;                                    // 32 and 64, 64 and 32
-  static constexpr int THREADS = 512;
-  // Stages: 16-wide tiles run where a compute unit has one or two workgroups and a stage takes 0.2 us: five on their way.  The 32-wide ones'
-  // take 0.43 us, and three workgroups share a unit.
-  static constexpr int NS = TILE == 16 ? 6 : 3;
+  static constexpr int EDGE = 2 * TILE, BK = f32_stage(TILE);                                    // 32 and 64, 64 and 32
+  static_assert(BK == 16 * F::GROUPS, "sixteen products a stage");
   template <bool ROWS> static constexpr int block_bytes() { return ROWS ? 1024 + 64 : 1024; }
   template <bool P_ROWS, bool Q_ROWS> static constexpr int stage_bytes() { return 8 * (block_bytes<P_ROWS>() + block_bytes<Q_ROWS>()); }
   // what lane `lane` of loader w brings in pass i = 0, 1 (block w + 4 i): row / element, and the first of its four elements / rows
@@ -123,6 +122,7 @@ template <int TILE> struct F32Gemm {
   static __device__ __forceinline__ void multiply(const unsigned char* ring, typename F::Acc& acc, int stages, int lane, int wave) {
     constexpr int STAGE = stage_bytes<P_ROWS, Q_ROWS>(), HALF = 3;      // (slots within reach of a constant)
     static_assert(NS % HALF == 0 && HALF * STAGE <= 65536, "every slot is a register and a constant");
+    static_assert(6 % NS == 0, "a round of six turns leaves the slots where they were");
     const int group = lane / TILE, at_p = (wave >> 1) * TILE + lane % TILE, at_q = (wave & 1) * TILE + lane % TILE;
     unsigned ap[NS / HALF][4], aq[NS / HALF][4];
     const unsigned ring_at = (unsigned)(size_t)(lds_void_ptr)ring;
@@ -176,19 +176,18 @@ template <int TILE> struct F32Gemm {
     if (left % 2 == 0) last(std::integral_constant<int, 0>{}); else last(std::integral_constant<int, 1>{});
   }
 };
-static_assert(6 % F32Gemm<16>::NS == 0 && 6 % F32Gemm<32>::NS == 0, "a round of six turns leaves the slots where they were");
 
 // Same view as igemm_kernel: Out[m][j] = sum_kk Agather(m, kk) * W(j, kk), rows m = pixels of an [N][HO][WO] grid,
 // kk = (r*S + s)*CA + c.  MODE 0 reads the weights as they lie, [NC][R][S][CA]; MODE 1 reads the forward filter
 // [CA][R][S][NC], so there is no transposed copy to keep.
-template <int MODE, int TILE>
+template <int MODE, int TILE, int NS>
 __global__ __launch_bounds__(512) void igemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ Bw,
                                                        float* Out, const float* __restrict__ ep_a,
                                                        const float* __restrict__ ep_b, int act, int accumulate, IgemmArgs g) {
   typedef F32Tile<TILE> F;
-  typedef F32Gemm<TILE> G;
+  typedef F32Gemm<TILE, NS> G;
   constexpr bool W_ROWS = MODE == 0;
-  __shared__ __attribute__((aligned(16))) unsigned char ring[G::NS * G::template stage_bytes<W_ROWS, true>()];
+  __shared__ __attribute__((aligned(16))) unsigned char ring[NS * G::template stage_bytes<W_ROWS, true>()];
   const int tid = threadIdx.x, lane = tid & 63, group = lane / TILE, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tile = xcd_contiguous(blockIdx.x, g.tiles_m * g.tiles_n);
   const int m0 = tile / g.tiles_n * G::EDGE, n0 = tile % g.tiles_n * G::EDGE;
@@ -353,12 +352,12 @@ __global__ __launch_bounds__(512) void igemm_f32_kernel(const float* __restrict_
 // dW[k][j] = sum over pixels of dy[m][k] * xcol[m][j], in pixel order (so bound by the chain on layers of many pixels and few
 // weights: 10 cycles a pixel, 8 of them the products').  Both operands are contiguous along their channels; a gathered pixel is addressed once per
 // four channels of a tap.
-template <int TILE>
+template <int TILE, int NS>
 __device__ __forceinline__ void wgrad_f32_block(const Blk& blk, const float* __restrict__ dy, const float* __restrict__ x,
                                                 float* __restrict__ dw, WgradTrArgs g) {
   typedef F32Tile<TILE> F;
-  typedef F32Gemm<TILE> G;
-  __shared__ __attribute__((aligned(16))) unsigned char ring[G::NS * G::template stage_bytes<false, false>()];
+  typedef F32Gemm<TILE, NS> G;
+  __shared__ __attribute__((aligned(16))) unsigned char ring[NS * G::template stage_bytes<false, false>()];
   const int tid = threadIdx.x, lane = tid & 63, group = lane / TILE, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tile = xcd_contiguous(blk.x, g.tiles_k * g.tiles_j);
   const int k0 = (tile / g.tiles_j) * G::EDGE, j0 = (tile % g.tiles_j) * G::EDGE;
@@ -447,10 +446,10 @@ __device__ __forceinline__ void wgrad_f32_block(const Blk& blk, const float* __r
     *reinterpret_cast<float4*>(dw + (size_t)k * g.J + j) = make_float4(o[0], o[1], o[2], o[3]);
   }
 }
-template <int TILE>
+template <int TILE, int NS>
 __global__ __launch_bounds__(512) void wgrad_f32_kernel(const float* __restrict__ dy, const float* __restrict__ x,
                                                        float* __restrict__ dw, WgradTrArgs g) {
-  wgrad_f32_block<TILE>(one_block(), dy, x, dw, g);
+  wgrad_f32_block<TILE, NS>(one_block(), dy, x, dw, g);
 }
 
 }  // namespace pbd

@@ -584,6 +584,12 @@ DmaCfg dma_cfg(long M, int NC, int Kred, int CA, int num_cu, int epi) {
 // with the line at 128 / 256 / 512 workgroups: VGG-16 at batch 64 2277 / 2189 / 2249, at batch 16 920 / 901 / 918, ResNet-50
 // x1.5 at batch 8 10.5 / 10.6 / 10.7 ms.
 inline int f32_tile(long rows, long cols) { return (rows + 63) / 64 * ((cols + 63) / 64) >= 256 ? 32 : 16; }
+// Stages of their ring (F32Gemm): three, of which three workgroups fit in a compute unit's LDS, and on 16-wide tiles, where a stage takes 0.2 us, six
+// while no unit gets a second workgroup.  Six everywhere on those tiles leaves room for one workgroup a unit, and short reductions run in rounds: us with
+// two register-staged buffers / six / three, 6272 rows, 96 -> 96, 1 x 1 7.4 / 9.9 / 7.0, 784 rows, 960 -> 160 backward-data 8.4 / 10.8 / 8.0, weight
+// gradient of 768 -> 768 over 49 pixels 9.4 / 10.9 / 7.2.  Three everywhere give up the unit that a long chain has to itself beside the other branches.
+// us a step with six / three / this line: VGG-16 at batch 64 1207 / 1297 / 1172, at batch 16 658 / 697 / 655, ResNet-50 x1.5 at batch 8 6175 / 5846 / 5824.
+inline int f32_stages(int tile, long wgs, int num_cu) { return tile == 32 || wgs > num_cu ? 3 : 6; }
 
 constexpr int kMseBlocks = 1024;
 
@@ -1023,7 +1029,8 @@ const ManyTable& many_table() {
     PBD_MANY(1, sum_partials, 32); PBD_MANY(1, sum_partials, 8);
     PBD_MANY(1, dw_wgrad, B, 3, 3); PBD_MANY(1, dw_wgrad, B, 7, 1);
     PBD_MANY(1, dw_wgrad, float, 3, 3); PBD_MANY(1, dw_wgrad, float, 7, 1);
-    put<&wgrad_f32_block<16>, F32Gemm<16>::THREADS, 2>(t, wgrad_f32_kernel<16>); put<&wgrad_f32_block<32>, F32Gemm<32>::THREADS, 2>(t, wgrad_f32_kernel<32>);
+    #define PBD_MANY_F32(TILE_, NS_) put<&wgrad_f32_block<TILE_, NS_>, kF32Threads, 2>(t, wgrad_f32_kernel<TILE_, NS_>)
+    PBD_MANY_F32(16, 6); PBD_MANY_F32(16, 3); PBD_MANY_F32(32, 3);
 #define PBD_MANY_DW(K_) PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, false, false, false, false); PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, false, false, true, false); \
     PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, false, true, true, false); PBD_MANY((K_ == 7 ? 3 : 4), dw_mfma, K_, true, false, false, false); \
     PBD_MANY(3, dw_wgrad_mfma, K_, false); PBD_MANY((K_ == 7 ? 2 : 3), dw_bwd_mfma, K_, true); PBD_MANY((K_ == 7 ? 3 : 4), dw_bwd_mfma, K_, false); \
@@ -1031,6 +1038,7 @@ const ManyTable& many_table() {
     PBD_MANY(1, dw_slide, B, K_, 1, 4, true); PBD_MANY(1, dw_dgrad_s2, B, K_)
     PBD_MANY_DW(3); PBD_MANY_DW(5); PBD_MANY_DW(7);
 #undef PBD_MANY_DW
+#undef PBD_MANY_F32
 #undef PBD_MANY_MODE
 #undef PBD_MANY_IG
 #undef PBD_MANY_IGR
@@ -1408,10 +1416,11 @@ template <class T> struct Exec {
                         double bytes, double flops) {
     const int tile = f32_tile(g.M, g.NC), edge = 2 * tile;
     g.tiles_m = (g.M + edge - 1) / edge; g.tiles_n = (g.NC + edge - 1) / edge;
+    const int stages = f32_stages(tile, g.tiles_m * g.tiles_n, c->num_cu);
     char name[32];
-    snprintf(name, sizeof name, "igemm_f32_%s_%d", MODE ? "dgrad" : "fwd", edge);
+    snprintf(name, sizeof name, "igemm_f32_%s_%dr%d", MODE ? "dgrad" : "fwd", edge, stages);
     ProfScope ps(c, name, bytes, flops, net, blk, opi);
-    launch(c, tile == 32 ? igemm_f32_kernel<MODE, 32> : igemm_f32_kernel<MODE, 16>, g.tiles_m * g.tiles_n, F32Gemm<16>::THREADS, 0, st, A, Bw, out, a, b, act,
+    launch(c, tile == 32 ? igemm_f32_kernel<MODE, 32, 3> : stages == 3 ? igemm_f32_kernel<MODE, 16, 3> : igemm_f32_kernel<MODE, 16, 6>, g.tiles_m * g.tiles_n, kF32Threads, 0, st, A, Bw, out, a, b, act,
            accumulate ? 1 : 0, g);
   }
 
@@ -1620,13 +1629,15 @@ template <class T> struct Exec {
     } else if (mfma_f32(op)) {
       if constexpr (sizeof(T) == 4) {
         const int tile = f32_tile(op.d.c_out, J), edge = 2 * tile;
-        const int px = tile == 32 ? F32Gemm<32>::BK : F32Gemm<16>::BK, pq = op.out.h * op.out.w;
+        const int px = f32_stage(tile), pq = op.out.h * op.out.w;
         const WgradTrArgs g{N, op.in.h, op.in.w, op.cin_p, op.out.h, op.out.w, op.d.c_out, op.d.k, op.d.k,
                             op.d.stride, op.d.pad, (int)M, J, (int)M, px / pq, (px % pq) / op.out.w, px % op.out.w,
                             (unsigned)(M * op.d.c_out * 4), (unsigned)((size_t)N * op.in.h * op.in.w * op.cin_p * 4),
                             (op.d.c_out + edge - 1) / edge, (J + edge - 1) / edge, 1};
-        ProfScope ps(c, tile == 32 ? "wgrad_f32_64" : "wgrad_f32_32", bytes, flops, net, blk, opi);
-        launch(c, tile == 32 ? wgrad_f32_kernel<32> : wgrad_f32_kernel<16>, g.tiles_k * g.tiles_j, F32Gemm<16>::THREADS, 0, st, dy, x, dw, g);
+        const int stages = f32_stages(tile, g.tiles_k * g.tiles_j, c->num_cu);
+        ProfScope ps(c, tile == 32 ? "wgrad_f32_64r3" : stages == 3 ? "wgrad_f32_32r3" : "wgrad_f32_32r6", bytes, flops, net, blk, opi);
+        launch(c, tile == 32 ? wgrad_f32_kernel<32, 3> : stages == 3 ? wgrad_f32_kernel<16, 3> : wgrad_f32_kernel<16, 6>, g.tiles_k * g.tiles_j, kF32Threads, 0,
+               st, dy, x, dw, g);
       }
     } else {
       ConvGeom g{N, op.in.h, op.in.w, op.cin_p, op.out.h, op.out.w, op.d.c_out, op.d.k, op.d.k, op.d.stride, op.d.pad};
