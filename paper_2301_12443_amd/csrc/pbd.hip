@@ -486,6 +486,10 @@ int igemm_splits(long M, int NC, int Kred, int CA) { return igemm_cfg(M, NC, Kre
 //   1360, 512 -> 512, 1 x 1          5.8 / 7.1 / 9.2     3136, 2048 -> 768, 1 x 1     25.9 / 22.0 / 23.2
 //   1617, 960 -> 160, 1 x 1          7.6 / 10.4 / 13.4   16660, 1024 -> 256, 1 x 1    23.1 / 23.9 / 20.5
 //   4096, 512 -> 512, 3 x 3          33.7 / 29.7 / 31.1  3136, 768 -> 768, 3 x 3      58.5 / 51.3 / 53.4
+// No 128 x 128 workgroup alone on its unit, which hides neither its first loads nor its store.  Where a unit would get one, us on 64 x 64 / 64 x 128 (two
+// on a unit) / 128 x 128, and on 64 x 128 with registers in place of the ring:
+//   3136, 64 -> 1024, 1 x 1    6.2 / 5.2 / 6.2, 5.6      1360, 512 -> 256, 3 x 3, cut in nine   18.7 / 17.5 / 20.3, 18.6
+//   3136, 512 -> 1024, 1 x 1   11.8 / 9.8 / 11.0, 10.5   2009, 256 -> 2048, 5 x 5               104.6 / 72.9 / 76.8, 83.1
 void free_tile(IgemmCfg& c, long M, int NC, int Kred, int num_cu) {
   if (c.BK != 64 || c.BN < 64 || c.BM != 64) return;        // (128 rows: 512 workgroups and more of those)
   static const int kBM[3] = {64, 64, 128}, kBN[3] = {128, 64, 128};
@@ -495,6 +499,7 @@ void free_tile(IgemmCfg& c, long M, int NC, int Kred, int num_cu) {
     if (NC <= 64 && kBN[i] > 64) continue;
     const long wgs = ((M + kBM[i] - 1) / kBM[i]) * ((NC + kBN[i] - 1) / kBN[i]) * ((nk + per - 1) / per);
     const long unit = (wgs + num_cu - 1) / num_cu;          // workgroups of the busiest compute unit
+    if (kBM[i] == 128 && unit == 1) continue;
     const double t = (double)unit * per * (kBM[i] + kBN[i]) * (unit == 1 ? 23.0 : unit == 2 ? 17.0 : 15.0);
     if (t < best * 0.999) { best = t; c.BM = kBM[i]; c.BN = kBN[i]; }
   }

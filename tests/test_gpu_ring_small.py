@@ -63,10 +63,11 @@ RINGS = [
     ((43, 7, 7, 2048, 320, 1), None, "64x128r2_store", "64x128r2_accum"),
     ((60, 13, 13, 256, 160, 2), "64x128r2_partial", None, None),
     ((20, 7, 7, 768, 768, 2), "64x128r2_partial", "64x128r2_partial", "64x128r2_partial"),
-    ((64, 7, 7, 256, 1024, 1), "128x128r2_store", None, None),             # four steps
-    ((64, 7, 7, 1024, 256, 1), None, "128x128r2_store", "128x128r2_accum"),
-    ((5, 4, 4, 512, 1024, 5), "128x128r2_partial", None, None),
-    ((5, 4, 4, 1024, 512, 5), None, "128x128r2_partial", "128x128r2_partial"),
+    ((64, 7, 7, 256, 2048, 1), "128x128r2_store", None, None),             # 400 tiles; four steps
+    ((64, 7, 7, 2048, 256, 1), None, "128x128r2_store", "128x128r2_accum"),
+    ((64, 7, 7, 256, 1024, 1), "64x128r3_store", None, None),              # (200 of them: one a unit)
+    ((80, 7, 7, 256, 640, 2), "128x128r2_partial", None, None),
+    ((64, 7, 7, 1024, 256, 2), None, "128x128r2_partial", "128x128r2_partial"),
     ((1, 9, 7, 256, 256, 2), "64x64r3_partial", "64x64r3_partial", "64x64r3_partial"),
     ((1, 9, 7, 64, 64, 3), "64x64r3_store", "64x64r3_store", "64x64r3_accum"),
     ((2, 9, 7, 64, 32, 3), "64x32r3_store", None, None),                   # (wave pairs that only load)
