@@ -17,8 +17,8 @@
 // 32-wide ones would not give every compute unit a workgroup.
 //
 // Measured, us, with the addresses and lane exchanges in the multiplying waves / with loaders: forward 64 -> 64, 3 x 3, 65536 pixels 57 / 51 (95
-// TFLOP/s), 256 -> 256, 4096 60 / 48, 512 -> 512, 1024 79 / 54 (90), 256 pixels 46 / 25; weight gradient of 64 -> 64, 1 x 1 over 65536 pixels 420 /
-// 284 (10.4 cycles a pixel), of 8 -> 16, 3 x 3 over 8192 55 / 38; VGG-16 at 64 x 32 x 32 1655 / 1295 a step (91 ms with one thread per result).
+// TFLOP/s), 256 -> 256, 4096 60 / 48, 512 -> 512, 1024 79 / 52 (93), 256 pixels 46 / 25; weight gradient of 64 -> 64, 1 x 1 over 65536 pixels 420 /
+// 284 (10.4 cycles a pixel), of 8 -> 16, 3 x 3 over 8192 55 / 38; VGG-16 at 64 x 32 x 32 1655 / 1295 a step with six stages throughout (91 ms with one thread per result).
 // Cutting a reduction over eight waves and adding the parts (other bits) is faster still where the chain is long.
 #pragma once
 #include "conv_kernels.h"
